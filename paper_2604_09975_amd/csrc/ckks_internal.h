@@ -73,12 +73,13 @@ struct ckks_params {
     std::vector<ckks::ModConst> hmod;
     std::vector<ckks::u64> hninv;      // [W][2]: N^-1 and N^-1 * psi^-(N/2) as plain residues
     ckks::ModConst *d_mod = nullptr;   // [W]
+    // twiddles of the plain transform kernel (N < 2^12 only; null above)
     ckks::u64 *d_tw_fwd = nullptr;     // [W][N]: psi^bitrev(idx), Montgomery form, idx in [1, N)
     ckks::u64 *d_tw_inv = nullptr;     // [W][N]: psi^-bitrev(idx), Montgomery form
     ckks::u64 *d_ninv = nullptr;       // [W][2]: N^-1 and N^-1 * psi^-(N/2), Montgomery form
     ckks::ModFp *d_modf = nullptr;     // [W]
     ckks::u64 *d_ninv_dn = nullptr;    // like d_ninv, special limbs scaled by (P/p_k)^-1
-    // the same constants for the lazy integer butterflies of the two-pass kernels (N = 2^12, 2^16): plain values paired
+    // the same constants for the lazy integer butterflies of the two-pass kernels (N >= 2^12): plain values paired
     // with their quotients floor(w * 2^64 / q); rows of limbs below 2^50 (fp64 butterflies) are left zero
     ckks::u64 *d_tws_fwd = nullptr;    // [W][N][2]
     ckks::u64 *d_tws_inv = nullptr;    // [W][N][2]
@@ -151,7 +152,7 @@ namespace ckks {
 // scaled_dn: inverse only, folds (P/p_k)^-1 into the output of the special limbs.
 int launch_ntt(const ckks_params *p, u64 *d_data, const LimbIds &ids, u32 n_limbs, u32 rows, bool inverse,
                hipStream_t stream, u32 pass_mask = 3, bool scaled_dn = false);
-inline bool fast_ring(const ckks_params *p) { return p->logN == 16 || p->logN == 12; }
+inline bool fast_ring(const ckks_params *p) { return p->logN >= 12; }   // the two-pass transform kernels
 
 // keyswitch.hip
 struct SwitchItem {

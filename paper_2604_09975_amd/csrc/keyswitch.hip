@@ -213,7 +213,7 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
         const u64 *src = c1_half + ((size_t)r * level + i) * N;
         auto load = [&](u32 idx) { return src[idx]; };
         auto store = [&](u32 idx, u64 v) { ylds[(grp * 16 + (idx >> 12)) * UP_COLS + col] = v; };
-        pass_a16_body<true>(make_field_fp(modf_up[i], twf_inv, i, logN), c0, load, store);
+        pass_a_body<true, 4>(make_field_fp(modf_up[i], twf_inv, i, logN), c0, load, store);
     }
     __syncthreads();
     u64 yraw[2][8];
@@ -292,16 +292,16 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
 #pragma unroll
                 for (u32 jj = 0; jj < 16; ++jj)
                     v[jj] = __longlong_as_double((long long)wlds[(grp * 16 + jj) * UP_COLS + col]);
-                radix16_fwd(ff, v, 0, 0);
+                radix_fwd<4>(ff, v, 0, 0);
 #pragma unroll
                 for (u32 jj = 0; jj < 16; ++jj) dst[jj * 4096 + c0] = ff.out(v[jj]);
             } else {
                 auto load = [&](u32 idx) { return wlds[(grp * 16 + (idx >> 12)) * UP_COLS + col]; };
                 auto store = [&](u32 idx, u64 v) { dst[idx] = v; };
                 if (mf.ok)
-                    pass_a16_body<false>(make_field_fp(mf, twf_fwd, gl, logN), c0, load, store);
+                    pass_a_body<false, 4>(make_field_fp(mf, twf_fwd, gl, logN), c0, load, store);
                 else
-                    pass_a16_body<false>(make_field_int(mods, tws_fwd, ninvs, gl, logN), c0, load, store);
+                    pass_a_body<false, 4>(make_field_int(mods, tws_fwd, ninvs, gl, logN), c0, load, store);
             }
         }
         __syncthreads();
@@ -613,9 +613,9 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
         auto store = [&](u32 idx, u64 v) { ylds[(grp * 16 + (idx >> 12)) * MID_COLS + col] = v; };
         const ModFp mf = modf_dn[gl];
         if (mf.ok)
-            pass_a16_body<true>(make_field_fp(mf, twf_inv, gl, logN), c0, load, store);
+            pass_a_body<true, 4>(make_field_fp(mf, twf_inv, gl, logN), c0, load, store);
         else
-            pass_a16_body<true>(make_field_int(mods, tw_inv, ninv_dn, gl, logN), c0, load, store);
+            pass_a_body<true, 4>(make_field_int(mods, tw_inv, ninv_dn, gl, logN), c0, load, store);
     }
     __syncthreads();
     // the two coefficients of this thread (rows 2*grp, 2*grp + 1 of this column) leave LDS as they are
@@ -684,7 +684,7 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
             double v[16];
 #pragma unroll
             for (u32 j = 0; j < 16; ++j) v[j] = __longlong_as_double((long long)wlds[(grp * 16 + j) * MID_COLS + col]);
-            radix16_fwd(ff, v, 0, 0);
+            radix_fwd<4>(ff, v, 0, 0);
 #pragma unroll
             for (u32 j = 0; j < 16; ++j) dst[j * 4096 + c0] = ff.out(v[j]);
         }

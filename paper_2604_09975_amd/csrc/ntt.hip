@@ -12,12 +12,11 @@
 // N^-1 into the last stage.
 //
 // Two implementations:
-//  * N = 2^12 and N = 2^16 (the benchmark rings): every thread keeps 16 residues in
-//    registers and does four stages (radix 16) between exchanges through LDS.
-//    Pass B covers 12 stages (three rounds, two exchanges) on a 4096-residue tile:
-//    the whole transform at N = 2^12, all but the first 4 stages at N = 2^16.
-//    Those 4 stages (pass A) pair residues 4096 apart, so a thread that owns a
-//    column holds its 16 rows in registers and needs no LDS at all -- which is what
+//  * N = 2^12 .. 2^17: every thread keeps 16 residues (pass A of 2^17: 32) in registers and does four stages (radix 16)
+//    between exchanges through LDS.  Pass B covers 12 stages (three rounds, two exchanges) on a 4096-residue tile: the
+//    whole transform at N = 2^12, all but the first log N - 12 stages above it.
+//    Those stages (pass A) pair residues 4096 apart, so a thread that owns a
+//    column holds its rows in registers and needs no LDS at all -- which is what
 //    lets the base conversions of key switching, which work column by column in the
 //    coefficient domain, carry the neighbouring pass A of both transforms.  Limbs whose prime is
 //    below 2^50 run their butterflies in fp64: residues, twiddles and the two halves
@@ -25,8 +24,9 @@
 //    quotient comes from one multiplication by 1/q, and values stay signed and
 //    unreduced for up to four stages (about 10 issue slots per butterfly instead of
 //    about 55 for the 64-bit Montgomery butterfly).  Larger primes (the 60-bit
-//    special primes) use Montgomery butterflies in the same kernels.
-//  * other ring sizes: a plain kernel with one LDS round trip per stage.
+//    special primes) use lazy integer butterflies with quotient-carrying twiddles in the same kernels.
+//  * N = 2^10 and 2^11: a plain kernel with one LDS round trip per stage.  (2^13 .. 2^15 and 2^17 ran on it too: 32
+//    polynomials of 9 limbs at 2^15 took 155 us in its two launches, 55 us in these two passes.)
 #include <algorithm>
 
 #include "ckks_internal.h"
@@ -97,11 +97,13 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_pass_kernel(u64 *__restrict__
 }
 
 
-// which: 0 = pass A (N = 2^16: first / last 4 stages, registers only), 2 = pass B (12 stages in a 4096 tile)
+// LOGR: 1 .. 5 = pass A of N = 2^(12+LOGR) (its first / last LOGR stages, registers only; a thread takes 16 residues,
+// i.e. 16 >> LOGR columns, so that short rows keep as many loads in flight per wavefront as long ones), 0 = pass B (12
+// stages in a 4096 tile)
 // FP: the kernel serves the rows whose prime is below 2^50 (fp64 butterflies) or the others (integer butterflies);
 // rows of the other kind return at once.  One kernel for both kinds needs the union of the two register budgets
 // (130 registers, 3 waves per SIMD in pass B, against 112 to 124 and 4 waves for the separate ones).
-template <bool INV, int WHICH, bool FP>
+template <bool INV, u32 LOGR, bool FP>
 __global__ __launch_bounds__(NTT_THREADS) void ntt_fast_kernel(u64 *__restrict__ data,
                                                                const ModConst *__restrict__ mods,
                                                                const ModFp *__restrict__ modf,
@@ -109,7 +111,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fast_kernel(u64 *__restrict__
                                                                const double *__restrict__ twf,
                                                                const u64 *__restrict__ ninv, LimbIds ids,
                                                                u32 n_limbs, u32 logN) {
-    __shared__ u64 lds[WHICH == 0 ? 1 : FAST_LDS_WORDS];
+    __shared__ u64 lds[LOGR ? 1 : FAST_LDS_WORDS];
     const u32 row = blockIdx.y;
     const u32 limb = ids.id[row % n_limbs];
     if (limb == SKIP_ROW) return;
@@ -118,20 +120,24 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fast_kernel(u64 *__restrict__
     u64 *poly = data + ((size_t)row << logN);
     auto load = [&](u32 idx) { return poly[idx]; };
     auto store = [&](u32 idx, u64 v) { poly[idx] = v; };
-    const u32 col = blockIdx.x * NTT_THREADS + threadIdx.x;
-    if (FP) {
-        const FieldFp f = make_field_fp(mf, twf, limb, logN);
-        if (WHICH == 0) pass_a16_body<INV>(f, col, load, store);
-        if (WHICH == 2) pass_b_body<INV>(f, logN, lds, load, store);
-    } else {
-        const FieldInt f = make_field_int(mods, tw, ninv, limb, logN);
-        if (WHICH == 0) pass_a16_body<INV>(f, col, load, store);
-        if (WHICH == 2) pass_b_body<INV>(f, logN, lds, load, store);
-    }
+    auto go = [&](const auto &f) {
+        if constexpr (LOGR == 0) {
+            pass_b_body<INV>(f, logN, lds, load, store);
+        } else {
+            constexpr u32 COLS = LOGR < 4 ? 16u >> LOGR : 1;     // columns of a thread
+#pragma unroll
+            for (u32 c = 0; c < COLS; ++c)
+                pass_a_body<INV, LOGR>(f, (c * gridDim.x + blockIdx.x) * NTT_THREADS + threadIdx.x, load, store);
+        }
+    };
+    if (FP)
+        go(make_field_fp(mf, twf, limb, logN));
+    else
+        go(make_field_int(mods, tw, ninv, limb, logN));
 }
 
-template <bool INV, int WHICH>
-static void launch_fast(const ckks_params *p, u64 *d_data, const LimbIds &ids, u32 n_limbs, u32 rows, u32 tiles,
+template <bool INV, u32 LOGR>
+static void launch_fast(const ckks_params *p, u64 *d_data, const LimbIds &ids, u32 n_limbs, u32 rows,
                         hipStream_t stream, bool scaled_dn) {
     bool any_fp = false, any_int = false;
     for (u32 i = 0; i < n_limbs; ++i) {
@@ -141,14 +147,28 @@ static void launch_fast(const ckks_params *p, u64 *d_data, const LimbIds &ids, u
         else
             any_int = true;
     }
+    const u32 blocks = LOGR == 0 ? p->N >> 12 : LOGR < 4 ? 1u << LOGR : 16;
 #define FAST_LAUNCH(FPK)                                                                                             \
-    hipLaunchKernelGGL((ntt_fast_kernel<INV, WHICH, FPK>), dim3(tiles, rows), dim3(NTT_THREADS), 0, stream, d_data,   \
+    hipLaunchKernelGGL((ntt_fast_kernel<INV, LOGR, FPK>), dim3(blocks, rows), dim3(NTT_THREADS), 0, stream, d_data,   \
                        p->d_mod, scaled_dn ? p->d_modf_dn : p->d_modf, INV ? p->d_tws_inv : p->d_tws_fwd,            \
                        INV ? p->d_twf_inv : p->d_twf_fwd, scaled_dn ? p->d_ninvs_dn : p->d_ninvs, ids, n_limbs,      \
                        p->logN)
     if (any_fp) FAST_LAUNCH(true);
     if (any_int) FAST_LAUNCH(false);
 #undef FAST_LAUNCH
+}
+
+// pass A of a ring above 2^12
+template <bool INV>
+static void launch_pass_a(const ckks_params *p, u64 *d_data, const LimbIds &ids, u32 n_limbs, u32 rows,
+                          hipStream_t stream, bool scaled_dn) {
+    switch (p->logN) {
+        case 13: launch_fast<INV, 1>(p, d_data, ids, n_limbs, rows, stream, scaled_dn); break;
+        case 14: launch_fast<INV, 2>(p, d_data, ids, n_limbs, rows, stream, scaled_dn); break;
+        case 15: launch_fast<INV, 3>(p, d_data, ids, n_limbs, rows, stream, scaled_dn); break;
+        case 16: launch_fast<INV, 4>(p, d_data, ids, n_limbs, rows, stream, scaled_dn); break;
+        case 17: launch_fast<INV, 5>(p, d_data, ids, n_limbs, rows, stream, scaled_dn); break;
+    }
 }
 
 int launch_ntt(const ckks_params *p, u64 *d_data, const LimbIds &ids, u32 n_limbs, u32 rows, bool inverse,
@@ -166,17 +186,16 @@ int launch_ntt(const ckks_params *p, u64 *d_data, const LimbIds &ids, u32 n_limb
         set_error("launch_ntt: %u rows exceed one launch", rows);
         return CKKS_E_INVAL;
     }
-    if (logN == 16 || logN == 12) {
-        // N = 2^16: pass A (4 stages) and pass B (12 stages); N = 2^12: pass B is the whole transform (forward: the
+    if (fast_ring(p)) {
+        // pass A (log N - 12 stages) and pass B (12 stages); N = 2^12: pass B is the whole transform (forward: the
         // "second" pass, inverse: the "first"), and carries the scaled last stage
-        const u32 tb = p->N >> 12;
-        const bool two = logN == 16;
+        const bool two = logN != 12;
         if (!inverse) {
-            if ((pass_mask & 1) && two) launch_fast<false, 0>(p, d_data, ids, n_limbs, rows, 16, stream, false);
-            if (pass_mask & 2) launch_fast<false, 2>(p, d_data, ids, n_limbs, rows, tb, stream, false);
+            if ((pass_mask & 1) && two) launch_pass_a<false>(p, d_data, ids, n_limbs, rows, stream, false);
+            if (pass_mask & 2) launch_fast<false, 0>(p, d_data, ids, n_limbs, rows, stream, false);
         } else {
-            if (pass_mask & 1) launch_fast<true, 2>(p, d_data, ids, n_limbs, rows, tb, stream, two ? false : scaled_dn);
-            if ((pass_mask & 2) && two) launch_fast<true, 0>(p, d_data, ids, n_limbs, rows, 16, stream, scaled_dn);
+            if (pass_mask & 1) launch_fast<true, 0>(p, d_data, ids, n_limbs, rows, stream, two ? false : scaled_dn);
+            if ((pass_mask & 2) && two) launch_pass_a<true>(p, d_data, ids, n_limbs, rows, stream, scaled_dn);
         }
         CKKS_LAUNCH_CHECK("ntt_fast_kernel");
         return CKKS_OK;

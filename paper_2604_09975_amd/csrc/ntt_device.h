@@ -1,4 +1,4 @@
-// Device-side building blocks of the radix-16 NTT (N = 2^12 and 2^16), shared by the transform kernels
+// Device-side building blocks of the radix-16 NTT (N = 2^12 .. 2^17), shared by the transform kernels
 // and by the key-switch kernels that fuse other work into a transform pass.
 #pragma once
 #include "ckks_internal.h"
@@ -109,15 +109,21 @@ struct FieldFp {
     }
 };
 
-// Four stages on the 16 values a thread holds.  The group is node `nb` of stage s0; at stage
-// s0 + t it covers nodes (nb << t) + k, k < 2^t, and values j, j + (8 >> t) pair up.
-template <class F>
-__device__ __forceinline__ void radix16_fwd(const F &f, typename F::T (&v)[16], u32 s0, u32 nb) {
+// LOGR stages on the 2^LOGR values a thread holds.  The group is node `nb` of stage s0; at stage
+// s0 + t it covers nodes (nb << t) + k, k < 2^t, and values j, j + (2^LOGR >> t + 1) pair up.
+// fp64 bounds: a product is below 0.9 q (a factor below 4q) or 0.7 q (below q), so four forward stages take a
+// normalised value (q/2) to 4 q = 2^52; an inverse stage doubles a value and hands the difference, twice as large, to
+// the product: two of them between normalisations.
+template <u32 LOGR, class F>
+__device__ __forceinline__ void radix_fwd(const F &f, typename F::T (&v)[1u << LOGR], u32 s0, u32 nb) {
+    constexpr u32 R = 1u << LOGR;
 #pragma unroll
-    for (u32 j = 0; j < 16; ++j) f.norm(v[j]);
+    for (u32 t = 0; t < LOGR; ++t) {
+        if (t % 4 == 0) {
 #pragma unroll
-    for (u32 t = 0; t < 4; ++t) {
-        const u32 g = 8u >> t;
+            for (u32 j = 0; j < R; ++j) f.norm(v[j]);
+        }
+        const u32 g = R >> (t + 1);
 #pragma unroll
         for (u32 k = 0; k < (1u << t); ++k) {
             const typename F::W w = f.twid((1u << (s0 + t)) + (nb << t) + k);
@@ -127,20 +133,20 @@ __device__ __forceinline__ void radix16_fwd(const F &f, typename F::T (&v)[16], 
     }
 }
 
-template <class F>
-__device__ __forceinline__ void radix16_inv(const F &f, typename F::T (&v)[16], u32 s0, u32 nb, bool last) {
+// last: the group's first stage (t = 0) ends the transform and folds in N^-1
+template <u32 LOGR, class F>
+__device__ __forceinline__ void radix_inv(const F &f, typename F::T (&v)[1u << LOGR], u32 s0, u32 nb, bool last) {
+    constexpr u32 R = 1u << LOGR;
 #pragma unroll
-    for (u32 j = 0; j < 16; ++j) f.norm(v[j]);
+    for (int t = (int)LOGR - 1; t >= 0; --t) {
+        const u32 g = R >> (t + 1);
+        if (((int)LOGR - 1 - t) % 2 == 0) {
 #pragma unroll
-    for (int t = 3; t >= 0; --t) {
-        const u32 g = 8u >> t;
-        if (t == 1) {
-#pragma unroll
-            for (u32 j = 0; j < 16; ++j) f.norm(v[j]);
+            for (u32 j = 0; j < R; ++j) f.norm(v[j]);
         }
         if (t == 0 && last) {
 #pragma unroll
-            for (u32 i = 0; i < 8; ++i) f.inv_last(v[i], v[i + 8]);
+            for (u32 i = 0; i < R / 2; ++i) f.inv_last(v[i], v[i + R / 2]);
         } else {
 #pragma unroll
             for (u32 k = 0; k < (1u << t); ++k) {
@@ -173,19 +179,19 @@ __device__ __forceinline__ void pass_b_fwd_to_lds(const F &f, u32 logN, u64 *lds
     typename F::T v[16];
 #pragma unroll
     for (u32 j = 0; j < 16; ++j) v[j] = f.in(load(base + j * 256 + tid));
-    radix16_fwd(f, v, logN - 12, blockIdx.x);
+    radix_fwd<4>(f, v, logN - 12, blockIdx.x);
 #pragma unroll
     for (u32 j = 0; j < 16; ++j) lds[lds_pad(j * 256 + tid)] = f.bits(v[j]);
     __syncthreads();
 #pragma unroll
     for (u32 j = 0; j < 16; ++j) v[j] = f.from_bits(lds[lds_pad(strided + j * 16)]);
-    radix16_fwd(f, v, logN - 8, run);
+    radix_fwd<4>(f, v, logN - 8, run);
 #pragma unroll
     for (u32 j = 0; j < 16; ++j) lds[lds_pad(strided + j * 16)] = f.bits(v[j]);   // a thread's own slots
     __syncthreads();
 #pragma unroll
     for (u32 j = 0; j < 16; ++j) v[j] = f.from_bits(lds[lds_pad(contig + j)]);
-    radix16_fwd(f, v, logN - 4, run * 16 + c);
+    radix_fwd<4>(f, v, logN - 4, run * 16 + c);
 #pragma unroll
     for (u32 j = 0; j < 16; ++j) {                                          // a thread's own slots
         if (RAW) {
@@ -210,19 +216,19 @@ __device__ __forceinline__ void pass_b_inv_from_lds(const F &f, u32 logN, u64 *l
     typename F::T v[16];
 #pragma unroll
     for (u32 j = 0; j < 16; ++j) v[j] = f.in(lds[lds_pad(contig + j)]);
-    radix16_inv(f, v, logN - 4, run * 16 + c, false);
+    radix_inv<4>(f, v, logN - 4, run * 16 + c, false);
 #pragma unroll
     for (u32 j = 0; j < 16; ++j) lds[lds_pad(contig + j)] = f.bits(v[j]);   // a thread's own slots
     __syncthreads();
 #pragma unroll
     for (u32 j = 0; j < 16; ++j) v[j] = f.from_bits(lds[lds_pad(strided + j * 16)]);
-    radix16_inv(f, v, logN - 8, run, false);
+    radix_inv<4>(f, v, logN - 8, run, false);
 #pragma unroll
     for (u32 j = 0; j < 16; ++j) lds[lds_pad(strided + j * 16)] = f.bits(v[j]);   // a thread's own slots
     __syncthreads();
 #pragma unroll
     for (u32 j = 0; j < 16; ++j) v[j] = f.from_bits(lds[lds_pad(j * 256 + tid)]);
-    radix16_inv(f, v, logN - 12, blockIdx.x, logN == 12);
+    radix_inv<4>(f, v, logN - 12, blockIdx.x, logN == 12);
 #pragma unroll
     for (u32 j = 0; j < 16; ++j) store(base + j * 256 + tid, f.out(v[j]));
 }
@@ -243,20 +249,21 @@ __device__ __forceinline__ void pass_b_body(const F &f, u32 logN, u64 *lds, Load
     }
 }
 
-// pass A for N = 2^16: the first 4 stages pair residues 4096 apart, so a thread that owns one of the 4096 columns
-// holds its 16 rows in registers: no LDS, every access a run of consecutive residues.  col: the thread's column;
-// load(idx) / store(idx, value) see canonical residues at index idx of the polynomial.
-template <bool INV, class F, class Load, class Store>
-__device__ __forceinline__ void pass_a16_body(const F &f, u32 col, Load load, Store store) {
-    typename F::T v[16];
+// pass A for N = 2^(12+LOGR): the first LOGR stages pair residues 4096 apart, so a thread that owns one of the 4096
+// columns holds its 2^LOGR rows in registers: no LDS, every access a run of consecutive residues.  col: the thread's
+// column; load(idx) / store(idx, value) see canonical residues at index idx of the polynomial.
+template <bool INV, u32 LOGR, class F, class Load, class Store>
+__device__ __forceinline__ void pass_a_body(const F &f, u32 col, Load load, Store store) {
+    constexpr u32 R = 1u << LOGR;
+    typename F::T v[R];
 #pragma unroll
-    for (u32 j = 0; j < 16; ++j) v[j] = f.in(load(j * 4096 + col));
+    for (u32 j = 0; j < R; ++j) v[j] = f.in(load(j * 4096 + col));
     if (!INV)
-        radix16_fwd(f, v, 0, 0);
+        radix_fwd<LOGR>(f, v, 0, 0);
     else
-        radix16_inv(f, v, 0, 0, true);
+        radix_inv<LOGR>(f, v, 0, 0, true);
 #pragma unroll
-    for (u32 j = 0; j < 16; ++j) store(j * 4096 + col, f.out(v[j]));
+    for (u32 j = 0; j < R; ++j) store(j * 4096 + col, f.out(v[j]));
 }
 
 // Field objects for limb `limb` from the parameter tables.

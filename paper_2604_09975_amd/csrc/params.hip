@@ -317,22 +317,25 @@ int ckks_params_create(uint32_t logN, const uint64_t *q, uint32_t L, const uint6
         P->hmod.push_back(make_mod(v));
         P->psi.push_back(smallest_root(v, logN));
     }
-    std::vector<u64> fwd((size_t)W * N, 0), inv((size_t)W * N, 0), ninv((size_t)W * 2);
+    std::vector<u64> fwd, inv, ninv((size_t)W * 2);
     std::vector<u64> pw(2 * (size_t)N);
     std::vector<double> fwd_f((size_t)W * N, 0.0), inv_f((size_t)W * N, 0.0);
     std::vector<ModFp> modf(W);
     std::vector<u64> ninv_plain((size_t)W * 2);
-    const bool two_pass = logN == 16 || logN == 12;
+    const bool two_pass = fast_ring(P);
     std::vector<u64> fwd_s, inv_s;
     if (two_pass) {
         fwd_s.assign((size_t)W * N * 2, 0);
         inv_s.assign((size_t)W * N * 2, 0);
+    } else {
+        fwd.assign((size_t)W * N, 0);
+        inv.assign((size_t)W * N, 0);
     }
     for (u32 i = 0; i < W; ++i) {
         const ModConst &m = P->hmod[i];
         pw[0] = 1;
         for (u32 e = 1; e < 2 * N; ++e) pw[e] = hmul(pw[e - 1], P->psi[i], m.q);
-        for (u32 idx = 1; idx < N; ++idx) {
+        for (u32 idx = 1; !two_pass && idx < N; ++idx) {
             u32 e = bitrev(idx, logN);
             fwd[(size_t)i * N + idx] = to_mont(pw[e], m);
             inv[(size_t)i * N + idx] = to_mont(pw[2 * N - e], m);
