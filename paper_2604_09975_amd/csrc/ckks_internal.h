@@ -16,6 +16,9 @@ constexpr u32 MAX_DIGIT = 16;     // alpha and K
 constexpr u32 ROT_BATCH = 32;     // key switches per batch of kernel launches
 constexpr u32 SKIP_ROW = 255;     // limb id meaning "leave this row alone"
 
+// row lengths of the factor tables of the fused base conversions: powers of two, padded with zeros
+inline u32 pad_pow2(u32 x) { return x <= 1 ? 1 : x <= 2 ? 2 : x <= 4 ? 4 : x <= 8 ? 8 : x; }
+
 constexpr u32 MAX_ROW_IDS = 128;  // rows described by one LimbIds pattern
 
 // limb id of each row of a [batch][n][N] array, row index taken modulo n
@@ -58,10 +61,12 @@ struct LevelTables {
     u64 *d_up_inv = nullptr;   // [level]: ((Q_D/q_i)^-1 mod q_i), Montgomery form, D = digit of i
     u64 *d_up_mat = nullptr;   // [level][level+K]: (Q_D/q_i mod t), Montgomery form w.r.t. t; 0 for t in D
     u64 *d_up_matf = nullptr;  // the same factors as doubles (bit patterns), for the conversions done in fp64
-    // for the fused decomposition kernel (N = 2^16, every active prime below 2^50):
+    // for the fused decomposition kernel (N = 2^12 .. 2^16, every active prime below 2^50):
     ModFp *d_modf_up = nullptr;   // [level]: the limb's ModFp with (Q_D/q_i)^-1 folded into the inverse transform's N^-1
-    double *d_up_mats = nullptr;  // [beta][K][8][2][3]: (Q_D/q_i) 2^(25b) 2^64 mod p_k cut into three 20-bit parts
-    double *d_up_ft = nullptr;    // [beta][level+K][8]: (Q_D/q_i) mod q_t for the ciphertext-prime targets t
+                                  // (N = 2^12: alone, the tile pass has applied N^-1)
+    // AM = alpha rounded up to a power of two, zero padding behind the digit's limbs
+    double *d_up_mats = nullptr;  // [beta][K][AM][2][3]: (Q_D/q_i) 2^(25b) 2^64 mod p_k cut into three 20-bit parts
+    double *d_up_ft = nullptr;    // [beta][level+K][AM]: (Q_D/q_i) mod q_t for the ciphertext-prime targets t
 };
 
 }  // namespace ckks
@@ -91,7 +96,7 @@ struct ckks_params {
     // ModDown tables (independent of the level)
     ckks::u64 *d_dn_inv = nullptr;     // [K]: (P/p_k)^-1 mod p_k
     ckks::u64 *d_dn_mat = nullptr;     // [K][L]: P/p_k mod q_i
-    double *d_dn_matf = nullptr;       // [L][K][3][2]: (2^(20a) * P/p_k) mod q_i as two 25-bit halves (doubles)
+    double *d_dn_matf = nullptr;       // [L][K padded][3][2]: (2^(20a) * P/p_k) mod q_i as two 25-bit halves (doubles)
     bool dn_fp = false;                // every special prime below 2^60: the fp64 ModDown conversion applies
     ckks::u64 *d_pinv = nullptr;       // [L]: P^-1 mod q_i
     double *d_pinvf = nullptr;         // [L]: the same as plain doubles (exact for primes below 2^53)
@@ -169,6 +174,7 @@ size_t digits_words(const ckks_params *p, u32 level);
 size_t switch_scratch_words(const ckks_params *p, u32 level, u32 n_items);
 int decompose(ckks_params *p, const u64 *const *c1, u32 n, u32 level, u64 *d_digits, u64 *d_tmp, hipStream_t stream);
 int switch_batch(ckks_params *p, u32 level, const SwitchItem *items, u32 n, u64 *d_work, hipStream_t stream);
+bool moddown_mid_ok(const ckks_params *p, u32 level);   // the fused ModDown (and ModDown + rescale) kernels apply
 int moddown_add(ckks_params *p, u32 level, u64 *d_u, u64 *const *dst, u32 n, u64 *d_w, hipStream_t stream);
 int moddown_rescale(ckks_params *p, u32 level, u64 *d_u, const u64 *const *z, u64 *const *out, u32 n, u64 *d_w,
                     u64 *d_t, hipStream_t stream);

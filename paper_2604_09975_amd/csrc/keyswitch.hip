@@ -170,21 +170,26 @@ __global__ __launch_bounds__(KS_THREADS) void modup_kernel(const u64 *__restrict
     }
 }
 
-// Decomposition between the two tile passes at N = 2^16, one kernel instead of four.  The last 4 stages of the
-// inverse transform of c1, the base conversion of every digit (ModUp) and the first 4 stages of the forward transform
-// of the extended rows all work on columns (residues 4096 apart); a workgroup owns UP_COLS columns of one digit of one
-// ciphertext:
-//   1. thread (a, col): column col of limb lo + a of the digit, 16 rows in registers, last inverse round with
+// Decomposition between the two tile passes at N = 2^(12+LOGR), one kernel instead of four.  The last LOGR stages of the
+// inverse transform of c1, the base conversion of every digit (ModUp) and the first LOGR stages of the forward transform
+// of the extended rows all work on columns (residues 4096 apart); a workgroup owns a tile of 512 coefficients, 512 >> LOGR
+// columns of 2^LOGR rows, of one digit of one ciphertext:
+//   1. group a of 32 threads: the columns of limb lo + a of the digit in registers, last inverse round with
 //      N^-1 (Q_D/q_i)^-1 folded in -> y_a in LDS;
-//   2. thread (row pair, col): for each group of UP_TG targets and each of its two coefficients: targets among the
-//      ciphertext primes as the exact fp64 sums of modup_kernel; targets among the special primes from 25-bit pieces
-//      of y and 20-bit parts of the factors (48 exact fp64 multiply-adds, then one Montgomery reduction of the
-//      recombined 90-bit sum) -> LDS;
-//   3. thread (target, col): 16 rows from LDS, first forward round (fp64 or integer butterflies), out.
+//   2. every thread takes two coefficients of the tile: for each group of UP_TG targets and each of its two coefficients:
+//      targets among the ciphertext primes as the exact fp64 sums of modup_kernel; targets among the special primes from
+//      25-bit pieces of y and 20-bit parts of the factors (6 AM exact fp64 multiply-adds, then one Montgomery reduction
+//      of the recombined 90-bit sum) -> LDS;
+//   3. group t of 32 threads: the columns of target t from LDS, first forward round (fp64 or integer butterflies), out.
+// At N = 2^12 (LOGR = 0) the tile passes are whole transforms: step 1 only scales, step 3 only stores.
 // c1_half [n][level][N]: c1 after the inverse tile pass; digits [n][beta][level+K][N]: rows of targets outside the
-// digit, ready for the forward tile pass.  Needs alpha, K <= 8, every active ciphertext prime below 2^50 and every
-// special prime below 2^60 (the launcher checks).  grid: x = column tile, y = digit, z = ciphertext.
-constexpr u32 UP_COLS = 32, UP_TG = 8;
+// digit, ready for the forward tile pass.  AM: the digit size alpha rounded up to a power of two; the factor tables are
+// padded with zeros to it.  Needs alpha, K <= 8, every active ciphertext prime below 2^50 and every special prime below
+// 2^60 (the launcher checks).  grid: x = column tile, y = digit, z = ciphertext.
+// With its counterpart moddown_mid_kernel, against separate column passes and conversions: a ciphertext product and rescale
+// at 2^15 (12 + 4 primes) 186 -> 159 us, a bank of 24 switches at 2^14 (level 5 of 6, 2 special primes) 257 -> 232 us.
+constexpr u32 MID_TILE = 512, UP_TG = 8;
+template <u32 LOGR, u32 AM>
 __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ c1_half, u64 *__restrict__ digits,
                                                         const ModConst *__restrict__ mods,
                                                         const ModFp *__restrict__ modf,
@@ -196,40 +201,45 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
                                                         const double *__restrict__ up_ft,
                                                         const double *__restrict__ up_mats, u32 level, u32 K, u32 L,
                                                         u32 alpha, u32 beta, u32 tsplit) {
-    constexpr u32 logN = 16, N = 1u << logN;
-    static_assert(UP_TG == 8, "the target tiles reuse the 8 rows of source tiles");
-    __shared__ u64 ylds[8 * 16 * UP_COLS];
+    constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, COLS = MID_TILE >> LOGR, PER = COLS / 32;
+    static_assert(UP_TG == 8 && AM <= 8, "the target tiles reuse the 8 rows of source tiles");
+    __shared__ u64 ylds[8 * MID_TILE];
     u64 *wlds = ylds;               // the sources live in registers once step 2 has read them: the same 32 KiB
-    const u32 tid = threadIdx.x, col = tid & (UP_COLS - 1), grp = tid / UP_COLS;   // grp < 8
+    const u32 tid = threadIdx.x, lane = tid & 31, grp = tid / 32;   // grp < 8
     // tsplit > 1 (few ciphertexts): the groups of targets of a tile go to tsplit workgroups, each of which redoes the
     // cheap step 1, so that a lone decomposition still fills the chip
-    const u32 tile = blockIdx.x % (4096 / UP_COLS), tpart = blockIdx.x / (4096 / UP_COLS);
-    const u32 c0 = tile * UP_COLS + col;
+    const u32 tile = blockIdx.x % (N / MID_TILE), tpart = blockIdx.x / (N / MID_TILE);
+    const u32 c0 = tile * COLS;
     const u32 j = blockIdx.y, r = blockIdx.z;
     const u32 Wl = level + K;
     const u32 lo = j * alpha, hi = min(lo + alpha, level), nd = hi - lo;
     if (grp < nd) {
         const u32 i = lo + grp;
         const u64 *src = c1_half + ((size_t)r * level + i) * N;
-        auto load = [&](u32 idx) { return src[idx]; };
-        auto store = [&](u32 idx, u64 v) { ylds[(grp * 16 + (idx >> 12)) * UP_COLS + col] = v; };
-        pass_a_body<true, 4>(make_field_fp(modf_up[i], twf_inv, i, logN), c0, load, store);
+        const FieldFp f = make_field_fp(modf_up[i], twf_inv, i, logN);
+#pragma unroll
+        for (u32 c = 0; c < PER; ++c) {
+            const u32 col = lane + 32 * c;
+            auto load = [&](u32 idx) { return src[idx]; };
+            auto store = [&](u32 idx, u64 v) { ylds[grp * MID_TILE + (idx >> 12) * COLS + col] = v; };
+            pass_a_body<true, LOGR>(f, c0 + col, load, store);
+        }
     }
     __syncthreads();
-    u64 yraw[2][8];
+    u64 yraw[2][AM];
 #pragma unroll
     for (u32 e = 0; e < 2; ++e)
 #pragma unroll
-        for (u32 a = 0; a < 8; ++a) yraw[e][a] = a < nd ? ylds[(a * 16 + 2 * grp + e) * UP_COLS + col] : 0;
+        for (u32 a = 0; a < AM; ++a) yraw[e][a] = a < nd ? ylds[a * MID_TILE + e * 256 + tid] : 0;
     __syncthreads();                // every thread has its y: the tile may be overwritten
     u64 *dig = digits + ((size_t)r * beta + j) * Wl * N;
     const u32 nt = Wl - nd;                                          // targets: all rows outside the digit
     for (u32 u0 = tpart * UP_TG; u0 < nt; u0 += tsplit * UP_TG) {
 #pragma unroll 1
         for (u32 e = 0; e < 2; ++e) {
-            double yd[8], yp[8][2];
+            double yd[AM], yp[AM][2];
 #pragma unroll
-            for (u32 a = 0; a < 8; ++a) {
+            for (u32 a = 0; a < AM; ++a) {
                 const u64 v = e ? yraw[1][a] : yraw[0][a];
                 yp[a][0] = __longlong_as_double((long long)(0x4330000000000000ull | (v & 0x1FFFFFFu))) - 4503599627370496.0;
                 yp[a][1] = __longlong_as_double((long long)(0x4330000000000000ull | (v >> 25))) - 4503599627370496.0;
@@ -242,10 +252,10 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
                     // target among the ciphertext primes: every product split exactly into h + l, brought below
                     // 0.9 q before it is added, the partial sum reduced every four terms
                     const double q = modf[t].q, u = modf[t].u;
-                    const double *fd = up_ft + ((size_t)j * Wl + t) * 8;   // zero beyond the digit's limbs, as y is
+                    const double *fd = up_ft + ((size_t)j * Wl + t) * AM;  // zero beyond the digit's limbs, as y is
                     double acc = 0.0;
 #pragma unroll
-                    for (u32 a = 0; a < 8; ++a) {
+                    for (u32 a = 0; a < AM; ++a) {
                         const double h = yd[a] * fd[a], l = fma(yd[a], fd[a], -h);
                         acc += fma(-rint(h * u), q, h) + l;
                         if ((a & 3) == 3) acc = fma(-rint(acc * u), q, acc);
@@ -255,10 +265,10 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
                 } else {
                     // target among the special primes: sum_a y_a F_a with F_a 2^64 2^(25b) mod p in 20-bit parts
                     const u32 k = t - level;
-                    const double *g = up_mats + ((size_t)j * K + k) * 48;   // zero beyond the digit's limbs
+                    const double *g = up_mats + ((size_t)j * K + k) * (AM * 6);   // zero beyond the digit's limbs
                     double s0 = 0.0, s1 = 0.0, s2 = 0.0;
 #pragma unroll
-                    for (u32 a = 0; a < 8; ++a) {
+                    for (u32 a = 0; a < AM; ++a) {
 #pragma unroll
                         for (u32 b = 0; b < 2; ++b) {
                             s0 = fma(yp[a][b], g[(a * 2 + b) * 3 + 0], s0);
@@ -277,7 +287,7 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
                     acc_add(acc, u128{i2 << 40, i2 >> 24});
                     res = redc_wide(acc, mods[L + k]);               // canonical: the factors carry 2^64
                 }
-                wlds[(tt * 16 + 2 * grp + e) * UP_COLS + col] = res;
+                wlds[tt * MID_TILE + e * 256 + tid] = res;
             }
         }
         __syncthreads();
@@ -286,25 +296,47 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
             const u32 gl = t < level ? t : L + (t - level);
             u64 *dst = dig + (size_t)t * N;
             const ModFp mf = modf[gl];
-            if (t < level) {
-                const FieldFp ff = make_field_fp(mf, twf_fwd, gl, logN);
-                double v[16];
 #pragma unroll
-                for (u32 jj = 0; jj < 16; ++jj)
-                    v[jj] = __longlong_as_double((long long)wlds[(grp * 16 + jj) * UP_COLS + col]);
-                radix_fwd<4>(ff, v, 0, 0);
+            for (u32 c = 0; c < PER; ++c) {
+                const u32 col = lane + 32 * c;
+                if (t < level) {
+                    const FieldFp ff = make_field_fp(mf, twf_fwd, gl, logN);
+                    double v[R];
 #pragma unroll
-                for (u32 jj = 0; jj < 16; ++jj) dst[jj * 4096 + c0] = ff.out(v[jj]);
-            } else {
-                auto load = [&](u32 idx) { return wlds[(grp * 16 + (idx >> 12)) * UP_COLS + col]; };
-                auto store = [&](u32 idx, u64 v) { dst[idx] = v; };
-                if (mf.ok)
-                    pass_a_body<false, 4>(make_field_fp(mf, twf_fwd, gl, logN), c0, load, store);
-                else
-                    pass_a_body<false, 4>(make_field_int(mods, tws_fwd, ninvs, gl, logN), c0, load, store);
+                    for (u32 jj = 0; jj < R; ++jj)
+                        v[jj] = __longlong_as_double((long long)wlds[grp * MID_TILE + jj * COLS + col]);
+                    radix_fwd<LOGR>(ff, v, 0, 0);
+#pragma unroll
+                    for (u32 jj = 0; jj < R; ++jj) dst[jj * 4096 + c0 + col] = ff.out(v[jj]);
+                } else {
+                    auto load = [&](u32 idx) { return wlds[grp * MID_TILE + (idx >> 12) * COLS + col]; };
+                    auto store = [&](u32 idx, u64 v) { dst[idx] = v; };
+                    if (mf.ok)
+                        pass_a_body<false, LOGR>(make_field_fp(mf, twf_fwd, gl, logN), c0 + col, load, store);
+                    else
+                        pass_a_body<false, LOGR>(make_field_int(mods, tws_fwd, ninvs, gl, logN), c0 + col, load, store);
+                }
             }
         }
         __syncthreads();
+    }
+}
+
+// the instance for a ring (N = 2^12 .. 2^16) and a digit size
+typedef decltype(&modup_mid_kernel<4, 8>) modup_mid_t;
+template <u32 LOGR>
+static modup_mid_t modup_mid_for(u32 am) {
+    return am == 1 ? modup_mid_kernel<LOGR, 1> : am == 2 ? modup_mid_kernel<LOGR, 2>
+         : am == 4 ? modup_mid_kernel<LOGR, 4> : modup_mid_kernel<LOGR, 8>;
+}
+static modup_mid_t modup_mid_for(const ckks_params *p) {
+    const u32 am = pad_pow2(p->alpha);
+    switch (p->logN) {
+        case 12: return modup_mid_for<0>(am);
+        case 13: return modup_mid_for<1>(am);
+        case 14: return modup_mid_for<2>(am);
+        case 15: return modup_mid_for<3>(am);
+        default: return modup_mid_for<4>(am);
     }
 }
 
@@ -479,7 +511,8 @@ __global__ __launch_bounds__(KS_THREADS) void moddown_conv_kernel(const u64 *__r
                                                                   const ModFp *__restrict__ modf,
                                                                   const u64 *__restrict__ dn_mat,
                                                                   const double *__restrict__ dn_matf, u32 level,
-                                                                  u32 K, u32 L, u32 N, u32 ystride, u32 yoff) {
+                                                                  u32 K, u32 L, u32 N, u32 ystride, u32 yoff, u32 kpad) {
+    // kpad: special primes per row of dn_matf (K and its zero padding)
     const u32 n = blockIdx.x * KS_THREADS + threadIdx.x;
     const u32 pc = blockIdx.y;   // (item, component)
     u64 yk[KMAX];
@@ -506,7 +539,7 @@ __global__ __launch_bounds__(KS_THREADS) void moddown_conv_kernel(const u64 *__r
         }
         for (u32 i = i0; i < i1; ++i) {
             const double q = modf[i].q, u = modf[i].u;
-            const double *f = dn_matf + (size_t)i * K * 6;
+            const double *f = dn_matf + (size_t)i * kpad * 6;
             double lo = 0.0, hi = 0.0;
 #pragma unroll
             for (u32 k = 0; k < KMAX; ++k)
@@ -534,46 +567,48 @@ __global__ __launch_bounds__(KS_THREADS) void moddown_conv_kernel(const u64 *__r
     }
 }
 
-// ModDown between the two tile passes at N = 2^16, one kernel instead of three.  The last 4 stages of the inverse
-// transform of the special limbs, the base conversion P -> q_i and the first 4 stages of the forward transform of the
-// correction w all work on columns (residues 4096 apart), so a workgroup that owns MID_COLS columns can do all
-// three without leaving the CU:
-//   1. thread (k, col): column col of special limb k, 16 rows in registers, last inverse round (which folds in
+// ModDown between the two tile passes at N = 2^(12+LOGR), one kernel instead of three.  The last LOGR stages of the
+// inverse transform of the special limbs, the base conversion P -> q_i and the first LOGR stages of the forward transform
+// of the correction w all work on columns (residues 4096 apart), so a workgroup that owns a tile of MID_TILE coefficients
+// (512 >> LOGR columns) can do all three without leaving the CU:
+//   1. group k of 32 threads: the columns of special limb k in registers, last inverse round (which folds in
 //      N^-1 (P/p_k)^-1) -> y_k in LDS;
-//   2. thread (row pair, col): its two coefficients' y_k cut into 20-bit pieces once, then for each group of
+//   2. every thread: its two coefficients' y_k cut into 20-bit pieces, then for each group of
 //      MID_TG target limbs the exact fp64 sums of moddown_conv_kernel -> w in LDS;
-//   3. thread (target, col): 16 rows of w_i from LDS, first forward round, out.
+//   3. group t of 32 threads: the columns of w_t from LDS, first forward round, out.
+// At N = 2^12 (LOGR = 0) the tile passes are whole transforms and this is the conversion alone.
 // y: rows (pc*ystride + yoff + k) hold the special limbs after the inverse tile pass; w [pc][level][N] receives the
 // correction ready for the forward tile pass.  Needs K <= 8, every target below 2^50 and every special prime below
 // 2^60 (the launcher checks).  grid: x = column tile, y = pc.
-constexpr u32 MID_COLS = 32, MID_TG = 8, MID_MAX_LEVEL = 32;
-// K8: exactly 8 special primes: no per-prime checks in the conversion loop, so a target's 48 factors arrive through the
-// scalar cache in one burst (with the checks the wave waited for each prime's six in turn).  Staging the factors in
-// LDS instead was measured slower: broadcast reads still take an LDS issue slot per pair of multiply-adds.
+constexpr u32 MID_TG = 8, MID_MAX_LEVEL = 32;
+// KM: K rounded up to a power of two; the factor table is padded with zeros to it, so the loop has no per-prime checks
+// and a target's 6 KM factors arrive through the scalar cache in one burst (with the checks the wave waited for each
+// prime's six in turn).  Staging the factors in LDS instead was measured slower: broadcast reads still take an LDS issue
+// slot per pair of multiply-adds.
 // w_i = sum_k y_k (P/p_k mod q_i) for the two coefficients of a thread, as doubles with |w| <= q/2: the exact fp64 sums
 // of moddown_conv_kernel (20-bit pieces of y times 25-bit halves of the factors)
-template <bool K8>
-__device__ __forceinline__ double mid_convert(const double (&yp)[8][3], const double *__restrict__ f, u32 K, double q,
+template <u32 KM>
+__device__ __forceinline__ double mid_convert(const double (&yp)[KM][3], const double *__restrict__ f, double q,
                                               double u) {
     double lo = 0.0, hi = 0.0;
 #pragma unroll
-    for (u32 k = 0; k < 8; ++k)
-        if (K8 || k < K) {
+    for (u32 k = 0; k < KM; ++k) {
 #pragma unroll
-            for (u32 a = 0; a < 3; ++a) {
-                lo = fma(yp[k][a], f[(k * 3 + a) * 2 + 0], lo);
-                hi = fma(yp[k][a], f[(k * 3 + a) * 2 + 1], hi);
-            }
+        for (u32 a = 0; a < 3; ++a) {
+            lo = fma(yp[k][a], f[(k * 3 + a) * 2 + 0], lo);
+            hi = fma(yp[k][a], f[(k * 3 + a) * 2 + 1], hi);
         }
+    }
     const double tt = hi * 33554432.0;                              // exact: a power of two
     const double x = fma(-rint(tt * u), q, tt) + lo;                // |.| < 0.75 q, plus low < 2^51
     return fma(-rint(x * u), q, x);                                 // |v| <= q/2
 }
 
 // the 20-bit pieces of the K special-limb values of one coefficient, as doubles
-__device__ __forceinline__ void mid_pieces(const u64 (&yraw)[8], double (&yp)[8][3]) {
+template <u32 KM>
+__device__ __forceinline__ void mid_pieces(const u64 (&yraw)[KM], double (&yp)[KM][3]) {
 #pragma unroll
-    for (u32 k = 0; k < 8; ++k) {
+    for (u32 k = 0; k < KM; ++k) {
         const u64 v = yraw[k];
         yp[k][0] = __longlong_as_double((long long)(0x4330000000000000ull | (v & 0xFFFFFu))) - 4503599627370496.0;
         yp[k][1] = __longlong_as_double((long long)(0x4330000000000000ull | ((v >> 20) & 0xFFFFFu))) - 4503599627370496.0;
@@ -587,7 +622,7 @@ __device__ __forceinline__ void mid_pieces(const u64 (&yraw)[8], double (&yp)[8]
 // r' = r + floor(q_{l-1}/2) mod q_{l-1}, the correction of limb i < l-1 becomes w_i P^-1 + (r' mod q_i - floor(q_{l-1}/2)
 // mod q_i): one forward transform per limb serves both the ModDown and the rescale, and the rows written are those of
 // the l-1 remaining limbs.  Exact modular arithmetic throughout: the same residues as ModDown followed by rescale.
-template <bool K8, bool RESC>
+template <u32 LOGR, u32 KM, bool RESC>
 __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict__ y, u64 *__restrict__ w,
                                                           const ModConst *__restrict__ mods,
                                                           const ModFp *__restrict__ modf,
@@ -599,31 +634,37 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
                                                           const double *__restrict__ dn_matf, u32 level, u32 K, u32 L,
                                                           u32 ystride, u32 yoff, const u64 *__restrict__ t_rows,
                                                           const double *__restrict__ pinvf) {
-    constexpr u32 logN = 16, N = 1u << logN;
-    static_assert(MID_TG == 8, "the correction tiles reuse the 8 rows of special-limb tiles");
-    __shared__ u64 ylds[8 * 16 * MID_COLS];
+    constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, COLS = MID_TILE >> LOGR, PER = COLS / 32;
+    static_assert(MID_TG == 8 && KM <= 8, "the correction tiles reuse the 8 rows of special-limb tiles");
+    __shared__ u64 ylds[8 * MID_TILE];
     u64 *wlds = ylds;               // y lives in registers once step 2 has read it: the same 32 KiB
-    const u32 tid = threadIdx.x, col = tid & (MID_COLS - 1), grp = tid / MID_COLS;   // grp < 8
-    const u32 c0 = blockIdx.x * MID_COLS + col;
+    const u32 tid = threadIdx.x, lane = tid & 31, grp = tid / 32;   // grp < 8
+    const u32 c0 = blockIdx.x * COLS;
     const u32 pc = blockIdx.y;
     if (grp < K) {
         const u32 gl = L + grp;
         const u64 *src = y + ((size_t)pc * ystride + yoff + grp) * N;
-        auto load = [&](u32 idx) { return src[idx]; };
-        auto store = [&](u32 idx, u64 v) { ylds[(grp * 16 + (idx >> 12)) * MID_COLS + col] = v; };
         const ModFp mf = modf_dn[gl];
-        if (mf.ok)
-            pass_a_body<true, 4>(make_field_fp(mf, twf_inv, gl, logN), c0, load, store);
-        else
-            pass_a_body<true, 4>(make_field_int(mods, tw_inv, ninv_dn, gl, logN), c0, load, store);
+#pragma unroll
+        for (u32 c = 0; c < PER; ++c) {
+            const u32 col = lane + 32 * c;
+            auto load = [&](u32 idx) { return src[idx]; };
+            auto store = [&](u32 idx, u64 v) { ylds[grp * MID_TILE + (idx >> 12) * COLS + col] = v; };
+            if (LOGR == 0)
+                store(0, load(c0 + col));                            // the tile pass was the whole transform, scaled
+            else if (mf.ok)
+                pass_a_body<true, LOGR>(make_field_fp(mf, twf_inv, gl, logN), c0 + col, load, store);
+            else
+                pass_a_body<true, LOGR>(make_field_int(mods, tw_inv, ninv_dn, gl, logN), c0 + col, load, store);
+        }
     }
     __syncthreads();
-    // the two coefficients of this thread (rows 2*grp, 2*grp + 1 of this column) leave LDS as they are
-    u64 yraw[2][8];
+    // the two coefficients of this thread leave LDS as they are
+    u64 yraw[2][KM];
 #pragma unroll
     for (u32 e = 0; e < 2; ++e)
 #pragma unroll
-        for (u32 k = 0; k < 8; ++k) yraw[e][k] = (K8 || k < K) ? ylds[(k * 16 + 2 * grp + e) * MID_COLS + col] : 0;
+        for (u32 k = 0; k < KM; ++k) yraw[e][k] = k < K ? ylds[k * MID_TILE + e * 256 + tid] : 0;
     __syncthreads();                // every thread has its y: the tile may be overwritten
     // rescale: the dropped limb first
     double rp[2] = {0.0, 0.0}, hq = 0.0;
@@ -639,10 +680,11 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
         hq = (double)(mods[il].q >> 1);
 #pragma unroll
         for (u32 e = 0; e < 2; ++e) {
-            double yp[8][3];
-            mid_pieces(yraw[e], yp);
-            const double wl = mid_convert<K8>(yp, dn_matf + (size_t)il * K * 6, K, ml.q, ml.u);
-            const double t = fl.in(t_rows[(size_t)pc * N + (2 * grp + e) * 4096 + c0]);
+            double yp[KM][3];
+            mid_pieces<KM>(yraw[e], yp);
+            const double wl = mid_convert<KM>(yp, dn_matf + (size_t)il * (KM * 6), ml.q, ml.u);
+            const u32 el = e * 256 + tid;
+            const double t = fl.in(t_rows[(size_t)pc * N + el / COLS * 4096 + c0 + el % COLS]);
             double r = t - fl.mul(wl, pinvf[il]);
             fl.norm(r);
             if (r < 0) r += ml.q;                                   // r in [0, q_last)
@@ -655,13 +697,13 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
         // which is what lets four waves share a SIMD)
 #pragma unroll 1
         for (u32 e = 0; e < 2; ++e) {
-            double yp[8][3];
-            mid_pieces(e ? yraw[1] : yraw[0], yp);
+            double yp[KM][3];
+            mid_pieces<KM>(e ? yraw[1] : yraw[0], yp);
             const double rpe = e ? rp[1] : rp[0];
             for (u32 t = 0; t < MID_TG && i0 + t < n_out; ++t) {
                 const u32 i = i0 + t;
                 const double q = modf[i].q, u = modf[i].u;
-                double v = mid_convert<K8>(yp, dn_matf + (size_t)i * K * 6, K, q, u);
+                double v = mid_convert<KM>(yp, dn_matf + (size_t)i * (KM * 6), q, u);
                 if (RESC) {
                     FieldFp fi;
                     fi.q = q;
@@ -673,7 +715,7 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
                     fi.norm(ri);                                    // r' mod q_i
                     v = fi.mul(v, pinvf[i]) + (ri - hi_);           // |.| < 2q: the forward round normalises
                 }
-                wlds[(t * 16 + 2 * grp + e) * MID_COLS + col] = (u64)__double_as_longlong(v);
+                wlds[t * MID_TILE + e * 256 + tid] = (u64)__double_as_longlong(v);
             }
         }
         __syncthreads();
@@ -681,12 +723,17 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
             const u32 i = i0 + grp;
             const FieldFp ff = make_field_fp(modf[i], twf_fwd, i, logN);
             u64 *dst = w + ((size_t)pc * level + i) * N;
-            double v[16];
 #pragma unroll
-            for (u32 j = 0; j < 16; ++j) v[j] = __longlong_as_double((long long)wlds[(grp * 16 + j) * MID_COLS + col]);
-            radix_fwd<4>(ff, v, 0, 0);
+            for (u32 c = 0; c < PER; ++c) {
+                const u32 col = lane + 32 * c;
+                double v[R];
 #pragma unroll
-            for (u32 j = 0; j < 16; ++j) dst[j * 4096 + c0] = ff.out(v[j]);
+                for (u32 j = 0; j < R; ++j)
+                    v[j] = __longlong_as_double((long long)wlds[grp * MID_TILE + j * COLS + col]);
+                radix_fwd<LOGR>(ff, v, 0, 0);
+#pragma unroll
+                for (u32 j = 0; j < R; ++j) dst[j * 4096 + c0 + col] = ff.out(v[j]);
+            }
         }
         __syncthreads();
     }
@@ -732,24 +779,35 @@ __global__ __launch_bounds__(KS_THREADS) void moddown_rescale_final_kernel(PtrPa
 }
 
 // Whether the fused kernel applies to this parameter set at this level.
-static bool moddown_mid_ok(const ckks_params *p, u32 level) {
-    bool ok = p->logN == 16 && p->dn_fp && p->K <= 8 && level <= MID_MAX_LEVEL;
+bool moddown_mid_ok(const ckks_params *p, u32 level) {
+    bool ok = p->logN >= 12 && p->logN <= 16 && p->dn_fp && p->K >= 1 && p->K <= 8 && level <= MID_MAX_LEVEL;
     for (u32 i = 0; i < level; ++i) ok = ok && (p->mod[i] >> 50) == 0;
     return ok;
 }
 
+typedef decltype(&moddown_mid_kernel<4, 8, false>) moddown_mid_t;
+template <u32 LOGR, bool RESC>
+static moddown_mid_t moddown_mid_for(u32 km) {
+    return km == 1 ? moddown_mid_kernel<LOGR, 1, RESC> : km == 2 ? moddown_mid_kernel<LOGR, 2, RESC>
+         : km == 4 ? moddown_mid_kernel<LOGR, 4, RESC> : moddown_mid_kernel<LOGR, 8, RESC>;
+}
+template <bool RESC>
+static moddown_mid_t moddown_mid_for(const ckks_params *p) {
+    const u32 km = pad_pow2(p->K);
+    switch (p->logN) {
+        case 12: return moddown_mid_for<0, RESC>(km);
+        case 13: return moddown_mid_for<1, RESC>(km);
+        case 14: return moddown_mid_for<2, RESC>(km);
+        case 15: return moddown_mid_for<3, RESC>(km);
+        default: return moddown_mid_for<4, RESC>(km);
+    }
+}
+
 static void launch_moddown_mid(const ckks_params *p, const u64 *y, u64 *w, u32 n, u32 level, u32 ystride, u32 yoff,
                                hipStream_t stream, const u64 *t_rows = nullptr) {
-#define MID_LAUNCH(K8, RESC)                                                                                         \
-    hipLaunchKernelGGL((moddown_mid_kernel<K8, RESC>), dim3(4096 / MID_COLS, n * 2), dim3(256), 0, stream, y, w,       \
-                       p->d_mod, p->d_modf, p->d_modf_dn, p->d_tws_inv, p->d_twf_inv, p->d_ninvs_dn, p->d_twf_fwd,    \
-                       p->d_dn_matf, level, p->K, p->L, ystride, yoff, t_rows, p->d_pinvf)
-    if (p->K == 8) {
-        if (t_rows) MID_LAUNCH(true, true); else MID_LAUNCH(true, false);
-    } else {
-        if (t_rows) MID_LAUNCH(false, true); else MID_LAUNCH(false, false);
-    }
-#undef MID_LAUNCH
+    hipLaunchKernelGGL(t_rows ? moddown_mid_for<true>(p) : moddown_mid_for<false>(p), dim3(p->N / MID_TILE, n * 2),
+                       dim3(256), 0, stream, y, w, p->d_mod, p->d_modf, p->d_modf_dn, p->d_tws_inv, p->d_twf_inv,
+                       p->d_ninvs_dn, p->d_twf_fwd, p->d_dn_matf, level, p->K, p->L, ystride, yoff, t_rows, p->d_pinvf);
 }
 
 // base conversion P -> q_i of n*2 polynomials; the rows of polynomial pc start at row pc * ystride + yoff of y
@@ -760,7 +818,7 @@ static void launch_moddown_conv(const ckks_params *p, const u64 *y, u64 *w, u32 
     for (u32 i = 0; i < level; ++i) fp = fp && (p->mod[i] >> 50) == 0;
 #define CONV_LAUNCH(KM, FPK)                                                                                      \
     hipLaunchKernelGGL((moddown_conv_kernel<KM, FPK>), grid, dim3(KS_THREADS), 0, stream, y, w, p->d_mod, p->d_modf, \
-                       p->d_dn_mat, p->d_dn_matf, level, p->K, p->L, p->N, ystride, yoff)
+                       p->d_dn_mat, p->d_dn_matf, level, p->K, p->L, p->N, ystride, yoff, pad_pow2(p->K))
     if (p->K <= 8) {
         if (fp) CONV_LAUNCH(8, true); else CONV_LAUNCH(8, false);
     } else {
@@ -989,6 +1047,29 @@ size_t switch_scratch_words(const ckks_params *p, u32 level, u32 n_items) {
     return (size_t)n_items * 2 * ((size_t)(level + p->K) + level) * p->N;
 }
 
+// forward transform (the passes of pass_mask) of the converted rows; the digit's own limbs are not filled and skipped
+static int transform_digits(ckks_params *p, u32 level, u32 n, u64 *d_digits, hipStream_t stream, u32 pass_mask) {
+    const u32 Wl = level + p->K, alpha = p->alpha, beta = (level + alpha - 1) / alpha;
+    LimbIds ids;
+    auto row_id = [&](u32 j, u32 t) -> uint8_t {
+        const u32 lo = j * alpha, hi = std::min(lo + alpha, level);
+        if (t >= lo && t < hi) return (uint8_t)SKIP_ROW;
+        return (uint8_t)(t < level ? t : p->L + (t - level));
+    };
+    if (beta * Wl <= MAX_ROW_IDS) {
+        for (u32 j = 0; j < beta; ++j)
+            for (u32 t = 0; t < Wl; ++t) ids.id[j * Wl + t] = row_id(j, t);
+        return launch_ntt(p, d_digits, ids, beta * Wl, n * beta * Wl, false, stream, pass_mask);
+    }
+    for (u32 r = 0; r < n; ++r)
+        for (u32 j = 0; j < beta; ++j) {
+            for (u32 t = 0; t < Wl; ++t) ids.id[t] = row_id(j, t);
+            const int rc = launch_ntt(p, d_digits + ((size_t)r * beta + j) * Wl * p->N, ids, Wl, Wl, false, stream, pass_mask);
+            if (rc) return rc;
+        }
+    return CKKS_OK;
+}
+
 // c1[r] [level][N] NTT domain (n <= ROT_BATCH device pointers) -> d_digits [n][beta][level+K][N] NTT domain;
 // d_tmp [n][level][N] scratch.
 int decompose(ckks_params *p, const u64 *const *c1, u32 n, u32 level, u64 *d_digits, u64 *d_tmp,
@@ -1012,23 +1093,16 @@ int decompose(ckks_params *p, const u64 *const *c1, u32 n, u32 level, u64 *d_dig
                            p->d_mod, p->d_modf, p->d_tws_inv, p->d_twf_inv, p->d_ninvs, level, p->logN);
         CKKS_LAUNCH_CHECK("gather_intt_kernel");
         p->limb_ntts += (u64)n * level;
-        if (p->logN == 16 && all_fp && sp60 && alpha <= 8 && K <= 8) {
+        if (p->logN <= 16 && all_fp && sp60 && alpha <= 8 && K <= 8) {
             // the column passes of both transforms ride in the base conversion: c1 read once, digits written once
-            const u32 tgroups = (Wl - std::min(alpha, level) + UP_TG - 1) / UP_TG;
-            const u32 tsplit = n * beta * (4096 / UP_COLS) < 1024 ? std::max<u32>(1, tgroups) : 1;
-            hipLaunchKernelGGL(modup_mid_kernel, dim3(4096 / UP_COLS * tsplit, beta, n), dim3(256), 0, stream, d_tmp,
+            const u32 tgroups = (Wl - std::min(alpha, level) + UP_TG - 1) / UP_TG, tiles = N / MID_TILE;
+            const u32 tsplit = n * beta * tiles < 1024 ? std::max<u32>(1, tgroups) : 1;
+            hipLaunchKernelGGL(modup_mid_for(p), dim3(tiles * tsplit, beta, n), dim3(256), 0, stream, d_tmp,
                                d_digits, p->d_mod, p->d_modf, lt->d_modf_up, p->d_twf_inv, p->d_twf_fwd, p->d_tws_fwd,
                                p->d_ninvs, lt->d_up_ft, lt->d_up_mats, level, K, L, alpha, beta, tsplit);
             CKKS_LAUNCH_CHECK("modup_mid_kernel");
             p->limb_ntts += (u64)n * beta * Wl - (u64)n * level;
-            auto row_id2 = [&](u32 j, u32 t) -> uint8_t {
-                u32 lo = j * alpha, hi = std::min(lo + alpha, level);
-                if (t >= lo && t < hi) return (uint8_t)SKIP_ROW;
-                return (uint8_t)(t < level ? t : L + (t - level));
-            };
-            for (u32 j = 0; j < beta; ++j)
-                for (u32 t = 0; t < Wl; ++t) ids.id[j * Wl + t] = row_id2(j, t);
-            return launch_ntt(p, d_digits, ids, beta * Wl, n * beta * Wl, false, stream, 2);
+            return transform_digits(p, level, n, d_digits, stream, 2);
         }
         rc = launch_ntt(p, d_tmp, ids, level, n * level, true, stream, 2);
     } else {
@@ -1059,26 +1133,7 @@ int decompose(ckks_params *p, const u64 *const *c1, u32 n, u32 level, u64 *d_dig
     }
 #undef MODUP_LAUNCH
     CKKS_LAUNCH_CHECK("modup_kernel");
-    // forward NTT of the converted rows; the digit's own limbs were copied and are skipped
-    auto row_id = [&](u32 j, u32 t) -> uint8_t {
-        u32 lo = j * alpha, hi = std::min(lo + alpha, level);
-        if (t >= lo && t < hi) return (uint8_t)SKIP_ROW;
-        return (uint8_t)(t < level ? t : L + (t - level));
-    };
-    if (beta * Wl <= MAX_ROW_IDS) {
-        for (u32 j = 0; j < beta; ++j)
-            for (u32 t = 0; t < Wl; ++t) ids.id[j * Wl + t] = row_id(j, t);
-        rc = launch_ntt(p, d_digits, ids, beta * Wl, n * beta * Wl, false, stream);
-        if (rc) return rc;
-    } else {
-        for (u32 r = 0; r < n; ++r)
-            for (u32 j = 0; j < beta; ++j) {
-                for (u32 t = 0; t < Wl; ++t) ids.id[t] = row_id(j, t);
-                rc = launch_ntt(p, d_digits + ((size_t)r * beta + j) * Wl * N, ids, Wl, Wl, false, stream);
-                if (rc) return rc;
-            }
-    }
-    return CKKS_OK;
+    return transform_digits(p, level, n, d_digits, stream, 3);
 }
 
 static u32 build_pack(const SwitchItem *items, u32 n, ItemPack &pack) {

@@ -932,12 +932,7 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
     u64 *d_yfull = d_acc + acc_w + u_w + lay.mg_w, *d_t = d_yfull + lay.yfull_w;
     if (rescale) d_ct_y = d_yfull;
     // ModDown and rescale of the merged giant step in one pass, where the fused kernels apply
-    const bool fused_rescale = rescale && merged && !conj_key && P->logN == 16 && P->K <= 8 && P->dn_fp &&
-                               [&] {
-                                   for (u32 i = 0; i < level; ++i)
-                                       if (P->mod[i] >> 50) return false;
-                                   return level <= 32;
-                               }();
+    const bool fused_rescale = rescale && merged && !conj_key && moddown_mid_ok(P, level);
 
     // 1. baby-step bank: the inputs are decomposed once (hoisting); the switches are issued step by step
     //    with the G inputs of one step next to each other, so that they share the reads of that step's key

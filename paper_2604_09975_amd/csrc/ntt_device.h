@@ -29,6 +29,7 @@ struct FieldInt {
     u64 q, q2;
     const ulonglong2 *tw;
     TwInt n0, n1;
+    __device__ __forceinline__ W scale() const { return n0; }
     __device__ __forceinline__ T in(u64 x) const { return x; }
     __device__ __forceinline__ u64 out(T x) const {
         if (x >= q2) x -= q2;
@@ -70,6 +71,7 @@ struct FieldFp {
     typedef double W;
     double q, u, n0, n1;
     const double *tw;
+    __device__ __forceinline__ W scale() const { return n0; }
     __device__ __forceinline__ T in(u64 x) const {
         return __longlong_as_double((long long)(x | 0x4330000000000000ull)) - 4503599627370496.0;
     }
@@ -258,10 +260,12 @@ __device__ __forceinline__ void pass_a_body(const F &f, u32 col, Load load, Stor
     typename F::T v[R];
 #pragma unroll
     for (u32 j = 0; j < R; ++j) v[j] = f.in(load(j * 4096 + col));
-    if (!INV)
-        radix_fwd<LOGR>(f, v, 0, 0);
-    else
+    if constexpr (INV && LOGR == 0)
+        v[0] = f.mul(v[0], f.scale());                              // N = 2^12: no stage is left, the scaling is
+    else if constexpr (INV)
         radix_inv<LOGR>(f, v, 0, 0, true);
+    else
+        radix_fwd<LOGR>(f, v, 0, 0);
 #pragma unroll
     for (u32 j = 0; j < R; ++j) store(j * 4096 + col, f.out(v[j]));
 }

@@ -181,8 +181,9 @@ int ckks_params::build_level_tables(u32 level) {
     // tables of the fused decomposition kernel
     std::vector<ModFp> modf_up(level);
     // per digit j and target row t (k for the special rows): the factors of the digit's up to 8 source limbs side
-    // by side, zero where the digit is shorter (alpha above 8 does not use these tables)
-    std::vector<double> mats((size_t)t.beta * K * 48, 0.0), ft((size_t)t.beta * Wl * 8, 0.0);
+    // by side, zero up to the next power of two (alpha above 8 does not use these tables)
+    const u32 am = pad_pow2(alpha);
+    std::vector<double> mats((size_t)t.beta * K * am * 6, 0.0), ft((size_t)t.beta * Wl * am, 0.0);
     for (u32 i = 0; i < level; ++i) {
         u32 lo = (i / alpha) * alpha, hi = std::min(lo + alpha, level);
         u64 qi = mod[i], prod = 1;
@@ -192,7 +193,7 @@ int ckks_params::build_level_tables(u32 level) {
         ModFp f;
         f.q = (double)qi;
         f.u = 1.0 / (double)qi;
-        f.ninv = (double)hmul(hninv[2 * i], invp, qi);
+        f.ninv = (double)(logN == 12 ? invp : hmul(hninv[2 * i], invp, qi));
         f.ninv_w = (double)hmul(hninv[2 * i + 1], invp, qi);
         f.ok = (qi >> 50) == 0;
         f.pad = 0;
@@ -206,7 +207,7 @@ int ckks_params::build_level_tables(u32 level) {
             for (u32 b = 0; b < 2; ++b) {
                 u64 g = hmul(hmul(fk, hpow(2, 25 * b, pk), pk), hmod[L + k].one, pk);
                 for (u32 c = 0; c < 3; ++c)
-                    mats[((((size_t)dj * K + k) * 8 + da) * 2 + b) * 3 + c] = (double)((g >> (20 * c)) & 0xFFFFFu);
+                    mats[((((size_t)dj * K + k) * am + da) * 2 + b) * 3 + c] = (double)((g >> (20 * c)) & 0xFFFFFu);
             }
         }
         for (u32 t2 = 0; t2 < level; ++t2) {
@@ -214,7 +215,7 @@ int ckks_params::build_level_tables(u32 level) {
             u64 mt = mod[t2], fq = 1;
             for (u32 b = lo; b < hi; ++b)
                 if (b != i) fq = hmul(fq, mod[b] % mt, mt);
-            ft[((size_t)dj * Wl + t2) * 8 + da] = (double)fq;       // exact below 2^53; used for targets below 2^50
+            ft[((size_t)dj * Wl + t2) * am + da] = (double)fq;       // exact below 2^53; used for targets below 2^50
         }
     }
     // entered into the map first, so that ckks_params_destroy frees whatever part was uploaded if a later part fails
@@ -378,7 +379,8 @@ int ckks_params_create(uint32_t logN, const uint64_t *q, uint32_t L, const uint6
         }
     P->hninv = ninv_plain;
     std::vector<u64> dn_inv(K), dn_mat((size_t)K * L), pinv(L), qlinv((size_t)L * L, 0);
-    std::vector<double> dn_matf((size_t)L * K * 6, 0.0), pinvf(L, 0.0);
+    const u32 kpad = pad_pow2(K);
+    std::vector<double> dn_matf((size_t)L * kpad * 6, 0.0), pinvf(L, 0.0);
     for (u32 k = 0; k < K; ++k) {
         u64 pk = mod[L + k], prod = 1;
         for (u32 b = 0; b < K; ++b)
@@ -393,8 +395,8 @@ int ckks_params_create(uint32_t logN, const uint64_t *q, uint32_t L, const uint6
             // conversion onto a prime below 2^50 is then a sum of exact 20-bit x 25-bit products in fp64
             for (u32 a = 0; a < 3; ++a) {
                 const u64 c = hmul(f, hpow(2, 20 * a, mod[i]), mod[i]);
-                dn_matf[(((size_t)i * K + k) * 3 + a) * 2 + 0] = (double)(c & ((1u << 25) - 1));
-                dn_matf[(((size_t)i * K + k) * 3 + a) * 2 + 1] = (double)(c >> 25);
+                dn_matf[(((size_t)i * kpad + k) * 3 + a) * 2 + 0] = (double)(c & ((1u << 25) - 1));
+                dn_matf[(((size_t)i * kpad + k) * 3 + a) * 2 + 1] = (double)(c >> 25);
             }
         }
     }

@@ -1,0 +1,40 @@
+"""GPU parity of the key switch with the column passes of the transforms inside the base conversions, on every ring these
+kernels are instantiated for (N = 2^12 .. 2^16, 1 to 16 rows per column) and the ring above them: digit sizes and
+special-prime counts at and off the powers of two their factor tables are padded to, partial last digits, more rows of
+digits than one launch describes, special primes below and above 2^50."""
+import numpy as np
+import pytest
+
+from tests import helpers
+from tests.gpu_util import make_pair
+from tests.test_gpu_matmul import run_case
+from tests.test_gpu_rotate import _run
+from paper_2604_09975_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("logN,L,K,dnum,level,pbits",
+                         [(12, 3, 1, 3, 3, 60), (12, 10, 6, 2, 8, 60), (12, 8, 8, 1, 8, 60), (12, 6, 3, 2, 4, 49),
+                          (13, 3, 1, 3, 2, 60), (13, 12, 4, 3, 11, 60), (13, 6, 3, 2, 5, 60), (13, 8, 8, 1, 7, 60),
+                          (13, 12, 1, 12, 12, 60), (13, 9, 9, 1, 9, 59),
+                          (14, 6, 2, 3, 5, 60), (14, 10, 5, 2, 9, 60), (14, 3, 1, 3, 3, 49), (14, 8, 7, 1, 8, 60),
+                          (15, 12, 4, 3, 9, 60), (15, 2, 1, 2, 1, 60), (15, 4, 2, 2, 4, 60), (15, 7, 8, 1, 7, 60),
+                          (16, 3, 1, 3, 3, 60), (16, 4, 2, 2, 3, 60), (16, 4, 4, 1, 4, 60),
+                          (17, 4, 2, 2, 3, 60)])
+def test_key_switch_shapes(logN, L, K, dnum, level, pbits):
+    O = helpers.small_oracle(logN, L=L, K=K, dnum=dnum, qbits=50 if pbits > 50 else 45, pbits=pbits)
+    _, P = make_pair(O)
+    _run(O, P, level, [1, "conj"], 1000 * logN + 10 * L + level, 2.0**40, hw=16)
+
+
+@pytest.mark.parametrize("logN,m,C,N1", [(12, 64, 8, 4), (13, 64, 8, 2), (14, 256, 8, 4), (15, 512, 4, 2)])
+def test_projection_with_fused_rescale(logN, m, C, N1):
+    """Merged giant step, ModDown and rescale in one pass (compared with the call without the flag and with the oracle)."""
+    O = helpers.small_oracle(logN, L=4, K=2, dnum=2, qbits=50, pbits=60)
+    _, P = make_pair(O)
+    r = W.rng(logN)
+    X, Wm = r.uniform(-1, 1, (m, C + 3)), r.uniform(-0.5, 0.5, (C + 3, 2 * C - 1))
+    Y, ref, _, _ = run_case(O, P, X, Wm, r.uniform(-0.5, 0.5, 2 * C - 1), m, C, N1, 40, 4, 40 + logN, hw=16, real=True,
+                            merged=True)
+    assert np.abs(Y - ref).max() <= 1e-3
