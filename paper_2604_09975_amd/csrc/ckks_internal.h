@@ -132,12 +132,12 @@ struct ckks_weights {
     const ckks_params *params = nullptr;
     ckks::u32 level = 0, m = 0, C = 0, G = 0, B_out = 0, N1 = 0, N2 = 0;
     // Diagonals, NTT domain, index ((b*N2 + p)*G + g)*N1 + q.  Two stores, each allocated when first needed:
-    // d_w  [diagonal][level][N] words: per limb a double (q < 2^50) or Montgomery form;
-    // d_wp [diagonal][level] packed half-limb records of 50-bit residues, for output blocks whose diagonals all
+    // d_w  [diagonal][level][N] words: per limb a balanced double (q < 2^50) or Montgomery form;
+    // d_wp packed half-limb records of 50-bit residues, for output blocks whose diagonals all
     //      encode real slot vectors when every active prime is below 2^50 (block_packed).
     ckks::u64 *d_w = nullptr;
     unsigned char *d_wp = nullptr;
-    unsigned char *d_wpf = nullptr;    // [diagonal][level] packed whole-limb records: general diagonals, same condition
+    unsigned char *d_wpf = nullptr;    // packed whole-limb records: general diagonals, same condition
     ckks::u64 *d_stage = nullptr;      // expansion buffer of the packed store (STAGE_DIAGS diagonals)
     bool packable = false;             // every active prime below 2^50 and N large enough for the palindrome kernel
     ckks::u64 *d_bias = nullptr;       // [B_out][level][N], NTT domain, canonical, times bias_mul; or null
@@ -169,6 +169,8 @@ struct SwitchItem {
     u64 *dst;            // [2][level][N]
     u64 galois_elt;
     u32 accumulate;      // add into dst instead of overwriting
+    u32 balanced;        // limbs below 2^50 leave as balanced doubles (bit patterns), |x| <= (q+1)/2: the projection's
+                         // bank, read by the multiply-accumulate kernels only (not with accumulate)
 };
 size_t digits_words(const ckks_params *p, u32 level);
 size_t switch_scratch_words(const ckks_params *p, u32 level, u32 n_items);

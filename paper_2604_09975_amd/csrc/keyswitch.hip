@@ -845,6 +845,7 @@ __global__ __launch_bounds__(KS_THREADS) void moddown_final_kernel(ItemPack pack
     if (comp == 0 && it.c0) v = add_mod(v, it.c0[(size_t)i * N + galois_index(k, it.galois_elt, logN)], m.q);
     u64 *dst = it.dst + ((size_t)comp * level + i) * N + k;
     if (it.accumulate) v = add_mod(v, *dst, m.q);
+    if (it.balanced && (m.q >> 50) == 0) v = (u64)__double_as_longlong((double)(int64_t)(v > m.q / 2 ? v - m.q : v));
     *dst = v;
 }
 
@@ -1007,7 +1008,13 @@ __global__ __launch_bounds__(NTT_THREADS) void passb_final_kernel(ItemPack pack,
                         if (j < beta) sum += ff.mul(ff.in(dv[e][z][j]), ff.in(kv[e][j][z]));
                     const double t = ff.mul(sum, c_sum) - ff.mul(ff.from_bits(lds[lds_pad(loc + z)]), c_w) +
                                      (ff.in(cv[e][z]) + ff.in(ov[e][z]));
-                    out[z] = ff.out(t);
+                    if (it.balanced) {
+                        double b = t;
+                        ff.norm(b);
+                        out[z] = ff.bits(b);
+                    } else {
+                        out[z] = ff.out(t);
+                    }
                 } else {
                     u128 acc = {0, 0};
 #pragma unroll
@@ -1188,6 +1195,7 @@ int moddown_add(ckks_params *p, u32 level, u64 *d_u, u64 *const *dst, u32 n, u64
         it.dst = dst[r < n ? r : 0];
         it.galois_elt = 1;
         it.accumulate = 1;
+        it.balanced = 0;
     }
     LimbIds ids;
     for (u32 t = 0; t < Wl; ++t) ids.id[t] = (uint8_t)(t < level ? SKIP_ROW : L + (t - level));
@@ -1229,6 +1237,7 @@ int moddown_rescale(ckks_params *p, u32 level, u64 *d_u, const u64 *const *z, u6
         it.dst = out[r < n ? r : 0];
         it.galois_elt = 1;
         it.accumulate = 0;
+        it.balanced = 0;
     }
     LimbIds ids;
     for (u32 t = 0; t < Wl; ++t) ids.id[t] = (uint8_t)(t < level ? SKIP_ROW : L + (t - level));
@@ -1375,6 +1384,7 @@ int rotate_hoisted(ckks_params *P, const u64 *d_ct_in, u32 level, const int32_t 
         it.dst = d_ct_out + (size_t)r * ctw;
         it.galois_elt = g;
         it.accumulate = 0;
+        it.balanced = 0;
         items.push_back(it);
     }
     for (u32 r : copies)
@@ -1548,6 +1558,7 @@ int ckks_ctmul(ckks_params_t *P, const uint64_t *d_ct_a, const uint64_t *d_ct_b,
     it.dst = d_ct_out;
     it.galois_elt = 1;
     it.accumulate = 1;
+    it.balanced = 0;
     return switch_batch(P, level, &it, 1, d_work, stream);
 }
 

@@ -13,7 +13,7 @@
 namespace ckks {
 
 constexpr u32 MM_THREADS = 256;
-constexpr u32 MM_TB = 8;   // (b,p) accumulators kept in registers per thread
+constexpr u32 MM_TB = 8;   // (b,p) accumulators kept in registers per thread on primes of 50 bits and more
 
 // int64 coefficients [count][N] -> canonical residues [count][level][N]
 __global__ __launch_bounds__(EW_THREADS) void expand_coeffs_kernel(const int64_t *__restrict__ coef,
@@ -37,41 +37,86 @@ __global__ __launch_bounds__(EW_THREADS) void scale_rows_kernel(u64 *data, const
     data[idx] = mont_mul(data[idx], cm, m);
 }
 
-// acc[bp][comp][i][k] = sum_{gq} bank[gq][comp][i][k] * w[bp][gq][i][k]
-// grid: x = tile of (b,p) pairs (fastest), y = run of coefficients, z = limb (slowest: one limb's bank slice
-//       stays resident in the Infinity Cache while all its tiles run).  An XCD-aware remapping of x/y and a
-//       variant whose four wavefronts share their bank loads were measured and did not help.
-// Weight limbs are stored in the library's internal form: for a prime below 2^50 the residue as a
-// double (products are then reduced with the exact FMA scheme of the NTT butterflies and summed as
-// signed doubles, about 7 issue slots per product), otherwise in Montgomery form (128-bit lazy sums;
-// flush = number of products that fit such a sum for the largest modulus).
-// blockIdx.z indexes `limbs`, the list of limbs this launch covers (fp64 limbs and Montgomery limbs
-// go to separate launches so that each kernel keeps its own register budget).
-// Each thread owns VEC adjacent coefficients (16-byte loads for VEC = 2) and TB (b,p) accumulators.
-// Packed weight records: 50 bits per residue instead of 64, in three parts: the low 32 bits, bits 32..47, and
-// bits 48..49 four residues to a byte.  A half record holds the first N/2 residues of a limb (real diagonals,
-// the rest is the mirror image), a whole-limb record all N.
-__host__ __device__ inline size_t packed_record_bytes(u32 N) { return (size_t)3 * N + N / 8; }
-// A record is a sequence of 800-byte chunks of 128 residues (what one wavefront reads per weight limb and step):
-// 512 bytes of low words, 256 of middle halves, 32 of top bits, so that the three loads of a wavefront fall into
-// one contiguous piece of memory.  Byte offsets of residue k's parts within the record:
-__host__ __device__ inline u32 packed_lo(u32 k) { return (k >> 7) * 800u + 4u * (k & 127u); }
-__host__ __device__ inline u32 packed_hi(u32 k) { return (k >> 7) * 800u + 512u + 2u * (k & 127u); }
-__host__ __device__ inline u32 packed_top(u32 k) { return (k >> 7) * 800u + 768u + ((k & 127u) >> 2); }
+// ---- acc[bp][comp][i][k] = sum_{gq} bank[gq][comp][i][k] * w[bp][gq][i][k] ------------------------------------------
+//
+// Operands.  On primes below 2^50 bank residues and weights are balanced, |x|, |w| <= (q+1)/2 <= 2^49, exact in doubles:
+// the key switches store the bank that way (SwitchItem::balanced), the unpacked weight store holds the doubles, and a
+// packed record holds w + 2^49.  Larger primes keep canonical bank residues and Montgomery weights (diag_mac_int_kernel).
+//
+// Packed weight records: 50 bits per residue, in the order in which a wavefront reads them, so that it has one stream:
+// [limb][chunk of 128 residues][tile of TB pairs][gq / 4][pair of the tile][3200 bytes].  A 3200-byte record holds the
+// chunk's residues of four steps: two parts of 16 bytes per lane (residues 2l, 2l+1 of two steps, low 32 bits), two of 8
+// bytes per lane (bits 32..47) and one of 4 bytes per pair of lanes (bits 48, 49; one byte per step), each a whole
+// number of 128-byte lines read by one load of the wavefront.  A half store holds the first N/2 residues of a limb (real
+// diagonals: the rest is the mirror image), a whole store all N.
+// What the order is worth, QKV layer (38 GB): parts that share lines 9.6 ms, whole lines with every pair's records in a
+// place of their own 8.54 ms, this order 8.43 ms.
+constexpr u32 TB = 4;                                              // (b,p) pairs of a tile
+constexpr u32 REC_BYTES = 3200, REC_CHUNK = 128, REC_MID = 2048, REC_TOP = 3072;
+struct PackedShape {
+    u32 GQ4, ntile, nch, level;                                    // records per pair and chunk, tiles, chunks per limb
+    __host__ __device__ size_t rec(u32 bp, u32 i, u32 chunk, u32 gq) const {
+        return (((((size_t)i * nch + chunk) * ntile + bp / TB) * GQ4 + (gq >> 2)) * TB + bp % TB) * REC_BYTES;
+    }
+    size_t bytes() const { return (size_t)level * nch * ntile * GQ4 * TB * REC_BYTES; }
+};
+static inline PackedShape packed_shape(u32 N, u32 level, u32 GQ, u32 BP, bool whole) {
+    return PackedShape{(GQ + 3) / 4, (BP + TB - 1) / TB, (whole ? N : N / 2) / REC_CHUNK, level};
+}
 
-// PACKED (VEC = 2): the weight limbs are whole-limb packed records.
-// FULL: every tile of the launch has all its TB pairs (no per-pair guards: the loop body stays one basic block and the
-// loaded registers are not copied around); tiles are numbered from tile0.
-template <u32 TB, u32 VEC, bool PACKED, bool FULL>
-__global__ __launch_bounds__(MM_THREADS) void diag_mac_kernel(const u64 *__restrict__ bank,
-                                                              const u64 *__restrict__ w, u64 *__restrict__ acc,
+// Sums of products in two doubles per output, without a reduction per product:
+//   H' = fma(x, w, H)   with H held between 2^102 and 2^103, so that the product is rounded to a multiple of 2^50,
+//   l  = fma(x, w, -(H' - H))   the rounded-off part, an exact integer, |l| <= 2^49,   L += l.
+// 8 products (each at most 2^98 - 2^60) keep H in its binade from 1.5 * 2^102 and |L| below 2^52 + 2^51; fold() then
+// moves H into L modulo q: with c = rint((H + L)/q), H - c q is an exact integer below 2^53, and the new |L| is below
+// 1.1 q.  4 instructions per product and 6 per 8 products, against 7 and 3 with a quotient per product.
+constexpr double MAC_H0 = 1.5 * 5070602400912917605986812821504.0;    // 1.5 * 2^102
+struct MacSum {
+    double h, l;
+    __device__ __forceinline__ void mac(double x, double w) {
+        const double n = fma(x, w, h);
+        l += fma(x, w, h - n);
+        h = n;
+    }
+    __device__ __forceinline__ void fold(double q, double u) {
+        const double s = h - MAC_H0;
+        const double c = rint(fma(s, u, l * u));
+        l = fma(-c, q, s) + l;
+        h = MAC_H0;
+    }
+    __device__ __forceinline__ u64 canonical(double q, double u) const {
+        double v = fma(-rint(l * u), q, l);
+        if (v < 0) v += q;
+        return (u64)__double_as_longlong(v + 4503599627370496.0) & 0x000fffffffffffffull;
+    }
+};
+
+// grid: x = tile of TB (b,p) pairs from tile0, y = run of 512 coefficients (SYM: and their mirrors), z = limb (limbs.id:
+// the limbs this launch covers).  A thread owns two adjacent coefficients k, k+1 and TB pairs, of which those from bp0 to
+// bp1 - 1 are stored; two steps' weights and two steps' bank residues are on their way while two are multiplied.
+// SYM: plaintexts that encode REAL slot vectors.  Such a polynomial is fixed by X -> X^-1, so its transform is a
+// palindrome: w[k] = w[N-1-k] (the exponents 2*bitrev(k)+1 and 2*bitrev(N-1-k)+1 are negatives of each other mod 2N).
+// Only the first half of every weight limb is read; each value serves coefficient k and its mirror: the thread owns
+// N-2-k, N-1-k as well.
+// TB = 4: 32 outputs of two doubles (128 registers) are what two waves per SIMD leave room for.
+// Steps gq0 .. gq1-1 of the GQ per pair are summed; accumulate: onto what acc already holds.
+// swizzle: workgroups go to the XCDs round-robin and each XCD has its own L2, so the linear workgroup id is unfolded to
+// let one XCD walk all (b,p) tiles of a run of coefficients back to back: the bank lines of that run are then fetched
+// into one L2 once.
+// What bounds it (QKV layer, 38.2 GB of records, 2.4 GB of bank, 1.8 GB of sums): memory.  8.45 ms; without the products
+// 8.40, without the record loads 4.36, without the bank loads 7.05 (5.4 TB/s, what a plain read reaches).  The kernel with
+// a quotient per product was bound by fp64 issue: 8.66 ms with the vector units 92 % busy; these sums keep them 55 % busy.
+template <bool SYM, bool PACKED>
+__global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *__restrict__ bank,
+                                                              const void *__restrict__ w, u64 *__restrict__ acc,
                                                               const ModFp *__restrict__ modf, LimbIds limbs,
                                                               u32 level, u32 N, u32 GQ, u32 BP, u32 swizzle,
-                                                              u32 gq0, u32 gq1, u32 accumulate, u32 tile0) {
-    // steps gq0 .. gq1-1 of the GQ per pair are summed; accumulate: onto what acc already holds
-    static_assert(!PACKED || VEC == 2, "packed weights are read in pairs");
-    typedef u64 vec_t __attribute__((ext_vector_type(VEC)));
-    // swizzle: one XCD walks all (b,p) tiles of a run of coefficients back to back (see diag_mac_sym_kernel)
+                                                              u32 gq0, u32 gq1, u32 accumulate, u32 bp0, u32 bp1) {
+    constexpr u32 CO = SYM ? 4 : 2, HV = CO / 2;                   // coefficients of a thread, pairs of them
+    typedef double dvec_t __attribute__((ext_vector_type(2)));
+    typedef u64 vec_t __attribute__((ext_vector_type(2)));
+    typedef u32 u32x2 __attribute__((ext_vector_type(2)));
+    typedef u32 u32x4 __attribute__((ext_vector_type(4)));
     u32 tile = blockIdx.x, run = blockIdx.y;
     if (swizzle) {
         const u32 lin = blockIdx.y * gridDim.x + blockIdx.x;
@@ -79,129 +124,187 @@ __global__ __launch_bounds__(MM_THREADS) void diag_mac_kernel(const u64 *__restr
         tile = slot % gridDim.x;
         run = (slot / gridDim.x) * 8 + xcd;
     }
-    const u32 bp0 = (tile0 + tile) * TB;
-    const u32 k = (run * MM_THREADS + threadIdx.x) * VEC;
+    const u32 bpt = (bp0 / TB + tile) * TB;                        // the tile's first pair
+    const u32 k = (run * MM_THREADS + threadIdx.x) * 2;            // SYM: k < N/2
+    const u32 kk[2] = {k, N - 2 - k};                              // SYM: the second holds the mirrors of k+1, k
     const u32 i = limbs.id[blockIdx.z];
-    const size_t limb_off = (size_t)i * N + k;
-    const size_t w_stride = (size_t)level * N;         // between consecutive gq of one (b,p)
-    const ModFp mf = modf[i];
-    const double q = mf.q, u = mf.u;
-    double a0[TB][VEC], a1[TB][VEC];
+    const size_t row = (size_t)i * N, w_stride = (size_t)level * N;
+    const double q = modf[i].q, u = modf[i].u;
+    MacSum a[TB][2][CO];
 #pragma unroll
     for (u32 t = 0; t < TB; ++t)
 #pragma unroll
-        for (u32 e = 0; e < VEC; ++e) a0[t][e] = a1[t][e] = 0.0;
-    // loads of step gq+1 are issued before the arithmetic of step gq
-    typedef u32 wvec_t __attribute__((ext_vector_type(4)));
-    vec_t xb0, xb1;
-    wvec_t wb[TB];
-    const size_t rec = 2 * packed_record_bytes(N);
-    const unsigned char *wbytes = reinterpret_cast<const unsigned char *>(w);
-    const u32 off_lo = packed_lo(k), off_hi = packed_hi(k), off_top = packed_top(k);
-    const u32 top_shift = (k & 2) * 2;
-    auto fetch = [&](u32 gq) {
-        xb0 = *reinterpret_cast<const vec_t *>(bank + ((size_t)gq * 2 + 0) * w_stride + limb_off);
-        xb1 = *reinterpret_cast<const vec_t *>(bank + ((size_t)gq * 2 + 1) * w_stride + limb_off);
+        for (u32 c = 0; c < 2; ++c)
 #pragma unroll
-        for (u32 t = 0; t < TB; ++t)
-            if (FULL || bp0 + t < BP) {
-                if (PACKED) {
-                    const unsigned char *r = wbytes + (((size_t)(bp0 + t) * GQ + gq) * level + i) * rec;
-                    const __amdgpu_buffer_rsrc_t rs =
-                        __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(r), 0, (int)rec, 0x00020000);
-                    typedef u32 u32x2 __attribute__((ext_vector_type(2)));
-                    const u32x2 lo = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off_lo, 0, 0);
-                    wb[t][0] = lo[0];
-                    wb[t][1] = lo[1];
-                    wb[t][2] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)off_hi, 0, 0);
-                    wb[t][3] = __builtin_amdgcn_raw_buffer_load_b8(rs, (int)off_top, 0, 0);
-                } else {
-                    const vec_t v = *reinterpret_cast<const vec_t *>(w + ((size_t)(bp0 + t) * GQ + gq) * w_stride + limb_off);
-#pragma unroll
-                    for (u32 e = 0; e < VEC; ++e) {
-                        wb[t][2 * e] = (u32)v[e];
-                        wb[t][2 * e + 1] = (u32)(v[e] >> 32);
-                    }
-                }
-            }
-    };
+            for (u32 e = 0; e < CO; ++e) a[t][c][e] = MacSum{MAC_H0, 0.0};
     if (accumulate) {
 #pragma unroll
         for (u32 t = 0; t < TB; ++t)
-            if (FULL || bp0 + t < BP) {
-                const vec_t p0 = *reinterpret_cast<const vec_t *>(acc + ((size_t)(bp0 + t) * 2 + 0) * w_stride + limb_off);
-                const vec_t p1 = *reinterpret_cast<const vec_t *>(acc + ((size_t)(bp0 + t) * 2 + 1) * w_stride + limb_off);
+            if (bpt + t >= bp0 && bpt + t < bp1)
 #pragma unroll
-                for (u32 e = 0; e < VEC; ++e) {
-                    a0[t][e] = (double)p0[e];
-                    a1[t][e] = (double)p1[e];
-                }
-            }
+                for (u32 c = 0; c < 2; ++c)
+#pragma unroll
+                    for (u32 h = 0; h < HV; ++h) {
+                        const vec_t v = *reinterpret_cast<const vec_t *>(acc + ((size_t)(bpt + t) * 2 + c) * w_stride + row + kk[h]);
+                        a[t][c][2 * h].l = (double)v[0];
+                        a[t][c][2 * h + 1].l = (double)v[1];
+                    }
     }
-    fetch(gq0);
-    for (u32 gq = gq0; gq < gq1; ++gq) {
-        double x0[VEC], x1[VEC];
+    dvec_t x[2][2][HV];                                            // [step & 1][component]
+    u32 wr[2][TB][6], wt[2][TB];                                   // two steps' weights as loaded, twice; four steps' top bits
+    double wp[2][TB][2];                                           // two steps' weights, unpacked store
+    // buffer loads: wavefront-uniform addresses stay in scalar registers, the lanes add 32-bit offsets; and a step outside
+    // the range reads zeros (a buffer of no records), so that the loop has no branches
+    const u32 r_first = gq0 >> 2, r_end = (gq1 + 3) >> 2;          // records of the range
+    const double *xp = bank + (size_t)r_first * 8 * w_stride + row;  // the next step to fetch
+    auto fetch_x = [&](u32 s, u32 gq) {
+        const int bytes = gq >= gq0 && gq < gq1 ? (int)(N * sizeof(double)) : 0;
 #pragma unroll
-        for (u32 e = 0; e < VEC; ++e) {
-            x0[e] = __longlong_as_double((long long)(xb0[e] | 0x4330000000000000ull)) - 4503599627370496.0;
-            x1[e] = __longlong_as_double((long long)(xb1[e] | 0x4330000000000000ull)) - 4503599627370496.0;
+        for (u32 c = 0; c < 2; ++c) {
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(xp), 0, bytes, 0x00020000);
+#pragma unroll
+            for (u32 h = 0; h < HV; ++h)
+                x[s][c][h] = __builtin_bit_cast(dvec_t, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(kk[h] * 8), 0, 0));
+            xp += w_stride;
         }
-        double wd[TB][VEC];
+    };
+    const u32 lane = threadIdx.x & 63, top_shift = (lane & 1) * 4;
+    const PackedShape ps{(GQ + 3) / 4, (BP + TB - 1) / TB, (SYM ? N / 2 : N) / REC_CHUNK, level};
+    const u32 chunk = __builtin_amdgcn_readfirstlane(k / REC_CHUNK);
+    const unsigned char *wrec = reinterpret_cast<const unsigned char *>(w) + ps.rec(bpt, i, chunk, 4 * r_first);
+    const double *wdbl[TB];                                        // unpacked store: pairs beyond the last repeat it
 #pragma unroll
-        for (u32 t = 0; t < TB; ++t) {
-            if (PACKED) {
-                const u32 top = wb[t][3] >> top_shift;
-                const u32 h0 = 0x43300000u | ((top & 3u) << 16) | (wb[t][2] & 0xffffu);
-                const u32 h1 = 0x43300000u | ((top & 12u) << 14) | (wb[t][2] >> 16);
-                wd[t][0] = __hiloint2double((int)h0, (int)wb[t][0]) - 4503599627370496.0;
-                wd[t][VEC - 1] = __hiloint2double((int)h1, (int)wb[t][1]) - 4503599627370496.0;
-            } else {
+    for (u32 t = 0; t < TB; ++t)
+        wdbl[t] = reinterpret_cast<const double *>(w) + ((size_t)min(bpt + t, BP - 1) * GQ + 4 * r_first) * w_stride + row;
+    // steps 2 g2, 2 g2 + 1 into buffer g2 & 1, with the even one the record's top bits into buffer (g2 / 2) & 1
+    auto fetch_w = [&](u32 buf, u32 tbuf, u32 g2) {
+        if (PACKED) {
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(wrec), 0,
+                                                                                TB * REC_BYTES, 0x00020000);
 #pragma unroll
-                for (u32 e = 0; e < VEC; ++e) wd[t][e] = __hiloint2double((int)wb[t][2 * e + 1], (int)wb[t][2 * e]);
+            for (u32 t = 0; t < TB; ++t) {
+                const int at = (int)(t * REC_BYTES);
+                const u32x4 lo = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(lane * 16), at + (int)(buf * 1024), 0);
+                const u32x2 mid = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(lane * 8), at + (int)(REC_MID + buf * 512), 0);
+#pragma unroll
+                for (u32 z = 0; z < 4; ++z) wr[buf][t][z] = lo[z];
+                wr[buf][t][4] = mid[0];
+                wr[buf][t][5] = mid[1];
+                if (buf == 0) wt[tbuf][t] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)((lane >> 1) * 4), at + (int)REC_TOP, 0);
             }
-        }
-        if (gq + 1 < gq1) fetch(gq + 1);
-#pragma unroll
-        for (u32 t = 0; t < TB; ++t) {
-            if (FULL || bp0 + t < BP) {
-#pragma unroll
-                for (u32 e = 0; e < VEC; ++e) {
-                    const double wv = wd[t][e];
-                    // x*w = h + l exactly; subtract the nearest multiple of q: |r| < 0.9 q
-                    const double h0 = x0[e] * wv, h1 = x1[e] * wv;
-                    const double l0 = fma(x0[e], wv, -h0), l1 = fma(x1[e], wv, -h1);
-                    const double c0 = rint(h0 * u), c1 = rint(h1 * u);
-                    a0[t][e] += fma(-c0, q, h0) + l0;
-                    a1[t][e] += fma(-c1, q, h1) + l1;
-                }
-            }
-        }
-        if (((gq - gq0) & 7) == 7) {   // keep the signed sums far below 2^53
+            if (buf == 1 && g2 + 1 < 2 * r_end) wrec += TB * REC_BYTES;   // the last record stays the last
+        } else {
 #pragma unroll
             for (u32 t = 0; t < TB; ++t)
 #pragma unroll
-                for (u32 e = 0; e < VEC; ++e) {
-                    a0[t][e] = fma(-rint(a0[t][e] * u), q, a0[t][e]);
-                    a1[t][e] = fma(-rint(a1[t][e] * u), q, a1[t][e]);
+                for (u32 s = 0; s < 2; ++s) {
+                    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                        const_cast<double *>(wdbl[t]), 0, 2 * g2 + s < GQ ? (int)(N * sizeof(double)) : 0, 0x00020000);
+                    const dvec_t v = __builtin_bit_cast(dvec_t, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(k * 8), 0, 0));
+                    wp[s][t][0] = v[0];
+                    wp[s][t][1] = v[1];
+                    wdbl[t] += w_stride;
                 }
         }
+    };
+    // Step s of two, pairs in order in the first and in reverse in the second: a product needs its sum's old and new
+    // high parts at once, and with this order the new one finds its place in the register the previous sum has left,
+    // and goes back in the next step, so that no copies are needed.  One pair at a time: the barriers keep the compiler
+    // from unpacking all pairs first, which takes more registers than two waves per SIMD have.
+    auto products = [&](u32 buf, u32 tbuf, u32 s) {
+#pragma unroll
+        for (u32 tt = 0; tt < TB; ++tt) {
+            const u32 t = s ? TB - 1 - tt : tt;
+            double wd[2];
+            if (PACKED) {
+                // (2^52 + w + 2^49) from its bits, then one exact subtraction
+                u32 top = wt[tbuf][t], mid = wr[buf][t][4 + s];
+                asm volatile("" : "+v"(top), "+v"(mid));
+                top >>= top_shift;
+#pragma unroll
+                for (u32 e = 0; e < 2; ++e) {
+                    const u32 hi = 0x43300000u | (((top >> (16 * buf + 8 * s + 2 * e)) & 3u) << 16) |
+                                   (e ? mid >> 16 : mid & 0xffffu);
+                    wd[e] = __hiloint2double((int)hi, (int)wr[buf][t][2 * s + e]) - (4503599627370496.0 + 562949953421312.0);
+                }
+            } else {
+                wd[0] = wp[s][t][0];
+                wd[1] = wp[s][t][1];
+            }
+            // weight of k serves k and N-1-k; weight of k+1 serves k+1 and N-2-k
+#pragma unroll
+            for (u32 oo = 0; oo < 2 * CO; ++oo) {
+                const u32 o = s ? 2 * CO - 1 - oo : oo, c = o / CO, e = o % CO;
+                a[t][c][e].mac(x[s][c][e >> 1][e & 1], wd[e < 2 ? e : 3 - e]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto fold = [&]() {
+#pragma unroll
+        for (u32 t = 0; t < TB; ++t)
+#pragma unroll
+            for (u32 c = 0; c < 2; ++c)
+#pragma unroll
+                for (u32 e = 0; e < CO; ++e) a[t][c][e].fold(q, u);
+    };
+    // two steps; the next two's weights are on their way before the products
+    auto two_steps = [&](u32 buf, u32 tbuf, u32 g2) {
+        if (PACKED) fetch_w(buf ^ 1, buf ? tbuf ^ 1 : tbuf, g2 + 1);
+        products(buf, tbuf, 0);
+        fetch_x(0, 2 * g2 + 2);
+        products(buf, tbuf, 1);
+        if (!PACKED) fetch_w(0, 0, g2 + 1);
+        fetch_x(1, 2 * g2 + 3);
+    };
+    // whole records of four steps, whatever the range: 8 products between two folds
+    fetch_w(0, 0, 2 * r_first);
+    fetch_x(0, 4 * r_first);
+    fetch_x(1, 4 * r_first + 1);
+    for (u32 r = r_first; r < r_end; r += 2) {
+        two_steps(0, 0, 2 * r);
+        two_steps(1, 0, 2 * r + 1);
+        if (r + 1 < r_end) {
+            two_steps(0, 1, 2 * r + 2);
+            two_steps(1, 1, 2 * r + 3);
+        }
+        fold();
     }
 #pragma unroll
     for (u32 t = 0; t < TB; ++t) {
-        if (FULL || bp0 + t < BP) {
-            vec_t o0, o1;
+        if (bpt + t >= bp0 && bpt + t < bp1) {
 #pragma unroll
-            for (u32 e = 0; e < VEC; ++e) {
-                double v0 = fma(-rint(a0[t][e] * u), q, a0[t][e]), v1 = fma(-rint(a1[t][e] * u), q, a1[t][e]);
-                if (v0 < 0) v0 += q;
-                if (v1 < 0) v1 += q;
-                o0[e] = (u64)__double_as_longlong(v0 + 4503599627370496.0) & 0x000fffffffffffffull;
-                o1[e] = (u64)__double_as_longlong(v1 + 4503599627370496.0) & 0x000fffffffffffffull;
-            }
-            *reinterpret_cast<vec_t *>(acc + ((size_t)(bp0 + t) * 2 + 0) * w_stride + limb_off) = o0;
-            *reinterpret_cast<vec_t *>(acc + ((size_t)(bp0 + t) * 2 + 1) * w_stride + limb_off) = o1;
+            for (u32 c = 0; c < 2; ++c)
+#pragma unroll
+                for (u32 h = 0; h < HV; ++h) {
+                    vec_t o;
+                    o[0] = a[t][c][2 * h].canonical(q, u);
+                    o[1] = a[t][c][2 * h + 1].canonical(q, u);
+                    *reinterpret_cast<vec_t *>(acc + ((size_t)(bpt + t) * 2 + c) * w_stride + row + kk[h]) = o;
+                }
         }
     }
+}
+
+// residue below 2^50 -> the balanced double of the same class
+__device__ __forceinline__ u64 balanced_bits(u64 x, u64 q) {
+    return (u64)__double_as_longlong((double)(int64_t)(x > q / 2 ? x - q : x));
+}
+
+// An input ciphertext as the bank entry of the identity rotation: balanced doubles on primes below 2^50, as it is on
+// the others.  blockIdx.y = component * level + limb, two residues per thread
+__global__ __launch_bounds__(EW_THREADS) void bank_entry_kernel(const u64 *__restrict__ src, u64 *__restrict__ dst,
+                                                                const ModConst *__restrict__ mods, u32 level, u32 N) {
+    typedef u64 vec_t __attribute__((ext_vector_type(2)));
+    const size_t k = (size_t)blockIdx.y * N + (blockIdx.x * EW_THREADS + threadIdx.x) * 2;
+    const u64 q = mods[blockIdx.y % level].q;
+    vec_t v = *reinterpret_cast<const vec_t *>(src + k);
+    if ((q >> 50) == 0) {
+        v[0] = balanced_bits(v[0], q);
+        v[1] = balanced_bits(v[1], q);
+    }
+    *reinterpret_cast<vec_t *>(dst + k) = v;
 }
 
 // dst[z][0 .. words) = src[z * src_stride + 0 .. words), z = blockIdx.z; words is a multiple of 2 * EW_THREADS
@@ -228,171 +331,6 @@ __global__ __launch_bounds__(EW_THREADS) void add_bias_kernel(u64 *__restrict__ 
     *dst = v;
 }
 
-// Same sum for plaintexts that encode REAL slot vectors.  Such a polynomial is fixed by X -> X^-1, so its
-// transform is a palindrome: w[k] = w[N-1-k] (the exponents 2*bitrev(k)+1 and 2*bitrev(N-1-k)+1 are
-// negatives of each other mod 2N).  Only the first half of every weight limb is read; each value serves
-// coefficient k and its mirror.  A thread owns coefficients k, k+1 and N-2-k, N-1-k and TB (b,p) pairs.
-// Workgroups go to the XCDs round-robin and each XCD has its own L2, so when the run count allows it the
-// linear workgroup id is unfolded to let one XCD walk all (b,p) tiles of a run of coefficients back to
-// back: the bank lines of that run are then fetched into one L2 once.
-// PACKED: the half limb is stored in 50 bits per residue instead of 64 (packed_record_bytes) in three parts,
-// the low 32 bits, bits 32..47, and bits 48..49 four residues to a byte.  The double is rebuilt as
-// (2^52 + x) - 2^52 from the bit pattern, one addition per weight.
-// FULL, tile0: as in diag_mac_kernel.
-template <u32 TB, bool PACKED, bool FULL>
-__global__ __launch_bounds__(MM_THREADS) void diag_mac_sym_kernel(const u64 *__restrict__ bank,
-                                                                  const u64 *__restrict__ w, u64 *__restrict__ acc,
-                                                                  const ModFp *__restrict__ modf, LimbIds limbs,
-                                                                  u32 level, u32 N, u32 GQ, u32 BP, u32 swizzle,
-                                                                  u32 gq0, u32 gq1, u32 accumulate, u32 tile0) {
-    // steps gq0 .. gq1-1 of the GQ per pair are summed; accumulate: onto what acc already holds
-    typedef u64 vec_t __attribute__((ext_vector_type(2)));
-    typedef u32 wvec_t __attribute__((ext_vector_type(4)));      // one (b,p) pair's two weights as loaded
-    u32 tile = blockIdx.x, run = blockIdx.y;
-    if (swizzle) {
-        const u32 lin = blockIdx.y * gridDim.x + blockIdx.x;
-        const u32 xcd = lin & 7, slot = lin >> 3;
-        tile = slot % gridDim.x;
-        run = (slot / gridDim.x) * 8 + xcd;
-    }
-    const u32 bp0 = (tile0 + tile) * TB;
-    const u32 k = (run * MM_THREADS + threadIdx.x) * 2;          // k < N/2
-    const u32 km = N - 2 - k;                                    // mirrors of k+1, k
-    const u32 i = limbs.id[blockIdx.z];
-    const size_t row = (size_t)i * N;
-    const size_t w_stride = (size_t)level * N;
-    const ModFp mf = modf[i];
-    const double q = mf.q, u = mf.u;
-    double a[TB][2][4];                                          // [pair][component][k, k+1, N-2-k, N-1-k]
-#pragma unroll
-    for (u32 t = 0; t < TB; ++t)
-#pragma unroll
-        for (u32 e = 0; e < 4; ++e) a[t][0][e] = a[t][1][e] = 0.0;
-    // loads of step gq+1 are issued before the arithmetic of step gq
-    vec_t xb[2][2];
-    wvec_t wb[TB];
-    const size_t rec = packed_record_bytes(N);
-    const unsigned char *wbytes = reinterpret_cast<const unsigned char *>(w);
-    const u32 off_lo = packed_lo(k), off_hi = packed_hi(k), off_top = packed_top(k);
-    auto fetch = [&](u32 gq) {
-#pragma unroll
-        for (u32 c = 0; c < 2; ++c) {
-            const u64 *b = bank + ((size_t)gq * 2 + c) * w_stride + row;
-            xb[c][0] = *reinterpret_cast<const vec_t *>(b + k);
-            xb[c][1] = *reinterpret_cast<const vec_t *>(b + km);
-        }
-#pragma unroll
-        for (u32 t = 0; t < TB; ++t)
-            if (FULL || bp0 + t < BP) {
-                if (PACKED) {
-                    // buffer loads: the record's address is workgroup-uniform (scalar registers) and the lanes
-                    // add 32-bit offsets, which keeps the 24 addresses of a step out of the vector registers
-                    const unsigned char *r = wbytes + (((size_t)(bp0 + t) * GQ + gq) * level + i) * rec;
-                    const __amdgpu_buffer_rsrc_t rs =
-                        __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(r), 0, (int)rec, 0x00020000);
-                    typedef u32 u32x2 __attribute__((ext_vector_type(2)));
-                    const u32x2 lo = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off_lo, 0, 0);
-                    wb[t][0] = lo[0];
-                    wb[t][1] = lo[1];
-                    wb[t][2] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)off_hi, 0, 0);
-                    wb[t][3] = __builtin_amdgcn_raw_buffer_load_b8(rs, (int)off_top, 0, 0);
-                } else {
-                    wb[t] = *reinterpret_cast<const wvec_t *>(w + ((size_t)(bp0 + t) * GQ + gq) * w_stride + row + k);
-                }
-            }
-    };
-    const u32 top_shift = (k & 2) * 2;                           // k is even: bits 0..3 or 4..7 of the byte
-    if (accumulate) {
-#pragma unroll
-        for (u32 t = 0; t < TB; ++t)
-            if (FULL || bp0 + t < BP) {
-#pragma unroll
-                for (u32 c = 0; c < 2; ++c) {
-                    const u64 *src = acc + ((size_t)(bp0 + t) * 2 + c) * w_stride + row;
-                    const vec_t lo = *reinterpret_cast<const vec_t *>(src + k);
-                    const vec_t hi = *reinterpret_cast<const vec_t *>(src + km);
-                    a[t][c][0] = (double)lo[0];
-                    a[t][c][1] = (double)lo[1];
-                    a[t][c][2] = (double)hi[0];
-                    a[t][c][3] = (double)hi[1];
-                }
-            }
-    }
-    fetch(gq0);
-    for (u32 gq = gq0; gq < gq1; ++gq) {
-        double x[2][4];
-#pragma unroll
-        for (u32 c = 0; c < 2; ++c) {
-            const u64 r[4] = {xb[c][0][0], xb[c][0][1], xb[c][1][0], xb[c][1][1]};
-#pragma unroll
-            for (u32 e = 0; e < 4; ++e)
-                x[c][e] = __longlong_as_double((long long)(r[e] | 0x4330000000000000ull)) - 4503599627370496.0;
-        }
-        // the weights leave their load registers as doubles before the next step's loads are issued into them
-        double wd[TB][2];
-#pragma unroll
-        for (u32 t = 0; t < TB; ++t) {
-            if (PACKED) {
-                const u32 top = wb[t][3] >> top_shift;
-                const u32 h0 = 0x43300000u | ((top & 3u) << 16) | (wb[t][2] & 0xffffu);
-                const u32 h1 = 0x43300000u | ((top & 12u) << 14) | (wb[t][2] >> 16);
-                wd[t][0] = __hiloint2double((int)h0, (int)wb[t][0]) - 4503599627370496.0;
-                wd[t][1] = __hiloint2double((int)h1, (int)wb[t][1]) - 4503599627370496.0;
-            } else {
-                wd[t][0] = __hiloint2double((int)wb[t][1], (int)wb[t][0]);
-                wd[t][1] = __hiloint2double((int)wb[t][3], (int)wb[t][2]);
-            }
-        }
-        if (gq + 1 < gq1) fetch(gq + 1);
-#pragma unroll
-        for (u32 t = 0; t < TB; ++t) {
-            if (FULL || bp0 + t < BP) {
-                // weight of k serves k and N-1-k; weight of k+1 serves k+1 and N-2-k
-                const double wv[4] = {wd[t][0], wd[t][1], wd[t][1], wd[t][0]};
-#pragma unroll
-                for (u32 c = 0; c < 2; ++c)
-#pragma unroll
-                    for (u32 e = 0; e < 4; ++e) {
-                        const double h = x[c][e] * wv[e];
-                        const double l = fma(x[c][e], wv[e], -h);
-                        a[t][c][e] += fma(-rint(h * u), q, h) + l;
-                    }
-            }
-        }
-        if (((gq - gq0) & 7) == 7) {
-#pragma unroll
-            for (u32 t = 0; t < TB; ++t)
-#pragma unroll
-                for (u32 c = 0; c < 2; ++c)
-#pragma unroll
-                    for (u32 e = 0; e < 4; ++e) a[t][c][e] = fma(-rint(a[t][c][e] * u), q, a[t][c][e]);
-        }
-    }
-#pragma unroll
-    for (u32 t = 0; t < TB; ++t) {
-        if (FULL || bp0 + t < BP) {
-#pragma unroll
-            for (u32 c = 0; c < 2; ++c) {
-                u64 o[4];
-#pragma unroll
-                for (u32 e = 0; e < 4; ++e) {
-                    double v = fma(-rint(a[t][c][e] * u), q, a[t][c][e]);
-                    if (v < 0) v += q;
-                    o[e] = (u64)__double_as_longlong(v + 4503599627370496.0) & 0x000fffffffffffffull;
-                }
-                u64 *dst = acc + ((size_t)(bp0 + t) * 2 + c) * w_stride + row;
-                vec_t lo, hi;
-                lo[0] = o[0];
-                lo[1] = o[1];
-                hi[0] = o[2];
-                hi[1] = o[3];
-                *reinterpret_cast<vec_t *>(dst + k) = lo;
-                *reinterpret_cast<vec_t *>(dst + km) = hi;
-            }
-        }
-    }
-}
-
 // sym[d] is cleared if polynomial d of the chunk is not fixed by X -> X^-1, i.e. breaks
 // c[N-j] == -c[j] for 0 < j < N (which also forces c[N/2] == 0)
 __global__ __launch_bounds__(EW_THREADS) void check_real_kernel(const int64_t *__restrict__ coef, u32 *sym, u32 N) {
@@ -402,48 +340,88 @@ __global__ __launch_bounds__(EW_THREADS) void check_real_kernel(const int64_t *_
     if (c[N - n] != -c[n]) sym[blockIdx.y] = 0;
 }
 
-// rows [rows][N] of canonical residues below 2^50 -> packed half-limb records (first N/2 residues of each row);
-// a thread packs four residues
-__global__ __launch_bounds__(EW_THREADS) void pack_half_kernel(const u64 *__restrict__ in,
-                                                               unsigned char *__restrict__ out, u32 N, u32 cnt) {
-    // cnt = N/2 (half records of real diagonals) or N (whole limbs of general ones)
+// Byte offsets within a record of step s (0..3), residue r (even, of 128) of its chunk: low words of r, r+1; middle
+// halves of r, r+1; the byte with the top bits of r & ~3 .. r | 3.
+__device__ __forceinline__ u32 rec_lo(u32 s, u32 r) { return (s >> 1) * 1024 + (r >> 1) * 16 + (s & 1) * 8; }
+__device__ __forceinline__ u32 rec_mid(u32 s, u32 r) { return REC_MID + (s >> 1) * 512 + (r >> 1) * 8 + (s & 1) * 4; }
+__device__ __forceinline__ u32 rec_top(u32 s, u32 r) { return REC_TOP + (r >> 2) * 4 + s; }
+
+// Canonical residues below 2^50 of c diagonals, consecutive steps gq0 .. gq0 + c - 1 of pair bp -> packed records of the
+// first cnt residues of each limb.  in [c][level][N].  A thread packs four residues of two steps that share a part of a
+// record (16-byte and 8-byte stores), or of the one of them that is there: the other is left alone.
+// grid: x = 1024 residues, y = (pair of steps of the run) * level + limb
+__global__ __launch_bounds__(EW_THREADS) void pack_records_kernel(const u64 *__restrict__ in,
+                                                                  unsigned char *__restrict__ out,
+                                                                  const ModConst *__restrict__ mods, PackedShape ps,
+                                                                  u32 N, u32 cnt, u32 bp, u32 gq0, u32 c) {
     const u32 k = (blockIdx.x * EW_THREADS + threadIdx.x) * 4;
     if (k >= cnt) return;
-    const u64 *src = in + (size_t)blockIdx.y * N + k;
-    unsigned char *r = out + (size_t)blockIdx.y * (cnt == N ? 2 : 1) * packed_record_bytes(N);
-    uint4 lo;
-    uint2 hi;
-    const u64 x0 = src[0], x1 = src[1], x2 = src[2], x3 = src[3];
-    lo.x = (u32)x0;
-    lo.y = (u32)x1;
-    lo.z = (u32)x2;
-    lo.w = (u32)x3;
-    hi.x = (u32)((x0 >> 32) & 0xffff) | ((u32)((x1 >> 32) & 0xffff) << 16);
-    hi.y = (u32)((x2 >> 32) & 0xffff) | ((u32)((x3 >> 32) & 0xffff) << 16);
-    *reinterpret_cast<uint4 *>(r + packed_lo(k)) = lo;
-    *reinterpret_cast<uint2 *>(r + packed_hi(k)) = hi;
-    r[packed_top(k)] =
-        (unsigned char)(((x0 >> 48) & 3) | (((x1 >> 48) & 3) << 2) | (((x2 >> 48) & 3) << 4) | (((x3 >> 48) & 3) << 6));
+    const u32 i = blockIdx.y % ps.level, g2 = (gq0 >> 1) + blockIdx.y / ps.level;
+    const u64 q = mods[i].q;
+    u32 lo[2][4], mid[2][2], top[2];
+    bool have[2];
+#pragma unroll
+    for (u32 s = 0; s < 2; ++s) {
+        const u32 gq = 2 * g2 + s;
+        have[s] = gq >= gq0 && gq < gq0 + c;
+        if (!have[s]) continue;
+        const u64 *src = in + ((size_t)(gq - gq0) * ps.level + i) * N + k;
+        u32 hi[4];
+        top[s] = 0;
+#pragma unroll
+        for (u32 e = 0; e < 4; ++e) {
+            const u64 x = src[e], v = (x > q / 2 ? x - q : x) + (1ull << 49);     // w + 2^49, below 2^50
+            lo[s][e] = (u32)v;
+            hi[e] = (u32)(v >> 32) & 0xffffu;
+            top[s] |= (u32)(v >> 48) << (2 * e);
+        }
+        mid[s][0] = hi[0] | (hi[1] << 16);
+        mid[s][1] = hi[2] | (hi[3] << 16);
+    }
+    const u32 r = k & (REC_CHUNK - 1), st = (2 * g2) & 3;
+    unsigned char *rec = out + ps.rec(bp, i, k / REC_CHUNK, 2 * g2);
+    if (have[0] && have[1]) {
+        *reinterpret_cast<uint4 *>(rec + rec_lo(st, r)) = make_uint4(lo[0][0], lo[0][1], lo[1][0], lo[1][1]);
+        *reinterpret_cast<uint4 *>(rec + rec_lo(st, r + 2)) = make_uint4(lo[0][2], lo[0][3], lo[1][2], lo[1][3]);
+        *reinterpret_cast<uint4 *>(rec + rec_mid(st, r)) = make_uint4(mid[0][0], mid[1][0], mid[0][1], mid[1][1]);
+        *reinterpret_cast<unsigned short *>(rec + rec_top(st, r)) = (unsigned short)(top[0] | (top[1] << 8));
+        return;
+    }
+#pragma unroll
+    for (u32 s = 0; s < 2; ++s)
+        if (have[s]) {
+            *reinterpret_cast<uint2 *>(rec + rec_lo(st + s, r)) = make_uint2(lo[s][0], lo[s][1]);
+            *reinterpret_cast<uint2 *>(rec + rec_lo(st + s, r + 2)) = make_uint2(lo[s][2], lo[s][3]);
+            *reinterpret_cast<u32 *>(rec + rec_mid(st + s, r)) = mid[s][0];
+            *reinterpret_cast<u32 *>(rec + rec_mid(st + s, r + 2)) = mid[s][1];
+            rec[rec_top(st + s, r)] = (unsigned char)top[s];
+        }
 }
 
-// half records [rows] -> whole-limb records [rows]: residue k of the second half is residue N-1-k of the first
-__global__ __launch_bounds__(EW_THREADS) void widen_half_kernel(const unsigned char *__restrict__ in,
-                                                                unsigned char *__restrict__ out, u32 N) {
+// steps gq0 .. gq0 + gridDim.y / level - 1 of pair bp: half records -> whole-limb records; residue k of the second half
+// is residue N-1-k of the first.  grid: x = 1024 residues, y = step * level + limb
+__global__ __launch_bounds__(EW_THREADS) void widen_records_kernel(const unsigned char *__restrict__ in,
+                                                                   unsigned char *__restrict__ out, PackedShape half,
+                                                                   PackedShape whole, u32 N, u32 bp, u32 gq0) {
     const u32 k = (blockIdx.x * EW_THREADS + threadIdx.x) * 4;
     if (k >= N) return;
-    const unsigned char *r = in + (size_t)blockIdx.y * packed_record_bytes(N);
-    unsigned char *o = out + (size_t)blockIdx.y * 2 * packed_record_bytes(N);
+    const u32 i = blockIdx.y % half.level, gq = gq0 + blockIdx.y / half.level, s = gq & 3;
     u32 lo[4], hi[4], top = 0;
 #pragma unroll
     for (u32 e = 0; e < 4; ++e) {
-        const u32 s = k + e < N / 2 ? k + e : N - 1 - (k + e);
-        lo[e] = *reinterpret_cast<const u32 *>(r + packed_lo(s));
-        hi[e] = *reinterpret_cast<const unsigned short *>(r + packed_hi(s));
-        top |= ((r[packed_top(s)] >> ((s & 3) * 2)) & 3u) << (2 * e);
+        const u32 m = k + e < N / 2 ? k + e : N - 1 - (k + e), r = m & (REC_CHUNK - 1);
+        const unsigned char *rec = in + half.rec(bp, i, m / REC_CHUNK, gq);
+        lo[e] = *reinterpret_cast<const u32 *>(rec + rec_lo(s, r) + (r & 1) * 4);
+        hi[e] = *reinterpret_cast<const unsigned short *>(rec + rec_mid(s, r) + (r & 1) * 2);
+        top |= ((rec[rec_top(s, r)] >> ((r & 3) * 2)) & 3u) << (2 * e);
     }
-    *reinterpret_cast<uint4 *>(o + packed_lo(k)) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-    *reinterpret_cast<uint2 *>(o + packed_hi(k)) = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
-    o[packed_top(k)] = (unsigned char)top;
+    const u32 r = k & (REC_CHUNK - 1);
+    unsigned char *rec = out + whole.rec(bp, i, k / REC_CHUNK, gq);
+    *reinterpret_cast<uint2 *>(rec + rec_lo(s, r)) = make_uint2(lo[0], lo[1]);
+    *reinterpret_cast<uint2 *>(rec + rec_lo(s, r + 2)) = make_uint2(lo[2], lo[3]);
+    *reinterpret_cast<u32 *>(rec + rec_mid(s, r)) = hi[0] | (hi[1] << 16);
+    *reinterpret_cast<u32 *>(rec + rec_mid(s, r + 2)) = hi[2] | (hi[3] << 16);
+    rec[rec_top(s, r)] = (unsigned char)top;
 }
 
 __global__ __launch_bounds__(EW_THREADS) void fill_u32_kernel(u32 *p, u32 v, u32 n) {
@@ -451,12 +429,7 @@ __global__ __launch_bounds__(EW_THREADS) void fill_u32_kernel(u32 *p, u32 v, u32
     if (i < n) p[i] = v;
 }
 
-// the fp64 multiply-accumulate kernels by weight store, FULL left open
-template <bool FULL> constexpr auto sym_packed = diag_mac_sym_kernel<MM_TB, true, FULL>;
-template <bool FULL> constexpr auto sym_plain = diag_mac_sym_kernel<MM_TB, false, FULL>;
-template <bool FULL> constexpr auto gen_packed = diag_mac_kernel<MM_TB, 2, true, FULL>;
-template <bool FULL> constexpr auto gen_plain = diag_mac_kernel<MM_TB, 2, false, FULL>;
-
+// Primes of 50 bits and more: 128-bit lazy sums, flushed after as many products as fit one for the largest modulus.
 __global__ __launch_bounds__(MM_THREADS) void diag_mac_int_kernel(const u64 *__restrict__ bank,
                                                                   const u64 *__restrict__ w, u64 *__restrict__ acc,
                                                                   const ModConst *__restrict__ mods, LimbIds limbs,
@@ -508,7 +481,7 @@ __global__ __launch_bounds__(MM_THREADS) void diag_mac_int_kernel(const u64 *__r
     }
 }
 
-// canonical residues -> the internal form diag_mac_kernel reads (rows [rows][N], limb = row % period)
+// canonical residues -> the internal form the multiply-accumulate kernels read (rows [rows][N], limb = row % period)
 __global__ __launch_bounds__(EW_THREADS) void to_weight_form_kernel(u64 *data, const ModConst *__restrict__ mods,
                                                                     const ModFp *__restrict__ modf, u32 period,
                                                                     u32 N) {
@@ -518,7 +491,7 @@ __global__ __launch_bounds__(EW_THREADS) void to_weight_form_kernel(u64 *data, c
     const size_t idx = (size_t)row * N + n;
     const u64 x = data[idx];
     if (modf[limb].ok) {
-        data[idx] = (u64)__double_as_longlong((double)x);   // exact: x < 2^50
+        data[idx] = balanced_bits(x, mods[limb].q);
     } else {
         const ModConst m = mods[limb];
         data[idx] = mont_mul(x, m.r2, m);
@@ -688,9 +661,9 @@ int ensure_full_store(ckks_weights *w) {
 // whole: the store of whole-limb records (general diagonals) instead of the store of half records (real ones)
 int ensure_packed_store(ckks_weights *w, bool whole) {
     const u32 N = w->params->N;
-    const size_t recs = (size_t)w->B_out * w->N2 * w->G * w->N1 * w->level;
-    if (!whole && !w->d_wp) CKKS_HIP(hipMalloc((void **)&w->d_wp, recs * packed_record_bytes(N)));
-    if (whole && !w->d_wpf) CKKS_HIP(hipMalloc((void **)&w->d_wpf, recs * 2 * packed_record_bytes(N)));
+    const size_t bytes = packed_shape(N, w->level, w->G * w->N1, w->B_out * w->N2, whole).bytes();
+    if (!whole && !w->d_wp) CKKS_HIP(hipMalloc((void **)&w->d_wp, bytes));
+    if (whole && !w->d_wpf) CKKS_HIP(hipMalloc((void **)&w->d_wpf, bytes));
     if (!w->d_stage) CKKS_HIP(hipMalloc((void **)&w->d_stage, (size_t)STAGE_DIAGS * w->level * N * sizeof(u64)));
     return CKKS_OK;
 }
@@ -699,14 +672,12 @@ int ensure_packed_store(ckks_weights *w, bool whole) {
 int widen_group(ckks_weights *w, u32 b, u32 g, hipStream_t stream) {
     int rc = ensure_packed_store(w, true);
     if (rc) return rc;
-    const u32 N = w->params->N;
-    const size_t rows = (size_t)w->N1 * w->level;            // the records of one (b, p, g)
+    const u32 N = w->params->N, GQ = w->G * w->N1;
     for (u32 p = 0; p < w->N2; ++p) {
-        const size_t first = ((((size_t)b * w->N2 + p) * w->G + g) * w->N1) * w->level;
-        hipLaunchKernelGGL(widen_half_kernel, dim3((N / 4 + EW_THREADS - 1) / EW_THREADS, (u32)rows), dim3(EW_THREADS),
-                           0, stream, w->d_wp + first * packed_record_bytes(N),
-                           w->d_wpf + first * 2 * packed_record_bytes(N), N);
-        CKKS_LAUNCH_CHECK("widen_half_kernel");
+        hipLaunchKernelGGL(widen_records_kernel, dim3((N / 4 + EW_THREADS - 1) / EW_THREADS, w->N1 * w->level),
+                           dim3(EW_THREADS), 0, stream, w->d_wp, w->d_wpf, packed_shape(N, w->level, GQ, w->B_out * w->N2, false),
+                           packed_shape(N, w->level, GQ, w->B_out * w->N2, true), N, b * w->N2 + p, g * w->N1);
+        CKKS_LAUNCH_CHECK("widen_records_kernel");
     }
     w->block_packed[(size_t)b * w->G + g] = 2;
     return CKKS_OK;
@@ -768,18 +739,21 @@ int ckks_weights_set_diagonals(ckks_weights_t *w, uint32_t first, uint32_t count
                 if (whole && w->block_packed[grp] == 1 && (rc = widen_group(w, b, g, (hipStream_t)stream))) return rc;
                 if ((rc = ensure_packed_store(w, whole))) return rc;
                 w->block_packed[grp] = whole ? 2 : 1;
-                const size_t recb = (whole ? 2 : 1) * packed_record_bytes(N);
                 unsigned char *store = whole ? w->d_wpf : w->d_wp;
-                const u32 cnt = whole ? N : N / 2;
-                for (u32 d = lo; d < hi; d += STAGE_DIAGS) {
-                    const u32 c = std::min(STAGE_DIAGS, hi - d);
+                const u32 cnt = whole ? N : N / 2, step0 = g * N1 - run * N1;      // gq of diagonal d: d + step0
+                const PackedShape ps = packed_shape(N, level, G * N1, w->B_out * w->N2, whole);
+                for (u32 d = lo; d < hi;) {
+                    // pieces end at even steps, so that the two steps of a record are packed together
+                    const u32 gq = d + step0, c = std::min(STAGE_DIAGS - (gq & 1), hi - d);
                     rc = expand_plain(P, level, d_coeffs + (size_t)(d - first) * N, c, w->d_stage, false,
                                       (hipStream_t)stream);
                     if (rc) return rc;
-                    hipLaunchKernelGGL(pack_half_kernel, dim3((cnt / 4 + EW_THREADS - 1) / EW_THREADS, c * level),
-                                       dim3(EW_THREADS), 0, (hipStream_t)stream, w->d_stage,
-                                       store + (size_t)d * level * recb, N, cnt);
-                    CKKS_LAUNCH_CHECK("pack_half_kernel");
+                    const u32 recs = ((gq + c + 1) >> 1) - (gq >> 1);
+                    hipLaunchKernelGGL(pack_records_kernel, dim3((cnt / 4 + EW_THREADS - 1) / EW_THREADS, recs * level),
+                                       dim3(EW_THREADS), 0, (hipStream_t)stream, w->d_stage, store, P->d_mod, ps, N, cnt,
+                                       run / G, gq, c);
+                    CKKS_LAUNCH_CHECK("pack_records_kernel");
+                    d += c;
                 }
             } else {
                 if ((rc = ensure_full_store(w))) return rc;
@@ -961,10 +935,13 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
                 const u64 *src = d_ct_x + (size_t)(g0 + r) * ctw;
                 u64 *dst = d_bank + ((size_t)(g0 + r) * N1 + q) * ctw;
                 if (baby_g[q] == 1) {
-                    CKKS_HIP(hipMemcpyAsync(dst, src, ctw * sizeof(u64), hipMemcpyDeviceToDevice, stream));
+                    hipLaunchKernelGGL(bank_entry_kernel, dim3(N / (2 * EW_THREADS), 2 * level), dim3(EW_THREADS), 0,
+                                       stream, src, dst, P->d_mod, level, N);
+                    CKKS_LAUNCH_CHECK("bank_entry_kernel");
                     continue;
                 }
                 SwitchItem &it = items[n_it++];
+                it.balanced = 1;
                 it.digits = d_digits + (size_t)r * dig_w;
                 it.c1 = src + (size_t)level * N;
                 it.c0 = src;
@@ -1013,12 +990,9 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
         for (u32 b0 = 0; n_fp && b0 < B;) {
             u32 b1 = b0 + 1;
             while (b1 < B && same_kinds(b0, b1)) ++b1;
-            const u32 bp_first = b0 * N2, bp_count = (b1 - b0) * N2;
-            const u64 *wp = w->d_w ? w->d_w + (size_t)bp_first * GQ * level * N : nullptr;
-            u64 *ap = d_acc + (size_t)bp_first * ctw;
+            const u32 bp0 = b0 * N2, bp1 = b1 * N2, tiles4 = (bp1 + TB - 1) / TB - bp0 / TB;
+            const double *bank = reinterpret_cast<const double *>(d_bank);
             const u32 runs = N / (4 * MM_THREADS), gen_runs = N / MM_THREADS / 2;
-            // full tiles of MM_TB pairs go to the unguarded kernels, a ragged last tile to the guarded ones
-            const u32 full_tiles = bp_count / MM_TB, rag = bp_count % MM_TB ? 1u : 0u;
             for (u32 g0 = 0; g0 < G;) {
                 const size_t grp = (size_t)b0 * G + g0;
                 u32 g1 = g0 + 1;
@@ -1026,31 +1000,18 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
                        w->block_packed[grp + (g1 - g0)] == w->block_packed[grp])
                     ++g1;
                 const u32 q0 = g0 * N1, q1 = g1 * N1, add = g0 ? 1u : 0u;
-                // 8 (b,p) pairs x 4 coefficients per thread with the next step's loads in flight measured best
-#define MM_LAUNCH(KERNEL, RUNS, WPTR)                                                                              \
-    do {                                                                                                           \
-        if (full_tiles)                                                                                            \
-            hipLaunchKernelGGL((KERNEL<true>), dim3(full_tiles, RUNS, n_fp), dim3(MM_THREADS), 0, stream, d_bank,  \
-                               WPTR, ap, P->d_modf, fp_limbs, level, N, GQ, bp_count, (RUNS) % 8 == 0 ? 1u : 0u,   \
-                               q0, q1, add, 0u);                                                                   \
-        if (rag)                                                                                                   \
-            hipLaunchKernelGGL((KERNEL<false>), dim3(1, RUNS, n_fp), dim3(MM_THREADS), 0, stream, d_bank, WPTR,    \
-                               ap, P->d_modf, fp_limbs, level, N, GQ, bp_count, (RUNS) % 8 == 0 ? 1u : 0u, q0, q1, \
-                               add, full_tiles);                                                                   \
-    } while (0)
-                if (w->block_packed[grp] == 1) {
-                    const u64 *pp = reinterpret_cast<const u64 *>(w->d_wp + (size_t)bp_first * GQ * level *
-                                                                                packed_record_bytes(N));
-                    MM_LAUNCH(sym_packed, runs, pp);
-                } else if (w->block_packed[grp] == 2) {
-                    const u64 *pp = reinterpret_cast<const u64 *>(w->d_wpf + (size_t)bp_first * GQ * level * 2 *
-                                                                                 packed_record_bytes(N));
-                    MM_LAUNCH(gen_packed, gen_runs, pp);
-                } else if (w->block_real[grp] && N >= 4 * MM_THREADS) {
-                    MM_LAUNCH(sym_plain, runs, wp);
-                } else {   // 8 accumulators x 2 coefficients per thread (16-byte loads)
-                    MM_LAUNCH(gen_plain, gen_runs, wp);
-                }
+#define MM_LAUNCH(SYM, PACKED, RUNS, WPTR)                                                                         \
+    hipLaunchKernelGGL((diag_mac_kernel<SYM, PACKED>), dim3(tiles4, RUNS, n_fp), dim3(MM_THREADS), 0, stream,      \
+                       bank, WPTR, d_acc, P->d_modf, fp_limbs, level, N, GQ, BP, (RUNS) % 8 == 0 ? 1u : 0u, q0,    \
+                       q1, add, bp0, bp1)
+                if (w->block_packed[grp] == 1)
+                    MM_LAUNCH(true, true, runs, w->d_wp);
+                else if (w->block_packed[grp] == 2)
+                    MM_LAUNCH(false, true, gen_runs, w->d_wpf);
+                else if (w->block_real[grp] && N >= 4 * MM_THREADS)
+                    MM_LAUNCH(true, false, runs, w->d_w);
+                else
+                    MM_LAUNCH(false, false, gen_runs, w->d_w);
 #undef MM_LAUNCH
                 g0 = g1;
             }
@@ -1085,6 +1046,7 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
                 items[r].dst = d_ct_y + (size_t)r * ctw;
                 items[r].galois_elt = conj_key->galois_elt;
                 items[r].accumulate = 0;
+                items[r].balanced = 0;
             }
             rc = switch_batch(P, level, items, na, d_work, stream);
             if (rc) return rc;
@@ -1202,6 +1164,7 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
                 items[r].dst = d_ct_y + (size_t)(b0 + r) * ctw;   // distinct b within a batch: no two items share dst
                 items[r].galois_elt = giant_g[p];
                 items[r].accumulate = 1;
+                items[r].balanced = 0;
             }
             rc = switch_batch(P, level, items, nb, d_work, stream);
             if (rc) return rc;
@@ -1225,6 +1188,7 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
                 items[r].dst = d_acc + (size_t)r * ctw;
                 items[r].galois_elt = conj_key->galois_elt;
                 items[r].accumulate = 0;
+                items[r].balanced = 0;
             }
             rc = switch_batch(P, level, items, nb, d_work, stream);
             if (rc) return rc;

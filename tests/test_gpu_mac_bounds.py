@@ -1,0 +1,51 @@
+"""The projection's multiply-accumulate at the ends of its operands' range: every bank residue and every weight of the first
+limb is +-(q-1)/2 with q the largest 50-bit prime of the ring, in the sign patterns that drive the running sums to their
+bounds, over step counts at and off the records of four steps and the folds after eight, pair counts at and off the
+tiles of four, real (half records) and general (whole records) diagonals.  With one column per ciphertext there are no
+rotations, so the expected residues follow from integers."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _dev(x):
+    return torch.tensor(x, dtype=torch.int64, device="cuda")
+
+
+@pytest.mark.parametrize("general", [False, True])
+@pytest.mark.parametrize("G,B_out", [(1, 1), (3, 4), (4, 5), (7, 3), (8, 8), (9, 2), (16, 4), (19, 7), (33, 1)])
+def test_sums_at_the_bounds(G, B_out, general):
+    from paper_2604_09975_amd import binding as B
+    logN, N = 12, 4096
+    q, p = B.ckks_find_primes(50, logN, 2), B.ckks_find_primes(60, logN, 1)
+    P = B.ckks_params_create(logN, q, p, 2)
+    h = (q[0] - 1) // 2
+    sign_x = [[1, -1, 1 if g % 2 else -1][(g // 8) % 3] if G > 8 else 1 for g in range(G)]
+    sign_w = [[(1, -1)[(b >> (g % 3)) & 1] for g in range(G)] for b in range(B_out)]
+    x = torch.empty((G, 2, 2, N), dtype=torch.int64, device="cuda")
+    for g in range(G):
+        for c in range(2):
+            for i in range(2):
+                v = (sign_x[g] * h * (1 if c == 0 else -1)) % q[i]
+                x[g, c, i] = v
+    # real: the constant polynomial +-h.  General: t X^(N/2), whose transform is t I on the first half and -t I on the
+    # second, I = psi^(N/2): with t = h / I the residues of limb 0 are +h and -h.
+    I = [pow(B.ckks_params_root(P, i), N // 2, q[i]) for i in range(2)]
+    w = B.ckks_weights_create(P, 2, 16, 1, G, B_out, 1)
+    coef = torch.zeros((B_out, G, N), dtype=torch.int64, device="cuda")
+    t = h * pow(I[0], -1, q[0]) % q[0]
+    for b in range(B_out):
+        for g in range(G):
+            coef[b, g, N // 2 if general else 0] = sign_w[b][g] * (t if general else h)
+    B.ckks_weights_set_diagonals(w, 0, coef.reshape(-1, N))
+    y, cnt = B.ckks_ctpt_matmul(P, w, x, [], [])
+    assert cnt.key_switches == 0 and cnt.ptmuls == G * B_out
+    for b in range(B_out):
+        for c in range(2):
+            for i in range(2):
+                for half in range(2):
+                    k = t * I[i] * (1, -1)[half] if general else h
+                    want = sum(sign_x[g] * h * (1 if c == 0 else -1) * sign_w[b][g] * k for g in range(G)) % q[i]
+                    row = y[b, c, i, half * (N // 2):(half + 1) * (N // 2)]
+                    assert bool((row == want).all()), (b, c, i, half)
