@@ -112,7 +112,7 @@ int ckks_galois_elt(const ckks_params_t *params, int32_t step, uint64_t *galois_
 /* Evaluation key for one Galois element (the "Galois keys" of Sec. 2.1).
  * d_key: [dnum][2][L+K][N], NTT domain, canonical residues; component 0 = b_j,
  * 1 = a_j with b_j = -a_j*s + e_j + P*T_j*sigma_g(s).  ckks_galois_key_load COPIES:
- * the library keeps its own copy in its internal (Montgomery) form, 96 MiB at
+ * the library keeps its own copy in its internal form, 96 MiB at
  * N = 2^16 with 24 + 8 primes, and d_key may be freed once `stream` has drained.
  * ckks_galois_key_adopt BORROWS: d_key is rewritten in place into the internal
  * form (it is no longer a canonical key afterwards) and the handle points at it; the

@@ -95,11 +95,11 @@ struct ckks_params {
     double *d_twf_inv = nullptr;       // [W][N]
     // ModDown tables (independent of the level)
     ckks::u64 *d_dn_inv = nullptr;     // [K]: (P/p_k)^-1 mod p_k
-    ckks::u64 *d_dn_mat = nullptr;     // [K][L]: P/p_k mod q_i
-    double *d_dn_matf = nullptr;       // [L][K padded][3][2]: (2^(20a) * P/p_k) mod q_i as two 25-bit halves (doubles)
+    // (P/p_k) P^-1 = p_k^-1 mod q_i: the ModDown conversion with the P^-1 that ends it
+    ckks::u64 *d_dn_mat = nullptr;     // [K][L]
+    double *d_dn_matf = nullptr;       // [L][K padded][3][2]: the same times 2^(20a) as two 25-bit halves (doubles)
     bool dn_fp = false;                // every special prime below 2^60: the fp64 ModDown conversion applies
     ckks::u64 *d_pinv = nullptr;       // [L]: P^-1 mod q_i
-    double *d_pinvf = nullptr;         // [L]: the same as plain doubles (exact for primes below 2^53)
     ckks::u64 *d_qlinv = nullptr;      // [L][L]: q_l^-1 mod q_i (rescale), row l
     std::map<ckks::u32, ckks::LevelTables> levels;
     // complex-slot encode / decode (built on first use): exp(-2*pi*i*e/N), e < N/2; exp(-i*pi*k/N), k < N; and the
@@ -124,7 +124,7 @@ struct ckks_params {
 struct ckks_gkey {
     const ckks_params *params = nullptr;
     ckks::u64 galois_elt = 0;
-    ckks::u64 *d_key = nullptr;        // [dnum][2][L+K][N], Montgomery form
+    ckks::u64 *d_key = nullptr;        // [dnum][2][L+K][N] in the form of key_form_kernel
     bool owned = true;                 // false: the caller's buffer, converted in place (ckks_galois_key_adopt)
 };
 
@@ -165,7 +165,7 @@ struct SwitchItem {
                          // limbs are NOT filled: they equal the source's own rows and are read from c1
     const u64 *c1;       // [level][N] the decomposed polynomial itself (NTT domain); must outlive the switch
     const u64 *c0;       // [level][N] source c0
-    const u64 *key;      // Montgomery-form key
+    const u64 *key;      // key in the library's form
     u64 *dst;            // [2][level][N]
     u64 galois_elt;
     u32 accumulate;      // add into dst instead of overwriting

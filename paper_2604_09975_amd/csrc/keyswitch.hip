@@ -16,6 +16,7 @@
 
 #include "ckks_internal.h"
 #include "common_kernels.h"
+#include "mac_device.h"
 #include "ntt_device.h"
 
 namespace ckks {
@@ -23,11 +24,47 @@ namespace ckks {
 constexpr u32 KS_THREADS = EW_THREADS;
 constexpr u32 DN_CHUNK = 24;   // target limbs per workgroup in ModDown (2, 3, 4, 6, 12, 24 measured: fewer, larger groups are faster)
 
-__device__ __forceinline__ u32 galois_index(u32 k, u64 g, u32 logN) {
+__device__ __forceinline__ u32 galois_index(u32 k, u32 g, u32 logN) {
     // entry k holds the value at psi^(2*bitrev(k)+1); sigma_g reads the value at that exponent times g
     u32 e = 2u * (__brev(k) >> (32 - logN)) + 1u;
-    u32 e2 = (u32)(((u64)e * g) & ((2ull << logN) - 1));
+    u32 e2 = (e * g) & ((2u << logN) - 1u);
     return __brev((e2 - 1u) >> 1) >> (32 - logN);
+}
+
+// Entries k, k + 1 (k even) of sigma_g of a row, from one 16-byte load: their exponents differ by N, and g is odd, so
+// their sources do too: they are entries kp and kp ^ 1, kp = galois_index(k).  load_pair gives them in memory order,
+// turned() in the order asked for; the kernels turn a pair where they use it (turned as it is loaded, every load is waited
+// for on its own: passb_final_kernel 602 us per 24 switches against 525 turned where used and 537 with two 8-byte loads).
+typedef u64 pair_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ pair_t load_pair(const u64 *__restrict__ row, u32 kp) {
+    return *reinterpret_cast<const pair_t *>(row + (kp & ~1u));
+}
+__device__ __forceinline__ pair_t turned(pair_t v, bool turn) { return turn ? pair_t{v[1], v[0]} : v; }
+
+// Evaluation keys as the library holds them: rows of ciphertext limbs carry the factor P^-1 of ModDown (the base
+// conversion P -> q_i carries it too, so that no kernel after the key product multiplies by it), on primes below 2^50 as
+// balanced doubles, on others in Montgomery form; rows of special limbs are in Montgomery form.  In place if in == out.
+// rows [rows][N], row r modulo limb r % W; four residues per thread (one per thread leaves too few bytes in flight: a
+// 25 MB key took 34 us longer).  grid: x = 1024 residues (N >= 1024), y = row
+__global__ __launch_bounds__(EW_THREADS) void key_form_kernel(const u64 *in, u64 *out,
+                                                              const ModConst *__restrict__ mods,
+                                                              const u64 *__restrict__ pinv, u32 L, u32 W, u32 N) {
+    const u32 limb = blockIdx.y % W;
+    const ModConst m = mods[limb];
+    const u64 f = limb < L ? pinv[limb] : 0;
+    const size_t idx = (size_t)blockIdx.y * N + (blockIdx.x * EW_THREADS + threadIdx.x) * 2;
+    pair_t v[2];
+#pragma unroll
+    for (u32 h = 0; h < 2; ++h) v[h] = *reinterpret_cast<const pair_t *>(in + idx + h * (N / 2));
+#pragma unroll
+    for (u32 h = 0; h < 2; ++h) {
+#pragma unroll
+        for (u32 e = 0; e < 2; ++e) {
+            const u64 x = limb < L ? mont_mul(v[h][e], f, m) : v[h][e];
+            v[h][e] = limb < L && (m.q >> 50) == 0 ? balanced_bits(x, m.q) : mont_mul(x, m.r2, m);
+        }
+        *reinterpret_cast<pair_t *>(out + idx + h * (N / 2)) = v[h];
+    }
 }
 
 struct PtrPack {
@@ -365,12 +402,16 @@ __global__ __launch_bounds__(KS_THREADS) void inner_product_kernel(ItemPack pack
     const u32 Wl = level + K, Wt = L + K;
     const u32 gl = t < level ? t : L + (t - level);
     const u64 *key = pack.it[first].key;
-    const u32 kp = galois_index(k, pack.it[first].galois_elt, logN);
+    const u32 kp = galois_index(k, (u32)pack.it[first].galois_elt, logN);
+    const ModConst m = mods[gl];
+    const bool fp = t < level && (m.q >> 50) == 0;               // keys of these rows are balanced doubles
+    const double q = (double)m.q, uq = 1.0 / q;
     u128 a0[KEY_GROUP], a1[KEY_GROUP];
+    MacSum f0[KEY_GROUP], f1[KEY_GROUP];
 #pragma unroll
     for (u32 r = 0; r < KEY_GROUP; ++r) {
-        a0[r] = {0, 0};
-        a1[r] = {0, 0};
+        a0[r] = a1[r] = {0, 0};
+        f0[r] = f1[r] = MacSum{MAC_H0, 0.0};
     }
     for (u32 j = 0; j < beta; ++j) {
         const u64 k0 = key[(((size_t)j * 2 + 0) * Wt + gl) * N + k];
@@ -381,34 +422,53 @@ __global__ __launch_bounds__(KS_THREADS) void inner_product_kernel(ItemPack pack
                 const SwitchItem &it = pack.it[first + r];
                 const u64 d = (t < level && t / alpha == j) ? it.c1[(size_t)t * N + kp]
                                                             : it.digits[((size_t)j * Wl + t) * N + kp];
-                mac(a0[r], d, k0);
-                mac(a1[r], d, k1);
+                if (fp) {
+                    const double x = canonical_double(d);
+                    f0[r].mac(x, __longlong_as_double((long long)k0));
+                    f1[r].mac(x, __longlong_as_double((long long)k1));
+                    if ((j & 3) == 3) {
+                        f0[r].fold(q, uq);
+                        f1[r].fold(q, uq);
+                    }
+                } else {
+                    mac(a0[r], d, k0);
+                    mac(a1[r], d, k1);
+                }
             }
         }
     }
-    const ModConst m = mods[gl];
 #pragma unroll
     for (u32 r = 0; r < KEY_GROUP; ++r) {
         if (r < cnt) {
             u64 *u0 = u + (((size_t)(first + r) * 2 + 0) * Wl + t) * N + k;
             u64 *u1 = u + (((size_t)(first + r) * 2 + 1) * Wl + t) * N + k;
-            *u0 = redc_wide(a0[r], m);
-            *u1 = redc_wide(a1[r], m);
+            if (fp) {
+                f0[r].fold(q, uq);
+                f1[r].fold(q, uq);
+                *u0 = f0[r].canonical(q, uq);
+                *u1 = f1[r].canonical(q, uq);
+            } else {
+                *u0 = redc_wide(a0[r], m);
+                *u1 = redc_wide(a1[r], m);
+            }
         }
     }
 }
 
 // Inner products of several rotations summed in the extended basis (the merged giant step): a thread owns one
 // coefficient of one limb for MR ciphertexts, so that a key residue, read once, serves MR multiply-accumulates.
-// The 128-bit sums are folded before more than 16 products (each below 2^124) have been added.
+// Rows of ciphertext primes below 2^50 (FP) sum in doubles, folded after each rotation's products; the others keep 128-bit
+// sums, folded before more than 16 products (each below 2^124) have been added.  grid.y indexes `rows`, the rows of the
+// extended basis this launch covers.
 constexpr u32 MR = 3;
+template <bool FP>
 __global__ __launch_bounds__(KS_THREADS) void merged_ip_kernel(MergedRot rots, const u64 *__restrict__ digits,
                                                                size_t dig_w, const u64 *__restrict__ c0_base,
                                                                size_t c0_stride_r, u64 *__restrict__ dst_base,
                                                                size_t dst_stride, u64 *__restrict__ u,
                                                                const ModConst *__restrict__ mods, u32 n, u32 level,
                                                                u32 K, u32 L, u32 beta, u32 alpha, u32 logN,
-                                                               u32 accumulate, u32 groups) {
+                                                               u32 accumulate, u32 groups, LimbIds rows) {
     const u32 N = 1u << logN;
     // grid x = ((chunk of 8 coefficient runs) * groups + group of MR ciphertexts) * 8 + run within the chunk: the
     // groups of ciphertexts, which read the same key rows, follow each other at a distance of 8 workgroups, i.e. on
@@ -416,23 +476,27 @@ __global__ __launch_bounds__(KS_THREADS) void merged_ip_kernel(MergedRot rots, c
     const u32 chunk = N / KS_THREADS < 8 ? N / KS_THREADS : 8;   // a power of two
     const u32 xg = blockIdx.x / chunk;
     const u32 k = ((xg / groups) * chunk + (blockIdx.x & (chunk - 1))) * KS_THREADS + threadIdx.x;
-    const u32 t = blockIdx.y;
+    const u32 t = rows.id[blockIdx.y];
     const u32 r0 = (xg % groups) * MR;
     const u32 Wl = level + K, Wt = L + K;
     const u32 gl = t < level ? t : L + (t - level);
     const u32 own = t < level ? t / alpha : ~0u;                 // the digit whose own limb t is: read from c1
     const ModConst m = mods[gl];
+    const double q = (double)m.q, uq = 1.0 / q;
     u128 a0[MR], a1[MR];
+    MacSum f0[MR], f1[MR];
+    double csf[MR];
     u64 s0[MR], s1[MR], cs[MR];
 #pragma unroll
     for (u32 r = 0; r < MR; ++r) {
-        a0[r] = {0, 0};
-        a1[r] = {0, 0};
+        a0[r] = a1[r] = {0, 0};
+        f0[r] = f1[r] = MacSum{MAC_H0, 0.0};
         s0[r] = s1[r] = cs[r] = 0;
+        csf[r] = 0.0;
     }
     u32 terms = 0;
     for (u32 i = 0; i < rots.n_rot; ++i) {
-        const u32 kp = galois_index(k, rots.galois_elt[i], logN);
+        const u32 kp = galois_index(k, (u32)rots.galois_elt[i], logN);
         const u64 *key = rots.key[i];
         // the loads of up to MAX_BETA digits are issued before their products
         for (u32 j0 = 0; j0 < beta; j0 += MAX_BETA) {
@@ -458,28 +522,46 @@ __global__ __launch_bounds__(KS_THREADS) void merged_ip_kernel(MergedRot rots, c
 #pragma unroll
                     for (u32 r = 0; r < MR; ++r)
                         if (r0 + r < n) {
-                            mac(a0[r], d[jj][r], k0[jj]);
-                            mac(a1[r], d[jj][r], k1[jj]);
+                            if (FP) {
+                                const double x = canonical_double(d[jj][r]);
+                                f0[r].mac(x, __longlong_as_double((long long)k0[jj]));
+                                f1[r].mac(x, __longlong_as_double((long long)k1[jj]));
+                            } else {
+                                mac(a0[r], d[jj][r], k0[jj]);
+                                mac(a1[r], d[jj][r], k1[jj]);
+                            }
                         }
                 }
+            if (FP) {                                            // at most MAX_BETA = 4 products since the last fold
+#pragma unroll
+                for (u32 r = 0; r < MR; ++r) {
+                    f0[r].fold(q, uq);
+                    f1[r].fold(q, uq);
+                }
+            }
         }
         if (t < level) {
 #pragma unroll
             for (u32 r = 0; r < MR; ++r)
-                if (r0 + r < n)
-                    cs[r] = add_mod(cs[r], c0_base[(size_t)(r0 + r) * c0_stride_r + rots.c0_off[i] + (size_t)t * N + kp],
-                                    m.q);
+                if (r0 + r < n) {
+                    const u64 c = c0_base[(size_t)(r0 + r) * c0_stride_r + rots.c0_off[i] + (size_t)t * N + kp];
+                    if (FP)
+                        csf[r] += canonical_double(c);           // up to MERGE_GROUP = 8 residues: below 2^53
+                    else
+                        cs[r] = add_mod(cs[r], c, m.q);
+                }
         }
-        terms += beta;
-        if (terms + beta > 16 || i + 1 == rots.n_rot) {
+        if (!FP) {
+            terms += beta;
+            if (terms + beta > 16 || i + 1 == rots.n_rot) {
 #pragma unroll
-            for (u32 r = 0; r < MR; ++r) {
-                s0[r] = add_mod(s0[r], redc_wide(a0[r], m), m.q);
-                s1[r] = add_mod(s1[r], redc_wide(a1[r], m), m.q);
-                a0[r] = {0, 0};
-                a1[r] = {0, 0};
+                for (u32 r = 0; r < MR; ++r) {
+                    s0[r] = add_mod(s0[r], redc_wide(a0[r], m), m.q);
+                    s1[r] = add_mod(s1[r], redc_wide(a1[r], m), m.q);
+                    a0[r] = a1[r] = {0, 0};
+                }
+                terms = 0;
             }
-            terms = 0;
         }
     }
 #pragma unroll
@@ -487,7 +569,12 @@ __global__ __launch_bounds__(KS_THREADS) void merged_ip_kernel(MergedRot rots, c
         if (r0 + r < n) {
             u64 *u0 = u + (((size_t)(r0 + r) * 2 + 0) * Wl + t) * N + k;
             u64 *u1 = u + (((size_t)(r0 + r) * 2 + 1) * Wl + t) * N + k;
-            u64 v0 = s0[r], v1 = s1[r];
+            u64 v0 = s0[r], v1 = s1[r], c = cs[r];
+            if (FP) {
+                v0 = f0[r].canonical(q, uq);
+                v1 = f1[r].canonical(q, uq);
+                c = MacSum{0.0, csf[r]}.canonical(q, uq);
+            }
             if (accumulate) {
                 v0 = add_mod(v0, *u0, m.q);
                 v1 = add_mod(v1, *u1, m.q);
@@ -496,7 +583,7 @@ __global__ __launch_bounds__(KS_THREADS) void merged_ip_kernel(MergedRot rots, c
             *u1 = v1;
             if (t < level) {
                 u64 *d = dst_base + (size_t)(r0 + r) * dst_stride + (size_t)t * N + k;
-                *d = add_mod(*d, cs[r], m.q);
+                *d = add_mod(*d, c, m.q);
             }
         }
     }
@@ -632,8 +719,7 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
                                                           const u64 *__restrict__ ninv_dn,
                                                           const double *__restrict__ twf_fwd,
                                                           const double *__restrict__ dn_matf, u32 level, u32 K, u32 L,
-                                                          u32 ystride, u32 yoff, const u64 *__restrict__ t_rows,
-                                                          const double *__restrict__ pinvf) {
+                                                          u32 ystride, u32 yoff, const u64 *__restrict__ t_rows) {
     constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, COLS = MID_TILE >> LOGR, PER = COLS / 32;
     static_assert(MID_TG == 8 && KM <= 8, "the correction tiles reuse the 8 rows of special-limb tiles");
     __shared__ u64 ylds[8 * MID_TILE];
@@ -685,7 +771,7 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
             const double wl = mid_convert<KM>(yp, dn_matf + (size_t)il * (KM * 6), ml.q, ml.u);
             const u32 el = e * 256 + tid;
             const double t = fl.in(t_rows[(size_t)pc * N + el / COLS * 4096 + c0 + el % COLS]);
-            double r = t - fl.mul(wl, pinvf[il]);
+            double r = t - wl;
             fl.norm(r);
             if (r < 0) r += ml.q;                                   // r in [0, q_last)
             r += hq;
@@ -713,7 +799,7 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
                     double hi_ = hq, ri = rpe;
                     fi.norm(hi_);                                   // floor(q_last / 2) mod q_i
                     fi.norm(ri);                                    // r' mod q_i
-                    v = fi.mul(v, pinvf[i]) + (ri - hi_);           // |.| < 2q: the forward round normalises
+                    v += ri - hi_;                                  // |.| < 2q: the forward round normalises
                 }
                 wlds[t * MID_TILE + e * 256 + tid] = (u64)__double_as_longlong(v);
             }
@@ -744,14 +830,13 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
 __global__ __launch_bounds__(KS_THREADS) void rescale_last_row_kernel(PtrPack z, const u64 *__restrict__ u,
                                                                       u64 *__restrict__ t,
                                                                       const ModConst *__restrict__ mods,
-                                                                      const u64 *__restrict__ pinv, u32 level, u32 K,
-                                                                      u32 N) {
+                                                                      u32 level, u32 K, u32 N) {
     const u32 k = blockIdx.x * KS_THREADS + threadIdx.x;
     const u32 pc = blockIdx.y, r = pc >> 1, comp = pc & 1, i = level - 1;
     const ModConst m = mods[i];
     const u64 zz = z.p[r][((size_t)comp * level + i) * N + k];
     const u64 uu = u[((size_t)pc * (level + K) + i) * N + k];
-    t[(size_t)pc * N + k] = add_mod(zz, mont_mul(uu, pinv[i], m), m.q);
+    t[(size_t)pc * N + k] = add_mod(zz, uu, m.q);
 }
 
 // out[r][comp][i][k] = (z[r][comp][i][k] + u P^-1 - NTT(w')[i][k]) q_{l-1}^-1 for the l-1 remaining limbs
@@ -759,7 +844,6 @@ __global__ __launch_bounds__(KS_THREADS) void moddown_rescale_final_kernel(PtrPa
                                                                            const u64 *__restrict__ u,
                                                                            const u64 *__restrict__ w,
                                                                            const ModConst *__restrict__ mods,
-                                                                           const u64 *__restrict__ pinv,
                                                                            const u64 *__restrict__ qlinv, u32 level,
                                                                            u32 K, u32 N) {
     typedef u64 vec_t __attribute__((ext_vector_type(2)));
@@ -772,7 +856,7 @@ __global__ __launch_bounds__(KS_THREADS) void moddown_rescale_final_kernel(PtrPa
     vec_t o;
 #pragma unroll
     for (u32 e = 0; e < 2; ++e) {
-        const u64 y = add_mod(zz[e], mont_mul(uu[e], pinv[i], m), m.q);
+        const u64 y = add_mod(zz[e], uu[e], m.q);
         o[e] = mont_mul(sub_mod(y, ww[e], m.q), qlinv[i], m);
     }
     *reinterpret_cast<vec_t *>(out.it[r].dst + ((size_t)comp * (level - 1) + i) * N + k) = o;
@@ -807,7 +891,7 @@ static void launch_moddown_mid(const ckks_params *p, const u64 *y, u64 *w, u32 n
                                hipStream_t stream, const u64 *t_rows = nullptr) {
     hipLaunchKernelGGL(t_rows ? moddown_mid_for<true>(p) : moddown_mid_for<false>(p), dim3(p->N / MID_TILE, n * 2),
                        dim3(256), 0, stream, y, w, p->d_mod, p->d_modf, p->d_modf_dn, p->d_tws_inv, p->d_twf_inv,
-                       p->d_ninvs_dn, p->d_twf_fwd, p->d_dn_matf, level, p->K, p->L, ystride, yoff, t_rows, p->d_pinvf);
+                       p->d_ninvs_dn, p->d_twf_fwd, p->d_dn_matf, level, p->K, p->L, ystride, yoff, t_rows);
 }
 
 // base conversion P -> q_i of n*2 polynomials; the rows of polynomial pc start at row pc * ystride + yoff of y
@@ -830,8 +914,7 @@ static void launch_moddown_conv(const ckks_params *p, const u64 *y, u64 *w, u32 
 // dst[comp][i][k] (+)= (u_{q_i} - NTT(w_i)) * P^-1  (+ sigma_g(c0)[i][k] for comp 0)
 __global__ __launch_bounds__(KS_THREADS) void moddown_final_kernel(ItemPack pack, const u64 *__restrict__ u,
                                                                    const u64 *__restrict__ w,
-                                                                   const ModConst *__restrict__ mods,
-                                                                   const u64 *__restrict__ pinv, u32 level, u32 K,
+                                                                   const ModConst *__restrict__ mods, u32 level, u32 K,
                                                                    u32 logN) {
     const u32 N = 1u << logN;
     const u32 k = blockIdx.x * KS_THREADS + threadIdx.x;
@@ -841,11 +924,11 @@ __global__ __launch_bounds__(KS_THREADS) void moddown_final_kernel(ItemPack pack
     const ModConst m = mods[i];
     const u64 uq = u[(((size_t)r * 2 + comp) * Wl + i) * N + k];
     const u64 wq = w[(((size_t)r * 2 + comp) * level + i) * N + k];
-    u64 v = mont_mul(sub_mod(uq, wq, m.q), pinv[i], m);
-    if (comp == 0 && it.c0) v = add_mod(v, it.c0[(size_t)i * N + galois_index(k, it.galois_elt, logN)], m.q);
+    u64 v = sub_mod(uq, wq, m.q);
+    if (comp == 0 && it.c0) v = add_mod(v, it.c0[(size_t)i * N + galois_index(k, (u32)it.galois_elt, logN)], m.q);
     u64 *dst = it.dst + ((size_t)comp * level + i) * N + k;
     if (it.accumulate) v = add_mod(v, *dst, m.q);
-    if (it.balanced && (m.q >> 50) == 0) v = (u64)__double_as_longlong((double)(int64_t)(v > m.q / 2 ? v - m.q : v));
+    if (it.balanced && (m.q >> 50) == 0) v = balanced_bits(v, m.q);
     *dst = v;
 }
 
@@ -857,9 +940,8 @@ __global__ __launch_bounds__(KS_THREADS) void moddown_final_kernel(ItemPack pack
 // KEY_NT: key rows are read with non-temporal loads.  Right when every item has a key of its own (the rows are used
 // once and would only push the digit rows, which every item re-reads, out of L2); wrong when neighbouring items share
 // a key, where it is the cached line that lets the second and third reader skip HBM.
-typedef u64 key_vec_t __attribute__((ext_vector_type(2)));
 template <bool NT>
-__device__ __forceinline__ key_vec_t load_key(const key_vec_t *p) {
+__device__ __forceinline__ pair_t load_key(const pair_t *p) {
     return NT ? __builtin_nontemporal_load(p) : *p;
 }
 
@@ -879,38 +961,39 @@ __global__ __launch_bounds__(NTT_THREADS) void ip_intt_kernel(ItemPack pack, u64
     const ModConst m = mods[gl];
     const u64 *dig = it.digits + (size_t)t * N;
     const u64 *key = it.key + ((size_t)comp * Wt + gl) * N;
-    const u64 g = it.galois_elt;
+    const u32 g = (u32)it.galois_elt;
     u64 *out = y + (((size_t)r * 2 + comp) * K + k) * N;
     auto store = [&](u32 idx, u64 v) { out[idx] = v; };
-    // inner product into LDS on pairs of adjacent residues (16-byte key loads), two pairs at a time so that
+    // inner product into LDS on pairs of adjacent residues (16-byte loads), two pairs at a time so that
     // their loads are in flight together
-    typedef u64 vec_t __attribute__((ext_vector_type(2)));
     const u32 tid = threadIdx.x, base = blockIdx.x << 12;
     constexpr u32 EPP = EPI / 2;
     for (u32 i0 = 0; i0 < 8; i0 += EPP) {
-        u64 dv[EPP][2][MAX_BETA];
-        vec_t kv[EPP][MAX_BETA];
+        pair_t dv[EPP][MAX_BETA], kv[EPP][MAX_BETA];
+        bool turn[EPP];
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
-            const u32 idx = base + 2 * (tid + 256 * (i0 + e));
-            const u32 kp0 = galois_index(idx, g, logN), kp1 = galois_index(idx + 1, g, logN);
+            const u32 idx = base + 2 * (tid + 256 * (i0 + e)), kp = galois_index(idx, g, logN);
+            turn[e] = kp & 1;
 #pragma unroll
             for (u32 j = 0; j < MAX_BETA; ++j)
                 if (j < beta) {
-                    dv[e][0][j] = dig[(size_t)j * Wl * N + kp0];
-                    dv[e][1][j] = dig[(size_t)j * Wl * N + kp1];
-                    kv[e][j] = load_key<KEY_NT>(reinterpret_cast<const vec_t *>(key + (size_t)j * 2 * Wt * N + idx));
+                    dv[e][j] = load_pair(dig + (size_t)j * Wl * N, kp);
+                    kv[e][j] = load_key<KEY_NT>(reinterpret_cast<const pair_t *>(key + (size_t)j * 2 * Wt * N + idx));
                 }
         }
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
             const u32 loc = 2 * (tid + 256 * (i0 + e));
 #pragma unroll
+            for (u32 j = 0; j < MAX_BETA; ++j)
+                if (j < beta) dv[e][j] = turned(dv[e][j], turn[e]);
+#pragma unroll
             for (u32 z = 0; z < 2; ++z) {
                 u128 acc = {0, 0};
 #pragma unroll
                 for (u32 j = 0; j < MAX_BETA; ++j)
-                    if (j < beta) mac(acc, dv[e][z][j], kv[e][j][z]);
+                    if (j < beta) mac(acc, dv[e][j][z], kv[e][j][z]);
                 lds[lds_pad(loc + z)] = redc_wide(acc, m);
             }
         }
@@ -924,7 +1007,8 @@ __global__ __launch_bounds__(NTT_THREADS) void ip_intt_kernel(ItemPack pack, u64
 }
 
 // Last pass of the forward transform of w fused with the rest of the key switch on limb q_i:
-//   dst[comp][i] (+)= ( sum_j sigma_g(d_j)[q_i] * key_j[comp][q_i] - NTT(w)[i] ) * P^-1  (+ sigma_g(c0)[i] if comp = 0)
+//   dst[comp][i] (+)= sum_j sigma_g(d_j)[q_i] * key_j[comp][q_i] - NTT(w)[i]  (+ sigma_g(c0)[i] if comp = 0)
+// (the keys and w carry the P^-1 of ModDown).
 // grid: x = tile of 4096, y = ((i*n + r)*2 + comp), neighbours share digit and key lines in L2 as above.
 template <bool KEY_NT>
 __global__ __launch_bounds__(NTT_THREADS) void passb_final_kernel(ItemPack pack, const u64 *__restrict__ w,
@@ -932,8 +1016,7 @@ __global__ __launch_bounds__(NTT_THREADS) void passb_final_kernel(ItemPack pack,
                                                                   const ModFp *__restrict__ modf,
                                                                   const u64 *__restrict__ tw_fwd,
                                                                   const double *__restrict__ twf_fwd,
-                                                                  const u64 *__restrict__ ninv,
-                                                                  const u64 *__restrict__ pinv, u32 n, u32 level,
+                                                                  const u64 *__restrict__ ninv, u32 n, u32 level,
                                                                   u32 K, u32 L, u32 beta, u32 alpha, u32 logN) {
     __shared__ u64 lds[FAST_LDS_WORDS];
     const u32 N = 1u << logN;
@@ -950,8 +1033,7 @@ __global__ __launch_bounds__(NTT_THREADS) void passb_final_kernel(ItemPack pack,
     const u64 *key = it.key + ((size_t)comp * Wt + i) * N;
     const u64 *c0 = it.c0 + (size_t)i * N;
     u64 *dst = it.dst + ((size_t)comp * level + i) * N;
-    const u64 g = it.galois_elt, pi = pinv[i];
-    const u32 accumulate = it.accumulate;
+    const u32 g = (u32)it.galois_elt, accumulate = it.accumulate;
     auto load = [&](u32 idx) -> u64 { return __builtin_nontemporal_load(wrow + idx); };
     const ModFp mf = modf[i];
     if (mf.ok)   // the fp64 epilogue takes the transformed correction as doubles, |x| <= q/2
@@ -961,71 +1043,60 @@ __global__ __launch_bounds__(NTT_THREADS) void passb_final_kernel(ItemPack pack,
     // epilogue on pairs of adjacent residues (16-byte accesses to the streamed operands), two pairs at a time so
     // that their loads are in flight together.  Keys, w and the output are streamed once: non-temporal, so that
     // they do not push the digit rows (re-read by every item of the batch) out of L2.
-    typedef u64 vec_t __attribute__((ext_vector_type(2)));
     const u32 tid = threadIdx.x, base = blockIdx.x << 12;
     constexpr u32 EPP = EPI / 2;
-    FieldFp ff;
-    ff.q = mf.q;
-    ff.u = mf.u;
-    ff.n0 = ff.n1 = 0.0;
-    ff.tw = nullptr;
-    const u64 pinv_plain = mont_mul(pi, 1, m);                       // P^-1 (pi is its Montgomery form)
-    const double c_w = ff.in(pinv_plain), c_sum = ff.in(mont_mul(pinv_plain, 1, m));
+    const bool fold = comp == 0 && it.c0;
     for (u32 i0 = 0; i0 < 8; i0 += EPP) {
-        u64 dv[EPP][2][MAX_BETA], cv[EPP][2];
-        vec_t kv[EPP][MAX_BETA], ov[EPP];
+        pair_t dv[EPP][MAX_BETA], kv[EPP][MAX_BETA], cv[EPP], ov[EPP];
+        bool turn[EPP];
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
-            const u32 idx = base + 2 * (tid + 256 * (i0 + e));
-            const u32 kp0 = galois_index(idx, g, logN), kp1 = galois_index(idx + 1, g, logN);
+            const u32 idx = base + 2 * (tid + 256 * (i0 + e)), kp = galois_index(idx, g, logN);
+            turn[e] = kp & 1;
 #pragma unroll
             for (u32 j = 0; j < MAX_BETA; ++j)
                 if (j < beta) {
-                    dv[e][0][j] = drow[j][kp0];
-                    dv[e][1][j] = drow[j][kp1];
-                    kv[e][j] = load_key<KEY_NT>(reinterpret_cast<const vec_t *>(key + (size_t)j * 2 * Wt * N + idx));
+                    dv[e][j] = load_pair(drow[j], kp);
+                    kv[e][j] = load_key<KEY_NT>(reinterpret_cast<const pair_t *>(key + (size_t)j * 2 * Wt * N + idx));
                 }
-            const bool fold = comp == 0 && it.c0;
-            cv[e][0] = fold ? c0[kp0] : 0;
-            cv[e][1] = fold ? c0[kp1] : 0;
-            if (accumulate)
-                ov[e] = __builtin_nontemporal_load(reinterpret_cast<const vec_t *>(dst + idx));
-            else
-                ov[e] = vec_t{0, 0};
+            cv[e] = fold ? load_pair(c0, kp) : pair_t{0, 0};
+            ov[e] = accumulate ? __builtin_nontemporal_load(reinterpret_cast<const pair_t *>(dst + idx)) : pair_t{0, 0};
         }
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
             const u32 loc = 2 * (tid + 256 * (i0 + e));
-            vec_t out;
+            __builtin_amdgcn_sched_barrier(0);
+            cv[e] = turned(cv[e], turn[e]);
+#pragma unroll
+            for (u32 j = 0; j < MAX_BETA; ++j)
+                if (j < beta) dv[e][j] = turned(dv[e][j], turn[e]);
+            pair_t out;
 #pragma unroll
             for (u32 z = 0; z < 2; ++z) {
                 if (mf.ok) {
-                    // primes below 2^50: the same residues through exact fp64 products.  The keys are in
-                    // Montgomery form (times 2^64), so the sum is multiplied by 2^-64 * P^-1 and w by P^-1.
-                    double sum = 0.0;
+                    // primes below 2^50: exact fp64 sums, keys are balanced doubles
+                    MacSum sum{MAC_H0, 0.0};
 #pragma unroll
                     for (u32 j = 0; j < MAX_BETA; ++j)
-                        if (j < beta) sum += ff.mul(ff.in(dv[e][z][j]), ff.in(kv[e][j][z]));
-                    const double t = ff.mul(sum, c_sum) - ff.mul(ff.from_bits(lds[lds_pad(loc + z)]), c_w) +
-                                     (ff.in(cv[e][z]) + ff.in(ov[e][z]));
-                    if (it.balanced) {
-                        double b = t;
-                        ff.norm(b);
-                        out[z] = ff.bits(b);
-                    } else {
-                        out[z] = ff.out(t);
-                    }
+                        if (j < beta) sum.mac(canonical_double(dv[e][j][z]), __longlong_as_double((long long)kv[e][j][z]));
+                    sum.fold(mf.q, mf.u);
+                    sum.l += (canonical_double(cv[e][z]) + canonical_double(ov[e][z])) -
+                             __longlong_as_double((long long)lds[lds_pad(loc + z)]);
+                    if (it.balanced)
+                        out[z] = (u64)__double_as_longlong(fma(-rint(sum.l * mf.u), mf.q, sum.l));
+                    else
+                        out[z] = sum.canonical(mf.q, mf.u);
                 } else {
                     u128 acc = {0, 0};
 #pragma unroll
                     for (u32 j = 0; j < MAX_BETA; ++j)
-                        if (j < beta) mac(acc, dv[e][z][j], kv[e][j][z]);
-                    u64 v = mont_mul(sub_mod(redc_wide(acc, m), lds[lds_pad(loc + z)], m.q), pi, m);
+                        if (j < beta) mac(acc, dv[e][j][z], kv[e][j][z]);
+                    u64 v = sub_mod(redc_wide(acc, m), lds[lds_pad(loc + z)], m.q);
                     v = add_mod(v, cv[e][z], m.q);
                     out[z] = add_mod(v, ov[e][z], m.q);
                 }
             }
-            __builtin_nontemporal_store(out, reinterpret_cast<vec_t *>(dst + base + loc));
+            __builtin_nontemporal_store(out, reinterpret_cast<pair_t *>(dst + base + loc));
         }
     }
 }
@@ -1173,9 +1244,21 @@ int switch_accumulate_merged(ckks_params *p, u32 level, const MergedRot &rots, u
     const u32 N = p->N, K = p->K, L = p->L, Wl = level + K;
     const u32 beta = (level + p->alpha - 1) / p->alpha;
     const u32 groups = (n + MR - 1) / MR;
-    hipLaunchKernelGGL(merged_ip_kernel, dim3(N / KS_THREADS * groups, Wl), dim3(KS_THREADS), 0, stream, rots,
-                       d_digits, digits_words(p, level), c0_base, c0_stride_r, dst_base, dst_stride, d_u, p->d_mod, n,
-                       level, K, L, beta, p->alpha, p->logN, accumulate ? 1u : 0u, groups);
+    LimbIds fp_rows, int_rows;
+    u32 n_fp = 0, n_int = 0;
+    for (u32 t = 0; t < Wl; ++t)
+        if (t < level && (p->mod[t] >> 50) == 0)
+            fp_rows.id[n_fp++] = (uint8_t)t;
+        else
+            int_rows.id[n_int++] = (uint8_t)t;
+    if (n_fp)
+        hipLaunchKernelGGL(merged_ip_kernel<true>, dim3(N / KS_THREADS * groups, n_fp), dim3(KS_THREADS), 0, stream, rots,
+                           d_digits, digits_words(p, level), c0_base, c0_stride_r, dst_base, dst_stride, d_u, p->d_mod, n,
+                           level, K, L, beta, p->alpha, p->logN, accumulate ? 1u : 0u, groups, fp_rows);
+    if (n_int)
+        hipLaunchKernelGGL(merged_ip_kernel<false>, dim3(N / KS_THREADS * groups, n_int), dim3(KS_THREADS), 0, stream,
+                           rots, d_digits, digits_words(p, level), c0_base, c0_stride_r, dst_base, dst_stride, d_u,
+                           p->d_mod, n, level, K, L, beta, p->alpha, p->logN, accumulate ? 1u : 0u, groups, int_rows);
     CKKS_LAUNCH_CHECK("merged_ip_kernel");
     return CKKS_OK;
 }
@@ -1214,7 +1297,7 @@ int moddown_add(ckks_params *p, u32 level, u64 *d_u, u64 *const *dst, u32 n, u64
     rc = launch_ntt(p, d_w, ids, level, n * 2 * level, false, stream, mid ? 2 : 3);
     if (rc) return rc;
     hipLaunchKernelGGL(moddown_final_kernel, dim3(N / KS_THREADS, level, n * 2), dim3(KS_THREADS), 0, stream, pack,
-                       d_u, d_w, p->d_mod, p->d_pinv, level, K, p->logN);
+                       d_u, d_w, p->d_mod, level, K, p->logN);
     CKKS_LAUNCH_CHECK("moddown_final_kernel");
     return CKKS_OK;
 }
@@ -1244,7 +1327,7 @@ int moddown_rescale(ckks_params *p, u32 level, u64 *d_u, const u64 *const *z, u6
     int rc = launch_ntt(p, d_u, ids, Wl, n * 2 * Wl, true, stream, 1, true);     // special limbs: inverse tile pass
     if (rc) return rc;
     hipLaunchKernelGGL(rescale_last_row_kernel, dim3(N / KS_THREADS, n * 2), dim3(KS_THREADS), 0, stream, zp, d_u, d_t,
-                       p->d_mod, p->d_pinv, level, K, N);
+                       p->d_mod, level, K, N);
     CKKS_LAUNCH_CHECK("rescale_last_row_kernel");
     ids.id[0] = (uint8_t)(level - 1);
     rc = launch_ntt(p, d_t, ids, 1, n * 2, true, stream);
@@ -1256,7 +1339,7 @@ int moddown_rescale(ckks_params *p, u32 level, u64 *d_u, const u64 *const *z, u6
     rc = launch_ntt(p, d_w, ids, level, n * 2 * level, false, stream, 2);
     if (rc) return rc;
     hipLaunchKernelGGL(moddown_rescale_final_kernel, dim3(N / KS_THREADS / 2, level - 1, n * 2), dim3(KS_THREADS), 0,
-                       stream, zp, op, d_u, d_w, p->d_mod, p->d_pinv, p->d_qlinv + (size_t)(level - 1) * L, level, K, N);
+                       stream, zp, op, d_u, d_w, p->d_mod, p->d_qlinv + (size_t)(level - 1) * L, level, K, N);
     CKKS_LAUNCH_CHECK("moddown_rescale_final_kernel");
     return CKKS_OK;
 }
@@ -1306,7 +1389,7 @@ int switch_batch(ckks_params *p, u32 level, const SwitchItem *items, u32 n, u64 
         }
         hipLaunchKernelGGL(own_keys ? passb_final_kernel<true> : passb_final_kernel<false>, dim3(tiles, n * 2 * level),
                            dim3(NTT_THREADS), 0, stream, pack, w, p->d_mod, p->d_modf, p->d_tws_fwd, p->d_twf_fwd,
-                           p->d_ninvs, p->d_pinv, n, level, K, L, beta, p->alpha, p->logN);
+                           p->d_ninvs, n, level, K, L, beta, p->alpha, p->logN);
         CKKS_LAUNCH_CHECK("passb_final_kernel");
         return CKKS_OK;
     }
@@ -1324,7 +1407,7 @@ int switch_batch(ckks_params *p, u32 level, const SwitchItem *items, u32 n, u64 
     rc = launch_ntt(p, w, ids, level, n * 2 * level, false, stream);
     if (rc) return rc;
     hipLaunchKernelGGL(moddown_final_kernel, dim3(N / KS_THREADS, level, n * 2), dim3(KS_THREADS), 0, stream, pack,
-                       u, w, p->d_mod, p->d_pinv, level, K, p->logN);
+                       u, w, p->d_mod, level, K, p->logN);
     CKKS_LAUNCH_CHECK("moddown_final_kernel");
     return CKKS_OK;
 }
@@ -1443,13 +1526,13 @@ int ckks_galois_key_load(const ckks_params_t *P, uint64_t galois_elt, const uint
         delete k;
         return hip_fail(e, "hipMalloc(key)");
     }
-    hipLaunchKernelGGL(to_mont_kernel, dim3(P->N / KS_THREADS, (u32)rows), dim3(KS_THREADS), 0, (hipStream_t)stream,
-                       d_key, k->d_key, P->d_mod, P->W, P->N);
+    hipLaunchKernelGGL(key_form_kernel, dim3(P->N / (4 * KS_THREADS), (u32)rows), dim3(KS_THREADS), 0, (hipStream_t)stream,
+                       d_key, k->d_key, P->d_mod, P->d_pinv, P->L, P->W, P->N);
     e = hipGetLastError();
     if (e != hipSuccess) {
         hipFree(k->d_key);
         delete k;
-        return hip_fail(e, "to_mont_kernel");
+        return hip_fail(e, "key_form_kernel");
     }
     *out = k;
     return CKKS_OK;
@@ -1472,9 +1555,9 @@ int ckks_galois_key_adopt(const ckks_params_t *P, uint64_t galois_elt, uint64_t 
     }
     const size_t rows = (size_t)P->dnum * 2 * P->W;
     // elementwise, each thread reads and writes its own word: in place is safe
-    hipLaunchKernelGGL(to_mont_kernel, dim3(P->N / KS_THREADS, (u32)rows), dim3(KS_THREADS), 0, (hipStream_t)stream,
-                       d_key, d_key, P->d_mod, P->W, P->N);
-    CKKS_LAUNCH_CHECK("to_mont_kernel");
+    hipLaunchKernelGGL(key_form_kernel, dim3(P->N / (4 * KS_THREADS), (u32)rows), dim3(KS_THREADS), 0, (hipStream_t)stream,
+                       d_key, d_key, P->d_mod, P->d_pinv, P->L, P->W, P->N);
+    CKKS_LAUNCH_CHECK("key_form_kernel");
     ckks_gkey *k = new ckks_gkey();
     k->params = P;
     k->galois_elt = galois_elt;
@@ -1503,13 +1586,13 @@ int ckks_relin_key_load(const ckks_params_t *P, const uint64_t *d_key, void *str
         delete k;
         return hip_fail(e, "hipMalloc(key)");
     }
-    hipLaunchKernelGGL(to_mont_kernel, dim3(P->N / KS_THREADS, (u32)rows), dim3(KS_THREADS), 0, (hipStream_t)stream,
-                       d_key, k->d_key, P->d_mod, P->W, P->N);
+    hipLaunchKernelGGL(key_form_kernel, dim3(P->N / (4 * KS_THREADS), (u32)rows), dim3(KS_THREADS), 0, (hipStream_t)stream,
+                       d_key, k->d_key, P->d_mod, P->d_pinv, P->L, P->W, P->N);
     e = hipGetLastError();
     if (e != hipSuccess) {
         hipFree(k->d_key);
         delete k;
-        return hip_fail(e, "to_mont_kernel");
+        return hip_fail(e, "key_form_kernel");
     }
     *out = k;
     return CKKS_OK;

@@ -380,16 +380,14 @@ int ckks_params_create(uint32_t logN, const uint64_t *q, uint32_t L, const uint6
     P->hninv = ninv_plain;
     std::vector<u64> dn_inv(K), dn_mat((size_t)K * L), pinv(L), qlinv((size_t)L * L, 0);
     const u32 kpad = pad_pow2(K);
-    std::vector<double> dn_matf((size_t)L * kpad * 6, 0.0), pinvf(L, 0.0);
+    std::vector<double> dn_matf((size_t)L * kpad * 6, 0.0);
     for (u32 k = 0; k < K; ++k) {
         u64 pk = mod[L + k], prod = 1;
         for (u32 b = 0; b < K; ++b)
             if (b != k) prod = hmul(prod, mod[L + b] % pk, pk);
         dn_inv[k] = to_mont(hinv(prod, pk), P->hmod[L + k]);
         for (u32 i = 0; i < L; ++i) {
-            u64 f = 1;
-            for (u32 b = 0; b < K; ++b)
-                if (b != k) f = hmul(f, mod[L + b] % mod[i], mod[i]);
+            const u64 f = hinv(pk % mod[i], mod[i]);                 // (P/p_k) P^-1
             dn_mat[(size_t)k * L + i] = to_mont(f, P->hmod[i]);
             // the same factor times 2^0, 2^20, 2^40 mod q_i, each split into 25-bit halves held as doubles: the
             // conversion onto a prime below 2^50 is then a sum of exact 20-bit x 25-bit products in fp64
@@ -407,7 +405,6 @@ int ckks_params_create(uint32_t logN, const uint64_t *q, uint32_t L, const uint6
         u64 pm = 1;
         for (u32 k = 0; k < K; ++k) pm = hmul(pm, mod[L + k] % mod[i], mod[i]);
         pinv[i] = to_mont(hinv(pm, mod[i]), P->hmod[i]);
-        pinvf[i] = (double)hinv(pm, mod[i]);
         for (u32 l = 0; l < L; ++l)
             if (l != i) qlinv[(size_t)l * L + i] = to_mont(hinv(mod[l] % mod[i], mod[i]), P->hmod[i]);
     }
@@ -444,7 +441,6 @@ int ckks_params_create(uint32_t logN, const uint64_t *q, uint32_t L, const uint6
     if (!rc) rc = upload(&P->d_dn_mat, dn_mat);
     if (!rc) rc = upload(&P->d_dn_matf, dn_matf);
     if (!rc) rc = upload(&P->d_pinv, pinv);
-    if (!rc) rc = upload(&P->d_pinvf, pinvf);
     if (!rc) rc = upload(&P->d_qlinv, qlinv);
     if (!rc) rc = upload(&P->d_tws_fwd, fwd_s);
     if (!rc) rc = upload(&P->d_tws_inv, inv_s);
@@ -502,7 +498,6 @@ void ckks_params_destroy(ckks_params_t *P) {
     hipFree(P->d_dn_mat);
     hipFree(P->d_dn_matf);
     hipFree(P->d_pinv);
-    hipFree(P->d_pinvf);
     hipFree(P->d_qlinv);
     hipFree(P->d_tws_fwd);
     hipFree(P->d_tws_inv);

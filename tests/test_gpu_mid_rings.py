@@ -38,3 +38,20 @@ def test_projection_with_fused_rescale(logN, m, C, N1):
     Y, ref, _, _ = run_case(O, P, X, Wm, r.uniform(-0.5, 0.5, 2 * C - 1), m, C, N1, 40, 4, 40 + logN, hw=16, real=True,
                             merged=True)
     assert np.abs(Y - ref).max() <= 1e-3
+
+
+def test_rotation_of_a_ciphertext_that_is_not_16_byte_aligned():
+    """The switches gather pairs of residues from the caller's ciphertext; its address need only be that of a word."""
+    import torch
+    from paper_2604_09975_amd import binding as B
+    O = helpers.small_oracle(13, L=4, K=2, dnum=2, qbits=50, pbits=60)
+    _, P = make_pair(O)
+    r = W.rng(77)
+    buf = torch.empty(2 * 4 * O.N + 1, dtype=torch.int64, device="cuda")
+    ct = torch.from_numpy(W.uniform_residues(r, O.q, O.N, lead=(2,)).view(np.int64)).cuda()
+    key = torch.from_numpy(W.uniform_residues(r, O.moduli, O.N, lead=(O.dnum, 2)).view(np.int64)).cuda()
+    h = B.ckks_galois_key_load(P, O.galois_elt(5), key)
+    odd = buf[1:].view(2, 4, O.N)
+    odd.copy_(ct)
+    assert odd.data_ptr() % 16 == 8
+    assert torch.equal(B.ckks_rotate_hoisted(P, odd, 4, [5], [h]), B.ckks_rotate_hoisted(P, ct, 4, [5], [h]))
