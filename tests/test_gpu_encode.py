@@ -74,16 +74,16 @@ def _round_trip(O, P, count, scale, seed):
 
 
 def test_encode_decode_toy_and_chunks():
-    O, P = make_pair(W.TOY_RING)               # N = 2^12: one transform pass; 70 vectors = two scratch chunks
+    O, P = make_pair(W.TOY_RING)               # N = 2^12: one workgroup per vector
     _check_encode(O, P, 70, 2.0**30, 501)
     _check_decode(O, P, 3, 2.0**30, 502, 1, 38)
     _check_decode(O, P, 3, 2.0**50, 503, 2, 66)
     _round_trip(O, P, 5, 2.0**30, 504)
 
 
-@pytest.mark.parametrize("logN", [10, 13, 14, 17])
+@pytest.mark.parametrize("logN", [10, 11, 13, 14, 15, 17])
 def test_encode_decode_other_degrees(logN):
-    """Transform geometry away from the two tuned ring sizes (one pass below 2^12, 5/6/9 + 8 stages above)."""
+    """Transform geometry at the ring sizes between and beyond the benchmark ones (one workgroup per vector up to 2^12, 4 .. 8 + 8 stages above)."""
     O = helpers.small_oracle(logN, L=3, K=1, dnum=3, qbits=45, pbits=47)
     _, P = make_pair(O)
     _check_encode(O, P, 2, 2.0**36, 510 + logN)
@@ -145,3 +145,39 @@ def test_encode_decode_errors():
     with pytest.raises(ValueError):
         B.ckks_encode(P, _cdev(np.zeros(7)), 2.0**30)
     assert B.ckks_encode(P, _cdev(np.zeros((0, O.n))), 2.0**30).shape == (0, O.N)
+
+
+def test_more_vectors_than_one_chunk():
+    """N = 2^13, 131 vectors: more than the 128 whose transforms the scratch holds; every vector equals its own single call."""
+    from paper_2604_09975_amd import binding as B
+    O = helpers.small_oracle(13, L=3, K=1, dnum=3, qbits=45, pbits=47)
+    _, P = make_pair(O)
+    z = _cdev(_slots(W.rng(610), 131, O.n))
+    got = B.ckks_encode(P, z, 2.0**30)
+    res = torch.remainder(got, int(O.q[0])).reshape(131, 1, O.N)
+    back = B.ckks_decode(P, res, 1, 2.0**30)
+    for i in (0, 1, 127, 128, 130):
+        assert torch.equal(got[i], B.ckks_encode(P, z[i:i + 1].contiguous(), 2.0**30)[0])
+        assert torch.equal(back[i], B.ckks_decode(P, res[i:i + 1].contiguous(), 1, 2.0**30)[0])
+    assert (back - z).abs().max().item() <= 0.5 * O.N / 2.0**30
+
+
+@pytest.mark.parametrize("qbits", [50, 55])
+@pytest.mark.parametrize("logN", [11, 14])
+def test_two_limb_lift_at_the_ends_of_its_range(logN, qbits):
+    """Coefficients at 0, +-1, around +-q0/2, +-q0 and at +-(Q-1)/2, the ends of the centred range (primes below 2^50 are
+    lifted in doubles, larger ones in 128-bit integers).  Constant polynomials decode to their constant in every slot, one
+    coefficient at a time, to within the rounding of a double."""
+    from paper_2604_09975_amd import binding as B
+    O = helpers.small_oracle(logN, L=2, K=1, dnum=2, qbits=qbits, pbits=57)
+    _, P = make_pair(O)
+    q0, q1 = int(O.q[0]), int(O.q[1])
+    Q = q0 * q1
+    vals = [0, 1, -1, q0 // 2, q0 // 2 + 1, -(q0 // 2), -(q0 // 2) - 1, q0, -q0, q0 - 1, 1 - q0, (Q - 1) // 2,
+            -((Q - 1) // 2), (Q - 1) // 2 - q0, -((Q - 1) // 2) + q0, Q // 3, -(Q // 3), 1 << 40, -(1 << 40)]
+    res = torch.zeros((len(vals), 2, O.N), dtype=torch.int64, device="cuda")
+    for i, v in enumerate(vals):
+        res[i, 0, 0], res[i, 1, 0] = v % q0, v % q1
+    got = B.ckks_decode(P, res, 2, 1.0).cpu().numpy()
+    for i, v in enumerate(vals):
+        assert np.abs(got[i].real - float(v)).max() <= abs(v) * 2.0 ** -51 and np.abs(got[i].imag).max() == 0, v
