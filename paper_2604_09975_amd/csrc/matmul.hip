@@ -285,6 +285,26 @@ __global__ __launch_bounds__(EW_THREADS) void copy_blocks_kernel(u64 *__restrict
         *reinterpret_cast<const vec_t *>(src + blockIdx.z * src_stride + k);
 }
 
+// y_b = base_b + the rotated accumulators of block b among the cn items of a batch; item r belongs to block (c0 + r) % B.
+// blockIdx.y = component * level + limb, blockIdx.z = block; two residues per thread.
+__global__ __launch_bounds__(EW_THREADS) void add_rotations_kernel(u64 *__restrict__ y, const u64 *base,
+                                                                   size_t base_stride, const u64 *__restrict__ items,
+                                                                   const ModConst *__restrict__ mods, u32 level, u32 N,
+                                                                   u32 b0, u32 B, u32 c0, u32 cn) {
+    typedef u64 vec_t __attribute__((ext_vector_type(2)));
+    const u32 b = b0 + blockIdx.z;
+    const size_t ctw = (size_t)2 * level * N;
+    const size_t k = (size_t)blockIdx.y * N + (blockIdx.x * EW_THREADS + threadIdx.x) * 2;
+    const u64 q = mods[blockIdx.y % level].q;
+    vec_t v = *reinterpret_cast<const vec_t *>(base + (size_t)b * base_stride + k);
+    for (u32 r = (b + B - c0 % B) % B; r < cn; r += B) {
+        const vec_t x = *reinterpret_cast<const vec_t *>(items + r * ctw + k);
+        v[0] = add_mod(v[0], x[0], q);
+        v[1] = add_mod(v[1], x[1], q);
+    }
+    *reinterpret_cast<vec_t *>(y + (size_t)b * ctw + k) = v;
+}
+
 // c0 of block b (at y + b * y_stride) += bias[b]: blockIdx.y = limb, blockIdx.z = output block, two residues per thread
 __global__ __launch_bounds__(EW_THREADS) void add_bias_kernel(u64 *__restrict__ y, size_t y_stride,
                                                               const u64 *__restrict__ bias,
@@ -517,11 +537,13 @@ static MatmulLayout matmul_layout(const ckks_params *P, const ckks_weights *w, b
     const size_t ctw = (size_t)2 * level * N;
     merged = merged && N2 > 1;
     l.in_chunk = std::min<u32>(ROT_BATCH, G);                    // inputs decomposed together
-    l.batch = std::min<u32>(ROT_BATCH, std::max(l.in_chunk, B));
+    // inputs, accumulators or (separate giant step) giant rotations decomposed and switched together
+    const u32 rots = (u32)std::min<u64>(ROT_BATCH, merged ? 0 : (u64)B * (N2 - 1));
+    l.batch = std::min<u32>(ROT_BATCH, std::max({l.in_chunk, B, rots}));
     l.dig_w = digits_words(P, level);
     l.tmp_w = (size_t)level * N;
     l.ks_w = l.batch * (l.dig_w + l.tmp_w) + switch_scratch_words(P, level, ROT_BATCH);
-    l.bank_w = (size_t)G * w->N1 * ctw;
+    l.bank_w = std::max<size_t>((size_t)G * w->N1, rots) * ctw;  // the rotated accumulators take the bank's place
     l.acc_w = (size_t)B * N2 * ctw;
     l.u_w = merged ? (size_t)B * 2 * (level + P->K) * N : 0;    // extended-basis sums of the giant step
     // merged giant step: the digits of up to MERGE_GROUP rotations of one batch of blocks are held together
@@ -1033,7 +1055,8 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
     const bool in_place = fused_rescale && !ps.empty();
     u64 *y_base = in_place ? d_acc : d_ct_y;
     const size_t y_stride = in_place ? (size_t)N2 * ctw : ctw;
-    for (u32 b0 = 0; !in_place && b0 < B; b0 += 65535) {
+    const bool batched = !merged && !ps.empty();              // y_b starts in the first batch of rotations
+    for (u32 b0 = 0; !in_place && !batched && b0 < B; b0 += 65535) {
         hipLaunchKernelGGL(copy_blocks_kernel, dim3((u32)(ctw / (2 * EW_THREADS)), 1, std::min<u32>(B - b0, 65535)),
                            dim3(EW_THREADS), 0, stream, d_ct_y + (size_t)b0 * ctw, d_acc + (size_t)b0 * N2 * ctw, ctw,
                            (size_t)N2 * ctw);
@@ -1107,36 +1130,44 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
             if (rc) return rc;
         }
     }
+    // Separate order: each rotation a complete key switch.  The switches of all rotations and blocks go out in batches of
+    // up to ROT_BATCH, rotation-major (neighbours share the key), into the area of the bank, which is free by now, and are
+    // summed from there.  (One batch per rotation before, which with few blocks is a chain of small launches: a 64-wide
+    // layer at N = 2^12 with 7 rotations of one block took 57 launches and 501 us, now 21 and 158 us.)
+    for (u64 c0 = 0; batched && c0 < (u64)ps.size() * B; c0 += batch) {
+        const u32 cn = (u32)std::min<u64>(batch, (u64)ps.size() * B - c0);
+        SwitchItem items[ROT_BATCH];
+        const u64 *c1s[ROT_BATCH];
+        for (u32 r = 0; r < cn; ++r) {
+            const u32 p = ps[(c0 + r) / B], b = (u32)((c0 + r) % B);
+            const u64 *src = d_acc + ((size_t)b * N2 + p) * ctw;
+            c1s[r] = src + (size_t)level * N;
+            items[r].digits = d_digits + (size_t)r * dig_w;
+            items[r].c1 = c1s[r];
+            items[r].c0 = src;
+            items[r].key = giant_keys[p - 1]->d_key;
+            items[r].dst = d_bank + (size_t)r * ctw;
+            items[r].galois_elt = giant_g[p];
+            items[r].accumulate = 0;
+            items[r].balanced = 0;
+        }
+        rc = decompose(P, c1s, cn, level, d_digits, d_tmp, stream);
+        if (rc) return rc;
+        rc = switch_batch(P, level, items, cn, d_work, stream);
+        if (rc) return rc;
+        for (u32 b0 = 0; b0 < B; b0 += 65535) {
+            hipLaunchKernelGGL(add_rotations_kernel, dim3(N / (2 * EW_THREADS), 2 * level, std::min<u32>(B - b0, 65535)),
+                               dim3(EW_THREADS), 0, stream, d_ct_y, c0 ? d_ct_y : d_acc, c0 ? ctw : (size_t)N2 * ctw,
+                               d_bank, P->d_mod, level, N, b0, B, (u32)(c0 % B), cn);
+            CKKS_LAUNCH_CHECK("add_rotations_kernel");
+        }
+    }
     for (u32 p = 1; !merged && p < N2; ++p) {
-        for (u32 b0 = 0; b0 < B; b0 += batch) {
-            const u32 nb = std::min(batch, B - b0);
-            if (giant_g[p] == 1) {   // a full turn: plain addition
-                for (u32 r = 0; r < nb; ++r) {
-                    hipLaunchKernelGGL(add_rows_kernel, dim3(N / EW_THREADS, 2 * level), dim3(EW_THREADS), 0, stream,
-                                       d_ct_y + (size_t)(b0 + r) * ctw, d_acc + ((size_t)(b0 + r) * N2 + p) * ctw,
-                                       P->d_mod, level, N);
-                    CKKS_LAUNCH_CHECK("add_rows_kernel");
-                }
-                continue;
-            }
-            SwitchItem items[ROT_BATCH];
-            const u64 *c1s[ROT_BATCH];
-            for (u32 r = 0; r < nb; ++r) c1s[r] = d_acc + ((size_t)(b0 + r) * N2 + p) * ctw + (size_t)level * N;
-            rc = decompose(P, c1s, nb, level, d_digits, d_tmp, stream);
-            if (rc) return rc;
-            for (u32 r = 0; r < nb; ++r) {
-                const u64 *src = d_acc + ((size_t)(b0 + r) * N2 + p) * ctw;
-                items[r].digits = d_digits + (size_t)r * dig_w;
-                items[r].c1 = src + (size_t)level * N;
-                items[r].c0 = src;
-                items[r].key = giant_keys[p - 1]->d_key;
-                items[r].dst = d_ct_y + (size_t)(b0 + r) * ctw;   // distinct b within a batch: no two items share dst
-                items[r].galois_elt = giant_g[p];
-                items[r].accumulate = 1;
-                items[r].balanced = 0;
-            }
-            rc = switch_batch(P, level, items, nb, d_work, stream);
-            if (rc) return rc;
+        if (giant_g[p] != 1) continue;                        // a full turn: plain addition
+        for (u32 b = 0; b < B; ++b) {
+            hipLaunchKernelGGL(add_rows_kernel, dim3(N / EW_THREADS, 2 * level), dim3(EW_THREADS), 0, stream,
+                               d_ct_y + (size_t)b * ctw, d_acc + ((size_t)b * N2 + p) * ctw, P->d_mod, level, N);
+            CKKS_LAUNCH_CHECK("add_rows_kernel");
         }
     }
     // 3b. decomplexification: y_b += conj(y_b), one key switch per output block.  The switch gathers from
