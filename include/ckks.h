@@ -324,7 +324,7 @@ int ckks_client_decrypt(ckks_params_t *params, const ckks_secret_t *secret, cons
 /* d_slots: device, [count][n] complex doubles (re, im interleaved).  d_coeffs: device, int64 [count][N], the
  * nearest integers to scale * m_k, ready for ckks_client_encrypt, ckks_plain_expand or
  * ckks_weights_set_diagonals.  scale * max|z| must stay below 2^62.  Enqueues on `stream`; uses the library's
- * scratch arena (128 vectors per pass). */
+ * scratch arena (64 vectors per pass). */
 int ckks_encode(ckks_params_t *params, const double *d_slots, uint32_t count, double scale, uint32_t flags,
                 int64_t *d_coeffs, void *stream);
 

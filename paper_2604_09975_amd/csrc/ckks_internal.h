@@ -102,9 +102,10 @@ struct ckks_params {
     ckks::u64 *d_pinv = nullptr;       // [L]: P^-1 mod q_i
     ckks::u64 *d_qlinv = nullptr;      // [L][L]: q_l^-1 mod q_i (rescale), row l
     std::map<ckks::u32, ckks::LevelTables> levels;
-    // twiddles of complex-slot encode / decode (built on first use): [N/2] complex, entry h + j, j < h: exp(2*pi*i*(5^j mod
-    // 8h)/(8h))
-    double *d_fft_tw = nullptr;
+    // tables of complex-slot encode / decode (built on first use), one after the other: decode twiddles [N/2] complex,
+    // entry h + j, j < h: exp(2*pi*i*(5^j mod 8h)/(8h)); encode twiddles [N] complex, entry h + j: exp(-2*pi*i*j/(2h)); twist
+    // [N] complex: exp(-i*pi*k/N); bins [N/2] u32: (5^j mod 2N - 1)/2; column order of encode's scratch rows [256] u32
+    double *d_fft = nullptr;
     // private scratch arena
     void *d_scratch = nullptr;
     size_t scratch_bytes = 0;

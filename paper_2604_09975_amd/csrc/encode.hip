@@ -1,23 +1,32 @@
 // Complex-slot encode / decode on the device (Sec. 2.1 Encode / Decode, Sec. 3.1 slot order).
-// Slot j of a plaintext m(X) is m(zeta^(5^j)), zeta = exp(i*pi/N), j < n = N/2.  With w_k = m_k + i*m_(k+n), k < n,
-// zeta^(5^j n) = i gives z_j = sum_k w_k zeta^(5^j k): n complex values in, n out.  Since 5^(n/2) = 1 + N (mod 2N), the
-// sum splits into the even and the odd k like an FFT,
-//   z_j, z_(j+n/2) = E_j +- zeta^(5^j) O_j,   j < n/2,
-// with E, O the same transform at half the length (5^j modulo a quarter of the roots each time).  Decode runs these
-// butterflies from length 2 up to n, on w in bit-reversed order; encode runs their inverses from n down to 2.  The slots
-// are in order on their side without a permutation, and the twiddle of butterfly j of half length h is
-// tw[h + j] = exp(2*pi*i*(5^j mod 8h)/(8h)).
+// Slot j of a plaintext m(X) is m(zeta^(5^j)), zeta = exp(i*pi/N).
 //
-// n >= 4096: two passes over 4096-element tiles, 16 elements per thread, at most four stages (radix 16) between exchanges
+// Decode.  With w_k = m_k + i*m_(k+n), k < n = N/2, zeta^(5^j n) = i gives z_j = sum_k w_k zeta^(5^j k): n complex values
+// in, n out.  Since 5^(n/2) = 1 + N (mod 2N), the sum splits into the even and the odd k like an FFT,
+//   z_j, z_(j+n/2) = E_j +- zeta^(5^j) O_j,   j < n/2,
+// with E, O the same transform at half the length.  The butterflies run from length 2 up to n on w in bit-reversed order;
+// the slots come out in order, and the twiddle of butterfly j of half length h is tw[h + j] = exp(2*pi*i*(5^j mod 8h)/(8h)).
+//
+// Encode.  With e_j = 5^j mod 2N and bin t_j = (e_j - 1)/2,
+//   m_k = (1/N) * Re( zeta^(-k) * sum_t v_t * exp(-2*pi*i*t*k/N) ),  v[t_j] = z_j,  v[N-1-t_j] = conj(z_j):
+// an N-point FFT, decimation in frequency with the twiddles w[j << s] of a table of N-th roots, and a twist.  (The
+// half-length form of decode would do for encode too, but rounds differently: an encoded integer next to a tie could
+// change by one, and with it every residue of a weight or message that a program encodes again.  These are the operations
+// of a plain radix-2 FFT in their order, so the integers are the same whatever the passes are.)
+//
+// Two passes over 4096-element tiles each, 16 elements per thread, at most four stages (radix 16) between exchanges
 // through LDS:
-//   far:  the stages of half length 256 and more, on columns (elements 256 apart), 2^S = n/256 rows of 4096 >> S columns;
-//         slots on one side, the scratch array on the other.
-//   near: the stages of half length up to 128, on 16 runs of 256 elements that lie n/16 apart: then the tile's k = bitrev(p)
-//         form runs of 16, a 128-byte line of the coefficients that are on the other side.
-// A pass reads and writes every element once, and nothing else touches memory.  n < 4096: one workgroup per vector.
-// Off the server's hot path.  96 real vectors at N = 2^16: 308 us with an N-point FFT between separate permutation, twist
-// and rounding kernels, 46 us now (4 TB/s over what it moves); 5 vectors decoded at N = 2^15: 45 us, 14 us now.
+//   far:  the stages of half length 256 and more, on columns (elements 256 apart); slots on one side, scratch on the other.
+//   near: the stages of half length up to 128, on 16 runs of 256 elements that lie a sixteenth of the array apart: then the
+//         tile's k = bitrev(p) form runs of 16, a 128-byte line of the coefficients on the other side.
+// Encode's far pass finds its columns by their slots: t_j mod 256 depends on j mod 128 alone, so the columns of COLS/2
+// neighbouring j mod 128 are read from whole lines of slots, and the columns 255 - (t mod 256) are their conjugates.  It
+// leaves column (group, member) at place group * COLS + member of the scratch rows.
+// A pass reads and writes every element once, and nothing else touches memory.  Short rings: one workgroup per vector.
+// Off the server's hot path.  96 real vectors at N = 2^16: 308 us with permutation, transform, twist and rounding in
+// five kernels, 92 us now; 5 vectors decoded at N = 2^15: 45 us, 14 us now.
 #include <cmath>
+#include <type_traits>
 
 #include "ckks_internal.h"
 #include "common_kernels.h"
@@ -27,7 +36,7 @@ namespace ckks {
 
 constexpr u32 FFT_THREADS = 256;
 constexpr u32 FFT_TILE = 4096;
-constexpr u32 ENC_CHUNK = 128;        // vectors transformed per scratch chunk (N = 2^16: 64 MiB)
+constexpr u32 ENC_CHUNK = 64;         // vectors transformed per scratch chunk (N = 2^16: 64 MiB for encode)
 // tile element i: one pad element after 16 and one after 256, so that runs of 16, strides of 16 and strides of 256 all
 // fall on distinct banks.  70 KB: two workgroups per CU.
 __device__ __forceinline__ u32 fft_slot(u32 i) { return i + (i >> 4) + (i >> 8); }
@@ -36,49 +45,45 @@ constexpr u32 FFT_LDS = FFT_TILE + FFT_TILE / 16 + FFT_TILE / 256;
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
-__device__ __forceinline__ double2 cmul_conj(double2 a, double2 b) {     // a * conj(b)
-    return make_double2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
-}
 __device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
 
-// LOGR stages on elements off + r * stride, r < 2^LOGR, of every block of 2^LOGR * stride: half lengths
-// stride << (LOGR-1) .. stride (INV: encode) or the other way round (decode)
-template <u32 LOGR, bool INV>
+// LOGR stages on elements off + r * stride, r < 2^LOGR, of every block of 2^LOGR * stride.  Encode: half lengths
+// stride << (LOGR-1) down to stride, (a + b, (a - b) w); decode: the other way round, (a + b w, a - b w).
+template <u32 LOGR, bool ENC>
 __device__ __forceinline__ void fft_group(double2 *v, const double2 *__restrict__ tw, u32 stride, u32 off) {
     constexpr u32 R = 1u << LOGR;
 #pragma unroll
     for (u32 s = 0; s < LOGR; ++s) {
-        const u32 t = INV ? s : LOGR - 1 - s, g = R >> (t + 1);
+        const u32 t = ENC ? s : LOGR - 1 - s, g = R >> (t + 1);
 #pragma unroll
         for (u32 i = 0; i < g; ++i) {
             const double2 w = tw[(g + i) * stride + off];
 #pragma unroll
             for (u32 k = 0; k < (1u << t); ++k) {
                 double2 &a = v[k * 2 * g + i], &b = v[k * 2 * g + i + g];
-                const double2 x = a, y = INV ? b : cmul(b, w);
+                const double2 x = a, y = ENC ? b : cmul(b, w);
                 a = cadd(x, y);
-                b = INV ? cmul_conj(csub(x, y), w) : csub(x, y);
+                b = ENC ? cmul(csub(x, y), w) : csub(x, y);
             }
         }
     }
 }
 
-// Where the coefficients meet the transform: w_k out of / into the caller's array.
+// Where the coefficients meet the transform of encode: X_k into the caller's array.
 struct EncodeOut {
     int64_t *c;                // the vector's N coefficients
-    u32 n, real;
+    const double2 *twist;      // [N]: zeta^(-k)
+    u32 N, real;
     double mul;
-    // Nearest integers to scale * m.  A real slot vector is fixed by conjugation, so its polynomial satisfies
-    // m[N-k] = -m[k] and m[N/2] = 0 exactly; real != 0 imposes that on the rounded values (the transform gives it only
-    // up to rounding).
-    __device__ __forceinline__ void put(u32 k, double2 w) const {
-        const int64_t re = (int64_t)rint(w.x * mul);
-        c[k] = re;
-        if (real)
-            c[k ? 2 * n - k : n] = k ? -re : 0;
-        else
-            c[n + k] = (int64_t)rint(w.y * mul);
+    // Coefficient k = nearest integer to (scale/N) * Re(zeta^(-k) * X_k).  A real slot vector is fixed by conjugation, so
+    // its polynomial satisfies m[N-k] = -m[k] and m[N/2] = 0 exactly; real != 0 imposes that on the rounded values (the
+    // transform gives it only up to rounding) and takes k < N/2 alone.
+    __device__ __forceinline__ void put(u32 k, double2 x) const {
+        const double2 t = twist[k];
+        const int64_t v = (int64_t)rint((x.x * t.x - x.y * t.y) * mul);
+        c[k] = v;
+        if (real) c[k ? N - k : N / 2] = k ? -v : 0;
     }
 };
 
@@ -124,12 +129,11 @@ struct DecodeIn {
     __device__ __forceinline__ double2 get(const Raw &w) const { return make_double2(lift(w.a0, w.a1), lift(w.b0, w.b1)); }
 };
 
-// far pass (see the head of the file).  INV: slots -> scratch; else scratch -> slots, times inv_scale.
+// Far pass of decode: scratch -> slots, times inv_scale.  n = 256 << S.
 // grid: x = group of 4096 >> S columns, y = vector
-template <u32 S, bool INV>
-__global__ __launch_bounds__(FFT_THREADS) void fft_far_kernel(const double2 *__restrict__ in, double2 *__restrict__ out,
-                                                              const double2 *__restrict__ tw, u32 real,
-                                                              double inv_scale) {
+template <u32 S>
+__global__ __launch_bounds__(FFT_THREADS) void decode_far_kernel(const double2 *__restrict__ in, double2 *__restrict__ out,
+                                                                 const double2 *__restrict__ tw, double inv_scale) {
     constexpr u32 COLS = FFT_TILE >> S, LOW = S - 4, SUB = 1u << LOW, n = 256u << S;
     __shared__ double2 tile[FFT_LDS];
     const u32 col = threadIdx.x % COLS, q = threadIdx.x / COLS;              // q < SUB
@@ -137,193 +141,270 @@ __global__ __launch_bounds__(FFT_THREADS) void fft_far_kernel(const double2 *__r
     const double2 *src = in + (size_t)blockIdx.y * n + pcol;
     double2 *dst = out + (size_t)blockIdx.y * n + pcol;
     double2 v[16];
-    // rows r * SUB + q: the top four row bits; rows (q + SUB * m) * SUB + r, r < SUB: the others
-    auto top_row = [&](u32 r) { return r * SUB + q; };
+    // rows (q + SUB * m) * SUB + r, r < SUB: the low row bits; rows r * SUB + q: the top four
     auto low_row = [&](u32 e) { return (q + SUB * (e >> LOW)) * SUB + (e & (SUB - 1)); };
-    auto top = [&]() { fft_group<4, INV>(v, tw, SUB * 256, q * 256 + pcol); };
-    auto low = [&]() {
-        if constexpr (LOW > 0) {
+    auto top_row = [&](u32 r) { return r * SUB + q; };
 #pragma unroll
-            for (u32 m = 0; m < (16u >> LOW); ++m) fft_group<LOW, INV>(v + m * SUB, tw, 256, pcol);
-        }
-    };
-    if (INV) {
+    for (u32 e = 0; e < 16; ++e) v[e] = src[low_row(e) * 256];
+    if constexpr (LOW > 0) {
 #pragma unroll
-        for (u32 r = 0; r < 16; ++r) {
-            v[r] = src[top_row(r) * 256];
-            if (real) v[r].y = 0.0;
-        }
-        top();
-        if constexpr (LOW > 0) {
+        for (u32 m = 0; m < (16u >> LOW); ++m) fft_group<LOW, false>(v + m * SUB, tw, 256, pcol);
 #pragma unroll
-            for (u32 r = 0; r < 16; ++r) tile[fft_slot(top_row(r) * COLS + col)] = v[r];
-            __syncthreads();
+        for (u32 e = 0; e < 16; ++e) tile[fft_slot(low_row(e) * COLS + col)] = v[e];
+        __syncthreads();
 #pragma unroll
-            for (u32 e = 0; e < 16; ++e) v[e] = tile[fft_slot(low_row(e) * COLS + col)];
-            low();
-        }
-#pragma unroll
-        for (u32 e = 0; e < 16; ++e) dst[low_row(e) * 256] = v[e];
-    } else {
-#pragma unroll
-        for (u32 e = 0; e < 16; ++e) v[e] = src[low_row(e) * 256];
-        if constexpr (LOW > 0) {
-            low();
-#pragma unroll
-            for (u32 e = 0; e < 16; ++e) tile[fft_slot(low_row(e) * COLS + col)] = v[e];
-            __syncthreads();
-#pragma unroll
-            for (u32 r = 0; r < 16; ++r) v[r] = tile[fft_slot(top_row(r) * COLS + col)];
-        }
-        top();
-#pragma unroll
-        for (u32 r = 0; r < 16; ++r) dst[top_row(r) * 256] = make_double2(v[r].x * inv_scale, v[r].y * inv_scale);
+        for (u32 r = 0; r < 16; ++r) v[r] = tile[fft_slot(top_row(r) * COLS + col)];
     }
+    fft_group<4, false>(v, tw, SUB * 256, q * 256 + pcol);
+#pragma unroll
+    for (u32 r = 0; r < 16; ++r) dst[top_row(r) * 256] = make_double2(v[r].x * inv_scale, v[r].y * inv_scale);
 }
 
-// near pass: INV: scratch -> coefficients (EncodeOut); else residues (DecodeIn) -> scratch.
-// grid: x = n / 4096, y = vector
-template <bool INV, class Coef>
-__global__ __launch_bounds__(FFT_THREADS) void fft_near_kernel(double2 *__restrict__ scratch,
-                                                               const double2 *__restrict__ tw, Coef first,
-                                                               size_t coef_stride, u32 logn) {
+// Near pass of decode: residues -> scratch.  grid: x = n / 4096, y = vector
+__global__ __launch_bounds__(FFT_THREADS) void decode_near_kernel(double2 *__restrict__ scratch,
+                                                                  const double2 *__restrict__ tw, DecodeIn coef,
+                                                                  size_t coef_stride, u32 logn) {
     __shared__ double2 tile[FFT_LDS];
     const u32 tid = threadIdx.x, h = tid >> 4, c = tid & 15, f = blockIdx.x, fb = logn - 12;
     double2 *v0 = scratch + ((size_t)blockIdx.y << logn) + (((h << fb) + f) << 8);     // run h of the tile
-    Coef coef = first;
-    if constexpr (INV)
-        coef.c += blockIdx.y * coef_stride;
-    else
-        coef.r += blockIdx.y * coef_stride;
+    coef.r += blockIdx.y * coef_stride;
     // coefficient side: thread (m & 15 = h, hh = c) holds element lo = bitrev8(m) of run bitrev4(hh), k as below
     const u32 ch = __brev(c) >> 28, fk = (fb ? __brev(f) >> (32 - fb) : 0) * 16 + c;
     auto side = [&](u32 r) { return fft_slot(ch * 256 + (__brev(h + 16 * r) >> 24)); };
     auto kidx = [&](u32 r) { return ((h + 16 * r) << (logn - 8)) + fk; };
     double2 v[16];
-    if constexpr (INV) {
 #pragma unroll
-        for (u32 r = 0; r < 16; ++r) v[r] = v0[c + 16 * r];
-        fft_group<4, true>(v, tw, 16, c);
+    for (u32 r0 = 0; r0 < 16; r0 += 8) {               // the loads of eight coefficients are in flight together
+        DecodeIn::Raw w[8];
 #pragma unroll
-        for (u32 r = 0; r < 16; ++r) tile[fft_slot(h * 256 + c + 16 * r)] = v[r];
-        __syncthreads();
+        for (u32 r = 0; r < 8; ++r) w[r] = coef.load(kidx(r0 + r));
 #pragma unroll
-        for (u32 r = 0; r < 16; ++r) v[r] = tile[fft_slot(h * 256 + c * 16 + r)];
-        fft_group<4, true>(v, tw, 1, 0);
+        for (u32 r = 0; r < 8; ++r) tile[side(r0 + r)] = coef.get(w[r]);
+    }
+    __syncthreads();
 #pragma unroll
-        for (u32 r = 0; r < 16; ++r) tile[fft_slot(h * 256 + c * 16 + r)] = v[r];      // a thread's own slots
-        __syncthreads();
+    for (u32 r = 0; r < 16; ++r) v[r] = tile[fft_slot(h * 256 + c * 16 + r)];
+    fft_group<4, false>(v, tw, 1, 0);
 #pragma unroll
-        for (u32 r = 0; r < 16; ++r) coef.put(kidx(r), tile[side(r)]);
-    } else {
+    for (u32 r = 0; r < 16; ++r) tile[fft_slot(h * 256 + c * 16 + r)] = v[r];          // a thread's own slots
+    __syncthreads();
 #pragma unroll
-        for (u32 r0 = 0; r0 < 16; r0 += 8) {               // the loads of eight coefficients are in flight together
-            DecodeIn::Raw w[8];
+    for (u32 r = 0; r < 16; ++r) v[r] = tile[fft_slot(h * 256 + c + 16 * r)];
+    fft_group<4, false>(v, tw, 16, c);
 #pragma unroll
-            for (u32 r = 0; r < 8; ++r) w[r] = coef.load(kidx(r0 + r));
-#pragma unroll
-            for (u32 r = 0; r < 8; ++r) tile[side(r0 + r)] = coef.get(w[r]);
+    for (u32 r = 0; r < 16; ++r) v0[c + 16 * r] = v[r];
+}
+
+// n < 4096: the whole decode of one vector in LDS, one exchange per stage.  grid: x = vector
+__global__ __launch_bounds__(FFT_THREADS) void decode_small_kernel(double2 *__restrict__ out,
+                                                                   const double2 *__restrict__ tw, DecodeIn coef,
+                                                                   size_t coef_stride, u32 logn, double inv_scale) {
+    __shared__ double2 tile[FFT_TILE / 2];
+    const u32 n = 1u << logn;
+    coef.r += blockIdx.x * coef_stride;
+    for (u32 i = threadIdx.x; i < n; i += FFT_THREADS) tile[i] = coef.get(coef.load(__brev(i) >> (32 - logn)));
+    __syncthreads();
+    for (u32 lh = 0; lh < logn; ++lh) {
+        const u32 half = 1u << lh;
+        for (u32 b = threadIdx.x; b < n / 2; b += FFT_THREADS) {
+            const u32 j = b & (half - 1), i0 = ((b >> lh) << (lh + 1)) + j, i1 = i0 + half;
+            const double2 x = tile[i0], y = cmul(tile[i1], tw[half + j]);
+            tile[i0] = cadd(x, y);
+            tile[i1] = csub(x, y);
         }
         __syncthreads();
+    }
+    for (u32 i = threadIdx.x; i < n; i += FFT_THREADS)
+        out[(size_t)blockIdx.x * n + i] = make_double2(tile[i].x * inv_scale, tile[i].y * inv_scale);
+}
+
+// Far pass of encode: slots -> scratch (columns in the order of their slots).  N = 256 << S rows of 256.
+// bin[j] = t_j.  grid: x = group of 4096 >> S columns, y = vector
+template <u32 S>
+__global__ __launch_bounds__(FFT_THREADS) void encode_far_kernel(const double2 *__restrict__ slots,
+                                                                 double2 *__restrict__ out,
+                                                                 const double2 *__restrict__ tw,
+                                                                 const u32 *__restrict__ bin, u32 real) {
+    constexpr u32 COLS = FFT_TILE >> S, SC = COLS / 2, ROWS = 1u << S, N = 256u << S, TPC = ROWS / 16;
+    __shared__ double2 tile[FFT_LDS];
+    const double2 *src = slots + (size_t)blockIdx.y * (N / 2) + blockIdx.x * SC;
 #pragma unroll
-        for (u32 r = 0; r < 16; ++r) v[r] = tile[fft_slot(h * 256 + c * 16 + r)];
-        fft_group<4, false>(v, tw, 1, 0);
+    for (u32 l = 0; l < FFT_TILE / 2 / FFT_THREADS; ++l) {
+        const u32 idx = threadIdx.x + FFT_THREADS * l, x = idx % SC, j = x + 128 * (idx / SC);
+        double2 z = src[j];
+        if (real) z.y = 0.0;
+        const u32 row = bin[blockIdx.x * SC + j] >> 8;
+        tile[fft_slot(row * COLS + x)] = z;
+        tile[fft_slot((ROWS - 1 - row) * COLS + SC + x)] = make_double2(z.x, -z.y);
+    }
+    __syncthreads();
+    const u32 col = threadIdx.x % COLS, q = threadIdx.x / COLS;              // q < TPC
+    const u32 t0 = bin[blockIdx.x * SC + col % SC] & 255, pcol = col < SC ? t0 : 255 - t0;
+    double2 *dst = out + (size_t)blockIdx.y * N + blockIdx.x * COLS + col;
+    // G stages on row bits B0 .. B0+G-1: a thread takes 16 >> G of the 2^(S-G) combinations of the other row bits
+    auto group = [&](auto b0, auto g, bool last) {
+        constexpr u32 B0 = decltype(b0)::value, G = decltype(g)::value, R = 1u << G;
+        double2 v[16];
+        auto row = [&](u32 m, u32 r) {
+            const u32 o = q + TPC * m;
+            return ((o >> B0) << (B0 + G)) + (r << B0) + (o & ((1u << B0) - 1));
+        };
 #pragma unroll
-        for (u32 r = 0; r < 16; ++r) tile[fft_slot(h * 256 + c * 16 + r)] = v[r];      // a thread's own slots
-        __syncthreads();
+        for (u32 m = 0; m < (16u >> G); ++m) {
 #pragma unroll
-        for (u32 r = 0; r < 16; ++r) v[r] = tile[fft_slot(h * 256 + c + 16 * r)];
-        fft_group<4, false>(v, tw, 16, c);
+            for (u32 r = 0; r < R; ++r) v[m * R + r] = tile[fft_slot(row(m, r) * COLS + col)];
+            fft_group<G, true>(v + m * R, tw, 256u << B0, ((q + TPC * m) & ((1u << B0) - 1)) * 256 + pcol);
+        }
 #pragma unroll
-        for (u32 r = 0; r < 16; ++r) v0[c + 16 * r] = v[r];
+        for (u32 m = 0; m < (16u >> G); ++m)
+#pragma unroll
+            for (u32 r = 0; r < R; ++r) {
+                if (last)
+                    dst[row(m, r) * 256] = v[m * R + r];
+                else
+                    tile[fft_slot(row(m, r) * COLS + col)] = v[m * R + r];                 // a thread's own slots
+            }
+        if (!last) __syncthreads();
+    };
+    using std::integral_constant;
+    group(integral_constant<u32, S - 4>(), integral_constant<u32, 4>(), S == 4);
+    if constexpr (S > 8) {
+        group(integral_constant<u32, S - 8>(), integral_constant<u32, 4>(), false);
+        group(integral_constant<u32, 0>(), integral_constant<u32, S - 8>(), true);
+    } else if constexpr (S > 4) {
+        group(integral_constant<u32, 0>(), integral_constant<u32, S - 4>(), true);
     }
 }
 
-// n < 4096: the whole transform of one vector in LDS, one exchange per stage.  grid: x = vector
-template <bool INV, class Coef>
-__global__ __launch_bounds__(FFT_THREADS) void fft_small_kernel(const double2 *__restrict__ in, double2 *__restrict__ out,
-                                                                const double2 *__restrict__ tw, Coef first,
-                                                                size_t coef_stride, u32 logn, u32 real,
-                                                                double inv_scale) {
-    __shared__ double2 tile[FFT_TILE / 2];
-    const u32 n = 1u << logn;
-    Coef coef = first;
-    if constexpr (INV)
-        coef.c += blockIdx.x * coef_stride;
-    else
-        coef.r += blockIdx.x * coef_stride;
-    for (u32 i = threadIdx.x; i < n; i += FFT_THREADS) {
-        double2 v;
-        if constexpr (INV) {
-            v = in[(size_t)blockIdx.x * n + i];
-            if (real) v.y = 0.0;
-        } else {
-            v = coef.get(coef.load(__brev(i) >> (32 - logn)));
-        }
-        tile[i] = v;
+// Near pass of encode: scratch -> coefficients.  colmap[place] = the column at that place of a scratch row.
+// grid: x = N / 4096, y = vector
+__global__ __launch_bounds__(FFT_THREADS) void encode_near_kernel(const double2 *__restrict__ scratch,
+                                                                  const double2 *__restrict__ tw,
+                                                                  const u32 *__restrict__ colmap, EncodeOut coef,
+                                                                  u32 logN) {
+    __shared__ double2 tile[FFT_LDS];
+    const u32 tid = threadIdx.x, h = tid >> 4, c = tid & 15, f = blockIdx.x, fb = logN - 12;
+    const double2 *v0 = scratch + ((size_t)blockIdx.y << logN) + (f << 8) + tid;
+    coef.c += (size_t)blockIdx.y << logN;
+    const u32 lo = colmap[tid];
+    double2 v[16];
+#pragma unroll
+    for (u32 r = 0; r < 16; ++r) v[r] = v0[(size_t)r << (fb + 8)];                     // run r
+#pragma unroll
+    for (u32 r = 0; r < 16; ++r) tile[fft_slot(r * 256 + lo)] = v[r];
+    __syncthreads();
+#pragma unroll
+    for (u32 r = 0; r < 16; ++r) v[r] = tile[fft_slot(h * 256 + c + 16 * r)];
+    fft_group<4, true>(v, tw, 16, c);
+#pragma unroll
+    for (u32 r = 0; r < 16; ++r) tile[fft_slot(h * 256 + c + 16 * r)] = v[r];          // a thread's own slots
+    __syncthreads();
+#pragma unroll
+    for (u32 r = 0; r < 16; ++r) v[r] = tile[fft_slot(h * 256 + c * 16 + r)];
+    fft_group<4, true>(v, tw, 1, 0);
+#pragma unroll
+    for (u32 r = 0; r < 16; ++r) tile[fft_slot(h * 256 + c * 16 + r)] = v[r];          // a thread's own slots
+    __syncthreads();
+    // thread (m & 15 = h, hh = c) writes k = m 2^(logN-8) + ..., element lo = bitrev8(m) of run bitrev4(hh)
+    const u32 ch = __brev(c) >> 28, fk = (fb ? __brev(f) >> (32 - fb) : 0) * 16 + c;
+#pragma unroll
+    for (u32 r = 0; r < 16; ++r) {
+        const u32 m = h + 16 * r;
+        if (coef.real && r >= 8) break;                                                // k >= N/2
+        coef.put((m << (logN - 8)) + fk, tile[fft_slot(ch * 256 + (__brev(m) >> 24))]);
+    }
+}
+
+// N <= 4096: the whole encode of one vector in LDS, one exchange per stage.  grid: x = vector
+__global__ __launch_bounds__(FFT_THREADS) void encode_small_kernel(const double2 *__restrict__ slots,
+                                                                   const double2 *__restrict__ tw,
+                                                                   const u32 *__restrict__ bin, EncodeOut coef,
+                                                                   u32 logN, u32 real) {
+    __shared__ double2 tile[FFT_TILE];
+    const u32 N = 1u << logN, n = N / 2;
+    coef.c += (size_t)blockIdx.x << logN;
+    for (u32 j = threadIdx.x; j < n; j += FFT_THREADS) {
+        double2 z = slots[(size_t)blockIdx.x * n + j];
+        if (real) z.y = 0.0;
+        const u32 t = bin[j];
+        tile[t] = z;
+        tile[N - 1 - t] = make_double2(z.x, -z.y);
     }
     __syncthreads();
-    for (u32 s = 0; s < logn; ++s) {
-        const u32 lh = INV ? logn - 1 - s : s, half = 1u << lh;
-        for (u32 b = threadIdx.x; b < n / 2; b += FFT_THREADS) {
+    for (u32 s = 0; s < logN; ++s) {
+        const u32 lh = logN - 1 - s, half = 1u << lh;
+        for (u32 b = threadIdx.x; b < n; b += FFT_THREADS) {
             const u32 j = b & (half - 1), i0 = ((b >> lh) << (lh + 1)) + j, i1 = i0 + half;
-            const double2 w = tw[half + j], x = tile[i0], y = INV ? tile[i1] : cmul(tile[i1], w);
+            const double2 x = tile[i0], y = tile[i1];
             tile[i0] = cadd(x, y);
-            tile[i1] = INV ? cmul_conj(csub(x, y), w) : csub(x, y);
+            tile[i1] = cmul(csub(x, y), tw[half + j]);
         }
         __syncthreads();
     }
-    for (u32 i = threadIdx.x; i < n; i += FFT_THREADS) {
-        const double2 v = tile[i];
-        if constexpr (INV)
-            coef.put(__brev(i) >> (32 - logn), v);
-        else
-            out[(size_t)blockIdx.x * n + i] = make_double2(v.x * inv_scale, v.y * inv_scale);
-    }
+    for (u32 k = threadIdx.x; k < (real ? n : N); k += FFT_THREADS) coef.put(k, tile[__brev(k) >> (32 - logN)]);
 }
 
 static int fft_tables(ckks_params *P) {
-    if (P->d_fft_tw) return CKKS_OK;
-    const u32 n = P->N / 2;
-    std::vector<double> w(2 * (size_t)n, 0.0);
+    if (P->d_fft) return CKKS_OK;
+    const u32 N = P->N, n = N / 2;
+    const size_t words = 2 * ((size_t)n + N + N) + (n + 256) / 2;           // see ckks_params::d_fft
+    std::vector<double> tab(words, 0.0);
+    double *dec = tab.data(), *enc = dec + 2 * (size_t)n, *twist = enc + 2 * (size_t)N;
+    u32 *bin = reinterpret_cast<u32 *>(twist + 2 * (size_t)N), *colmap = bin + n;
     const long double pi = 3.14159265358979323846264338327950288L;
     for (u32 h = 1; h < n; h *= 2) {
         u32 e = 1;                                          // 5^j mod 8h
         for (u32 j = 0; j < h; ++j) {
             const long double a = 2 * pi * e / (8.0L * h);
-            w[2 * (h + j)] = (double)cosl(a);
-            w[2 * (h + j) + 1] = (double)sinl(a);
+            dec[2 * (h + j)] = (double)cosl(a);
+            dec[2 * (h + j) + 1] = (double)sinl(a);
             e = e * 5 % (8 * h);
         }
     }
-    double *d_w = nullptr;
-    CKKS_HIP(hipMalloc(&d_w, w.size() * sizeof(double)));
-    hipError_t e_w = hipMemcpy(d_w, w.data(), w.size() * sizeof(double), hipMemcpyHostToDevice);
-    if (e_w != hipSuccess) {
-        hipFree(d_w);
-        return hip_fail(e_w, "hipMemcpy (transform roots)");
+    // the N-th roots of the last half length, every 2^s-th of them for the shorter ones
+    for (u32 e = 0; e < n; ++e) {
+        enc[2 * (n + e)] = (double)cosl(2 * pi * e / N);
+        enc[2 * (n + e) + 1] = (double)-sinl(2 * pi * e / N);
     }
-    P->d_fft_tw = d_w;
+    for (u32 h = n / 2; h >= 1; h /= 2)
+        for (u32 j = 0; j < h; ++j) {
+            enc[2 * (h + j)] = enc[2 * (n + j * (n / h))];
+            enc[2 * (h + j) + 1] = enc[2 * (n + j * (n / h)) + 1];
+        }
+    for (u32 k = 0; k < N; ++k) {
+        twist[2 * k] = (double)cosl(pi * k / N);
+        twist[2 * k + 1] = (double)-sinl(pi * k / N);
+    }
+    u64 e = 1;
+    for (u32 j = 0; j < n; ++j) {
+        bin[j] = (u32)((e - 1) >> 1);
+        e = e * 5 % (2ull * N);
+    }
+    if (P->logN > 12) {
+        const u32 cols = FFT_TILE >> (P->logN - 8), sc = cols / 2;          // columns of a far group
+        for (u32 pl = 0; pl < 256; ++pl) {
+            const u32 x = pl % cols, t0 = bin[pl / cols * sc + x % sc] & 255;
+            colmap[pl] = x < sc ? t0 : 255 - t0;
+        }
+    }
+    double *d = nullptr;
+    CKKS_HIP(hipMalloc(&d, words * sizeof(double)));
+    const hipError_t err = hipMemcpy(d, tab.data(), words * sizeof(double), hipMemcpyHostToDevice);
+    if (err != hipSuccess) {
+        hipFree(d);
+        return hip_fail(err, "hipMemcpy (transform tables)");
+    }
+    P->d_fft = d;
     return CKKS_OK;
 }
 
-// the far pass of a ring of 2^13 and more
-template <bool INV>
-static void launch_far(const ckks_params *P, const double2 *in, double2 *out, u32 count, u32 real, double inv_scale,
-                       hipStream_t stream) {
-    const double2 *tw = (const double2 *)P->d_fft_tw;
-#define FAR_LAUNCH(S)                                                                                              \
-    hipLaunchKernelGGL((fft_far_kernel<S, INV>), dim3(1u << (S - 4), count), dim3(FFT_THREADS), 0, stream, in, out, \
-                       tw, real, inv_scale)
-    switch (P->logN) {
-        case 13: FAR_LAUNCH(4); break;
-        case 14: FAR_LAUNCH(5); break;
-        case 15: FAR_LAUNCH(6); break;
-        case 16: FAR_LAUNCH(7); break;
-        case 17: FAR_LAUNCH(8); break;
-    }
-#undef FAR_LAUNCH
-}
+struct FftTables {
+    const double2 *dec, *enc, *twist;
+    const u32 *bin, *colmap;
+    explicit FftTables(const ckks_params *P)
+        : dec((const double2 *)P->d_fft), enc(dec + P->N / 2), twist(enc + P->N), bin((const u32 *)(twist + P->N)),
+          colmap(bin + P->N / 2) {}
+};
 
 static u64 inv_mod_host(u64 a, u64 q) {   // q prime
     unsigned __int128 r = 1, b = a % q;
@@ -354,26 +435,35 @@ int ckks_encode(ckks_params_t *P, const double *d_slots, uint32_t count, double 
     hipStream_t stream = (hipStream_t)stream_;
     int rc = fft_tables(P);
     if (rc) return rc;
-    const u32 N = P->N, n = N / 2, logn = P->logN - 1, chunk = std::min<u32>(count, ENC_CHUNK);
+    const u32 N = P->N, n = N / 2, chunk = std::min<u32>(count, ENC_CHUNK);
     const u32 real = flags & CKKS_ENCODE_REAL;
-    const double2 *tw = (const double2 *)P->d_fft_tw;
-    rc = P->ensure_scratch((size_t)chunk * n * sizeof(double2), stream);
+    const FftTables ft(P);
+    rc = P->ensure_scratch((size_t)chunk * N * sizeof(double2), stream);
     if (rc) return rc;
     double2 *v = (double2 *)P->d_scratch;
     for (u32 done = 0; done < count; done += chunk) {
         const u32 c = std::min(chunk, count - done);
         const double2 *slots = (const double2 *)d_slots + (size_t)done * n;
-        const EncodeOut out{d_coeffs + (size_t)done * N, n, real, scale / n};
-        if (n >= FFT_TILE) {
-            launch_far<true>(P, slots, v, c, real, 1.0, stream);
-            CKKS_LAUNCH_CHECK("fft_far_kernel");
-            hipLaunchKernelGGL((fft_near_kernel<true, EncodeOut>), dim3(n / FFT_TILE, c), dim3(FFT_THREADS), 0, stream, v,
-                               tw, out, (size_t)N, logn);
-            CKKS_LAUNCH_CHECK("fft_near_kernel");
-        } else {
-            hipLaunchKernelGGL((fft_small_kernel<true, EncodeOut>), dim3(c), dim3(FFT_THREADS), 0, stream, slots, nullptr,
-                               tw, out, (size_t)N, logn, real, 1.0);
-            CKKS_LAUNCH_CHECK("fft_small_kernel");
+        const EncodeOut out{d_coeffs + (size_t)done * N, ft.twist, N, real, scale / N};
+#define FAR_LAUNCH(S)                                                                                                \
+    hipLaunchKernelGGL(encode_far_kernel<S>, dim3(1u << (S - 4), c), dim3(FFT_THREADS), 0, stream, slots, v, ft.enc, \
+                       ft.bin, real)
+        switch (P->logN) {
+            case 13: FAR_LAUNCH(5); break;
+            case 14: FAR_LAUNCH(6); break;
+            case 15: FAR_LAUNCH(7); break;
+            case 16: FAR_LAUNCH(8); break;
+            case 17: FAR_LAUNCH(9); break;
+            default:
+                hipLaunchKernelGGL(encode_small_kernel, dim3(c), dim3(FFT_THREADS), 0, stream, slots, ft.enc, ft.bin, out,
+                                   P->logN, real);
+        }
+#undef FAR_LAUNCH
+        CKKS_LAUNCH_CHECK("encode_far_kernel");
+        if (P->logN > 12) {
+            hipLaunchKernelGGL(encode_near_kernel, dim3(N / FFT_TILE, c), dim3(FFT_THREADS), 0, stream, v, ft.enc,
+                               ft.colmap, out, P->logN);
+            CKKS_LAUNCH_CHECK("encode_near_kernel");
         }
     }
     return CKKS_OK;
@@ -398,7 +488,7 @@ int ckks_decode(ckks_params_t *P, const uint64_t *d_res, uint32_t nlimbs, uint32
     int rc = fft_tables(P);
     if (rc) return rc;
     const u32 N = P->N, n = N / 2, logn = P->logN - 1, chunk = std::min<u32>(count, ENC_CHUNK);
-    const double2 *tw = (const double2 *)P->d_fft_tw;
+    const FftTables ft(P);
     rc = P->ensure_scratch((size_t)chunk * n * sizeof(double2), stream);
     if (rc) return rc;
     double2 *v = (double2 *)P->d_scratch;
@@ -416,17 +506,26 @@ int ckks_decode(ckks_params_t *P, const uint64_t *d_res, uint32_t nlimbs, uint32
         const u32 c = std::min(chunk, count - done);
         double2 *slots = (double2 *)d_slots + (size_t)done * n;
         const DecodeIn in{d_res + done * stride, n, nlimbs, q0, q1, q0inv, m1, q0inv_fp, nlimbs > 1 ? 1.0 / (double)q1 : 0.0};
+#define FAR_LAUNCH(S)                                                                                                \
+    hipLaunchKernelGGL(decode_far_kernel<S>, dim3(1u << (S - 4), c), dim3(FFT_THREADS), 0, stream, v, slots, ft.dec, \
+                       1.0 / scale)
         if (n >= FFT_TILE) {
-            hipLaunchKernelGGL((fft_near_kernel<false, DecodeIn>), dim3(n / FFT_TILE, c), dim3(FFT_THREADS), 0, stream, v,
-                               tw, in, stride, logn);
-            CKKS_LAUNCH_CHECK("fft_near_kernel");
-            launch_far<false>(P, v, slots, c, 0, 1.0 / scale, stream);
-            CKKS_LAUNCH_CHECK("fft_far_kernel");
-        } else {
-            hipLaunchKernelGGL((fft_small_kernel<false, DecodeIn>), dim3(c), dim3(FFT_THREADS), 0, stream, nullptr, slots,
-                               tw, in, stride, logn, 0u, 1.0 / scale);
-            CKKS_LAUNCH_CHECK("fft_small_kernel");
+            hipLaunchKernelGGL(decode_near_kernel, dim3(n / FFT_TILE, c), dim3(FFT_THREADS), 0, stream, v, ft.dec, in, stride,
+                               logn);
+            CKKS_LAUNCH_CHECK("decode_near_kernel");
         }
+        switch (P->logN) {
+            case 13: FAR_LAUNCH(4); break;
+            case 14: FAR_LAUNCH(5); break;
+            case 15: FAR_LAUNCH(6); break;
+            case 16: FAR_LAUNCH(7); break;
+            case 17: FAR_LAUNCH(8); break;
+            default:
+                hipLaunchKernelGGL(decode_small_kernel, dim3(c), dim3(FFT_THREADS), 0, stream, slots, ft.dec, in, stride, logn,
+                                   1.0 / scale);
+        }
+#undef FAR_LAUNCH
+        CKKS_LAUNCH_CHECK("decode_far_kernel");
     }
     return CKKS_OK;
 }

@@ -451,7 +451,7 @@ int ckks_params_create(uint32_t logN, const uint64_t *q, uint32_t L, const uint6
     // at the top level (ckks_rotate_hoisted with any number of steps, ckks_ctmul, ckks_rot_first, the key holder's
     // calls), ckks_rescale of up to 64 ciphertexts, ckks_encode / ckks_decode
     if (!rc) {
-        size_t words = (size_t)128 * N + 4 * (size_t)W * N;                   // rescale; encode: 128 vectors of N/2 complex values
+        size_t words = (size_t)128 * N + 4 * (size_t)W * N;                   // rescale; encode: 64 complex vectors
         words = std::max(words, (size_t)64 * 2 * N);
         words = std::max(words, (size_t)dnum * W * N + W);                    // key generation
         if (K) words = std::max(words, (size_t)ROT_BATCH * 2 * L * N + rotate_hoisted_scratch_words(P, L, ROT_BATCH));   // ckks_shift_bank
@@ -511,7 +511,7 @@ void ckks_params_destroy(ckks_params_t *P) {
         hipFree(kv.second.d_up_mats);
         hipFree(kv.second.d_up_ft);
     }
-    hipFree(P->d_fft_tw);
+    hipFree(P->d_fft);
     hipFree(P->d_scratch);
     for (hipEvent_t ev : P->prof_ev) hipEventDestroy(ev);
     delete P;
