@@ -100,10 +100,15 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_pass_kernel(u64 *__restrict__
 // LOGR: 1 .. 5 = pass A of N = 2^(12+LOGR) (its first / last LOGR stages, registers only; a thread takes 16 residues,
 // i.e. 16 >> LOGR columns, so that short rows keep as many loads in flight per wavefront as long ones), 0 = pass B (12
 // stages in a 4096 tile)
-// FP: the kernel serves the rows whose prime is below 2^50 (fp64 butterflies) or the others (integer butterflies);
-// rows of the other kind return at once.  One kernel for both kinds needs the union of the two register budgets
-// (130 registers, 3 waves per SIMD in pass B, against 112 to 124 and 4 waves for the separate ones).
-template <bool INV, u32 LOGR, bool FP>
+// KIND: the kernel serves the rows whose prime is below 2^50 (FP_ROWS: fp64 butterflies), the others (INT_ROWS: integer
+// butterflies), rows of the other kind returning at once, or both.  One kernel for both kinds needs the union of the two
+// register budgets (130 registers, 3 waves per SIMD in pass B, against 112 to 124 and 4 waves for the separate ones), so
+// large launches go out separately; a launch that does not fill the chip (BOTH_MAX workgroups) is bound by the latency of
+// one workgroup, and two of them one after the other take twice that (the digits of one ciphertext at level 17 of 24 + 8
+// primes: 17 + 25 us; a whole rotation 182 us with two launches, 166 us with one).
+constexpr int INT_ROWS = 0, FP_ROWS = 1, BOTH_ROWS = 2;
+constexpr u32 BOTH_MAX = 2048;
+template <bool INV, u32 LOGR, int KIND>
 __global__ __launch_bounds__(NTT_THREADS) void ntt_fast_kernel(u64 *__restrict__ data,
                                                                const ModConst *__restrict__ mods,
                                                                const ModFp *__restrict__ modf,
@@ -112,11 +117,11 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fast_kernel(u64 *__restrict__
                                                                const u64 *__restrict__ ninv, LimbIds ids,
                                                                u32 n_limbs, u32 logN) {
     __shared__ u64 lds[LOGR ? 1 : FAST_LDS_WORDS];
-    const u32 row = blockIdx.y;
+    const u32 row = KIND == BOTH_ROWS ? gridDim.y - 1 - blockIdx.y : blockIdx.y;   // special limbs come last: start with them
     const u32 limb = ids.id[row % n_limbs];
     if (limb == SKIP_ROW) return;
     const ModFp mf = modf[limb];
-    if ((mf.ok != 0) != FP) return;
+    if (KIND != BOTH_ROWS && (mf.ok != 0) != (KIND == FP_ROWS)) return;
     u64 *poly = data + ((size_t)row << logN);
     auto load = [&](u32 idx) { return poly[idx]; };
     auto store = [&](u32 idx, u64 v) { poly[idx] = v; };
@@ -130,7 +135,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fast_kernel(u64 *__restrict__
                 pass_a_body<INV, LOGR>(f, (c * gridDim.x + blockIdx.x) * NTT_THREADS + threadIdx.x, load, store);
         }
     };
-    if (FP)
+    if (KIND == FP_ROWS || (KIND == BOTH_ROWS && mf.ok))
         go(make_field_fp(mf, twf, limb, logN));
     else
         go(make_field_int(mods, tw, ninv, limb, logN));
@@ -148,13 +153,17 @@ static void launch_fast(const ckks_params *p, u64 *d_data, const LimbIds &ids, u
             any_int = true;
     }
     const u32 blocks = LOGR == 0 ? p->N >> 12 : LOGR < 4 ? 1u << LOGR : 16;
-#define FAST_LAUNCH(FPK)                                                                                             \
-    hipLaunchKernelGGL((ntt_fast_kernel<INV, LOGR, FPK>), dim3(blocks, rows), dim3(NTT_THREADS), 0, stream, d_data,   \
+#define FAST_LAUNCH(KIND)                                                                                            \
+    hipLaunchKernelGGL((ntt_fast_kernel<INV, LOGR, KIND>), dim3(blocks, rows), dim3(NTT_THREADS), 0, stream, d_data,   \
                        p->d_mod, scaled_dn ? p->d_modf_dn : p->d_modf, INV ? p->d_tws_inv : p->d_tws_fwd,            \
                        INV ? p->d_twf_inv : p->d_twf_fwd, scaled_dn ? p->d_ninvs_dn : p->d_ninvs, ids, n_limbs,      \
                        p->logN)
-    if (any_fp) FAST_LAUNCH(true);
-    if (any_int) FAST_LAUNCH(false);
+    if (any_fp && any_int && (u64)blocks * rows <= BOTH_MAX) {
+        FAST_LAUNCH(BOTH_ROWS);
+    } else {
+        if (any_fp) FAST_LAUNCH(FP_ROWS);
+        if (any_int) FAST_LAUNCH(INT_ROWS);
+    }
 #undef FAST_LAUNCH
 }
 
