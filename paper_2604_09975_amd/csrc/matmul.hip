@@ -10,6 +10,7 @@
 #include "ckks_internal.h"
 #include "common_kernels.h"
 #include "mac_device.h"
+#include "ntt_device.h"
 
 namespace ckks {
 
@@ -487,6 +488,123 @@ __global__ __launch_bounds__(EW_THREADS) void to_weight_form_kernel(u64 *data, c
     }
 }
 
+// ---- rescale on rings of 2^12 .. 2^16 with every active prime below 2^50: three kernels, each reading and writing a
+// residue once.  (The plain form below takes six: copy of the dropped limb, two inverse passes, rounding terms, two forward
+// passes and the division; a ciphertext product and rescale at 2^15 151 us with it, 136 with these; a bank of 12 at 2^14 with
+// rescale 194 and 167.)
+//   rescale_intt_kernel:  inverse tile pass of the dropped limb, read where it lies;
+//   rescale_mid_kernel:   its column pass, r' = r + floor(q_l/2) mod q_l, the rounding term r' mod q_i - floor(q_l/2) mod
+//                         q_i of every remaining limb and the column pass of its forward transform, on tiles of
+//                         512 coefficients as in moddown_mid_kernel;
+//   rescale_tile_kernel:  forward tile pass and (c - NTT(delta)) q_l^-1.
+// At N = 2^12 (LOGR = 0) the tile passes are whole transforms.
+constexpr u32 RS_TILE = 512;
+
+// grid: x = 4096-residue tiles, y = row
+__global__ __launch_bounds__(NTT_THREADS) void rescale_intt_kernel(const u64 *__restrict__ in, u64 *__restrict__ r,
+                                                                   const ModFp *__restrict__ modf,
+                                                                   const double *__restrict__ twf_inv, u32 level,
+                                                                   u32 logN) {
+    __shared__ u64 lds[FAST_LDS_WORDS];
+    const u64 *src = in + (((size_t)blockIdx.y * level + level - 1) << logN);
+    u64 *dst = r + ((size_t)blockIdx.y << logN);
+    auto load = [&](u32 idx) { return src[idx]; };
+    auto store = [&](u32 idx, u64 v) { dst[idx] = v; };
+    pass_b_body<true>(make_field_fp(modf[level - 1], twf_inv, level - 1, logN), logN, lds, load, store);
+}
+
+// grid: x = tiles of 512 coefficients, y = row; out rows [rows][level-1]
+template <u32 LOGR>
+__global__ __launch_bounds__(256) void rescale_mid_kernel(const u64 *__restrict__ r, u64 *__restrict__ out,
+                                                          const ModFp *__restrict__ modf,
+                                                          const ModConst *__restrict__ mods,
+                                                          const double *__restrict__ twf_inv,
+                                                          const double *__restrict__ twf_fwd, u32 level) {
+    constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, COLS = RS_TILE >> LOGR, PER = COLS / 32;
+    __shared__ u64 lds[8 * RS_TILE];
+    const u32 tid = threadIdx.x, lane = tid & 31, grp = tid / 32, c0 = blockIdx.x * COLS, row = blockIdx.y;
+    const u32 il = level - 1;
+    const ModFp ml = modf[il];
+    if (grp == 0) {
+        const FieldFp f = make_field_fp(ml, twf_inv, il, logN);
+        const u64 *src = r + (size_t)row * N;
+#pragma unroll
+        for (u32 c = 0; c < PER; ++c) {
+            const u32 col = lane + 32 * c;
+            auto load = [&](u32 idx) { return src[idx]; };
+            auto store = [&](u32 idx, u64 v) { lds[(idx >> 12) * COLS + col] = v; };
+            if (LOGR == 0)
+                store(0, load(c0 + col));
+            else
+                pass_a_body<true, LOGR>(f, c0 + col, load, store);
+        }
+    }
+    __syncthreads();
+    const double h = (double)(mods[il].q >> 1);
+    double rp[2];
+#pragma unroll
+    for (u32 e = 0; e < 2; ++e) {
+        rp[e] = canonical_double(lds[e * 256 + tid]) + h;
+        if (rp[e] >= ml.q) rp[e] -= ml.q;                           // r' = (r + h) mod q_l
+    }
+    __syncthreads();
+    for (u32 i0 = 0; i0 < il; i0 += 8) {
+        for (u32 t = 0; t < 8 && i0 + t < il; ++t) {
+            const double q = modf[i0 + t].q, u = modf[i0 + t].u, hi = fma(-rint(h * u), q, h);
+#pragma unroll
+            for (u32 e = 0; e < 2; ++e)
+                lds[t * RS_TILE + e * 256 + tid] = (u64)__double_as_longlong(fma(-rint(rp[e] * u), q, rp[e]) - hi);
+        }
+        __syncthreads();
+        if (i0 + grp < il) {
+            const u32 i = i0 + grp;
+            const FieldFp ff = make_field_fp(modf[i], twf_fwd, i, logN);
+            u64 *dst = out + ((size_t)row * il + i) * N;
+#pragma unroll
+            for (u32 c = 0; c < PER; ++c) {
+                const u32 col = lane + 32 * c;
+                double v[R];
+#pragma unroll
+                for (u32 j = 0; j < R; ++j)
+                    v[j] = __longlong_as_double((long long)lds[grp * RS_TILE + j * COLS + col]);
+                radix_fwd<LOGR>(ff, v, 0, 0);
+#pragma unroll
+                for (u32 j = 0; j < R; ++j) dst[j * 4096 + c0 + col] = ff.out(v[j]);
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// grid: x = 4096-residue tiles, y = limb, z = row; out holds delta after its column pass on entry
+__global__ __launch_bounds__(NTT_THREADS) void rescale_tile_kernel(const u64 *__restrict__ in, u64 *out,
+                                                                   const ModFp *__restrict__ modf,
+                                                                   const ModConst *__restrict__ mods,
+                                                                   const double *__restrict__ twf_fwd,
+                                                                   const u64 *__restrict__ qlinv, u32 level, u32 logN) {
+    typedef u64 vec_t __attribute__((ext_vector_type(2)));
+    __shared__ u64 lds[FAST_LDS_WORDS];
+    const u32 i = blockIdx.y, row = blockIdx.z, tid = threadIdx.x, base = blockIdx.x << 12;
+    const u64 *src = in + (((size_t)row * level + i) << logN);
+    u64 *dst = out + (((size_t)row * (level - 1) + i) << logN);
+    const FieldFp f = make_field_fp(modf[i], twf_fwd, i, logN);
+    const double c = canonical_double(mont_mul(qlinv[i], 1, mods[i]));        // q_l^-1 (stored in Montgomery form)
+    vec_t x[8];
+#pragma unroll
+    for (u32 e = 0; e < 8; ++e) x[e] = *reinterpret_cast<const vec_t *>(src + base + 2 * (tid + 256 * e));
+    auto load = [&](u32 idx) { return dst[idx]; };
+    pass_b_fwd_to_lds<true>(f, logN, lds, load);
+#pragma unroll
+    for (u32 e = 0; e < 8; ++e) {
+        const u32 loc = 2 * (tid + 256 * e);
+#pragma unroll
+        for (u32 z = 0; z < 2; ++z)
+            x[e][z] = f.out(f.mul(canonical_double(x[e][z]) - __longlong_as_double((long long)lds[lds_pad(loc + z)]), c));
+        *reinterpret_cast<vec_t *>(dst + base + loc) = x[e];
+    }
+}
+
+// ---- rescale, plain form
 // delta[pc][i][n] = ((r + h) mod q_l) mod q_i - h mod q_i, r = coefficient-domain last limb, h = floor(q_l/2)
 __global__ __launch_bounds__(EW_THREADS) void rescale_delta_kernel(const u64 *__restrict__ r, u64 *__restrict__ out,
                                                                    const ModConst *__restrict__ mods, u32 level,
@@ -1233,6 +1351,25 @@ namespace ckks {
 static int rescale_rows(ckks_params *P, const u64 *d_in, u32 level, u32 rows, u64 *d_out, u64 *d_r,
                         hipStream_t stream) {
     const u32 N = P->N;
+    bool fused = P->logN >= 12 && P->logN <= 16;
+    for (u32 i = 0; i < level; ++i) fused = fused && (P->mod[i] >> 50) == 0;
+    if (fused) {
+        const u64 *qlinv = P->d_qlinv + (size_t)(level - 1) * P->L;
+        hipLaunchKernelGGL(rescale_intt_kernel, dim3(N >> 12, rows), dim3(NTT_THREADS), 0, stream, d_in, d_r, P->d_modf,
+                           P->d_twf_inv, level, P->logN);
+        CKKS_LAUNCH_CHECK("rescale_intt_kernel");
+        const auto mid = P->logN == 12 ? rescale_mid_kernel<0> : P->logN == 13 ? rescale_mid_kernel<1>
+                       : P->logN == 14 ? rescale_mid_kernel<2> : P->logN == 15 ? rescale_mid_kernel<3>
+                                                                               : rescale_mid_kernel<4>;
+        hipLaunchKernelGGL(mid, dim3(N / RS_TILE, rows), dim3(256), 0, stream, d_r, d_out, P->d_modf, P->d_mod,
+                           P->d_twf_inv, P->d_twf_fwd, level);
+        CKKS_LAUNCH_CHECK("rescale_mid_kernel");
+        hipLaunchKernelGGL(rescale_tile_kernel, dim3(N >> 12, level - 1, rows), dim3(NTT_THREADS), 0, stream, d_in, d_out,
+                           P->d_modf, P->d_mod, P->d_twf_fwd, qlinv, level, P->logN);
+        CKKS_LAUNCH_CHECK("rescale_tile_kernel");
+        P->limb_ntts += (u64)rows * level;
+        return CKKS_OK;
+    }
     hipLaunchKernelGGL(take_last_limb_kernel, dim3(N / EW_THREADS, rows), dim3(EW_THREADS), 0, stream, d_in, d_r,
                        level, N);
     CKKS_LAUNCH_CHECK("take_last_limb_kernel");
