@@ -28,6 +28,44 @@ __global__ __launch_bounds__(EW_THREADS) void expand_coeffs_kernel(const int64_t
     for (u32 i = 0; i < level; ++i) out[((size_t)d * level + i) * N + n] = reduce_signed(v, mods[i]);
 }
 
+// The same with the first pass of the forward transform (rings of 2^12 and more): row (d, i) of out leaves as the column
+// pass (LOGR stages) or, at N = 2^12 (LOGR = 0), the whole transform of coefficient vector d modulo limb i would leave it.
+// The canonical residues never reach memory: 32 vectors on 9 limbs at 2^15 took 16 + 18 us for the two kernels this
+// replaces, 26 us for this one (the call 71 and 55 us).
+// grid: x = workgroups of a column pass (tiles), y = d * level + i: the limbs of a vector follow each other and find its
+// coefficients in L2.
+template <u32 LOGR>
+__global__ __launch_bounds__(NTT_THREADS) void expand_pass_kernel(const int64_t *__restrict__ coef, u64 *__restrict__ out,
+                                                                  const ModConst *__restrict__ mods,
+                                                                  const ModFp *__restrict__ modf,
+                                                                  const u64 *__restrict__ tws,
+                                                                  const double *__restrict__ twf,
+                                                                  const u64 *__restrict__ ninvs, u32 level) {
+    constexpr u32 logN = 12 + LOGR;
+    __shared__ u64 lds[LOGR ? 1 : FAST_LDS_WORDS];
+    const u32 d = blockIdx.y / level, i = blockIdx.y % level;
+    const ModConst m = mods[i];
+    const ModFp mf = modf[i];
+    const int64_t *src = coef + ((size_t)d << logN);
+    u64 *dst = out + ((size_t)blockIdx.y << logN);
+    auto load = [&](u32 idx) { return reduce_signed(src[idx], m); };
+    auto store = [&](u32 idx, u64 v) { dst[idx] = v; };
+    auto go = [&](const auto &f) {
+        if constexpr (LOGR == 0) {
+            pass_b_body<false>(f, logN, lds, load, store);
+        } else {
+            constexpr u32 COLS = LOGR < 4 ? 16u >> LOGR : 1;
+#pragma unroll
+            for (u32 c = 0; c < COLS; ++c)
+                pass_a_body<false, LOGR>(f, (c * gridDim.x + blockIdx.x) * NTT_THREADS + threadIdx.x, load, store);
+        }
+    };
+    if (mf.ok)
+        go(make_field_fp(mf, twf, i, logN));
+    else
+        go(make_field_int(mods, tws, ninvs, i, logN));
+}
+
 // rows [rows][N], row r modulo limb r % level: x <- x * c mod q (c canonical, any size)
 __global__ __launch_bounds__(EW_THREADS) void scale_rows_kernel(u64 *data, const ModConst *__restrict__ mods,
                                                                 u32 level, u32 N, u64 c) {
@@ -686,10 +724,23 @@ int expand_plain(const ckks_params *P, u32 level, const int64_t *d_coeffs, u32 c
     for (u32 done = 0; done < count; done += per) {
         const u32 c = std::min(per, count - done);
         u64 *o = d_out + (size_t)done * level * N;
-        hipLaunchKernelGGL(expand_coeffs_kernel, dim3(N / EW_THREADS, c), dim3(EW_THREADS), 0, stream,
-                           d_coeffs + (size_t)done * N, o, P->d_mod, level, N);
-        CKKS_LAUNCH_CHECK("expand_coeffs_kernel");
-        int rc = launch_ntt(P, o, ids, level, c * level, false, stream);
+        int rc;
+        if (fast_ring(P) && P->logN <= 16) {
+            const auto kernel = P->logN == 12 ? expand_pass_kernel<0> : P->logN == 13 ? expand_pass_kernel<1>
+                              : P->logN == 14 ? expand_pass_kernel<2> : P->logN == 15 ? expand_pass_kernel<3>
+                                                                                      : expand_pass_kernel<4>;
+            hipLaunchKernelGGL(kernel, dim3(N >> 12, c * level), dim3(NTT_THREADS), 0, stream,
+                               d_coeffs + (size_t)done * N, o, P->d_mod, P->d_modf, P->d_tws_fwd, P->d_twf_fwd, P->d_ninvs,
+                               level);
+            CKKS_LAUNCH_CHECK("expand_pass_kernel");
+            P->limb_ntts += (u64)c * level;
+            rc = P->logN == 12 ? CKKS_OK : launch_ntt(P, o, ids, level, c * level, false, stream, 2);
+        } else {
+            hipLaunchKernelGGL(expand_coeffs_kernel, dim3(N / EW_THREADS, c), dim3(EW_THREADS), 0, stream,
+                               d_coeffs + (size_t)done * N, o, P->d_mod, level, N);
+            CKKS_LAUNCH_CHECK("expand_coeffs_kernel");
+            rc = launch_ntt(P, o, ids, level, c * level, false, stream);
+        }
         if (rc) return rc;
         if (mont) {
             hipLaunchKernelGGL(to_weight_form_kernel, dim3(N / EW_THREADS, c * level), dim3(EW_THREADS), 0, stream, o,

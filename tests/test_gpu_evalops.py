@@ -219,3 +219,19 @@ def test_probe_kernels_compute_what_they_time():
         B.ckks_probe_mulmod(P, 0, B.PROBE_INT64, 100, iters)
     with pytest.raises(B.CkksError):
         B.ckks_probe_stream(dst, src, 3)
+
+
+@pytest.mark.parametrize("logN,qbits", [(11, 50), (12, 50), (13, 50), (14, 45), (15, 50), (16, 50), (17, 50), (13, 55), (15, 60)])
+def test_plain_expand_rings(logN, qbits):
+    """Coefficients to residues and transform, on every ring the fused first pass is instantiated for and beside them, with
+    the ends of the int64 range."""
+    from paper_2604_09975_amd import binding as B
+    O = helpers.small_oracle(logN, L=3, K=1, dnum=3, qbits=qbits, pbits=57)
+    _, P = make_pair(O)
+    c = W.rng(logN).integers(-(1 << 62), 1 << 62, (2, O.N))
+    c[0, :6] = [0, 1, -1, (1 << 63) - 1, -(1 << 63), -(1 << 63) + 1]
+    got = to_host(B.ckks_plain_expand(P, 3, to_dev(c)))
+    for d in range(2):
+        for i in range(3):
+            want = O.ntt(i, np.array([int(v) % int(O.q[i]) for v in c[d]], dtype=np.uint64))
+            assert (got[d, i] == want).all(), (d, i)
