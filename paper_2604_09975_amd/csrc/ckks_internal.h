@@ -66,7 +66,7 @@ struct LevelTables {
                                   // (N = 2^12: alone, the tile pass has applied N^-1)
     // AM = alpha rounded up to a power of two, zero padding behind the digit's limbs
     double *d_up_mats = nullptr;  // [beta][K][AM][2][3]: (Q_D/q_i) 2^(25b) 2^64 mod p_k cut into three 20-bit parts
-    double *d_up_ft = nullptr;    // [beta][level+K][AM]: (Q_D/q_i) mod q_t for the ciphertext-prime targets t
+    double *d_up_ft = nullptr;    // [beta][level+K][AM]: (Q_D/q_i) mod q_t, balanced, for the ciphertext-prime targets t
 };
 
 }  // namespace ckks

@@ -215,7 +215,8 @@ int ckks_params::build_level_tables(u32 level) {
             u64 mt = mod[t2], fq = 1;
             for (u32 b = lo; b < hi; ++b)
                 if (b != i) fq = hmul(fq, mod[b] % mt, mt);
-            ft[((size_t)dj * Wl + t2) * am + da] = (double)fq;       // exact below 2^53; used for targets below 2^50
+            // balanced; used for targets below 2^50
+            ft[((size_t)dj * Wl + t2) * am + da] = fq > mt / 2 ? -(double)(mt - fq) : (double)fq;
         }
     }
     // entered into the map first, so that ckks_params_destroy frees whatever part was uploaded if a later part fails
