@@ -243,8 +243,8 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
     __shared__ u64 ylds[8 * MID_TILE];
     u64 *wlds = ylds;               // the sources live in registers once step 2 has read them: the same 32 KiB
     const u32 tid = threadIdx.x, lane = tid & 31, grp = tid / 32;   // grp < 8
-    // tsplit > 1 (few ciphertexts): the groups of targets of a tile go to tsplit workgroups, each of which redoes the
-    // cheap step 1, so that a lone decomposition still fills the chip
+    // tsplit > 1 (few ciphertexts): the groups of targets of a tile go to tsplit workgroups, each of which redoes
+    // step 1, so that a lone decomposition still fills the chip
     const u32 tile = blockIdx.x % (N / MID_TILE), tpart = blockIdx.x / (N / MID_TILE);
     const u32 c0 = tile * COLS;
     const u32 j = blockIdx.y, r = blockIdx.z;
@@ -728,13 +728,15 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
                                                           const u64 *__restrict__ ninv_dn,
                                                           const double *__restrict__ twf_fwd,
                                                           const double *__restrict__ dn_matf, u32 level, u32 K, u32 L,
-                                                          u32 ystride, u32 yoff, const u64 *__restrict__ t_rows) {
+                                                          u32 ystride, u32 yoff, const u64 *__restrict__ t_rows,
+                                                          u32 tsplit) {
     constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, COLS = MID_TILE >> LOGR, PER = COLS / 32;
     static_assert(MID_TG == 8 && KM <= 8, "the correction tiles reuse the 8 rows of special-limb tiles");
     __shared__ u64 ylds[8 * MID_TILE];
     u64 *wlds = ylds;               // y lives in registers once step 2 has read it: the same 32 KiB
     const u32 tid = threadIdx.x, lane = tid & 31, grp = tid / 32;   // grp < 8
-    const u32 c0 = blockIdx.x * COLS;
+    // tsplit > 1 (few polynomials): the groups of targets go to tsplit workgroups, each of which redoes step 1
+    const u32 c0 = blockIdx.x % (N / MID_TILE) * COLS, tpart = blockIdx.x / (N / MID_TILE);
     const u32 pc = blockIdx.y;
     if (grp < K) {
         const u32 gl = L + grp;
@@ -787,7 +789,7 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
             rp[e] = r >= ml.q ? r - ml.q : r;                       // r' = (r + h) mod q_last
         }
     }
-    for (u32 i0 = 0; i0 < n_out; i0 += MID_TG) {
+    for (u32 i0 = tpart * MID_TG; i0 < n_out; i0 += tsplit * MID_TG) {
         // one coefficient at a time: its 24 pieces are rebuilt per group of targets (24 doubles live instead of 48,
         // which is what lets four waves share a SIMD)
 #pragma unroll 1
@@ -896,11 +898,19 @@ static moddown_mid_t moddown_mid_for(const ckks_params *p) {
     }
 }
 
+// Workgroups among which ModDown splits the target groups of a tile: as many as fill the chip once (three workgroups per
+// CU at N = 2^16, 256 CUs) and no more.  One rotation at level 17 of 2^16: 256 workgroups 34 us, 768 25 us; one product at
+// 2^15 (12 + 4 primes) 128 and 256 workgroups, 19 and 14 us.  (ModUp's rule differs: its step 1 is cheap fp64 work, and 1152
+// workgroups in two rounds were no slower than 768 in one.)
+static u32 target_split(u32 workgroups, u32 groups) { return std::max<u32>(1, std::min<u32>(groups, 768 / workgroups)); }
+
 static void launch_moddown_mid(const ckks_params *p, const u64 *y, u64 *w, u32 n, u32 level, u32 ystride, u32 yoff,
                                hipStream_t stream, const u64 *t_rows = nullptr) {
-    hipLaunchKernelGGL(t_rows ? moddown_mid_for<true>(p) : moddown_mid_for<false>(p), dim3(p->N / MID_TILE, n * 2),
+    const u32 tiles = p->N / MID_TILE;
+    const u32 tsplit = target_split(tiles * n * 2, (level - (t_rows ? 1 : 0) + MID_TG - 1) / MID_TG);
+    hipLaunchKernelGGL(t_rows ? moddown_mid_for<true>(p) : moddown_mid_for<false>(p), dim3(tiles * tsplit, n * 2),
                        dim3(256), 0, stream, y, w, p->d_mod, p->d_modf, p->d_modf_dn, p->d_tws_inv, p->d_twf_inv,
-                       p->d_ninvs_dn, p->d_twf_fwd, p->d_dn_matf, level, p->K, p->L, ystride, yoff, t_rows);
+                       p->d_ninvs_dn, p->d_twf_fwd, p->d_dn_matf, level, p->K, p->L, ystride, yoff, t_rows, tsplit);
 }
 
 // base conversion P -> q_i of n*2 polynomials; the rows of polynomial pc start at row pc * ystride + yoff of y
