@@ -14,6 +14,7 @@ namespace ckks {
 constexpr u32 MAX_LIMBS = 64;     // L + K
 constexpr u32 MAX_DIGIT = 16;     // alpha and K
 constexpr u32 ROT_BATCH = 32;     // key switches per batch of kernel launches
+constexpr size_t STREAM_BYTES = (size_t)256 << 20;  // the Infinity Cache: larger arrays are streamed past the caches
 constexpr u32 SKIP_ROW = 255;     // limb id meaning "leave this row alone"
 
 // row lengths of the factor tables of the fused base conversions: powers of two, padded with zeros

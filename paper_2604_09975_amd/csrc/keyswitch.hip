@@ -218,7 +218,8 @@ __global__ __launch_bounds__(KS_THREADS) void modup_kernel(const u64 *__restrict
 //      25-bit pieces of y and 20-bit parts of the factors (6 AM exact fp64 multiply-adds, then one Montgomery reduction
 //      of the recombined 90-bit sum) -> LDS;
 //   3. group t of 32 threads: the columns of target t from LDS, first forward round (fp64 or integer butterflies), out.
-// At N = 2^12 (LOGR = 0) the tile passes are whole transforms: step 1 only scales, step 3 only stores.
+// At N = 2^12 (LOGR = 0) the tile passes are whole transforms: a thread scales, converts and stores its own coefficients,
+// without LDS (through it, 32 threads each scaled or stored a limb: MEASR12).
 // c1_half [n][level][N]: c1 after the inverse tile pass; digits [n][beta][level+K][N]: rows of targets outside the
 // digit, ready for the forward tile pass.  AM: the digit size alpha rounded up to a power of two; the factor tables are
 // padded with zeros to it.  Needs alpha, K <= 8, every active ciphertext prime below 2^50 and every special prime below
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
                                                         u32 alpha, u32 beta, u32 tsplit) {
     constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, COLS = MID_TILE >> LOGR, PER = COLS / 32;
     static_assert(UP_TG == 8 && AM <= 8, "the target tiles reuse the 8 rows of source tiles");
-    __shared__ u64 ylds[8 * MID_TILE];
+    __shared__ u64 ylds[LOGR ? 8 * MID_TILE : 1];
     u64 *wlds = ylds;               // the sources live in registers once step 2 has read them: the same 32 KiB
     const u32 tid = threadIdx.x, lane = tid & 31, grp = tid / 32;   // grp < 8
     // tsplit > 1 (few ciphertexts): the groups of targets of a tile go to tsplit workgroups, each of which redoes
@@ -250,7 +251,22 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
     const u32 j = blockIdx.y, r = blockIdx.z;
     const u32 Wl = level + K;
     const u32 lo = j * alpha, hi = min(lo + alpha, level), nd = hi - lo;
-    if (grp < nd) {
+    u64 yraw[2][AM];
+    if constexpr (LOGR == 0) {
+#pragma unroll
+        for (u32 a = 0; a < AM; ++a) {
+            yraw[0][a] = yraw[1][a] = 0;
+            if (a < nd) {
+                const u32 i = lo + a;
+                const u64 *src = c1_half + ((size_t)r * level + i) * N;
+                const FieldFp f = make_field_fp(modf_up[i], twf_inv, i, logN);
+#pragma unroll
+                for (u32 e = 0; e < 2; ++e)
+                    pass_a_body<true, 0>(f, c0 + e * 256 + tid, [&](u32 idx) { return src[idx]; },
+                                         [&](u32, u64 v) { yraw[e][a] = v; });
+            }
+        }
+    } else if (grp < nd) {
         const u32 i = lo + grp;
         const u64 *src = c1_half + ((size_t)r * level + i) * N;
         const FieldFp f = make_field_fp(modf_up[i], twf_inv, i, logN);
@@ -262,13 +278,14 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
             pass_a_body<true, LOGR>(f, c0 + col, load, store);
         }
     }
-    __syncthreads();
-    u64 yraw[2][AM];
+    if constexpr (LOGR != 0) {
+        __syncthreads();
 #pragma unroll
-    for (u32 e = 0; e < 2; ++e)
+        for (u32 e = 0; e < 2; ++e)
 #pragma unroll
-        for (u32 a = 0; a < AM; ++a) yraw[e][a] = a < nd ? ylds[a * MID_TILE + e * 256 + tid] : 0;
-    __syncthreads();                // every thread has its y: the tile may be overwritten
+            for (u32 a = 0; a < AM; ++a) yraw[e][a] = a < nd ? ylds[a * MID_TILE + e * 256 + tid] : 0;
+        __syncthreads();            // every thread has its y: the tile may be overwritten
+    }
     u64 *dig = digits + ((size_t)r * beta + j) * Wl * N;
     const u32 nt = Wl - nd;                                          // targets: all rows outside the digit
     for (u32 u0 = tpart * UP_TG; u0 < nt; u0 += tsplit * UP_TG) {
@@ -307,7 +324,11 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
                         l += s1.l;
                     }
                     const double c = rint(fma(h, u, l * u));
-                    res = (u64)__double_as_longlong(fma(-c, q, h) + l);
+                    const double v = fma(-c, q, h) + l;
+                    if constexpr (LOGR == 0)
+                        res = make_field_fp(modf[t], twf_fwd, t, logN).out(v);
+                    else
+                        res = (u64)__double_as_longlong(v);
                 } else {
                     // target among the special primes: sum_a y_a F_a with F_a 2^64 2^(25b) mod p in 20-bit parts
                     const u32 k = t - level;
@@ -333,9 +354,13 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
                     acc_add(acc, u128{i2 << 40, i2 >> 24});
                     res = redc_wide(acc, mods[L + k]);               // canonical: the factors carry 2^64
                 }
-                wlds[tt * MID_TILE + e * 256 + tid] = res;
+                if constexpr (LOGR == 0)
+                    dig[(size_t)t * N + c0 + e * 256 + tid] = res;
+                else
+                    wlds[tt * MID_TILE + e * 256 + tid] = res;
             }
         }
+        if constexpr (LOGR == 0) continue;
         __syncthreads();
         if (u0 + grp < nt) {
             const u32 uu = u0 + grp, t = uu < lo ? uu : uu + nd;
@@ -672,7 +697,7 @@ __global__ __launch_bounds__(KS_THREADS) void moddown_conv_kernel(const u64 *__r
 //   2. every thread: its two coefficients' y_k cut into 20-bit pieces, then for each group of
 //      MID_TG target limbs the exact fp64 sums of moddown_conv_kernel -> w in LDS;
 //   3. group t of 32 threads: the columns of w_t from LDS, first forward round, out.
-// At N = 2^12 (LOGR = 0) the tile passes are whole transforms and this is the conversion alone.
+// At N = 2^12 (LOGR = 0) the tile passes are whole transforms and this is the conversion alone, without LDS.
 // y: rows (pc*ystride + yoff + k) hold the special limbs after the inverse tile pass; w [pc][level][N] receives the
 // correction ready for the forward tile pass.  Needs K <= 8, every target below 2^50 and every special prime below
 // 2^60 (the launcher checks).  grid: x = column tile, y = pc.
@@ -729,16 +754,23 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
                                                           const double *__restrict__ twf_fwd,
                                                           const double *__restrict__ dn_matf, u32 level, u32 K, u32 L,
                                                           u32 ystride, u32 yoff, const u64 *__restrict__ t_rows,
-                                                          u32 tsplit) {
+                                                          u32 tsplit, bool streamed) {
     constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, COLS = MID_TILE >> LOGR, PER = COLS / 32;
     static_assert(MID_TG == 8 && KM <= 8, "the correction tiles reuse the 8 rows of special-limb tiles");
-    __shared__ u64 ylds[8 * MID_TILE];
+    __shared__ u64 ylds[LOGR ? 8 * MID_TILE : 1];
     u64 *wlds = ylds;               // y lives in registers once step 2 has read it: the same 32 KiB
     const u32 tid = threadIdx.x, lane = tid & 31, grp = tid / 32;   // grp < 8
     // tsplit > 1 (few polynomials): the groups of targets go to tsplit workgroups, each of which redoes step 1
     const u32 c0 = blockIdx.x % (N / MID_TILE) * COLS, tpart = blockIdx.x / (N / MID_TILE);
     const u32 pc = blockIdx.y;
-    if (grp < K) {
+    u64 yraw[2][KM];
+    if constexpr (LOGR == 0) {
+#pragma unroll
+        for (u32 k = 0; k < KM; ++k)
+#pragma unroll
+            for (u32 e = 0; e < 2; ++e)                              // the tile pass was the whole transform, scaled
+                yraw[e][k] = k < K ? y[((size_t)pc * ystride + yoff + k) * N + c0 + e * 256 + tid] : 0;
+    } else if (grp < K) {
         const u32 gl = L + grp;
         const u64 *src = y + ((size_t)pc * ystride + yoff + grp) * N;
         const ModFp mf = modf_dn[gl];
@@ -747,22 +779,21 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
             const u32 col = lane + 32 * c;
             auto load = [&](u32 idx) { return src[idx]; };
             auto store = [&](u32 idx, u64 v) { ylds[grp * MID_TILE + (idx >> 12) * COLS + col] = v; };
-            if (LOGR == 0)
-                store(0, load(c0 + col));                            // the tile pass was the whole transform, scaled
-            else if (mf.ok)
+            if (mf.ok)
                 pass_a_body<true, LOGR>(make_field_fp(mf, twf_inv, gl, logN), c0 + col, load, store);
             else
                 pass_a_body<true, LOGR>(make_field_int(mods, tw_inv, ninv_dn, gl, logN), c0 + col, load, store);
         }
     }
-    __syncthreads();
-    // the two coefficients of this thread leave LDS as they are
-    u64 yraw[2][KM];
+    if constexpr (LOGR != 0) {
+        __syncthreads();
+        // the two coefficients of this thread leave LDS as they are
 #pragma unroll
-    for (u32 e = 0; e < 2; ++e)
+        for (u32 e = 0; e < 2; ++e)
 #pragma unroll
-        for (u32 k = 0; k < KM; ++k) yraw[e][k] = k < K ? ylds[k * MID_TILE + e * 256 + tid] : 0;
-    __syncthreads();                // every thread has its y: the tile may be overwritten
+            for (u32 k = 0; k < KM; ++k) yraw[e][k] = k < K ? ylds[k * MID_TILE + e * 256 + tid] : 0;
+        __syncthreads();            // every thread has its y: the tile may be overwritten
+    }
     // rescale: the dropped limb first
     double rp[2] = {0.0, 0.0}, hq = 0.0;
     const u32 n_out = RESC ? level - 1 : level;
@@ -812,9 +843,13 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
                     fi.norm(ri);                                    // r' mod q_i
                     v += ri - hi_;                                  // |.| < 2q: the forward round normalises
                 }
-                wlds[t * MID_TILE + e * 256 + tid] = (u64)__double_as_longlong(v);
+                if constexpr (LOGR == 0)
+                    w[((size_t)pc * level + i) * N + c0 + e * 256 + tid] = make_field_fp(modf[i], twf_fwd, i, logN).out(v);
+                else
+                    wlds[t * MID_TILE + e * 256 + tid] = (u64)__double_as_longlong(v);
             }
         }
+        if constexpr (LOGR == 0) continue;
         __syncthreads();
         if (i0 + grp < n_out) {
             const u32 i = i0 + grp;
@@ -828,8 +863,15 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
                 for (u32 j = 0; j < R; ++j)
                     v[j] = __longlong_as_double((long long)wlds[grp * MID_TILE + j * COLS + col]);
                 radix_fwd<LOGR>(ff, v, 0, 0);
+                // w of a large batch goes past the caches: it is read once, by the next kernel, which then finds the digit
+                // rows there (passb_final_kernel of 24 switches 524 -> 510 us)
+                if (streamed) {
 #pragma unroll
-                for (u32 j = 0; j < R; ++j) dst[j * 4096 + c0 + col] = ff.out(v[j]);
+                    for (u32 j = 0; j < R; ++j) __builtin_nontemporal_store(ff.out(v[j]), dst + j * 4096 + c0 + col);
+                } else {
+#pragma unroll
+                    for (u32 j = 0; j < R; ++j) dst[j * 4096 + c0 + col] = ff.out(v[j]);
+                }
             }
         }
         __syncthreads();
@@ -910,7 +952,8 @@ static void launch_moddown_mid(const ckks_params *p, const u64 *y, u64 *w, u32 n
     const u32 tsplit = target_split(tiles * n * 2, (level - (t_rows ? 1 : 0) + MID_TG - 1) / MID_TG);
     hipLaunchKernelGGL(t_rows ? moddown_mid_for<true>(p) : moddown_mid_for<false>(p), dim3(tiles * tsplit, n * 2),
                        dim3(256), 0, stream, y, w, p->d_mod, p->d_modf, p->d_modf_dn, p->d_tws_inv, p->d_twf_inv,
-                       p->d_ninvs_dn, p->d_twf_fwd, p->d_dn_matf, level, p->K, p->L, ystride, yoff, t_rows, tsplit);
+                       p->d_ninvs_dn, p->d_twf_fwd, p->d_dn_matf, level, p->K, p->L, ystride, yoff, t_rows, tsplit,
+                       (size_t)n * 2 * level * p->N * sizeof(u64) > STREAM_BYTES);
 }
 
 // base conversion P -> q_i of n*2 polynomials; the rows of polynomial pc start at row pc * ystride + yoff of y

@@ -294,7 +294,11 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
                     vec_t o;
                     o[0] = a[t][c][2 * h].canonical(q, u);
                     o[1] = a[t][c][2 * h + 1].canonical(q, u);
-                    *reinterpret_cast<vec_t *>(acc + ((size_t)(bpt + t) * 2 + c) * w_stride + row + kk[h]) = o;
+                    vec_t *dst = reinterpret_cast<vec_t *>(acc + ((size_t)(bpt + t) * 2 + c) * w_stride + row + kk[h]);
+                    if ((size_t)BP * 2 * w_stride * sizeof(u64) > STREAM_BYTES)
+                        __builtin_nontemporal_store(o, dst);       // the bank keeps its place in L2 (8449 -> 8316 us)
+                    else
+                        *dst = o;
                 }
         }
     }

@@ -107,8 +107,12 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_pass_kernel(u64 *__restrict__
 // one workgroup, and two of them one after the other take twice that (the digits of one ciphertext at level 17 of 24 + 8
 // primes: 17 + 25 us; a whole rotation 182 us with two launches, 166 us with one).
 constexpr int INT_ROWS = 0, FP_ROWS = 1, BOTH_ROWS = 2;
+// + STREAMED: residues go past the caches' replacement order (arrays above STREAM_BYTES): a pass uses each once, and the
+// twiddles, as many bytes as a tile and shared by the rows of a limb, stay in L2.  64 x 24 rows at 2^16: tile pass 409 ->
+// 383 us, column pass 273 -> 250.  Below that the next pass finds them there: 25 x 14 rows at 2^16 164 us, streamed 182.
+constexpr int STREAMED = 4;
 constexpr u32 BOTH_MAX = 2048;
-template <bool INV, u32 LOGR, int KIND>
+template <bool INV, u32 LOGR, int KIND_NT>
 __global__ __launch_bounds__(NTT_THREADS) void ntt_fast_kernel(u64 *__restrict__ data,
                                                                const ModConst *__restrict__ mods,
                                                                const ModFp *__restrict__ modf,
@@ -116,6 +120,8 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fast_kernel(u64 *__restrict__
                                                                const double *__restrict__ twf,
                                                                const u64 *__restrict__ ninv, LimbIds ids,
                                                                u32 n_limbs, u32 logN) {
+    constexpr int KIND = KIND_NT & 3;
+    constexpr bool NT = (KIND_NT & STREAMED) != 0;
     __shared__ u64 lds[LOGR ? 1 : FAST_LDS_WORDS];
     const u32 row = KIND == BOTH_ROWS ? gridDim.y - 1 - blockIdx.y : blockIdx.y;   // special limbs come last: start with them
     const u32 limb = ids.id[row % n_limbs];
@@ -123,8 +129,13 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fast_kernel(u64 *__restrict__
     const ModFp mf = modf[limb];
     if (KIND != BOTH_ROWS && (mf.ok != 0) != (KIND == FP_ROWS)) return;
     u64 *poly = data + ((size_t)row << logN);
-    auto load = [&](u32 idx) { return poly[idx]; };
-    auto store = [&](u32 idx, u64 v) { poly[idx] = v; };
+    auto load = [&](u32 idx) { return NT ? __builtin_nontemporal_load(poly + idx) : poly[idx]; };
+    auto store = [&](u32 idx, u64 v) {
+        if (NT)
+            __builtin_nontemporal_store(v, poly + idx);
+        else
+            poly[idx] = v;
+    };
     auto go = [&](const auto &f) {
         if constexpr (LOGR == 0) {
             pass_b_body<INV>(f, logN, lds, load, store);
@@ -160,6 +171,9 @@ static void launch_fast(const ckks_params *p, u64 *d_data, const LimbIds &ids, u
                        p->logN)
     if (any_fp && any_int && (u64)blocks * rows <= BOTH_MAX) {
         FAST_LAUNCH(BOTH_ROWS);
+    } else if ((u64)rows * p->N * sizeof(u64) > STREAM_BYTES) {
+        if (any_fp) FAST_LAUNCH(FP_ROWS + STREAMED);
+        if (any_int) FAST_LAUNCH(INT_ROWS + STREAMED);
     } else {
         if (any_fp) FAST_LAUNCH(FP_ROWS);
         if (any_int) FAST_LAUNCH(INT_ROWS);
