@@ -22,6 +22,7 @@ sys.path.insert(0, ROOT)
 
 FP64_ISSUE_PEAK = 256 * 64 * 2.4e9      # fp64 vector instructions per second per lane-op: 256 CUs x 64 lanes x 2.4 GHz (78.6 TFLOP/s / 2)
 HBM_PEAK_GBS = 8000.0
+MAC_INSTS = 4.0                         # fp64 instructions of one product in an exact two-double sum: two FMAs, two additions
 GIANT_NAMES = {True: "one ModDown per output block (rotated accumulators summed over the extended basis)",
                False: "one complete key switch per rotation"}
 
@@ -671,9 +672,9 @@ def main():
         n_cplx = G * n1 * (B_out // 2) * N2
         mac_bytes += n_cplx * level * (limb_poly - half_limb_packed)
         mac_bytes_8 += n_cplx * level * limb_poly // 2
-    # the same launch in double-precision operations: 7 per residue product (exact product split, quotient,
-    # remainder, two additions), 4 products per stored weight residue
-    mac_ops = 7.0 * 4.0 * n_diag * level * (N // 2)
+    # the same launch in double-precision operations: MAC_INSTS per residue product (the quotient is taken once per
+    # eight products, not counted here), 4 products per stored weight residue
+    mac_ops = MAC_INSTS * 4.0 * n_diag * level * (N // 2)
     achieved = mac_bytes / (mac_ms * 1e-3) / 1e9
     ks_bytes = key_switch_bytes(N, level, P.K, P.L, P.dnum)
     traffic = read_traffic(spec.name, n1) if not (args.fused_qk or args.pair_compression) else None
@@ -718,7 +719,7 @@ def main():
                          "frac_as_stored": (step_bytes_stored / (ms_per_step * 1e-3)) / (HBM_PEAK_GBS * 1e9)},
         "max_abs_err": max_err,
         "wall_s_timed_region": wall,
-        "roofline": {"bound": "hbm", "kernel": "diag_mac_sym_kernel", "achieved": achieved, "peak": HBM_PEAK_GBS,
+        "roofline": {"bound": "hbm", "kernel": "diag_mac_kernel", "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "traffic_source": "profiles/bert_qkv_diag_mac_hbm_traffic.txt (rocprofv3 --pmc FETCH_SIZE / "
                                        "WRITE_SIZE runs of this command, committed; not measured in this run)"
@@ -736,7 +737,7 @@ def main():
     out["measured_ceilings"] = ceil
     out["roofline"]["frac_of_measured_read"] = achieved / ceil["read_GBps"]
     if "fp64_mulmod_per_s" in ceil:     # 4 products per stored weight residue, against the bare product chain
-        out["roofline"]["frac_of_measured_fp64_mulmod"] = (mac_ops / 7.0) / (mac_ms * 1e-3) / ceil["fp64_mulmod_per_s"]
+        out["roofline"]["frac_of_measured_fp64_mulmod"] = (mac_ops / MAC_INSTS) / (mac_ms * 1e-3) / ceil["fp64_mulmod_per_s"]
     if steps:
         out["hoisted_batch"]["frac_of_measured_copy"] = ks_bytes * ks_per_s / (ceil["copy_GBps"] * 1e9)
     if not args.no_extras and not (args.fused_qk or args.pair_compression or args.n1):

@@ -116,8 +116,9 @@ static inline PackedShape packed_shape(u32 N, u32 level, u32 GQ, u32 BP, bool wh
 // swizzle: workgroups go to the XCDs round-robin and each XCD has its own L2, so the linear workgroup id is unfolded to
 // let one XCD walk all (b,p) tiles of a run of coefficients back to back: the bank lines of that run are then fetched
 // into one L2 once.
-// What bounds it (QKV layer, 38.2 GB of records, 2.4 GB of bank, 1.8 GB of sums): memory.  8.45 ms; without the products
-// 8.40, without the record loads 4.36, without the bank loads 7.05 (5.4 TB/s, what a plain read reaches).  The kernel with
+// What bounds it (QKV layer, 34.0 GB of records, 2.4 GB of bank, 1.8 GB of sums): memory.  8.32 ms; without the products
+// 8.40, without the record loads 4.36, without the bank loads 7.05 (5.1 TB/s; a plain read reaches 5.3) when the whole
+// took 8.45.  The kernel with
 // a quotient per product was bound by fp64 issue: 8.66 ms with the vector units 92 % busy; these sums keep them 55 % busy.
 template <bool SYM, bool PACKED>
 __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *__restrict__ bank,

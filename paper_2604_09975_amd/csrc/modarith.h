@@ -1,9 +1,10 @@
 // 64-bit modular arithmetic for gfx950, built from 32x32->64 multiply-adds.
 //
 // All residues live in canonical form [0, q) with q < 2^62.  Every constant
-// operand the library owns (twiddles, base-conversion factors, key and weight
-// limbs) is stored in Montgomery form x*2^64 mod q, so that one Montgomery
-// reduction of (canonical * Montgomery-form) lands back in canonical form.
+// operand of this arithmetic that the library owns (twiddles, base-conversion
+// factors, key and weight limbs on primes from 2^50 up) is stored in Montgomery
+// form x*2^64 mod q, so that one Montgomery reduction of (canonical *
+// Montgomery-form) lands back in canonical form.  Limbs below 2^50 are doubles.
 // Sums of products are kept as 128-bit integers and reduced once.
 #pragma once
 #include <hip/hip_runtime.h>
