@@ -324,14 +324,15 @@ int ckks_client_decrypt(ckks_params_t *params, const ckks_secret_t *secret, cons
 /* d_slots: device, [count][n] complex doubles (re, im interleaved).  d_coeffs: device, int64 [count][N], the
  * nearest integers to scale * m_k, ready for ckks_client_encrypt, ckks_plain_expand or
  * ckks_weights_set_diagonals.  scale * max|z| must stay below 2^62.  Enqueues on `stream`; uses the library's
- * scratch arena (64 vectors per pass). */
+ * scratch arena (64 vectors per pass).  d_coeffs may overlap d_slots (both may be one buffer), since a pass reads its
+ * vectors before it writes: CKKS_E_INVAL if a pass would write over slots of a later one. */
 int ckks_encode(ckks_params_t *params, const double *d_slots, uint32_t count, double scale, uint32_t flags,
                 int64_t *d_coeffs, void *stream);
 
 /* d_res: device, [count][nlimbs][N] canonical residues of the plaintext polynomial on the first nlimbs (1 or 2)
  * ciphertext primes, coefficient domain (what ckks_client_decrypt writes); the centred lift must be the
  * plaintext itself, i.e. |coefficients| < q_0/2 (or q_0*q_1/2).  d_slots: device, [count][n] complex doubles,
- * m(zeta^(5^j)) / scale. */
+ * m(zeta^(5^j)) / scale; may overlap d_res as d_coeffs may overlap d_slots in ckks_encode. */
 int ckks_decode(ckks_params_t *params, const uint64_t *d_res, uint32_t nlimbs, uint32_t count, double scale,
                 double *d_slots, void *stream);
 

@@ -415,6 +415,16 @@ static u64 inv_mod_host(u64 a, u64 q) {   // q prime
     return (u64)r;
 }
 
+// The vectors go chunk by chunk, each chunk read whole before any of it is written: in [count][win] words, out
+// [count][wout].  What may then happen to buffers that overlap.
+enum Overlap { APART, SERVED, REFUSED };   // REFUSED: a chunk would write over words that a later one reads
+static Overlap overlap_of(const void *in, size_t win, const void *out, size_t wout, u32 count) {
+    if (!words_overlap(in, count * win, out, count * wout)) return APART;
+    for (size_t done = ENC_CHUNK; done < count; done += ENC_CHUNK)
+        if (words_overlap((const u64 *)in + done * win, (count - done) * win, out, done * wout)) return REFUSED;
+    return SERVED;
+}
+
 }  // namespace ckks
 
 using namespace ckks;
@@ -432,11 +442,17 @@ int ckks_encode(ckks_params_t *P, const double *d_slots, uint32_t count, double 
         return CKKS_E_INVAL;
     }
     if (count == 0) return CKKS_OK;
+    const Overlap lap = overlap_of(d_slots, P->N, d_coeffs, P->N, count);
+    if (lap == REFUSED) {
+        set_error("ckks_encode: d_coeffs overlaps slots that are read after it is written");
+        return CKKS_E_INVAL;
+    }
     hipStream_t stream = (hipStream_t)stream_;
     int rc = fft_tables(P);
     if (rc) return rc;
     const u32 N = P->N, n = N / 2, chunk = std::min<u32>(count, ENC_CHUNK);
     const u32 real = flags & CKKS_ENCODE_REAL;
+    const bool aside = lap != APART && P->logN <= 12;     // one kernel reads and writes: its results wait in the scratch
     const FftTables ft(P);
     rc = P->ensure_scratch((size_t)chunk * N * sizeof(double2), stream);
     if (rc) return rc;
@@ -444,7 +460,8 @@ int ckks_encode(ckks_params_t *P, const double *d_slots, uint32_t count, double 
     for (u32 done = 0; done < count; done += chunk) {
         const u32 c = std::min(chunk, count - done);
         const double2 *slots = (const double2 *)d_slots + (size_t)done * n;
-        const EncodeOut out{d_coeffs + (size_t)done * N, ft.twist, N, real, scale / N};
+        int64_t *coeffs = d_coeffs + (size_t)done * N;
+        const EncodeOut out{aside ? (int64_t *)v : coeffs, ft.twist, N, real, scale / N};
 #define FAR_LAUNCH(S)                                                                                                \
     hipLaunchKernelGGL(encode_far_kernel<S>, dim3(1u << (S - 4), c), dim3(FFT_THREADS), 0, stream, slots, v, ft.enc, \
                        ft.bin, real)
@@ -460,6 +477,7 @@ int ckks_encode(ckks_params_t *P, const double *d_slots, uint32_t count, double 
         }
 #undef FAR_LAUNCH
         CKKS_LAUNCH_CHECK("encode_far_kernel");
+        if (aside) CKKS_HIP(hipMemcpyAsync(coeffs, v, (size_t)c * N * sizeof(u64), hipMemcpyDeviceToDevice, stream));
         if (P->logN > 12) {
             hipLaunchKernelGGL(encode_near_kernel, dim3(N / FFT_TILE, c), dim3(FFT_THREADS), 0, stream, v, ft.enc,
                                ft.colmap, out, P->logN);
@@ -484,6 +502,12 @@ int ckks_decode(ckks_params_t *P, const uint64_t *d_res, uint32_t nlimbs, uint32
         return CKKS_E_INVAL;
     }
     if (count == 0) return CKKS_OK;
+    const Overlap lap = overlap_of(d_res, (size_t)nlimbs * P->N, d_slots, P->N, count);
+    if (lap == REFUSED) {
+        set_error("ckks_decode: d_slots overlaps residues that are read after it is written");
+        return CKKS_E_INVAL;
+    }
+    const bool aside = lap != APART && P->logN <= 12;     // as in ckks_encode
     hipStream_t stream = (hipStream_t)stream_;
     int rc = fft_tables(P);
     if (rc) return rc;
@@ -521,11 +545,12 @@ int ckks_decode(ckks_params_t *P, const uint64_t *d_res, uint32_t nlimbs, uint32
             case 16: FAR_LAUNCH(7); break;
             case 17: FAR_LAUNCH(8); break;
             default:
-                hipLaunchKernelGGL(decode_small_kernel, dim3(c), dim3(FFT_THREADS), 0, stream, slots, ft.dec, in, stride, logn,
-                                   1.0 / scale);
+                hipLaunchKernelGGL(decode_small_kernel, dim3(c), dim3(FFT_THREADS), 0, stream, aside ? v : slots, ft.dec, in,
+                                   stride, logn, 1.0 / scale);
         }
 #undef FAR_LAUNCH
         CKKS_LAUNCH_CHECK("decode_far_kernel");
+        if (aside) CKKS_HIP(hipMemcpyAsync(slots, v, (size_t)c * n * sizeof(double2), hipMemcpyDeviceToDevice, stream));
     }
     return CKKS_OK;
 }

@@ -181,3 +181,41 @@ def test_two_limb_lift_at_the_ends_of_its_range(logN, qbits):
     got = B.ckks_decode(P, res, 2, 1.0).cpu().numpy()
     for i, v in enumerate(vals):
         assert np.abs(got[i].real - float(v)).max() <= abs(v) * 2.0 ** -51 and np.abs(got[i].imag).max() == 0, v
+
+
+@pytest.mark.parametrize("count", [1, 5, 64, 70, 130])
+@pytest.mark.parametrize("logN", [10, 12, 13])
+def test_buffers_that_overlap(logN, count):
+    """Slots written over the residues they come from (one and two limbs) and coefficients over their slots, at the same
+    place and one vector below, are what separate buffers give, however the 64 vectors of a pass and the workgroups of a
+    launch fall; an output one vector above its input is refused once a second pass would read what the first has written."""
+    from paper_2604_09975_amd import binding as B
+    O = helpers.small_oracle(logN, L=3, K=1, dnum=3, qbits=45, pbits=47)
+    _, P = make_pair(O)
+    N, n = O.N, O.n
+    r = W.rng(620 + logN)
+    for nlimbs in (1, 2):
+        res = torch.from_numpy(W.uniform_residues(r, O.q[:nlimbs], N, lead=(count,)).view(np.int64)).cuda()
+        want = B.ckks_decode(P, res, nlimbs, 2.0**30)
+        for below in (0, 1):
+            buf = torch.empty((below + count * nlimbs, N), dtype=torch.int64, device="cuda")
+            src = buf[below:].view(count, nlimbs, N)
+            src.copy_(res)
+            dst = buf[:count].view(-1).view(torch.complex128).view(count, n)
+            assert torch.equal(B.ckks_decode(P, src, nlimbs, 2.0**30, d_slots=dst), want)
+    z = _cdev(_slots(r, count, n))
+    want = B.ckks_encode(P, z, 2.0**30)
+    for below in (0, 1):
+        buf = torch.empty((below + count, n), dtype=torch.complex128, device="cuda")
+        buf[below:].copy_(z)
+        dst = torch.view_as_real(buf[:count]).view(torch.int64).view(count, N)
+        assert torch.equal(B.ckks_encode(P, buf[below:], 2.0**30, d_coeffs=dst), want)
+    buf = torch.empty((count + 1, n), dtype=torch.complex128, device="cuda")
+    buf[:count].copy_(z)
+    dst = torch.view_as_real(buf[1:]).view(torch.int64).view(count, N)
+    if count <= 64:
+        assert torch.equal(B.ckks_encode(P, buf[:count], 2.0**30, d_coeffs=dst), want)
+    else:
+        with pytest.raises(B.CkksError) as e:
+            B.ckks_encode(P, buf[:count], 2.0**30, d_coeffs=dst)
+        assert e.value.code == -1 and "overlaps" in str(e.value)
