@@ -217,7 +217,8 @@ int ckks_ctpt_matmul(ckks_params_t *params, const ckks_weights_t *w, const uint6
 
 /* Plaintext in evaluation form for ckks_ptmul / ckks_rot_first: int64 coefficient polynomials d_coeffs
  * [count][N] (an encoding at the caller's scale, Sec. 2.2) -> canonical NTT-domain residues d_out
- * [count][level][N] on limbs 0..level-1. */
+ * [count][level][N] on limbs 0..level-1.  d_coeffs may lie on a row of d_out if count = 1, and start where d_out does if
+ * level = 1; CKKS_E_INVAL for any other overlap. */
 int ckks_plain_expand(const ckks_params_t *params, uint32_t level, const int64_t *d_coeffs, uint32_t count,
                       uint64_t *d_out, void *stream);
 

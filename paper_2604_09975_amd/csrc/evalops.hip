@@ -182,6 +182,13 @@ int ckks_plain_expand(const ckks_params_t *P, uint32_t level, const int64_t *d_c
     }
     int rc = check_level(P, level, 1, "ckks_plain_expand");
     if (rc || count == 0) return rc;
+    // residues may replace coefficients only where each takes the place of its own one, or of one read with it
+    const ptrdiff_t off = (const char *)d_coeffs - (const char *)d_out;
+    if (words_overlap(d_coeffs, (size_t)count * P->N, d_out, (size_t)count * level * P->N) &&
+        (off % (ptrdiff_t)(P->N * sizeof(u64)) != 0 || (count > 1 && (level > 1 || off != 0)))) {
+        set_error("ckks_plain_expand: d_out overlaps coefficients that are read after it is written");
+        return CKKS_E_INVAL;
+    }
     return expand_plain(P, level, d_coeffs, count, d_out, false, (hipStream_t)stream);
 }
 

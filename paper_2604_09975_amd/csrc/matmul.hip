@@ -730,7 +730,8 @@ int expand_plain(const ckks_params *P, u32 level, const int64_t *d_coeffs, u32 c
         const u32 c = std::min(per, count - done);
         u64 *o = d_out + (size_t)done * level * N;
         int rc;
-        if (fast_ring(P) && P->logN <= 16) {
+        // (the fused pass reads a vector once per limb, so its rows may not lie on the vector)
+        if (fast_ring(P) && P->logN <= 16 && !words_overlap(d_coeffs, (size_t)count * N, d_out, (size_t)count * level * N)) {
             const auto kernel = P->logN == 12 ? expand_pass_kernel<0> : P->logN == 13 ? expand_pass_kernel<1>
                               : P->logN == 14 ? expand_pass_kernel<2> : P->logN == 15 ? expand_pass_kernel<3>
                                                                                       : expand_pass_kernel<4>;

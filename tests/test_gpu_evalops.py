@@ -235,3 +235,26 @@ def test_plain_expand_rings(logN, qbits):
         for i in range(3):
             want = O.ntt(i, np.array([int(v) % int(O.q[i]) for v in c[d]], dtype=np.uint64))
             assert (got[d, i] == want).all(), (d, i)
+
+
+@pytest.mark.parametrize("logN", [11, 12, 13, 15])
+def test_plain_expand_onto_its_coefficients(logN):
+    """One vector on any row of its residues, and any number of vectors on one limb at their own places, give what separate
+    buffers give; other overlaps, where a row would be written before it is read for another, are refused."""
+    from paper_2604_09975_amd import binding as B
+    O = helpers.small_oracle(logN, L=3, K=1, dnum=3, qbits=45, pbits=47)
+    _, P = make_pair(O)
+    N = O.N
+    c = torch.from_numpy(W.rng(logN).integers(-(1 << 40), 1 << 40, (5, N))).cuda()
+    want = B.ckks_plain_expand(P, 3, c[:1])
+    for row in range(3):
+        buf = torch.zeros((1, 3, N), dtype=torch.int64, device="cuda")
+        buf[0, row].copy_(c[0])
+        assert torch.equal(B.ckks_plain_expand(P, 3, buf[0, row], buf), want), row
+    buf = c.clone()
+    assert torch.equal(B.ckks_plain_expand(P, 1, buf, buf.view(5, 1, N)), B.ckks_plain_expand(P, 1, c))
+    buf = torch.zeros(6 * N, dtype=torch.int64, device="cuda")
+    for count, level, at in ((2, 3, 0), (2, 3, 4 * N), (5, 1, N), (1, 1, 8), (1, 3, N + 2)):
+        with pytest.raises(B.CkksError) as e:
+            B.ckks_plain_expand(P, level, buf[at:at + count * N], buf[:count * level * N])
+        assert e.value.code == -1 and "overlaps" in str(e.value)
