@@ -124,6 +124,10 @@ static int shift_bank(ckks_params_t *P, const uint64_t *d_ct_in, uint32_t level,
     }
     // scratch: rotated copies of one chunk of outputs, then the hoisted digits and the switch workspace
     const u32 chunk_out = MASK_OUTS;
+    // masks that lie in the output area: one output after the other, so that an output may replace masks already used
+    u32 per = MASK_OUTS;
+    for (size_t s = 0; s < gel.size(); ++s)
+        if (words_overlap(masks[s], (size_t)level * N, d_ct_out, (size_t)n_out * ctw)) per = 1;
     const size_t rot_w = (size_t)ROT_BATCH * ctw, dig_w = digits_words(P, level), tmp_w = (size_t)level * N;
     rc = P->ensure_scratch((rot_w + dig_w + tmp_w + switch_scratch_words(P, level, ROT_BATCH)) * sizeof(u64), stream);
     if (rc) return rc;
@@ -157,17 +161,20 @@ static int shift_bank(ckks_params_t *P, const uint64_t *d_ct_in, uint32_t level,
         }
         rc = switch_batch(P, level, items, n_it, d_work, stream);
         if (rc) return rc;
-        MaskPack pack;
-        for (u32 o = 0; o < MASK_OUTS; ++o) {
-            const u32 z = o < no ? o : 0;
-            pack.r1[o] = term[2 * z];
-            pack.r2[o] = term[2 * z + 1];
-            pack.a[o] = masks[2 * (o0 + z)];
-            pack.b[o] = masks[2 * (o0 + z) + 1];
+        for (u32 o = 0; o < no; o += per) {
+            const u32 cnt = std::min(per, no - o);
+            MaskPack pack;
+            for (u32 x = 0; x < MASK_OUTS; ++x) {
+                const u32 z = o + (x < cnt ? x : 0);
+                pack.r1[x] = term[2 * z];
+                pack.r2[x] = term[2 * z + 1];
+                pack.a[x] = masks[2 * (o0 + z)];
+                pack.b[x] = masks[2 * (o0 + z) + 1];
+            }
+            hipLaunchKernelGGL(masked_sum_kernel, dim3(N / (2 * EW_THREADS), level, cnt), dim3(EW_THREADS), 0, stream, pack,
+                               d_ct_out + (size_t)(o0 + o) * ctw, P->d_mod, level, N);
+            CKKS_LAUNCH_CHECK("masked_sum_kernel");
         }
-        hipLaunchKernelGGL(masked_sum_kernel, dim3(N / (2 * EW_THREADS), level, no), dim3(EW_THREADS), 0, stream, pack,
-                           d_ct_out + (size_t)o0 * ctw, P->d_mod, level, N);
-        CKKS_LAUNCH_CHECK("masked_sum_kernel");
     }
     return CKKS_OK;
 }

@@ -258,3 +258,19 @@ def test_plain_expand_onto_its_coefficients(logN):
         with pytest.raises(B.CkksError) as e:
             B.ckks_plain_expand(P, level, buf[at:at + count * N], buf[:count * level * N])
         assert e.value.code == -1 and "overlaps" in str(e.value)
+
+
+@pytest.mark.parametrize("above", [0, 1])
+def test_shift_bank_over_masks_already_used(above):
+    """Outputs written over the masks, at the same place or one output below: output by output, each after its masks have
+    been read.  19 outputs of identity terms, more than one launch takes."""
+    from paper_2604_09975_amd import binding as B
+    O = helpers.small_oracle(12, L=3, K=1, dnum=3, qbits=45, pbits=47)
+    _, P = make_pair(O)
+    r = W.rng(70)
+    ct = torch.from_numpy(W.uniform_residues(r, O.q, O.N, lead=(2,)).view(np.int64)).cuda()
+    masks = torch.from_numpy(W.uniform_residues(r, O.q, O.N, lead=(19, 2)).view(np.int64)).cuda()
+    want = B.ckks_shift_bank(P, ct, 3, [0] * 38, [None] * 38, masks)
+    buf = torch.empty((19 + above, 2, 3, O.N), dtype=torch.int64, device="cuda")
+    buf[above:].copy_(masks)
+    assert torch.equal(B.ckks_shift_bank(P, ct, 3, [0] * 38, [None] * 38, buf[above:], d_ct_out=buf[:19]), want)
