@@ -330,8 +330,9 @@ __global__ __launch_bounds__(EW_THREADS) void copy_blocks_kernel(u64 *__restrict
 }
 
 // y_b = base_b + the rotated accumulators of block b among the cn items of a batch; item r belongs to block (c0 + r) % B.
-// blockIdx.y = component * level + limb, blockIdx.z = block; two residues per thread.
-__global__ __launch_bounds__(EW_THREADS) void add_rotations_kernel(u64 *__restrict__ y, const u64 *base,
+// base is y itself from the second batch on.  blockIdx.y = component * level + limb, blockIdx.z = block; two residues per
+// thread.
+__global__ __launch_bounds__(EW_THREADS) void add_rotations_kernel(u64 *y, const u64 *base,
                                                                    size_t base_stride, const u64 *__restrict__ items,
                                                                    const ModConst *__restrict__ mods, u32 level, u32 N,
                                                                    u32 b0, u32 B, u32 c0, u32 cn) {

@@ -445,3 +445,16 @@ def test_adopted_key_gives_the_same_rotation():
     torch.cuda.synchronize()
     assert torch.equal(a, b)
     assert (to_host(a)[0] == O.rotate_hoisted(to_host(ct), 4, [g], [key])[0]).all()
+
+
+@pytest.mark.parametrize("C,d_in,d_out", [(16, 16, 40), (2, 3, 80), (16, 5, 16)])
+def test_separate_giant_step_over_several_batches(C, d_in, d_out):
+    """Every giant rotation a complete switch: 45 rotations of three blocks, 40 blocks of one rotation (more than a batch
+    holds, batches that end inside a rotation, sums that go on from what the last batch left) and 15 of one block."""
+    O = helpers.small_oracle(12, L=3, K=1, dnum=3, qbits=40, pbits=42)
+    _, P = make_pair(O)
+    r = W.rng(64)
+    X, Wm = r.uniform(-1, 1, (4, d_in)), r.uniform(-0.5, 0.5, (d_in, d_out))
+    Y, ref, cnt, _ = run_case(O, P, X, Wm, r.uniform(-0.5, 0.5, d_out), 4, C, 1, 30, 3, 65, hw=16, real=True)
+    assert np.abs(Y - ref).max() <= 1e-3
+    assert cnt.key_switches == -(-d_out // C) * (C - 1)
