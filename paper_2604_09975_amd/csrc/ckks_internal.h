@@ -110,6 +110,7 @@ struct ckks_params {
     // private scratch arena
     void *d_scratch = nullptr;
     size_t scratch_bytes = 0;
+    size_t scratch_floor = 0;          // what ckks_params_create reserved
 
     // optional timing of the diagonal multiply-accumulate kernel (ckks_profile_*)
     bool prof_on = false;

@@ -693,19 +693,19 @@ struct MatmulLayout {
 constexpr u32 RESCALE_CHUNK = 64;
 static int rescale_rows(ckks_params *P, const u64 *d_in, u32 level, u32 rows, u64 *d_out, u64 *d_r, hipStream_t stream);
 
-static MatmulLayout matmul_layout(const ckks_params *P, const ckks_weights *w, bool merged, bool rescale = true) {
+constexpr size_t SEPARATE_EXTRA = (size_t)256 << 20;
+static MatmulLayout matmul_layout_of(const ckks_params *P, const ckks_weights *w, bool merged, bool rescale, u32 batch) {
     MatmulLayout l;
     const u32 N = P->N, level = w->level, G = w->G, B = w->B_out, N2 = w->N2;
     const size_t ctw = (size_t)2 * level * N;
-    merged = merged && N2 > 1;
     l.in_chunk = std::min<u32>(ROT_BATCH, G);                    // inputs decomposed together
-    // inputs, accumulators or (separate giant step) giant rotations decomposed and switched together
-    const u32 rots = (u32)std::min<u64>(ROT_BATCH, merged ? 0 : (u64)B * (N2 - 1));
-    l.batch = std::min<u32>(ROT_BATCH, std::max({l.in_chunk, B, rots}));
+    l.batch = batch;                                             // inputs or accumulators decomposed and switched together
     l.dig_w = digits_words(P, level);
     l.tmp_w = (size_t)level * N;
     l.ks_w = l.batch * (l.dig_w + l.tmp_w) + switch_scratch_words(P, level, ROT_BATCH);
-    l.bank_w = std::max<size_t>((size_t)G * w->N1, rots) * ctw;  // the rotated accumulators take the bank's place
+    // separate giant step: the rotated accumulators of a batch take the bank's place
+    const u64 rotated = merged ? 0 : std::min<u64>(l.batch, (u64)B * (N2 - 1));
+    l.bank_w = std::max<size_t>((size_t)G * w->N1, rotated) * ctw;
     l.acc_w = (size_t)B * N2 * ctw;
     l.u_w = merged ? (size_t)B * 2 * (level + P->K) * N : 0;    // extended-basis sums of the giant step
     // merged giant step: the digits of up to MERGE_GROUP rotations of one batch of blocks are held together
@@ -715,6 +715,24 @@ static MatmulLayout matmul_layout(const ckks_params *P, const ckks_weights *w, b
     l.yfull_w = rescale ? (size_t)B * ctw : 0;
     l.t_w = rescale ? (size_t)std::max<u32>(l.batch, RESCALE_CHUNK) * 2 * N : 0;
     return l;
+}
+
+static MatmulLayout matmul_layout(const ckks_params *P, const ckks_weights *w, bool merged, bool rescale = true) {
+    const u32 G = w->G, B = w->B_out, N2 = w->N2;
+    merged = merged && N2 > 1;
+    u32 batch = std::min<u32>(ROT_BATCH, std::max(G, B));
+    if (!merged && N2 > 1) {
+        // Separate giant step: rotations of several p share a batch as far as memory allows that is reserved anyway, for the
+        // merged order of the same projection or by ckks_params_create (a block's worth always fits: the merged order
+        // holds larger sums), and a quarter of it, or 256 MiB, beyond.  One block of
+        // 256 columns at 2^16, N1 = 16: 15 rotations in one batch 2.98 ms and 3.5 GiB, in two 3.22 ms and 3.1 GiB, one by one
+        // 4.58 ms.  Of 64 columns, N1 = 2: all 31 in one batch 3.85 ms and 5.1 GiB, 13 to a batch 4.01 ms and 3.8 GiB.
+        size_t have = std::max(matmul_layout_of(P, w, true, true, batch).total(), P->scratch_floor / sizeof(u64));
+        have += std::max(have / 4, SEPARATE_EXTRA / sizeof(u64));
+        const u32 most = (u32)std::min<u64>(ROT_BATCH, (u64)B * (N2 - 1));
+        while (batch < most && matmul_layout_of(P, w, false, true, batch + 1).total() <= have) ++batch;
+    }
+    return matmul_layout_of(P, w, merged, rescale, batch);
 }
 
 size_t matmul_scratch_words(const ckks_params *P, const ckks_weights *w, bool merged) {
@@ -1307,7 +1325,7 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
         }
     }
     // Separate order: each rotation a complete key switch.  The switches of all rotations and blocks go out in batches of
-    // up to ROT_BATCH, rotation-major (neighbours share the key), into the area of the bank, which is free by now, and are
+    // lay.batch, rotation-major (neighbours share the key), into the area of the bank, which is free by now, and are
     // summed from there.  (One batch per rotation before, which with few blocks is a chain of small launches: a 64-wide
     // layer at N = 2^12 with 7 rotations of one block took 57 launches and 501 us, now 21 and 158 us.)
     for (u64 c0 = 0; batched && c0 < (u64)ps.size() * B; c0 += batch) {

@@ -457,6 +457,7 @@ int ckks_params_create(uint32_t logN, const uint64_t *q, uint32_t L, const uint6
         words = std::max(words, (size_t)dnum * W * N + W);                    // key generation
         if (K) words = std::max(words, (size_t)ROT_BATCH * 2 * L * N + rotate_hoisted_scratch_words(P, L, ROT_BATCH));   // ckks_shift_bank
         rc = P->ensure_scratch(words * sizeof(u64), nullptr);
+        P->scratch_floor = words * sizeof(u64);
     }
     if (rc) {
         ckks_params_destroy(P);

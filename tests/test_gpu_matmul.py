@@ -458,3 +458,28 @@ def test_separate_giant_step_over_several_batches(C, d_in, d_out):
     Y, ref, cnt, _ = run_case(O, P, X, Wm, r.uniform(-0.5, 0.5, d_out), 4, C, 1, 30, 3, 65, hw=16, real=True)
     assert np.abs(Y - ref).max() <= 1e-3
     assert cnt.key_switches == -(-d_out // C) * (C - 1)
+
+
+@pytest.mark.parametrize("L,dnum,C,N1,G,B_out", [(3, 3, 128, 8, 1, 1), (3, 3, 128, 128, 2, 1), (12, 12, 64, 2, 1, 1),
+                                                 (3, 3, 32, 1, 2, 40), (12, 4, 64, 4, 2, 2)])
+def test_arena_of_a_projection(L, dnum, C, N1, G, B_out):
+    """ckks_weights_create reserves what either giant-step order needs with one rotation of up to 32 blocks (or 32 inputs) per
+    batch; that the separate order takes several rotations into a batch costs at most a quarter more, or 256 MiB."""
+    B = _B()
+    O = helpers.small_oracle(13, L=L, K=1, dnum=dnum, qbits=50, pbits=60)
+    _, P = make_pair(O)
+    level, K, N, N2 = L, 1, O.N, C // N1
+    before = B.ckks_params_scratch_bytes(P)
+    w = B.ckks_weights_create(P, level, 4, C, G, B_out, N1)
+    ctw, digits = 2 * level * N, dnum * (level + K) * N
+    batch = min(32, max(G, B_out))
+    words = batch * (digits + level * N) + 32 * 2 * (2 * level + K) * N        # key switch
+    words += (G * N1 + B_out * N2) * ctw                                       # bank, accumulators
+    words += B_out * ctw + 64 * 2 * N                                          # blocks and dropped limbs of the rescale
+    if N2 > 1:
+        words += B_out * 2 * (level + K) * N + min(8, N2 - 1) * min(batch, B_out) * digits     # merged order
+    one = max(before, 8 * words)
+    got = B.ckks_params_scratch_bytes(P)
+    assert one <= got <= max(one * 5 // 4, one + (256 << 20))
+    assert N2 > 1 or got == one
+    w.close()
