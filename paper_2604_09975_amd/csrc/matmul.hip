@@ -87,21 +87,32 @@ __global__ __launch_bounds__(EW_THREADS) void scale_rows_kernel(u64 *data, const
 // [limb][chunk of 128 residues][tile of TB pairs][gq / 4][pair of the tile][3200 bytes].  A 3200-byte record holds the
 // chunk's residues of four steps: two parts of 16 bytes per lane (residues 2l, 2l+1 of two steps, low 32 bits), two of 8
 // bytes per lane (bits 32..47) and one of 4 bytes per pair of lanes (bits 48, 49; one byte per step), each a whole
-// number of 128-byte lines read by one load of the wavefront.  A half store holds the first N/2 residues of a limb (real
-// diagonals: the rest is the mirror image), a whole store all N.
+// number of 128-byte lines read by one load of the wavefront.  The steps behind the last whole record follow in an area of
+// their own, one 800-byte record per step ([limb][chunk][tile][step][pair]: 512 + 256 + 32 bytes), and a last tile of
+// fewer pairs holds those alone, so that nothing is stored or read for padding.  A half store holds the first N/2 residues
+// of a limb (real diagonals: the rest is the mirror image), a whole store all N.
 // What the order is worth, QKV layer (38 GB): parts that share lines 9.6 ms, whole lines with every pair's records in a
-// place of their own 8.54 ms, this order 8.43 ms.
+// place of their own 8.54 ms, this order 8.43 ms.  What the exact sizes are worth, 24 limbs at 2^16, real diagonals: 64 steps
+// of one pair 539 us with tile and record filled up, 374 now; 5 steps of 16 pairs 227 and 188; 7 steps of 9 pairs 174 and 145.
 constexpr u32 TB = 4;                                              // (b,p) pairs of a tile
 constexpr u32 REC_BYTES = 3200, REC_CHUNK = 128, REC_MID = 2048, REC_TOP = 3072;
+constexpr u32 STEP_BYTES = 800, STEP_MID = 512, STEP_TOP = 768;    // the record of a single step
 struct PackedShape {
-    u32 GQ4, ntile, nch, level;                                    // records per pair and chunk, tiles, chunks per limb
-    __host__ __device__ size_t rec(u32 bp, u32 i, u32 chunk, u32 gq) const {
-        return (((((size_t)i * nch + chunk) * ntile + bp / TB) * GQ4 + (gq >> 2)) * TB + bp % TB) * REC_BYTES;
+    u32 GQ, BP, nch, level;                                        // steps, pairs, chunks per limb
+    __host__ __device__ u32 records() const { return GQ / 4; }     // whole ones, per pair and chunk
+    // pairs of the tile of pair bp, and where their r-th records (or the records of step 4 * records() + r) lie
+    __host__ __device__ u32 pairs(u32 bp) const { return BP - bp / TB * TB < TB ? BP - bp / TB * TB : TB; }
+    __host__ __device__ size_t rec(u32 bp, u32 i, u32 chunk, u32 r) const {
+        return ((((size_t)i * nch + chunk) * BP + bp / TB * TB) * records() + (size_t)r * pairs(bp) + bp % TB) * REC_BYTES;
     }
-    size_t bytes() const { return (size_t)level * nch * ntile * GQ4 * TB * REC_BYTES; }
+    __host__ __device__ size_t step(u32 bp, u32 i, u32 chunk, u32 r) const {
+        return (size_t)level * nch * BP * records() * REC_BYTES +
+               ((((size_t)i * nch + chunk) * BP + bp / TB * TB) * (GQ % 4) + (size_t)r * pairs(bp) + bp % TB) * STEP_BYTES;
+    }
+    __host__ __device__ size_t bytes() const { return (size_t)level * nch * BP * GQ * STEP_BYTES; }
 };
 static inline PackedShape packed_shape(u32 N, u32 level, u32 GQ, u32 BP, bool whole) {
-    return PackedShape{(GQ + 3) / 4, (BP + TB - 1) / TB, (whole ? N : N / 2) / REC_CHUNK, level};
+    return PackedShape{GQ, BP, (whole ? N : N / 2) / REC_CHUNK, level};
 }
 
 // grid: x = tile of TB (b,p) pairs from tile0, y = run of 512 coefficients (SYM: and their mirrors), z = limb (limbs.id:
@@ -112,6 +123,10 @@ static inline PackedShape packed_shape(u32 N, u32 level, u32 GQ, u32 BP, bool wh
 // Only the first half of every weight limb is read; each value serves coefficient k and its mirror: the thread owns
 // N-2-k, N-1-k as well.
 // TB = 4: 32 outputs of two doubles (128 registers) are what two waves per SIMD leave room for.
+// NP: pairs a thread computes.  A lone tile of one or two pairs takes an instance of that many (109 and 154 registers instead
+// of 250, no products for absent pairs) while the bank fits the Infinity Cache and latency counts: 24 limbs at 2^16, one pair
+// of 1 / 5 / 8 steps 18.4 / 43 / 52 us with NP = 4, 13.5 / 32 / 48 with NP = 1.  Larger banks are a stream, and more
+// wavefronts on it do not help: 16 steps, general diagonals, 128 us with NP = 4, 138 with NP = 1.
 // Steps gq0 .. gq1-1 of the GQ per pair are summed; accumulate: onto what acc already holds.
 // swizzle: workgroups go to the XCDs round-robin and each XCD has its own L2, so the linear workgroup id is unfolded to
 // let one XCD walk all (b,p) tiles of a run of coefficients back to back: the bank lines of that run are then fetched
@@ -120,7 +135,7 @@ static inline PackedShape packed_shape(u32 N, u32 level, u32 GQ, u32 BP, bool wh
 // 8.40, without the record loads 4.36, without the bank loads 7.05 (5.1 TB/s; a plain read reaches 5.3) when the whole
 // took 8.45.  The kernel with
 // a quotient per product was bound by fp64 issue: 8.66 ms with the vector units 92 % busy; these sums keep them 55 % busy.
-template <bool SYM, bool PACKED>
+template <bool SYM, bool PACKED, u32 NP>
 __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *__restrict__ bank,
                                                               const void *__restrict__ w, u64 *__restrict__ acc,
                                                               const ModFp *__restrict__ modf, LimbIds limbs,
@@ -144,16 +159,16 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
     const u32 i = limbs.id[blockIdx.z];
     const size_t row = (size_t)i * N, w_stride = (size_t)level * N;
     const double q = modf[i].q, u = modf[i].u;
-    MacSum a[TB][2][CO];
+    MacSum a[NP][2][CO];
 #pragma unroll
-    for (u32 t = 0; t < TB; ++t)
+    for (u32 t = 0; t < NP; ++t)
 #pragma unroll
         for (u32 c = 0; c < 2; ++c)
 #pragma unroll
             for (u32 e = 0; e < CO; ++e) a[t][c][e] = MacSum{MAC_H0, 0.0};
     if (accumulate) {
 #pragma unroll
-        for (u32 t = 0; t < TB; ++t)
+        for (u32 t = 0; t < NP; ++t)
             if (bpt + t >= bp0 && bpt + t < bp1)
 #pragma unroll
                 for (u32 c = 0; c < 2; ++c)
@@ -165,14 +180,16 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
                     }
     }
     dvec_t x[2][2][HV];                                            // [step & 1][component]
-    u32 wr[2][TB][6], wt[2][TB];                                   // two steps' weights as loaded, twice; four steps' top bits
-    double wp[2][TB][2];                                           // two steps' weights, unpacked store
+    u32 wr[2][NP][6], wt[2][NP];                                   // two steps' weights as loaded, twice; four steps' top bits
+    double wp[2][NP][2];                                           // two steps' weights, unpacked store
     // buffer loads: wavefront-uniform addresses stay in scalar registers, the lanes add 32-bit offsets; and a step outside
     // the range reads zeros (a buffer of no records), so that the loop has no branches
-    const u32 r_first = gq0 >> 2, r_end = (gq1 + 3) >> 2;          // records of the range
+    const PackedShape ps{GQ, BP, (SYM ? N / 2 : N) / REC_CHUNK, level};
+    const u32 gq_end = PACKED ? min(gq1, 4 * ps.records()) : gq1;  // the steps in whole records; the others come last
+    const u32 r_first = gq0 >> 2, r_end = (gq_end + 3) >> 2;       // records of the range
     const double *xp = bank + (size_t)r_first * 8 * w_stride + row;  // the next step to fetch
     auto fetch_x = [&](u32 s, u32 gq) {
-        const int bytes = gq >= gq0 && gq < gq1 ? (int)(N * sizeof(double)) : 0;
+        const int bytes = gq >= gq0 && gq < gq_end ? (int)(N * sizeof(double)) : 0;
 #pragma unroll
         for (u32 c = 0; c < 2; ++c) {
             const __amdgpu_buffer_rsrc_t rs =
@@ -184,37 +201,40 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
         }
     };
     const u32 lane = threadIdx.x & 63, top_shift = (lane & 1) * 4;
-    const PackedShape ps{(GQ + 3) / 4, (BP + TB - 1) / TB, (SYM ? N / 2 : N) / REC_CHUNK, level};
-    const u32 chunk = __builtin_amdgcn_readfirstlane(k / REC_CHUNK);
-    const unsigned char *wrec = reinterpret_cast<const unsigned char *>(w) + ps.rec(bpt, i, chunk, 4 * r_first);
-    const double *wdbl[TB];                                        // unpacked store: pairs beyond the last repeat it
+    const u32 chunk = __builtin_amdgcn_readfirstlane(k / REC_CHUNK), wpairs = ps.pairs(bpt);
+    const unsigned char *wrec = reinterpret_cast<const unsigned char *>(w) + ps.rec(bpt, i, chunk, r_first);
+    // pairs of the tile that are not summed here have no records: their loads return zeros without traffic
+    auto bytes_of = [&](u32 t, u32 bytes, bool live) { return live && bpt + t >= bp0 && bpt + t < bp1 ? (int)bytes : 0; };
+    const double *wdbl[NP];                                        // unpacked store: pairs beyond the last repeat it
 #pragma unroll
-    for (u32 t = 0; t < TB; ++t)
+    for (u32 t = 0; t < NP; ++t)
         wdbl[t] = reinterpret_cast<const double *>(w) + ((size_t)min(bpt + t, BP - 1) * GQ + 4 * r_first) * w_stride + row;
     // steps 2 g2, 2 g2 + 1 into buffer g2 & 1, with the even one the record's top bits into buffer (g2 / 2) & 1
     auto fetch_w = [&](u32 buf, u32 tbuf, u32 g2) {
         if (PACKED) {
-            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(wrec), 0,
-                                                                                TB * REC_BYTES, 0x00020000);
 #pragma unroll
-            for (u32 t = 0; t < TB; ++t) {
-                const int at = (int)(t * REC_BYTES);
-                const u32x4 lo = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(lane * 16), at + (int)(buf * 1024), 0);
-                const u32x2 mid = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(lane * 8), at + (int)(REC_MID + buf * 512), 0);
+            for (u32 t = 0; t < NP; ++t) {
+                unsigned char *const at = const_cast<unsigned char *>(wrec) + t * REC_BYTES;
+                const __amdgpu_buffer_rsrc_t rs =
+                    __builtin_amdgcn_make_buffer_rsrc(at, 0, bytes_of(t, REC_BYTES, true), 0x00020000);
+                const u32x4 lo = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(lane * 16 + buf * 1024), 0, 0);
+                const u32x2 mid = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(lane * 8 + REC_MID + buf * 512), 0, 0);
 #pragma unroll
                 for (u32 z = 0; z < 4; ++z) wr[buf][t][z] = lo[z];
                 wr[buf][t][4] = mid[0];
                 wr[buf][t][5] = mid[1];
-                if (buf == 0) wt[tbuf][t] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)((lane >> 1) * 4), at + (int)REC_TOP, 0);
+                if (buf == 0)
+                    wt[tbuf][t] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)((lane >> 1) * 4 + REC_TOP), 0, 0);
             }
-            if (buf == 1 && g2 + 1 < 2 * r_end) wrec += TB * REC_BYTES;   // the last record stays the last
+            if (buf == 1 && g2 + 1 < 2 * r_end) wrec += wpairs * REC_BYTES;   // the last record stays the last
         } else {
 #pragma unroll
-            for (u32 t = 0; t < TB; ++t)
+            for (u32 t = 0; t < NP; ++t)
 #pragma unroll
                 for (u32 s = 0; s < 2; ++s) {
+                    const bool live = 2 * g2 + s >= gq0 && 2 * g2 + s < gq1;
                     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-                        const_cast<double *>(wdbl[t]), 0, 2 * g2 + s < GQ ? (int)(N * sizeof(double)) : 0, 0x00020000);
+                        const_cast<double *>(wdbl[t]), 0, bytes_of(t, N * sizeof(double), live), 0x00020000);
                     const dvec_t v = __builtin_bit_cast(dvec_t, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(k * 8), 0, 0));
                     wp[s][t][0] = v[0];
                     wp[s][t][1] = v[1];
@@ -222,25 +242,27 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
                 }
         }
     };
+    // the weight whose w + 2^49 has the bits hi:lo: 2^52 + (w + 2^49) from its bits, then one exact subtraction
+    auto unpack = [](u32 hi, u32 lo) {
+        return __hiloint2double((int)(0x43300000u | hi), (int)lo) - (4503599627370496.0 + 562949953421312.0);
+    };
     // Step s of two, pairs in order in the first and in reverse in the second: a product needs its sum's old and new
     // high parts at once, and with this order the new one finds its place in the register the previous sum has left,
     // and goes back in the next step, so that no copies are needed.  One pair at a time: the barriers keep the compiler
     // from unpacking all pairs first, which takes more registers than two waves per SIMD have.
     auto products = [&](u32 buf, u32 tbuf, u32 s) {
 #pragma unroll
-        for (u32 tt = 0; tt < TB; ++tt) {
-            const u32 t = s ? TB - 1 - tt : tt;
+        for (u32 tt = 0; tt < NP; ++tt) {
+            const u32 t = s ? NP - 1 - tt : tt;
             double wd[2];
             if (PACKED) {
-                // (2^52 + w + 2^49) from its bits, then one exact subtraction
                 u32 top = wt[tbuf][t], mid = wr[buf][t][4 + s];
                 asm volatile("" : "+v"(top), "+v"(mid));
                 top >>= top_shift;
 #pragma unroll
                 for (u32 e = 0; e < 2; ++e) {
-                    const u32 hi = 0x43300000u | (((top >> (16 * buf + 8 * s + 2 * e)) & 3u) << 16) |
-                                   (e ? mid >> 16 : mid & 0xffffu);
-                    wd[e] = __hiloint2double((int)hi, (int)wr[buf][t][2 * s + e]) - (4503599627370496.0 + 562949953421312.0);
+                    wd[e] = unpack((((top >> (16 * buf + 8 * s + 2 * e)) & 3u) << 16) | (e ? mid >> 16 : mid & 0xffffu),
+                                   wr[buf][t][2 * s + e]);
                 }
             } else {
                 wd[0] = wp[s][t][0];
@@ -257,7 +279,7 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
     };
     auto fold = [&]() {
 #pragma unroll
-        for (u32 t = 0; t < TB; ++t)
+        for (u32 t = 0; t < NP; ++t)
 #pragma unroll
             for (u32 c = 0; c < 2; ++c)
 #pragma unroll
@@ -273,9 +295,11 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
         fetch_x(1, 2 * g2 + 3);
     };
     // whole records of four steps, whatever the range: 8 products between two folds
-    fetch_w(0, 0, 2 * r_first);
-    fetch_x(0, 4 * r_first);
-    fetch_x(1, 4 * r_first + 1);
+    if (r_first < r_end) {
+        fetch_w(0, 0, 2 * r_first);
+        fetch_x(0, 4 * r_first);
+        fetch_x(1, 4 * r_first + 1);
+    }
     for (u32 r = r_first; r < r_end; r += 2) {
         two_steps(0, 0, 2 * r);
         two_steps(1, 0, 2 * r + 1);
@@ -285,8 +309,57 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
         }
         fold();
     }
+    // the up to three steps behind the last whole record: all their loads, then the products
+    const u32 s0 = max(gq0, 4 * ps.records());
+    if (PACKED && s0 < gq1) {
+        dvec_t xs[3][2][HV];
+        u32x2 lo[3][NP];
+        u32 mid[3][NP], top[3][NP];
 #pragma unroll
-    for (u32 t = 0; t < TB; ++t) {
+        for (u32 s = 0; s < 3; ++s) {
+            const double *xs_at = bank + (size_t)(s0 + s) * 2 * w_stride + row;
+#pragma unroll
+            for (u32 c = 0; c < 2; ++c) {
+                const __amdgpu_buffer_rsrc_t rs =
+                    __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(xs_at + c * w_stride), 0,
+                                                      s0 + s < gq1 ? (int)(N * sizeof(double)) : 0, 0x00020000);
+#pragma unroll
+                for (u32 h = 0; h < HV; ++h)
+                    xs[s][c][h] = __builtin_bit_cast(dvec_t, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(kk[h] * 8), 0, 0));
+            }
+            const unsigned char *at = reinterpret_cast<const unsigned char *>(w) + ps.step(bpt, i, chunk, s0 - 4 * ps.records() + s);
+#pragma unroll
+            for (u32 t = 0; t < NP; ++t) {
+                const __amdgpu_buffer_rsrc_t rs =
+                    __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(at) + t * STEP_BYTES, 0,
+                                                      bytes_of(t, STEP_BYTES, s0 + s < gq1), 0x00020000);
+                lo[s][t] = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(lane * 8), 0, 0);
+                mid[s][t] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(lane * 4 + STEP_MID), 0, 0);
+                top[s][t] = __builtin_amdgcn_raw_buffer_load_b8(rs, (int)((lane >> 1) + STEP_TOP), 0, 0);
+            }
+        }
+#pragma unroll
+        for (u32 s = 0; s < 3; ++s)
+            if (s0 + s < gq1) {
+#pragma unroll
+                for (u32 t = 0; t < NP; ++t) {
+                    const u32 hb = top[s][t] >> top_shift;
+                    double wd[2];
+#pragma unroll
+                    for (u32 e = 0; e < 2; ++e)
+                        wd[e] = unpack(((hb >> (2 * e)) & 3u) << 16 | (e ? mid[s][t] >> 16 : mid[s][t] & 0xffffu), lo[s][t][e]);
+#pragma unroll
+                    for (u32 o = 0; o < 2 * CO; ++o) {
+                        const u32 c = o / CO, e = o % CO;
+                        a[t][c][e].mac(xs[s][c][e >> 1][e & 1], wd[e < 2 ? e : 3 - e]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        fold();
+    }
+#pragma unroll
+    for (u32 t = 0; t < NP; ++t) {
         if (bpt + t >= bp0 && bpt + t < bp1) {
 #pragma unroll
             for (u32 c = 0; c < 2; ++c)
@@ -374,11 +447,26 @@ __global__ __launch_bounds__(EW_THREADS) void check_real_kernel(const int64_t *_
     if (c[N - n] != -c[n]) sym[blockIdx.y] = 0;
 }
 
-// Byte offsets within a record of step s (0..3), residue r (even, of 128) of its chunk: low words of r, r+1; middle
-// halves of r, r+1; the byte with the top bits of r & ~3 .. r | 3.
-__device__ __forceinline__ u32 rec_lo(u32 s, u32 r) { return (s >> 1) * 1024 + (r >> 1) * 16 + (s & 1) * 8; }
-__device__ __forceinline__ u32 rec_mid(u32 s, u32 r) { return REC_MID + (s >> 1) * 512 + (r >> 1) * 8 + (s & 1) * 4; }
+// Byte offsets within a record of step s (0..3), residue r of its chunk (r even: its pair's): low word, middle half, the
+// byte with the top bits of r & ~3 .. r | 3.
+__device__ __forceinline__ u32 rec_lo(u32 s, u32 r) { return (s >> 1) * 1024 + (r >> 1) * 16 + (s & 1) * 8 + (r & 1) * 4; }
+__device__ __forceinline__ u32 rec_mid(u32 s, u32 r) {
+    return REC_MID + (s >> 1) * 512 + (r >> 1) * 8 + (s & 1) * 4 + (r & 1) * 2;
+}
 __device__ __forceinline__ u32 rec_top(u32 s, u32 r) { return REC_TOP + (r >> 2) * 4 + s; }
+// The same from the start of the store, for step gq of pair bp and residue k of limb i, in a record of four or of one.
+struct PackedPlace {
+    size_t lo, mid, top;
+};
+__device__ __forceinline__ PackedPlace packed_place(const PackedShape &ps, u32 bp, u32 i, u32 gq, u32 k) {
+    const u32 r = k & (REC_CHUNK - 1), g = gq >> 2, s = gq & 3;
+    if (g < ps.records()) {
+        const size_t at = ps.rec(bp, i, k / REC_CHUNK, g);
+        return PackedPlace{at + rec_lo(s, r), at + rec_mid(s, r), at + rec_top(s, r)};
+    }
+    const size_t at = ps.step(bp, i, k / REC_CHUNK, s);
+    return PackedPlace{at + r * 4, at + STEP_MID + r * 2, at + STEP_TOP + (r >> 2)};
+}
 
 // Canonical residues below 2^50 of c diagonals, consecutive steps gq0 .. gq0 + c - 1 of pair bp -> packed records of the
 // first cnt residues of each limb.  in [c][level][N].  A thread packs four residues of two steps that share a part of a
@@ -412,9 +500,9 @@ __global__ __launch_bounds__(EW_THREADS) void pack_records_kernel(const u64 *__r
         mid[s][0] = hi[0] | (hi[1] << 16);
         mid[s][1] = hi[2] | (hi[3] << 16);
     }
-    const u32 r = k & (REC_CHUNK - 1), st = (2 * g2) & 3;
-    unsigned char *rec = out + ps.rec(bp, i, k / REC_CHUNK, 2 * g2);
-    if (have[0] && have[1]) {
+    if (have[0] && have[1] && g2 >> 1 < ps.records()) {
+        const u32 r = k & (REC_CHUNK - 1), st = (2 * g2) & 3;
+        unsigned char *rec = out + ps.rec(bp, i, k / REC_CHUNK, g2 >> 1);
         *reinterpret_cast<uint4 *>(rec + rec_lo(st, r)) = make_uint4(lo[0][0], lo[0][1], lo[1][0], lo[1][1]);
         *reinterpret_cast<uint4 *>(rec + rec_lo(st, r + 2)) = make_uint4(lo[0][2], lo[0][3], lo[1][2], lo[1][3]);
         *reinterpret_cast<uint4 *>(rec + rec_mid(st, r)) = make_uint4(mid[0][0], mid[1][0], mid[0][1], mid[1][1]);
@@ -424,11 +512,12 @@ __global__ __launch_bounds__(EW_THREADS) void pack_records_kernel(const u64 *__r
 #pragma unroll
     for (u32 s = 0; s < 2; ++s)
         if (have[s]) {
-            *reinterpret_cast<uint2 *>(rec + rec_lo(st + s, r)) = make_uint2(lo[s][0], lo[s][1]);
-            *reinterpret_cast<uint2 *>(rec + rec_lo(st + s, r + 2)) = make_uint2(lo[s][2], lo[s][3]);
-            *reinterpret_cast<u32 *>(rec + rec_mid(st + s, r)) = mid[s][0];
-            *reinterpret_cast<u32 *>(rec + rec_mid(st + s, r + 2)) = mid[s][1];
-            rec[rec_top(st + s, r)] = (unsigned char)top[s];
+            const PackedPlace a = packed_place(ps, bp, i, 2 * g2 + s, k), b = packed_place(ps, bp, i, 2 * g2 + s, k + 2);
+            *reinterpret_cast<uint2 *>(out + a.lo) = make_uint2(lo[s][0], lo[s][1]);
+            *reinterpret_cast<uint2 *>(out + b.lo) = make_uint2(lo[s][2], lo[s][3]);
+            *reinterpret_cast<u32 *>(out + a.mid) = mid[s][0];
+            *reinterpret_cast<u32 *>(out + b.mid) = mid[s][1];
+            out[a.top] = (unsigned char)top[s];
         }
 }
 
@@ -439,23 +528,22 @@ __global__ __launch_bounds__(EW_THREADS) void widen_records_kernel(const unsigne
                                                                    PackedShape whole, u32 N, u32 bp, u32 gq0) {
     const u32 k = (blockIdx.x * EW_THREADS + threadIdx.x) * 4;
     if (k >= N) return;
-    const u32 i = blockIdx.y % half.level, gq = gq0 + blockIdx.y / half.level, s = gq & 3;
+    const u32 i = blockIdx.y % half.level, gq = gq0 + blockIdx.y / half.level;
     u32 lo[4], hi[4], top = 0;
 #pragma unroll
     for (u32 e = 0; e < 4; ++e) {
-        const u32 m = k + e < N / 2 ? k + e : N - 1 - (k + e), r = m & (REC_CHUNK - 1);
-        const unsigned char *rec = in + half.rec(bp, i, m / REC_CHUNK, gq);
-        lo[e] = *reinterpret_cast<const u32 *>(rec + rec_lo(s, r) + (r & 1) * 4);
-        hi[e] = *reinterpret_cast<const unsigned short *>(rec + rec_mid(s, r) + (r & 1) * 2);
-        top |= ((rec[rec_top(s, r)] >> ((r & 3) * 2)) & 3u) << (2 * e);
+        const u32 m = k + e < N / 2 ? k + e : N - 1 - (k + e);
+        const PackedPlace a = packed_place(half, bp, i, gq, m);
+        lo[e] = *reinterpret_cast<const u32 *>(in + a.lo);
+        hi[e] = *reinterpret_cast<const unsigned short *>(in + a.mid);
+        top |= ((in[a.top] >> ((m & 3) * 2)) & 3u) << (2 * e);
     }
-    const u32 r = k & (REC_CHUNK - 1);
-    unsigned char *rec = out + whole.rec(bp, i, k / REC_CHUNK, gq);
-    *reinterpret_cast<uint2 *>(rec + rec_lo(s, r)) = make_uint2(lo[0], lo[1]);
-    *reinterpret_cast<uint2 *>(rec + rec_lo(s, r + 2)) = make_uint2(lo[2], lo[3]);
-    *reinterpret_cast<u32 *>(rec + rec_mid(s, r)) = hi[0] | (hi[1] << 16);
-    *reinterpret_cast<u32 *>(rec + rec_mid(s, r + 2)) = hi[2] | (hi[3] << 16);
-    rec[rec_top(s, r)] = (unsigned char)top;
+    const PackedPlace a = packed_place(whole, bp, i, gq, k), b = packed_place(whole, bp, i, gq, k + 2);
+    *reinterpret_cast<uint2 *>(out + a.lo) = make_uint2(lo[0], lo[1]);
+    *reinterpret_cast<uint2 *>(out + b.lo) = make_uint2(lo[2], lo[3]);
+    *reinterpret_cast<u32 *>(out + a.mid) = hi[0] | (hi[1] << 16);
+    *reinterpret_cast<u32 *>(out + b.mid) = hi[2] | (hi[3] << 16);
+    out[a.top] = (unsigned char)top;
 }
 
 __global__ __launch_bounds__(EW_THREADS) void fill_u32_kernel(u32 *p, u32 v, u32 n) {
@@ -1176,6 +1264,8 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
             u32 b1 = b0 + 1;
             while (b1 < B && same_kinds(b0, b1)) ++b1;
             const u32 bp0 = b0 * N2, bp1 = b1 * N2, tiles4 = (bp1 + TB - 1) / TB - bp0 / TB;
+            const u32 in_tile = tiles4 == 1 ? bp1 - bp0 / TB * TB : TB;     // pairs of a lone tile, from its first one
+            const bool few = (size_t)GQ * ctw * sizeof(u64) <= STREAM_BYTES;
             const double *bank = reinterpret_cast<const double *>(d_bank);
             const u32 runs = N / (4 * MM_THREADS), gen_runs = N / MM_THREADS / 2;
             for (u32 g0 = 0; g0 < G;) {
@@ -1185,18 +1275,28 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
                        w->block_packed[grp + (g1 - g0)] == w->block_packed[grp])
                     ++g1;
                 const u32 q0 = g0 * N1, q1 = g1 * N1, add = g0 ? 1u : 0u;
-#define MM_LAUNCH(SYM, PACKED, RUNS, WPTR)                                                                         \
-    hipLaunchKernelGGL((diag_mac_kernel<SYM, PACKED>), dim3(tiles4, RUNS, n_fp), dim3(MM_THREADS), 0, stream,      \
+#define MM_LAUNCH(SYM, PACKED, NP, RUNS, WPTR)                                                                     \
+    hipLaunchKernelGGL((diag_mac_kernel<SYM, PACKED, NP>), dim3(tiles4, RUNS, n_fp), dim3(MM_THREADS), 0, stream,  \
                        bank, WPTR, d_acc, P->d_modf, fp_limbs, level, N, GQ, BP, (RUNS) % 8 == 0 ? 1u : 0u, q0,    \
                        q1, add, bp0, bp1)
+#define MM_LAUNCH_PAIRS(SYM, RUNS, WPTR)                                                                           \
+    do {                                                                                                           \
+        if (few && in_tile == 1)                                                                                   \
+            MM_LAUNCH(SYM, true, 1, RUNS, WPTR);                                                                   \
+        else if (few && in_tile == 2)                                                                              \
+            MM_LAUNCH(SYM, true, 2, RUNS, WPTR);                                                                   \
+        else                                                                                                       \
+            MM_LAUNCH(SYM, true, TB, RUNS, WPTR);                                                                  \
+    } while (0)
                 if (w->block_packed[grp] == 1)
-                    MM_LAUNCH(true, true, runs, w->d_wp);
+                    MM_LAUNCH_PAIRS(true, runs, w->d_wp);
                 else if (w->block_packed[grp] == 2)
-                    MM_LAUNCH(false, true, gen_runs, w->d_wpf);
+                    MM_LAUNCH_PAIRS(false, gen_runs, w->d_wpf);
                 else if (w->block_real[grp] && N >= 4 * MM_THREADS)
-                    MM_LAUNCH(true, false, runs, w->d_w);
+                    MM_LAUNCH(true, false, TB, runs, w->d_w);
                 else
-                    MM_LAUNCH(false, false, gen_runs, w->d_w);
+                    MM_LAUNCH(false, false, TB, gen_runs, w->d_w);
+#undef MM_LAUNCH_PAIRS
 #undef MM_LAUNCH
                 g0 = g1;
             }

@@ -49,3 +49,23 @@ def test_sums_at_the_bounds(G, B_out, general):
                     want = sum(sign_x[g] * h * (1 if c == 0 else -1) * sign_w[b][g] * k for g in range(G)) % q[i]
                     row = y[b, c, i, half * (N // 2):(half + 1) * (N // 2)]
                     assert bool((row == want).all()), (b, c, i, half)
+
+
+@pytest.mark.parametrize("G,B_out,general", [(64, 1, False), (65, 2, False), (34, 1, True)])
+def test_weight_store_holds_what_the_diagonals_need(G, B_out, general):
+    """50 bits per residue, half a limb for a real diagonal: pairs off the tiles of four and steps off the records of four
+    take no more than their own bytes (checked on the device's free memory, to 16 MiB)."""
+    from paper_2604_09975_amd import binding as B
+    logN, N, L = 14, 1 << 14, 6
+    P = B.ckks_params_create(logN, B.ckks_find_primes(50, logN, L), B.ckks_find_primes(60, logN, 2), 3)
+    w = B.ckks_weights_create(P, L, 16, 1, G, B_out, 1)
+    c = torch.zeros((G * B_out, N), dtype=torch.int64, device="cuda")
+    c[:, N // 2 if general else 0] = 1
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    B.ckks_weights_set_diagonals(w, 0, c)
+    torch.cuda.synchronize()
+    used = free - torch.cuda.mem_get_info()[0]
+    store, stage = G * B_out * L * N * 50 // 8 // (1 if general else 2), 32 * L * N * 8
+    assert used <= store + stage + (16 << 20), (used, store, stage)
+    w.close()
