@@ -31,15 +31,18 @@ __device__ __forceinline__ u32 galois_index(u32 k, u32 g, u32 logN) {
     return __brev((e2 - 1u) >> 1) >> (32 - logN);
 }
 
-// Entries k, k + 1 (k even) of sigma_g of a row, from one 16-byte load: their exponents differ by N, and g is odd, so
-// their sources do too: they are entries kp and kp ^ 1, kp = galois_index(k).  load_pair gives them in memory order,
-// turned() in the order asked for; the kernels turn a pair where they use it (turned as it is loaded, every load is waited
-// for on its own: passb_final_kernel 602 us per 24 switches against 525 turned where used and 537 with two 8-byte loads).
+// Entries k, k + 1 (k even) of sigma_g of a row: their exponents differ by N, and g is odd, so their sources do too: they are
+// entries kp and kp ^ 1, kp = galois_index(k).  PAIR: one 16-byte load gives them in memory order, turned() puts them in the
+// order asked for; the kernels turn a pair where they use it (turned as it is loaded, every load is waited for on its own:
+// passb_final_kernel 602 us per 24 switches against 525 turned where used and 537 with two 8-byte loads).  Otherwise: two
+// 8-byte loads in the order asked for, which a launch of few workgroups, bound by the latency of one of them, has sooner.
 typedef u64 pair_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ pair_t load_pair(const u64 *__restrict__ row, u32 kp) {
-    return *reinterpret_cast<const pair_t *>(row + (kp & ~1u));
+template <bool PAIR>
+__device__ __forceinline__ pair_t load_two(const u64 *__restrict__ row, u32 kp) {
+    return PAIR ? *reinterpret_cast<const pair_t *>(row + (kp & ~1u)) : pair_t{row[kp], row[kp ^ 1u]};
 }
-__device__ __forceinline__ pair_t turned(pair_t v, bool turn) { return turn ? pair_t{v[1], v[0]} : v; }
+template <bool PAIR>
+__device__ __forceinline__ pair_t turned(pair_t v, u32 kp) { return PAIR && (kp & 1) ? pair_t{v[1], v[0]} : v; }
 
 // Evaluation keys as the library holds them: rows of ciphertext limbs carry the factor P^-1 of ModDown (the base
 // conversion P -> q_i carries it too, so that no kernel after the key product multiplies by it), on primes below 2^50 as
@@ -1026,30 +1029,26 @@ __global__ __launch_bounds__(NTT_THREADS) void ip_intt_kernel(ItemPack pack, u64
     const u32 g = (u32)it.galois_elt;
     u64 *out = y + (((size_t)r * 2 + comp) * K + k) * N;
     auto store = [&](u32 idx, u64 v) { out[idx] = v; };
-    // inner product into LDS on pairs of adjacent residues (16-byte loads), two pairs at a time so that
-    // their loads are in flight together
+    // inner product into LDS on pairs of adjacent residues (16-byte key loads), two pairs at a time so that
+    // their loads are in flight together.  (Digits by 16-byte loads as well: a bank of two at level 2 of 2^16 98.5 us instead
+    // of 97.7, 27 at level 24 the same.)
     const u32 tid = threadIdx.x, base = blockIdx.x << 12;
     constexpr u32 EPP = EPI / 2;
     for (u32 i0 = 0; i0 < 8; i0 += EPP) {
         pair_t dv[EPP][MAX_BETA], kv[EPP][MAX_BETA];
-        bool turn[EPP];
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
             const u32 idx = base + 2 * (tid + 256 * (i0 + e)), kp = galois_index(idx, g, logN);
-            turn[e] = kp & 1;
 #pragma unroll
             for (u32 j = 0; j < MAX_BETA; ++j)
                 if (j < beta) {
-                    dv[e][j] = load_pair(dig + (size_t)j * Wl * N, kp);
+                    dv[e][j] = load_two<false>(dig + (size_t)j * Wl * N, kp);
                     kv[e][j] = load_key<KEY_NT>(reinterpret_cast<const pair_t *>(key + (size_t)j * 2 * Wt * N + idx));
                 }
         }
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
             const u32 loc = 2 * (tid + 256 * (i0 + e));
-#pragma unroll
-            for (u32 j = 0; j < MAX_BETA; ++j)
-                if (j < beta) dv[e][j] = turned(dv[e][j], turn[e]);
 #pragma unroll
             for (u32 z = 0; z < 2; ++z) {
                 u128 acc = {0, 0};
@@ -1072,7 +1071,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ip_intt_kernel(ItemPack pack, u64
 //   dst[comp][i] (+)= sum_j sigma_g(d_j)[q_i] * key_j[comp][q_i] - NTT(w)[i]  (+ sigma_g(c0)[i] if comp = 0)
 // (the keys and w carry the P^-1 of ModDown).
 // grid: x = tile of 4096, y = ((i*n + r)*2 + comp), neighbours share digit and key lines in L2 as above.
-template <bool KEY_NT>
+template <bool KEY_NT, bool PAIR>
 __global__ __launch_bounds__(NTT_THREADS) void passb_final_kernel(ItemPack pack, const u64 *__restrict__ w,
                                                                   const ModConst *__restrict__ mods,
                                                                   const ModFp *__restrict__ modf,
@@ -1110,28 +1109,28 @@ __global__ __launch_bounds__(NTT_THREADS) void passb_final_kernel(ItemPack pack,
     const bool fold = comp == 0 && it.c0;
     for (u32 i0 = 0; i0 < 8; i0 += EPP) {
         pair_t dv[EPP][MAX_BETA], kv[EPP][MAX_BETA], cv[EPP], ov[EPP];
-        bool turn[EPP];
+        u32 kp[EPP];
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
-            const u32 idx = base + 2 * (tid + 256 * (i0 + e)), kp = galois_index(idx, g, logN);
-            turn[e] = kp & 1;
+            const u32 idx = base + 2 * (tid + 256 * (i0 + e));
+            kp[e] = galois_index(idx, g, logN);
 #pragma unroll
             for (u32 j = 0; j < MAX_BETA; ++j)
                 if (j < beta) {
-                    dv[e][j] = load_pair(drow[j], kp);
+                    dv[e][j] = load_two<PAIR>(drow[j], kp[e]);
                     kv[e][j] = load_key<KEY_NT>(reinterpret_cast<const pair_t *>(key + (size_t)j * 2 * Wt * N + idx));
                 }
-            cv[e] = fold ? load_pair(c0, kp) : pair_t{0, 0};
+            cv[e] = fold ? load_two<PAIR>(c0, kp[e]) : pair_t{0, 0};
             ov[e] = accumulate ? __builtin_nontemporal_load(reinterpret_cast<const pair_t *>(dst + idx)) : pair_t{0, 0};
         }
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
             const u32 loc = 2 * (tid + 256 * (i0 + e));
             __builtin_amdgcn_sched_barrier(0);
-            cv[e] = turned(cv[e], turn[e]);
+            cv[e] = turned<PAIR>(cv[e], kp[e]);
 #pragma unroll
             for (u32 j = 0; j < MAX_BETA; ++j)
-                if (j < beta) dv[e][j] = turned(dv[e][j], turn[e]);
+                if (j < beta) dv[e][j] = turned<PAIR>(dv[e][j], kp[e]);
             pair_t out;
 #pragma unroll
             for (u32 z = 0; z < 2; ++z) {
@@ -1449,7 +1448,13 @@ int switch_batch(ckks_params *p, u32 level, const SwitchItem *items, u32 n, u64 
             rc = launch_ntt(p, w, ids, level, n * 2 * level, false, stream, 1, false);
             if (rc) return rc;
         }
-        hipLaunchKernelGGL(own_keys ? passb_final_kernel<true> : passb_final_kernel<false>, dim3(tiles, n * 2 * level),
+        // 16-byte gathers above three workgroups per CU: one rotation at 2^16, level 24 (768 workgroups) by 8-byte loads 165.0
+        // us, by 16-byte ones 165.5; 24 switches at 2^14, level 5 (960) and the rest of their call 169 and 167; eight rotations
+        // at 2^16, level 24 (6144) 496 and 493.
+        const bool pair = tiles * n * 2 * level > 768;
+        const auto passb = own_keys ? (pair ? passb_final_kernel<true, true> : passb_final_kernel<true, false>)
+                                    : (pair ? passb_final_kernel<false, true> : passb_final_kernel<false, false>);
+        hipLaunchKernelGGL(passb, dim3(tiles, n * 2 * level),
                            dim3(NTT_THREADS), 0, stream, pack, w, p->d_mod, p->d_modf, p->d_tws_fwd, p->d_twf_fwd,
                            p->d_ninvs, n, level, K, L, beta, p->alpha, p->logN);
         CKKS_LAUNCH_CHECK("passb_final_kernel");

@@ -55,3 +55,34 @@ def test_rotation_of_a_ciphertext_that_is_not_16_byte_aligned():
     odd.copy_(ct)
     assert odd.data_ptr() % 16 == 8
     assert torch.equal(B.ckks_rotate_hoisted(P, odd, 4, [5], [h]), B.ckks_rotate_hoisted(P, ct, 4, [5], [h]))
+
+
+@pytest.mark.parametrize("steps", [[5], [5] * 32, [5, 9] * 16])
+def test_rotations_by_either_gather(steps):
+    """Few workgroups gather digits residue by residue, many by pairs, whose loads must not need more than a word's alignment:
+    32 switches at 2^14 are above the line between the two, one is below; keys shared by neighbours and not."""
+    import torch
+    from paper_2604_09975_amd import binding as B
+    O = helpers.small_oracle(14, L=4, K=2, dnum=2, qbits=50, pbits=60)
+    _, P = make_pair(O)
+    r = W.rng(78)
+    ct = W.uniform_residues(r, O.q, O.N, lead=(2,))
+    keys = {s: W.uniform_residues(r, O.moduli, O.N, lead=(O.dnum, 2)) for s in set(steps)}
+    h = {s: B.ckks_galois_key_load(P, O.galois_elt(s), torch.from_numpy(k.view(np.int64)).cuda()) for s, k in keys.items()}
+    buf = torch.empty(2 * 4 * O.N + 1, dtype=torch.int64, device="cuda")
+    odd = buf[1:].view(2, 4, O.N)
+    odd.copy_(torch.from_numpy(ct.view(np.int64)))
+    got = B.ckks_rotate_hoisted(P, odd, 4, steps, [h[s] for s in steps])
+    for s in set(steps):
+        want = torch.from_numpy(O.rotate_hoisted(ct, 4, [O.galois_elt(s)], [keys[s]])[0].view(np.int64)).cuda()
+        for i in range(len(steps)):
+            assert steps[i] != s or torch.equal(got[i], want), i
+
+
+@pytest.mark.parametrize("logN,level", [(12, 11), (13, 12), (16, 12)])
+def test_more_digit_rows_than_one_launch_describes(logN, level):
+    """Twelve digits of one limb: 132 rows and more of extended digits, above the 128 of one row map; the forward tile passes go
+    out digit by digit."""
+    O = helpers.small_oracle(logN, L=12, K=1, dnum=12, qbits=50, pbits=60)
+    _, P = make_pair(O)
+    _run(O, P, level, [3], 1300 + logN, 2.0**40, hw=16)
