@@ -148,7 +148,7 @@ def test_encode_decode_errors():
 
 
 def test_more_vectors_than_one_chunk():
-    """N = 2^13, 131 vectors: more than the 128 whose transforms the scratch holds; every vector equals its own single call."""
+    """N = 2^13, 131 vectors, three passes of up to 64: vectors at both ends of each pass equal their own single calls."""
     from paper_2604_09975_amd import binding as B
     O = helpers.small_oracle(13, L=3, K=1, dnum=3, qbits=45, pbits=47)
     _, P = make_pair(O)
@@ -156,7 +156,7 @@ def test_more_vectors_than_one_chunk():
     got = B.ckks_encode(P, z, 2.0**30)
     res = torch.remainder(got, int(O.q[0])).reshape(131, 1, O.N)
     back = B.ckks_decode(P, res, 1, 2.0**30)
-    for i in (0, 1, 127, 128, 130):
+    for i in (0, 1, 63, 64, 127, 128, 130):
         assert torch.equal(got[i], B.ckks_encode(P, z[i:i + 1].contiguous(), 2.0**30)[0])
         assert torch.equal(back[i], B.ckks_decode(P, res[i:i + 1].contiguous(), 1, 2.0**30)[0])
     assert (back - z).abs().max().item() <= 0.5 * O.N / 2.0**30
