@@ -314,7 +314,8 @@ int ckks_client_decrypt(ckks_params_t *params, const ckks_secret_t *secret, cons
 
 /* ---- complex-slot encode / decode on the device (Sec. 2.1 Encode / Decode; slot order of Sec. 3.1) ----
  * Slot j of a plaintext m(X) is m(zeta^(5^j)), zeta = exp(i*pi/N), j < n = N/2, so that a rotation by r is the
- * cyclic left shift of the slot vector.  fp64 throughout (one N-point complex transform per vector); results agree
+ * cyclic left shift of the slot vector.  fp64 throughout (a complex transform of N points per vector for encode, of N/2
+ * for decode); results agree
  * with an exact evaluation to about 1e-13 * N * max|z| relative to the scale, so a rounded coefficient can differ by
  * one unit from another fp64 implementation's when it falls next to a half-integer. */
 

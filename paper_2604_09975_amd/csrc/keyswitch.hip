@@ -10,8 +10,8 @@
 //               domain, fused into the loads) -> INTT of the K special limbs ->
 //               base conversion P -> Q, subtract, times P^-1 (ModDown) ->
 //               + sigma_g(c0).
-// Base conversions use no floating-point correction term; sums of products are
-// accumulated in 128 bits and reduced once.
+// Base conversions use no floating-point correction term.  Sums of products modulo primes below 2^50 are kept in two
+// doubles and folded every few products (mac_device.h), modulo larger primes in 128 bits; either is reduced once.
 #include <algorithm>
 
 #include "ckks_internal.h"
@@ -426,9 +426,6 @@ struct ItemPack {
 // u[r][comp][t][k] = sum_j digits_r[j][t][sigma_g(k)] * key[j][comp][limb(t)][k] for the items r of one
 // group (same key, same Galois element): each key residue is loaded once and used for all of them.
 // grid: x = coefficients, y = limb t, z = group.
-// accumulate: add to what u holds (merged giant step: sums over the giant index stay in the extended basis).
-// fold_c0: also add sigma_g(c0) of each item into component 0 of its dst (the part of a rotation that needs
-// no key), so that nothing but ModDown(u) is left to add later.
 __global__ __launch_bounds__(KS_THREADS) void inner_product_kernel(ItemPack pack, u64 *__restrict__ u,
                                                                    const ModConst *__restrict__ mods, u32 level,
                                                                    u32 K, u32 L, u32 beta, u32 alpha, u32 logN) {
@@ -944,9 +941,11 @@ static moddown_mid_t moddown_mid_for(const ckks_params *p) {
 }
 
 // Workgroups among which ModDown splits the target groups of a tile: as many as fill the chip once (three workgroups per
-// CU at N = 2^16, 256 CUs) and no more.  One rotation at level 17 of 2^16: 256 workgroups 34 us, 768 25 us; one product at
-// 2^15 (12 + 4 primes) 128 and 256 workgroups, 19 and 14 us.  (ModUp's rule differs: its step 1 is cheap fp64 work, and 1152
-// workgroups in two rounds were no slower than 768 in one.)
+// CU at N = 2^16, 256 CUs) and no more.  Whole calls with at most 256 / 512 / 768 / 1024 / 1536 workgroups, us: one rotation
+// at 2^16, level 24: 180 / 170 / 164.5 / 164.5 / 164.5, level 17: 167 / 159 / 156.8 / 156.7 / 156.7, two at level 24: 214.4 up
+// to 1024, 211.6; a product and rescale at 2^16, level 24: 241 / 232 / 225.5 and no less above; at 2^15, 12 + 4 primes, two
+// switches 116.8, then 112.5, four 128.4 / 128.4 / 128.4 / 126.0 / 126.0; 2^14 the same at all.  (ModUp's rule differs: its
+// step 1 is cheap fp64 work, and 1152 workgroups in two rounds were no slower than 768 in one.)
 static u32 target_split(u32 workgroups, u32 groups) { return std::max<u32>(1, std::min<u32>(groups, 768 / workgroups)); }
 
 static void launch_moddown_mid(const ckks_params *p, const u64 *y, u64 *w, u32 n, u32 level, u32 ystride, u32 yoff,
@@ -997,7 +996,7 @@ __global__ __launch_bounds__(KS_THREADS) void moddown_final_kernel(ItemPack pack
     *dst = v;
 }
 
-// ---- fused kernels for N = 2^12 / 2^16 -------------------------------------------------------------
+// ---- kernels fused into the tile passes, N = 2^12 .. 2^17 ------------------------------------------
 // Key inner product on the special limbs feeding straight into the first pass of their inverse transform:
 // row (comp, k, r) of y = INTT-pass-B( sum_j sigma_g(d_j)[p_k] * key_j[comp][p_k] ).
 // grid: x = tile of 4096, y = ((k*n + r)*2 + comp): the two components of an item (same digit reads) and the
@@ -1621,7 +1620,7 @@ int ckks_galois_key_adopt(const ckks_params_t *P, uint64_t galois_elt, uint64_t 
         return CKKS_E_INVAL;
     }
     const size_t rows = (size_t)P->dnum * 2 * P->W;
-    // elementwise, each thread reads and writes its own word: in place is safe
+    // each thread reads the residues it writes before it writes them: in place is safe
     hipLaunchKernelGGL(key_form_kernel, dim3(P->N / (4 * KS_THREADS), (u32)rows), dim3(KS_THREADS), 0, (hipStream_t)stream,
                        d_key, d_key, P->d_mod, P->d_pinv, P->L, P->W, P->N);
     CKKS_LAUNCH_CHECK("key_form_kernel");

@@ -115,9 +115,9 @@ static inline PackedShape packed_shape(u32 N, u32 level, u32 GQ, u32 BP, bool wh
     return PackedShape{GQ, BP, (whole ? N : N / 2) / REC_CHUNK, level};
 }
 
-// grid: x = tile of TB (b,p) pairs from tile0, y = run of 512 coefficients (SYM: and their mirrors), z = limb (limbs.id:
-// the limbs this launch covers).  A thread owns two adjacent coefficients k, k+1 and TB pairs, of which those from bp0 to
-// bp1 - 1 are stored; two steps' weights and two steps' bank residues are on their way while two are multiplied.
+// grid: x = tile of TB (b,p) pairs, from the one that holds bp0, y = run of 512 coefficients (SYM: and their mirrors), z = limb (limbs.id:
+// the limbs this launch covers).  A thread owns two adjacent coefficients k, k+1 and NP pairs, of which those from bp0 to
+// bp1 - 1 are read and stored; two steps' weights and two steps' bank residues are on their way while two are multiplied.
 // SYM: plaintexts that encode REAL slot vectors.  Such a polynomial is fixed by X -> X^-1, so its transform is a
 // palindrome: w[k] = w[N-1-k] (the exponents 2*bitrev(k)+1 and 2*bitrev(N-1-k)+1 are negatives of each other mod 2N).
 // Only the first half of every weight limb is read; each value serves coefficient k and its mirror: the thread owns
@@ -131,10 +131,10 @@ static inline PackedShape packed_shape(u32 N, u32 level, u32 GQ, u32 BP, bool wh
 // swizzle: workgroups go to the XCDs round-robin and each XCD has its own L2, so the linear workgroup id is unfolded to
 // let one XCD walk all (b,p) tiles of a run of coefficients back to back: the bank lines of that run are then fetched
 // into one L2 once.
-// What bounds it (QKV layer, 34.0 GB of records, 2.4 GB of bank, 1.8 GB of sums): memory.  8.32 ms; without the products
-// 8.40, without the record loads 4.36, without the bank loads 7.05 (5.1 TB/s; a plain read reaches 5.3) when the whole
-// took 8.45.  The kernel with
-// a quotient per product was bound by fp64 issue: 8.66 ms with the vector units 92 % busy; these sums keep them 55 % busy.
+// What bounds it (QKV layer, 34.0 GB of records, 2.4 GB of bank, 1.8 GB of sums): memory.  8.43 ms (8.32 to 8.47 from card to
+// card); an earlier form that took 8.45 ms took 8.40 without the products, 4.36 without the record loads and 7.05 without the
+// bank loads (5.1 TB/s; a plain read reaches 5.3).  The kernel with a quotient per product was bound by fp64 issue: 8.66 ms
+// with the vector units 92 % busy; these sums keep them 55 % busy.
 template <bool SYM, bool PACKED, u32 NP>
 __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *__restrict__ bank,
                                                               const void *__restrict__ w, u64 *__restrict__ acc,
@@ -1681,7 +1681,8 @@ int ckks_rescale_static(ckks_params_t *P, const uint64_t *d_ct_in, uint32_t leve
     u64 *d_r = nullptr;
     int rc = static_scratch_ptr(device, &d_r);
     if (rc) return rc;
-    // every word of the buffer this call reads is written first (take_last_limb_kernel): nothing to clear
+    // every word of the buffer this call reads is written first, by rescale_intt_kernel or (other rings and chains)
+    // take_last_limb_kernel: nothing to clear
     return rescale_rows(P, d_ct_in, level, 2 * n_ct, d_ct_out, d_r, stream);
 }
 
