@@ -1009,7 +1009,7 @@ __device__ __forceinline__ pair_t load_key(const pair_t *p) {
     return NT ? __builtin_nontemporal_load(p) : *p;
 }
 
-template <bool KEY_NT>
+template <bool KEY_NT, bool PAIR>
 __global__ __launch_bounds__(NTT_THREADS) void ip_intt_kernel(ItemPack pack, u64 *__restrict__ y,
                                                               const ModConst *__restrict__ mods,
                                                               const ModFp *__restrict__ modf,
@@ -1029,25 +1029,29 @@ __global__ __launch_bounds__(NTT_THREADS) void ip_intt_kernel(ItemPack pack, u64
     u64 *out = y + (((size_t)r * 2 + comp) * K + k) * N;
     auto store = [&](u32 idx, u64 v) { out[idx] = v; };
     // inner product into LDS on pairs of adjacent residues (16-byte key loads), two pairs at a time so that
-    // their loads are in flight together.  (Digits by 16-byte loads as well: a bank of two at level 2 of 2^16 98.5 us instead
-    // of 97.7, 27 at level 24 the same.)
+    // their loads are in flight together
     const u32 tid = threadIdx.x, base = blockIdx.x << 12;
     constexpr u32 EPP = EPI / 2;
     for (u32 i0 = 0; i0 < 8; i0 += EPP) {
         pair_t dv[EPP][MAX_BETA], kv[EPP][MAX_BETA];
+        u32 kp[EPP];
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
-            const u32 idx = base + 2 * (tid + 256 * (i0 + e)), kp = galois_index(idx, g, logN);
+            const u32 idx = base + 2 * (tid + 256 * (i0 + e));
+            kp[e] = galois_index(idx, g, logN);
 #pragma unroll
             for (u32 j = 0; j < MAX_BETA; ++j)
                 if (j < beta) {
-                    dv[e][j] = load_two<false>(dig + (size_t)j * Wl * N, kp);
+                    dv[e][j] = load_two<PAIR>(dig + (size_t)j * Wl * N, kp[e]);
                     kv[e][j] = load_key<KEY_NT>(reinterpret_cast<const pair_t *>(key + (size_t)j * 2 * Wt * N + idx));
                 }
         }
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
             const u32 loc = 2 * (tid + 256 * (i0 + e));
+#pragma unroll
+            for (u32 j = 0; j < MAX_BETA; ++j)
+                if (j < beta) dv[e][j] = turned<PAIR>(dv[e][j], kp[e]);
 #pragma unroll
             for (u32 z = 0; z < 2; ++z) {
                 u128 acc = {0, 0};
@@ -1424,10 +1428,15 @@ int switch_batch(ckks_params *p, u32 level, const SwitchItem *items, u32 n, u64 
         // at N = 2^12 the tile pass is the whole inverse transform and carries the (P/p_k)^-1 scaling itself
         const bool whole = p->logN == 12;
         const bool own_keys = n_groups == n;               // no two neighbouring items share a key
-        hipLaunchKernelGGL(own_keys ? ip_intt_kernel<true> : ip_intt_kernel<false>, dim3(tiles, n * 2 * K),
-                           dim3(NTT_THREADS), 0, stream, pack, y, p->d_mod, whole ? p->d_modf_dn : p->d_modf,
-                           p->d_tws_inv, p->d_twf_inv, whole ? p->d_ninvs_dn : p->d_ninvs, n, level, K, L, beta,
-                           p->logN);
+        // digits by 16-byte gathers above eight workgroups per CU: by 8-byte and by 16-byte loads one rotation at level 1 of
+        // 2^16 (256 workgroups) 85.8 and 86.6 us, two at level 1 94.9 and 95.7, four at level 24 (1024) 299.7 and 300.2, 27
+        // (6912) the same within the runs' 0.3 %
+        const bool ip_pair = tiles * n * 2 * K > 2048;
+        const auto ip_intt = own_keys ? (ip_pair ? ip_intt_kernel<true, true> : ip_intt_kernel<true, false>)
+                                      : (ip_pair ? ip_intt_kernel<false, true> : ip_intt_kernel<false, false>);
+        hipLaunchKernelGGL(ip_intt, dim3(tiles, n * 2 * K), dim3(NTT_THREADS), 0, stream, pack, y, p->d_mod,
+                           whole ? p->d_modf_dn : p->d_modf, p->d_tws_inv, p->d_twf_inv,
+                           whole ? p->d_ninvs_dn : p->d_ninvs, n, level, K, L, beta, p->logN);
         CKKS_LAUNCH_CHECK("ip_intt_kernel");
         p->limb_ntts += (u64)n * 2 * K;
         int rc;

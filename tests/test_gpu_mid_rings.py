@@ -60,21 +60,22 @@ def test_rotation_of_a_ciphertext_that_is_not_16_byte_aligned():
 @pytest.mark.parametrize("steps", [[5], [5] * 32, [5, 9] * 16])
 def test_rotations_by_either_gather(steps):
     """Few workgroups gather digits residue by residue, many by pairs, whose loads must not need more than a word's alignment:
-    32 switches at 2^14 are above the line between the two, one is below; keys shared by neighbours and not."""
+    32 switches at 2^15 with six special primes are above the lines between the two in both kernels, one is below; keys
+    shared by neighbours and not."""
     import torch
     from paper_2604_09975_amd import binding as B
-    O = helpers.small_oracle(14, L=4, K=2, dnum=2, qbits=50, pbits=60)
+    O = helpers.small_oracle(15, L=6, K=6, dnum=1, qbits=50, pbits=60)
     _, P = make_pair(O)
     r = W.rng(78)
     ct = W.uniform_residues(r, O.q, O.N, lead=(2,))
     keys = {s: W.uniform_residues(r, O.moduli, O.N, lead=(O.dnum, 2)) for s in set(steps)}
     h = {s: B.ckks_galois_key_load(P, O.galois_elt(s), torch.from_numpy(k.view(np.int64)).cuda()) for s, k in keys.items()}
-    buf = torch.empty(2 * 4 * O.N + 1, dtype=torch.int64, device="cuda")
-    odd = buf[1:].view(2, 4, O.N)
+    buf = torch.empty(2 * 6 * O.N + 1, dtype=torch.int64, device="cuda")
+    odd = buf[1:].view(2, 6, O.N)
     odd.copy_(torch.from_numpy(ct.view(np.int64)))
-    got = B.ckks_rotate_hoisted(P, odd, 4, steps, [h[s] for s in steps])
+    got = B.ckks_rotate_hoisted(P, odd, 6, steps, [h[s] for s in steps])
     for s in set(steps):
-        want = torch.from_numpy(O.rotate_hoisted(ct, 4, [O.galois_elt(s)], [keys[s]])[0].view(np.int64)).cuda()
+        want = torch.from_numpy(O.rotate_hoisted(ct, 6, [O.galois_elt(s)], [keys[s]])[0].view(np.int64)).cuda()
         for i in range(len(steps)):
             assert steps[i] != s or torch.equal(got[i], want), i
 
