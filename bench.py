@@ -668,10 +668,10 @@ def main():
     # the same count with unpacked half limbs (8 bytes per residue), the unit the byte budget of the method is
     # usually stated in
     mac_bytes_8 = (n_diag * level // 2 + G * n1 * 2 * level + B_out * N2 * 2 * level) * limb_poly
-    if args.fused_qk:   # the complex Q+iK blocks (half of the blocks) are read in full, 8 bytes per residue
-        n_cplx = G * n1 * (B_out // 2) * N2
-        mac_bytes += n_cplx * level * (limb_poly - half_limb_packed)
-        mac_bytes_8 += n_cplx * level * limb_poly // 2
+    # complex diagonals (the Q+iK half of the blocks, or all of complex pairs) are whole limbs in the same store
+    n_cplx = G * n1 * (B_out // 2) * N2 if args.fused_qk else n_diag if args.pair_compression else 0
+    mac_bytes += n_cplx * level * half_limb_packed
+    mac_bytes_8 += n_cplx * level * limb_poly // 2
     # the same launch in double-precision operations: MAC_INSTS per residue product (the quotient is taken once per
     # eight products, not counted here), 4 products per stored weight residue
     mac_ops = MAC_INSTS * 4.0 * n_diag * level * (N // 2)
@@ -684,9 +684,7 @@ def main():
     key_bytes = (len(S["baby"]) + len(S["giant"]) + (1 if S["conj"] is not None else 0)) * P.dnum * 2 * (P.L + P.K) * limb_poly
     io_bytes = (G + B_out) * 2 * level * limb_poly
     step_bytes_8 = n_diag * level * limb_poly + key_bytes + io_bytes
-    n_cplx_w = (G * n1 * (B_out // 2) * N2) if args.fused_qk else (n_diag if args.pair_compression else 0)
-    step_bytes_stored = (n_diag - n_cplx_w) * level * half_limb_packed + n_cplx_w * level * 2 * half_limb_packed \
-        + key_bytes + io_bytes
+    step_bytes_stored = (n_diag + n_cplx) * level * half_limb_packed + key_bytes + io_bytes
     out = {
         "metric": "ct-pt matmul latency ms (128x768x2304)",
         "value": ms_per_step,
