@@ -944,8 +944,8 @@ static moddown_mid_t moddown_mid_for(const ckks_params *p) {
 // CU at N = 2^16, 256 CUs) and no more.  Whole calls with at most 256 / 512 / 768 / 1024 / 1536 workgroups, us: one rotation
 // at 2^16, level 24: 180 / 170 / 164.5 / 164.5 / 164.5, level 17: 167 / 159 / 156.8 / 156.7 / 156.7, two at level 24: 214.4 up
 // to 1024, 211.6; a product and rescale at 2^16, level 24: 241 / 232 / 225.5 and no less above; at 2^15, 12 + 4 primes, two
-// switches 116.8, then 112.5, four 128.4 / 128.4 / 128.4 / 126.0 / 126.0; 2^14 the same at all.  (ModUp's rule differs: its
-// step 1 is cheap fp64 work, and 1152 workgroups in two rounds were no slower than 768 in one.)
+// switches 116.8, then 112.5, four 128.4 / 128.4 / 128.4 / 126.0 / 126.0; 2^14 the same at all.  (ModUp's step 1 is
+// cheap fp64 work, and its rule differs: see decompose.)
 static u32 target_split(u32 workgroups, u32 groups) { return std::max<u32>(1, std::min<u32>(groups, 768 / workgroups)); }
 
 static void launch_moddown_mid(const ckks_params *p, const u64 *y, u64 *w, u32 n, u32 level, u32 ystride, u32 yoff,
@@ -1238,6 +1238,9 @@ int decompose(ckks_params *p, const u64 *const *c1, u32 n, u32 level, u64 *d_dig
         if (p->logN <= 16 && all_fp && sp60 && alpha <= 8 && K <= 8) {
             // the column passes of both transforms ride in the base conversion: c1 read once, digits written once
             const u32 tgroups = (Wl - std::min(alpha, level) + UP_TG - 1) / UP_TG, tiles = N / MID_TILE;
+            // all target groups apart below 1024 workgroups: one rotation at 2^16, level 24 / 17 / 9, a product and rescale at
+            // 2^16 and 2^15 165.1 / 155.1 / 115.6, 222.2 and 131.3 us; never split 169.4 / 158.5 / 120.8, 226.4 and 135.8; split
+            // as ModDown's are 166.1 / 156.7 / 115.5, 223.5 and 131.3; with the line at 3072 as at 1024, projections too
             const u32 tsplit = n * beta * tiles < 1024 ? std::max<u32>(1, tgroups) : 1;
             hipLaunchKernelGGL(modup_mid_for(p), dim3(tiles * tsplit, beta, n), dim3(256), 0, stream, d_tmp,
                                d_digits, p->d_mod, p->d_modf, lt->d_modf_up, p->d_twf_inv, p->d_twf_fwd, p->d_tws_fwd,
