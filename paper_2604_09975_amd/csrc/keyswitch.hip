@@ -84,13 +84,14 @@ __global__ __launch_bounds__(KS_THREADS) void gather_c1_kernel(PtrPack src, u64 
 // The same collection fused with the first pass of the inverse transform (rings with the two-pass kernels):
 // reads the c1 halves where they are, writes tmp[r][i] half transformed.  grid: x = 4096-residue tiles,
 // y = r * level + i.
-__global__ __launch_bounds__(NTT_THREADS) void gather_intt_kernel(PtrPack src, u64 *__restrict__ tmp,
+template <u32 RL>
+__global__ __launch_bounds__(Tile<RL>::THREADS) void gather_intt_kernel(PtrPack src, u64 *__restrict__ tmp,
                                                                   const ModConst *__restrict__ mods,
                                                                   const ModFp *__restrict__ modf,
                                                                   const u64 *__restrict__ tw,
                                                                   const double *__restrict__ twf,
                                                                   const u64 *__restrict__ ninv, u32 level, u32 logN) {
-    __shared__ u64 lds[FAST_LDS_WORDS];
+    __shared__ u64 lds[Tile<RL>::WORDS];
     const u32 r = blockIdx.y / level, i = blockIdx.y % level;
     const u64 *in = src.p[r] + ((size_t)i << logN);
     u64 *out = tmp + ((size_t)blockIdx.y << logN);
@@ -98,9 +99,9 @@ __global__ __launch_bounds__(NTT_THREADS) void gather_intt_kernel(PtrPack src, u
     auto store = [&](u32 idx, u64 v) { out[idx] = v; };
     const ModFp mf = modf[i];
     if (mf.ok)
-        pass_b_body<true>(make_field_fp(mf, twf, i, logN), logN, lds, load, store);
+        pass_b_body<true, RL>(make_field_fp(mf, twf, i, logN), logN, lds, load, store);
     else
-        pass_b_body<true>(make_field_int(mods, tw, ninv, i, logN), logN, lds, load, store);
+        pass_b_body<true, RL>(make_field_int(mods, tw, ninv, i, logN), logN, lds, load, store);
 }
 
 // Per ciphertext r and digit j: y_i = c_i * (Q_D/q_i)^-1 mod q_i for the limbs of the digit, then for
@@ -1009,15 +1010,16 @@ __device__ __forceinline__ pair_t load_key(const pair_t *p) {
     return NT ? __builtin_nontemporal_load(p) : *p;
 }
 
-template <bool KEY_NT, bool PAIR>
-__global__ __launch_bounds__(NTT_THREADS) void ip_intt_kernel(ItemPack pack, u64 *__restrict__ y,
+template <bool KEY_NT, bool PAIR, u32 RL>
+__global__ __launch_bounds__(Tile<RL>::THREADS) void ip_intt_kernel(ItemPack pack, u64 *__restrict__ y,
                                                               const ModConst *__restrict__ mods,
                                                               const ModFp *__restrict__ modf,
                                                               const u64 *__restrict__ tw_inv,
                                                               const double *__restrict__ twf_inv,
                                                               const u64 *__restrict__ ninv, u32 n, u32 level, u32 K,
                                                               u32 L, u32 beta, u32 logN) {
-    __shared__ u64 lds[FAST_LDS_WORDS];
+    typedef Tile<RL> TL;
+    __shared__ u64 lds[TL::WORDS];
     const u32 N = 1u << logN;
     const u32 comp = blockIdx.y & 1, r = (blockIdx.y >> 1) % n, k = (blockIdx.y >> 1) / n;
     const u32 gl = L + k, t = level + k, Wl = level + K, Wt = L + K;
@@ -1028,16 +1030,16 @@ __global__ __launch_bounds__(NTT_THREADS) void ip_intt_kernel(ItemPack pack, u64
     const u32 g = (u32)it.galois_elt;
     u64 *out = y + (((size_t)r * 2 + comp) * K + k) * N;
     auto store = [&](u32 idx, u64 v) { out[idx] = v; };
-    // inner product into LDS on pairs of adjacent residues (16-byte key loads), two pairs at a time so that
-    // their loads are in flight together
+    // inner product into LDS on pairs of adjacent residues (16-byte key loads), two pairs (RL < 4: all of them) at a time so
+    // that their loads are in flight together
     const u32 tid = threadIdx.x, base = blockIdx.x << 12;
-    constexpr u32 EPP = EPI / 2;
-    for (u32 i0 = 0; i0 < 8; i0 += EPP) {
+    constexpr u32 EPP = RL < 4 ? TL::R / 2 : EPI / 2;
+    for (u32 i0 = 0; i0 < TL::R / 2; i0 += EPP) {
         pair_t dv[EPP][MAX_BETA], kv[EPP][MAX_BETA];
         u32 kp[EPP];
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
-            const u32 idx = base + 2 * (tid + 256 * (i0 + e));
+            const u32 idx = base + TL::pair(tid, i0 + e);
             kp[e] = galois_index(idx, g, logN);
 #pragma unroll
             for (u32 j = 0; j < MAX_BETA; ++j)
@@ -1048,7 +1050,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ip_intt_kernel(ItemPack pack, u64
         }
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
-            const u32 loc = 2 * (tid + 256 * (i0 + e));
+            const u32 loc = TL::pair(tid, i0 + e);
 #pragma unroll
             for (u32 j = 0; j < MAX_BETA; ++j)
                 if (j < beta) dv[e][j] = turned<PAIR>(dv[e][j], kp[e]);
@@ -1058,31 +1060,32 @@ __global__ __launch_bounds__(NTT_THREADS) void ip_intt_kernel(ItemPack pack, u64
 #pragma unroll
                 for (u32 j = 0; j < MAX_BETA; ++j)
                     if (j < beta) mac(acc, dv[e][j][z], kv[e][j][z]);
-                lds[lds_pad(loc + z)] = redc_wide(acc, m);
+                lds[TL::slot(loc + z)] = redc_wide(acc, m);
             }
         }
     }
-    __syncthreads();
     const ModFp mf = modf[gl];
     if (mf.ok)
-        pass_b_inv_from_lds(make_field_fp(mf, twf_inv, gl, logN), logN, lds, store);
+        pass_b_inv_from_lds<RL>(make_field_fp(mf, twf_inv, gl, logN), logN, lds, store);
     else
-        pass_b_inv_from_lds(make_field_int(mods, tw_inv, ninv, gl, logN), logN, lds, store);
+        pass_b_inv_from_lds<RL>(make_field_int(mods, tw_inv, ninv, gl, logN), logN, lds, store);
 }
 
 // Last pass of the forward transform of w fused with the rest of the key switch on limb q_i:
 //   dst[comp][i] (+)= sum_j sigma_g(d_j)[q_i] * key_j[comp][q_i] - NTT(w)[i]  (+ sigma_g(c0)[i] if comp = 0)
 // (the keys and w carry the P^-1 of ModDown).
 // grid: x = tile of 4096, y = ((i*n + r)*2 + comp), neighbours share digit and key lines in L2 as above.
-template <bool KEY_NT, bool PAIR>
-__global__ __launch_bounds__(NTT_THREADS) void passb_final_kernel(ItemPack pack, const u64 *__restrict__ w,
+template <bool KEY_NT, bool PAIR, u32 RL>
+__global__ __launch_bounds__(Tile<RL>::THREADS) void passb_final_kernel(ItemPack pack, const u64 *__restrict__ w,
                                                                   const ModConst *__restrict__ mods,
                                                                   const ModFp *__restrict__ modf,
                                                                   const u64 *__restrict__ tw_fwd,
                                                                   const double *__restrict__ twf_fwd,
                                                                   const u64 *__restrict__ ninv, u32 n, u32 level,
                                                                   u32 K, u32 L, u32 beta, u32 alpha, u32 logN) {
-    __shared__ u64 lds[FAST_LDS_WORDS];
+    typedef Tile<RL> TL;
+    static_assert(RL == 4 || !PAIR, "operands that share a register with gathered ones are not turned");
+    __shared__ u64 lds[TL::WORDS];
     const u32 N = 1u << logN;
     const u32 comp = blockIdx.y & 1, r = (blockIdx.y >> 1) % n, i = (blockIdx.y >> 1) / n;
     const u32 Wl = level + K, Wt = L + K;
@@ -1100,22 +1103,19 @@ __global__ __launch_bounds__(NTT_THREADS) void passb_final_kernel(ItemPack pack,
     const u32 g = (u32)it.galois_elt, accumulate = it.accumulate;
     auto load = [&](u32 idx) -> u64 { return __builtin_nontemporal_load(wrow + idx); };
     const ModFp mf = modf[i];
-    if (mf.ok)   // the fp64 epilogue takes the transformed correction as doubles, |x| <= q/2
-        pass_b_fwd_to_lds<true>(make_field_fp(mf, twf_fwd, i, logN), logN, lds, load);
-    else
-        pass_b_fwd_to_lds(make_field_int(mods, tw_fwd, ninv, i, logN), logN, lds, load);
     // epilogue on pairs of adjacent residues (16-byte accesses to the streamed operands), two pairs at a time so
-    // that their loads are in flight together.  Keys, w and the output are streamed once: non-temporal, so that
+    // that their loads are in flight together (RL < 4: all of them, during the transform).  Keys, w and the output are streamed once: non-temporal, so that
     // they do not push the digit rows (re-read by every item of the batch) out of L2.
     const u32 tid = threadIdx.x, base = blockIdx.x << 12;
-    constexpr u32 EPP = EPI / 2;
+    constexpr u32 EPP = RL < 4 ? TL::R / 2 : EPI / 2;
     const bool fold = comp == 0 && it.c0;
-    for (u32 i0 = 0; i0 < 8; i0 += EPP) {
-        pair_t dv[EPP][MAX_BETA], kv[EPP][MAX_BETA], cv[EPP], ov[EPP];
-        u32 kp[EPP];
+    pair_t dv[EPP][MAX_BETA], kv[EPP][MAX_BETA], cv[EPP], ov[EPP];
+    u32 kp[EPP];
+    auto load_dst = [&](u32 idx) { return __builtin_nontemporal_load(reinterpret_cast<const pair_t *>(dst + idx)); };
+    auto load_operands = [&](u32 i0) {
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
-            const u32 idx = base + 2 * (tid + 256 * (i0 + e));
+            const u32 idx = base + TL::pair(tid, i0 + e);
             kp[e] = galois_index(idx, g, logN);
 #pragma unroll
             for (u32 j = 0; j < MAX_BETA; ++j)
@@ -1123,12 +1123,23 @@ __global__ __launch_bounds__(NTT_THREADS) void passb_final_kernel(ItemPack pack,
                     dv[e][j] = load_two<PAIR>(drow[j], kp[e]);
                     kv[e][j] = load_key<KEY_NT>(reinterpret_cast<const pair_t *>(key + (size_t)j * 2 * Wt * N + idx));
                 }
-            cv[e] = fold ? load_two<PAIR>(c0, kp[e]) : pair_t{0, 0};
-            ov[e] = accumulate ? __builtin_nontemporal_load(reinterpret_cast<const pair_t *>(dst + idx)) : pair_t{0, 0};
+            cv[e] = fold ? load_two<PAIR>(c0, kp[e]) : accumulate && RL < 4 ? load_dst(idx) : pair_t{0, 0};
+            if (RL == 4) ov[e] = accumulate ? load_dst(idx) : pair_t{0, 0};
         }
+    };
+    if (RL < 4) load_operands(0);
+    if (mf.ok)   // the fp64 epilogue takes the transformed correction as doubles, |x| <= q/2
+        pass_b_fwd_to_lds<true, RL>(make_field_fp(mf, twf_fwd, i, logN), logN, lds, load);
+    else
+        pass_b_fwd_to_lds<false, RL>(make_field_int(mods, tw_fwd, ninv, i, logN), logN, lds, load);
+    for (u32 i0 = 0; i0 < TL::R / 2; i0 += EPP) {
+        if (RL == 4) load_operands(i0);
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
-            const u32 loc = 2 * (tid + 256 * (i0 + e));
+            const u32 loc = TL::pair(tid, i0 + e);
+            // RL < 4: one array for c0 or dst (128 registers is what 16 wavefronts a workgroup leave); where both are added,
+            // dst comes now
+            if (RL < 4) ov[e] = accumulate && fold ? load_dst(base + loc) : pair_t{0, 0};
             __builtin_amdgcn_sched_barrier(0);
             cv[e] = turned<PAIR>(cv[e], kp[e]);
 #pragma unroll
@@ -1145,7 +1156,7 @@ __global__ __launch_bounds__(NTT_THREADS) void passb_final_kernel(ItemPack pack,
                         if (j < beta) sum.mac(canonical_double(dv[e][j][z]), __longlong_as_double((long long)kv[e][j][z]));
                     sum.fold(mf.q, mf.u);
                     sum.l += (canonical_double(cv[e][z]) + canonical_double(ov[e][z])) -
-                             __longlong_as_double((long long)lds[lds_pad(loc + z)]);
+                             __longlong_as_double((long long)lds[TL::slot(loc + z)]);
                     if (it.balanced)
                         out[z] = (u64)__double_as_longlong(fma(-rint(sum.l * mf.u), mf.q, sum.l));
                     else
@@ -1155,7 +1166,7 @@ __global__ __launch_bounds__(NTT_THREADS) void passb_final_kernel(ItemPack pack,
 #pragma unroll
                     for (u32 j = 0; j < MAX_BETA; ++j)
                         if (j < beta) mac(acc, dv[e][j][z], kv[e][j][z]);
-                    u64 v = sub_mod(redc_wide(acc, m), lds[lds_pad(loc + z)], m.q);
+                    u64 v = sub_mod(redc_wide(acc, m), lds[TL::slot(loc + z)], m.q);
                     v = add_mod(v, cv[e][z], m.q);
                     out[z] = add_mod(v, ov[e][z], m.q);
                 }
@@ -1231,7 +1242,9 @@ int decompose(ckks_params *p, const u64 *const *c1, u32 n, u32 level, u64 *d_dig
     bool sp60 = true;
     for (u32 k = 0; k < K; ++k) sp60 = sp60 && (p->mod[L + k] >> 60) == 0;
     if (fast_ring(p)) {
-        hipLaunchKernelGGL(gather_intt_kernel, dim3(N >> 12, n * level), dim3(NTT_THREADS), 0, stream, src, d_tmp,
+        const bool wide = wide_tiles((u64)(N >> 12) * n * level);
+        hipLaunchKernelGGL(wide ? gather_intt_kernel<WIDE_RL> : gather_intt_kernel<4>, dim3(N >> 12, n * level),
+                           dim3(tile_threads(wide)), 0, stream, src, d_tmp,
                            p->d_mod, p->d_modf, p->d_tws_inv, p->d_twf_inv, p->d_ninvs, level, p->logN);
         CKKS_LAUNCH_CHECK("gather_intt_kernel");
         p->limb_ntts += (u64)n * level;
@@ -1435,9 +1448,14 @@ int switch_batch(ckks_params *p, u32 level, const SwitchItem *items, u32 n, u64 
         // 2^16 (256 workgroups) 85.8 and 86.6 us, two at level 1 94.9 and 95.7, four at level 24 (1024) 299.7 and 300.2, 27
         // (6912) the same within the runs' 0.3 %
         const bool ip_pair = tiles * n * 2 * K > 2048;
-        const auto ip_intt = own_keys ? (ip_pair ? ip_intt_kernel<true, true> : ip_intt_kernel<true, false>)
-                                      : (ip_pair ? ip_intt_kernel<false, true> : ip_intt_kernel<false, false>);
-        hipLaunchKernelGGL(ip_intt, dim3(tiles, n * 2 * K), dim3(NTT_THREADS), 0, stream, pack, y, p->d_mod,
+        const bool ip_wide = wide_tiles(tiles * n * 2 * K);
+        const auto ip_intt = own_keys ? (ip_wide   ? ip_intt_kernel<true, false, WIDE_RL>
+                                         : ip_pair ? ip_intt_kernel<true, true, 4>
+                                                   : ip_intt_kernel<true, false, 4>)
+                                      : (ip_wide   ? ip_intt_kernel<false, false, WIDE_RL>
+                                         : ip_pair ? ip_intt_kernel<false, true, 4>
+                                                   : ip_intt_kernel<false, false, 4>);
+        hipLaunchKernelGGL(ip_intt, dim3(tiles, n * 2 * K), dim3(tile_threads(ip_wide)), 0, stream, pack, y, p->d_mod,
                            whole ? p->d_modf_dn : p->d_modf, p->d_tws_inv, p->d_twf_inv,
                            whole ? p->d_ninvs_dn : p->d_ninvs, n, level, K, L, beta, p->logN);
         CKKS_LAUNCH_CHECK("ip_intt_kernel");
@@ -1463,10 +1481,15 @@ int switch_batch(ckks_params *p, u32 level, const SwitchItem *items, u32 n, u64 
         // us, by 16-byte ones 165.5; 24 switches at 2^14, level 5 (960) and the rest of their call 169 and 167; eight rotations
         // at 2^16, level 24 (6144) 496 and 493.
         const bool pair = tiles * n * 2 * level > 768;
-        const auto passb = own_keys ? (pair ? passb_final_kernel<true, true> : passb_final_kernel<true, false>)
-                                    : (pair ? passb_final_kernel<false, true> : passb_final_kernel<false, false>);
+        const bool wide = wide_tiles(tiles * n * 2 * level);
+        const auto passb = own_keys ? (wide   ? passb_final_kernel<true, false, WIDE_RL>
+                                       : pair ? passb_final_kernel<true, true, 4>
+                                              : passb_final_kernel<true, false, 4>)
+                                    : (wide   ? passb_final_kernel<false, false, WIDE_RL>
+                                       : pair ? passb_final_kernel<false, true, 4>
+                                              : passb_final_kernel<false, false, 4>);
         hipLaunchKernelGGL(passb, dim3(tiles, n * 2 * level),
-                           dim3(NTT_THREADS), 0, stream, pack, w, p->d_mod, p->d_modf, p->d_tws_fwd, p->d_twf_fwd,
+                           dim3(tile_threads(wide)), 0, stream, pack, w, p->d_mod, p->d_modf, p->d_tws_fwd, p->d_twf_fwd,
                            p->d_ninvs, n, level, K, L, beta, p->alpha, p->logN);
         CKKS_LAUNCH_CHECK("passb_final_kernel");
         return CKKS_OK;

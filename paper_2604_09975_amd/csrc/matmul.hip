@@ -42,7 +42,7 @@ __global__ __launch_bounds__(NTT_THREADS) void expand_pass_kernel(const int64_t 
                                                                   const double *__restrict__ twf,
                                                                   const u64 *__restrict__ ninvs, u32 level) {
     constexpr u32 logN = 12 + LOGR;
-    __shared__ u64 lds[LOGR ? 1 : FAST_LDS_WORDS];
+    __shared__ u64 lds[LOGR ? 1 : Tile<4>::WORDS];
     const u32 d = blockIdx.y / level, i = blockIdx.y % level;
     const ModConst m = mods[i];
     const ModFp mf = modf[i];
@@ -633,16 +633,17 @@ __global__ __launch_bounds__(EW_THREADS) void to_weight_form_kernel(u64 *data, c
 constexpr u32 RS_TILE = 512;
 
 // grid: x = 4096-residue tiles, y = row
-__global__ __launch_bounds__(NTT_THREADS) void rescale_intt_kernel(const u64 *__restrict__ in, u64 *__restrict__ r,
+template <u32 RL>
+__global__ __launch_bounds__(Tile<RL>::THREADS) void rescale_intt_kernel(const u64 *__restrict__ in, u64 *__restrict__ r,
                                                                    const ModFp *__restrict__ modf,
                                                                    const double *__restrict__ twf_inv, u32 level,
                                                                    u32 logN) {
-    __shared__ u64 lds[FAST_LDS_WORDS];
+    __shared__ u64 lds[Tile<RL>::WORDS];
     const u64 *src = in + (((size_t)blockIdx.y * level + level - 1) << logN);
     u64 *dst = r + ((size_t)blockIdx.y << logN);
     auto load = [&](u32 idx) { return src[idx]; };
     auto store = [&](u32 idx, u64 v) { dst[idx] = v; };
-    pass_b_body<true>(make_field_fp(modf[level - 1], twf_inv, level - 1, logN), logN, lds, load, store);
+    pass_b_body<true, RL>(make_field_fp(modf[level - 1], twf_inv, level - 1, logN), logN, lds, load, store);
 }
 
 // grid: x = tiles of 512 coefficients, y = row; out rows [rows][level-1]
@@ -709,29 +710,31 @@ __global__ __launch_bounds__(256) void rescale_mid_kernel(const u64 *__restrict_
 }
 
 // grid: x = 4096-residue tiles, y = limb, z = row; out holds delta after its column pass on entry
-__global__ __launch_bounds__(NTT_THREADS) void rescale_tile_kernel(const u64 *__restrict__ in, u64 *out,
+template <u32 RL>
+__global__ __launch_bounds__(Tile<RL>::THREADS) void rescale_tile_kernel(const u64 *__restrict__ in, u64 *out,
                                                                    const ModFp *__restrict__ modf,
                                                                    const ModConst *__restrict__ mods,
                                                                    const double *__restrict__ twf_fwd,
                                                                    const u64 *__restrict__ qlinv, u32 level, u32 logN) {
     typedef u64 vec_t __attribute__((ext_vector_type(2)));
-    __shared__ u64 lds[FAST_LDS_WORDS];
+    typedef Tile<RL> TL;
+    __shared__ u64 lds[TL::WORDS];
     const u32 i = blockIdx.y, row = blockIdx.z, tid = threadIdx.x, base = blockIdx.x << 12;
     const u64 *src = in + (((size_t)row * level + i) << logN);
     u64 *dst = out + (((size_t)row * (level - 1) + i) << logN);
     const FieldFp f = make_field_fp(modf[i], twf_fwd, i, logN);
     const double c = canonical_double(mont_mul(qlinv[i], 1, mods[i]));        // q_l^-1 (stored in Montgomery form)
-    vec_t x[8];
+    vec_t x[TL::R / 2];
 #pragma unroll
-    for (u32 e = 0; e < 8; ++e) x[e] = *reinterpret_cast<const vec_t *>(src + base + 2 * (tid + 256 * e));
+    for (u32 e = 0; e < TL::R / 2; ++e) x[e] = *reinterpret_cast<const vec_t *>(src + base + TL::pair(tid, e));
     auto load = [&](u32 idx) { return dst[idx]; };
-    pass_b_fwd_to_lds<true>(f, logN, lds, load);
+    pass_b_fwd_to_lds<true, RL>(f, logN, lds, load);
 #pragma unroll
-    for (u32 e = 0; e < 8; ++e) {
-        const u32 loc = 2 * (tid + 256 * e);
+    for (u32 e = 0; e < TL::R / 2; ++e) {
+        const u32 loc = TL::pair(tid, e);
 #pragma unroll
         for (u32 z = 0; z < 2; ++z)
-            x[e][z] = f.out(f.mul(canonical_double(x[e][z]) - __longlong_as_double((long long)lds[lds_pad(loc + z)]), c));
+            x[e][z] = f.out(f.mul(canonical_double(x[e][z]) - __longlong_as_double((long long)lds[TL::slot(loc + z)]), c));
         *reinterpret_cast<vec_t *>(dst + base + loc) = x[e];
     }
 }
@@ -1531,7 +1534,9 @@ static int rescale_rows(ckks_params *P, const u64 *d_in, u32 level, u32 rows, u6
     for (u32 i = 0; i < level; ++i) fused = fused && (P->mod[i] >> 50) == 0;
     if (fused) {
         const u64 *qlinv = P->d_qlinv + (size_t)(level - 1) * P->L;
-        hipLaunchKernelGGL(rescale_intt_kernel, dim3(N >> 12, rows), dim3(NTT_THREADS), 0, stream, d_in, d_r, P->d_modf,
+        const bool wide_in = wide_tiles((u64)(N >> 12) * rows), wide_out = wide_tiles((u64)(N >> 12) * rows * (level - 1));
+        hipLaunchKernelGGL(wide_in ? rescale_intt_kernel<WIDE_RL> : rescale_intt_kernel<4>, dim3(N >> 12, rows),
+                           dim3(tile_threads(wide_in)), 0, stream, d_in, d_r, P->d_modf,
                            P->d_twf_inv, level, P->logN);
         CKKS_LAUNCH_CHECK("rescale_intt_kernel");
         const auto mid = P->logN == 12 ? rescale_mid_kernel<0> : P->logN == 13 ? rescale_mid_kernel<1>
@@ -1540,7 +1545,8 @@ static int rescale_rows(ckks_params *P, const u64 *d_in, u32 level, u32 rows, u6
         hipLaunchKernelGGL(mid, dim3(N / RS_TILE, rows), dim3(256), 0, stream, d_r, d_out, P->d_modf, P->d_mod,
                            P->d_twf_inv, P->d_twf_fwd, level);
         CKKS_LAUNCH_CHECK("rescale_mid_kernel");
-        hipLaunchKernelGGL(rescale_tile_kernel, dim3(N >> 12, level - 1, rows), dim3(NTT_THREADS), 0, stream, d_in, d_out,
+        hipLaunchKernelGGL(wide_out ? rescale_tile_kernel<WIDE_RL> : rescale_tile_kernel<4>, dim3(N >> 12, level - 1, rows),
+                           dim3(tile_threads(wide_out)), 0, stream, d_in, d_out,
                            P->d_modf, P->d_mod, P->d_twf_fwd, qlinv, level, P->logN);
         CKKS_LAUNCH_CHECK("rescale_tile_kernel");
         P->limb_ntts += (u64)rows * level;

@@ -112,8 +112,9 @@ constexpr int INT_ROWS = 0, FP_ROWS = 1, BOTH_ROWS = 2;
 // 383 us, column pass 273 -> 250.  Below that the next pass finds them there: 25 x 14 rows at 2^16 164 us, streamed 182.
 constexpr int STREAMED = 4;
 constexpr u32 BOTH_MAX = 2048;
+constexpr int WIDE = 8;                      // + WIDE: tiles by 1024 threads (pass B only)
 template <bool INV, u32 LOGR, int KIND_NT>
-__global__ __launch_bounds__(NTT_THREADS) void ntt_fast_kernel(u64 *__restrict__ data,
+__global__ __launch_bounds__((KIND_NT & WIDE) != 0 ? Tile<WIDE_RL>::THREADS : NTT_THREADS) void ntt_fast_kernel(u64 *__restrict__ data,
                                                                const ModConst *__restrict__ mods,
                                                                const ModFp *__restrict__ modf,
                                                                const u64 *__restrict__ tw,
@@ -122,7 +123,8 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fast_kernel(u64 *__restrict__
                                                                u32 n_limbs, u32 logN) {
     constexpr int KIND = KIND_NT & 3;
     constexpr bool NT = (KIND_NT & STREAMED) != 0;
-    __shared__ u64 lds[LOGR ? 1 : FAST_LDS_WORDS];
+    constexpr u32 RL = (KIND_NT & WIDE) != 0 ? WIDE_RL : 4;
+    __shared__ u64 lds[LOGR ? 1 : Tile<RL>::WORDS];
     const u32 row = KIND == BOTH_ROWS ? gridDim.y - 1 - blockIdx.y : blockIdx.y;   // special limbs come last: start with them
     const u32 limb = ids.id[row % n_limbs];
     if (limb == SKIP_ROW) return;
@@ -138,7 +140,7 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_fast_kernel(u64 *__restrict__
     };
     auto go = [&](const auto &f) {
         if constexpr (LOGR == 0) {
-            pass_b_body<INV>(f, logN, lds, load, store);
+            pass_b_body<INV, RL>(f, logN, lds, load, store);
         } else {
             constexpr u32 COLS = LOGR < 4 ? 16u >> LOGR : 1;     // columns of a thread
 #pragma unroll
@@ -165,11 +167,19 @@ static void launch_fast(const ckks_params *p, u64 *d_data, const LimbIds &ids, u
     }
     const u32 blocks = LOGR == 0 ? p->N >> 12 : LOGR < 4 ? 1u << LOGR : 16;
 #define FAST_LAUNCH(KIND)                                                                                            \
-    hipLaunchKernelGGL((ntt_fast_kernel<INV, LOGR, KIND>), dim3(blocks, rows), dim3(NTT_THREADS), 0, stream, d_data,   \
+    hipLaunchKernelGGL((ntt_fast_kernel<INV, LOGR, KIND>), dim3(blocks, rows), dim3(tile_threads((KIND) & WIDE)), 0, stream, d_data,   \
                        p->d_mod, scaled_dn ? p->d_modf_dn : p->d_modf, INV ? p->d_tws_inv : p->d_tws_fwd,            \
                        INV ? p->d_twf_inv : p->d_twf_fwd, scaled_dn ? p->d_ninvs_dn : p->d_ninvs, ids, n_limbs,      \
                        p->logN)
-    if (any_fp && any_int && (u64)blocks * rows <= BOTH_MAX) {
+    if (LOGR == 0 && wide_tiles((u64)blocks * rows)) {
+        constexpr int W = LOGR == 0 ? WIDE : 0;
+        if (any_fp && any_int) {
+            FAST_LAUNCH(BOTH_ROWS + W);
+        } else {
+            if (any_fp) FAST_LAUNCH(FP_ROWS + W);
+            if (any_int) FAST_LAUNCH(INT_ROWS + W);
+        }
+    } else if (any_fp && any_int && (u64)blocks * rows <= BOTH_MAX) {
         FAST_LAUNCH(BOTH_ROWS);
     } else if ((u64)rows * p->N * sizeof(u64) > STREAM_BYTES) {
         if (any_fp) FAST_LAUNCH(FP_ROWS + STREAMED);

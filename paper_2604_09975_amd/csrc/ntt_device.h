@@ -7,12 +7,52 @@ namespace ckks {
 
 constexpr u32 NTT_THREADS = 256;
 
-// LDS slot of tile element i: one padding word after every 16 elements.  The three access patterns of the tile pass
-// (residues 256 apart, 16 apart, and 16 consecutive ones per thread) then fall on distinct banks, and, unlike an
-// XOR fold, every slot a thread touches is its base slot plus a compile-time offset: no address registers, which is
-// what brings the pass from 130 to under 100 vector registers.  A tile takes 34 KiB; four fit a CU.
-__device__ __forceinline__ u32 lds_pad(u32 i) { return i + (i >> 4); }
-constexpr u32 FAST_LDS_WORDS = 4096 + 256;
+// A tile of 4096 residues and the workgroup that transforms it, 2^RL residues a thread: 256 threads with 16 residues each
+// (RL = 4), or 1024 with 4 (RL = WIDE_RL) in launches of few workgroups.
+// LDS slot of tile element i: one padding word after every 2^RL elements.  The access patterns of the tile pass
+// (residues 2^(12-RL) apart down to 2^RL consecutive ones per thread) then fall on distinct banks but for a few pairs, and,
+// unlike an XOR fold, every slot a thread touches is its base slot plus a compile-time offset: no address registers, which
+// is what brings the pass from 130 to under 100 vector registers.  A tile takes 34 KiB (RL = 2: 40); four fit a CU.
+template <u32 RL>
+struct Tile {
+    static constexpr u32 R = 1u << RL, THREADS = 4096u >> RL, WORDS = 4096 + (4096u >> RL), ROUNDS = 12 / RL;
+    // WAVE: outside the pass's first round (forward: after it, inverse: before it) a wavefront touches 64 R consecutive
+    // elements of its own only
+    static constexpr bool WAVE = RL < 4;
+    static __device__ __forceinline__ u32 slot(u32 i) { return i + (i >> RL); }
+    // the i-th single element and the i-th pair of elements of a thread at the pass's LDS end
+    static __device__ __forceinline__ u32 one(u32 tid, u32 i) {
+        return WAVE ? (tid & ~63u) * R + (tid & 63u) + 64 * i : tid + THREADS * i;
+    }
+    static __device__ __forceinline__ u32 pair(u32 tid, u32 i) {
+        return WAVE ? (tid & ~63u) * R + (tid & 63u) * 2 + 128 * i : 2 * (tid + THREADS * i);
+    }
+};
+
+// A launch of few workgroups lasts as long as one of them, and with 256 threads that is one wavefront per SIMD waiting for
+// its operands, then for each round's twiddles and exchange.  With 1024 threads four wavefronts share the wait, every load
+// of the operands is on its way at once, and the operands of a key switch's last pass arrive during its transform.  512
+// workgroups of 1024 threads are as many as the chip holds at a time.  us with 256 threads, with wide tiles up to 512 and up
+// to 1024 workgroups: ip_intt_kernel of 7 switches at 2^12 (14 workgroups) 19.3 -> 11.5; whole calls: toy projection at 2^12
+// 145 / 112 / 112, product and rescale at 2^15 (12 + 4 primes) 130 / 104 / 104, one rotation at 2^16, level 17 (544 and 928
+// workgroups in two of its kernels) 154 / 137 / 143, 24 switches and 12 rescales at 2^14 (960 in one) 165 / 146 / 155.  512
+// threads with 8 residues: 113, 105, 140, 151.
+constexpr u32 WIDE_RL = 2;
+inline bool wide_tiles(u64 workgroups) { return workgroups <= 512; }
+inline u32 tile_threads(bool wide) { return wide ? 1024 : 256; }
+
+// After the exchange through LDS of data that goes no further than SPAN threads.  Within a wavefront LDS instructions
+// execute in order, and only the compiler has to be kept from moving them.
+template <u32 SPAN>
+__device__ __forceinline__ void exchange_sync() {
+    if constexpr (SPAN > 64) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+}
 
 // Integer butterflies for primes that do not fit the fp64 scheme (the 60-bit special primes): lazy values and
 // twiddles with a precomputed quotient.  A twiddle is the pair (w, w') with w' = floor(w * 2^64 / q); for any 64-bit
@@ -38,8 +78,8 @@ struct FieldInt {
     }
     __device__ __forceinline__ u64 bits(T x) const { return x; }
     __device__ __forceinline__ T from_bits(u64 x) const { return x; }
-    __device__ __forceinline__ W twid(u32 idx) const {
-        const ulonglong2 t = tw[idx];
+    __device__ __forceinline__ W twid(u32 idx, u32 k) const {
+        const ulonglong2 t = (tw + idx)[k];
         return TwInt{t.x, t.y};
     }
     __device__ __forceinline__ void norm(T &) const {}
@@ -86,7 +126,7 @@ struct FieldFp {
     }
     __device__ __forceinline__ u64 bits(T x) const { return (u64)__double_as_longlong(x); }
     __device__ __forceinline__ T from_bits(u64 x) const { return __longlong_as_double((long long)x); }
-    __device__ __forceinline__ T twid(u32 idx) const { return tw[idx]; }
+    __device__ __forceinline__ W twid(u32 idx, u32 k) const { return (tw + idx)[k]; }   // entry idx + k; k constant: wide loads
     __device__ __forceinline__ T mul(T a, T w) const {
         const double h = a * w;
         const double l = fma(a, w, -h);
@@ -116,8 +156,8 @@ struct FieldFp {
 // fp64 bounds: a product is below 0.9 q (a factor below 4q) or 0.7 q (below q), so four forward stages take a
 // normalised value (q/2) to 4 q = 2^52; an inverse stage doubles a value and hands the difference, twice as large, to
 // the product: two of them between normalisations.
-template <u32 LOGR, class F>
-__device__ __forceinline__ void radix_fwd(const F &f, typename F::T (&v)[1u << LOGR], u32 s0, u32 nb) {
+template <u32 LOGR, class F, class Tw>
+__device__ __forceinline__ void radix_fwd_by(const F &f, typename F::T (&v)[1u << LOGR], Tw tw) {
     constexpr u32 R = 1u << LOGR;
 #pragma unroll
     for (u32 t = 0; t < LOGR; ++t) {
@@ -128,16 +168,20 @@ __device__ __forceinline__ void radix_fwd(const F &f, typename F::T (&v)[1u << L
         const u32 g = R >> (t + 1);
 #pragma unroll
         for (u32 k = 0; k < (1u << t); ++k) {
-            const typename F::W w = f.twid((1u << (s0 + t)) + (nb << t) + k);
+            const typename F::W w = tw(t, k);
 #pragma unroll
             for (u32 i = 0; i < g; ++i) f.fwd(v[k * 2 * g + i], v[k * 2 * g + i + g], w);
         }
     }
 }
+template <u32 LOGR, class F>
+__device__ __forceinline__ void radix_fwd(const F &f, typename F::T (&v)[1u << LOGR], u32 s0, u32 nb) {
+    radix_fwd_by<LOGR>(f, v, [&](u32 t, u32 k) { return f.twid((1u << (s0 + t)) + (nb << t), k); });
+}
 
 // last: the group's first stage (t = 0) ends the transform and folds in N^-1
-template <u32 LOGR, class F>
-__device__ __forceinline__ void radix_inv(const F &f, typename F::T (&v)[1u << LOGR], u32 s0, u32 nb, bool last) {
+template <u32 LOGR, class F, class Tw>
+__device__ __forceinline__ void radix_inv_by(const F &f, typename F::T (&v)[1u << LOGR], Tw tw, bool last) {
     constexpr u32 R = 1u << LOGR;
 #pragma unroll
     for (int t = (int)LOGR - 1; t >= 0; --t) {
@@ -152,102 +196,179 @@ __device__ __forceinline__ void radix_inv(const F &f, typename F::T (&v)[1u << L
         } else {
 #pragma unroll
             for (u32 k = 0; k < (1u << t); ++k) {
-                const typename F::W w = f.twid((1u << (s0 + t)) + (nb << t) + k);
+                const typename F::W w = tw((u32)t, k);
 #pragma unroll
                 for (u32 i = 0; i < g; ++i) f.inv(v[k * 2 * g + i], v[k * 2 * g + i + g], w);
             }
         }
     }
 }
-
-// pass B: the last 12 stages act inside aligned runs of 4096 consecutive residues, one workgroup per run, in three
-// radix-16 rounds with an LDS exchange between them:
-//   round 1 (stages logN-12 .. logN-9): thread t holds residues j*256 + t          (2 KiB runs in global memory)
-//   round 2 (stages logN-8  .. logN-5): thread (blk, c) holds blk*256 + c + 16*j
-//   round 3 (stages logN-4  .. logN-1): thread (blk, c) holds blk*256 + 16*c + j
-// For N = 2^12 this is the whole transform.  The passes come in halves so that callers can put their own code
-// between global memory and LDS.  LDS slot of residue e of the tile: lds[lds_pad(e)].
-//
-// forward: load(idx) gives the canonical residue at index idx of the polynomial (round-1 pattern: coalesced); on
-// return the tile's transformed, canonical residues are in LDS and the workgroup is synced.  RAW: the residues are
-// left in the field's own form instead (f.bits of a value brought back by f.norm: for the fp64 field a double with
-// |x| <= q/2), for a caller that goes on computing in that field and would only convert them back.
-template <bool RAW = false, class F, class Load>
-__device__ __forceinline__ void pass_b_fwd_to_lds(const F &f, u32 logN, u64 *lds, Load load) {
-    const u32 tid = threadIdx.x, blk = tid >> 4, c = tid & 15;
-    const u32 base = blockIdx.x << 12;
-    const u32 run = (base >> 8) + blk;              // which run of 256 in the polynomial
-    const u32 strided = blk * 256 + c, contig = blk * 256 + c * 16;
-    typename F::T v[16];
-#pragma unroll
-    for (u32 j = 0; j < 16; ++j) v[j] = f.in(load(base + j * 256 + tid));
-    radix_fwd<4>(f, v, logN - 12, blockIdx.x);
-#pragma unroll
-    for (u32 j = 0; j < 16; ++j) lds[lds_pad(j * 256 + tid)] = f.bits(v[j]);
-    __syncthreads();
-#pragma unroll
-    for (u32 j = 0; j < 16; ++j) v[j] = f.from_bits(lds[lds_pad(strided + j * 16)]);
-    radix_fwd<4>(f, v, logN - 8, run);
-#pragma unroll
-    for (u32 j = 0; j < 16; ++j) lds[lds_pad(strided + j * 16)] = f.bits(v[j]);   // a thread's own slots
-    __syncthreads();
-#pragma unroll
-    for (u32 j = 0; j < 16; ++j) v[j] = f.from_bits(lds[lds_pad(contig + j)]);
-    radix_fwd<4>(f, v, logN - 4, run * 16 + c);
-#pragma unroll
-    for (u32 j = 0; j < 16; ++j) {                                          // a thread's own slots
-        if (RAW) {
-            f.norm(v[j]);
-            lds[lds_pad(contig + j)] = f.bits(v[j]);
-        } else {
-            lds[lds_pad(contig + j)] = f.out(v[j]);
-        }
-    }
-    __syncthreads();
+template <u32 LOGR, class F>
+__device__ __forceinline__ void radix_inv(const F &f, typename F::T (&v)[1u << LOGR], u32 s0, u32 nb, bool last) {
+    radix_inv_by<LOGR>(f, v, [&](u32 t, u32 k) { return f.twid((1u << (s0 + t)) + (nb << t), k); }, last);
 }
 
-// inverse: expects the tile's canonical residues in LDS (workgroup synced); store(idx, value) receives the
-// canonical results in the round-1 pattern (coalesced).  whole: the tile is the whole polynomial (N = 2^12), so the
-// last round ends the transform and folds in N^-1.
-template <class F, class Store>
-__device__ __forceinline__ void pass_b_inv_from_lds(const F &f, u32 logN, u64 *lds, Store store) {
-    const u32 tid = threadIdx.x, blk = tid >> 4, c = tid & 15;
+// pass B: the last 12 stages act inside aligned runs of 4096 consecutive residues, one workgroup per run, in 12 / RL
+// rounds of RL stages with an LDS exchange between them.  In round r a thread holds 2^RL residues S = 4096 >> RL (r + 1)
+// apart, those of block tid / S from tid % S on:
+//   RL = 4: 256 apart (2 KiB runs in global memory), 16 apart, consecutive;  RL = 2: 1024, 256, 64, 16, 4 apart, consecutive.
+// The exchange behind round r stays among the S threads of a block: within a wavefront from S = 64 down.
+// For N = 2^12 this is the whole transform.  The passes come in halves so that callers can put their own code
+// between global memory and LDS.  LDS slot of residue e of the tile: lds[Tile<RL>::slot(e)].
+// RL < 4: each round's twiddles are loaded a round ahead, as there are few wavefronts to hide the wait; RL = 4 has none of
+// the registers that takes.
+template <u32 RL, u32 RD>
+struct Round {
+    static constexpr u32 S = 4096u >> (RL * (RD + 1));
+    static constexpr u32 BEHIND = RL < 4 ? S : (4096u >> RL);        // threads that the exchange behind the round spans
+    static constexpr u32 FRONT = RL < 4 ? S << RL : (4096u >> RL);   // and the one in front of it
+    static __device__ __forceinline__ u32 first() { return threadIdx.x / S * (S << RL) + threadIdx.x % S; }
+    static __device__ __forceinline__ u32 elem(u32 j) { return first() + j * S; }
+    // Tile<RL>::slot(elem(j)), written so that the j are constant offsets: S is 1 or a multiple of 2^RL
+    static __device__ __forceinline__ u32 slot(u32 j) { return Tile<RL>::slot(first()) + j * (S + (S >> RL)); }
+    static __device__ __forceinline__ u32 node() {
+        const u32 blk = S >= 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / S) : threadIdx.x / S;
+        return (blockIdx.x << (RL * RD)) + blk;
+    }
+    static __device__ __forceinline__ u32 stage(u32 logN) { return logN - 12 + RL * RD; }
+};
+
+template <u32 RL, class F>
+struct Twids {
+    typename F::W w[RL < 4 ? (1u << RL) - 1 : 1];
+};
+template <u32 RL, u32 RD, class F>
+__device__ __forceinline__ void load_twids(const F &f, u32 logN, Twids<RL, F> &tw) {
+    if constexpr (RL < 4 && RD < 12 / RL) {
+        const u32 s0 = Round<RL, RD>::stage(logN), nb = Round<RL, RD>::node();
+#pragma unroll
+        for (u32 t = 0; t < RL; ++t)
+#pragma unroll
+            for (u32 k = 0; k < (1u << t); ++k) tw.w[(1u << t) - 1 + k] = f.twid((1u << (s0 + t)) + (nb << t), k);
+    }
+}
+template <u32 RL, u32 RD, class F>
+__device__ __forceinline__ void round_fwd(const F &f, typename F::T (&v)[1u << RL], u32 logN, const Twids<RL, F> &tw) {
+    if constexpr (RL < 4)
+        radix_fwd_by<RL>(f, v, [&](u32 t, u32 k) { return tw.w[(1u << t) - 1 + k]; });
+    else
+        radix_fwd<RL>(f, v, Round<RL, RD>::stage(logN), Round<RL, RD>::node());
+}
+template <u32 RL, u32 RD, class F>
+__device__ __forceinline__ void round_inv(const F &f, typename F::T (&v)[1u << RL], u32 logN, const Twids<RL, F> &tw,
+                                          bool last) {
+    if constexpr (RL < 4)
+        radix_inv_by<RL>(f, v, [&](u32 t, u32 k) { return tw.w[(1u << t) - 1 + k]; }, last);
+    else
+        radix_inv<RL>(f, v, Round<RL, RD>::stage(logN), Round<RL, RD>::node(), last);
+}
+
+// forward rounds from RD on, LDS to LDS
+template <bool RAW, u32 RL, u32 RD, class F>
+__device__ __forceinline__ void fwd_rounds(const F &f, u32 logN, u64 *lds, const Twids<RL, F> &tw) {
+    typedef Tile<RL> TL;
+    typedef Round<RL, RD> RN;
+    Twids<RL, F> next;
+    load_twids<RL, RD + 1>(f, logN, next);
+    typename F::T v[TL::R];
+#pragma unroll
+    for (u32 j = 0; j < TL::R; ++j) v[j] = f.from_bits(lds[RN::slot(j)]);
+    round_fwd<RL, RD>(f, v, logN, tw);
+#pragma unroll
+    for (u32 j = 0; j < TL::R; ++j) {                              // a thread's own slots
+        if (RD + 1 < TL::ROUNDS) {
+            lds[RN::slot(j)] = f.bits(v[j]);
+        } else if (RAW) {
+            f.norm(v[j]);
+            lds[RN::slot(j)] = f.bits(v[j]);
+        } else {
+            lds[RN::slot(j)] = f.out(v[j]);
+        }
+    }
+    exchange_sync<RN::BEHIND>();
+    if constexpr (RD + 1 < TL::ROUNDS) fwd_rounds<RAW, RL, RD + 1>(f, logN, lds, next);
+}
+
+// forward: load(idx) gives the canonical residue at index idx of the polynomial (first round's pattern: coalesced); on
+// return the tile's transformed, canonical residues are in LDS, where a thread may read what Tile::one or Tile::pair give
+// it (RL = 4: the workgroup is synced).  RAW: the residues are
+// left in the field's own form instead (f.bits of a value brought back by f.norm: for the fp64 field a double with
+// |x| <= q/2), for a caller that goes on computing in that field and would only convert them back.
+template <bool RAW = false, u32 RL = 4, class F, class Load>
+__device__ __forceinline__ void pass_b_fwd_to_lds(const F &f, u32 logN, u64 *lds, Load load) {
+    typedef Tile<RL> TL;
+    typedef Round<RL, 0> RN;
     const u32 base = blockIdx.x << 12;
-    const u32 run = (base >> 8) + blk;
-    const u32 strided = blk * 256 + c, contig = blk * 256 + c * 16;
-    typename F::T v[16];
+    Twids<RL, F> tw, next;
+    load_twids<RL, 0>(f, logN, tw);
+    typename F::T v[TL::R];
 #pragma unroll
-    for (u32 j = 0; j < 16; ++j) v[j] = f.in(lds[lds_pad(contig + j)]);
-    radix_inv<4>(f, v, logN - 4, run * 16 + c, false);
+    for (u32 j = 0; j < TL::R; ++j) v[j] = f.in(load(base + RN::elem(j)));
+    load_twids<RL, 1>(f, logN, next);
+    round_fwd<RL, 0>(f, v, logN, tw);
 #pragma unroll
-    for (u32 j = 0; j < 16; ++j) lds[lds_pad(contig + j)] = f.bits(v[j]);   // a thread's own slots
-    __syncthreads();
+    for (u32 j = 0; j < TL::R; ++j) lds[RN::slot(j)] = f.bits(v[j]);
+    exchange_sync<RN::BEHIND>();
+    fwd_rounds<RAW, RL, 1>(f, logN, lds, next);
+}
+
+// inverse rounds from RD down to the second, LDS to LDS; the residues in front of the first of them are canonical
+template <u32 RL, u32 RD, class F>
+__device__ __forceinline__ void inv_rounds(const F &f, u32 logN, u64 *lds, const Twids<RL, F> &tw, Twids<RL, F> &tw0) {
+    typedef Tile<RL> TL;
+    typedef Round<RL, RD> RN;
+    Twids<RL, F> next;
+    load_twids<RL, RD - 1>(f, logN, next);
+    typename F::T v[TL::R];
 #pragma unroll
-    for (u32 j = 0; j < 16; ++j) v[j] = f.from_bits(lds[lds_pad(strided + j * 16)]);
-    radix_inv<4>(f, v, logN - 8, run, false);
+    for (u32 j = 0; j < TL::R; ++j) {
+        const u64 x = lds[RN::slot(j)];
+        v[j] = RD + 1 == TL::ROUNDS ? f.in(x) : f.from_bits(x);
+    }
+    round_inv<RL, RD>(f, v, logN, tw, false);
 #pragma unroll
-    for (u32 j = 0; j < 16; ++j) lds[lds_pad(strided + j * 16)] = f.bits(v[j]);   // a thread's own slots
-    __syncthreads();
+    for (u32 j = 0; j < TL::R; ++j) lds[RN::slot(j)] = f.bits(v[j]);   // a thread's own slots
+    exchange_sync<RN::FRONT>();
+    if constexpr (RD > 1)
+        inv_rounds<RL, RD - 1>(f, logN, lds, next, tw0);
+    else
+        tw0 = next;
+}
+
+// inverse: expects the tile's canonical residues in LDS, written in the pattern of Tile::one or Tile::pair (the exchange
+// itself is synced here);
+// store(idx, value) receives the canonical results in the first round's pattern (coalesced).  A tile that is the whole
+// polynomial (N = 2^12) ends the transform in the last round, which folds in N^-1.
+template <u32 RL = 4, class F, class Store>
+__device__ __forceinline__ void pass_b_inv_from_lds(const F &f, u32 logN, u64 *lds, Store store) {
+    typedef Tile<RL> TL;
+    typedef Round<RL, 0> RN;
+    const u32 base = blockIdx.x << 12;
+    Twids<RL, F> tw, tw0;
+    load_twids<RL, TL::ROUNDS - 1>(f, logN, tw);
+    exchange_sync<TL::WAVE ? 64 : TL::THREADS>();
+    inv_rounds<RL, TL::ROUNDS - 1>(f, logN, lds, tw, tw0);
+    typename F::T v[TL::R];
 #pragma unroll
-    for (u32 j = 0; j < 16; ++j) v[j] = f.from_bits(lds[lds_pad(j * 256 + tid)]);
-    radix_inv<4>(f, v, logN - 12, blockIdx.x, logN == 12);
+    for (u32 j = 0; j < TL::R; ++j) v[j] = f.from_bits(lds[RN::slot(j)]);
+    round_inv<RL, 0>(f, v, logN, tw0, logN == 12);
 #pragma unroll
-    for (u32 j = 0; j < 16; ++j) store(base + j * 256 + tid, f.out(v[j]));
+    for (u32 j = 0; j < TL::R; ++j) store(base + RN::elem(j), f.out(v[j]));
 }
 
 // Whole pass with coalesced stores (forward) / coalesced loads (inverse).
-template <bool INV, class F, class Load, class Store>
+template <bool INV, u32 RL = 4, class F, class Load, class Store>
 __device__ __forceinline__ void pass_b_body(const F &f, u32 logN, u64 *lds, Load load, Store store) {
+    typedef Tile<RL> TL;
     const u32 tid = threadIdx.x, base = blockIdx.x << 12;
     if (!INV) {
-        pass_b_fwd_to_lds(f, logN, lds, load);
+        pass_b_fwd_to_lds<false, RL>(f, logN, lds, load);
 #pragma unroll
-        for (u32 i = 0; i < 16; ++i) store(base + tid + 256 * i, lds[lds_pad(tid + 256 * i)]);
+        for (u32 i = 0; i < TL::R; ++i) store(base + TL::one(tid, i), lds[TL::slot(TL::one(tid, i))]);
     } else {
 #pragma unroll
-        for (u32 i = 0; i < 16; ++i) lds[lds_pad(tid + 256 * i)] = load(base + tid + 256 * i);
-        __syncthreads();
-        pass_b_inv_from_lds(f, logN, lds, store);
+        for (u32 i = 0; i < TL::R; ++i) lds[TL::slot(TL::one(tid, i))] = load(base + TL::one(tid, i));
+        pass_b_inv_from_lds<RL>(f, logN, lds, store);
     }
 }
 

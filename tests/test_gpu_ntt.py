@@ -46,6 +46,21 @@ def test_small_rings_bit_exact(logN, batch):
     assert (to_host(d2) == O.ntt_batch(x, ids, inverse=True)).all()
 
 
+@pytest.mark.parametrize("logN,ids,batch", [(12, [0], 512), (12, [0], 513), (12, [3], 512), (12, [3], 513),
+                                            (12, [4, 1], 256), (12, [4, 1], 257), (13, [2, 4], 128), (13, [2, 4], 129)])
+def test_either_side_of_the_wide_tiles(logN, ids, batch):
+    """Up to 512 workgroups take a tile with 1024 threads, more with 256: rows of primes below 2^50, above, and both."""
+    B = _B()
+    O = helpers.small_oracle(logN, L=3, K=2, dnum=3, qbits=50, pbits=60)
+    _, P = make_pair(O)
+    x = W.uniform_residues(W.rng(batch), [O.moduli[i] for i in ids], O.N, lead=(batch,))
+    x[-1] = np.array([O.moduli[i] - 1 for i in ids], dtype=np.uint64)[:, None]
+    for inverse in (False, True):
+        d = to_dev(x)
+        (B.ckks_intt if inverse else B.ckks_ntt)(P, d, ids, batch)
+        assert (to_host(d) == O.ntt_batch(x, ids, inverse=inverse)).all()
+
+
 def test_toy_ring_bit_exact():
     B = _B()
     O, P = make_pair(W.TOY_RING)
