@@ -624,6 +624,174 @@ __global__ __launch_bounds__(KS_THREADS) void merged_ip_kernel(MergedRot rots, c
     }
 }
 
+// The same sum straight from digits that still lack their forward tile pass (decompose with `half`): sigma_g moves whole
+// tiles (the top bits of an index fix its exponent modulo 2N / 4096), so a workgroup that owns output tile T of row t of one
+// ciphertext transforms, rotation by rotation and digit by digit, the one tile that sigma_g brings to T, in LDS, and takes
+// its products from there: the transformed digits, each used once, never reach memory.
+// Bound by the chain of a workgroup's loads, transform and gather (two workgroups of 512 threads per CU hide each other's)
+// and by the integer butterflies of the special limbs.  RL = 3: eight residues a thread, whose sums, keys and transform fit
+// the 128 registers that two workgroups leave (RL = 4 takes 200 and more; any spilling costs more than the fusion gives: 2.98
+// ms where this takes 2.0).  A digit's key loads are issued before the barrier in front of its products; the next digit
+// loaded there as well spills or gains nothing.  QKV projection, 63 rotations of 24 + 8 limbs: 1.43 ms of tile passes and
+// 1.04 of merged_ip_kernel before, 1.7 now (the call 17.05 -> 16.38 ms).
+template <u32 RL>
+__global__ __launch_bounds__(Tile<RL>::THREADS, 4) void merged_tile_kernel(MergedRot rots, const u64 *__restrict__ digits,
+                                                                        size_t dig_w, const u64 *__restrict__ c0_base,
+                                                                        size_t c0_stride_r, u64 *__restrict__ dst_base,
+                                                                        size_t dst_stride, u64 *__restrict__ u,
+                                                                        const ModConst *__restrict__ mods,
+                                                                        const ModFp *__restrict__ modf,
+                                                                        const u64 *__restrict__ tw_fwd,
+                                                                        const double *__restrict__ twf_fwd,
+                                                                        const u64 *__restrict__ ninv, u32 n, u32 level,
+                                                                        u32 K, u32 L, u32 beta, u32 alpha, u32 logN,
+                                                                        u32 accumulate, LimbIds rows) {
+    typedef Tile<RL> TL;
+    constexpr u32 PP = TL::R / 2;
+    __shared__ u64 lds[TL::WORDS];
+    const u32 N = 1u << logN, Wl = level + K, Wt = L + K, tid = threadIdx.x;
+    // units (row, tile) in chunks of eight, the ciphertexts of a unit eight workgroups apart: on one XCD at about the same
+    // time, where one of them fetches the key lines for all.  Special limbs, the longest rows, first.
+    const u32 tiles = N >> 12, xg = blockIdx.x >> 3, unit = xg / n * 8 + (blockIdx.x & 7), r = xg % n;
+    if (unit >= tiles * Wl) return;
+    const u32 t = rows.id[unit / tiles], tile = unit % tiles, base = tile << 12;
+    const u32 gl = t < level ? t : L + (t - level);
+    const u32 own = t < level ? t / alpha : ~0u;                 // the digit whose own limb t is: read from c1
+    const ModConst m = mods[gl];
+    const ModFp mf = modf[gl];
+    u64 *u0 = u + (((size_t)r * 2) * Wl + t) * N + base, *u1 = u0 + (size_t)Wl * N;
+    auto tile_of = [&](u32 i) { return galois_index(base, (u32)rots.galois_elt[i], logN) >> 12; };
+    auto go = [&](const auto &f, auto zero, auto mac, auto in, auto norm, auto out) {
+        decltype(zero) a0[TL::R], a1[TL::R];
+#pragma unroll
+        for (u32 e = 0; e < TL::R; ++e) a0[e] = a1[e] = zero;
+        u64 raw[TL::R];                                          // the next digit to transform, on its way
+        auto fetch = [&](u32 i, u32 j) {
+            const u64 *row = digits + ((size_t)i * n + r) * dig_w + ((size_t)j * Wl + t) * N + ((size_t)tile_of(i) << 12);
+#pragma unroll
+            for (u32 e = 0; e < TL::R; ++e) raw[e] = __builtin_nontemporal_load(row + Round<RL, 0>::elem(e));
+        };
+        for (u32 i = 0; i < rots.n_rot; ++i) {
+            for (u32 j = 0; j < beta; ++j) {
+                // opaque: twiddles and gather addresses kept over the digits would take the registers of another workgroup
+                u32 g = (u32)rots.galois_elt[i], src_tile = tile_of(i);
+                asm volatile("" : "+s"(src_tile), "+s"(g));
+                const u64 *key = rots.key[i] + ((size_t)j * 2 * Wt + gl) * N + base;
+                auto products = [&](u32 e, auto x0, auto x1, pair_t k0, pair_t k1) {
+                    a0[2 * e] = mac(a0[2 * e], x0, k0[0]);
+                    a1[2 * e] = mac(a1[2 * e], x0, k1[0]);
+                    a0[2 * e + 1] = mac(a0[2 * e + 1], x1, k0[1]);
+                    a1[2 * e + 1] = mac(a1[2 * e + 1], x1, k1[1]);
+                };
+                auto load0 = [&](u32 e) { return *reinterpret_cast<const pair_t *>(key + TL::pair(tid, e)); };
+                auto load1 = [&](u32 e) { return *reinterpret_cast<const pair_t *>(key + (size_t)Wt * N + TL::pair(tid, e)); };
+                if (j != own) {
+                    fetch(i, j);
+                    pass_b_fwd_from_regs<true, RL>(f, logN, lds, raw, src_tile);
+                    pair_t k0[PP], k1[PP];
+#pragma unroll
+                    for (u32 e = 0; e < PP; ++e) {
+                        k0[e] = load0(e);
+                        k1[e] = load1(e);
+                    }
+                    __syncthreads();
+#pragma unroll
+                    for (u32 e = 0; e < PP; ++e) {
+                        const u32 l = galois_index(base + TL::pair(tid, e), g, logN) & 4095;
+                        products(e, f.from_bits(lds[TL::slot(l)]), f.from_bits(lds[TL::slot(l ^ 1)]), k0[e], k1[e]);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    __syncthreads();
+                } else {
+                    // the digit's own limb, transformed as it is; two pairs at a time, for the registers
+                    const u64 *row = c0_base + (size_t)r * c0_stride_r + rots.c0_off[i] + ((size_t)level + t) * N;
+#pragma unroll
+                    for (u32 e0 = 0; e0 < PP; e0 += 2) {
+                        pair_t k0[2], k1[2], d[2];
+                        u32 kp[2];
+#pragma unroll
+                        for (u32 e = 0; e < 2; ++e) {
+                            kp[e] = galois_index(base + TL::pair(tid, e0 + e), g, logN);
+                            d[e] = load_two<true>(row, kp[e]);
+                            k0[e] = load0(e0 + e);
+                            k1[e] = load1(e0 + e);
+                        }
+#pragma unroll
+                        for (u32 e = 0; e < 2; ++e) {
+                            const pair_t v = turned<true>(d[e], kp[e]);
+                            products(e0 + e, in(v[0]), in(v[1]), k0[e], k1[e]);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+                if ((j & 3) == 3 || j + 1 == beta) {                // fp64: q/2 and four products below 0.9 q, under 2^53
+#pragma unroll
+                    for (u32 e = 0; e < TL::R; ++e) {
+                        norm(a0[e]);
+                        norm(a1[e]);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (u32 e = 0; e < PP; ++e) {
+            pair_t v0{out(a0[2 * e]), out(a0[2 * e + 1])}, v1{out(a1[2 * e]), out(a1[2 * e + 1])};
+            pair_t *p0 = reinterpret_cast<pair_t *>(u0 + TL::pair(tid, e)), *p1 = reinterpret_cast<pair_t *>(u1 + TL::pair(tid, e));
+            if (accumulate) {
+                const pair_t o0 = *p0, o1 = *p1;
+#pragma unroll
+                for (u32 z = 0; z < 2; ++z) {
+                    v0[z] = add_mod(v0[z], o0[z], m.q);
+                    v1[z] = add_mod(v1[z], o1[z], m.q);
+                }
+            }
+            *p0 = v0;
+            *p1 = v1;
+        }
+    };
+    if (mf.ok && t < level) {
+        const FieldFp f = make_field_fp(mf, twf_fwd, gl, logN);
+        go(f, 0.0, [&](double a, double x, u64 k) { return a + f.mul(x, __longlong_as_double((long long)k)); },
+           [&](u64 x) { return canonical_double(x); }, [&](double &a) { f.norm(a); }, [&](double a) { return f.out(a); });
+    } else if (mf.ok) {                                          // a special prime below 2^50
+        const FieldFp f = make_field_fp(mf, twf_fwd, gl, logN);
+        go(f, (u64)0, [&](u64 a, double x, u64 k) { return add_mod(a, mont_mul(f.out(x), k, m), m.q); },
+           [&](u64 x) { return canonical_double(x); }, [&](u64 &) {}, [&](u64 a) { return a; });
+    } else {
+        const FieldInt f = make_field_int(mods, tw_fwd, ninv, gl, logN);
+        go(f, (u64)0, [&](u64 a, u64 x, u64 k) { return add_mod(a, mont_mul(f.out(x), k, m), m.q); }, [&](u64 x) { return x; },
+           [&](u64 &) {}, [&](u64 a) { return a; });
+    }
+    if (t < level) {
+        u64 cs[TL::R];
+#pragma unroll
+        for (u32 e = 0; e < TL::R; ++e) cs[e] = 0;
+        for (u32 i = 0; i < rots.n_rot; ++i) {
+            const u64 *row = c0_base + (size_t)r * c0_stride_r + rots.c0_off[i] + (size_t)t * N;
+            pair_t d[PP];
+            u32 kp[PP];
+#pragma unroll
+            for (u32 e = 0; e < PP; ++e) {
+                kp[e] = galois_index(base + TL::pair(tid, e), (u32)rots.galois_elt[i], logN);
+                d[e] = load_two<true>(row, kp[e]);
+            }
+#pragma unroll
+            for (u32 e = 0; e < PP; ++e) {
+                const pair_t v = turned<true>(d[e], kp[e]);
+#pragma unroll
+                for (u32 z = 0; z < 2; ++z) cs[2 * e + z] = add_mod(cs[2 * e + z], v[z], m.q);
+            }
+        }
+        u64 *dst = dst_base + (size_t)r * dst_stride + (size_t)t * N + base;
+#pragma unroll
+        for (u32 e = 0; e < PP; ++e) {
+            pair_t *p = reinterpret_cast<pair_t *>(dst + TL::pair(tid, e));
+            const pair_t o = *p;
+            *p = pair_t{add_mod(o[0], cs[2 * e], m.q), add_mod(o[1], cs[2 * e + 1], m.q)};
+        }
+    }
+}
+
 // y holds, per (item, component), the K special-limb rows y_k = INTT(u_{p_k}) * (P/p_k)^-1 in the coefficient
 // domain (the scaling comes out of the inverse transform); row (pc, k) starts at y + (pc*ystride + yoff + k)*N.
 // w_i = sum_k y_k * (P/p_k mod q_i) mod q_i for a chunk of target limbs i.
@@ -1226,7 +1394,7 @@ static int transform_digits(ckks_params *p, u32 level, u32 n, u64 *d_digits, hip
 // c1[r] [level][N] NTT domain (n <= ROT_BATCH device pointers) -> d_digits [n][beta][level+K][N] NTT domain;
 // d_tmp [n][level][N] scratch.
 int decompose(ckks_params *p, const u64 *const *c1, u32 n, u32 level, u64 *d_digits, u64 *d_tmp,
-              hipStream_t stream) {
+              hipStream_t stream, bool half) {
     if (n == 0) return CKKS_OK;
     const u32 N = p->N, K = p->K, L = p->L, Wl = level + K, alpha = p->alpha;
     const LevelTables *lt = nullptr;
@@ -1260,7 +1428,7 @@ int decompose(ckks_params *p, const u64 *const *c1, u32 n, u32 level, u64 *d_dig
                                p->d_ninvs, lt->d_up_ft, lt->d_up_mats, level, K, L, alpha, beta, tsplit);
             CKKS_LAUNCH_CHECK("modup_mid_kernel");
             p->limb_ntts += (u64)n * beta * Wl - (u64)n * level;
-            return transform_digits(p, level, n, d_digits, stream, 2);
+            return half ? CKKS_OK : transform_digits(p, level, n, d_digits, stream, 2);
         }
         rc = launch_ntt(p, d_tmp, ids, level, n * level, true, stream, 2);
     } else {
@@ -1291,7 +1459,7 @@ int decompose(ckks_params *p, const u64 *const *c1, u32 n, u32 level, u64 *d_dig
     }
 #undef MODUP_LAUNCH
     CKKS_LAUNCH_CHECK("modup_kernel");
-    return transform_digits(p, level, n, d_digits, stream, 3);
+    return transform_digits(p, level, n, d_digits, stream, half ? 1 : 3);
 }
 
 static u32 build_pack(const SwitchItem *items, u32 n, ItemPack &pack) {
@@ -1311,11 +1479,19 @@ static u32 build_pack(const SwitchItem *items, u32 n, ItemPack &pack) {
     return n_groups;
 }
 
+// From 320 workgroups on: each is a chain of all rotations and digits, so fewer of them leave the chip idle that long.
+// Projections, separate tile passes / merged_tile_kernel, us: 128 workgroups (2^15, 1 block) 548 / 627, 256 (2^15, 2 blocks)
+// 694 / 729, 256 (2^13, 32 blocks) 571 / 537, 320 (2^16, level 12) 2259 / 2244, 384 (2^15) 856 / 841, 512 (2^14) 926 / 697,
+// 1536 (2^15) 2262 / 2034, 2048 (2^16) 5125 / 4753.
+bool merged_from_half(const ckks_params *p, u32 level, u32 n) {
+    return fast_ring(p) && (u64)(p->N >> 12) * (level + p->K) * n >= 320;
+}
+
 // Merged giant step, part 1: d_u[r] (+)= the key inner products of rots.n_rot rotations of ciphertext r over all
 // level+K limbs (NTT domain), dst_r.c0 += the rotated c0 parts.  d_u [n][2][level+K][N].
 int switch_accumulate_merged(ckks_params *p, u32 level, const MergedRot &rots, u32 n, const u64 *d_digits,
                              const u64 *c0_base, size_t c0_stride_r, u64 *dst_base, size_t dst_stride, u64 *d_u,
-                             bool accumulate, hipStream_t stream) {
+                             bool accumulate, bool half, hipStream_t stream) {
     if (n == 0 || rots.n_rot == 0) return CKKS_OK;
     if (n > ROT_BATCH || rots.n_rot > MERGE_GROUP) {
         set_error("switch_accumulate_merged: %u ciphertexts x %u rotations exceed one launch", n, rots.n_rot);
@@ -1323,6 +1499,20 @@ int switch_accumulate_merged(ckks_params *p, u32 level, const MergedRot &rots, u
     }
     const u32 N = p->N, K = p->K, L = p->L, Wl = level + K;
     const u32 beta = (level + p->alpha - 1) / p->alpha;
+    if (half) {
+        LimbIds rows;                                            // the longest rows, those of larger primes, first
+        u32 n_rows = 0;
+        for (u32 pass = 0; pass < 2; ++pass)
+            for (u32 t = Wl; t-- > 0;)
+                if ((p->mod[t < level ? t : L + (t - level)] >> 50 == 0) == (pass == 1)) rows.id[n_rows++] = (uint8_t)t;
+        const u32 units = ((N >> 12) * Wl + 7) / 8 * 8;
+        hipLaunchKernelGGL(merged_tile_kernel<3>, dim3(units * n), dim3(Tile<3>::THREADS), 0, stream, rots, d_digits,
+                           digits_words(p, level), c0_base, c0_stride_r, dst_base, dst_stride, d_u, p->d_mod, p->d_modf,
+                           p->d_tws_fwd, p->d_twf_fwd, p->d_ninvs, n, level, K, L, beta, p->alpha, p->logN,
+                           accumulate ? 1u : 0u, rows);
+        CKKS_LAUNCH_CHECK("merged_tile_kernel");
+        return CKKS_OK;
+    }
     const u32 groups = (n + MR - 1) / MR;
     LimbIds fp_rows, int_rows;
     u32 n_fp = 0, n_int = 0;

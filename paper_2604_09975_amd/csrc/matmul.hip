@@ -1385,6 +1385,7 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
         }
         for (u32 b0 = 0; !ps.empty() && b0 < B; b0 += batch) {
             const u32 nb = std::min(batch, B - b0);
+            const bool half = merged_from_half(P, level, nb);
             u64 *u_b = d_u + (size_t)b0 * 2 * (level + P->K) * N;
             for (size_t i0 = 0; i0 < ps.size(); i0 += mg_rots) {
                 MergedRot rots;
@@ -1400,7 +1401,7 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
                         const u32 i = (c0 + c) / nb, r = (c0 + c) % nb;
                         c1s[c] = d_acc + ((size_t)(b0 + r) * N2 + ps[i0 + i]) * ctw + (size_t)level * N;
                     }
-                    rc = decompose(P, c1s, cn, level, d_mdig + (size_t)c0 * dig_w, d_work, stream);
+                    rc = decompose(P, c1s, cn, level, d_mdig + (size_t)c0 * dig_w, d_work, stream, half);
                     if (rc) return rc;
                 }
                 for (u32 i = 0; i < rots.n_rot; ++i) {
@@ -1411,7 +1412,7 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
                 }
                 rc = switch_accumulate_merged(P, level, rots, nb, d_mdig, d_acc + (size_t)b0 * N2 * ctw,
                                               (size_t)N2 * ctw, y_base + (size_t)b0 * y_stride, y_stride, u_b, i0 > 0,
-                                              stream);
+                                              half, stream);
                 if (rc) return rc;
             }
             u64 *dsts[ROT_BATCH];

@@ -215,8 +215,8 @@ __device__ __forceinline__ void radix_inv(const F &f, typename F::T (&v)[1u << L
 // The exchange behind round r stays among the S threads of a block: within a wavefront from S = 64 down.
 // For N = 2^12 this is the whole transform.  The passes come in halves so that callers can put their own code
 // between global memory and LDS.  LDS slot of residue e of the tile: lds[Tile<RL>::slot(e)].
-// RL < 4: each round's twiddles are loaded a round ahead, as there are few wavefronts to hide the wait; RL = 4 has none of
-// the registers that takes.
+// RL = WIDE_RL: each round's twiddles are loaded a round ahead, as there are few wavefronts to hide the wait; larger RL have
+// none of the registers that takes.
 template <u32 RL, u32 RD>
 struct Round {
     static constexpr u32 S = 4096u >> (RL * (RD + 1));
@@ -226,21 +226,21 @@ struct Round {
     static __device__ __forceinline__ u32 elem(u32 j) { return first() + j * S; }
     // Tile<RL>::slot(elem(j)), written so that the j are constant offsets: S is 1 or a multiple of 2^RL
     static __device__ __forceinline__ u32 slot(u32 j) { return Tile<RL>::slot(first()) + j * (S + (S >> RL)); }
-    static __device__ __forceinline__ u32 node() {
+    static __device__ __forceinline__ u32 node(u32 tile) {
         const u32 blk = S >= 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / S) : threadIdx.x / S;
-        return (blockIdx.x << (RL * RD)) + blk;
+        return (tile << (RL * RD)) + blk;
     }
     static __device__ __forceinline__ u32 stage(u32 logN) { return logN - 12 + RL * RD; }
 };
 
 template <u32 RL, class F>
 struct Twids {
-    typename F::W w[RL < 4 ? (1u << RL) - 1 : 1];
+    typename F::W w[RL == WIDE_RL ? (1u << RL) - 1 : 1];
 };
 template <u32 RL, u32 RD, class F>
-__device__ __forceinline__ void load_twids(const F &f, u32 logN, Twids<RL, F> &tw) {
-    if constexpr (RL < 4 && RD < 12 / RL) {
-        const u32 s0 = Round<RL, RD>::stage(logN), nb = Round<RL, RD>::node();
+__device__ __forceinline__ void load_twids(const F &f, u32 logN, u32 tile, Twids<RL, F> &tw) {
+    if constexpr (RL == WIDE_RL && RD < 12 / RL) {
+        const u32 s0 = Round<RL, RD>::stage(logN), nb = Round<RL, RD>::node(tile);
 #pragma unroll
         for (u32 t = 0; t < RL; ++t)
 #pragma unroll
@@ -248,32 +248,33 @@ __device__ __forceinline__ void load_twids(const F &f, u32 logN, Twids<RL, F> &t
     }
 }
 template <u32 RL, u32 RD, class F>
-__device__ __forceinline__ void round_fwd(const F &f, typename F::T (&v)[1u << RL], u32 logN, const Twids<RL, F> &tw) {
-    if constexpr (RL < 4)
+__device__ __forceinline__ void round_fwd(const F &f, typename F::T (&v)[1u << RL], u32 logN, u32 tile,
+                                          const Twids<RL, F> &tw) {
+    if constexpr (RL == WIDE_RL)
         radix_fwd_by<RL>(f, v, [&](u32 t, u32 k) { return tw.w[(1u << t) - 1 + k]; });
     else
-        radix_fwd<RL>(f, v, Round<RL, RD>::stage(logN), Round<RL, RD>::node());
+        radix_fwd<RL>(f, v, Round<RL, RD>::stage(logN), Round<RL, RD>::node(tile));
 }
 template <u32 RL, u32 RD, class F>
-__device__ __forceinline__ void round_inv(const F &f, typename F::T (&v)[1u << RL], u32 logN, const Twids<RL, F> &tw,
-                                          bool last) {
-    if constexpr (RL < 4)
+__device__ __forceinline__ void round_inv(const F &f, typename F::T (&v)[1u << RL], u32 logN, u32 tile,
+                                          const Twids<RL, F> &tw, bool last) {
+    if constexpr (RL == WIDE_RL)
         radix_inv_by<RL>(f, v, [&](u32 t, u32 k) { return tw.w[(1u << t) - 1 + k]; }, last);
     else
-        radix_inv<RL>(f, v, Round<RL, RD>::stage(logN), Round<RL, RD>::node(), last);
+        radix_inv<RL>(f, v, Round<RL, RD>::stage(logN), Round<RL, RD>::node(tile), last);
 }
 
 // forward rounds from RD on, LDS to LDS
 template <bool RAW, u32 RL, u32 RD, class F>
-__device__ __forceinline__ void fwd_rounds(const F &f, u32 logN, u64 *lds, const Twids<RL, F> &tw) {
+__device__ __forceinline__ void fwd_rounds(const F &f, u32 logN, u32 tile, u64 *lds, const Twids<RL, F> &tw) {
     typedef Tile<RL> TL;
     typedef Round<RL, RD> RN;
     Twids<RL, F> next;
-    load_twids<RL, RD + 1>(f, logN, next);
+    load_twids<RL, RD + 1>(f, logN, tile, next);
     typename F::T v[TL::R];
 #pragma unroll
     for (u32 j = 0; j < TL::R; ++j) v[j] = f.from_bits(lds[RN::slot(j)]);
-    round_fwd<RL, RD>(f, v, logN, tw);
+    round_fwd<RL, RD>(f, v, logN, tile, tw);
 #pragma unroll
     for (u32 j = 0; j < TL::R; ++j) {                              // a thread's own slots
         if (RD + 1 < TL::ROUNDS) {
@@ -286,7 +287,7 @@ __device__ __forceinline__ void fwd_rounds(const F &f, u32 logN, u64 *lds, const
         }
     }
     exchange_sync<RN::BEHIND>();
-    if constexpr (RD + 1 < TL::ROUNDS) fwd_rounds<RAW, RL, RD + 1>(f, logN, lds, next);
+    if constexpr (RD + 1 < TL::ROUNDS) fwd_rounds<RAW, RL, RD + 1>(f, logN, tile, lds, next);
 }
 
 // forward: load(idx) gives the canonical residue at index idx of the polynomial (first round's pattern: coalesced); on
@@ -294,22 +295,28 @@ __device__ __forceinline__ void fwd_rounds(const F &f, u32 logN, u64 *lds, const
 // it (RL = 4: the workgroup is synced).  RAW: the residues are
 // left in the field's own form instead (f.bits of a value brought back by f.norm: for the fp64 field a double with
 // |x| <= q/2), for a caller that goes on computing in that field and would only convert them back.
-template <bool RAW = false, u32 RL = 4, class F, class Load>
-__device__ __forceinline__ void pass_b_fwd_to_lds(const F &f, u32 logN, u64 *lds, Load load) {
+template <bool RAW = false, u32 RL = 4, class F>
+__device__ __forceinline__ void pass_b_fwd_from_regs(const F &f, u32 logN, u64 *lds, const u64 (&raw)[1u << RL], u32 tile) {
     typedef Tile<RL> TL;
     typedef Round<RL, 0> RN;
-    const u32 base = blockIdx.x << 12;
     Twids<RL, F> tw, next;
-    load_twids<RL, 0>(f, logN, tw);
+    load_twids<RL, 0>(f, logN, tile, tw);
     typename F::T v[TL::R];
 #pragma unroll
-    for (u32 j = 0; j < TL::R; ++j) v[j] = f.in(load(base + RN::elem(j)));
-    load_twids<RL, 1>(f, logN, next);
-    round_fwd<RL, 0>(f, v, logN, tw);
+    for (u32 j = 0; j < TL::R; ++j) v[j] = f.in(raw[j]);
+    load_twids<RL, 1>(f, logN, tile, next);
+    round_fwd<RL, 0>(f, v, logN, tile, tw);
 #pragma unroll
     for (u32 j = 0; j < TL::R; ++j) lds[RN::slot(j)] = f.bits(v[j]);
     exchange_sync<RN::BEHIND>();
-    fwd_rounds<RAW, RL, 1>(f, logN, lds, next);
+    fwd_rounds<RAW, RL, 1>(f, logN, tile, lds, next);
+}
+template <bool RAW = false, u32 RL = 4, class F, class Load>
+__device__ __forceinline__ void pass_b_fwd_to_lds(const F &f, u32 logN, u64 *lds, Load load) {
+    u64 raw[1u << RL];
+#pragma unroll
+    for (u32 j = 0; j < (1u << RL); ++j) raw[j] = load((blockIdx.x << 12) + Round<RL, 0>::elem(j));
+    pass_b_fwd_from_regs<RAW, RL>(f, logN, lds, raw, blockIdx.x);
 }
 
 // inverse rounds from RD down to the second, LDS to LDS; the residues in front of the first of them are canonical
@@ -318,14 +325,14 @@ __device__ __forceinline__ void inv_rounds(const F &f, u32 logN, u64 *lds, const
     typedef Tile<RL> TL;
     typedef Round<RL, RD> RN;
     Twids<RL, F> next;
-    load_twids<RL, RD - 1>(f, logN, next);
+    load_twids<RL, RD - 1>(f, logN, blockIdx.x, next);
     typename F::T v[TL::R];
 #pragma unroll
     for (u32 j = 0; j < TL::R; ++j) {
         const u64 x = lds[RN::slot(j)];
         v[j] = RD + 1 == TL::ROUNDS ? f.in(x) : f.from_bits(x);
     }
-    round_inv<RL, RD>(f, v, logN, tw, false);
+    round_inv<RL, RD>(f, v, logN, blockIdx.x, tw, false);
 #pragma unroll
     for (u32 j = 0; j < TL::R; ++j) lds[RN::slot(j)] = f.bits(v[j]);   // a thread's own slots
     exchange_sync<RN::FRONT>();
@@ -345,13 +352,13 @@ __device__ __forceinline__ void pass_b_inv_from_lds(const F &f, u32 logN, u64 *l
     typedef Round<RL, 0> RN;
     const u32 base = blockIdx.x << 12;
     Twids<RL, F> tw, tw0;
-    load_twids<RL, TL::ROUNDS - 1>(f, logN, tw);
+    load_twids<RL, TL::ROUNDS - 1>(f, logN, blockIdx.x, tw);
     exchange_sync<TL::WAVE ? 64 : TL::THREADS>();
     inv_rounds<RL, TL::ROUNDS - 1>(f, logN, lds, tw, tw0);
     typename F::T v[TL::R];
 #pragma unroll
     for (u32 j = 0; j < TL::R; ++j) v[j] = f.from_bits(lds[RN::slot(j)]);
-    round_inv<RL, 0>(f, v, logN, tw0, logN == 12);
+    round_inv<RL, 0>(f, v, logN, blockIdx.x, tw0, logN == 12);
 #pragma unroll
     for (u32 j = 0; j < TL::R; ++j) store(base + RN::elem(j), f.out(v[j]));
 }

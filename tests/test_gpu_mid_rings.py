@@ -40,6 +40,22 @@ def test_projection_with_fused_rescale(logN, m, C, N1):
     assert np.abs(Y - ref).max() <= 1e-3
 
 
+@pytest.mark.parametrize("logN,L,K,dnum,level,qbits,pbits,blocks,N1",
+                         [(12, 6, 6, 3, 6, 50, 60, 27, 1), (12, 6, 6, 3, 5, 50, 60, 27, 1),     # 324 and 297 workgroups
+                          (12, 8, 4, 2, 7, 45, 49, 30, 2), (12, 5, 6, 1, 5, 50, 60, 32, 4),     # special primes below 2^50; one digit
+                          (13, 5, 2, 5, 5, 50, 60, 24, 2), (13, 4, 2, 2, 3, 52, 60, 33, 2)])    # five digits; integer rows; two batches
+def test_merged_giant_step_on_either_side_of_the_fused_tile_pass(logN, L, K, dnum, level, qbits, pbits, blocks, N1):
+    """From 320 workgroups on the giant step's digits are transformed where their products are taken."""
+    O = helpers.small_oracle(logN, L=L, K=K, dnum=dnum, qbits=qbits, pbits=pbits)
+    _, P = make_pair(O)
+    r = W.rng(logN + blocks)
+    m, C = O.n // 8, 8
+    Wm = r.uniform(-0.5, 0.5, (C, blocks * C))
+    Y, ref, _, _ = run_case(O, P, r.uniform(-1, 1, (m, C)), Wm, None, m, C, N1, 40, level, 50 + logN, hw=16, merged=True,
+                            oracle_blocks=[0, blocks // 2, blocks - 1])
+    assert np.abs(Y - ref).max() <= 1e-3
+
+
 def test_rotation_of_a_ciphertext_that_is_not_16_byte_aligned():
     """The switches gather pairs of residues from the caller's ciphertext; its address need only be that of a word."""
     import torch
