@@ -66,8 +66,8 @@ struct LevelTables {
     ModFp *d_modf_up = nullptr;   // [level]: the limb's ModFp with (Q_D/q_i)^-1 folded into the inverse transform's N^-1
                                   // (N = 2^12: alone, the tile pass has applied N^-1)
     // AM = alpha rounded up to a power of two, zero padding behind the digit's limbs
-    double *d_up_mats = nullptr;  // [beta][K][AM][2][3]: (Q_D/q_i) 2^(25b) 2^64 mod p_k cut into three 20-bit parts
-    double *d_up_ft = nullptr;    // [beta][level+K][AM]: (Q_D/q_i) mod q_t, balanced, for the ciphertext-prime targets t
+    u32 *d_up_mats = nullptr;     // [beta][K][AM][2][2]: (Q_D/q_i) 2^(25b) 2^64 mod p_k cut into two 30-bit parts
+    u32 *d_up_ft = nullptr;       // [beta][level+K][AM][2][2]: (Q_D/q_i) 2^(25b) mod q_t in two 25-bit halves, ciphertext-prime targets t
 };
 
 }  // namespace ckks
@@ -99,6 +99,7 @@ struct ckks_params {
     // (P/p_k) P^-1 = p_k^-1 mod q_i: the ModDown conversion with the P^-1 that ends it
     ckks::u64 *d_dn_mat = nullptr;     // [K][L]
     double *d_dn_matf = nullptr;       // [L][K padded][3][2]: the same times 2^(20a) as two 25-bit halves (doubles)
+    ckks::u32 *d_dn_mats = nullptr;    // [L][K padded][2][2]: the same times 2^(30a) as two 25-bit halves (moddown_mid_kernel)
     bool dn_fp = false;                // every special prime below 2^60: the fp64 ModDown conversion applies
     ckks::u64 *d_pinv = nullptr;       // [L]: P^-1 mod q_i
     ckks::u64 *d_qlinv = nullptr;      // [L][L]: q_l^-1 mod q_i (rescale), row l

@@ -211,16 +211,51 @@ __global__ __launch_bounds__(KS_THREADS) void modup_kernel(const u64 *__restrict
     }
 }
 
+// The base conversions of the two fused kernels below sum products of 32 x 32-bit multiply-adds, which run at the rate of fp64
+// ones here (31e12 per second, both) and are exact in 64 bits instead of 53: a source limb costs a target 4 of them, where exact
+// sums in doubles take 6 (60-bit sources, or targets of 60 bits; two-double sums 4), three times the factor bytes and twice
+// the registers, so that a thread's two coefficients now share each factor.  us before and after: moddown_mid_kernel of a bank
+// of 27 switches at 2^16 406 and 350, with the rescale (9 blocks) 150 and 118, one switch 25.2 and 21.3; modup_mid_kernel of 32
+// ciphertexts of 24 limbs 467 and 421, one of 17 37.8 and 30.1, three of 2^15 (11 limbs) 57.7 and 50.1.
+//
+// The two BITS-bit pieces of the source limbs' values of a coefficient:
+template <u32 KM, u32 BITS>
+__device__ __forceinline__ void mid_pieces(const u64 (&yraw)[KM], u32 (&yp)[KM][2]) {
+#pragma unroll
+    for (u32 k = 0; k < KM; ++k) {
+        yp[k][0] = (u32)yraw[k] & ((1u << BITS) - 1);
+        yp[k][1] = (u32)(yraw[k] >> BITS);
+    }
+}
+
+// sum_k y_k F_k mod q (below 2^50) as a double, at most q + 2^32: the pieces (at most 30 bits) times the factors F_k 2^(BITS a)
+// mod q in 25-bit halves, 16 products of 55 bits.  The sums' words then become doubles: hi 2^25 + lo = (hh 2^25 + lh) 2^32 +
+// hl 2^25 + ll, the first two terms exact (52 and 32 significant bits) and reduced one by one.
+template <u32 KM>
+__device__ __forceinline__ double mid_convert(const u32 (&yp)[KM][2], const u32 *__restrict__ f, double q, double u) {
+    u64 lo = 0, hi = 0;
+#pragma unroll
+    for (u32 k = 0; k < KM; ++k) {
+#pragma unroll
+        for (u32 a = 0; a < 2; ++a) {
+            lo += (u64)yp[k][a] * f[(k * 2 + a) * 2 + 0];
+            hi += (u64)yp[k][a] * f[(k * 2 + a) * 2 + 1];
+        }
+    }
+    const double t1 = fma((double)(u32)(hi >> 32), 33554432.0, (double)(u32)(lo >> 32)) * 4294967296.0;
+    const double t2 = (double)(u32)hi * 33554432.0;
+    return (fma(-rint(t1 * u), q, t1) + fma(-rint(t2 * u), q, t2)) + (double)(u32)lo;
+}
+
 // Decomposition between the two tile passes at N = 2^(12+LOGR), one kernel instead of four.  The last LOGR stages of the
 // inverse transform of c1, the base conversion of every digit (ModUp) and the first LOGR stages of the forward transform
 // of the extended rows all work on columns (residues 4096 apart); a workgroup owns a tile of 512 coefficients, 512 >> LOGR
 // columns of 2^LOGR rows, of one digit of one ciphertext:
 //   1. group a of 32 threads: the columns of limb lo + a of the digit in registers, last inverse round with
 //      N^-1 (Q_D/q_i)^-1 folded in -> y_a in LDS;
-//   2. every thread takes two coefficients of the tile: for each group of UP_TG targets and each of its two coefficients:
-//      targets among the ciphertext primes as exact two-double sums; targets among the special primes from
-//      25-bit pieces of y and 20-bit parts of the factors (6 AM exact fp64 multiply-adds, then one Montgomery reduction
-//      of the recombined 90-bit sum) -> LDS;
+//   2. every thread takes two coefficients of the tile, both at once for each target of a group of UP_TG (a target's factors
+//      arrive once for both): exact sums of 25-bit pieces of y, onto the ciphertext primes by mid_convert, onto the special
+//      primes with factors in 30-bit parts and one Montgomery reduction of the recombined 90-bit sum -> LDS;
 //   3. group t of 32 threads: the columns of target t from LDS, first forward round (fp64 or integer butterflies), out.
 // At N = 2^12 (LOGR = 0) the tile passes are whole transforms: a thread scales, converts and stores its own coefficients,
 // without LDS (through it, where 32 threads scale or store a whole limb, a bank of 6 switches at level 1 took 45.4 us, now 41.3).
@@ -240,8 +275,8 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
                                                         const double *__restrict__ twf_fwd,
                                                         const u64 *__restrict__ tws_fwd,
                                                         const u64 *__restrict__ ninvs,
-                                                        const double *__restrict__ up_ft,
-                                                        const double *__restrict__ up_mats, u32 level, u32 K, u32 L,
+                                                        const u32 *__restrict__ up_ft,
+                                                        const u32 *__restrict__ up_mats, u32 level, u32 K, u32 L,
                                                         u32 alpha, u32 beta, u32 tsplit) {
     constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, COLS = MID_TILE >> LOGR, PER = COLS / 32;
     static_assert(UP_TG == 8 && AM <= 8, "the target tiles reuse the 8 rows of source tiles");
@@ -290,78 +325,53 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
             for (u32 a = 0; a < AM; ++a) yraw[e][a] = a < nd ? ylds[a * MID_TILE + e * 256 + tid] : 0;
         __syncthreads();            // every thread has its y: the tile may be overwritten
     }
+    u32 yp[2][AM][2];
+#pragma unroll
+    for (u32 e = 0; e < 2; ++e) mid_pieces<AM, 25>(yraw[e], yp[e]);
     u64 *dig = digits + ((size_t)r * beta + j) * Wl * N;
     const u32 nt = Wl - nd;                                          // targets: all rows outside the digit
     for (u32 u0 = tpart * UP_TG; u0 < nt; u0 += tsplit * UP_TG) {
-#pragma unroll 1
-        for (u32 e = 0; e < 2; ++e) {
-            double yd[AM], yp[AM][2];
+        for (u32 tt = 0; tt < UP_TG && u0 + tt < nt; ++tt) {
+            const u32 uu = u0 + tt, t = uu < lo ? uu : uu + nd;      // row of the extended basis
+            u64 res[2];
+            if (t < level) {
+                // target among the ciphertext primes
+                const double q = modf[t].q, u = modf[t].u;
+                const u32 *f = up_ft + ((size_t)j * Wl + t) * (AM * 4);   // zero beyond the digit's limbs, as y is
 #pragma unroll
-            for (u32 a = 0; a < AM; ++a) {
-                const u64 v = e ? yraw[1][a] : yraw[0][a];
-                yp[a][0] = __longlong_as_double((long long)(0x4330000000000000ull | (v & 0x1FFFFFFu))) - 4503599627370496.0;
-                yp[a][1] = __longlong_as_double((long long)(0x4330000000000000ull | (v >> 25))) - 4503599627370496.0;
-                yd[a] = fma(yp[a][1], 33554432.0, yp[a][0]);         // exact: y < 2^50
-            }
-            for (u32 tt = 0; tt < UP_TG && u0 + tt < nt; ++tt) {
-                const u32 uu = u0 + tt, t = uu < lo ? uu : uu + nd;  // row of the extended basis
-                u64 res;
-                if (t < level) {
-                    // target among the ciphertext primes: two-double sums of at most four products of y (canonical)
-                    // and a balanced factor, two of them for wide digits; the high parts together are a multiple of
-                    // 2^50 below 2^102, the low parts below 2^52, and c is off the rounded quotient by less than 1.5,
-                    // so every step is exact and |acc| < 2 q: the forward round normalises what it takes (4 instructions
-                    // per product instead of 7: 503 -> 464 us per 32 ciphertexts of 24 limbs)
-                    const double q = modf[t].q, u = modf[t].u;
-                    const double *fd = up_ft + ((size_t)j * Wl + t) * AM;  // zero beyond the digit's limbs, as y is
-                    MacSum s0{MAC_H0, 0.0}, s1{MAC_H0, 0.0};
-#pragma unroll
-                    for (u32 a = 0; a < AM; ++a) {
-                        if (a < 4)
-                            s0.mac(yd[a], fd[a]);
-                        else
-                            s1.mac(yd[a], fd[a]);
-                    }
-                    double h = s0.h - MAC_H0, l = s0.l;
-                    if (AM > 4) {
-                        h += s1.h - MAC_H0;
-                        l += s1.l;
-                    }
-                    const double c = rint(fma(h, u, l * u));
-                    const double v = fma(-c, q, h) + l;
+                for (u32 e = 0; e < 2; ++e) {
+                    const double v = mid_convert<AM>(yp[e], f, q, u);    // the forward round normalises it
                     if constexpr (LOGR == 0)
-                        res = make_field_fp(modf[t], twf_fwd, t, logN).out(v);
+                        res[e] = make_field_fp(modf[t], twf_fwd, t, logN).out(v);
                     else
-                        res = (u64)__double_as_longlong(v);
-                } else {
-                    // target among the special primes: sum_a y_a F_a with F_a 2^64 2^(25b) mod p in 20-bit parts
-                    const u32 k = t - level;
-                    const double *g = up_mats + ((size_t)j * K + k) * (AM * 6);   // zero beyond the digit's limbs
-                    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+                        res[e] = (u64)__double_as_longlong(v);
+                }
+            } else {
+                // target among the special primes: sum_a sum_b y_ab F_ab, F_ab = F_a 2^64 2^(25b) mod p in two 30-bit parts
+                const u32 k = t - level;
+                const u32 *f = up_mats + ((size_t)j * K + k) * (AM * 4);
 #pragma unroll
-                    for (u32 a = 0; a < AM; ++a) {
+                for (u32 e = 0; e < 2; ++e) {
+                    u64 s0 = 0, s1 = 0;                              // 16 products of 55 bits each
+#pragma unroll
+                    for (u32 a = 0; a < AM; ++a)
 #pragma unroll
                         for (u32 b = 0; b < 2; ++b) {
-                            s0 = fma(yp[a][b], g[(a * 2 + b) * 3 + 0], s0);
-                            s1 = fma(yp[a][b], g[(a * 2 + b) * 3 + 1], s1);
-                            s2 = fma(yp[a][b], g[(a * 2 + b) * 3 + 2], s2);
+                            s0 += (u64)yp[e][a][b] * f[(a * 2 + b) * 2 + 0];
+                            s1 += (u64)yp[e][a][b] * f[(a * 2 + b) * 2 + 1];
                         }
-                    }
-                    // each sum is an exact integer below 2^49; s0 + s1 2^20 + s2 2^40 < 2^90 as a 128-bit number
-                    const u64 i0 = (u64)__double_as_longlong(s0 + 4503599627370496.0) & 0x000fffffffffffffull;
-                    const u64 i1 = (u64)__double_as_longlong(s1 + 4503599627370496.0) & 0x000fffffffffffffull;
-                    const u64 i2 = (u64)__double_as_longlong(s2 + 4503599627370496.0) & 0x000fffffffffffffull;
-                    u128 acc;
-                    acc.lo = i0;
-                    acc.hi = 0;
-                    acc_add(acc, u128{i1 << 20, i1 >> 44});
-                    acc_add(acc, u128{i2 << 40, i2 >> 24});
-                    res = redc_wide(acc, mods[L + k]);               // canonical: the factors carry 2^64
+                    u128 acc{s0, 0};                                 // s0 + s1 2^30 < 2^90
+                    acc_add(acc, u128{s1 << 30, s1 >> 34});
+                    res[e] = redc(acc, mods[L + k]);                 // canonical: the factors carry 2^64
+                    if (LOGR != 0 && modf[L + k].ok) res[e] = (u64)__double_as_longlong(canonical_double(res[e]));
                 }
+            }
+#pragma unroll
+            for (u32 e = 0; e < 2; ++e) {
                 if constexpr (LOGR == 0)
-                    dig[(size_t)t * N + c0 + e * 256 + tid] = res;
+                    dig[(size_t)t * N + c0 + e * 256 + tid] = res[e];
                 else
-                    wlds[tt * MID_TILE + e * 256 + tid] = res;
+                    wlds[tt * MID_TILE + e * 256 + tid] = res[e];
             }
         }
         if constexpr (LOGR == 0) continue;
@@ -374,7 +384,7 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
 #pragma unroll
             for (u32 c = 0; c < PER; ++c) {
                 const u32 col = lane + 32 * c;
-                if (t < level) {
+                if (mf.ok) {
                     const FieldFp ff = make_field_fp(mf, twf_fwd, gl, logN);
                     double v[R];
 #pragma unroll
@@ -386,10 +396,7 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
                 } else {
                     auto load = [&](u32 idx) { return wlds[grp * MID_TILE + (idx >> 12) * COLS + col]; };
                     auto store = [&](u32 idx, u64 v) { dst[idx] = v; };
-                    if (mf.ok)
-                        pass_a_body<false, LOGR>(make_field_fp(mf, twf_fwd, gl, logN), c0 + col, load, store);
-                    else
-                        pass_a_body<false, LOGR>(make_field_int(mods, tws_fwd, ninvs, gl, logN), c0 + col, load, store);
+                    pass_a_body<false, LOGR>(make_field_int(mods, tws_fwd, ninvs, gl, logN), c0 + col, load, store);
                 }
             }
         }
@@ -863,8 +870,8 @@ __global__ __launch_bounds__(KS_THREADS) void moddown_conv_kernel(const u64 *__r
 // (512 >> LOGR columns) can do all three without leaving the CU:
 //   1. group k of 32 threads: the columns of special limb k in registers, last inverse round (which folds in
 //      N^-1 (P/p_k)^-1) -> y_k in LDS;
-//   2. every thread: its two coefficients' y_k cut into 20-bit pieces, then for each group of
-//      MID_TG target limbs the exact fp64 sums of moddown_conv_kernel -> w in LDS;
+//   2. every thread: its two coefficients' y_k cut into 30-bit pieces, then for each group of
+//      MID_TG target limbs the exact sums of mid_convert -> w in LDS;
 //   3. group t of 32 threads: the columns of w_t from LDS, first forward round, out.
 // At N = 2^12 (LOGR = 0) the tile passes are whole transforms and this is the conversion alone, without LDS.
 // y: rows (pc*ystride + yoff + k) hold the special limbs after the inverse tile pass; w [pc][level][N] receives the
@@ -872,40 +879,9 @@ __global__ __launch_bounds__(KS_THREADS) void moddown_conv_kernel(const u64 *__r
 // 2^60 (the launcher checks).  grid: x = column tile, y = pc.
 constexpr u32 MID_TG = 8, MID_MAX_LEVEL = 32;
 // KM: K rounded up to a power of two; the factor table is padded with zeros to it, so the loop has no per-prime checks
-// and a target's 6 KM factors arrive through the scalar cache in one burst (with the checks the wave waited for each
+// and a target's 4 KM factors arrive through the scalar cache in one burst (with the checks the wave waited for each
 // prime's six in turn).  Staging the factors in LDS instead was measured slower: broadcast reads still take an LDS issue
 // slot per pair of multiply-adds.
-// w_i = sum_k y_k (P/p_k mod q_i) for the two coefficients of a thread, as doubles with |w| <= q/2: the exact fp64 sums
-// of moddown_conv_kernel (20-bit pieces of y times 25-bit halves of the factors)
-template <u32 KM>
-__device__ __forceinline__ double mid_convert(const double (&yp)[KM][3], const double *__restrict__ f, double q,
-                                              double u) {
-    double lo = 0.0, hi = 0.0;
-#pragma unroll
-    for (u32 k = 0; k < KM; ++k) {
-#pragma unroll
-        for (u32 a = 0; a < 3; ++a) {
-            lo = fma(yp[k][a], f[(k * 3 + a) * 2 + 0], lo);
-            hi = fma(yp[k][a], f[(k * 3 + a) * 2 + 1], hi);
-        }
-    }
-    const double tt = hi * 33554432.0;                              // exact: a power of two
-    const double x = fma(-rint(tt * u), q, tt) + lo;                // |.| < 0.75 q, plus low < 2^51
-    return fma(-rint(x * u), q, x);                                 // |v| <= q/2
-}
-
-// the 20-bit pieces of the K special-limb values of one coefficient, as doubles
-template <u32 KM>
-__device__ __forceinline__ void mid_pieces(const u64 (&yraw)[KM], double (&yp)[KM][3]) {
-#pragma unroll
-    for (u32 k = 0; k < KM; ++k) {
-        const u64 v = yraw[k];
-        yp[k][0] = __longlong_as_double((long long)(0x4330000000000000ull | (v & 0xFFFFFu))) - 4503599627370496.0;
-        yp[k][1] = __longlong_as_double((long long)(0x4330000000000000ull | ((v >> 20) & 0xFFFFFu))) - 4503599627370496.0;
-        yp[k][2] = __longlong_as_double((long long)(0x4330000000000000ull | (v >> 40))) - 4503599627370496.0;
-    }
-}
-
 // RESC: ModDown and rescale in one (the merged giant step's last act).  The rescale needs the dropped limb of the
 // brought-down ciphertext in the coefficient domain, r = INTT(z + u P^-1)[l-1] - w_{l-1} P^-1, with z the part of the
 // ciphertext that needs no ModDown; t_rows holds INTT(z + u P^-1)[l-1] and w_{l-1} is computed here first.  With
@@ -921,7 +897,7 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
                                                           const double *__restrict__ twf_inv,
                                                           const u64 *__restrict__ ninv_dn,
                                                           const double *__restrict__ twf_fwd,
-                                                          const double *__restrict__ dn_matf, u32 level, u32 K, u32 L,
+                                                          const u32 *__restrict__ dn_mats, u32 level, u32 K, u32 L,
                                                           u32 ystride, u32 yoff, const u64 *__restrict__ t_rows,
                                                           u32 tsplit, bool streamed) {
     constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, COLS = MID_TILE >> LOGR, PER = COLS / 32;
@@ -963,6 +939,9 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
             for (u32 k = 0; k < KM; ++k) yraw[e][k] = k < K ? ylds[k * MID_TILE + e * 256 + tid] : 0;
         __syncthreads();            // every thread has its y: the tile may be overwritten
     }
+    u32 yp[2][KM][2];
+#pragma unroll
+    for (u32 e = 0; e < 2; ++e) mid_pieces<KM, 30>(yraw[e], yp[e]);
     // rescale: the dropped limb first
     double rp[2] = {0.0, 0.0}, hq = 0.0;
     const u32 n_out = RESC ? level - 1 : level;
@@ -977,9 +956,7 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
         hq = (double)(mods[il].q >> 1);
 #pragma unroll
         for (u32 e = 0; e < 2; ++e) {
-            double yp[KM][3];
-            mid_pieces<KM>(yraw[e], yp);
-            const double wl = mid_convert<KM>(yp, dn_matf + (size_t)il * (KM * 6), ml.q, ml.u);
+            const double wl = mid_convert<KM>(yp[e], dn_mats + (size_t)il * (KM * 4), ml.q, ml.u);
             const u32 el = e * 256 + tid;
             const double t = fl.in(t_rows[(size_t)pc * N + el / COLS * 4096 + c0 + el % COLS]);
             double r = t - wl;
@@ -990,27 +967,22 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
         }
     }
     for (u32 i0 = tpart * MID_TG; i0 < n_out; i0 += tsplit * MID_TG) {
-        // one coefficient at a time: its 24 pieces are rebuilt per group of targets (24 doubles live instead of 48,
-        // which is what lets four waves share a SIMD)
-#pragma unroll 1
-        for (u32 e = 0; e < 2; ++e) {
-            double yp[KM][3];
-            mid_pieces<KM>(e ? yraw[1] : yraw[0], yp);
-            const double rpe = e ? rp[1] : rp[0];
-            for (u32 t = 0; t < MID_TG && i0 + t < n_out; ++t) {
-                const u32 i = i0 + t;
-                const double q = modf[i].q, u = modf[i].u;
-                double v = mid_convert<KM>(yp, dn_matf + (size_t)i * (KM * 6), q, u);
+        for (u32 t = 0; t < MID_TG && i0 + t < n_out; ++t) {
+            const u32 i = i0 + t;
+            const double q = modf[i].q, u = modf[i].u;
+#pragma unroll
+            for (u32 e = 0; e < 2; ++e) {
+                double v = mid_convert<KM>(yp[e], dn_mats + (size_t)i * (KM * 4), q, u);
                 if (RESC) {
                     FieldFp fi;
                     fi.q = q;
                     fi.u = u;
                     fi.n0 = fi.n1 = 0.0;
                     fi.tw = nullptr;
-                    double hi_ = hq, ri = rpe;
+                    double hi_ = hq, ri = rp[e];
                     fi.norm(hi_);                                   // floor(q_last / 2) mod q_i
                     fi.norm(ri);                                    // r' mod q_i
-                    v += ri - hi_;                                  // |.| < 2q: the forward round normalises
+                    v += ri - hi_;                                  // |.| < 2q + 2^32: the forward round normalises
                 }
                 if constexpr (LOGR == 0)
                     w[((size_t)pc * level + i) * N + c0 + e * 256 + tid] = make_field_fp(modf[i], twf_fwd, i, logN).out(v);
@@ -1123,7 +1095,7 @@ static void launch_moddown_mid(const ckks_params *p, const u64 *y, u64 *w, u32 n
     const u32 tsplit = target_split(tiles * n * 2, (level - (t_rows ? 1 : 0) + MID_TG - 1) / MID_TG);
     hipLaunchKernelGGL(t_rows ? moddown_mid_for<true>(p) : moddown_mid_for<false>(p), dim3(tiles * tsplit, n * 2),
                        dim3(256), 0, stream, y, w, p->d_mod, p->d_modf, p->d_modf_dn, p->d_tws_inv, p->d_twf_inv,
-                       p->d_ninvs_dn, p->d_twf_fwd, p->d_dn_matf, level, p->K, p->L, ystride, yoff, t_rows, tsplit,
+                       p->d_ninvs_dn, p->d_twf_fwd, p->d_dn_mats, level, p->K, p->L, ystride, yoff, t_rows, tsplit,
                        (size_t)n * 2 * level * p->N * sizeof(u64) > STREAM_BYTES);
 }
 

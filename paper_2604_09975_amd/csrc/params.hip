@@ -183,7 +183,8 @@ int ckks_params::build_level_tables(u32 level) {
     // per digit j and target row t (k for the special rows): the factors of the digit's up to 8 source limbs side
     // by side, zero up to the next power of two (alpha above 8 does not use these tables)
     const u32 am = pad_pow2(alpha);
-    std::vector<double> mats((size_t)t.beta * K * am * 6, 0.0), ft((size_t)t.beta * Wl * am, 0.0);
+    std::vector<u32> mats((size_t)t.beta * K * am * 4, 0);
+    std::vector<u32> ft((size_t)t.beta * Wl * am * 4, 0);
     for (u32 i = 0; i < level; ++i) {
         u32 lo = (i / alpha) * alpha, hi = std::min(lo + alpha, level);
         u64 qi = mod[i], prod = 1;
@@ -206,8 +207,8 @@ int ckks_params::build_level_tables(u32 level) {
                 if (b != i) fk = hmul(fk, mod[b] % pk, pk);
             for (u32 b = 0; b < 2; ++b) {
                 u64 g = hmul(hmul(fk, hpow(2, 25 * b, pk), pk), hmod[L + k].one, pk);
-                for (u32 c = 0; c < 3; ++c)
-                    mats[((((size_t)dj * K + k) * am + da) * 2 + b) * 3 + c] = (double)((g >> (20 * c)) & 0xFFFFFu);
+                for (u32 c = 0; c < 2; ++c)                    // used for primes below 2^60
+                    mats[((((size_t)dj * K + k) * am + da) * 2 + b) * 2 + c] = (u32)(g >> (30 * c)) & 0x3FFFFFFFu;
             }
         }
         for (u32 t2 = 0; t2 < level; ++t2) {
@@ -215,8 +216,11 @@ int ckks_params::build_level_tables(u32 level) {
             u64 mt = mod[t2], fq = 1;
             for (u32 b = lo; b < hi; ++b)
                 if (b != i) fq = hmul(fq, mod[b] % mt, mt);
-            // balanced; used for targets below 2^50
-            ft[((size_t)dj * Wl + t2) * am + da] = fq > mt / 2 ? -(double)(mt - fq) : (double)fq;
+            for (u32 b = 0; b < 2; ++b) {                      // used for targets below 2^50
+                const u64 g = hmul(fq, hpow(2, 25 * b, mt), mt);
+                for (u32 c = 0; c < 2; ++c)
+                    ft[((((size_t)dj * Wl + t2) * am + da) * 2 + b) * 2 + c] = (u32)(g >> (25 * c)) & 0x1FFFFFFu;
+            }
         }
     }
     // entered into the map first, so that ckks_params_destroy frees whatever part was uploaded if a later part fails
@@ -382,6 +386,7 @@ int ckks_params_create(uint32_t logN, const uint64_t *q, uint32_t L, const uint6
     std::vector<u64> dn_inv(K), dn_mat((size_t)K * L), pinv(L), qlinv((size_t)L * L, 0);
     const u32 kpad = pad_pow2(K);
     std::vector<double> dn_matf((size_t)L * kpad * 6, 0.0);
+    std::vector<u32> dn_mats((size_t)L * kpad * 4, 0);
     for (u32 k = 0; k < K; ++k) {
         u64 pk = mod[L + k], prod = 1;
         for (u32 b = 0; b < K; ++b)
@@ -396,6 +401,11 @@ int ckks_params_create(uint32_t logN, const uint64_t *q, uint32_t L, const uint6
                 const u64 c = hmul(f, hpow(2, 20 * a, mod[i]), mod[i]);
                 dn_matf[(((size_t)i * kpad + k) * 3 + a) * 2 + 0] = (double)(c & ((1u << 25) - 1));
                 dn_matf[(((size_t)i * kpad + k) * 3 + a) * 2 + 1] = (double)(c >> 25);
+            }
+            for (u32 a = 0; a < 2; ++a) {                            // 30-bit pieces, integer halves (targets below 2^50)
+                const u64 c = hmul(f, hpow(2, 30 * a, mod[i]), mod[i]);
+                dn_mats[(((size_t)i * kpad + k) * 2 + a) * 2 + 0] = (u32)(c & ((1u << 25) - 1));
+                dn_mats[(((size_t)i * kpad + k) * 2 + a) * 2 + 1] = (u32)(c >> 25);
             }
         }
     }
@@ -441,6 +451,7 @@ int ckks_params_create(uint32_t logN, const uint64_t *q, uint32_t L, const uint6
     if (!rc) rc = upload(&P->d_dn_inv, dn_inv);
     if (!rc) rc = upload(&P->d_dn_mat, dn_mat);
     if (!rc) rc = upload(&P->d_dn_matf, dn_matf);
+    if (!rc) rc = upload(&P->d_dn_mats, dn_mats);
     if (!rc) rc = upload(&P->d_pinv, pinv);
     if (!rc) rc = upload(&P->d_qlinv, qlinv);
     if (!rc) rc = upload(&P->d_tws_fwd, fwd_s);
@@ -499,6 +510,7 @@ void ckks_params_destroy(ckks_params_t *P) {
     hipFree(P->d_dn_inv);
     hipFree(P->d_dn_mat);
     hipFree(P->d_dn_matf);
+    hipFree(P->d_dn_mats);
     hipFree(P->d_pinv);
     hipFree(P->d_qlinv);
     hipFree(P->d_tws_fwd);
