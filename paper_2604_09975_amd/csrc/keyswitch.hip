@@ -1200,7 +1200,10 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void ip_intt_kernel(ItemPack pac
 #pragma unroll
                 for (u32 j = 0; j < MAX_BETA; ++j)
                     if (j < beta) mac(acc, dv[e][j][z], kv[e][j][z]);
-                lds[TL::slot(loc + z)] = redc_wide(acc, m);
+                // up to four products of residues below 2^62: a sum below q 2^64 (redc_wide's loop is a branch per residue: 24
+                // switches at 2^14 30.4 us, without it 26.3, one at 2^16 18.7 and 16.2, 27 346 and 340)
+                static_assert(MAX_BETA <= 4, "the sum has to stay below q 2^64");
+                lds[TL::slot(loc + z)] = redc(acc, m);
             }
         }
     }
@@ -1306,7 +1309,7 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void passb_final_kernel(ItemPack
 #pragma unroll
                     for (u32 j = 0; j < MAX_BETA; ++j)
                         if (j < beta) mac(acc, dv[e][j][z], kv[e][j][z]);
-                    u64 v = sub_mod(redc_wide(acc, m), lds[TL::slot(loc + z)], m.q);
+                    u64 v = sub_mod(redc(acc, m), lds[TL::slot(loc + z)], m.q);    // as in ip_intt_kernel
                     v = add_mod(v, cv[e][z], m.q);
                     out[z] = add_mod(v, ov[e][z], m.q);
                 }
