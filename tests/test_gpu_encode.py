@@ -162,6 +162,22 @@ def test_more_vectors_than_one_chunk():
     assert (back - z).abs().max().item() <= 0.5 * O.N / 2.0**30
 
 
+@pytest.mark.parametrize("logN,count", [(13, 64), (15, 63), (16, 32), (16, 33)])
+def test_decode_on_either_side_of_the_wide_near_pass(logN, count):
+    """Up to 256 workgroups the near pass takes 1024 threads, above 256: the same operations on the same values, so a batch
+    (256 workgroups at 2^16 x 32, 264 at x 33) gives the bits of single calls, and both are the oracle's slots."""
+    from paper_2604_09975_amd import binding as B
+    O = helpers.small_oracle(logN, L=2, K=1, dnum=2, qbits=50, pbits=57)
+    _, P = make_pair(O)
+    m = W.rng(630 + logN).integers(-(1 << 40), 1 << 40, (count, O.N))
+    res = to_dev(np.stack([(m % int(q)).astype(np.uint64) for q in O.q], axis=1))
+    got = B.ckks_decode(P, res, 2, 2.0**36)
+    for i in (0, count // 2, count - 1):
+        assert torch.equal(torch.view_as_real(got[i]), torch.view_as_real(B.ckks_decode(P, res[i:i + 1].contiguous(), 2, 2.0**36)[0]))
+    want = E.decode(m[0], 2.0**36, O.N)
+    assert np.abs(got[0].cpu().numpy() - want).max() / np.abs(want).max() < 1e-13
+
+
 @pytest.mark.parametrize("qbits", [50, 55])
 @pytest.mark.parametrize("logN", [11, 14])
 def test_two_limb_lift_at_the_ends_of_its_range(logN, qbits):
