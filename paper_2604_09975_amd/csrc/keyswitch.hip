@@ -638,9 +638,9 @@ __global__ __launch_bounds__(KS_THREADS) void merged_ip_kernel(MergedRot rots, c
 // Bound by the chain of a workgroup's loads, transform and gather (two workgroups of 512 threads per CU hide each other's)
 // and by the integer butterflies of the special limbs.  RL = 3: eight residues a thread, whose sums, keys and transform fit
 // the 128 registers that two workgroups leave (RL = 4 takes 200 and more; any spilling costs more than the fusion gives: 2.98
-// ms where this takes 2.0).  A digit's key loads are issued before the barrier in front of its products; the next digit
+// ms where this takes 1.81).  A digit's key loads are issued before the barrier in front of its products; the next digit
 // loaded there as well spills or gains nothing.  QKV projection, 63 rotations of 24 + 8 limbs: 1.43 ms of tile passes and
-// 1.04 of merged_ip_kernel before, 1.7 now (the call 17.05 -> 16.38 ms).
+// 1.04 of merged_ip_kernel before, 1.81 now (the call 17.05 -> 16.38 ms).
 template <u32 RL>
 __global__ __launch_bounds__(Tile<RL>::THREADS, 4) void merged_tile_kernel(MergedRot rots, const u64 *__restrict__ digits,
                                                                         size_t dig_w, const u64 *__restrict__ c0_base,
@@ -766,7 +766,8 @@ __global__ __launch_bounds__(Tile<RL>::THREADS, 4) void merged_tile_kernel(Merge
            [&](u64 x) { return canonical_double(x); }, [&](u64 &) {}, [&](u64 a) { return a; });
     } else {
         const FieldInt f = make_field_int(mods, tw_fwd, ninv, gl, logN);
-        go(f, (u64)0, [&](u64 a, u64 x, u64 k) { return add_mod(a, mont_mul(f.out(x), k, m), m.q); }, [&](u64 x) { return x; },
+        // x as the butterflies leave it, below 4q <= 2^64: a product below q 2^64
+        go(f, (u64)0, [&](u64 a, u64 x, u64 k) { return add_mod(a, mont_mul(x, k, m), m.q); }, [&](u64 x) { return x; },
            [&](u64 &) {}, [&](u64 a) { return a; });
     }
     if (t < level) {
