@@ -1084,9 +1084,9 @@ static moddown_mid_t moddown_mid_for(const ckks_params *p) {
 
 // Workgroups among which ModDown splits the target groups of a tile: as many as fill the chip once (three workgroups per
 // CU at N = 2^16, 256 CUs) and no more.  Whole calls with at most 256 / 512 / 768 / 1024 / 1536 workgroups, us: one rotation
-// at 2^16, level 24: 180 / 170 / 164.5 / 164.5 / 164.5, level 17: 167 / 159 / 156.8 / 156.7 / 156.7, two at level 24: 214.4 up
-// to 1024, 211.6; a product and rescale at 2^16, level 24: 241 / 232 / 225.5 and no less above; at 2^15, 12 + 4 primes, two
-// switches 116.8, then 112.5, four 128.4 / 128.4 / 128.4 / 126.0 / 126.0; 2^14 the same at all.  (ModUp's step 1 is
+// at 2^16, level 24: 146.6 / 143.7 / 141.3 / 141.5 / 143.6, level 17: 130.6 / 127.8 / 127.6 / 127.9 / 129.5, two at level 24
+// 192.1 / 191.6 / 189.6 / 192.9 / 198.0; a product and rescale at 2^16, level 24: 202.7 / 198.4 / 194.9 / 195.4 / 197.0; at
+// 2^15, 12 + 4 primes, two switches 88.8 and 86.5 from 512 on, four 102.8 to 103.6; 2^14 the same at all.  (ModUp's step 1 is
 // cheap fp64 work, and its rule differs: see decompose.)
 static u32 target_split(u32 workgroups, u32 groups) { return std::max<u32>(1, std::min<u32>(groups, 768 / workgroups)); }
 
@@ -1395,9 +1395,9 @@ int decompose(ckks_params *p, const u64 *const *c1, u32 n, u32 level, u64 *d_dig
         if (p->logN <= 16 && all_fp && sp60 && alpha <= 8 && K <= 8) {
             // the column passes of both transforms ride in the base conversion: c1 read once, digits written once
             const u32 tgroups = (Wl - std::min(alpha, level) + UP_TG - 1) / UP_TG, tiles = N / MID_TILE;
-            // all target groups apart below 1024 workgroups: one rotation at 2^16, level 24 / 17 / 9, a product and rescale at
-            // 2^16 and 2^15 165.1 / 155.1 / 115.6, 222.2 and 131.3 us; never split 169.4 / 158.5 / 120.8, 226.4 and 135.8; split
-            // as ModDown's are 166.1 / 156.7 / 115.5, 223.5 and 131.3; with the line at 3072 as at 1024, projections too
+            // all target groups apart below 1024 workgroups: one rotation at 2^16, level 24 / 17 / 9, two at level 24, a product
+            // and rescale at 2^16 and 2^15 141.3 / 127.6 / 91.4, 189.6, 194.9 and 97.0 us; never split 141.9 / 131.6 / 95.5,
+            // 191.4, 196.0 and 100.2; with the line at 3072 142.4 / 128.7 / 91.5, 190.6, 196.5 and 97.1
             const u32 tsplit = n * beta * tiles < 1024 ? std::max<u32>(1, tgroups) : 1;
             hipLaunchKernelGGL(modup_mid_for(p), dim3(tiles * tsplit, beta, n), dim3(256), 0, stream, d_tmp,
                                d_digits, p->d_mod, p->d_modf, lt->d_modf_up, p->d_twf_inv, p->d_twf_fwd, p->d_tws_fwd,
@@ -1610,9 +1610,9 @@ int switch_batch(ckks_params *p, u32 level, const SwitchItem *items, u32 n, u64 
         // at N = 2^12 the tile pass is the whole inverse transform and carries the (P/p_k)^-1 scaling itself
         const bool whole = p->logN == 12;
         const bool own_keys = n_groups == n;               // no two neighbouring items share a key
-        // digits by 16-byte gathers above eight workgroups per CU: by 8-byte and by 16-byte loads one rotation at level 1 of
-        // 2^16 (256 workgroups) 85.8 and 86.6 us, two at level 1 94.9 and 95.7, four at level 24 (1024) 299.7 and 300.2, 27
-        // (6912) the same within the runs' 0.3 %
+        // digits by 16-byte gathers above eight workgroups per CU: in tiles of 256 threads one rotation at level 1 of 2^16 (256
+        // workgroups) took 85.8 us by 8-byte and 86.6 by 16-byte loads, two at level 1 94.9 and 95.7, four at level 24 (1024)
+        // 299.7 and 300.2, 27 (6912) the same within the runs' 0.3 %; wide tiles, up to 512 workgroups, always 8-byte ones
         const bool ip_pair = tiles * n * 2 * K > 2048;
         const bool ip_wide = wide_tiles(tiles * n * 2 * K);
         const auto ip_intt = own_keys ? (ip_wide   ? ip_intt_kernel<true, false, WIDE_RL>
@@ -1645,7 +1645,7 @@ int switch_batch(ckks_params *p, u32 level, const SwitchItem *items, u32 n, u64 
         }
         // 16-byte gathers above three workgroups per CU: one rotation at 2^16, level 24 (768 workgroups) by 8-byte loads 165.0
         // us, by 16-byte ones 165.5; 24 switches at 2^14, level 5 (960) and the rest of their call 169 and 167; eight rotations
-        // at 2^16, level 24 (6144) 496 and 493.
+        // at 2^16, level 24 (6144) 496 and 493 (calls as long as they were then; wide tiles by 8-byte ones).
         const bool pair = tiles * n * 2 * level > 768;
         const bool wide = wide_tiles(tiles * n * 2 * level);
         const auto passb = own_keys ? (wide   ? passb_final_kernel<true, false, WIDE_RL>
