@@ -646,16 +646,19 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void rescale_intt_kernel(const u
     pass_b_body<true, RL>(make_field_fp(modf[level - 1], twf_inv, level - 1, logN), logN, lds, load, store);
 }
 
-// grid: x = tiles of 512 coefficients, y = row; out rows [rows][level-1]
+// grid: x = tiles of 512 coefficients, tsplit times, y = row; out rows [rows][level-1].  tsplit > 1 (few rows): the groups of
+// limbs of a tile go to that many workgroups, each of which redoes the dropped limb's column pass
 template <u32 LOGR>
 __global__ __launch_bounds__(256) void rescale_mid_kernel(const u64 *__restrict__ r, u64 *__restrict__ out,
                                                           const ModFp *__restrict__ modf,
                                                           const ModConst *__restrict__ mods,
                                                           const double *__restrict__ twf_inv,
-                                                          const double *__restrict__ twf_fwd, u32 level) {
+                                                          const double *__restrict__ twf_fwd, u32 level,
+                                                          u32 tsplit) {
     constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, COLS = RS_TILE >> LOGR, PER = COLS / 32;
     __shared__ u64 lds[8 * RS_TILE];
-    const u32 tid = threadIdx.x, lane = tid & 31, grp = tid / 32, c0 = blockIdx.x * COLS, row = blockIdx.y;
+    const u32 tid = threadIdx.x, lane = tid & 31, grp = tid / 32, row = blockIdx.y;
+    const u32 c0 = blockIdx.x % (N / RS_TILE) * COLS, tpart = blockIdx.x / (N / RS_TILE);
     const u32 il = level - 1;
     const ModFp ml = modf[il];
     if (grp == 0) {
@@ -681,7 +684,7 @@ __global__ __launch_bounds__(256) void rescale_mid_kernel(const u64 *__restrict_
         if (rp[e] >= ml.q) rp[e] -= ml.q;                           // r' = (r + h) mod q_l
     }
     __syncthreads();
-    for (u32 i0 = 0; i0 < il; i0 += 8) {
+    for (u32 i0 = tpart * 8; i0 < il; i0 += tsplit * 8) {
         for (u32 t = 0; t < 8 && i0 + t < il; ++t) {
             const double q = modf[i0 + t].q, u = modf[i0 + t].u, hi = fma(-rint(h * u), q, h);
 #pragma unroll
@@ -1543,8 +1546,12 @@ static int rescale_rows(ckks_params *P, const u64 *d_in, u32 level, u32 rows, u6
         const auto mid = P->logN == 12 ? rescale_mid_kernel<0> : P->logN == 13 ? rescale_mid_kernel<1>
                        : P->logN == 14 ? rescale_mid_kernel<2> : P->logN == 15 ? rescale_mid_kernel<3>
                                                                                : rescale_mid_kernel<4>;
-        hipLaunchKernelGGL(mid, dim3(N / RS_TILE, rows), dim3(256), 0, stream, d_r, d_out, P->d_modf, P->d_mod,
-                           P->d_twf_inv, P->d_twf_fwd, level);
+        // as many workgroups as fill the chip, as for ModDown.  One ciphertext, never split / up to 512 / 768 / 1024 / 2048
+        // workgroups, us: 2^16, level 24 37.2 / 34.9 / 33.7 / 33.6 / 33.3, level 12 28.5 and 27.7, 2^15, level 12 20.7 and 19.4;
+        // two at 2^15 27.7 and 26.9, six 41.1 / 40.8 / 40.9 / 41.0 / 42.3, four at 2^16 84.5 / 84.7 / 84.3 / 84.4 / 86.5
+        const u32 tsplit = std::max<u32>(1, std::min<u32>((level - 1 + 7) / 8, 768 / (N / RS_TILE * rows)));
+        hipLaunchKernelGGL(mid, dim3(N / RS_TILE * tsplit, rows), dim3(256), 0, stream, d_r, d_out, P->d_modf, P->d_mod,
+                           P->d_twf_inv, P->d_twf_fwd, level, tsplit);
         CKKS_LAUNCH_CHECK("rescale_mid_kernel");
         hipLaunchKernelGGL(wide_out ? rescale_tile_kernel<WIDE_RL> : rescale_tile_kernel<4>, dim3(N >> 12, level - 1, rows),
                            dim3(tile_threads(wide_out)), 0, stream, d_in, d_out,

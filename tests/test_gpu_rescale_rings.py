@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("logN,L,level,qbits,n_ct", [(11, 4, 4, 50, 2), (12, 3, 3, 50, 3), (12, 11, 11, 40, 1), (12, 4, 3, 52, 2),
                                                      (13, 10, 9, 50, 2), (13, 2, 2, 50, 1), (14, 6, 5, 50, 2),
                                                      (15, 9, 9, 50, 1), (16, 18, 17, 50, 1), (16, 2, 2, 50, 2), (17, 3, 3, 50, 1),
-                                                     (12, 2, 2, 50, 70)])
+                                                     (12, 2, 2, 50, 70),
+                                                     # three groups of limbs among three workgroups, two and one
+                                                     (13, 18, 18, 50, 8), (13, 18, 18, 50, 12), (13, 18, 18, 50, 25)])
 def test_rescale_shapes(logN, L, level, qbits, n_ct):
     from paper_2604_09975_amd import binding as B
     O = helpers.small_oracle(logN, L=L, K=1, dnum=2 if L % 2 == 0 else 1, qbits=qbits, pbits=57)
