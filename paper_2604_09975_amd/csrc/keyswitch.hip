@@ -1455,12 +1455,27 @@ static u32 build_pack(const SwitchItem *items, u32 n, ItemPack &pack) {
     return n_groups;
 }
 
-// From 320 workgroups on: each is a chain of all rotations and digits, so fewer of them leave the chip idle that long.
-// Projections, separate tile passes / merged_tile_kernel, us: 128 workgroups (2^15, 1 block) 548 / 627, 256 (2^15, 2 blocks)
-// 694 / 729, 256 (2^13, 32 blocks) 571 / 537, 320 (2^16, level 12) 2259 / 2244, 384 (2^15) 856 / 841, 512 (2^14) 926 / 697,
-// 1536 (2^15) 2262 / 2034, 2048 (2^16) 5125 / 4753.
+// A workgroup of merged_tile_kernel is a chain of all rotations and digits, so few of them leave the chip idle that long, and 512
+// fit at a time.  Workgroups (ring, ciphertexts, digits), whole calls with 15 rotations, separate tile passes /
+// merged_tile_kernel, us:
+//   up to three digits: 256 (2^15, 2, 3) 767 / 826, 288 (2^13, 12, 2) 675 / 656, 312 (2^15, 3, 3) 864 / 907, 320 (2^16, 1, 2)
+//     851 / 821, 384 (2^15, 3, 3) 1033 / 988, 512 (2^14, 16, 3) 1606 / 1109, 544 (2^14, 17, 3) 1720 / 1171;
+//   more digits, of few ciphertexts: longer chains, beside a separate kernel that reads a key once for three ciphertexts: 320
+//     (2^16, 2, 4) 1074 / 1157, 336 (2^14, 4, 6) 1512 / 1564, 480 (2^16, 3, 4) 1449 / 1328; of more: 336 (2^15, 7, 5) 1426 / 1368;
+//   ciphertext primes from 2^50 up: the transforms of the chain take twice as long: 384 (2^15, 3, 3) 1619 / 1692, 512 (2^15, 4,
+//     3) 2083 / 1973, 576 (2^14, 9, 5; the second round nearly empty) 3438 / 3576, 640 (2^14, 10, 5) 3836 / 3813; two digits:
+//     352 (2^12, 32, 2) 1271 / 1176.
+// More rows of digits than one row map describes: their own tile passes are a launch per digit and ciphertext (2^14, 11
+// ciphertexts, 12 digits: 19130 / 3783).
 bool merged_from_half(const ckks_params *p, u32 level, u32 n) {
-    return fast_ring(p) && (u64)(p->N >> 12) * (level + p->K) * n >= 320;
+    const u32 Wl = level + p->K, beta = (level + p->alpha - 1) / p->alpha;
+    const u64 workgroups = (u64)(p->N >> 12) * Wl * n;
+    if (!fast_ring(p) || workgroups < 320) return false;
+    if (beta * Wl > MAX_ROW_IDS) return true;
+    u32 n_int = 0;
+    for (u32 i = 0; i < level; ++i) n_int += (p->mod[i] >> 50) != 0;
+    if (2 * n_int > level && beta > 2) return workgroups >= 640 || (workgroups >= 448 && workgroups <= 512);
+    return beta < 4 || n > 4 || workgroups >= 384;
 }
 
 // Merged giant step, part 1: d_u[r] (+)= the key inner products of rots.n_rot rotations of ciphertext r over all

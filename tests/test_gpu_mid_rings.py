@@ -43,9 +43,15 @@ def test_projection_with_fused_rescale(logN, m, C, N1):
 @pytest.mark.parametrize("logN,L,K,dnum,level,qbits,pbits,blocks,N1",
                          [(12, 6, 6, 3, 6, 50, 60, 27, 1), (12, 6, 6, 3, 5, 50, 60, 27, 1),     # 324 and 297 workgroups
                           (12, 8, 4, 2, 7, 45, 49, 30, 2), (12, 5, 6, 1, 5, 50, 60, 32, 4),     # special primes below 2^50; one digit
-                          (13, 5, 2, 5, 5, 50, 60, 24, 2), (13, 4, 2, 2, 3, 52, 60, 33, 2)])    # five digits; integer rows; two batches
+                          (13, 5, 2, 5, 5, 50, 60, 24, 2), (13, 4, 2, 2, 3, 52, 60, 33, 2),     # five digits; integer rows; two batches
+                          (14, 6, 2, 3, 6, 50, 60, 10, 4), (17, 2, 2, 2, 2, 50, 60, 3, 4),
+                          (15, 4, 8, 4, 4, 50, 60, 4, 4), (15, 4, 7, 4, 4, 50, 60, 4, 4),       # four digits of four: 384 and 352
+                          (12, 6, 8, 3, 6, 52, 60, 32, 4), (12, 6, 8, 3, 6, 52, 60, 31, 4),     # three digits, integer rows: 448 and 434,
+                          (13, 6, 8, 3, 6, 52, 60, 19, 4), (13, 6, 8, 3, 6, 52, 60, 23, 4),     # 532 and 644
+                          (12, 12, 1, 12, 12, 50, 60, 25, 4)])                                  # 156 rows of digits
 def test_merged_giant_step_on_either_side_of_the_fused_tile_pass(logN, L, K, dnum, level, qbits, pbits, blocks, N1):
-    """From 320 workgroups on the giant step's digits are transformed where their products are taken."""
+    """From 320 workgroups on the giant step's digits are transformed where their products are taken, with more than three
+    digits of few ciphertexts from 384 on, with three and more on integer rows from 448 to 512 and from 640 on."""
     O = helpers.small_oracle(logN, L=L, K=K, dnum=dnum, qbits=qbits, pbits=pbits)
     _, P = make_pair(O)
     r = W.rng(logN + blocks)
