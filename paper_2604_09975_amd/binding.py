@@ -78,10 +78,16 @@ def _check(rc):
         raise CkksError(rc, lib.ckks_last_error().decode())
 
 
+# The raw handle of torch's current stream.  torch.cuda.current_stream() makes a Stream object around it, 3 us where a whole
+# call of two launches took 13 to enqueue (decode of 5 vectors at N = 2^15, 12.9 us; 11.8 with the handle), but it is the
+# public name: it serves a torch that has not the other.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    # the handle itself: torch.cuda.current_stream() makes a Stream object around it, 3 us where a whole call of two launches
-    # took 13 to enqueue (decode of 5 vectors at N = 2^15, 12.9 us; 10.3 with the handle)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dev(t):

@@ -3,6 +3,8 @@ argument validation and prime search work without a GPU."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -84,3 +86,13 @@ def test_null_arguments_are_errors_not_crashes():
     B.lib.ckks_galois_key_destroy(None)
     B.lib.ckks_weights_destroy(None)
     assert b"null" in B.lib.ckks_last_error()
+
+
+def test_stream_of_a_torch_without_the_raw_handle():
+    """The handle of the current stream comes from torch's public Stream where torch has no private function for it."""
+    code = ("import torch, types\n"
+            "if hasattr(torch._C, '_cuda_getCurrentRawStream'): del torch._C._cuda_getCurrentRawStream\n"
+            "from paper_2604_09975_amd import binding as B\n"
+            "torch.cuda.current_stream = lambda: types.SimpleNamespace(cuda_stream=7)\n"
+            "assert B._stream() == 7\n")
+    subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True)
