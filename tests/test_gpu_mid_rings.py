@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from tests import helpers
-from tests.gpu_util import make_pair
+from tests.gpu_util import make_pair, to_dev, to_host
 from tests.test_gpu_matmul import run_case
 from tests.test_gpu_rotate import _run
 from paper_2604_09975_amd import workload as W
@@ -109,3 +109,69 @@ def test_more_digit_rows_than_one_launch_describes(logN, level):
     O = helpers.small_oracle(logN, L=12, K=1, dnum=12, qbits=50, pbits=60)
     _, P = make_pair(O)
     _run(O, P, level, [3], 1300 + logN, 2.0**40, hw=16)
+
+
+def _edge_residues(r, moduli, N, lead):
+    """Uniform residues, one in five q - 1."""
+    x = W.uniform_residues(r, moduli, N, lead=lead)
+    top = np.array(moduli, dtype=np.uint64)[:, None] - np.uint64(1)
+    return np.where(r.integers(0, 5, x.shape) == 0, top, x)
+
+
+def _large_primes(logN, L, K, qbits, pbits):
+    import oracle
+    p = oracle.find_primes(pbits, logN, K + (L if pbits == qbits else 0))
+    return (p[K:] if pbits == qbits else oracle.find_primes(qbits, logN, L)), p[:K]
+
+
+@pytest.mark.parametrize("logN,L,K,dnum,level,qbits,pbits,steps", [(12, 4, 2, 4, 4, 50, 62, 2), (12, 4, 4, 4, 4, 62, 62, 3),
+                                                                   (13, 8, 4, 4, 8, 61, 62, 2), (13, 4, 4, 1, 4, 62, 61, 1),
+                                                                   (14, 4, 4, 4, 4, 62, 62, 20), (16, 4, 2, 4, 3, 50, 61, 2)])
+def test_key_switch_at_the_largest_primes(logN, L, K, dnum, level, qbits, pbits, steps):
+    """Four digits on primes next to 2^62, where the key inner product's four products of residues leave the reduction the least
+    room (4 q^2 < q 2^64): residues of q - 1 among uniform ones, and a ciphertext whose every residue is q - 1 under keys whose
+    every residue is; a launch of wide tiles, and one above them (20 switches at 2^14)."""
+    import oracle
+    from paper_2604_09975_amd import binding as B
+    O, P = make_pair(oracle.Oracle(logN, *_large_primes(logN, L, K, qbits, pbits), dnum))
+    r = W.rng(100 * logN + pbits)
+    st = [3, 5, 7][:steps] if steps < 4 else [3] * steps
+    cts = [_edge_residues(r, O.q[:level], O.N, (2,)), np.empty((2, level, O.N), dtype=np.uint64)]
+    keys = [{s: _edge_residues(r, O.moduli, O.N, (dnum, 2)) for s in set(st)}, {}]
+    cts[1][:] = np.array(O.q[:level], dtype=np.uint64)[:, None] - np.uint64(1)
+    for s in set(st):
+        keys[1][s] = np.broadcast_to(np.array(O.moduli, dtype=np.uint64)[:, None] - np.uint64(1), keys[0][s].shape).copy()
+    for ct, ks in zip(cts, keys):
+        h = {s: B.ckks_galois_key_load(P, O.galois_elt(s), to_dev(k)) for s, k in ks.items()}
+        got = to_host(B.ckks_rotate_hoisted(P, to_dev(ct), level, st, [h[s] for s in st]))
+        for s in set(st):
+            want = O.rotate_hoisted(ct, level, [O.galois_elt(s)], [ks[s]])[0]
+            for i in range(len(st)):
+                assert st[i] != s or (got[i] == want).all(), i
+
+
+@pytest.mark.parametrize("logN,L,K,dnum,qbits,pbits,blocks,pair", [(13, 4, 4, 4, 50, 62, 20, False), (13, 4, 4, 4, 62, 62, 28, False),
+                                                                   (14, 6, 2, 3, 50, 60, 10, True), (15, 4, 2, 2, 50, 60, 7, True)])
+def test_merged_projection_of_uniform_residues(logN, L, K, dnum, qbits, pbits, blocks, pair):
+    """The fused tile pass of the giant step (320 workgroups and more) at the largest primes, whose transform values reach 2^64
+    where it multiplies them, with residues of q - 1 among the inputs and keys; and in a layer of complex-packed pairs."""
+    import oracle
+    from paper_2604_09975_amd import binding as B
+    O, P = make_pair(oracle.Oracle(logN, *_large_primes(logN, L, K, qbits, pbits), dnum))
+    r = W.rng(logN + blocks)
+    m, C, N1, G = O.n // 8, 8, 2, 1
+    N2 = C // N1
+    diag = r.integers(-1 << 40, 1 << 40, (blocks, N2, G, N1, O.N))
+    x = _edge_residues(r, O.q, O.N, (G, 2))
+    steps = [q * m for q in range(1, N1)], [p * N1 * m for p in range(1, N2)], ["conj"] if pair else []
+    keys = [[_edge_residues(r, O.moduli, O.N, (dnum, 2)) for _ in s] for s in steps]
+    baby, giant, conj = [[B.ckks_galois_key_load(P, O.galois_elt(s), to_dev(k)) for s, k in zip(ss, kk)]
+                         for ss, kk in zip(steps, keys)]
+    w = B.ckks_weights_create(P, L, m, C, G, blocks, N1)
+    B.ckks_weights_set_diagonals(w, 0, to_dev(diag.reshape(-1, O.N)))
+    y, _ = B.ckks_ctpt_matmul(P, w, to_dev(x), baby, giant, conj_key=conj[0] if pair else None, flags=B.MATMUL_MERGED_GIANT)
+    got = to_host(y)
+    for b in (0, blocks // 2, blocks - 1):
+        want = O.ctpt_matmul(L, m, G, blocks, N1, N2, diag, None, 0, x, keys[0], keys[1], b_first=b, b_count=1,
+                             conj_key=keys[2][0] if pair else None, merged=True)
+        assert (got[b] == want[b]).all(), b
