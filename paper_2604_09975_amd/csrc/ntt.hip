@@ -101,11 +101,13 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_pass_kernel(u64 *__restrict__
 // i.e. 16 >> LOGR columns, so that short rows keep as many loads in flight per wavefront as long ones), 0 = pass B (12
 // stages in a 4096 tile)
 // KIND: the kernel serves the rows whose prime is below 2^50 (FP_ROWS: fp64 butterflies), the others (INT_ROWS: integer
-// butterflies), rows of the other kind returning at once, or both.  One kernel for both kinds needs the union of the two
-// register budgets (130 registers, 3 waves per SIMD in pass B, against 112 to 124 and 4 waves for the separate ones), so
-// large launches go out separately; a launch that does not fill the chip (BOTH_MAX workgroups) is bound by the latency of
-// one workgroup, and two of them one after the other take twice that (the digits of one ciphertext at level 17 of 24 + 8
-// primes: 17 + 25 us; a whole rotation 182 us with two launches, 166 us with one).
+// butterflies), rows of the other kind returning at once, or both.  A launch that does not fill the chip (BOTH_MAX
+// workgroups) is bound by the latency of one workgroup, and two of them one after the other take twice that (the digits of
+// one ciphertext at level 17 of 24 + 8 primes: 17 + 25 us; a whole rotation 182 us with two launches, 166 us with one).  The
+// line stands where one kernel with the union of the two register budgets lost a wavefront per SIMD in pass B (130
+// registers, against 112 to 124).  As pass B is now (72 and 92 registers, against 66 to 90) one launch is no slower above it
+// either: mixed rows by two launches and by one, forward, inverse, us: 4096 workgroups at 2^16 123 / 109, 130 / 114, 2560 at
+// 2^15 94 / 73, 98 / 74, 2080 at 2^12 77 / 50, 82 / 51 (the line has not been moved).
 constexpr int INT_ROWS = 0, FP_ROWS = 1, BOTH_ROWS = 2;
 // + STREAMED: residues go past the caches' replacement order (arrays above STREAM_BYTES): a pass uses each once, and the
 // twiddles, as many bytes as a tile and shared by the rows of a limb, stay in L2.  64 x 24 rows at 2^16: tile pass 409 ->

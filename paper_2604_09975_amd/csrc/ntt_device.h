@@ -16,9 +16,11 @@ constexpr u32 NTT_THREADS = 256;
 template <u32 RL>
 struct Tile {
     static constexpr u32 R = 1u << RL, THREADS = 4096u >> RL, WORDS = 4096 + (4096u >> RL), ROUNDS = 12 / RL;
-    // WAVE: outside the pass's first round (forward: after it, inverse: before it) a wavefront touches 64 R consecutive
-    // elements of its own only
+    // WAVE: in the rounds whose residues lie at most 64 apart (all but the first at RL = 3, all but the first two at RL = 2), and
+    // so at the pass's LDS end, a wavefront touches 64 R consecutive elements of its own only.  The exchanges among rounds
+    // with more between their residues are the workgroup's (Round::BEHIND, Round::FRONT).
     static constexpr bool WAVE = RL < 4;
+    static_assert(12 % RL == 0 && (!WAVE || (4096u >> (RL * ROUNDS) << RL) <= 64 * R), "the last round is a wavefront's own");
     static __device__ __forceinline__ u32 slot(u32 i) { return i + (i >> RL); }
     // the i-th single element and the i-th pair of elements of a thread at the pass's LDS end
     static __device__ __forceinline__ u32 one(u32 tid, u32 i) {
@@ -31,12 +33,19 @@ struct Tile {
 
 // A launch of few workgroups lasts as long as one of them, and with 256 threads that is one wavefront per SIMD waiting for
 // its operands, then for each round's twiddles and exchange.  With 1024 threads four wavefronts share the wait, every load
-// of the operands is on its way at once, and the operands of a key switch's last pass arrive during its transform.  512
-// workgroups of 1024 threads are as many as the chip holds at a time.  us with 256 threads, with wide tiles up to 512 and up
-// to 1024 workgroups: ip_intt_kernel of 7 switches at 2^12 (14 workgroups) 19.3 -> 11.5; whole calls: toy projection at 2^12
-// 145 / 112 / 112, product and rescale at 2^15 (12 + 4 primes) 130 / 104 / 104, one rotation at 2^16, level 17 (544 and 928
-// workgroups in two of its kernels) 154 / 137 / 143, 24 switches and 12 rescales at 2^14 (960 in one) 165 / 146 / 155.  512
-// threads with 8 residues: 113, 105, 140, 151.
+// of the operands is on its way at once, and the operands of a key switch's last pass arrive during its transform.
+// 512 workgroups of 1024 threads are two per CU, which is what runs at a time of the kernels of up to 64 registers (the
+// transforms, gather_intt, the rescales).  us with 256 threads, with wide tiles up to 512 and up to 1024 workgroups:
+// ip_intt_kernel of 7 switches at 2^12 (14 workgroups) 19.3 -> 11.5; whole calls: toy projection at 2^12 145 / 112 / 112,
+// product and rescale at 2^15 (12 + 4 primes) 130 / 104 / 104, one rotation at 2^16, level 17 (544 and 928 workgroups in two of
+// its kernels) 154 / 137 / 143, 24 switches and 12 rescales at 2^14 (960 in one) 165 / 146 / 155.  512 threads with 8
+// residues: 113, 105, 140, 151.
+// ip_intt_kernel (82 registers) and passb_final_kernel (128) run one such workgroup per CU, so from 257 on there are two
+// rounds of them.  The first is the faster one all the same: calls of 320 / 480 / 512 workgroups in it (five switches at 2^15,
+// 30 at 2^14, two at 2^16) 83.7 / 127.0 / 87.3 us, by 256 threads from 257 on 87.6 / 133.4 / 90.1.  The second is not always,
+// 0.5 to 2.9 % of a call either way: one rotation at 2^16, levels 9 / 12 / 16 (288 / 384 / 512 in it) 91.6 / 93.2 / 96.6, by 256
+// threads 90.0 / 92.4 / 95.5, three at 2^15, level 6 (288) 70.1 and 68.0; two at 2^16, level 8 (512) 87.3 and 87.9, fifteen at
+// 2^14, level 4 (480) 69.6 and 71.7.
 constexpr u32 WIDE_RL = 2;
 inline bool wide_tiles(u64 workgroups) { return workgroups <= 512; }
 inline u32 tile_threads(bool wide) { return wide ? 1024 : 256; }
