@@ -1462,19 +1462,24 @@ static u32 build_pack(const SwitchItem *items, u32 n, ItemPack &pack) {
 //     851 / 821, 384 (2^15, 3, 3) 1033 / 988, 512 (2^14, 16, 3) 1606 / 1109, 544 (2^14, 17, 3) 1720 / 1171;
 //   more digits, of few ciphertexts: longer chains, beside a separate kernel that reads a key once for three ciphertexts: 320
 //     (2^16, 2, 4) 1074 / 1157, 336 (2^14, 4, 6) 1512 / 1564, 480 (2^16, 3, 4) 1449 / 1328; of more: 336 (2^15, 7, 5) 1426 / 1368;
-//   ciphertext primes from 2^50 up: the transforms of the chain take twice as long: 384 (2^15, 3, 3) 1619 / 1692, 512 (2^15, 4,
-//     3) 2083 / 1973, 576 (2^14, 9, 5; the second round nearly empty) 3438 / 3576, 640 (2^14, 10, 5) 3836 / 3813; two digits:
-//     352 (2^12, 32, 2) 1271 / 1176.
+//   ciphertext primes from 2^50 up: the transforms of the chain take twice as long, and a round nearly empty, of two per CU on
+//     the XCD with most units, costs more than the fusion gives: 384 (2^15, 3, 3) 1619 / 1692, 440 (2^14, 22, 4; two rounds on
+//     half of the XCDs) 2393 / 2612, 512 (2^15, 4, 3) 2083 / 1973, 576 (2^14, 9, 5) 3438 / 3576, 640 (2^14, 20, 3) 2728 / 2600,
+//     792 (2^14, 9, 5) 4517 / 4646, 896 (2^14, 14, 5) 5211 / 5006, 1160 (2^14, 29, 4) 5510 / 5200; two digits: 352 (2^12, 32, 2)
+//     1271 / 1176.
 // More rows of digits than one row map describes: their own tile passes are a launch per digit and ciphertext (2^14, 11
 // ciphertexts, 12 digits: 19130 / 3783).
 bool merged_from_half(const ckks_params *p, u32 level, u32 n) {
-    const u32 Wl = level + p->K, beta = (level + p->alpha - 1) / p->alpha;
-    const u64 workgroups = (u64)(p->N >> 12) * Wl * n;
+    const u32 Wl = level + p->K, beta = (level + p->alpha - 1) / p->alpha, units = (p->N >> 12) * Wl;
+    const u32 workgroups = units * n;                            // at most 2^5 * 64 * 32
     if (!fast_ring(p) || workgroups < 320) return false;
     if (beta * Wl > MAX_ROW_IDS) return true;
     u32 n_int = 0;
     for (u32 i = 0; i < level; ++i) n_int += (p->mod[i] >> 50) != 0;
-    if (2 * n_int > level && beta > 2) return workgroups >= 640 || (workgroups >= 448 && workgroups <= 512);
+    if (2 * n_int > level && beta > 2) {
+        const u32 rounds = ((units + 7) / 8 * n + 63) / 64;
+        return workgroups >= (beta == 3 ? 640u : 1152u) || workgroups >= 448 * rounds;
+    }
     return beta < 4 || n > 4 || workgroups >= 384;
 }
 

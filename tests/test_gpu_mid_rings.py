@@ -48,10 +48,12 @@ def test_projection_with_fused_rescale(logN, m, C, N1):
                           (15, 4, 8, 4, 4, 50, 60, 4, 4), (15, 4, 7, 4, 4, 50, 60, 4, 4),       # four digits of four: 384 and 352
                           (12, 6, 8, 3, 6, 52, 60, 32, 4), (12, 6, 8, 3, 6, 52, 60, 31, 4),     # three digits, integer rows: 448 and 434,
                           (13, 6, 8, 3, 6, 52, 60, 19, 4), (13, 6, 8, 3, 6, 52, 60, 23, 4),     # 532 and 644
+                          (14, 8, 4, 4, 8, 52, 60, 16, 4), (14, 8, 4, 4, 8, 52, 60, 24, 4),     # four digits, integer rows: 768 and 1152
                           (12, 12, 1, 12, 12, 50, 60, 25, 4)])                                  # 156 rows of digits
 def test_merged_giant_step_on_either_side_of_the_fused_tile_pass(logN, L, K, dnum, level, qbits, pbits, blocks, N1):
     """From 320 workgroups on the giant step's digits are transformed where their products are taken, with more than three
-    digits of few ciphertexts from 384 on, with three and more on integer rows from 448 to 512 and from 640 on."""
+    digits of few ciphertexts from 384 on, with three and more on integer rows where rounds of 512 are 7/8 full and above 640
+    (three digits) or 1152."""
     O = helpers.small_oracle(logN, L=L, K=K, dnum=dnum, qbits=qbits, pbits=pbits)
     _, P = make_pair(O)
     r = W.rng(logN + blocks)
