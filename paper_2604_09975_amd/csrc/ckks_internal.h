@@ -31,7 +31,8 @@ struct LimbIds {
 struct ModFp {
     double q, u;           // q and its rounded reciprocal
     double ninv, ninv_w;   // N^-1 and N^-1 * psi^-(N/2) as plain integers
-    u32 ok, pad;           // 1 if q < 2^50 (the FMA butterflies apply)
+    u32 ok;                // 1 if q < 2^50 (the FMA butterflies apply)
+    u32 pm;                // 1 if q = 2^b - c, 51 <= b <= 60, c < 2^(b-35) (the folding integer butterflies apply)
 };
 
 // Half-open device ranges [a, a + na) and [b, b + nb) of 64-bit words share a word.
@@ -85,8 +86,9 @@ struct ckks_params {
     ckks::u64 *d_ninv = nullptr;       // [W][2]: N^-1 and N^-1 * psi^-(N/2), Montgomery form
     ckks::ModFp *d_modf = nullptr;     // [W]
     ckks::u64 *d_ninv_dn = nullptr;    // like d_ninv, special limbs scaled by (P/p_k)^-1
-    // the same constants for the lazy integer butterflies of the two-pass kernels (N >= 2^12): plain values paired
-    // with their quotients floor(w * 2^64 / q); rows of limbs below 2^50 (fp64 butterflies) are left zero
+    // the same constants for the integer butterflies of the two-pass kernels (N >= 2^12): plain values paired with their
+    // quotients floor(w * 2^64 / q), or on primes that fold (ModFp::pm) w and 2^32 w mod q in signed halves (TwPm); rows of
+    // limbs below 2^50 (fp64 butterflies) are left zero
     ckks::u64 *d_tws_fwd = nullptr;    // [W][N][2]
     ckks::u64 *d_tws_inv = nullptr;    // [W][N][2]
     ckks::u64 *d_ninvs = nullptr;      // [W][4]

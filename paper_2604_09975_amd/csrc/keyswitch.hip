@@ -97,11 +97,7 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void gather_intt_kernel(PtrPack 
     u64 *out = tmp + ((size_t)blockIdx.y << logN);
     auto load = [&](u32 idx) { return in[idx]; };
     auto store = [&](u32 idx, u64 v) { out[idx] = v; };
-    const ModFp mf = modf[i];
-    if (mf.ok)
-        pass_b_body<true, RL>(make_field_fp(mf, twf, i, logN), logN, lds, load, store);
-    else
-        pass_b_body<true, RL>(make_field_int(mods, tw, ninv, i, logN), logN, lds, load, store);
+    with_field(modf[i], mods, tw, twf, ninv, i, logN, [&](const auto &f) { pass_b_body<true, RL>(f, logN, lds, load, store); });
 }
 
 // Per ciphertext r and digit j: y_i = c_i * (Q_D/q_i)^-1 mod q_i for the limbs of the digit, then for
@@ -249,14 +245,18 @@ __device__ __forceinline__ double mid_convert(const u32 (&yp)[KM][2], const u32 
 
 // Decomposition between the two tile passes at N = 2^(12+LOGR), one kernel instead of four.  The last LOGR stages of the
 // inverse transform of c1, the base conversion of every digit (ModUp) and the first LOGR stages of the forward transform
-// of the extended rows all work on columns (residues 4096 apart); a workgroup owns a tile of 512 coefficients, 512 >> LOGR
+// of the extended rows all work on columns (residues 4096 apart); a workgroup owns a tile of 1024 coefficients, 1024 >> LOGR
 // columns of 2^LOGR rows, of one digit of one ciphertext:
-//   1. group a of 32 threads: the columns of limb lo + a of the digit in registers, last inverse round with
+//   1. wavefront a: the columns of limb lo + a of the digit in registers, last inverse round with
 //      N^-1 (Q_D/q_i)^-1 folded in -> y_a in LDS;
 //   2. every thread takes two coefficients of the tile, both at once for each target of a group of UP_TG (a target's factors
 //      arrive once for both): exact sums of 25-bit pieces of y, onto the ciphertext primes by mid_convert, onto the special
 //      primes with factors in 30-bit parts and one Montgomery reduction of the recombined 90-bit sum -> LDS;
-//   3. group t of 32 threads: the columns of target t from LDS, first forward round (fp64 or integer butterflies), out.
+//   3. wavefront t: the columns of target t from LDS, first forward round (fp64 or integer butterflies), out.
+// A wavefront per row has the row's twiddles, modulus and addresses in scalar registers: 124 vector registers for digits of
+// eight limbs, which two such workgroups per CU leave.  With 32 threads per row (tiles of 512 coefficients, 256 threads) it is
+// 148 and 186 registers with the quotient and the folding butterflies, two or three wavefronts per SIMD for four: 32
+// ciphertexts of 24 limbs 421 and 444 us, 365 now.
 // At N = 2^12 (LOGR = 0) the tile passes are whole transforms: a thread scales, converts and stores its own coefficients,
 // without LDS (through it, where 32 threads scale or store a whole limb, a bank of 6 switches at level 1 took 45.4 us, now 41.3).
 // c1_half [n][level][N]: c1 after the inverse tile pass; digits [n][beta][level+K][N]: rows of targets outside the
@@ -265,9 +265,15 @@ __device__ __forceinline__ double mid_convert(const u32 (&yp)[KM][2], const u32 
 // 2^60 (the launcher checks).  grid: x = column tile, y = digit, z = ciphertext.
 // With its counterpart moddown_mid_kernel, against separate column passes and conversions: a ciphertext product and rescale
 // at 2^15 (12 + 4 primes) 186 -> 159 us, a bank of 24 switches at 2^14 (level 5 of 6, 2 special primes) 257 -> 232 us.
-constexpr u32 MID_TILE = 512, UP_TG = 8;
+// MidTile: the workgroup and tile of these kernels (2^12: no tile in LDS, small workgroups).
+template <u32 LOGR>
+struct MidTile {
+    static constexpr u32 THREADS = LOGR ? 512 : 256, SIZE = 2 * THREADS, COLS = SIZE >> LOGR, PER = LOGR ? COLS / 64 : 0;
+};
+inline u32 mid_tile(const ckks_params *p) { return p->logN == 12 ? MidTile<0>::SIZE : MidTile<1>::SIZE; }
+constexpr u32 UP_TG = 8;
 template <u32 LOGR, u32 AM>
-__global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ c1_half, u64 *__restrict__ digits,
+__global__ __launch_bounds__(MidTile<LOGR>::THREADS, 4) void modup_mid_kernel(const u64 *__restrict__ c1_half, u64 *__restrict__ digits,
                                                         const ModConst *__restrict__ mods,
                                                         const ModFp *__restrict__ modf,
                                                         const ModFp *__restrict__ modf_up,
@@ -278,11 +284,12 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
                                                         const u32 *__restrict__ up_ft,
                                                         const u32 *__restrict__ up_mats, u32 level, u32 K, u32 L,
                                                         u32 alpha, u32 beta, u32 tsplit) {
-    constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, COLS = MID_TILE >> LOGR, PER = COLS / 32;
+    typedef MidTile<LOGR> MT;
+    constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, MID_TILE = MT::SIZE, COLS = MT::COLS, PER = MT::PER;
     static_assert(UP_TG == 8 && AM <= 8, "the target tiles reuse the 8 rows of source tiles");
     __shared__ u64 ylds[LOGR ? 8 * MID_TILE : 1];
-    u64 *wlds = ylds;               // the sources live in registers once step 2 has read them: the same 32 KiB
-    const u32 tid = threadIdx.x, lane = tid & 31, grp = tid / 32;   // grp < 8
+    u64 *wlds = ylds;               // the sources live in registers once step 2 has read them: the same 64 KiB
+    const u32 tid = threadIdx.x, lane = tid & 63, grp = __builtin_amdgcn_readfirstlane(tid / 64);   // grp < 8
     // tsplit > 1 (few ciphertexts): the groups of targets of a tile go to tsplit workgroups, each of which redoes
     // step 1, so that a lone decomposition still fills the chip
     const u32 tile = blockIdx.x % (N / MID_TILE), tpart = blockIdx.x / (N / MID_TILE);
@@ -301,19 +308,19 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
                 const FieldFp f = make_field_fp(modf_up[i], twf_inv, i, logN);
 #pragma unroll
                 for (u32 e = 0; e < 2; ++e)
-                    pass_a_body<true, 0>(f, c0 + e * 256 + tid, [&](u32 idx) { return src[idx]; },
-                                         [&](u32, u64 v) { yraw[e][a] = v; });
+                    pass_a_body<true, 0>(f, c0 + e * MT::THREADS + tid, [&](u32, u32 col) { return src[col]; },
+                                         [&](u32, u32, u64 v) { yraw[e][a] = v; });
             }
         }
     } else if (grp < nd) {
         const u32 i = lo + grp;
-        const u64 *src = c1_half + ((size_t)r * level + i) * N;
+        const RowBuf src(c1_half + ((size_t)r * level + i) * N, N);
         const FieldFp f = make_field_fp(modf_up[i], twf_inv, i, logN);
 #pragma unroll
         for (u32 c = 0; c < PER; ++c) {
-            const u32 col = lane + 32 * c;
-            auto load = [&](u32 idx) { return src[idx]; };
-            auto store = [&](u32 idx, u64 v) { ylds[grp * MID_TILE + (idx >> 12) * COLS + col] = v; };
+            const u32 col = lane + 64 * c;
+            auto load = [&](u32 at, u32) { return src.load(at + c0, col); };
+            auto store = [&](u32 at, u32, u64 v) { ylds[grp * MID_TILE + (at >> 12) * COLS + col] = v; };
             pass_a_body<true, LOGR>(f, c0 + col, load, store);
         }
     }
@@ -322,7 +329,7 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
 #pragma unroll
         for (u32 e = 0; e < 2; ++e)
 #pragma unroll
-            for (u32 a = 0; a < AM; ++a) yraw[e][a] = a < nd ? ylds[a * MID_TILE + e * 256 + tid] : 0;
+            for (u32 a = 0; a < AM; ++a) yraw[e][a] = a < nd ? ylds[a * MID_TILE + e * MT::THREADS + tid] : 0;
         __syncthreads();            // every thread has its y: the tile may be overwritten
     }
     u32 yp[2][AM][2];
@@ -369,9 +376,9 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
 #pragma unroll
             for (u32 e = 0; e < 2; ++e) {
                 if constexpr (LOGR == 0)
-                    dig[(size_t)t * N + c0 + e * 256 + tid] = res[e];
+                    dig[(size_t)t * N + c0 + e * MT::THREADS + tid] = res[e];
                 else
-                    wlds[tt * MID_TILE + e * 256 + tid] = res[e];
+                    wlds[tt * MID_TILE + e * MT::THREADS + tid] = res[e];
             }
         }
         if constexpr (LOGR == 0) continue;
@@ -379,11 +386,11 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
         if (u0 + grp < nt) {
             const u32 uu = u0 + grp, t = uu < lo ? uu : uu + nd;
             const u32 gl = t < level ? t : L + (t - level);
-            u64 *dst = dig + (size_t)t * N;
+            const RowBuf dst(dig + (size_t)t * N, N);
             const ModFp mf = modf[gl];
 #pragma unroll
             for (u32 c = 0; c < PER; ++c) {
-                const u32 col = lane + 32 * c;
+                const u32 col = lane + 64 * c;
                 if (mf.ok) {
                     const FieldFp ff = make_field_fp(mf, twf_fwd, gl, logN);
                     double v[R];
@@ -392,11 +399,12 @@ __global__ __launch_bounds__(256) void modup_mid_kernel(const u64 *__restrict__ 
                         v[jj] = __longlong_as_double((long long)wlds[grp * MID_TILE + jj * COLS + col]);
                     radix_fwd<LOGR>(ff, v, 0, 0);
 #pragma unroll
-                    for (u32 jj = 0; jj < R; ++jj) dst[jj * 4096 + c0 + col] = ff.out(v[jj]);
+                    for (u32 jj = 0; jj < R; ++jj) dst.store(jj * 4096 + c0, col, ff.out(v[jj]));
                 } else {
-                    auto load = [&](u32 idx) { return wlds[grp * MID_TILE + (idx >> 12) * COLS + col]; };
-                    auto store = [&](u32 idx, u64 v) { dst[idx] = v; };
-                    pass_a_body<false, LOGR>(make_field_int(mods, tws_fwd, ninvs, gl, logN), c0 + col, load, store);
+                    auto load = [&](u32 at, u32) { return wlds[grp * MID_TILE + (at >> 12) * COLS + col]; };
+                    auto store = [&](u32 at, u32, u64 v) { dst.store(at + c0, col, v); };
+                    with_int_field(mf, mods, tws_fwd, ninvs, gl, logN,
+                                   [&](const auto &f) { pass_a_body<false, LOGR>(f, c0 + col, load, store); });
                 }
             }
         }
@@ -764,6 +772,11 @@ __global__ __launch_bounds__(Tile<RL>::THREADS, 4) void merged_tile_kernel(Merge
         const FieldFp f = make_field_fp(mf, twf_fwd, gl, logN);
         go(f, (u64)0, [&](u64 a, double x, u64 k) { return add_mod(a, mont_mul(f.out(x), k, m), m.q); },
            [&](u64 x) { return canonical_double(x); }, [&](u64 &) {}, [&](u64 a) { return a; });
+    } else if (mf.pm) {
+        const FieldPm f = make_field_pm(mods, tw_fwd, ninv, gl, logN);
+        // x normalised, so x + q in (0, 2q)
+        go(f, (u64)0, [&](u64 a, int64_t x, u64 k) { return add_mod(a, mont_mul((u64)x + m.q, k, m), m.q); },
+           [&](u64 x) { return (int64_t)x; }, [&](u64 &) {}, [&](u64 a) { return a; });
     } else {
         const FieldInt f = make_field_int(mods, tw_fwd, ninv, gl, logN);
         // x as the butterflies leave it, below 4q <= 2^64: a product below q 2^64
@@ -867,13 +880,13 @@ __global__ __launch_bounds__(KS_THREADS) void moddown_conv_kernel(const u64 *__r
 
 // ModDown between the two tile passes at N = 2^(12+LOGR), one kernel instead of three.  The last LOGR stages of the
 // inverse transform of the special limbs, the base conversion P -> q_i and the first LOGR stages of the forward transform
-// of the correction w all work on columns (residues 4096 apart), so a workgroup that owns a tile of MID_TILE coefficients
-// (512 >> LOGR columns) can do all three without leaving the CU:
-//   1. group k of 32 threads: the columns of special limb k in registers, last inverse round (which folds in
+// of the correction w all work on columns (residues 4096 apart), so a workgroup that owns a tile of 1024 coefficients
+// (1024 >> LOGR columns) can do all three without leaving the CU:
+//   1. wavefront k: the columns of special limb k in registers, last inverse round (which folds in
 //      N^-1 (P/p_k)^-1) -> y_k in LDS;
 //   2. every thread: its two coefficients' y_k cut into 30-bit pieces, then for each group of
 //      MID_TG target limbs the exact sums of mid_convert -> w in LDS;
-//   3. group t of 32 threads: the columns of w_t from LDS, first forward round, out.
+//   3. wavefront t: the columns of w_t from LDS, first forward round, out.
 // At N = 2^12 (LOGR = 0) the tile passes are whole transforms and this is the conversion alone, without LDS.
 // y: rows (pc*ystride + yoff + k) hold the special limbs after the inverse tile pass; w [pc][level][N] receives the
 // correction ready for the forward tile pass.  Needs K <= 8, every target below 2^50 and every special prime below
@@ -890,7 +903,7 @@ constexpr u32 MID_TG = 8, MID_MAX_LEVEL = 32;
 // mod q_i): one forward transform per limb serves both the ModDown and the rescale, and the rows written are those of
 // the l-1 remaining limbs.  Exact modular arithmetic throughout: the same residues as ModDown followed by rescale.
 template <u32 LOGR, u32 KM, bool RESC>
-__global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict__ y, u64 *__restrict__ w,
+__global__ __launch_bounds__(MidTile<LOGR>::THREADS, 4) void moddown_mid_kernel(const u64 *__restrict__ y, u64 *__restrict__ w,
                                                           const ModConst *__restrict__ mods,
                                                           const ModFp *__restrict__ modf,
                                                           const ModFp *__restrict__ modf_dn,
@@ -901,11 +914,12 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
                                                           const u32 *__restrict__ dn_mats, u32 level, u32 K, u32 L,
                                                           u32 ystride, u32 yoff, const u64 *__restrict__ t_rows,
                                                           u32 tsplit, bool streamed) {
-    constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, COLS = MID_TILE >> LOGR, PER = COLS / 32;
+    typedef MidTile<LOGR> MT;
+    constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, MID_TILE = MT::SIZE, COLS = MT::COLS, PER = MT::PER;
     static_assert(MID_TG == 8 && KM <= 8, "the correction tiles reuse the 8 rows of special-limb tiles");
     __shared__ u64 ylds[LOGR ? 8 * MID_TILE : 1];
-    u64 *wlds = ylds;               // y lives in registers once step 2 has read it: the same 32 KiB
-    const u32 tid = threadIdx.x, lane = tid & 31, grp = tid / 32;   // grp < 8
+    u64 *wlds = ylds;               // y lives in registers once step 2 has read it: the same 64 KiB
+    const u32 tid = threadIdx.x, lane = tid & 63, grp = __builtin_amdgcn_readfirstlane(tid / 64);   // grp < 8
     // tsplit > 1 (few polynomials): the groups of targets go to tsplit workgroups, each of which redoes step 1
     const u32 c0 = blockIdx.x % (N / MID_TILE) * COLS, tpart = blockIdx.x / (N / MID_TILE);
     const u32 pc = blockIdx.y;
@@ -915,20 +929,18 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
         for (u32 k = 0; k < KM; ++k)
 #pragma unroll
             for (u32 e = 0; e < 2; ++e)                              // the tile pass was the whole transform, scaled
-                yraw[e][k] = k < K ? y[((size_t)pc * ystride + yoff + k) * N + c0 + e * 256 + tid] : 0;
+                yraw[e][k] = k < K ? y[((size_t)pc * ystride + yoff + k) * N + c0 + e * MT::THREADS + tid] : 0;
     } else if (grp < K) {
         const u32 gl = L + grp;
-        const u64 *src = y + ((size_t)pc * ystride + yoff + grp) * N;
+        const RowBuf src(y + ((size_t)pc * ystride + yoff + grp) * N, N);
         const ModFp mf = modf_dn[gl];
 #pragma unroll
         for (u32 c = 0; c < PER; ++c) {
-            const u32 col = lane + 32 * c;
-            auto load = [&](u32 idx) { return src[idx]; };
-            auto store = [&](u32 idx, u64 v) { ylds[grp * MID_TILE + (idx >> 12) * COLS + col] = v; };
-            if (mf.ok)
-                pass_a_body<true, LOGR>(make_field_fp(mf, twf_inv, gl, logN), c0 + col, load, store);
-            else
-                pass_a_body<true, LOGR>(make_field_int(mods, tw_inv, ninv_dn, gl, logN), c0 + col, load, store);
+            const u32 col = lane + 64 * c;
+            auto load = [&](u32 at, u32) { return src.load(at + c0, col); };
+            auto store = [&](u32 at, u32, u64 v) { ylds[grp * MID_TILE + (at >> 12) * COLS + col] = v; };
+            with_field(mf, mods, tw_inv, twf_inv, ninv_dn, gl, logN,
+                       [&](const auto &f) { pass_a_body<true, LOGR>(f, c0 + col, load, store); });
         }
     }
     if constexpr (LOGR != 0) {
@@ -937,7 +949,7 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
 #pragma unroll
         for (u32 e = 0; e < 2; ++e)
 #pragma unroll
-            for (u32 k = 0; k < KM; ++k) yraw[e][k] = k < K ? ylds[k * MID_TILE + e * 256 + tid] : 0;
+            for (u32 k = 0; k < KM; ++k) yraw[e][k] = k < K ? ylds[k * MID_TILE + e * MT::THREADS + tid] : 0;
         __syncthreads();            // every thread has its y: the tile may be overwritten
     }
     u32 yp[2][KM][2];
@@ -958,7 +970,7 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
 #pragma unroll
         for (u32 e = 0; e < 2; ++e) {
             const double wl = mid_convert<KM>(yp[e], dn_mats + (size_t)il * (KM * 4), ml.q, ml.u);
-            const u32 el = e * 256 + tid;
+            const u32 el = e * MT::THREADS + tid;
             const double t = fl.in(t_rows[(size_t)pc * N + el / COLS * 4096 + c0 + el % COLS]);
             double r = t - wl;
             fl.norm(r);
@@ -986,9 +998,9 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
                     v += ri - hi_;                                  // |.| < 2q + 2^32: the forward round normalises
                 }
                 if constexpr (LOGR == 0)
-                    w[((size_t)pc * level + i) * N + c0 + e * 256 + tid] = make_field_fp(modf[i], twf_fwd, i, logN).out(v);
+                    w[((size_t)pc * level + i) * N + c0 + e * MT::THREADS + tid] = make_field_fp(modf[i], twf_fwd, i, logN).out(v);
                 else
-                    wlds[t * MID_TILE + e * 256 + tid] = (u64)__double_as_longlong(v);
+                    wlds[t * MID_TILE + e * MT::THREADS + tid] = (u64)__double_as_longlong(v);
             }
         }
         if constexpr (LOGR == 0) continue;
@@ -996,10 +1008,10 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
         if (i0 + grp < n_out) {
             const u32 i = i0 + grp;
             const FieldFp ff = make_field_fp(modf[i], twf_fwd, i, logN);
-            u64 *dst = w + ((size_t)pc * level + i) * N;
+            const RowBuf dst(w + ((size_t)pc * level + i) * N, N);
 #pragma unroll
             for (u32 c = 0; c < PER; ++c) {
-                const u32 col = lane + 32 * c;
+                const u32 col = lane + 64 * c;
                 double v[R];
 #pragma unroll
                 for (u32 j = 0; j < R; ++j)
@@ -1009,10 +1021,10 @@ __global__ __launch_bounds__(256) void moddown_mid_kernel(const u64 *__restrict_
                 // rows there (passb_final_kernel of 24 switches 524 -> 510 us)
                 if (streamed) {
 #pragma unroll
-                    for (u32 j = 0; j < R; ++j) __builtin_nontemporal_store(ff.out(v[j]), dst + j * 4096 + c0 + col);
+                    for (u32 j = 0; j < R; ++j) dst.store<true>(j * 4096 + c0, col, ff.out(v[j]));
                 } else {
 #pragma unroll
-                    for (u32 j = 0; j < R; ++j) dst[j * 4096 + c0 + col] = ff.out(v[j]);
+                    for (u32 j = 0; j < R; ++j) dst.store(j * 4096 + c0, col, ff.out(v[j]));
                 }
             }
         }
@@ -1092,10 +1104,10 @@ static u32 target_split(u32 workgroups, u32 groups) { return std::max<u32>(1, st
 
 static void launch_moddown_mid(const ckks_params *p, const u64 *y, u64 *w, u32 n, u32 level, u32 ystride, u32 yoff,
                                hipStream_t stream, const u64 *t_rows = nullptr) {
-    const u32 tiles = p->N / MID_TILE;
+    const u32 tiles = p->N / mid_tile(p), threads = mid_tile(p) / 2;
     const u32 tsplit = target_split(tiles * n * 2, (level - (t_rows ? 1 : 0) + MID_TG - 1) / MID_TG);
     hipLaunchKernelGGL(t_rows ? moddown_mid_for<true>(p) : moddown_mid_for<false>(p), dim3(tiles * tsplit, n * 2),
-                       dim3(256), 0, stream, y, w, p->d_mod, p->d_modf, p->d_modf_dn, p->d_tws_inv, p->d_twf_inv,
+                       dim3(threads), 0, stream, y, w, p->d_mod, p->d_modf, p->d_modf_dn, p->d_tws_inv, p->d_twf_inv,
                        p->d_ninvs_dn, p->d_twf_fwd, p->d_dn_mats, level, p->K, p->L, ystride, yoff, t_rows, tsplit,
                        (size_t)n * 2 * level * p->N * sizeof(u64) > STREAM_BYTES);
 }
@@ -1208,11 +1220,8 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void ip_intt_kernel(ItemPack pac
             }
         }
     }
-    const ModFp mf = modf[gl];
-    if (mf.ok)
-        pass_b_inv_from_lds<RL>(make_field_fp(mf, twf_inv, gl, logN), logN, lds, store);
-    else
-        pass_b_inv_from_lds<RL>(make_field_int(mods, tw_inv, ninv, gl, logN), logN, lds, store);
+    with_field(modf[gl], mods, tw_inv, twf_inv, ninv, gl, logN,
+               [&](const auto &f) { pass_b_inv_from_lds<RL>(f, logN, lds, store); });
 }
 
 // Last pass of the forward transform of w fused with the rest of the key switch on limb q_i:
@@ -1271,11 +1280,14 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void passb_final_kernel(ItemPack
             if (RL == 4) ov[e] = accumulate ? load_dst(idx) : pair_t{0, 0};
         }
     };
-    if (RL < 4) load_operands(0);
-    if (mf.ok)   // the fp64 epilogue takes the transformed correction as doubles, |x| <= q/2
+    if (mf.ok) {   // the fp64 epilogue takes the transformed correction as doubles, |x| <= q/2
+        if (RL < 4) load_operands(0);
         pass_b_fwd_to_lds<true, RL>(make_field_fp(mf, twf_fwd, i, logN), logN, lds, load);
-    else
-        pass_b_fwd_to_lds<false, RL>(make_field_int(mods, tw_fwd, ninv, i, logN), logN, lds, load);
+    } else {       // the integer transforms have no registers left for them
+        with_int_field(mf, mods, tw_fwd, ninv, i, logN,
+                       [&](const auto &f) { pass_b_fwd_to_lds<false, RL>(f, logN, lds, load); });
+        if (RL < 4) load_operands(0);
+    }
     for (u32 i0 = 0; i0 < TL::R / 2; i0 += EPP) {
         if (RL == 4) load_operands(i0);
 #pragma unroll
@@ -1394,12 +1406,12 @@ int decompose(ckks_params *p, const u64 *const *c1, u32 n, u32 level, u64 *d_dig
         p->limb_ntts += (u64)n * level;
         if (p->logN <= 16 && all_fp && sp60 && alpha <= 8 && K <= 8) {
             // the column passes of both transforms ride in the base conversion: c1 read once, digits written once
-            const u32 tgroups = (Wl - std::min(alpha, level) + UP_TG - 1) / UP_TG, tiles = N / MID_TILE;
+            const u32 tgroups = (Wl - std::min(alpha, level) + UP_TG - 1) / UP_TG, tiles = N / mid_tile(p);
             // all target groups apart below 1024 workgroups: one rotation at 2^16, level 24 / 17 / 9, two at level 24, a product
             // and rescale at 2^16 and 2^15 141.3 / 127.6 / 91.4, 189.6, 194.9 and 97.0 us; never split 141.9 / 131.6 / 95.5,
             // 191.4, 196.0 and 100.2; with the line at 3072 142.4 / 128.7 / 91.5, 190.6, 196.5 and 97.1
             const u32 tsplit = n * beta * tiles < 1024 ? std::max<u32>(1, tgroups) : 1;
-            hipLaunchKernelGGL(modup_mid_for(p), dim3(tiles * tsplit, beta, n), dim3(256), 0, stream, d_tmp,
+            hipLaunchKernelGGL(modup_mid_for(p), dim3(tiles * tsplit, beta, n), dim3(mid_tile(p) / 2), 0, stream, d_tmp,
                                d_digits, p->d_mod, p->d_modf, lt->d_modf_up, p->d_twf_inv, p->d_twf_fwd, p->d_tws_fwd,
                                p->d_ninvs, lt->d_up_ft, lt->d_up_mats, level, K, L, alpha, beta, tsplit);
             CKKS_LAUNCH_CHECK("modup_mid_kernel");

@@ -50,6 +50,8 @@ __global__ __launch_bounds__(NTT_THREADS) void expand_pass_kernel(const int64_t 
     u64 *dst = out + ((size_t)blockIdx.y << logN);
     auto load = [&](u32 idx) { return reduce_signed(src[idx], m); };
     auto store = [&](u32 idx, u64 v) { dst[idx] = v; };
+    auto load_a = [&](u32 at, u32 col) { return reduce_signed((src + at)[col], m); };
+    auto store_a = [&](u32 at, u32 col, u64 v) { (dst + at)[col] = v; };
     auto go = [&](const auto &f) {
         if constexpr (LOGR == 0) {
             pass_b_body<false>(f, logN, lds, load, store);
@@ -57,13 +59,10 @@ __global__ __launch_bounds__(NTT_THREADS) void expand_pass_kernel(const int64_t 
             constexpr u32 COLS = LOGR < 4 ? 16u >> LOGR : 1;
 #pragma unroll
             for (u32 c = 0; c < COLS; ++c)
-                pass_a_body<false, LOGR>(f, (c * gridDim.x + blockIdx.x) * NTT_THREADS + threadIdx.x, load, store);
+                pass_a_body<false, LOGR>(f, (c * gridDim.x + blockIdx.x) * NTT_THREADS + threadIdx.x, load_a, store_a);
         }
     };
-    if (mf.ok)
-        go(make_field_fp(mf, twf, i, logN));
-    else
-        go(make_field_int(mods, tws, ninvs, i, logN));
+    with_field(mf, mods, tws, twf, ninvs, i, logN, go);
 }
 
 // rows [rows][N], row r modulo limb r % level: x <- x * c mod q (c canonical, any size)
@@ -667,10 +666,10 @@ __global__ __launch_bounds__(256) void rescale_mid_kernel(const u64 *__restrict_
 #pragma unroll
         for (u32 c = 0; c < PER; ++c) {
             const u32 col = lane + 32 * c;
-            auto load = [&](u32 idx) { return src[idx]; };
-            auto store = [&](u32 idx, u64 v) { lds[(idx >> 12) * COLS + col] = v; };
+            auto load = [&](u32 at, u32 c_) { return (src + at)[c_]; };
+            auto store = [&](u32 at, u32, u64 v) { lds[(at >> 12) * COLS + col] = v; };
             if (LOGR == 0)
-                store(0, load(c0 + col));
+                store(0, 0, load(0, c0 + col));
             else
                 pass_a_body<true, LOGR>(f, c0 + col, load, store);
         }
@@ -705,7 +704,7 @@ __global__ __launch_bounds__(256) void rescale_mid_kernel(const u64 *__restrict_
                     v[j] = __longlong_as_double((long long)lds[grp * RS_TILE + j * COLS + col]);
                 radix_fwd<LOGR>(ff, v, 0, 0);
 #pragma unroll
-                for (u32 j = 0; j < R; ++j) dst[j * 4096 + c0 + col] = ff.out(v[j]);
+                for (u32 j = 0; j < R; ++j) (dst + j * 4096 + c0)[col] = ff.out(v[j]);
             }
         }
         __syncthreads();

@@ -140,6 +140,9 @@ __global__ __launch_bounds__((KIND_NT & WIDE) != 0 ? Tile<WIDE_RL>::THREADS : NT
         else
             poly[idx] = v;
     };
+    // (addresses formed per row: with a scalar part the compiler takes 98 registers for 70 here)
+    auto load_a = [&](u32 at, u32 col) { return load(at + col); };
+    auto store_a = [&](u32 at, u32 col, u64 v) { store(at + col, v); };
     auto go = [&](const auto &f) {
         if constexpr (LOGR == 0) {
             pass_b_body<INV, RL>(f, logN, lds, load, store);
@@ -147,13 +150,13 @@ __global__ __launch_bounds__((KIND_NT & WIDE) != 0 ? Tile<WIDE_RL>::THREADS : NT
             constexpr u32 COLS = LOGR < 4 ? 16u >> LOGR : 1;     // columns of a thread
 #pragma unroll
             for (u32 c = 0; c < COLS; ++c)
-                pass_a_body<INV, LOGR>(f, (c * gridDim.x + blockIdx.x) * NTT_THREADS + threadIdx.x, load, store);
+                pass_a_body<INV, LOGR>(f, (c * gridDim.x + blockIdx.x) * NTT_THREADS + threadIdx.x, load_a, store_a);
         }
     };
     if (KIND == FP_ROWS || (KIND == BOTH_ROWS && mf.ok))
         go(make_field_fp(mf, twf, limb, logN));
     else
-        go(make_field_int(mods, tw, ninv, limb, logN));
+        with_int_field(mf, mods, tw, ninv, limb, logN, go);
 }
 
 template <bool INV, u32 LOGR>

@@ -1,6 +1,7 @@
 // Host side of a parameter set: validation of the modulus chain, roots of
 // unity, twiddle tables and base-conversion tables (all uploaded in Montgomery
 // form), and the private scratch arena.
+#include <cstdint>
 #include <cstring>
 #include <stdarg.h>
 #include <stdio.h>
@@ -107,6 +108,27 @@ static ModConst make_mod(u64 q) {
 static u64 to_mont(u64 x, const ModConst &m) { return hmul(x % m.q, m.one, m.q); }
 static u64 shoup(u64 w, u64 q) { return (u64)((((wide)w) << 64) / q); }   // floor(w * 2^64 / q), w < q
 
+// q = 2^b - c with 51 <= b <= 60 and 0 < c < 2^(b-35): products fold at 2^b (FieldPm)
+static bool folds(u64 q) {
+    const u32 b = 64 - (u32)__builtin_clzll(q);
+    return b > 50 && b <= 60 && (((u64)1 << b) - q) >> (b - 35) == 0;
+}
+// w mod q as signed halves of 32 bits, w = hi 2^s + lo with |lo| <= 2^(s-1), s = b - 32
+static u64 fold_halves(u64 w, u64 q) {
+    const u32 s = 32 - (u32)__builtin_clzll(q), sh = 64 - s;
+    int64_t z = w > q / 2 ? (int64_t)(w - q) : (int64_t)w, lo = (int64_t)((u64)z << sh) >> sh;
+    if ((z - lo) >> s > INT32_MAX) {       // q/2, rounded up: its negative fits
+        z -= (int64_t)q;
+        lo = (int64_t)((u64)z << sh) >> sh;
+    }
+    return (u64)(u32)lo | (u64)(u32)((z - lo) >> s) << 32;
+}
+// the two words of a constant factor w < q in the integer butterflies
+static void int_factor(u64 w, u64 q, u64 *out) {
+    out[0] = folds(q) ? fold_halves(w, q) : w;
+    out[1] = folds(q) ? fold_halves(hmul(w, (u64)1 << 32, q), q) : shoup(w, q);
+}
+
 template <typename T>
 static int upload(T **dst, const std::vector<T> &src) {
     *dst = nullptr;
@@ -197,7 +219,7 @@ int ckks_params::build_level_tables(u32 level) {
         f.ninv = (double)(logN == 12 ? invp : hmul(hninv[2 * i], invp, qi));
         f.ninv_w = (double)hmul(hninv[2 * i + 1], invp, qi);
         f.ok = (qi >> 50) == 0;
-        f.pad = 0;
+        f.pm = 0;
         modf_up[i] = f;
         const u32 dj = i / alpha, da = i - lo;
         if (da >= 8) continue;
@@ -358,7 +380,7 @@ int ckks_params_create(uint32_t logN, const uint64_t *q, uint32_t L, const uint6
         f.ninv = (double)ni;
         f.ninv_w = (double)hmul(ni, pw[2 * N - N / 2], m.q);
         f.ok = (m.q >> 50) == 0;
-        f.pad = 0;
+        f.pm = !f.ok && folds(m.q);
         modf[i] = f;
         if (f.ok)
             for (u32 idx = 1; idx < N; ++idx) {
@@ -370,18 +392,13 @@ int ckks_params_create(uint32_t logN, const uint64_t *q, uint32_t L, const uint6
             for (u32 idx = 1; idx < N; ++idx) {
                 u32 e = bitrev(idx, logN);
                 const size_t o = ((size_t)i * N + idx) * 2;
-                fwd_s[o] = pw[e];
-                fwd_s[o + 1] = shoup(pw[e], m.q);
-                inv_s[o] = pw[2 * N - e];
-                inv_s[o + 1] = shoup(pw[2 * N - e], m.q);
+                int_factor(pw[e], m.q, &fwd_s[o]);
+                int_factor(pw[2 * N - e], m.q, &inv_s[o]);
             }
     }
     std::vector<u64> ninvs((size_t)W * 4);
     for (u32 i = 0; i < W; ++i)
-        for (u32 z = 0; z < 2; ++z) {
-            ninvs[4 * i + 2 * z] = ninv_plain[2 * i + z];
-            ninvs[4 * i + 2 * z + 1] = shoup(ninv_plain[2 * i + z], mod[i]);
-        }
+        for (u32 z = 0; z < 2; ++z) int_factor(ninv_plain[2 * i + z], mod[i], &ninvs[4 * i + 2 * z]);
     P->hninv = ninv_plain;
     std::vector<u64> dn_inv(K), dn_mat((size_t)K * L), pinv(L), qlinv((size_t)L * L, 0);
     const u32 kpad = pad_pow2(K);
@@ -432,10 +449,8 @@ int ckks_params_create(uint32_t logN, const uint64_t *q, uint32_t L, const uint6
         u64 n0 = hmul(ninv_plain[2 * (L + k)], f, pk), n1 = hmul(ninv_plain[2 * (L + k) + 1], f, pk);
         ninv_dn[2 * (L + k)] = to_mont(n0, m);
         ninv_dn[2 * (L + k) + 1] = to_mont(n1, m);
-        ninvs_dn[4 * (L + k)] = n0;
-        ninvs_dn[4 * (L + k) + 1] = shoup(n0, pk);
-        ninvs_dn[4 * (L + k) + 2] = n1;
-        ninvs_dn[4 * (L + k) + 3] = shoup(n1, pk);
+        int_factor(n0, pk, &ninvs_dn[4 * (L + k)]);
+        int_factor(n1, pk, &ninvs_dn[4 * (L + k) + 2]);
         modf_dn[L + k].ninv = (double)n0;
         modf_dn[L + k].ninv_w = (double)n1;
     }
