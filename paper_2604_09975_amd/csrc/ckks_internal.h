@@ -67,7 +67,8 @@ struct LevelTables {
     ModFp *d_modf_up = nullptr;   // [level]: the limb's ModFp with (Q_D/q_i)^-1 folded into the inverse transform's N^-1
                                   // (N = 2^12: alone, the tile pass has applied N^-1)
     // AM = alpha rounded up to a power of two, zero padding behind the digit's limbs
-    u32 *d_up_mats = nullptr;     // [beta][K][AM][2][2]: (Q_D/q_i) 2^(25b) 2^64 mod p_k cut into two 30-bit parts
+    u32 *d_up_mats = nullptr;     // [beta][K][AM][2][2]: (Q_D/q_i) 2^(25b) 2^64 mod p_k cut into two 30-bit parts;
+                                  // without the 2^64 on primes that fold
     u32 *d_up_ft = nullptr;       // [beta][level+K][AM][2][2]: (Q_D/q_i) 2^(25b) mod q_t in two 25-bit halves, ciphertext-prime targets t
 };
 

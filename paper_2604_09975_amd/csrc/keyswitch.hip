@@ -355,8 +355,10 @@ __global__ __launch_bounds__(MidTile<LOGR>::THREADS, 4) void modup_mid_kernel(co
                 }
             } else {
                 // target among the special primes: sum_a sum_b y_ab F_ab, F_ab = F_a 2^64 2^(25b) mod p in two 30-bit parts
+                // (without the 2^64 on primes that fold, where the sum folds like a product does)
                 const u32 k = t - level;
                 const u32 *f = up_mats + ((size_t)j * K + k) * (AM * 4);
+                const bool pm = modf[L + k].pm;
 #pragma unroll
                 for (u32 e = 0; e < 2; ++e) {
                     u64 s0 = 0, s1 = 0;                              // 16 products of 55 bits each
@@ -367,6 +369,10 @@ __global__ __launch_bounds__(MidTile<LOGR>::THREADS, 4) void modup_mid_kernel(co
                             s0 += (u64)yp[e][a][b] * f[(a * 2 + b) * 2 + 0];
                             s1 += (u64)yp[e][a][b] * f[(a * 2 + b) * 2 + 1];
                         }
+                    if (pm) {
+                        res[e] = make_field_pm(mods, tws_fwd, ninvs, L + k, logN).fold30(s0, s1, LOGR == 0);
+                        continue;
+                    }
                     u128 acc{s0, 0};                                 // s0 + s1 2^30 < 2^90
                     acc_add(acc, u128{s1 << 30, s1 >> 34});
                     res[e] = redc(acc, mods[L + k]);                 // canonical: the factors carry 2^64
@@ -399,7 +405,7 @@ __global__ __launch_bounds__(MidTile<LOGR>::THREADS, 4) void modup_mid_kernel(co
                         v[jj] = __longlong_as_double((long long)wlds[grp * MID_TILE + jj * COLS + col]);
                     radix_fwd<LOGR>(ff, v, 0, 0);
 #pragma unroll
-                    for (u32 jj = 0; jj < R; ++jj) dst.store(jj * 4096 + c0, col, ff.out(v[jj]));
+                    for (u32 jj = 0; jj < R; ++jj) dst.store(jj * 4096 + c0, col, ff.half(v[jj]));
                 } else {
                     auto load = [&](u32 at, u32) { return wlds[grp * MID_TILE + (at >> 12) * COLS + col]; };
                     auto store = [&](u32 at, u32, u64 v) { dst.store(at + c0, col, v); };
@@ -1021,10 +1027,10 @@ __global__ __launch_bounds__(MidTile<LOGR>::THREADS, 4) void moddown_mid_kernel(
                 // rows there (passb_final_kernel of 24 switches 524 -> 510 us)
                 if (streamed) {
 #pragma unroll
-                    for (u32 j = 0; j < R; ++j) dst.store<true>(j * 4096 + c0, col, ff.out(v[j]));
+                    for (u32 j = 0; j < R; ++j) dst.store<true>(j * 4096 + c0, col, ff.half(v[j]));
                 } else {
 #pragma unroll
-                    for (u32 j = 0; j < R; ++j) dst.store(j * 4096 + c0, col, ff.out(v[j]));
+                    for (u32 j = 0; j < R; ++j) dst.store(j * 4096 + c0, col, ff.half(v[j]));
                 }
             }
         }

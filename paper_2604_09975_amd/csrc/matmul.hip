@@ -704,7 +704,7 @@ __global__ __launch_bounds__(256) void rescale_mid_kernel(const u64 *__restrict_
                     v[j] = __longlong_as_double((long long)lds[grp * RS_TILE + j * COLS + col]);
                 radix_fwd<LOGR>(ff, v, 0, 0);
 #pragma unroll
-                for (u32 j = 0; j < R; ++j) (dst + j * 4096 + c0)[col] = ff.out(v[j]);
+                for (u32 j = 0; j < R; ++j) (dst + j * 4096 + c0)[col] = LOGR == 0 ? ff.out(v[j]) : ff.half(v[j]);
             }
         }
         __syncthreads();

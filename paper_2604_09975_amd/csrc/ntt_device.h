@@ -87,6 +87,7 @@ struct FieldInt {
         return x;
     }
     __device__ __forceinline__ u64 bits(T x) const { return x; }
+    __device__ __forceinline__ u64 half(T x) const { return x; }
     __device__ __forceinline__ T from_bits(u64 x) const { return x; }
     template <bool U>
     __device__ __forceinline__ TwInt twid(u32 idx, u32 k) const {
@@ -143,7 +144,7 @@ struct FieldPm {
     static constexpr u32 NORMED = 129, INV_BASE = 264, LIMIT = 2022;
     static constexpr u32 product(u32 b) { return 201 + (9 * b + 255) / 256; }
     u64 q, q8;
-    int64_t r31, half;                      // 2^31 and -2^(b-1)
+    int64_t r31, mid;                       // 2^31 and -2^(b-1)
     int c;
     u32 s, p2s;                             // s and 2^s
     const int4 *tw;
@@ -157,6 +158,10 @@ struct FieldPm {
         return r >= q ? r - q : r;
     }
     __device__ __forceinline__ u64 bits(T x) const { return (u64)x; }
+    __device__ __forceinline__ u64 half(T x) const {
+        norm(x);
+        return (u64)x;
+    }
     __device__ __forceinline__ T from_bits(u64 x) const { return (T)x; }
     template <bool U>
     __device__ __forceinline__ TwPm<U> twid(u32 idx, u32 k) const {
@@ -180,16 +185,23 @@ struct FieldPm {
     "v_mad_i64_i32 %1, %2, %4, %8, %1\n\tv_mad_i64_i32 %0, %2, %4, %7, %0"
         if constexpr (U)
             asm(PM_PARTS : "=&v"(p0), "=&v"(p1), "=&s"(co)
-                : "v"(yl), "v"(yh), "s"(w.w0), "s"(w.w1), "s"(w.v0), "s"(w.v1), "v"(r31), "v"(half));
+                : "v"(yl), "v"(yh), "s"(w.w0), "s"(w.w1), "s"(w.v0), "s"(w.v1), "v"(r31), "v"(mid));
         else
             asm(PM_PARTS : "=&v"(p0), "=&v"(p1), "=&s"(co)
-                : "v"(yl), "v"(yh), "v"(w.w0), "v"(w.w1), "v"(w.v0), "v"(w.v1), "v"(r31), "v"(half));
+                : "v"(yl), "v"(yh), "v"(w.w0), "v"(w.w1), "v"(w.v0), "v"(w.v1), "v"(r31), "v"(mid));
 #undef PM_PARTS
         T r;
         asm("v_mad_u64_u32 %0, %1, %3, %5, %6\n\tv_mad_i64_i32 %0, %1, %2, %4, %0"
             : "=&v"(r), "=&s"(co)
             : "v"((int)(p1 >> 32)), "v"((u32)p1), "s"(c), "s"(p2s), "v"(p0));
         return r;
+    }
+    // lo + hi 2^30 for lo < 2^59, hi < 2^(b-1): normalised, or canonical
+    __device__ __forceinline__ u64 fold30(u64 lo, u64 hi, bool canonical) const {
+        const u32 sh = s + 2, top = (u32)(hi >> sh), low = (u32)hi & ((1u << sh) - 1);      // hi 2^30 = top 2^b + low 2^30
+        T x = (T)((u64)top * (u32)c + lo + ((u64)low << 30));                               // below 2^61
+        norm(x);
+        return canonical ? out(x) : (u64)x;
     }
     template <bool U>
     __device__ __forceinline__ void fwd(T &x, T &y, const TwPm<U> &w) const {
@@ -233,6 +245,7 @@ struct FieldFp {
         return (u64)__double_as_longlong(x + 4503599627370496.0) & 0x000fffffffffffffull;
     }
     __device__ __forceinline__ u64 bits(T x) const { return (u64)__double_as_longlong(x); }
+    __device__ __forceinline__ u64 half(T x) const { return (u64)__double_as_longlong(x); }
     __device__ __forceinline__ T from_bits(u64 x) const { return __longlong_as_double((long long)x); }
     template <bool U>
     __device__ __forceinline__ double twid(u32 idx, u32 k) const { return (tw + idx)[k]; }   // entry idx + k; k constant: wide loads
@@ -277,13 +290,14 @@ constexpr u32 radix_out(u32 in, u32 stages) {
     return in;
 }
 constexpr u32 CANONICAL = 256;
-template <u32 LOGR, u32 IN, class F, class Tw>
+// S0: stages since values were normalised
+template <u32 LOGR, u32 IN, u32 S0 = 0, class F, class Tw>
 __device__ __forceinline__ void radix_fwd_by(const F &f, typename F::T (&v)[1u << LOGR], Tw tw) {
     constexpr u32 R = 1u << LOGR;
     u32 bound = IN;
 #pragma unroll
     for (u32 t = 0; t < LOGR; ++t) {
-        bool norm = t % 4 == 0;
+        bool norm = (S0 + t) % 4 == 0;
         if constexpr (F::BOUNDED) {
             norm = bound + F::product(bound) > F::LIMIT;
             if (norm) bound = F::NORMED;
@@ -361,6 +375,10 @@ __device__ __forceinline__ void radix_inv(const F &f, typename F::T (&v)[1u << L
     radix_inv_by<LOGR, MORE>(f, v, [&](u32 t, u32 k) { return f.template twid<U>((1u << (s0 + t)) + (nb << t), k); }, last);
 }
 
+// Between the two passes of a transform (N above 2^12) a row holds the field's own values as the first pass leaves them,
+// half(): doubles of up to 4 q, lazy integers, normalised ones on primes that fold.  The second pass starts by normalising
+// doubles anyway; canonical residues there cost a conversion each way, ten instructions of the hundred of a tile pass.
+//
 // pass B: the last 12 stages act inside aligned runs of 4096 consecutive residues, one workgroup per run, in 12 / RL
 // rounds of RL stages with an LDS exchange between them.  In round r a thread holds 2^RL residues S = 4096 >> RL (r + 1)
 // apart, those of block tid / S from tid % S on:
@@ -407,7 +425,7 @@ __device__ __forceinline__ void round_fwd(const F &f, typename F::T (&v)[1u << R
                                           const Twids<RL, RD, F> &tw) {
     constexpr u32 IN = radix_out<F>(CANONICAL, RL * RD);
     if constexpr (RL == WIDE_RL)
-        radix_fwd_by<RL, IN>(f, v, [&](u32 t, u32 k) { return tw.w[(1u << t) - 1 + k]; });
+        radix_fwd_by<RL, IN, RL * RD>(f, v, [&](u32 t, u32 k) { return tw.w[(1u << t) - 1 + k]; });
     else
         radix_fwd<RL, Round<RL, RD>::UNIFORM, IN>(f, v, Round<RL, RD>::stage(logN), Round<RL, RD>::node(tile));
 }
@@ -446,7 +464,8 @@ __device__ __forceinline__ void fwd_rounds(const F &f, u32 logN, u32 tile, u64 *
     if constexpr (RD + 1 < TL::ROUNDS) fwd_rounds<RAW, RL, RD + 1>(f, logN, tile, lds, next);
 }
 
-// forward: load(idx) gives the canonical residue at index idx of the polynomial (first round's pattern: coalesced); on
+// forward: load(idx) gives the residue at index idx of the polynomial, as the first pass has left it (N = 2^12: canonical; first
+// round's pattern: coalesced); on
 // return the tile's transformed, canonical residues are in LDS, where a thread may read what Tile::one or Tile::pair give
 // it (RL = 4: the workgroup is synced).  RAW: the residues are
 // left in the field's own form instead (f.bits of a value brought back by f.norm: for the fp64 field a double with
@@ -459,8 +478,13 @@ __device__ __forceinline__ void pass_b_fwd_from_regs(const F &f, u32 logN, u64 *
     Twids<RL, 1, F> next;
     load_twids<RL, 0>(f, logN, tile, tw);
     typename F::T v[TL::R];
+    if (logN == 12) {
 #pragma unroll
-    for (u32 j = 0; j < TL::R; ++j) v[j] = f.in(raw[j]);
+        for (u32 j = 0; j < TL::R; ++j) v[j] = f.in(raw[j]);
+    } else {
+#pragma unroll
+        for (u32 j = 0; j < TL::R; ++j) v[j] = f.from_bits(raw[j]);
+    }
     load_twids<RL, 1>(f, logN, tile, next);
     round_fwd<RL, 0>(f, v, logN, tile, tw);
 #pragma unroll
@@ -501,7 +525,7 @@ __device__ __forceinline__ void inv_rounds(const F &f, u32 logN, u64 *lds, const
 
 // inverse: expects the tile's canonical residues in LDS, written in the pattern of Tile::one or Tile::pair (the exchange
 // itself is synced here);
-// store(idx, value) receives the canonical results in the first round's pattern (coalesced).  A tile that is the whole
+// store(idx, value) receives the results in the first round's pattern (coalesced), for the other pass to go on with.  A tile that is the whole
 // polynomial (N = 2^12) ends the transform in the last round, which folds in N^-1.
 template <u32 RL = 4, class F, class Store>
 __device__ __forceinline__ void pass_b_inv_from_lds(const F &f, u32 logN, u64 *lds, Store store) {
@@ -518,7 +542,7 @@ __device__ __forceinline__ void pass_b_inv_from_lds(const F &f, u32 logN, u64 *l
     for (u32 j = 0; j < TL::R; ++j) v[j] = f.from_bits(lds[RN::slot(j)]);
     round_inv<RL, 0>(f, v, logN, blockIdx.x, tw0, logN == 12);
 #pragma unroll
-    for (u32 j = 0; j < TL::R; ++j) store(base + RN::elem(j), f.out(v[j]));
+    for (u32 j = 0; j < TL::R; ++j) store(base + RN::elem(j), logN == 12 ? f.out(v[j]) : f.half(v[j]));
 }
 
 // Whole pass with coalesced stores (forward) / coalesced loads (inverse).
@@ -555,14 +579,15 @@ struct RowBuf {
 
 // pass A for N = 2^(12+LOGR): the first LOGR stages pair residues 4096 apart, so a thread that owns one of the 4096
 // columns holds its 2^LOGR rows in registers: no LDS, every access a run of consecutive residues.  col: the thread's
-// column; load(at, col) / store(at, col, value) see canonical residues at index at + col of the polynomial, at the same for
+// column; load(at, col) / store(at, col, value) see residues at index at + col of the polynomial, canonical on the
+// side of the coefficients, at the same for
 // all threads: a scalar address to which a thread adds one 32-bit offset (an address per row would take 32 registers).
 template <bool INV, u32 LOGR, class F, class Load, class Store>
 __device__ __forceinline__ void pass_a_body(const F &f, u32 col, Load load, Store store) {
     constexpr u32 R = 1u << LOGR;
     typename F::T v[R];
 #pragma unroll
-    for (u32 j = 0; j < R; ++j) v[j] = f.in(load(j * 4096, col));
+    for (u32 j = 0; j < R; ++j) v[j] = INV && LOGR != 0 ? f.from_bits(load(j * 4096, col)) : f.in(load(j * 4096, col));
     if constexpr (INV && LOGR == 0)
         v[0] = f.mul(v[0], f.scale());                              // N = 2^12: no stage is left, the scaling is
     else if constexpr (INV)
@@ -570,7 +595,7 @@ __device__ __forceinline__ void pass_a_body(const F &f, u32 col, Load load, Stor
     else
         radix_fwd<LOGR>(f, v, 0, 0);
 #pragma unroll
-    for (u32 j = 0; j < R; ++j) store(j * 4096, col, f.out(v[j]));
+    for (u32 j = 0; j < R; ++j) store(j * 4096, col, INV || LOGR == 0 ? f.out(v[j]) : f.half(v[j]));
 }
 
 // Field objects for limb `limb` from the parameter tables.
@@ -597,8 +622,8 @@ __device__ __forceinline__ FieldPm make_field_pm(const ModConst *mods, const u64
     f.p2s = 1u << f.s;
     f.c = (int)(((u64)1 << b) - f.q);
     f.r31 = (int64_t)1 << 31;
-    f.half = -((int64_t)1 << (b - 1));
-    asm("" : "+v"(f.r31), "+v"(f.half));            // kept in vector registers: an instruction reads one scalar operand
+    f.mid = -((int64_t)1 << (b - 1));
+    asm("" : "+v"(f.r31), "+v"(f.mid));             // kept in vector registers: an instruction reads one scalar operand
     f.tw = reinterpret_cast<const int4 *>(tws) + ((size_t)limb << logN);
     f.n0 = pm_words(ninvs + 4 * limb);
     f.n1 = pm_words(ninvs + 4 * limb + 2);
