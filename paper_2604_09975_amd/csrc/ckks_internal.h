@@ -65,7 +65,6 @@ struct LevelTables {
     u64 *d_up_matf = nullptr;  // the same factors as doubles (bit patterns), for the conversions done in fp64
     // for the fused decomposition kernel (N = 2^12 .. 2^16, every active prime below 2^50):
     ModFp *d_modf_up = nullptr;   // [level]: the limb's ModFp with (Q_D/q_i)^-1 folded into the inverse transform's N^-1
-                                  // (N = 2^12: alone, the tile pass has applied N^-1)
     // AM = alpha rounded up to a power of two, zero padding behind the digit's limbs
     u32 *d_up_mats = nullptr;     // [beta][K][AM][2][2]: (Q_D/q_i) 2^(25b) 2^64 mod p_k cut into two 30-bit parts;
                                   // without the 2^64 on primes that fold

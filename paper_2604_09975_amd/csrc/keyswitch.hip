@@ -224,6 +224,13 @@ __device__ __forceinline__ void mid_pieces(const u64 (&yraw)[KM], u32 (&yp)[KM][
     }
 }
 
+// hi 2^25 + lo mod q (below 2^50) as a double, at most q + 2^32; hi and lo below 2^60
+__device__ __forceinline__ double mid_reduce(u64 lo, u64 hi, double q, double u) {
+    const double t1 = fma((double)(u32)(hi >> 32), 33554432.0, (double)(u32)(lo >> 32)) * 4294967296.0;
+    const double t2 = (double)(u32)hi * 33554432.0;
+    return (fma(-rint(t1 * u), q, t1) + fma(-rint(t2 * u), q, t2)) + (double)(u32)lo;
+}
+
 // sum_k y_k F_k mod q (below 2^50) as a double, at most q + 2^32: the pieces (at most 30 bits) times the factors F_k 2^(BITS a)
 // mod q in 25-bit halves, 16 products of 55 bits.  The sums' words then become doubles: hi 2^25 + lo = (hh 2^25 + lh) 2^32 +
 // hl 2^25 + ll, the first two terms exact (52 and 32 significant bits) and reduced one by one.
@@ -238,9 +245,97 @@ __device__ __forceinline__ double mid_convert(const u32 (&yp)[KM][2], const u32 
             hi += (u64)yp[k][a] * f[(k * 2 + a) * 2 + 1];
         }
     }
-    const double t1 = fma((double)(u32)(hi >> 32), 33554432.0, (double)(u32)(lo >> 32)) * 4294967296.0;
-    const double t2 = (double)(u32)hi * 33554432.0;
-    return (fma(-rint(t1 * u), q, t1) + fma(-rint(t2 * u), q, t2)) + (double)(u32)lo;
+    return mid_reduce(lo, hi, q, u);
+}
+
+// The same sums at N = 2^12, where a tile pass is a whole transform and a base conversion needs no columns: the workgroup that
+// transforms a target row forms it, residue by residue of its first round, from the n rows of canonical y behind one another at
+// `rows` (four residues of four rows on their way together).  done(j, s0, s1): the two sums of the j-th residue, of BITS-bit
+// pieces; f: the target's factors, 4 words a source row.  Conversions as launches of their own took 3 to 4 us each, three in a
+// switch and rescale, and their rows a write and a read: the toy projection (2^12, two batches of switches) 110.5 -> 95.7 us.
+template <u32 RL, u32 BITS, class Done>
+__device__ __forceinline__ void tile_convert(const u64 *__restrict__ rows, u32 n, const u32 *__restrict__ f, Done done) {
+    constexpr u32 R = 1u << RL, G = 4;
+#pragma unroll
+    for (u32 j0 = 0; j0 < R; j0 += G) {
+        u64 s0[G], s1[G];
+#pragma unroll
+        for (u32 j = 0; j < G; ++j) s0[j] = s1[j] = 0;
+        for (u32 k0 = 0; k0 < n; k0 += 4) {
+            u64 y[4][G];
+#pragma unroll
+            for (u32 k = 0; k < 4; ++k)
+#pragma unroll
+                for (u32 j = 0; j < G; ++j) y[k][j] = k0 + k < n ? rows[(size_t)(k0 + k) * 4096 + Round<RL, 0>::elem(j0 + j)] : 0;
+#pragma unroll
+            for (u32 k = 0; k < 4; ++k) {
+                if (k0 + k >= n) break;
+                const u32 *fk = f + (k0 + k) * 4;
+#pragma unroll
+                for (u32 j = 0; j < G; ++j) {
+                    const u32 lo = (u32)y[k][j] & ((1u << BITS) - 1), hi = (u32)(y[k][j] >> BITS);
+                    s0[j] += (u64)lo * fk[0];
+                    s1[j] += (u64)lo * fk[1];
+                    s0[j] += (u64)hi * fk[2];
+                    s1[j] += (u64)hi * fk[3];
+                }
+            }
+        }
+#pragma unroll
+        for (u32 j = 0; j < G; ++j) done(j0 + j, s0[j], s1[j]);
+    }
+}
+
+// ModUp at N = 2^12: conversion and transform of a target row in one workgroup.  y [n][level][N]: canonical c1 (Q_D/q_i)^-1 in
+// the coefficient domain; digits as modup_mid_kernel's, transformed.  Needs what that kernel needs.
+// grid: x = row of the extended basis, y = digit, z = ciphertext
+template <u32 RL>
+__global__ __launch_bounds__(Tile<RL>::THREADS) void modup_tile_kernel(const u64 *__restrict__ y, u64 *__restrict__ digits,
+                                                                 const ModConst *__restrict__ mods,
+                                                                 const ModFp *__restrict__ modf,
+                                                                 const double *__restrict__ twf_fwd,
+                                                                 const u64 *__restrict__ tws_fwd,
+                                                                 const u64 *__restrict__ ninvs,
+                                                                 const u32 *__restrict__ up_ft,
+                                                                 const u32 *__restrict__ up_mats, u32 level, u32 K, u32 L,
+                                                                 u32 alpha, u32 am, u32 beta) {
+    typedef Tile<RL> TL;
+    __shared__ u64 lds[TL::WORDS];
+    const u32 t = blockIdx.x, j = blockIdx.y, r = blockIdx.z, Wl = level + K;
+    const u32 lo = j * alpha, nd = min(alpha, level - lo);
+    if (t >= lo && t < lo + nd) return;                              // the digit's own limbs
+    const u32 gl = t < level ? t : L + (t - level);
+    const u64 *src = y + ((size_t)r * level + lo) * 4096;
+    u64 *dst = digits + (((size_t)r * beta + j) * Wl + t) * 4096;
+    const ModFp mf = modf[gl];
+    u64 raw[TL::R];
+    auto go = [&](const auto &f) {
+        pass_b_fwd_from_regs<false, RL, true>(f, 12, lds, raw, 0);
+#pragma unroll
+        for (u32 i = 0; i < TL::R; ++i) dst[TL::one(threadIdx.x, i)] = lds[TL::slot(TL::one(threadIdx.x, i))];
+    };
+    if (t < level) {
+        tile_convert<RL, 25>(src, nd, up_ft + ((size_t)j * Wl + t) * (am * 4), [&](u32 i, u64 s0, u64 s1) {
+            raw[i] = (u64)__double_as_longlong(mid_reduce(s0, s1, mf.q, mf.u));
+        });
+        go(make_field_fp(mf, twf_fwd, gl, 12));
+        return;
+    }
+    const u32 *f = up_mats + ((size_t)j * K + (t - level)) * (am * 4);
+    if (mf.pm) {
+        const FieldPm fp = make_field_pm(mods, tws_fwd, ninvs, gl, 12);
+        tile_convert<RL, 25>(src, nd, f, [&](u32 i, u64 s0, u64 s1) { raw[i] = fp.fold30(s0, s1, false); });
+        go(fp);
+        return;
+    }
+    const ModConst m = mods[gl];
+    tile_convert<RL, 25>(src, nd, f, [&](u32 i, u64 s0, u64 s1) {
+        u128 acc{s0, 0};                                             // s0 + s1 2^30 < 2^90
+        acc_add(acc, u128{s1 << 30, s1 >> 34});
+        raw[i] = redc(acc, m);
+        if (mf.ok) raw[i] = (u64)__double_as_longlong(canonical_double(raw[i]));
+    });
+    with_field(mf, mods, tws_fwd, twf_fwd, ninvs, gl, 12, go);
 }
 
 // Decomposition between the two tile passes at N = 2^(12+LOGR), one kernel instead of four.  The last LOGR stages of the
@@ -257,8 +352,8 @@ __device__ __forceinline__ double mid_convert(const u32 (&yp)[KM][2], const u32 
 // eight limbs, which two such workgroups per CU leave.  With 32 threads per row (tiles of 512 coefficients, 256 threads) it is
 // 148 and 186 registers with the quotient and the folding butterflies, two or three wavefronts per SIMD for four: 32
 // ciphertexts of 24 limbs 421 and 444 us, 365 now.
-// At N = 2^12 (LOGR = 0) the tile passes are whole transforms: a thread scales, converts and stores its own coefficients,
-// without LDS (through it, where 32 threads scale or store a whole limb, a bank of 6 switches at level 1 took 45.4 us, now 41.3).
+// At N = 2^12 (LOGR = 0; for consumers that transform the digits themselves) the tile passes are whole transforms, the inverse
+// one carries the scaling, and a thread converts and stores its own coefficients, without LDS.
 // c1_half [n][level][N]: c1 after the inverse tile pass; digits [n][beta][level+K][N]: rows of targets outside the
 // digit, ready for the forward tile pass.  AM: the digit size alpha rounded up to a power of two; the factor tables are
 // padded with zeros to it.  Needs alpha, K <= 8, every active ciphertext prime below 2^50 and every special prime below
@@ -303,13 +398,9 @@ __global__ __launch_bounds__(MidTile<LOGR>::THREADS, 4) void modup_mid_kernel(co
         for (u32 a = 0; a < AM; ++a) {
             yraw[0][a] = yraw[1][a] = 0;
             if (a < nd) {
-                const u32 i = lo + a;
-                const u64 *src = c1_half + ((size_t)r * level + i) * N;
-                const FieldFp f = make_field_fp(modf_up[i], twf_inv, i, logN);
+                const u64 *src = c1_half + ((size_t)r * level + lo + a) * N + c0 + tid;
 #pragma unroll
-                for (u32 e = 0; e < 2; ++e)
-                    pass_a_body<true, 0>(f, c0 + e * MT::THREADS + tid, [&](u32, u32 col) { return src[col]; },
-                                         [&](u32, u32, u64 v) { yraw[e][a] = v; });
+                for (u32 e = 0; e < 2; ++e) yraw[e][a] = src[e * MT::THREADS];
             }
         }
     } else if (grp < nd) {
@@ -1234,8 +1325,11 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void ip_intt_kernel(ItemPack pac
 //   dst[comp][i] (+)= sum_j sigma_g(d_j)[q_i] * key_j[comp][q_i] - NTT(w)[i]  (+ sigma_g(c0)[i] if comp = 0)
 // (the keys and w carry the P^-1 of ModDown).
 // grid: x = tile of 4096, y = ((i*n + r)*2 + comp), neighbours share digit and key lines in L2 as above.
-template <bool KEY_NT, bool PAIR, u32 RL>
+// CONV (N = 2^12): w holds the K special rows of an (item, component) instead, scaled by (P/p_k)^-1, and the workgroup converts
+// its row of the correction from them itself (dn_mats: the factors, kpad source rows a target).
+template <bool KEY_NT, bool PAIR, u32 RL, bool CONV>
 __global__ __launch_bounds__(Tile<RL>::THREADS) void passb_final_kernel(ItemPack pack, const u64 *__restrict__ w,
+                                                                  const u32 *__restrict__ dn_mats, u32 kpad,
                                                                   const ModConst *__restrict__ mods,
                                                                   const ModFp *__restrict__ modf,
                                                                   const u64 *__restrict__ tw_fwd,
@@ -1286,7 +1380,13 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void passb_final_kernel(ItemPack
             if (RL == 4) ov[e] = accumulate ? load_dst(idx) : pair_t{0, 0};
         }
     };
-    if (mf.ok) {   // the fp64 epilogue takes the transformed correction as doubles, |x| <= q/2
+    if (CONV) {
+        u64 raw[TL::R];
+        tile_convert<RL, 30>(w + ((size_t)r * 2 + comp) * K * 4096, K, dn_mats + (size_t)i * (kpad * 4),
+                             [&](u32 j, u64 s0, u64 s1) { raw[j] = (u64)__double_as_longlong(mid_reduce(s0, s1, mf.q, mf.u)); });
+        if (RL < 4) load_operands(0);
+        pass_b_fwd_from_regs<true, RL, true>(make_field_fp(mf, twf_fwd, i, 12), 12, lds, raw, 0);
+    } else if (mf.ok) {   // the fp64 epilogue takes the transformed correction as doubles, |x| <= q/2
         if (RL < 4) load_operands(0);
         pass_b_fwd_to_lds<true, RL>(make_field_fp(mf, twf_fwd, i, logN), logN, lds, load);
     } else {       // the integer transforms have no registers left for them
@@ -1310,7 +1410,7 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void passb_final_kernel(ItemPack
             pair_t out;
 #pragma unroll
             for (u32 z = 0; z < 2; ++z) {
-                if (mf.ok) {
+                if (CONV || mf.ok) {
                     // primes below 2^50: exact fp64 sums, keys are balanced doubles
                     MacSum sum{MAC_H0, 0.0};
 #pragma unroll
@@ -1405,12 +1505,23 @@ int decompose(ckks_params *p, const u64 *const *c1, u32 n, u32 level, u64 *d_dig
     for (u32 k = 0; k < K; ++k) sp60 = sp60 && (p->mod[L + k] >> 60) == 0;
     if (fast_ring(p)) {
         const bool wide = wide_tiles((u64)(N >> 12) * n * level);
+        const bool mid = p->logN <= 16 && all_fp && sp60 && alpha <= 8 && K <= 8, whole = p->logN == 12;
         hipLaunchKernelGGL(wide ? gather_intt_kernel<WIDE_RL> : gather_intt_kernel<4>, dim3(N >> 12, n * level),
                            dim3(tile_threads(wide)), 0, stream, src, d_tmp,
-                           p->d_mod, p->d_modf, p->d_tws_inv, p->d_twf_inv, p->d_ninvs, level, p->logN);
+                           p->d_mod, mid && whole ? lt->d_modf_up : p->d_modf, p->d_tws_inv, p->d_twf_inv, p->d_ninvs, level,
+                           p->logN);
         CKKS_LAUNCH_CHECK("gather_intt_kernel");
         p->limb_ntts += (u64)n * level;
-        if (p->logN <= 16 && all_fp && sp60 && alpha <= 8 && K <= 8) {
+        if (mid && whole && !half) {
+            const bool wide_up = wide_tiles((u64)n * beta * Wl - (u64)n * level);
+            hipLaunchKernelGGL(wide_up ? modup_tile_kernel<WIDE_RL> : modup_tile_kernel<4>, dim3(Wl, beta, n),
+                               dim3(tile_threads(wide_up)), 0, stream, d_tmp, d_digits, p->d_mod, p->d_modf, p->d_twf_fwd,
+                               p->d_tws_fwd, p->d_ninvs, lt->d_up_ft, lt->d_up_mats, level, K, L, alpha, pad_pow2(alpha), beta);
+            CKKS_LAUNCH_CHECK("modup_tile_kernel");
+            p->limb_ntts += (u64)n * beta * Wl - (u64)n * level;
+            return CKKS_OK;
+        }
+        if (mid) {
             // the column passes of both transforms ride in the base conversion: c1 read once, digits written once
             const u32 tgroups = (Wl - std::min(alpha, level) + UP_TG - 1) / UP_TG, tiles = N / mid_tile(p);
             // all target groups apart below 1024 workgroups: one rotation at 2^16, level 24 / 17 / 9, two at level 24, a product
@@ -1628,6 +1739,17 @@ int moddown_rescale(ckks_params *p, u32 level, u64 *d_u, const u64 *const *z, u6
     return CKKS_OK;
 }
 
+typedef decltype(&passb_final_kernel<true, true, 4, false>) passb_t;
+template <bool CONV>
+static passb_t passb_for(bool own_keys, bool wide, bool pair) {
+    return own_keys ? (wide   ? passb_final_kernel<true, false, WIDE_RL, CONV>
+                       : pair ? passb_final_kernel<true, true, 4, CONV>
+                              : passb_final_kernel<true, false, 4, CONV>)
+                    : (wide   ? passb_final_kernel<false, false, WIDE_RL, CONV>
+                       : pair ? passb_final_kernel<false, true, 4, CONV>
+                              : passb_final_kernel<false, false, 4, CONV>);
+}
+
 // n <= ROT_BATCH key switches from ready digits.  d_work: switch_scratch_words(level, n).
 int switch_batch(ckks_params *p, u32 level, const SwitchItem *items, u32 n, u64 *d_work, hipStream_t stream) {
     if (n == 0) return CKKS_OK;
@@ -1665,7 +1787,11 @@ int switch_batch(ckks_params *p, u32 level, const SwitchItem *items, u32 n, u64 
         CKKS_LAUNCH_CHECK("ip_intt_kernel");
         p->limb_ntts += (u64)n * 2 * K;
         int rc;
-        if (moddown_mid_ok(p, level)) {
+        // at N = 2^12 the base conversion rides in the last kernel: a row of the correction needs no other's columns
+        const bool mid = moddown_mid_ok(p, level), conv = mid && whole;
+        if (conv) {
+            p->limb_ntts += (u64)n * 2 * level;
+        } else if (mid) {
             // column passes of the inverse transform (special limbs) and of the forward one (correction) inside the
             // base conversion: one kernel, y read once, w written once
             launch_moddown_mid(p, y, w, n, level, K, 0u, stream);
@@ -1686,14 +1812,9 @@ int switch_batch(ckks_params *p, u32 level, const SwitchItem *items, u32 n, u64 
         // at 2^16, level 24 (6144) 496 and 493 (calls as long as they were then; wide tiles by 8-byte ones).
         const bool pair = tiles * n * 2 * level > 768;
         const bool wide = wide_tiles(tiles * n * 2 * level);
-        const auto passb = own_keys ? (wide   ? passb_final_kernel<true, false, WIDE_RL>
-                                       : pair ? passb_final_kernel<true, true, 4>
-                                              : passb_final_kernel<true, false, 4>)
-                                    : (wide   ? passb_final_kernel<false, false, WIDE_RL>
-                                       : pair ? passb_final_kernel<false, true, 4>
-                                              : passb_final_kernel<false, false, 4>);
-        hipLaunchKernelGGL(passb, dim3(tiles, n * 2 * level),
-                           dim3(tile_threads(wide)), 0, stream, pack, w, p->d_mod, p->d_modf, p->d_tws_fwd, p->d_twf_fwd,
+        const auto passb = conv ? passb_for<true>(own_keys, wide, pair) : passb_for<false>(own_keys, wide, pair);
+        hipLaunchKernelGGL(passb, dim3(tiles, n * 2 * level), dim3(tile_threads(wide)), 0, stream, pack, conv ? y : w,
+                           p->d_dn_mats, pad_pow2(K), p->d_mod, p->d_modf, p->d_tws_fwd, p->d_twf_fwd,
                            p->d_ninvs, n, level, K, L, beta, p->alpha, p->logN);
         CKKS_LAUNCH_CHECK("passb_final_kernel");
         return CKKS_OK;

@@ -628,7 +628,7 @@ __global__ __launch_bounds__(EW_THREADS) void to_weight_form_kernel(u64 *data, c
 //                         q_i of every remaining limb and the column pass of its forward transform, on tiles of
 //                         512 coefficients as in moddown_mid_kernel;
 //   rescale_tile_kernel:  forward tile pass and (c - NTT(delta)) q_l^-1.
-// At N = 2^12 (LOGR = 0) the tile passes are whole transforms.
+// At N = 2^12 the tile passes are whole transforms, and the last kernel forms the rounding terms it transforms itself.
 constexpr u32 RS_TILE = 512;
 
 // grid: x = 4096-residue tiles, y = row
@@ -647,6 +647,7 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void rescale_intt_kernel(const u
 
 // grid: x = tiles of 512 coefficients, tsplit times, y = row; out rows [rows][level-1].  tsplit > 1 (few rows): the groups of
 // limbs of a tile go to that many workgroups, each of which redoes the dropped limb's column pass
+__device__ __forceinline__ double rounding_term(double rp, double hi, double q, double u) { return fma(-rint(rp * u), q, rp) - hi; }
 template <u32 LOGR>
 __global__ __launch_bounds__(256) void rescale_mid_kernel(const u64 *__restrict__ r, u64 *__restrict__ out,
                                                           const ModFp *__restrict__ modf,
@@ -668,10 +669,7 @@ __global__ __launch_bounds__(256) void rescale_mid_kernel(const u64 *__restrict_
             const u32 col = lane + 32 * c;
             auto load = [&](u32 at, u32 c_) { return (src + at)[c_]; };
             auto store = [&](u32 at, u32, u64 v) { lds[(at >> 12) * COLS + col] = v; };
-            if (LOGR == 0)
-                store(0, 0, load(0, c0 + col));
-            else
-                pass_a_body<true, LOGR>(f, c0 + col, load, store);
+            pass_a_body<true, LOGR>(f, c0 + col, load, store);
         }
     }
     __syncthreads();
@@ -688,7 +686,7 @@ __global__ __launch_bounds__(256) void rescale_mid_kernel(const u64 *__restrict_
             const double q = modf[i0 + t].q, u = modf[i0 + t].u, hi = fma(-rint(h * u), q, h);
 #pragma unroll
             for (u32 e = 0; e < 2; ++e)
-                lds[t * RS_TILE + e * 256 + tid] = (u64)__double_as_longlong(fma(-rint(rp[e] * u), q, rp[e]) - hi);
+                lds[t * RS_TILE + e * 256 + tid] = (u64)__double_as_longlong(rounding_term(rp[e], hi, q, u));
         }
         __syncthreads();
         if (i0 + grp < il) {
@@ -704,16 +702,18 @@ __global__ __launch_bounds__(256) void rescale_mid_kernel(const u64 *__restrict_
                     v[j] = __longlong_as_double((long long)lds[grp * RS_TILE + j * COLS + col]);
                 radix_fwd<LOGR>(ff, v, 0, 0);
 #pragma unroll
-                for (u32 j = 0; j < R; ++j) (dst + j * 4096 + c0)[col] = LOGR == 0 ? ff.out(v[j]) : ff.half(v[j]);
+                for (u32 j = 0; j < R; ++j) (dst + j * 4096 + c0)[col] = ff.half(v[j]);
             }
         }
         __syncthreads();
     }
 }
 
-// grid: x = 4096-residue tiles, y = limb, z = row; out holds delta after its column pass on entry
+// grid: x = 4096-residue tiles, y = limb, z = row; out holds delta after its column pass on entry (N = 2^12: r the dropped
+// limb's coefficients)
 template <u32 RL>
 __global__ __launch_bounds__(Tile<RL>::THREADS) void rescale_tile_kernel(const u64 *__restrict__ in, u64 *out,
+                                                                   const u64 *__restrict__ r,
                                                                    const ModFp *__restrict__ modf,
                                                                    const ModConst *__restrict__ mods,
                                                                    const double *__restrict__ twf_fwd,
@@ -729,8 +729,21 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void rescale_tile_kernel(const u
     vec_t x[TL::R / 2];
 #pragma unroll
     for (u32 e = 0; e < TL::R / 2; ++e) x[e] = *reinterpret_cast<const vec_t *>(src + base + TL::pair(tid, e));
-    auto load = [&](u32 idx) { return dst[idx]; };
-    pass_b_fwd_to_lds<true, RL>(f, logN, lds, load);
+    u64 raw[TL::R];
+    if (logN == 12) {
+        const ModFp ml = modf[level - 1];
+        const double h = (double)(mods[level - 1].q >> 1), hi = fma(-rint(h * f.u), f.q, h);
+#pragma unroll
+        for (u32 j = 0; j < TL::R; ++j) {
+            double rp = canonical_double(r[(size_t)row * 4096 + Round<RL, 0>::elem(j)]) + h;
+            if (rp >= ml.q) rp -= ml.q;
+            raw[j] = f.bits(rounding_term(rp, hi, f.q, f.u));
+        }
+    } else {
+#pragma unroll
+        for (u32 j = 0; j < TL::R; ++j) raw[j] = dst[base + Round<RL, 0>::elem(j)];
+    }
+    pass_b_fwd_from_regs<true, RL, true>(f, logN, lds, raw, blockIdx.x);
 #pragma unroll
     for (u32 e = 0; e < TL::R / 2; ++e) {
         const u32 loc = TL::pair(tid, e);
@@ -1542,18 +1555,19 @@ static int rescale_rows(ckks_params *P, const u64 *d_in, u32 level, u32 rows, u6
                            dim3(tile_threads(wide_in)), 0, stream, d_in, d_r, P->d_modf,
                            P->d_twf_inv, level, P->logN);
         CKKS_LAUNCH_CHECK("rescale_intt_kernel");
-        const auto mid = P->logN == 12 ? rescale_mid_kernel<0> : P->logN == 13 ? rescale_mid_kernel<1>
+        const auto mid = P->logN == 12 ? nullptr : P->logN == 13 ? rescale_mid_kernel<1>
                        : P->logN == 14 ? rescale_mid_kernel<2> : P->logN == 15 ? rescale_mid_kernel<3>
                                                                                : rescale_mid_kernel<4>;
         // as many workgroups as fill the chip, as for ModDown.  One ciphertext, never split / up to 512 / 768 / 1024 / 2048
         // workgroups, us: 2^16, level 24 37.2 / 34.9 / 33.7 / 33.6 / 33.3, level 12 28.5 and 27.7, 2^15, level 12 20.7 and 19.4;
         // two at 2^15 27.7 and 26.9, six 41.1 / 40.8 / 40.9 / 41.0 / 42.3, four at 2^16 84.5 / 84.7 / 84.3 / 84.4 / 86.5
         const u32 tsplit = std::max<u32>(1, std::min<u32>((level - 1 + 7) / 8, 768 / (N / RS_TILE * rows)));
-        hipLaunchKernelGGL(mid, dim3(N / RS_TILE * tsplit, rows), dim3(256), 0, stream, d_r, d_out, P->d_modf, P->d_mod,
+        if (mid)
+            hipLaunchKernelGGL(mid, dim3(N / RS_TILE * tsplit, rows), dim3(256), 0, stream, d_r, d_out, P->d_modf, P->d_mod,
                            P->d_twf_inv, P->d_twf_fwd, level, tsplit);
         CKKS_LAUNCH_CHECK("rescale_mid_kernel");
         hipLaunchKernelGGL(wide_out ? rescale_tile_kernel<WIDE_RL> : rescale_tile_kernel<4>, dim3(N >> 12, level - 1, rows),
-                           dim3(tile_threads(wide_out)), 0, stream, d_in, d_out,
+                           dim3(tile_threads(wide_out)), 0, stream, d_in, d_out, d_r,
                            P->d_modf, P->d_mod, P->d_twf_fwd, qlinv, level, P->logN);
         CKKS_LAUNCH_CHECK("rescale_tile_kernel");
         P->limb_ntts += (u64)rows * level;

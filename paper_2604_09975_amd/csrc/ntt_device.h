@@ -470,7 +470,8 @@ __device__ __forceinline__ void fwd_rounds(const F &f, u32 logN, u32 tile, u64 *
 // it (RL = 4: the workgroup is synced).  RAW: the residues are
 // left in the field's own form instead (f.bits of a value brought back by f.norm: for the fp64 field a double with
 // |x| <= q/2), for a caller that goes on computing in that field and would only convert them back.
-template <bool RAW = false, u32 RL = 4, class F>
+// FIELD: raw holds the field's own values whatever the ring.
+template <bool RAW = false, u32 RL = 4, bool FIELD = false, class F>
 __device__ __forceinline__ void pass_b_fwd_from_regs(const F &f, u32 logN, u64 *lds, const u64 (&raw)[1u << RL], u32 tile) {
     typedef Tile<RL> TL;
     typedef Round<RL, 0> RN;
@@ -478,7 +479,7 @@ __device__ __forceinline__ void pass_b_fwd_from_regs(const F &f, u32 logN, u64 *
     Twids<RL, 1, F> next;
     load_twids<RL, 0>(f, logN, tile, tw);
     typename F::T v[TL::R];
-    if (logN == 12) {
+    if (!FIELD && logN == 12) {
 #pragma unroll
         for (u32 j = 0; j < TL::R; ++j) v[j] = f.in(raw[j]);
     } else {

@@ -216,7 +216,7 @@ int ckks_params::build_level_tables(u32 level) {
         ModFp f;
         f.q = (double)qi;
         f.u = 1.0 / (double)qi;
-        f.ninv = (double)(logN == 12 ? invp : hmul(hninv[2 * i], invp, qi));
+        f.ninv = (double)hmul(hninv[2 * i], invp, qi);
         f.ninv_w = (double)hmul(hninv[2 * i + 1], invp, qi);
         f.ok = (qi >> 50) == 0;
         f.pm = 0;
