@@ -100,6 +100,71 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void gather_intt_kernel(PtrPack 
     with_field(modf[i], mods, tw, twf, ninv, i, logN, [&](const auto &f) { pass_b_body<true, RL>(f, logN, lds, load, store); });
 }
 
+// (out0, out1, t2) = (a0 b0, a0 b1 + a1 b0, a1 b1), pointwise, and the inverse tile pass of t2, which the relinearisation
+// decomposes: t2 as it is and, half transformed, tmp.  As two kernels a product and rescale at 2^15 (12 + 4 primes) took 4.5 us
+// longer: a launch, and 64-bit Montgomery products where primes below 2^50 have cheaper ones.
+// grid: x = 4096-residue tiles, y = limb
+template <u32 RL>
+__global__ __launch_bounds__(Tile<RL>::THREADS) void tensor_intt_kernel(const u64 *__restrict__ a, const u64 *__restrict__ b,
+                                                                  u64 *__restrict__ out, u64 *__restrict__ t2,
+                                                                  u64 *__restrict__ tmp, const ModConst *__restrict__ mods,
+                                                                  const ModFp *__restrict__ modf,
+                                                                  const u64 *__restrict__ tw,
+                                                                  const double *__restrict__ twf,
+                                                                  const u64 *__restrict__ ninv, u32 level, u32 logN) {
+    typedef Tile<RL> TL;
+    __shared__ u64 lds[TL::WORDS];
+    const u32 i = blockIdx.y, tid = threadIdx.x;
+    const size_t row = ((size_t)i << logN) + (blockIdx.x << 12), half = (size_t)level << logN;
+    u64 *dst = tmp + ((size_t)i << logN);
+    auto store = [&](u32 idx, u64 v) { dst[idx] = v; };
+    const ModFp mf = modf[i];
+    auto pointwise = [&](auto products) {
+#pragma unroll
+        for (u32 e0 = 0; e0 < TL::R; e0 += 4) {                     // four residues' operands on their way together
+            u64 x[4][4];
+#pragma unroll
+            for (u32 e = 0; e < 4; ++e) {
+                const size_t k = row + TL::one(tid, e0 + e);
+                x[e][0] = a[k];
+                x[e][1] = a[half + k];
+                x[e][2] = b[k];
+                x[e][3] = b[half + k];
+            }
+#pragma unroll
+            for (u32 e = 0; e < 4; ++e) {
+                const u32 loc = TL::one(tid, e0 + e);
+                u64 r0, r1, r2;
+                products(x[e][0], x[e][1], x[e][2], x[e][3], r0, r1, r2);
+                out[row + loc] = r0;
+                out[half + row + loc] = r1;
+                t2[row + loc] = r2;
+                lds[TL::slot(loc)] = r2;
+            }
+        }
+    };
+    if (mf.ok) {
+        const FieldFp f = make_field_fp(mf, twf, i, logN);
+        pointwise([&](u64 a0, u64 a1, u64 b0, u64 b1, u64 &r0, u64 &r1, u64 &r2) {
+            const double x0 = f.in(a0), x1 = f.in(a1), y0 = f.in(b0), y1 = f.in(b1);
+            r0 = f.out(f.mul(x0, y0));
+            r1 = f.out(f.mul(x0, y1) + f.mul(x1, y0));
+            r2 = f.out(f.mul(x1, y1));
+        });
+        pass_b_inv_from_lds<RL>(f, logN, lds, store);
+    } else {
+        const ModConst m = mods[i];
+        pointwise([&](u64 a0, u64 a1, u64 b0, u64 b1, u64 &r0, u64 &r1, u64 &r2) {
+            b0 = mont_mul(b0, m.r2, m);
+            b1 = mont_mul(b1, m.r2, m);
+            r0 = mont_mul(a0, b0, m);
+            r1 = add_mod(mont_mul(a0, b1, m), mont_mul(a1, b0, m), m.q);
+            r2 = mont_mul(a1, b1, m);
+        });
+        with_int_field(mf, mods, tw, ninv, i, logN, [&](const auto &f) { pass_b_inv_from_lds<RL>(f, logN, lds, store); });
+    }
+}
+
 // Per ciphertext r and digit j: y_i = c_i * (Q_D/q_i)^-1 mod q_i for the limbs of the digit, then for
 // every target t outside the digit out_t = sum_i y_i * (Q_D/q_i mod t) mod t (coefficient domain).
 // Targets inside the digit are left out: in the NTT domain they are the input's own rows, which the consumers
@@ -1195,12 +1260,10 @@ static moddown_mid_t moddown_mid_for(const ckks_params *p) {
     }
 }
 
-// Workgroups among which ModDown splits the target groups of a tile: as many as fill the chip once (three workgroups per
-// CU at N = 2^16, 256 CUs) and no more.  Whole calls with at most 256 / 512 / 768 / 1024 / 1536 workgroups, us: one rotation
-// at 2^16, level 24: 146.6 / 143.7 / 141.3 / 141.5 / 143.6, level 17: 130.6 / 127.8 / 127.6 / 127.9 / 129.5, two at level 24
-// 192.1 / 191.6 / 189.6 / 192.9 / 198.0; a product and rescale at 2^16, level 24: 202.7 / 198.4 / 194.9 / 195.4 / 197.0; at
-// 2^15, 12 + 4 primes, two switches 88.8 and 86.5 from 512 on, four 102.8 to 103.6; 2^14 the same at all.  (ModUp's step 1 is
-// cheap fp64 work, and its rule differs: see decompose.)
+// Workgroups among which ModDown splits the target groups of a tile: up to three for each of the 256 CUs, which run two at a
+// time.  The line hardly matters: whole calls with at most 256 / 384 / 512 / 768 / 1024 / 1536 workgroups, us: one rotation at
+// 2^16, level 24 134.4 / 133.3 / 133.4 / 133.2 / 133.5 / 133.3, three at level 17 189.7 / 189.6 / 189.5 / 186.4 / 186.5 / 190.4,
+// two at level 24 185.5 / 185.4 / 186.7 / 184.5 / 184.5 / 184.8; products, and calls of 2^15 and less, within 0.5 %.
 static u32 target_split(u32 workgroups, u32 groups) { return std::max<u32>(1, std::min<u32>(groups, 768 / workgroups)); }
 
 static void launch_moddown_mid(const ckks_params *p, const u64 *y, u64 *w, u32 n, u32 level, u32 ystride, u32 yoff,
@@ -1489,34 +1552,59 @@ static int transform_digits(ckks_params *p, u32 level, u32 n, u64 *d_digits, hip
     return CKKS_OK;
 }
 
+// the kernels that convert between the column passes (or, at N = 2^12, in the transforms) apply to ModUp
+static bool modup_mid_ok(const ckks_params *p, u32 level) {
+    bool ok = p->logN >= 12 && p->logN <= 16 && p->alpha <= 8 && p->K <= 8;
+    for (u32 i = 0; i < level; ++i) ok = ok && (p->mod[i] >> 50) == 0;
+    for (u32 k = 0; k < p->K; ++k) ok = ok && (p->mod[p->L + k] >> 60) == 0;
+    return ok;
+}
+// constants of the first pass of the decomposition's inverse transform: at N = 2^12 it is the whole one and scales for ModUp
+static const ModFp *decompose_modf(const ckks_params *p, const LevelTables *lt) {
+    return p->logN == 12 && modup_mid_ok(p, lt->level) ? lt->d_modf_up : p->d_modf;
+}
+
+static int decompose_from_tmp(ckks_params *p, const LevelTables *lt, u32 n, u64 *d_digits, u64 *d_tmp, hipStream_t stream,
+                              bool half);
+
 // c1[r] [level][N] NTT domain (n <= ROT_BATCH device pointers) -> d_digits [n][beta][level+K][N] NTT domain;
 // d_tmp [n][level][N] scratch.
 int decompose(ckks_params *p, const u64 *const *c1, u32 n, u32 level, u64 *d_digits, u64 *d_tmp,
               hipStream_t stream, bool half) {
     if (n == 0) return CKKS_OK;
-    const u32 N = p->N, K = p->K, L = p->L, Wl = level + K, alpha = p->alpha;
+    const u32 N = p->N;
     const LevelTables *lt = nullptr;
     int rc = p->level_tables(level, &lt);
     if (rc) return rc;
-    const u32 beta = lt->beta;
     PtrPack src;
     for (u32 r = 0; r < ROT_BATCH; ++r) src.p[r] = c1[r < n ? r : 0];
-    LimbIds ids;
-    for (u32 i = 0; i < level; ++i) ids.id[i] = (uint8_t)i;
-    bool all_fp = true;
-    for (u32 i = 0; i < level; ++i) all_fp = all_fp && (p->mod[i] >> 50) == 0;
-    bool sp60 = true;
-    for (u32 k = 0; k < K; ++k) sp60 = sp60 && (p->mod[L + k] >> 60) == 0;
     if (fast_ring(p)) {
         const bool wide = wide_tiles((u64)(N >> 12) * n * level);
-        const bool mid = p->logN <= 16 && all_fp && sp60 && alpha <= 8 && K <= 8, whole = p->logN == 12;
         hipLaunchKernelGGL(wide ? gather_intt_kernel<WIDE_RL> : gather_intt_kernel<4>, dim3(N >> 12, n * level),
-                           dim3(tile_threads(wide)), 0, stream, src, d_tmp,
-                           p->d_mod, mid && whole ? lt->d_modf_up : p->d_modf, p->d_tws_inv, p->d_twf_inv, p->d_ninvs, level,
-                           p->logN);
+                           dim3(tile_threads(wide)), 0, stream, src, d_tmp, p->d_mod, decompose_modf(p, lt), p->d_tws_inv,
+                           p->d_twf_inv, p->d_ninvs, level, p->logN);
         CKKS_LAUNCH_CHECK("gather_intt_kernel");
         p->limb_ntts += (u64)n * level;
-        if (mid && whole && !half) {
+    } else {
+        LimbIds ids;
+        for (u32 i = 0; i < level; ++i) ids.id[i] = (uint8_t)i;
+        hipLaunchKernelGGL(gather_c1_kernel, dim3(N / KS_THREADS, level, n), dim3(KS_THREADS), 0, stream, src, d_tmp,
+                           level, N);
+        CKKS_LAUNCH_CHECK("gather_c1_kernel");
+        rc = launch_ntt(p, d_tmp, ids, level, n * level, true, stream);
+        if (rc) return rc;
+    }
+    return decompose_from_tmp(p, lt, n, d_digits, d_tmp, stream, half);
+}
+
+// The rest of it: d_tmp holds the polynomials after the first pass of their inverse transform (plain-kernel rings: the whole).
+static int decompose_from_tmp(ckks_params *p, const LevelTables *lt, u32 n, u64 *d_digits, u64 *d_tmp, hipStream_t stream,
+                              bool half) {
+    const u32 N = p->N, K = p->K, L = p->L, level = lt->level, Wl = level + K, alpha = p->alpha, beta = lt->beta;
+    bool all_fp = true;
+    for (u32 i = 0; i < level; ++i) all_fp = all_fp && (p->mod[i] >> 50) == 0;
+    if (modup_mid_ok(p, level)) {
+        if (p->logN == 12 && !half) {
             const bool wide_up = wide_tiles((u64)n * beta * Wl - (u64)n * level);
             hipLaunchKernelGGL(wide_up ? modup_tile_kernel<WIDE_RL> : modup_tile_kernel<4>, dim3(Wl, beta, n),
                                dim3(tile_threads(wide_up)), 0, stream, d_tmp, d_digits, p->d_mod, p->d_modf, p->d_twf_fwd,
@@ -1525,28 +1613,25 @@ int decompose(ckks_params *p, const u64 *const *c1, u32 n, u32 level, u64 *d_dig
             p->limb_ntts += (u64)n * beta * Wl - (u64)n * level;
             return CKKS_OK;
         }
-        if (mid) {
-            // the column passes of both transforms ride in the base conversion: c1 read once, digits written once
-            const u32 tgroups = (Wl - std::min(alpha, level) + UP_TG - 1) / UP_TG, tiles = N / mid_tile(p);
-            // all target groups apart below 1024 workgroups: one rotation at 2^16, level 24 / 17 / 9, two at level 24, a product
-            // and rescale at 2^16 and 2^15 141.3 / 127.6 / 91.4, 189.6, 194.9 and 97.0 us; never split 141.9 / 131.6 / 95.5,
-            // 191.4, 196.0 and 100.2; with the line at 3072 142.4 / 128.7 / 91.5, 190.6, 196.5 and 97.1
-            const u32 tsplit = n * beta * tiles < 1024 ? std::max<u32>(1, tgroups) : 1;
-            hipLaunchKernelGGL(modup_mid_for(p), dim3(tiles * tsplit, beta, n), dim3(mid_tile(p) / 2), 0, stream, d_tmp,
-                               d_digits, p->d_mod, p->d_modf, lt->d_modf_up, p->d_twf_inv, p->d_twf_fwd, p->d_tws_fwd,
-                               p->d_ninvs, lt->d_up_ft, lt->d_up_mats, level, K, L, alpha, beta, tsplit);
-            CKKS_LAUNCH_CHECK("modup_mid_kernel");
-            p->limb_ntts += (u64)n * beta * Wl - (u64)n * level;
-            return half ? CKKS_OK : transform_digits(p, level, n, d_digits, stream, 2);
-        }
-        rc = launch_ntt(p, d_tmp, ids, level, n * level, true, stream, 2);
-    } else {
-        hipLaunchKernelGGL(gather_c1_kernel, dim3(N / KS_THREADS, level, n), dim3(KS_THREADS), 0, stream, src, d_tmp,
-                           level, N);
-        CKKS_LAUNCH_CHECK("gather_c1_kernel");
-        rc = launch_ntt(p, d_tmp, ids, level, n * level, true, stream);
+        // the column passes of both transforms ride in the base conversion: c1 read once, digits written once
+        const u32 tgroups = (Wl - std::min(alpha, level) + UP_TG - 1) / UP_TG, tiles = N / mid_tile(p);
+        // all target groups apart below 1024 workgroups (two per CU run at a time): one rotation at 2^16, level 24 / 17 / 9, two
+        // at level 24, a product and rescale at 2^16 and 2^15 133.4 / 120.4 / 83.8, 184.2, 188.5 and 85.2 us; never split 135.0 /
+        // 123.8 / 88.8, 186.0, 190.3 and 89.6; as many parts as make up to 256, 512, 768 or 1536 workgroups within 0.5 % of either
+        const u32 tsplit = n * beta * tiles < 1024 ? std::max<u32>(1, tgroups) : 1;
+        hipLaunchKernelGGL(modup_mid_for(p), dim3(tiles * tsplit, beta, n), dim3(mid_tile(p) / 2), 0, stream, d_tmp,
+                           d_digits, p->d_mod, p->d_modf, lt->d_modf_up, p->d_twf_inv, p->d_twf_fwd, p->d_tws_fwd,
+                           p->d_ninvs, lt->d_up_ft, lt->d_up_mats, level, K, L, alpha, beta, tsplit);
+        CKKS_LAUNCH_CHECK("modup_mid_kernel");
+        p->limb_ntts += (u64)n * beta * Wl - (u64)n * level;
+        return half ? CKKS_OK : transform_digits(p, level, n, d_digits, stream, 2);
     }
-    if (rc) return rc;
+    if (fast_ring(p)) {
+        LimbIds ids;
+        for (u32 i = 0; i < level; ++i) ids.id[i] = (uint8_t)i;
+        const int rc = launch_ntt(p, d_tmp, ids, level, n * level, true, stream, 2);
+        if (rc) return rc;
+    }
     // two launches: the ciphertext-prime targets (fp64 arithmetic when every active prime is below 2^50) and the
     // special-prime targets (integer arithmetic); each keeps only its own form of y in registers
 #define MODUP_LAUNCH(A, FPK, T0, T1)                                                                               \
@@ -2057,11 +2142,24 @@ int ckks_ctmul(ckks_params_t *P, const uint64_t *d_ct_a, const uint64_t *d_ct_b,
     int rc = P->ensure_scratch((dig_w + 2 * lim_w + switch_scratch_words(P, level, 1)) * sizeof(u64), stream);
     if (rc) return rc;
     u64 *d_digits = (u64 *)P->d_scratch, *d_tmp = d_digits + dig_w, *d_t2 = d_tmp + lim_w, *d_work = d_t2 + lim_w;
-    hipLaunchKernelGGL(tensor_kernel, dim3(N / KS_THREADS, level), dim3(KS_THREADS), 0, stream, d_ct_a, d_ct_b,
-                       d_ct_out, d_t2, P->d_mod, level, N);
-    CKKS_LAUNCH_CHECK("tensor_kernel");
-    const u64 *c1 = d_t2;
-    rc = decompose(P, &c1, 1, level, d_digits, d_tmp, stream);
+    if (fast_ring(P)) {
+        const LevelTables *lt = nullptr;
+        rc = P->level_tables(level, &lt);
+        if (rc) return rc;
+        const bool wide = wide_tiles((u64)(N >> 12) * level);
+        hipLaunchKernelGGL(wide ? tensor_intt_kernel<WIDE_RL> : tensor_intt_kernel<4>, dim3(N >> 12, level),
+                           dim3(tile_threads(wide)), 0, stream, d_ct_a, d_ct_b, d_ct_out, d_t2, d_tmp, P->d_mod,
+                           decompose_modf(P, lt), P->d_tws_inv, P->d_twf_inv, P->d_ninvs, level, P->logN);
+        CKKS_LAUNCH_CHECK("tensor_intt_kernel");
+        P->limb_ntts += level;
+        rc = decompose_from_tmp(P, lt, 1, d_digits, d_tmp, stream, false);
+    } else {
+        hipLaunchKernelGGL(tensor_kernel, dim3(N / KS_THREADS, level), dim3(KS_THREADS), 0, stream, d_ct_a, d_ct_b,
+                           d_ct_out, d_t2, P->d_mod, level, N);
+        CKKS_LAUNCH_CHECK("tensor_kernel");
+        const u64 *c1 = d_t2;
+        rc = decompose(P, &c1, 1, level, d_digits, d_tmp, stream);
+    }
     if (rc) return rc;
     SwitchItem it;
     it.digits = d_digits;

@@ -42,6 +42,26 @@ def test_small_rings_generic_path(L, K, dnum, level, qbits, pbits):
     _case(O, P, level, 80 + L, 2.0**30, 16)
 
 
+@pytest.mark.parametrize("logN,L,K,dnum,level,qbits,pbits", [(12, 4, 2, 2, 3, 50, 60), (12, 4, 4, 1, 4, 52, 60), (12, 3, 3, 1, 2, 61, 62),
+                                                              (13, 4, 2, 2, 4, 50, 60), (14, 3, 2, 3, 3, 56, 61),
+                                                              (17, 18, 3, 6, 17, 50, 60)])     # 544 tiles
+def test_tensor_product_within_the_first_transform_pass(logN, L, K, dnum, level, qbits, pbits):
+    """Rows of either kind of prime, the ring whose tile is the whole transform, more tiles than go out wide; residues of q - 1
+    among uniform ones, and a ciphertext times itself."""
+    from paper_2604_09975_amd import binding as B
+    O = helpers.small_oracle(logN, L=L, K=K, dnum=dnum, qbits=qbits, pbits=pbits)
+    _, P = make_pair(O)
+    r = W.rng(logN + L)
+    top = np.array(O.q[:level], dtype=np.uint64)[:, None] - np.uint64(1)
+    a, b = (np.where(r.integers(0, 5, x.shape) == 0, top, x) for x in W.uniform_residues(r, O.q[:level], O.N, lead=(2, 2)))
+    rk = W.uniform_residues(r, O.moduli, O.N, lead=(dnum, 2))
+    h = B.ckks_relin_key_load(P, to_dev(rk))
+    for y in (b, a):
+        da = to_dev(a)
+        got = to_host(B.ckks_ctmul(P, da, da if y is a else to_dev(y), level, h))
+        assert (got == O.ctmul(a, y, level, rk)).all()
+
+
 def test_full_ring():
     O, P = make_pair(W.BIG_RING)
     from paper_2604_09975_amd import binding as B
