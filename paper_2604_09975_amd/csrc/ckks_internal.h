@@ -173,9 +173,9 @@ struct SwitchItem {
     const u64 *key;      // key in the library's form
     u64 *dst;            // [2][level][N]
     u64 galois_elt;
-    u32 accumulate;      // add into dst instead of overwriting
+    const u64 *add;      // [2][level][N] added to the result (dst: accumulation), or null
     u32 balanced;        // limbs below 2^50 leave as balanced doubles (bit patterns), |x| <= (q+1)/2: the projection's
-                         // bank, read by the multiply-accumulate kernels only (not with accumulate)
+                         // bank, read by the multiply-accumulate kernels only (not with add)
 };
 size_t digits_words(const ckks_params *p, u32 level);
 size_t switch_scratch_words(const ckks_params *p, u32 level, u32 n_items);
@@ -183,9 +183,10 @@ int decompose(ckks_params *p, const u64 *const *c1, u32 n, u32 level, u64 *d_dig
               bool half = false);   // half: the forward tile pass of the digits is left to the consumer
 int switch_batch(ckks_params *p, u32 level, const SwitchItem *items, u32 n, u64 *d_work, hipStream_t stream);
 bool moddown_mid_ok(const ckks_params *p, u32 level);   // the fused ModDown (and ModDown + rescale) kernels apply
-int moddown_add(ckks_params *p, u32 level, u64 *d_u, u64 *const *dst, u32 n, u64 *d_w, hipStream_t stream);
-int moddown_rescale(ckks_params *p, u32 level, u64 *d_u, const u64 *const *z, u64 *const *out, u32 n, u64 *d_w,
-                    u64 *d_t, hipStream_t stream);
+int moddown_add(ckks_params *p, u32 level, u64 *d_u, const u64 *const *z, u64 *const *out, u32 n, u64 *d_w,
+                hipStream_t stream);
+int moddown_rescale(ckks_params *p, u32 level, u64 *d_u, const u64 *const *z, const u64 *bias, u64 *const *out, u32 n,
+                    u64 *d_w, u64 *d_t, hipStream_t stream);
 // Several rotations of n ciphertexts each, summed over the extended basis in one pass:
 //   u_r (+)= sum_i sum_j sigma_{g_i}(digits_{i,r,j}) * key_{i,j},   dst_r.c0 += sum_i sigma_{g_i}(c0_{i,r}),
 // r < n <= ROT_BATCH, i < n_rot <= MERGE_GROUP.  digits of (i, r) at d_digits + (i*n + r)*digits_words, half: as decompose

@@ -156,7 +156,7 @@ static int shift_bank(ckks_params_t *P, const uint64_t *d_ct_in, uint32_t level,
             it.key = keys[gs]->d_key;
             it.dst = d_rot + (size_t)s * ctw;
             it.galois_elt = gel[gs];
-            it.accumulate = 0;
+            it.add = nullptr;
             it.balanced = 0;
         }
         rc = switch_batch(P, level, items, n_it, d_work, stream);

@@ -52,7 +52,7 @@ __device__ __forceinline__ pair_t turned(pair_t v, u32 kp) { return PAIR && (kp 
 __global__ __launch_bounds__(EW_THREADS) void key_form_kernel(const u64 *in, u64 *out,
                                                               const ModConst *__restrict__ mods,
                                                               const u64 *__restrict__ pinv, u32 L, u32 W, u32 N) {
-    const u32 limb = blockIdx.y % W;
+    const u32 limb = blockIdx.y - uniform_div(blockIdx.y, W) * W;
     const ModConst m = mods[limb];
     const u64 f = limb < L ? pinv[limb] : 0;
     const size_t idx = (size_t)blockIdx.y * N + (blockIdx.x * EW_THREADS + threadIdx.x) * 2;
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void gather_intt_kernel(PtrPack 
                                                                   const double *__restrict__ twf,
                                                                   const u64 *__restrict__ ninv, u32 level, u32 logN) {
     __shared__ u64 lds[Tile<RL>::WORDS];
-    const u32 r = blockIdx.y / level, i = blockIdx.y % level;
+    const u32 r = uniform_div(blockIdx.y, level), i = blockIdx.y - r * level;
     const u64 *in = src.p[r] + ((size_t)i << logN);
     u64 *out = tmp + ((size_t)blockIdx.y << logN);
     auto load = [&](u32 idx) { return in[idx]; };
@@ -686,13 +686,14 @@ __global__ __launch_bounds__(KS_THREADS) void merged_ip_kernel(MergedRot rots, c
     // groups of ciphertexts, which read the same key rows, follow each other at a distance of 8 workgroups, i.e. on
     // the same XCD at about the same time, so one of them fetches a key line and the others find it in that L2
     const u32 chunk = N / KS_THREADS < 8 ? N / KS_THREADS : 8;   // a power of two
-    const u32 xg = blockIdx.x / chunk;
-    const u32 k = ((xg / groups) * chunk + (blockIdx.x & (chunk - 1))) * KS_THREADS + threadIdx.x;
+    const u32 xg = uniform_div(blockIdx.x, chunk);
+    const u32 xd = uniform_div(xg, groups);
+    const u32 k = (xd * chunk + (blockIdx.x & (chunk - 1))) * KS_THREADS + threadIdx.x;
     const u32 t = rows.id[blockIdx.y];
-    const u32 r0 = (xg % groups) * MR;
+    const u32 r0 = (xg - xd * groups) * MR;
     const u32 Wl = level + K, Wt = L + K;
     const u32 gl = t < level ? t : L + (t - level);
-    const u32 own = t < level ? t / alpha : ~0u;                 // the digit whose own limb t is: read from c1
+    const u32 own = t < level ? uniform_div(t, alpha) : ~0u;                 // the digit whose own limb t is: read from c1
     const ModConst m = mods[gl];
     const double q = (double)m.q, uq = 1.0 / q;
     u128 a0[MR], a1[MR];
@@ -829,11 +830,11 @@ __global__ __launch_bounds__(Tile<RL>::THREADS, 4) void merged_tile_kernel(Merge
     const u32 N = 1u << logN, Wl = level + K, Wt = L + K, tid = threadIdx.x;
     // units (row, tile) in chunks of eight, the ciphertexts of a unit eight workgroups apart: on one XCD at about the same
     // time, where one of them fetches the key lines for all.  Special limbs, the longest rows, first.
-    const u32 tiles = N >> 12, xg = blockIdx.x >> 3, unit = xg / n * 8 + (blockIdx.x & 7), r = xg % n;
+    const u32 tiles = N >> 12, xg = blockIdx.x >> 3, xn = uniform_div(xg, n), unit = xn * 8 + (blockIdx.x & 7), r = xg - xn * n;
     if (unit >= tiles * Wl) return;
-    const u32 t = rows.id[unit / tiles], tile = unit % tiles, base = tile << 12;
+    const u32 t = rows.id[unit >> (logN - 12)], tile = unit & (tiles - 1), base = tile << 12;
     const u32 gl = t < level ? t : L + (t - level);
-    const u32 own = t < level ? t / alpha : ~0u;                 // the digit whose own limb t is: read from c1
+    const u32 own = t < level ? uniform_div(t, alpha) : ~0u;                 // the digit whose own limb t is: read from c1
     const ModConst m = mods[gl];
     const ModFp mf = modf[gl];
     u64 *u0 = u + (((size_t)r * 2) * Wl + t) * N + base, *u1 = u0 + (size_t)Wl * N;
@@ -1198,9 +1199,10 @@ __global__ __launch_bounds__(MidTile<LOGR>::THREADS, 4) void moddown_mid_kernel(
     }
 }
 
-// t[pc][k] = z[pc][l-1][k] + u[pc][l-1][k] P^-1 mod q_{l-1} (NTT domain): the dropped limb of the ciphertext before its
-// special-limb correction.  z_r: component-major ciphertexts [2][level][N]; u [n][2][level+K][N].
+// t[pc][k] = z[pc][l-1][k] + u[pc][l-1][k] P^-1 mod q_{l-1} (NTT domain; component 0: + bias[r][l-1][k], where there is one): the
+// dropped limb of the ciphertext before its special-limb correction.  z_r: component-major ciphertexts [2][level][N]; u [n][2][level+K][N].
 __global__ __launch_bounds__(KS_THREADS) void rescale_last_row_kernel(PtrPack z, const u64 *__restrict__ u,
+                                                                      const u64 *__restrict__ bias,
                                                                       u64 *__restrict__ t,
                                                                       const ModConst *__restrict__ mods,
                                                                       u32 level, u32 K, u32 N) {
@@ -1209,30 +1211,63 @@ __global__ __launch_bounds__(KS_THREADS) void rescale_last_row_kernel(PtrPack z,
     const ModConst m = mods[i];
     const u64 zz = z.p[r][((size_t)comp * level + i) * N + k];
     const u64 uu = u[((size_t)pc * (level + K) + i) * N + k];
-    t[(size_t)pc * N + k] = add_mod(zz, uu, m.q);
+    u64 v = add_mod(zz, uu, m.q);
+    if (bias && comp == 0) v = add_mod(v, bias[((size_t)r * level + i) * N + k], m.q);
+    t[(size_t)pc * N + k] = v;
 }
 
-// out[r][comp][i][k] = (z[r][comp][i][k] + u P^-1 - NTT(w')[i][k]) q_{l-1}^-1 for the l-1 remaining limbs
-__global__ __launch_bounds__(KS_THREADS) void moddown_rescale_final_kernel(PtrPack z, ItemPack out,
-                                                                           const u64 *__restrict__ u,
-                                                                           const u64 *__restrict__ w,
-                                                                           const ModConst *__restrict__ mods,
-                                                                           const u64 *__restrict__ qlinv, u32 level,
-                                                                           u32 K, u32 N) {
-    typedef u64 vec_t __attribute__((ext_vector_type(2)));
-    const u32 k = (blockIdx.x * KS_THREADS + threadIdx.x) * 2;
-    const u32 i = blockIdx.y, pc = blockIdx.z, r = pc >> 1, comp = pc & 1;
-    const ModConst m = mods[i];
-    const vec_t zz = *reinterpret_cast<const vec_t *>(z.p[r] + ((size_t)comp * level + i) * N + k);
-    const vec_t uu = *reinterpret_cast<const vec_t *>(u + ((size_t)pc * (level + K) + i) * N + k);
-    const vec_t ww = *reinterpret_cast<const vec_t *>(w + ((size_t)pc * level + i) * N + k);
-    vec_t o;
+// The end of a ModDown: the forward tile pass of the correction w and what is done with it, limb i of component comp of
+// ciphertext r:
+//   out = z + u P^-1 - NTT(w),                                       or with RESC, on the l-1 remaining limbs,
+//   out = (z + u P^-1 - NTT(w') (+ bias, component 0)) q_{l-1}^-1.
+// z: ciphertexts [2][level][N], which out may be (not RESC).  Bound by memory, 32 bytes a residue at a copy's rate; as a tile
+// pass and a kernel behind it, 48: nine blocks of 24 limbs at 2^16 249 -> 189 us.  grid: x = 4096-residue tiles, y = limb, z = pc
+template <u32 RL, bool RESC>
+__global__ __launch_bounds__(Tile<RL>::THREADS) void moddown_tile_kernel(PtrPack z, PtrPack out, const u64 *__restrict__ u,
+                                                                   const u64 *__restrict__ w, const u64 *__restrict__ bias,
+                                                                   const ModFp *__restrict__ modf,
+                                                                   const ModConst *__restrict__ mods,
+                                                                   const double *__restrict__ twf_fwd,
+                                                                   const u64 *__restrict__ qlinv, u32 level, u32 K,
+                                                                   u32 logN) {
+    typedef Tile<RL> TL;
+    __shared__ u64 lds[TL::WORDS];
+    const u32 i = blockIdx.y, pc = blockIdx.z, r = pc >> 1, comp = pc & 1, tid = threadIdx.x, base = blockIdx.x << 12;
+    const u64 *zr = z.p[r] + (((size_t)comp * level + i) << logN) + base;
+    const u64 *ur = u + (((size_t)pc * (level + K) + i) << logN) + base;
+    const u64 *br = RESC && bias && comp == 0 ? bias + (((size_t)r * level + i) << logN) + base : nullptr;
+    const u64 *wr = w + (((size_t)pc * level + i) << logN);
+    u64 *dst = const_cast<u64 *>(out.p[r]) + (((size_t)comp * (RESC ? level - 1 : level) + i) << logN) + base;
+    const FieldFp f = make_field_fp(modf[i], twf_fwd, i, logN);
+    const double c = RESC ? canonical_double(mont_mul(qlinv[i], 1, mods[i])) : 0.0;     // q_l^-1 (stored in Montgomery form)
+    constexpr u32 EPP = RL < 4 ? TL::R / 2 : EPI / 2;
+    pair_t zv[EPP], uv[EPP], bv[EPP];
+    auto load_operands = [&](u32 i0) {
 #pragma unroll
-    for (u32 e = 0; e < 2; ++e) {
-        const u64 y = add_mod(zz[e], uu[e], m.q);
-        o[e] = mont_mul(sub_mod(y, ww[e], m.q), qlinv[i], m);
+        for (u32 e = 0; e < EPP; ++e) {
+            const u32 loc = TL::pair(tid, i0 + e);
+            zv[e] = *reinterpret_cast<const pair_t *>(zr + loc);
+            uv[e] = *reinterpret_cast<const pair_t *>(ur + loc);
+            bv[e] = br ? *reinterpret_cast<const pair_t *>(br + loc) : pair_t{0, 0};
+        }
+    };
+    if (RL < 4) load_operands(0);
+    pass_b_fwd_to_lds<true, RL>(f, logN, lds, [&](u32 idx) { return wr[idx]; });
+    for (u32 i0 = 0; i0 < TL::R / 2; i0 += EPP) {
+        if (RL == 4) load_operands(i0);
+#pragma unroll
+        for (u32 e = 0; e < EPP; ++e) {
+            const u32 loc = TL::pair(tid, i0 + e);
+            pair_t o;
+#pragma unroll
+            for (u32 s = 0; s < 2; ++s) {
+                const double x = (canonical_double(zv[e][s]) + canonical_double(uv[e][s])) + canonical_double(bv[e][s]) -
+                                 __longlong_as_double((long long)lds[TL::slot(loc + s)]);
+                o[s] = f.out(RESC ? f.mul(x, c) : x);
+            }
+            *reinterpret_cast<pair_t *>(dst + loc) = o;
+        }
     }
-    *reinterpret_cast<vec_t *>(out.it[r].dst + ((size_t)comp * (level - 1) + i) * N + k) = o;
 }
 
 // Whether the fused kernel applies to this parameter set at this level.
@@ -1309,7 +1344,7 @@ __global__ __launch_bounds__(KS_THREADS) void moddown_final_kernel(ItemPack pack
     u64 v = sub_mod(uq, wq, m.q);
     if (comp == 0 && it.c0) v = add_mod(v, it.c0[(size_t)i * N + galois_index(k, (u32)it.galois_elt, logN)], m.q);
     u64 *dst = it.dst + ((size_t)comp * level + i) * N + k;
-    if (it.accumulate) v = add_mod(v, *dst, m.q);
+    if (it.add) v = add_mod(v, it.add[((size_t)comp * level + i) * N + k], m.q);
     if (it.balanced && (m.q >> 50) == 0) v = balanced_bits(v, m.q);
     *dst = v;
 }
@@ -1338,7 +1373,7 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void ip_intt_kernel(ItemPack pac
     typedef Tile<RL> TL;
     __shared__ u64 lds[TL::WORDS];
     const u32 N = 1u << logN;
-    const u32 comp = blockIdx.y & 1, r = (blockIdx.y >> 1) % n, k = (blockIdx.y >> 1) / n;
+    const u32 comp = blockIdx.y & 1, k = uniform_div(blockIdx.y >> 1, n), r = (blockIdx.y >> 1) - k * n;
     const u32 gl = L + k, t = level + k, Wl = level + K, Wt = L + K;
     const SwitchItem &it = pack.it[r];
     const ModConst m = mods[gl];
@@ -1407,20 +1442,23 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void passb_final_kernel(ItemPack
     static_assert(RL == 4 || !PAIR, "operands that share a register with gathered ones are not turned");
     __shared__ u64 lds[TL::WORDS];
     const u32 N = 1u << logN;
-    const u32 comp = blockIdx.y & 1, r = (blockIdx.y >> 1) % n, i = (blockIdx.y >> 1) / n;
+    const u32 comp = blockIdx.y & 1, i = uniform_div(blockIdx.y >> 1, n), r = (blockIdx.y >> 1) - i * n;
     const u32 Wl = level + K, Wt = L + K;
     const SwitchItem &it = pack.it[r];
     const ModConst m = mods[i];
     const u64 *wrow = w + (((size_t)r * 2 + comp) * level + i) * N;
     // row of limb i in digit j; the digit that owns limb i is not stored: its row is the source's own
     const u64 *drow[MAX_BETA];
+    const u32 own = uniform_div(i, alpha);
 #pragma unroll
     for (u32 j = 0; j < MAX_BETA; ++j)
-        drow[j] = j == i / alpha ? it.c1 + (size_t)i * N : it.digits + ((size_t)j * Wl + i) * N;
+        drow[j] = j == own ? it.c1 + (size_t)i * N : it.digits + ((size_t)j * Wl + i) * N;
     const u64 *key = it.key + ((size_t)comp * Wt + i) * N;
     const u64 *c0 = it.c0 + (size_t)i * N;
     u64 *dst = it.dst + ((size_t)comp * level + i) * N;
-    const u32 g = (u32)it.galois_elt, accumulate = it.accumulate;
+    const u32 g = (u32)it.galois_elt;
+    const bool accumulate = it.add != nullptr;
+    const u64 *add = it.add + ((size_t)comp * level + i) * N + (blockIdx.x << 12);   // read only if it.add is there
     auto load = [&](u32 idx) -> u64 { return __builtin_nontemporal_load(wrow + idx); };
     const ModFp mf = modf[i];
     // epilogue on pairs of adjacent residues (16-byte accesses to the streamed operands), two pairs at a time so
@@ -1431,7 +1469,7 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void passb_final_kernel(ItemPack
     const bool fold = comp == 0 && it.c0;
     pair_t dv[EPP][MAX_BETA], kv[EPP][MAX_BETA], cv[EPP], ov[EPP];
     u32 kp[EPP];
-    auto load_dst = [&](u32 idx) { return __builtin_nontemporal_load(reinterpret_cast<const pair_t *>(dst + idx)); };
+    auto load_add = [&](u32 loc) { return __builtin_nontemporal_load(reinterpret_cast<const pair_t *>(add + loc)); };
     auto load_operands = [&](u32 i0) {
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
@@ -1443,8 +1481,8 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void passb_final_kernel(ItemPack
                     dv[e][j] = load_two<PAIR>(drow[j], kp[e]);
                     kv[e][j] = load_key<KEY_NT>(reinterpret_cast<const pair_t *>(key + (size_t)j * 2 * Wt * N + idx));
                 }
-            cv[e] = fold ? load_two<PAIR>(c0, kp[e]) : accumulate && RL < 4 ? load_dst(idx) : pair_t{0, 0};
-            if (RL == 4) ov[e] = accumulate ? load_dst(idx) : pair_t{0, 0};
+            cv[e] = fold ? load_two<PAIR>(c0, kp[e]) : accumulate && RL < 4 ? load_add(TL::pair(tid, i0 + e)) : pair_t{0, 0};
+            if (RL == 4) ov[e] = accumulate ? load_add(TL::pair(tid, i0 + e)) : pair_t{0, 0};
         }
     };
     if (CONV) {
@@ -1466,9 +1504,9 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void passb_final_kernel(ItemPack
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
             const u32 loc = TL::pair(tid, i0 + e);
-            // RL < 4: one array for c0 or dst (128 registers is what 16 wavefronts a workgroup leave); where both are added,
-            // dst comes now
-            if (RL < 4) ov[e] = accumulate && fold ? load_dst(base + loc) : pair_t{0, 0};
+            // RL < 4: one array for c0 or the addend (128 registers is what 16 wavefronts a workgroup leave); where both are added,
+            // the addend comes now
+            if (RL < 4) ov[e] = accumulate && fold ? load_add(loc) : pair_t{0, 0};
             __builtin_amdgcn_sched_barrier(0);
             cv[e] = turned<PAIR>(cv[e], kp[e]);
 #pragma unroll
@@ -1747,23 +1785,22 @@ int switch_accumulate_merged(ckks_params *p, u32 level, const MergedRot &rots, u
     return CKKS_OK;
 }
 
-// Merged giant step, part 2: dst_r += ModDown(d_u[r]) for n <= ROT_BATCH ciphertexts; d_u is consumed.
-// d_w: n*2*level*N words of scratch.
-int moddown_add(ckks_params *p, u32 level, u64 *d_u, u64 *const *dst, u32 n, u64 *d_w, hipStream_t stream) {
+template <bool RESC>
+static void launch_moddown_tile(const ckks_params *p, const PtrPack &z, const PtrPack &out, const u64 *u, const u64 *w,
+                                const u64 *bias, u32 n, u32 level, hipStream_t stream) {
+    const u32 limbs = RESC ? level - 1 : level, tiles = p->N >> 12;
+    const bool wide = wide_tiles((u64)tiles * limbs * n * 2);
+    hipLaunchKernelGGL((wide ? moddown_tile_kernel<WIDE_RL, RESC> : moddown_tile_kernel<4, RESC>), dim3(tiles, limbs, n * 2),
+                       dim3(tile_threads(wide)), 0, stream, z, out, u, w, bias, p->d_modf, p->d_mod, p->d_twf_fwd,
+                       p->d_qlinv + (size_t)(level - 1) * p->L, level, p->K, p->logN);
+}
+
+// Merged giant step, part 2: out_r = z_r + ModDown(d_u[r]) for n <= ROT_BATCH ciphertexts [2][level][N]; d_u is consumed.
+// d_w: n*2*level*N words of scratch.  out_r may be z_r, and is where moddown_mid_ok says no.
+int moddown_add(ckks_params *p, u32 level, u64 *d_u, const u64 *const *z, u64 *const *out, u32 n, u64 *d_w,
+                hipStream_t stream) {
     if (n == 0) return CKKS_OK;
     const u32 N = p->N, K = p->K, L = p->L, Wl = level + K;
-    ItemPack pack;
-    for (u32 r = 0; r < ROT_BATCH; ++r) {
-        SwitchItem &it = pack.it[r];
-        it.digits = nullptr;
-        it.c1 = nullptr;
-        it.c0 = nullptr;                       // already folded in by switch_accumulate_merged
-        it.key = nullptr;
-        it.dst = dst[r < n ? r : 0];
-        it.galois_elt = 1;
-        it.accumulate = 1;
-        it.balanced = 0;
-    }
     LimbIds ids;
     for (u32 t = 0; t < Wl; ++t) ids.id[t] = (uint8_t)(t < level ? SKIP_ROW : L + (t - level));
     const bool mid = moddown_mid_ok(p, level);      // the column passes of both transforms ride in the conversion
@@ -1773,13 +1810,32 @@ int moddown_add(ckks_params *p, u32 level, u64 *d_u, u64 *const *dst, u32 n, u64
         launch_moddown_mid(p, d_u, d_w, n, level, Wl, level, stream);
         CKKS_LAUNCH_CHECK("moddown_mid_kernel");
         p->limb_ntts += (u64)n * 2 * level;
-    } else {
-        launch_moddown_conv(p, d_u, d_w, n, level, Wl, level, stream);
-        CKKS_LAUNCH_CHECK("moddown_conv_kernel");
+        PtrPack zp, op;
+        for (u32 r = 0; r < ROT_BATCH; ++r) {
+            zp.p[r] = z[r < n ? r : 0];
+            op.p[r] = out[r < n ? r : 0];
+        }
+        launch_moddown_tile<false>(p, zp, op, d_u, d_w, nullptr, n, level, stream);
+        CKKS_LAUNCH_CHECK("moddown_tile_kernel");
+        return CKKS_OK;
     }
+    launch_moddown_conv(p, d_u, d_w, n, level, Wl, level, stream);
+    CKKS_LAUNCH_CHECK("moddown_conv_kernel");
     for (u32 i = 0; i < level; ++i) ids.id[i] = (uint8_t)i;
-    rc = launch_ntt(p, d_w, ids, level, n * 2 * level, false, stream, mid ? 2 : 3);
+    rc = launch_ntt(p, d_w, ids, level, n * 2 * level, false, stream);
     if (rc) return rc;
+    ItemPack pack;
+    for (u32 r = 0; r < ROT_BATCH; ++r) {
+        SwitchItem &it = pack.it[r];
+        it.digits = nullptr;
+        it.c1 = nullptr;
+        it.c0 = nullptr;                       // already folded in by switch_accumulate_merged
+        it.key = nullptr;
+        it.dst = out[r < n ? r : 0];
+        it.add = z[r < n ? r : 0];
+        it.galois_elt = 1;
+        it.balanced = 0;
+    }
     hipLaunchKernelGGL(moddown_final_kernel, dim3(N / KS_THREADS, level, n * 2), dim3(KS_THREADS), 0, stream, pack,
                        d_u, d_w, p->d_mod, level, K, p->logN);
     CKKS_LAUNCH_CHECK("moddown_final_kernel");
@@ -1787,30 +1843,24 @@ int moddown_add(ckks_params *p, u32 level, u64 *d_u, u64 *const *dst, u32 n, u64
 }
 
 // ModDown and rescale in one pass over the correction (merged giant step with CKKS_MATMUL_RESCALE):
-//   out_r = rescale( z_r + ModDown(d_u[r]) ),   z_r [2][level][N] -> out_r [2][level-1][N],   n <= ROT_BATCH.
-// d_u is consumed; d_w: n*2*level*N words, d_t: n*2*N words of scratch.  Returns CKKS_E_INVAL if the fused kernels do
-// not apply to this parameter set (the caller then brings down and rescales in two steps).
-int moddown_rescale(ckks_params *p, u32 level, u64 *d_u, const u64 *const *z, u64 *const *out, u32 n, u64 *d_w,
-                    u64 *d_t, hipStream_t stream) {
+//   out_r = rescale( z_r + ModDown(d_u[r]) + (bias_r, 0) ),   z_r [2][level][N] -> out_r [2][level-1][N],   n <= ROT_BATCH;
+// bias [n][level][N] or null.  d_u is consumed; d_w: n*2*level*N words, d_t: n*2*N words of scratch.  Returns CKKS_E_INVAL if
+// the fused kernels do not apply to this parameter set (the caller then brings down and rescales in two steps).
+int moddown_rescale(ckks_params *p, u32 level, u64 *d_u, const u64 *const *z, const u64 *bias, u64 *const *out, u32 n,
+                    u64 *d_w, u64 *d_t, hipStream_t stream) {
     if (n == 0) return CKKS_OK;
     if (!moddown_mid_ok(p, level) || level < 2) return CKKS_E_INVAL;
     const u32 N = p->N, K = p->K, L = p->L, Wl = level + K;
-    PtrPack zp;
-    ItemPack op;
+    PtrPack zp, op;
     for (u32 r = 0; r < ROT_BATCH; ++r) {
         zp.p[r] = z[r < n ? r : 0];
-        SwitchItem &it = op.it[r];
-        it.digits = it.c1 = it.c0 = it.key = nullptr;
-        it.dst = out[r < n ? r : 0];
-        it.galois_elt = 1;
-        it.accumulate = 0;
-        it.balanced = 0;
+        op.p[r] = out[r < n ? r : 0];
     }
     LimbIds ids;
     for (u32 t = 0; t < Wl; ++t) ids.id[t] = (uint8_t)(t < level ? SKIP_ROW : L + (t - level));
     int rc = launch_ntt(p, d_u, ids, Wl, n * 2 * Wl, true, stream, 1, true);     // special limbs: inverse tile pass
     if (rc) return rc;
-    hipLaunchKernelGGL(rescale_last_row_kernel, dim3(N / KS_THREADS, n * 2), dim3(KS_THREADS), 0, stream, zp, d_u, d_t,
+    hipLaunchKernelGGL(rescale_last_row_kernel, dim3(N / KS_THREADS, n * 2), dim3(KS_THREADS), 0, stream, zp, d_u, bias, d_t,
                        p->d_mod, level, K, N);
     CKKS_LAUNCH_CHECK("rescale_last_row_kernel");
     ids.id[0] = (uint8_t)(level - 1);
@@ -1819,12 +1869,8 @@ int moddown_rescale(ckks_params *p, u32 level, u64 *d_u, const u64 *const *z, u6
     launch_moddown_mid(p, d_u, d_w, n, level, Wl, level, stream, d_t);
     CKKS_LAUNCH_CHECK("moddown_mid_kernel");
     p->limb_ntts += (u64)n * 2 * (level - 1);
-    for (u32 i = 0; i < level; ++i) ids.id[i] = (uint8_t)(i + 1 < level ? i : SKIP_ROW);
-    rc = launch_ntt(p, d_w, ids, level, n * 2 * level, false, stream, 2);
-    if (rc) return rc;
-    hipLaunchKernelGGL(moddown_rescale_final_kernel, dim3(N / KS_THREADS / 2, level - 1, n * 2), dim3(KS_THREADS), 0,
-                       stream, zp, op, d_u, d_w, p->d_mod, p->d_qlinv + (size_t)(level - 1) * L, level, K, N);
-    CKKS_LAUNCH_CHECK("moddown_rescale_final_kernel");
+    launch_moddown_tile<true>(p, zp, op, d_u, d_w, bias, n, level, stream);
+    CKKS_LAUNCH_CHECK("moddown_tile_kernel");
     return CKKS_OK;
 }
 
@@ -1981,7 +2027,7 @@ int rotate_hoisted(ckks_params *P, const u64 *d_ct_in, u32 level, const int32_t 
         it.key = keys[r]->d_key;
         it.dst = d_ct_out + (size_t)r * ctw;
         it.galois_elt = g;
-        it.accumulate = 0;
+        it.add = nullptr;
         it.balanced = 0;
         items.push_back(it);
     }
@@ -2168,7 +2214,7 @@ int ckks_ctmul(ckks_params_t *P, const uint64_t *d_ct_a, const uint64_t *d_ct_b,
     it.key = relin_key->d_key;
     it.dst = d_ct_out;
     it.galois_elt = 1;
-    it.accumulate = 1;
+    it.add = d_ct_out;
     it.balanced = 0;
     return switch_batch(P, level, &it, 1, d_work, stream);
 }

@@ -43,7 +43,7 @@ __global__ __launch_bounds__(NTT_THREADS) void expand_pass_kernel(const int64_t 
                                                                   const u64 *__restrict__ ninvs, u32 level) {
     constexpr u32 logN = 12 + LOGR;
     __shared__ u64 lds[LOGR ? 1 : Tile<4>::WORDS];
-    const u32 d = blockIdx.y / level, i = blockIdx.y % level;
+    const u32 d = uniform_div(blockIdx.y, level), i = blockIdx.y - d * level;
     const ModConst m = mods[i];
     const ModFp mf = modf[i];
     const int64_t *src = coef + ((size_t)d << logN);
@@ -149,8 +149,9 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
     if (swizzle) {
         const u32 lin = blockIdx.y * gridDim.x + blockIdx.x;
         const u32 xcd = lin & 7, slot = lin >> 3;
-        tile = slot % gridDim.x;
-        run = (slot / gridDim.x) * 8 + xcd;
+        const u32 d = uniform_div(slot, gridDim.x);
+        tile = slot - d * gridDim.x;
+        run = d * 8 + xcd;
     }
     const u32 bpt = (bp0 / TB + tile) * TB;                        // the tile's first pair
     const u32 k = (run * MM_THREADS + threadIdx.x) * 2;            // SYM: k < N/2
@@ -383,7 +384,7 @@ __global__ __launch_bounds__(EW_THREADS) void bank_entry_kernel(const u64 *__res
                                                                 const ModConst *__restrict__ mods, u32 level, u32 N) {
     typedef u64 vec_t __attribute__((ext_vector_type(2)));
     const size_t k = (size_t)blockIdx.y * N + (blockIdx.x * EW_THREADS + threadIdx.x) * 2;
-    const u64 q = mods[blockIdx.y % level].q;
+    const u64 q = mods[blockIdx.y < level ? blockIdx.y : blockIdx.y - level].q;
     vec_t v = *reinterpret_cast<const vec_t *>(src + k);
     if ((q >> 50) == 0) {
         v[0] = balanced_bits(v[0], q);
@@ -402,18 +403,24 @@ __global__ __launch_bounds__(EW_THREADS) void copy_blocks_kernel(u64 *__restrict
 }
 
 // y_b = base_b + the rotated accumulators of block b among the cn items of a batch; item r belongs to block (c0 + r) % B.
-// base is y itself from the second batch on.  blockIdx.y = component * level + limb, blockIdx.z = block; two residues per
+// base is y itself from the second batch on.  bias: [B][level][N] added to component 0, or null.  blockIdx.y = component * level + limb, blockIdx.z = block; two residues per
 // thread.
 __global__ __launch_bounds__(EW_THREADS) void add_rotations_kernel(u64 *y, const u64 *base,
                                                                    size_t base_stride, const u64 *__restrict__ items,
+                                                                   const u64 *__restrict__ bias,
                                                                    const ModConst *__restrict__ mods, u32 level, u32 N,
                                                                    u32 b0, u32 B, u32 c0, u32 cn) {
     typedef u64 vec_t __attribute__((ext_vector_type(2)));
     const u32 b = b0 + blockIdx.z;
     const size_t ctw = (size_t)2 * level * N;
     const size_t k = (size_t)blockIdx.y * N + (blockIdx.x * EW_THREADS + threadIdx.x) * 2;
-    const u64 q = mods[blockIdx.y % level].q;
+    const u64 q = mods[blockIdx.y < level ? blockIdx.y : blockIdx.y - level].q;
     vec_t v = *reinterpret_cast<const vec_t *>(base + (size_t)b * base_stride + k);
+    if (bias && blockIdx.y < level) {
+        const vec_t x = *reinterpret_cast<const vec_t *>(bias + (size_t)b * level * N + k);
+        v[0] = add_mod(v[0], x[0], q);
+        v[1] = add_mod(v[1], x[1], q);
+    }
     for (u32 r = (b + B - c0 % B) % B; r < cn; r += B) {
         const vec_t x = *reinterpret_cast<const vec_t *>(items + r * ctw + k);
         v[0] = add_mod(v[0], x[0], q);
@@ -422,14 +429,14 @@ __global__ __launch_bounds__(EW_THREADS) void add_rotations_kernel(u64 *y, const
     *reinterpret_cast<vec_t *>(y + (size_t)b * ctw + k) = v;
 }
 
-// c0 of block b (at y + b * y_stride) += bias[b]: blockIdx.y = limb, blockIdx.z = output block, two residues per thread
-__global__ __launch_bounds__(EW_THREADS) void add_bias_kernel(u64 *__restrict__ y, size_t y_stride,
+// c0 of block b of y [B][2][level][N] += bias[b]: blockIdx.y = limb, blockIdx.z = output block, two residues per thread
+__global__ __launch_bounds__(EW_THREADS) void add_bias_kernel(u64 *__restrict__ y,
                                                               const u64 *__restrict__ bias,
                                                               const ModConst *__restrict__ mods, u32 level, u32 N) {
     typedef u64 vec_t __attribute__((ext_vector_type(2)));
     const u32 k = (blockIdx.x * EW_THREADS + threadIdx.x) * 2, i = blockIdx.y, b = blockIdx.z;
     const u64 q = mods[i].q;
-    vec_t *dst = reinterpret_cast<vec_t *>(y + (size_t)b * y_stride + (size_t)i * N + k);
+    vec_t *dst = reinterpret_cast<vec_t *>(y + ((size_t)b * 2 * level + i) * N + k);
     const vec_t s = *reinterpret_cast<const vec_t *>(bias + ((size_t)b * level + i) * N + k);
     vec_t v = *dst;
     v[0] = add_mod(v[0], s[0], q);
@@ -1239,7 +1246,7 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
                 it.key = bk[q]->d_key;
                 it.dst = dst;
                 it.galois_elt = baby_g[q];
-                it.accumulate = 0;
+                it.add = nullptr;
             }
         }
         rc = switch_batch(P, level, items, n_it, d_work, stream);
@@ -1348,7 +1355,7 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
                 items[r].key = conj_key->d_key;
                 items[r].dst = d_ct_y + (size_t)r * ctw;
                 items[r].galois_elt = conj_key->galois_elt;
-                items[r].accumulate = 0;
+                items[r].add = nullptr;
                 items[r].balanced = 0;
             }
             rc = switch_batch(P, level, items, na, d_work, stream);
@@ -1360,31 +1367,23 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
     }
     // 3. giant steps: y_b = acc_{b,0} + sum_p rot(acc_{b,p}).  Where ModDown and rescale are one pass and at least one
     //    rotation needs a key, that pass writes the caller's buffer itself and y_b is assembled where acc_{b,0} lies;
-    //    otherwise y_b starts as a copy of acc_{b,0} in the output (or its full-level stand-in).
+    //    otherwise y_b starts as a copy of acc_{b,0} in the output (or its full-level stand-in).  The plain ModDown can write
+    //    elsewhere than it reads as well (`apart`: no copy); a conjugation behind it then adds its source itself.
     std::vector<u32> ps;                                      // giant rotations that are not a full turn
     for (u32 p = 1; p < N2; ++p)
         if (giant_g[p] != 1) ps.push_back(p);
     const bool in_place = fused_rescale && !ps.empty();
-    u64 *y_base = in_place ? d_acc : d_ct_y;
-    const size_t y_stride = in_place ? (size_t)N2 * ctw : ctw;
+    const bool apart = !in_place && merged && !ps.empty() && moddown_mid_ok(P, level);
+    const bool conj_after = conj_key && !conj_per_acc;
+    u64 *y_base = in_place || apart ? d_acc : d_ct_y;
+    const size_t y_stride = in_place || apart ? (size_t)N2 * ctw : ctw;
     const bool batched = !merged && !ps.empty();              // y_b starts in the first batch of rotations
-    for (u32 b0 = 0; !in_place && !batched && b0 < B; b0 += 65535) {
+    for (u32 b0 = 0; !in_place && !apart && !batched && b0 < B; b0 += 65535) {
         hipLaunchKernelGGL(copy_blocks_kernel, dim3((u32)(ctw / (2 * EW_THREADS)), 1, std::min<u32>(B - b0, 65535)),
                            dim3(EW_THREADS), 0, stream, d_ct_y + (size_t)b0 * ctw, d_acc + (size_t)b0 * N2 * ctw, ctw,
                            (size_t)N2 * ctw);
         CKKS_LAUNCH_CHECK("copy_blocks_kernel");
     }
-    auto add_bias = [&]() -> int {
-        for (u32 b0 = 0; w->d_bias && b0 < B; b0 += 65535) {
-            hipLaunchKernelGGL(add_bias_kernel, dim3(N / (2 * EW_THREADS), level, std::min<u32>(B - b0, 65535)),
-                               dim3(EW_THREADS), 0, stream, y_base + (size_t)b0 * y_stride, y_stride,
-                               w->d_bias + (size_t)b0 * level * N, P->d_mod, level, N);
-            CKKS_LAUNCH_CHECK("add_bias_kernel");
-        }
-        return CKKS_OK;
-    };
-    if (fused_rescale && (rc = add_bias())) return rc;      // the rescale needs the complete dropped limb
-    bool any_giant = false;
     u64 *d_u = d_acc + acc_w, *d_mdig = d_u + u_w;
     if (merged) {
         // rotations that are a full turn are plain additions; the others are grouped: the accumulators of a
@@ -1430,16 +1429,20 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
                                               half, stream);
                 if (rc) return rc;
             }
-            u64 *dsts[ROT_BATCH];
-            for (u32 r = 0; r < nb; ++r) dsts[r] = y_base + (size_t)(b0 + r) * y_stride;
-            any_giant = true;
-            if (fused_rescale) {
-                u64 *outs[ROT_BATCH];
-                for (u32 r = 0; r < nb; ++r) outs[r] = d_out_final + (size_t)(b0 + r) * (ctw - 2 * N);
-                rc = moddown_rescale(P, level, u_b, dsts, outs, nb, d_work, d_t, stream);
-            } else {
-                rc = moddown_add(P, level, u_b, dsts, nb, d_work, stream);
+            const u64 *zs[ROT_BATCH];
+            u64 *outs[ROT_BATCH];
+            for (u32 r = 0; r < nb; ++r) {
+                u64 *z = y_base + (size_t)(b0 + r) * y_stride;
+                zs[r] = z;
+                outs[r] = fused_rescale           ? d_out_final + (size_t)(b0 + r) * (ctw - 2 * N)
+                        : apart && !conj_after    ? d_ct_y + (size_t)(b0 + r) * ctw
+                                                  : z;
             }
+            if (fused_rescale)       // the bias before the ModDown: the rescale needs the complete dropped limb
+                rc = moddown_rescale(P, level, u_b, zs, w->d_bias ? w->d_bias + (size_t)b0 * level * N : nullptr, outs, nb,
+                                     d_work, d_t, stream);
+            else
+                rc = moddown_add(P, level, u_b, zs, outs, nb, d_work, stream);
             if (rc) return rc;
         }
     }
@@ -1447,6 +1450,7 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
     // lay.batch, rotation-major (neighbours share the key), into the area of the bank, which is free by now, and are
     // summed from there.  (One batch per rotation before, which with few blocks is a chain of small launches: a 64-wide
     // layer at N = 2^12 with 7 rotations of one block took 57 launches and 501 us, now 21 and 158 us.)
+    const bool bias_done = batched && !conj_after;            // the last batch adds it
     for (u64 c0 = 0; batched && c0 < (u64)ps.size() * B; c0 += batch) {
         const u32 cn = (u32)std::min<u64>(batch, (u64)ps.size() * B - c0);
         SwitchItem items[ROT_BATCH];
@@ -1461,7 +1465,7 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
             items[r].key = giant_keys[p - 1]->d_key;
             items[r].dst = d_bank + (size_t)r * ctw;
             items[r].galois_elt = giant_g[p];
-            items[r].accumulate = 0;
+            items[r].add = nullptr;
             items[r].balanced = 0;
         }
         rc = decompose(P, c1s, cn, level, d_digits, d_tmp, stream);
@@ -1471,7 +1475,8 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
         for (u32 b0 = 0; b0 < B; b0 += 65535) {
             hipLaunchKernelGGL(add_rotations_kernel, dim3(N / (2 * EW_THREADS), 2 * level, std::min<u32>(B - b0, 65535)),
                                dim3(EW_THREADS), 0, stream, d_ct_y, c0 ? d_ct_y : d_acc, c0 ? ctw : (size_t)N2 * ctw,
-                               d_bank, P->d_mod, level, N, b0, B, (u32)(c0 % B), cn);
+                               d_bank, bias_done && c0 + batch >= (u64)ps.size() * B ? w->d_bias : nullptr, P->d_mod, level, N, b0,
+                               B, (u32)(c0 % B), cn);
             CKKS_LAUNCH_CHECK("add_rotations_kernel");
         }
     }
@@ -1484,36 +1489,41 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
         }
     }
     // 3b. decomplexification: y_b += conj(y_b), one key switch per output block.  The switch gathers from
-    //     y_b while it writes, so it goes to the (now free) accumulator area first.
-    if (conj_key && !conj_per_acc) {
+    //     y_b while it writes: where y_b lies apart from its final place, it goes there, y_b added; otherwise to the (now
+    //     free) accumulator area first.
+    if (conj_after) {
         for (u32 b0 = 0; b0 < B; b0 += batch) {
             const u32 nb = std::min(batch, B - b0);
             SwitchItem items[ROT_BATCH];
             const u64 *c1s[ROT_BATCH];
-            for (u32 r = 0; r < nb; ++r) c1s[r] = d_ct_y + (size_t)(b0 + r) * ctw + (size_t)level * N;
+            for (u32 r = 0; r < nb; ++r) c1s[r] = y_base + (size_t)(b0 + r) * y_stride + (size_t)level * N;
             rc = decompose(P, c1s, nb, level, d_digits, d_tmp, stream);
             if (rc) return rc;
             for (u32 r = 0; r < nb; ++r) {
                 items[r].digits = d_digits + (size_t)r * dig_w;
-                items[r].c1 = d_ct_y + (size_t)(b0 + r) * ctw + (size_t)level * N;
-                items[r].c0 = d_ct_y + (size_t)(b0 + r) * ctw;
+                items[r].c1 = c1s[r];
+                items[r].c0 = c1s[r] - (size_t)level * N;
                 items[r].key = conj_key->d_key;
-                items[r].dst = d_acc + (size_t)r * ctw;
+                items[r].dst = apart ? d_ct_y + (size_t)(b0 + r) * ctw : d_acc + (size_t)r * ctw;
                 items[r].galois_elt = conj_key->galois_elt;
-                items[r].accumulate = 0;
+                items[r].add = apart ? items[r].c0 : nullptr;
                 items[r].balanced = 0;
             }
             rc = switch_batch(P, level, items, nb, d_work, stream);
             if (rc) return rc;
+            if (apart) continue;
             hipLaunchKernelGGL(add_rows_kernel, dim3(N / EW_THREADS, nb * 2 * level), dim3(EW_THREADS), 0, stream,
                                d_ct_y + (size_t)b0 * ctw, d_acc, P->d_mod, level, N);
             CKKS_LAUNCH_CHECK("add_rows_kernel");
         }
     }
     // 4. bias into c0 of every block; 5. rescale, unless the giant step's ModDown already did both
-    const bool rescaled = fused_rescale && any_giant;
-    if (!fused_rescale && (rc = add_bias())) return rc;
-    if (rescale && !rescaled) {
+    for (u32 b0 = 0; w->d_bias && !in_place && !bias_done && b0 < B; b0 += 65535) {
+        hipLaunchKernelGGL(add_bias_kernel, dim3(N / (2 * EW_THREADS), level, std::min<u32>(B - b0, 65535)), dim3(EW_THREADS), 0,
+                           stream, d_ct_y + (size_t)b0 * ctw, w->d_bias + (size_t)b0 * level * N, P->d_mod, level, N);
+        CKKS_LAUNCH_CHECK("add_bias_kernel");
+    }
+    if (rescale && !in_place) {
         for (u32 b0 = 0; b0 < B; b0 += RESCALE_CHUNK) {
             const u32 c = std::min(RESCALE_CHUNK, B - b0);
             rc = rescale_rows(P, d_ct_y + (size_t)b0 * ctw, level, 2 * c, d_out_final + (size_t)b0 * (ctw - 2 * N), d_t,

@@ -15,6 +15,14 @@ namespace ckks {
 typedef uint64_t u64;
 typedef uint32_t u32;
 
+// a / b for values that are the same in all lanes.  The compiler divides on the vector unit and keeps what follows from the
+// quotient there: row addresses as vector registers, formed and waited for lane by lane.
+__device__ __forceinline__ u32 uniform_div(u32 a, u32 b) {
+    u32 q = a / b;
+    asm("" : "+v"(q));                       // or the compiler sees that q is uniform and drops the move to a scalar
+    return __builtin_amdgcn_readfirstlane(q);
+}
+
 struct u128 {
     u64 lo, hi;
 };

@@ -128,7 +128,7 @@ __global__ __launch_bounds__((KIND_NT & WIDE) != 0 ? Tile<WIDE_RL>::THREADS : NT
     constexpr u32 RL = (KIND_NT & WIDE) != 0 ? WIDE_RL : 4;
     __shared__ u64 lds[LOGR ? 1 : Tile<RL>::WORDS];
     const u32 row = KIND == BOTH_ROWS ? gridDim.y - 1 - blockIdx.y : blockIdx.y;   // special limbs come last: start with them
-    const u32 limb = ids.id[row % n_limbs];
+    const u32 limb = ids.id[row - uniform_div(row, n_limbs) * n_limbs];
     if (limb == SKIP_ROW) return;
     const ModFp mf = modf[limb];
     if (KIND != BOTH_ROWS && (mf.ok != 0) != (KIND == FP_ROWS)) return;
