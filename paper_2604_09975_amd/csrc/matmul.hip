@@ -130,17 +130,23 @@ static inline PackedShape packed_shape(u32 N, u32 level, u32 GQ, u32 BP, bool wh
 // swizzle: workgroups go to the XCDs round-robin and each XCD has its own L2, so the linear workgroup id is unfolded to
 // let one XCD walk all (b,p) tiles of a run of coefficients back to back: the bank lines of that run are then fetched
 // into one L2 once.
-// What bounds it (QKV layer, 34.0 GB of records, 2.4 GB of bank, 1.8 GB of sums): memory.  8.43 ms (8.32 to 8.47 from card to
-// card); an earlier form that took 8.45 ms took 8.40 without the products, 4.36 without the record loads and 7.05 without the
+// SH = 2, 4 (packed stores; share_of): SH wavefronts of a workgroup take consecutive tiles of one chunk of 128 coefficients and
+// share its bank residues, two steps at a time, through LDS (16 KiB): each brings 1 / SH of them two steps ahead.  The bank then
+// crosses from L2 to the CUs once per SH tiles and is fetched into L2 less often; the records go past L2's replacement order
+// (7818 -> 7742 us).  Every wavefront of a workgroup runs every step, those beyond the last tile for the barriers alone.  (Waves
+// that read the bank through the vector L1 together, without LDS, take 12 to 19 ms.)
+// What bounds it (QKV layer, 34.0 GB of records, 2.4 GB of bank, 1.8 GB of sums): memory, 4.95 TB/s with SH = 4, 7.74 ms; 8.43
+// ms with a bank stream for each wavefront (8.32 to 8.47 from card to card), an earlier form of which, 8.45 ms, took 8.40 without the products, 4.36 without the record loads and 7.05 without the
 // bank loads (5.1 TB/s; a plain read reaches 5.3).  The kernel with a quotient per product was bound by fp64 issue: 8.66 ms
 // with the vector units 92 % busy; these sums keep them 55 % busy.
-template <bool SYM, bool PACKED, u32 NP>
+template <bool SYM, bool PACKED, u32 NP, u32 SH = 0>
 __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *__restrict__ bank,
                                                               const void *__restrict__ w, u64 *__restrict__ acc,
                                                               const ModFp *__restrict__ modf, LimbIds limbs,
                                                               u32 level, u32 N, u32 GQ, u32 BP, u32 swizzle,
                                                               u32 gq0, u32 gq1, u32 accumulate, u32 bp0, u32 bp1) {
     constexpr u32 CO = SYM ? 4 : 2, HV = CO / 2;                   // coefficients of a thread, pairs of them
+    constexpr int NTW = SH ? 2 : 0;                                // non-temporal
     typedef double dvec_t __attribute__((ext_vector_type(2)));
     typedef u64 vec_t __attribute__((ext_vector_type(2)));
     typedef u32 u32x2 __attribute__((ext_vector_type(2)));
@@ -153,8 +159,11 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
         tile = slot - d * gridDim.x;
         run = d * 8 + xcd;
     }
+    const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (SH) tile = tile * SH + wave % SH;
     const u32 bpt = (bp0 / TB + tile) * TB;                        // the tile's first pair
-    const u32 k = (run * MM_THREADS + threadIdx.x) * 2;            // SYM: k < N/2
+    const u32 k = SH ? (run * (4 / SH) + wave / SH) * REC_CHUNK + 2 * lane
+                     : (run * MM_THREADS + threadIdx.x) * 2;       // SYM: k < N/2
     const u32 kk[2] = {k, N - 2 - k};                              // SYM: the second holds the mirrors of k+1, k
     const u32 i = limbs.id[blockIdx.z];
     const size_t row = (size_t)i * N, w_stride = (size_t)level * N;
@@ -179,7 +188,10 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
                         a[t][c][2 * h + 1].l = (double)v[1];
                     }
     }
-    dvec_t x[2][2][HV];                                            // [step & 1][component]
+    dvec_t x[SH ? 1 : 2][2][HV];                                   // [step & 1][component]
+    constexpr u32 SHC = SH ? 4 / SH : 1, SEGS = 4 * HV, SEG = SHC * HV;   // chunks, segments of one, segments that a wavefront brings
+    __shared__ dvec_t xs[SH ? 2 : 1][SH ? SHC * SEGS * 64 : 1];    // [buffer][chunk][step][component][half][lane]
+    dvec_t xg[SEG];
     u32 wr[2][NP][6], wt[2][NP];                                   // two steps' weights as loaded, twice; four steps' top bits
     double wp[2][NP][2];                                           // two steps' weights, unpacked store
     // buffer loads: wavefront-uniform addresses stay in scalar registers, the lanes add 32-bit offsets; and a step outside
@@ -200,7 +212,32 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
             xp += w_stride;
         }
     };
-    const u32 lane = threadIdx.x & 63, top_shift = (lane & 1) * 4;
+    const u32 top_shift = (lane & 1) * 4;
+    const bool live = bpt < bp1;
+    // SH: segment wave * SEG + z of two steps' bank residues
+    auto fetch_shared = [&](u32 g2) {
+#pragma unroll
+        for (u32 z = 0; z < SEG; ++z) {
+            const u32 sg = wave * SEG + z, cw = sg / SEGS, st = sg / (2 * HV) % 2, c = sg / HV % 2, h = sg % HV, gq = 2 * g2 + st;
+            const u32 cb = (run * SHC + cw) * REC_CHUNK;
+            const int bytes = gq >= gq0 && gq < gq_end ? (int)(N * sizeof(double)) : 0;
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<double *>(bank + ((size_t)gq * 2 + c) * w_stride + row), 0, bytes, 0x00020000);
+            xg[z] = __builtin_bit_cast(dvec_t, __builtin_amdgcn_raw_buffer_load_b128(
+                                                   rs, (int)(lane * 16), (int)((h ? N - REC_CHUNK - cb : cb) * 8), 0));
+        }
+    };
+    auto keep_shared = [&](u32 buf) {
+#pragma unroll
+        for (u32 z = 0; z < SEG; ++z) xs[buf][(wave * SEG + z) * 64 + lane] = xg[z];
+    };
+    auto take_shared = [&](u32 buf, u32 st) {
+#pragma unroll
+        for (u32 c = 0; c < 2; ++c)
+#pragma unroll
+            for (u32 h = 0; h < HV; ++h)
+                x[0][c][h] = xs[buf][((wave / (SH ? SH : 1)) * SEGS + (st * 2 + c) * HV + h) * 64 + (h ? 63 - lane : lane)];
+    };
     const u32 chunk = __builtin_amdgcn_readfirstlane(k / REC_CHUNK), wpairs = ps.pairs(bpt);
     const unsigned char *wrec = reinterpret_cast<const unsigned char *>(w) + ps.rec(bpt, i, chunk, r_first);
     // pairs of the tile that are not summed here have no records: their loads return zeros without traffic
@@ -217,14 +254,14 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
                 unsigned char *const at = const_cast<unsigned char *>(wrec) + t * REC_BYTES;
                 const __amdgpu_buffer_rsrc_t rs =
                     __builtin_amdgcn_make_buffer_rsrc(at, 0, bytes_of(t, REC_BYTES, true), 0x00020000);
-                const u32x4 lo = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(lane * 16 + buf * 1024), 0, 0);
-                const u32x2 mid = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(lane * 8 + REC_MID + buf * 512), 0, 0);
+                const u32x4 lo = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(lane * 16 + buf * 1024), 0, NTW);
+                const u32x2 mid = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(lane * 8 + REC_MID + buf * 512), 0, NTW);
 #pragma unroll
                 for (u32 z = 0; z < 4; ++z) wr[buf][t][z] = lo[z];
                 wr[buf][t][4] = mid[0];
                 wr[buf][t][5] = mid[1];
                 if (buf == 0)
-                    wt[tbuf][t] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)((lane >> 1) * 4 + REC_TOP), 0, 0);
+                    wt[tbuf][t] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)((lane >> 1) * 4 + REC_TOP), 0, NTW);
             }
             if (buf == 1 && g2 + 1 < 2 * r_end) wrec += wpairs * REC_BYTES;   // the last record stays the last
         } else {
@@ -272,7 +309,7 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
 #pragma unroll
             for (u32 oo = 0; oo < 2 * CO; ++oo) {
                 const u32 o = s ? 2 * CO - 1 - oo : oo, c = o / CO, e = o % CO;
-                a[t][c][e].mac(x[s][c][e >> 1][e & 1], wd[e < 2 ? e : 3 - e]);
+                a[t][c][e].mac(x[SH ? 0 : s][c][e >> 1][e & 1], wd[e < 2 ? e : 3 - e]);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -287,6 +324,19 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
     };
     // two steps; the next two's weights are on their way before the products
     auto two_steps = [&](u32 buf, u32 tbuf, u32 g2) {
+        if (SH) {
+            fetch_shared(g2 + 1);
+            if (live) {
+                fetch_w(buf ^ 1, buf ? tbuf ^ 1 : tbuf, g2 + 1);
+                take_shared(buf, 0);
+                products(buf, tbuf, 0);
+                take_shared(buf, 1);
+                products(buf, tbuf, 1);
+            }
+            keep_shared(buf ^ 1);
+            __syncthreads();
+            return;
+        }
         if (PACKED) fetch_w(buf ^ 1, buf ? tbuf ^ 1 : tbuf, g2 + 1);
         products(buf, tbuf, 0);
         fetch_x(0, 2 * g2 + 2);
@@ -297,8 +347,14 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
     // whole records of four steps, whatever the range: 8 products between two folds
     if (r_first < r_end) {
         fetch_w(0, 0, 2 * r_first);
-        fetch_x(0, 4 * r_first);
-        fetch_x(1, 4 * r_first + 1);
+        if (SH) {
+            fetch_shared(2 * r_first);
+            keep_shared(0);
+            __syncthreads();
+        } else {
+            fetch_x(0, 4 * r_first);
+            fetch_x(1, 4 * r_first + 1);
+        }
     }
     for (u32 r = r_first; r < r_end; r += 2) {
         two_steps(0, 0, 2 * r);
@@ -376,6 +432,23 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
                 }
         }
     }
+}
+
+// Wavefronts that share a chunk's bank residues, by the store (1: half records, 2: whole limbs) and the tiles of the launch:
+// four where at most a third more wavefronts go out than have pairs, two for an even number of tiles of whole limbs that would
+// waste more than a fifth by four, 1 (each its own) otherwise, for launches that leave CUs idle, and for whole limbs whose bank
+// the Infinity Cache holds.  us, own / two / four, tiles in brackets:
+//   half records: 2^16 [18] 8417 / 8027 / 7737, [10] 1649 / 1587 / 1548, [9] 1499 / 1478 / 1442, [7] 1168 / 1174 / 1103, [5] 863 /
+//     862 / 903, [3] 1158 / 1192 / 1079, [2] 231 / 229 / 232; 2^15 [6] 266 / 250 / 245, [4] 186 / 172 / 160, [3] 158 / 148 / 132;
+//     2^14 [4] 54 / 56 / 47, [3] 49 / 49 / 42; 2^13 [4] (96 workgroups) 12.1 / 14.0 / 13.8.  Two spill registers there.
+//   whole limbs: 2^15 [8] 1433 / 1340 / 1341, [7] 1295 / 1248 / 1203, [6] 605 / 556 / 590, [5] 951 / 953 / 1015, [4] 768 / 708 / 715,
+//     [3] 625 / 614 / 569; 2^16 [3] 917 / 918 / 865, [2] 667 / 618 / 648; a small bank, 2^14 [6] 63.1 / 65.1 / 65.1, 2^13 [4] 10.8 /
+//     13.1 / 12.9.
+static u32 share_of(u32 store, u32 tiles, u32 N, u32 n_limbs, bool small_bank) {
+    const u32 four = (tiles + 3) / 4 * 4, chunks = N / REC_CHUNK / (store == 1 ? 2 : 1);
+    if ((store != 1 && (store != 2 || small_bank)) || tiles < 2 || (u64)(four / 4) * chunks * n_limbs < 256) return 1;
+    if (store == 2 && tiles % 2 == 0 && 5 * four > 6 * tiles) return 2;
+    return 3 * four <= 4 * tiles ? 4 : 1;
 }
 
 // An input ciphertext as the bank entry of the identity rotation: balanced doubles on primes below 2^50, as it is on
@@ -1304,6 +1377,10 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
     hipLaunchKernelGGL((diag_mac_kernel<SYM, PACKED, NP>), dim3(tiles4, RUNS, n_fp), dim3(MM_THREADS), 0, stream,  \
                        bank, WPTR, d_acc, P->d_modf, fp_limbs, level, N, GQ, BP, (RUNS) % 8 == 0 ? 1u : 0u, q0,    \
                        q1, add, bp0, bp1)
+#define MM_SHARED(SYM, S, RUNS, WPTR)                                                                              \
+    hipLaunchKernelGGL((diag_mac_kernel<SYM, true, TB, S>), dim3((tiles4 + S - 1) / S, RUNS, n_fp), dim3(MM_THREADS), 0,     \
+                       stream, bank, WPTR, d_acc, P->d_modf, fp_limbs, level, N, GQ, BP, (RUNS) % 8 == 0 ? 1u : 0u, q0, q1,  \
+                       add, bp0, bp1)
 #define MM_LAUNCH_PAIRS(SYM, RUNS, WPTR)                                                                           \
     do {                                                                                                           \
         if (few && in_tile == 1)                                                                                   \
@@ -1313,7 +1390,14 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
         else                                                                                                       \
             MM_LAUNCH(SYM, true, TB, RUNS, WPTR);                                                                  \
     } while (0)
-                if (w->block_packed[grp] == 1)
+                const u32 share = share_of(w->block_packed[grp], tiles4, N, n_fp, few);
+                if (w->block_packed[grp] == 1 && share == 4)
+                    MM_SHARED(true, 4, N / 256, w->d_wp);
+                else if (w->block_packed[grp] == 2 && share == 4)
+                    MM_SHARED(false, 4, N / 128, w->d_wpf);
+                else if (w->block_packed[grp] == 2 && share == 2)
+                    MM_SHARED(false, 2, N / 256, w->d_wpf);
+                else if (w->block_packed[grp] == 1)
                     MM_LAUNCH_PAIRS(true, runs, w->d_wp);
                 else if (w->block_packed[grp] == 2)
                     MM_LAUNCH_PAIRS(false, gen_runs, w->d_wpf);
@@ -1321,6 +1405,7 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
                     MM_LAUNCH(true, false, TB, runs, w->d_w);
                 else
                     MM_LAUNCH(false, false, TB, gen_runs, w->d_w);
+#undef MM_SHARED
 #undef MM_LAUNCH_PAIRS
 #undef MM_LAUNCH
                 g0 = g1;

@@ -483,3 +483,34 @@ def test_arena_of_a_projection(L, dnum, C, N1, G, B_out):
     assert one <= got <= max(one * 5 // 4, one + (256 << 20))
     assert N2 > 1 or got == one
     w.close()
+
+
+@pytest.mark.parametrize("logN,level,C,G,B_out,N1,kinds", [(14, 5, 4, 3, 6, 2, "r"), (14, 5, 4, 3, 5, 2, "r"), (14, 4, 4, 5, 13, 2, "r"),
+                                                            (14, 5, 4, 3, 7, 2, "gr"),          # general inputs, then a real one
+                                                            (16, 4, 2, 66, 4, 1, "g"), (16, 4, 2, 66, 6, 1, "g"),
+                                                            (16, 4, 2, 67, 5, 1, "g")])
+def test_wavefronts_that_share_the_bank(logN, level, C, G, B_out, N1, kinds):
+    """Launches of 256 workgroups and more whose wavefronts share bank residues by four (three and seven tiles, the last ones short,
+    steps behind the last whole record) and by two; kinds of the input groups, the first letter for all but the last of two."""
+    import oracle
+    B = _B()
+    O = oracle.Oracle(logN, oracle.find_primes(50, logN, level), oracle.find_primes(60, logN, 2), 1 if level > 8 else level)
+    P = B.ckks_params_create(O.logN, O.q, O.p, O.dnum)
+    r = W.rng(logN + G + B_out)
+    m, N2 = O.n // 8, C // N1
+    diag = r.integers(-1 << 40, 1 << 40, (B_out, N2, G, N1, O.N))
+    for g in range(G):
+        if kinds[0 if g + 1 < G or len(kinds) == 1 else 1] == "r":
+            diag[:, :, g] = make_real(diag[:, :, g])
+    top = np.array(O.q, dtype=np.uint64)[:, None] - np.uint64(1)
+    x = W.uniform_residues(r, O.q, O.N, lead=(G, 2))
+    x = np.where(r.integers(0, 5, x.shape) == 0, top, x)
+    steps = [q * m for q in range(1, N1)], [p * N1 * m for p in range(1, N2)]
+    keys = [[W.uniform_residues(r, O.moduli, O.N, lead=(O.dnum, 2)) for _ in s] for s in steps]
+    baby, giant = [[B.ckks_galois_key_load(P, O.galois_elt(s), to_dev(k)) for s, k in zip(ss, kk)] for ss, kk in zip(steps, keys)]
+    w = B.ckks_weights_create(P, level, m, C, G, B_out, N1)
+    B.ckks_weights_set_diagonals(w, 0, to_dev(diag.reshape(-1, O.N)))
+    got = to_host(B.ckks_ctpt_matmul(P, w, to_dev(x), baby, giant)[0])
+    for b in (0, B_out - 1):
+        want = O.ctpt_matmul(level, m, G, B_out, N1, N2, diag, None, 0, x, keys[0], keys[1], b_first=b, b_count=1)
+        assert (got[b] == want[b]).all(), b
