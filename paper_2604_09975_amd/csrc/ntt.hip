@@ -100,20 +100,18 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_pass_kernel(u64 *__restrict__
 // LOGR: 1 .. 5 = pass A of N = 2^(12+LOGR) (its first / last LOGR stages, registers only; a thread takes 16 residues,
 // i.e. 16 >> LOGR columns, so that short rows keep as many loads in flight per wavefront as long ones), 0 = pass B (12
 // stages in a 4096 tile)
-// KIND: the kernel serves the rows whose prime is below 2^50 (FP_ROWS: fp64 butterflies), the others (INT_ROWS: integer
-// butterflies), rows of the other kind returning at once, or both.  A launch that does not fill the chip (BOTH_MAX
-// workgroups) is bound by the latency of one workgroup, and two of them one after the other take twice that (the digits of
-// one ciphertext at level 17 of 24 + 8 primes: 17 + 25 us; a whole rotation 182 us with two launches, 166 us with one).  The
-// line stands where one kernel with the union of the two register budgets lost a wavefront per SIMD in pass B (130
-// registers, against 112 to 124).  As pass B is now (72 and 92 registers, against 66 to 90) one launch is no slower above it
-// either: mixed rows by two launches and by one, forward, inverse, us: 4096 workgroups at 2^16 123 / 109, 130 / 114, 2560 at
-// 2^15 94 / 73, 98 / 74, 2080 at 2^12 77 / 50, 82 / 51 (the line has not been moved).
+// KIND: the rows' primes are all below 2^50 (FP_ROWS: fp64 butterflies), all above (INT_ROWS: integer butterflies) or of
+// both kinds (BOTH_ROWS).  One launch for rows of both kinds at every size: a launch each, the workgroups of the other kind
+// returning at once, costs the latency of a workgroup twice where the chip is not full (the digits of one ciphertext at level
+// 17 of 24 + 8 primes 17 + 25 us) and its last waves twice where it is, and the union of the two register budgets (pass B 90
+// and 98, against 72 and 70 of the fp64 butterflies) keeps the wavefronts that the LDS tile admits.  Two launches and one,
+// transform of 50- and 60-bit rows, forward, us: 4096 workgroups at 2^16 112 / 105, 26624 650 / 629, 2560 at 2^15 78 / 63,
+// 10240 279 / 251, 2560 and 12800 at 2^14 103 / 68 and 513 / 333, 16000 at 2^13 683 / 418, 3072 at 2^17 93 / 83; inverse alike.
 constexpr int INT_ROWS = 0, FP_ROWS = 1, BOTH_ROWS = 2;
 // + STREAMED: residues go past the caches' replacement order (arrays above STREAM_BYTES): a pass uses each once, and the
 // twiddles, as many bytes as a tile and shared by the rows of a limb, stay in L2.  64 x 24 rows at 2^16: tile pass 409 ->
 // 383 us, column pass 273 -> 250.  Below that the next pass finds them there: 25 x 14 rows at 2^16 164 us, streamed 182.
 constexpr int STREAMED = 4;
-constexpr u32 BOTH_MAX = 2048;
 constexpr int WIDE = 8;                      // + WIDE: tiles by 1024 threads (pass B only)
 template <bool INV, u32 LOGR, int KIND_NT>
 __global__ __launch_bounds__((KIND_NT & WIDE) != 0 ? Tile<WIDE_RL>::THREADS : NTT_THREADS) void ntt_fast_kernel(u64 *__restrict__ data,
@@ -131,7 +129,6 @@ __global__ __launch_bounds__((KIND_NT & WIDE) != 0 ? Tile<WIDE_RL>::THREADS : NT
     const u32 limb = ids.id[row - uniform_div(row, n_limbs) * n_limbs];
     if (limb == SKIP_ROW) return;
     const ModFp mf = modf[limb];
-    if (KIND != BOTH_ROWS && (mf.ok != 0) != (KIND == FP_ROWS)) return;
     u64 *poly = data + ((size_t)row << logN);
     auto load = [&](u32 idx) { return NT ? __builtin_nontemporal_load(poly + idx) : poly[idx]; };
     auto store = [&](u32 idx, u64 v) {
@@ -176,23 +173,23 @@ static void launch_fast(const ckks_params *p, u64 *d_data, const LimbIds &ids, u
                        p->d_mod, scaled_dn ? p->d_modf_dn : p->d_modf, INV ? p->d_tws_inv : p->d_tws_fwd,            \
                        INV ? p->d_twf_inv : p->d_twf_fwd, scaled_dn ? p->d_ninvs_dn : p->d_ninvs, ids, n_limbs,      \
                        p->logN)
-    if (LOGR == 0 && wide_tiles((u64)blocks * rows)) {
-        constexpr int W = LOGR == 0 ? WIDE : 0;
-        if (any_fp && any_int) {
-            FAST_LAUNCH(BOTH_ROWS + W);
-        } else {
-            if (any_fp) FAST_LAUNCH(FP_ROWS + W);
-            if (any_int) FAST_LAUNCH(INT_ROWS + W);
-        }
-    } else if (any_fp && any_int && (u64)blocks * rows <= BOTH_MAX) {
-        FAST_LAUNCH(BOTH_ROWS);
-    } else if ((u64)rows * p->N * sizeof(u64) > STREAM_BYTES) {
-        if (any_fp) FAST_LAUNCH(FP_ROWS + STREAMED);
-        if (any_int) FAST_LAUNCH(INT_ROWS + STREAMED);
-    } else {
-        if (any_fp) FAST_LAUNCH(FP_ROWS);
-        if (any_int) FAST_LAUNCH(INT_ROWS);
-    }
+#define FAST_LAUNCH_KIND(F)                                                                                          \
+    do {                                                                                                             \
+        if (any_fp && any_int)                                                                                       \
+            FAST_LAUNCH(BOTH_ROWS + (F));                                                                            \
+        else if (any_fp)                                                                                             \
+            FAST_LAUNCH(FP_ROWS + (F));                                                                              \
+        else if (any_int)                                                                                            \
+            FAST_LAUNCH(INT_ROWS + (F));                                                                             \
+    } while (0)
+    constexpr int W = LOGR == 0 ? WIDE : 0;
+    if (LOGR == 0 && wide_tiles((u64)blocks * rows))
+        FAST_LAUNCH_KIND(W);
+    else if ((u64)rows * p->N * sizeof(u64) > STREAM_BYTES)
+        FAST_LAUNCH_KIND(STREAMED);
+    else
+        FAST_LAUNCH_KIND(0);
+#undef FAST_LAUNCH_KIND
 #undef FAST_LAUNCH
 }
 

@@ -61,6 +61,27 @@ def test_either_side_of_the_wide_tiles(logN, ids, batch):
         assert (to_host(d) == O.ntt_batch(x, ids, inverse=inverse)).all()
 
 
+@pytest.mark.parametrize("logN,batch", [(12, 700), (14, 300), (14, 720)])
+def test_many_rows_of_both_kinds(logN, batch):
+    """More than 2048 workgroups of rows below and above 2^50 in one launch, cached and (the last, 270 MiB) streamed: the
+    words that separate calls for the primes of each kind give, and the oracle's in the first and the last polynomial."""
+    B = _B()
+    O = helpers.small_oracle(logN, L=3, K=2, dnum=3, qbits=50, pbits=60)
+    _, P = make_pair(O)
+    ids = [4, 0, 1]
+    x = W.uniform_residues(W.rng(batch), [O.moduli[i] for i in ids], O.N, lead=(batch,))
+    for inverse in (False, True):
+        f = B.ckks_intt if inverse else B.ckks_ntt
+        d = to_dev(x)
+        parts = [d[:, :1].clone(), d[:, 1:].clone()]
+        f(P, d, ids, batch)
+        for part, own in zip(parts, (ids[:1], ids[1:])):
+            f(P, part, own, batch)
+        assert torch.equal(d, torch.cat(parts, dim=1))
+        ends = np.stack([x[0], x[-1]])
+        assert (to_host(d[[0, batch - 1]]) == O.ntt_batch(ends, ids, inverse=inverse)).all()
+
+
 def test_toy_ring_bit_exact():
     B = _B()
     O, P = make_pair(W.TOY_RING)
