@@ -108,7 +108,8 @@ struct ckks_params {
     std::map<ckks::u32, ckks::LevelTables> levels;
     // tables of complex-slot encode / decode (built on first use), one after the other: decode twiddles [N/2] complex,
     // entry h + j, j < h: exp(2*pi*i*(5^j mod 8h)/(8h)); encode twiddles [N] complex, entry h + j: exp(-2*pi*i*j/(2h)); twist
-    // [N] complex: exp(-i*pi*k/N); bins [N/2] u32: (5^j mod 2N - 1)/2; column order of encode's scratch rows [256] u32
+    // [N] complex: exp(-i*pi*k/N); bins [N/2] u32: (5^j mod 2N - 1)/2; column order of encode's scratch rows [256] u32,
+    // in which entries of h >= 256 lie too (N > 2^12)
     double *d_fft = nullptr;
     // private scratch arena
     void *d_scratch = nullptr;

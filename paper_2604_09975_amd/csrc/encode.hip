@@ -14,17 +14,20 @@
 // change by one, and with it every residue of a weight or message that a program encodes again.  These are the operations
 // of a plain radix-2 FFT in their order, so the integers are the same whatever the passes are.)
 //
-// Two passes over 4096-element tiles each, 16 elements per thread, at most four stages (radix 16) between exchanges
-// through LDS:
+// Two passes over 4096-element tiles each, 16 elements per thread and at most four stages (radix 16) between exchanges
+// through LDS in decode, 8 and three in encode:
 //   far:  the stages of half length 256 and more, on columns (elements 256 apart); slots on one side, scratch on the other.
 //   near: the stages of half length up to 128, on 16 runs of 256 elements that lie a sixteenth of the array apart: then the
 //         tile's k = bitrev(p) form runs of 16, a 128-byte line of the coefficients on the other side.
 // Encode's far pass finds its columns by their slots: t_j mod 256 depends on j mod 128 alone, so the columns of COLS/2
 // neighbouring j mod 128 are read from whole lines of slots, and the columns 255 - (t mod 256) are their conjugates.  It
-// leaves column (group, member) at place group * COLS + member of the scratch rows.
+// leaves column (group, member) at place group * COLS + member of the scratch rows, and reads twiddles laid out by place:
+// by column, each lane's lies in a cache line of its own, and the pass waits for the lines (96 vectors at N = 2^16: the two
+// launches 50.6 us, 37.6 so).
 // A pass reads and writes every element once, and nothing else touches memory.  Short rings: one workgroup per vector.
 // Off the server's hot path.  96 real vectors at N = 2^16: 308 us with permutation, transform, twist and rounding in
-// five kernels, 92 us now; 5 vectors decoded at N = 2^15: 45 us, 14 us now.
+// five kernels, 75 us now (0.3 GB past the caches: 60 at the rate of a copy); 5 vectors decoded at N = 2^15: 45 us, 12 us now.
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -35,8 +38,13 @@
 
 namespace ckks {
 
-constexpr u32 FFT_THREADS = 256;
 constexpr u32 FFT_TILE = 4096;
+// Threads of a workgroup.  Two tiles fit a CU's LDS, so a wavefront count per SIMD of 2 with 16 elements per thread and of 4
+// with 8, for one exchange more (3 + 3 + 2 stages instead of 4 + 4).  Encode, us, 16 and 8 elements per thread: 1 / 40 / 200
+// vectors at 2^13 12.3 / 14.5 / 63 and 10.6 / 13.0 / 56, 4 / 96 at 2^15 14.1 / 58.0 and 13.1 / 55.5, 16 / 200 at 2^16
+// 28.5 / 210 and 25.4 / 191.  Decode's far pass gains nothing by it: 1 / 5 / 64 vectors at 2^15 10.9 / 12.0 / 22.3 and
+// 11.2 / 12.1 / 22.9, 200 at 2^16 132 and 131.
+constexpr u32 FFT_THREADS = 256, ENC_THREADS = 512;
 constexpr u32 ENC_CHUNK = 64;         // vectors transformed per scratch chunk (N = 2^16: 64 MiB for encode)
 // tile element i: one pad element after 16 and one after 256, so that runs of 16, strides of 16 and strides of 256 all
 // fall on distinct banks.  70 KB: two workgroups per CU.
@@ -284,16 +292,16 @@ __global__ __launch_bounds__(FFT_THREADS) void decode_small_kernel(double2 *__re
 // Far pass of encode: slots -> scratch (columns in the order of their slots).  N = 256 << S rows of 256.
 // bin[j] = t_j.  grid: x = group of 4096 >> S columns, y = vector
 template <u32 S>
-__global__ __launch_bounds__(FFT_THREADS) void encode_far_kernel(const double2 *__restrict__ slots,
+__global__ __launch_bounds__(ENC_THREADS, 4) void encode_far_kernel(const double2 *__restrict__ slots,
                                                                  double2 *__restrict__ out,
                                                                  const double2 *__restrict__ tw,
                                                                  const u32 *__restrict__ bin, u32 real) {
-    constexpr u32 COLS = FFT_TILE >> S, SC = COLS / 2, ROWS = 1u << S, N = 256u << S, TPC = ROWS / 16;
+    constexpr u32 COLS = FFT_TILE >> S, SC = COLS / 2, ROWS = 1u << S, N = 256u << S, TPC = ROWS / 8;
     __shared__ double2 tile[FFT_LDS];
     const double2 *src = slots + (size_t)blockIdx.y * (N / 2) + blockIdx.x * SC;
 #pragma unroll
-    for (u32 l = 0; l < FFT_TILE / 2 / FFT_THREADS; ++l) {
-        const u32 idx = threadIdx.x + FFT_THREADS * l, x = idx % SC, j = x + 128 * (idx / SC);
+    for (u32 l = 0; l < FFT_TILE / 2 / ENC_THREADS; ++l) {
+        const u32 idx = threadIdx.x + ENC_THREADS * l, x = idx % SC, j = x + 128 * (idx / SC);
         double2 z = src[j];
         if (real) z.y = 0.0;
         const u32 row = bin[blockIdx.x * SC + j] >> 8;
@@ -302,78 +310,92 @@ __global__ __launch_bounds__(FFT_THREADS) void encode_far_kernel(const double2 *
     }
     __syncthreads();
     const u32 col = threadIdx.x % COLS, q = threadIdx.x / COLS;              // q < TPC
-    const u32 t0 = bin[blockIdx.x * SC + col % SC] & 255, pcol = col < SC ? t0 : 255 - t0;
-    double2 *dst = out + (size_t)blockIdx.y * N + blockIdx.x * COLS + col;
-    // G stages on row bits B0 .. B0+G-1: a thread takes 16 >> G of the 2^(S-G) combinations of the other row bits
-    auto group = [&](auto b0, auto g, bool last) {
+    const u32 place = blockIdx.x * COLS + col;                               // as the twiddles lie
+    double2 *dst = out + (size_t)blockIdx.y * N + place;
+    // G stages on row bits B0 .. B0+G-1: a thread takes 8 >> G of the 2^(S-G) combinations of the other row bits
+    auto group = [&](auto b0, auto g) {
         constexpr u32 B0 = decltype(b0)::value, G = decltype(g)::value, R = 1u << G;
-        double2 v[16];
+        double2 v[8];
         auto row = [&](u32 m, u32 r) {
             const u32 o = q + TPC * m;
             return ((o >> B0) << (B0 + G)) + (r << B0) + (o & ((1u << B0) - 1));
         };
 #pragma unroll
-        for (u32 m = 0; m < (16u >> G); ++m) {
+        for (u32 m = 0; m < (8u >> G); ++m) {
 #pragma unroll
             for (u32 r = 0; r < R; ++r) v[m * R + r] = tile[fft_slot(row(m, r) * COLS + col)];
-            fft_group<G, true>(v + m * R, tw, 256u << B0, ((q + TPC * m) & ((1u << B0) - 1)) * 256 + pcol);
+            fft_group<G, true>(v + m * R, tw, 256u << B0, ((q + TPC * m) & ((1u << B0) - 1)) * 256 + place);
         }
 #pragma unroll
-        for (u32 m = 0; m < (16u >> G); ++m)
+        for (u32 m = 0; m < (8u >> G); ++m)
 #pragma unroll
             for (u32 r = 0; r < R; ++r) {
-                if (last)
+                if (B0 == 0)
                     dst[row(m, r) * 256] = v[m * R + r];
                 else
                     tile[fft_slot(row(m, r) * COLS + col)] = v[m * R + r];                 // a thread's own slots
             }
-        if (!last) __syncthreads();
+        if (B0 != 0) __syncthreads();
     };
     using std::integral_constant;
-    group(integral_constant<u32, S - 4>(), integral_constant<u32, 4>(), S == 4);
-    if constexpr (S > 8) {
-        group(integral_constant<u32, S - 8>(), integral_constant<u32, 4>(), false);
-        group(integral_constant<u32, 0>(), integral_constant<u32, S - 8>(), true);
-    } else if constexpr (S > 4) {
-        group(integral_constant<u32, 0>(), integral_constant<u32, S - 4>(), true);
+    group(integral_constant<u32, S - 3>(), integral_constant<u32, 3>());
+    if constexpr (S > 6) {
+        group(integral_constant<u32, S - 6>(), integral_constant<u32, 3>());
+        group(integral_constant<u32, 0>(), integral_constant<u32, S - 6>());
+    } else {
+        group(integral_constant<u32, 0>(), integral_constant<u32, S - 3>());
     }
 }
 
 // Near pass of encode: scratch -> coefficients.  colmap[place] = the column at that place of a scratch row.
 // grid: x = N / 4096, y = vector
-__global__ __launch_bounds__(FFT_THREADS) void encode_near_kernel(const double2 *__restrict__ scratch,
-                                                                  const double2 *__restrict__ tw,
-                                                                  const u32 *__restrict__ colmap, EncodeOut coef,
-                                                                  u32 logN) {
+__global__ __launch_bounds__(ENC_THREADS, 4) void encode_near_kernel(const double2 *__restrict__ scratch,
+                                                                     const double2 *__restrict__ tw,
+                                                                     const u32 *__restrict__ colmap, EncodeOut coef,
+                                                                     u32 logN) {
     __shared__ double2 tile[FFT_LDS];
-    const u32 tid = threadIdx.x, h = tid >> 4, c = tid & 15, f = blockIdx.x, fb = logN - 12;
-    const double2 *v0 = scratch + ((size_t)blockIdx.y << logN) + (f << 8) + tid;
+    const u32 tid = threadIdx.x, f = blockIdx.x, fb = logN - 12;
     coef.c += (size_t)blockIdx.y << logN;
-    const u32 lo = colmap[tid];
-    double2 v[16];
+    double2 v[8];
+    {
+        const u32 place = tid & 255, odd = tid >> 8, lo = colmap[place];
+        const double2 *v0 = scratch + ((size_t)blockIdx.y << logN) + (f << 8) + place;
 #pragma unroll
-    for (u32 r = 0; r < 16; ++r) v[r] = v0[(size_t)r << (fb + 8)];                     // run r
+        for (u32 r = 0; r < 8; ++r) v[r] = v0[(size_t)(2 * r + odd) << (fb + 8)];      // run 2r + odd
 #pragma unroll
-    for (u32 r = 0; r < 16; ++r) tile[fft_slot(r * 256 + lo)] = v[r];
+        for (u32 r = 0; r < 8; ++r) tile[fft_slot((2 * r + odd) * 256 + lo)] = v[r];
+    }
     __syncthreads();
+    const u32 run = tid >> 5 << 8, c = tid & 31;                                       // half a wavefront per run
+    // 3, 3 and 2 of the 8 stages
+    auto first = [&](u32 r) { return fft_slot(run + c + 32 * r); };
+    auto second = [&](u32 r) { return fft_slot(run + (c >> 2) * 32 + (c & 3) + 4 * r); };
+    auto third = [&](u32 r) { return fft_slot(run + c * 8 + r); };
 #pragma unroll
-    for (u32 r = 0; r < 16; ++r) v[r] = tile[fft_slot(h * 256 + c + 16 * r)];
-    fft_group<4, true>(v, tw, 16, c);
+    for (u32 r = 0; r < 8; ++r) v[r] = tile[first(r)];
+    fft_group<3, true>(v, tw, 32, c);
 #pragma unroll
-    for (u32 r = 0; r < 16; ++r) tile[fft_slot(h * 256 + c + 16 * r)] = v[r];          // a thread's own slots
+    for (u32 r = 0; r < 8; ++r) tile[first(r)] = v[r];                                 // a thread's own slots
+    exchange_sync<64>();
+#pragma unroll
+    for (u32 r = 0; r < 8; ++r) v[r] = tile[second(r)];
+    fft_group<3, true>(v, tw, 4, c & 3);
+#pragma unroll
+    for (u32 r = 0; r < 8; ++r) tile[second(r)] = v[r];                                // a thread's own slots
+    exchange_sync<64>();
+#pragma unroll
+    for (u32 r = 0; r < 8; ++r) v[r] = tile[third(r)];
+    fft_group<2, true>(v, tw, 1, 0);
+    fft_group<2, true>(v + 4, tw, 1, 0);
+#pragma unroll
+    for (u32 r = 0; r < 8; ++r) tile[third(r)] = v[r];                                 // a thread's own slots
     __syncthreads();
+    // thread (m & 31, hh = low bits) writes k = m 2^(logN-8) + ..., element lo = bitrev8(m) of run bitrev4(hh)
+    const u32 h = tid >> 4, hh = tid & 15, ch = __brev(hh) >> 28, fk = (fb ? __brev(f) >> (32 - fb) : 0) * 16 + hh;
 #pragma unroll
-    for (u32 r = 0; r < 16; ++r) v[r] = tile[fft_slot(h * 256 + c * 16 + r)];
-    fft_group<4, true>(v, tw, 1, 0);
-#pragma unroll
-    for (u32 r = 0; r < 16; ++r) tile[fft_slot(h * 256 + c * 16 + r)] = v[r];          // a thread's own slots
-    __syncthreads();
-    // thread (m & 15 = h, hh = c) writes k = m 2^(logN-8) + ..., element lo = bitrev8(m) of run bitrev4(hh)
-    const u32 ch = __brev(c) >> 28, fk = (fb ? __brev(f) >> (32 - fb) : 0) * 16 + c;
-#pragma unroll
-    for (u32 r = 0; r < 16; ++r) {
-        const u32 m = h + 16 * r;
-        if (coef.real && r >= 8) break;                                                // k >= N/2
+    for (u32 r = 0; r < 8; ++r) {
+        const u32 m = h + 32 * r;
+        if (coef.real && r >= 4) break;                                                // k >= N/2
         coef.put((m << (logN - 8)) + fk, tile[fft_slot(ch * 256 + (__brev(m) >> 24))]);
     }
 }
@@ -448,6 +470,12 @@ static int fft_tables(ckks_params *P) {
         for (u32 pl = 0; pl < 256; ++pl) {
             const u32 x = pl % cols, t0 = bin[pl / cols * sc + x % sc] & 255;
             colmap[pl] = x < sc ? t0 : 255 - t0;
+        }
+        std::vector<double> row(512);
+        for (u32 b = 1; b < N / 256; ++b) {
+            double *w = enc + 512 * (size_t)b;
+            std::copy(w, w + 512, row.begin());
+            for (u32 pl = 0; pl < 256; ++pl) std::copy_n(row.begin() + 2 * colmap[pl], 2, w + 2 * pl);
         }
     }
     double *d = nullptr;
@@ -526,7 +554,7 @@ int ckks_encode(ckks_params_t *P, const double *d_slots, uint32_t count, double 
         int64_t *coeffs = d_coeffs + (size_t)done * N;
         const EncodeOut out{aside ? (int64_t *)v : coeffs, ft.twist, N, real, scale / N};
 #define FAR_LAUNCH(S)                                                                                                \
-    hipLaunchKernelGGL(encode_far_kernel<S>, dim3(1u << (S - 4), c), dim3(FFT_THREADS), 0, stream, slots, v, ft.enc, \
+    hipLaunchKernelGGL(encode_far_kernel<S>, dim3(1u << (S - 4), c), dim3(ENC_THREADS), 0, stream, slots, v, ft.enc, \
                        ft.bin, real)
         switch (P->logN) {
             case 13: FAR_LAUNCH(5); break;
@@ -542,7 +570,7 @@ int ckks_encode(ckks_params_t *P, const double *d_slots, uint32_t count, double 
         CKKS_LAUNCH_CHECK("encode_far_kernel");
         if (aside) CKKS_HIP(hipMemcpyAsync(coeffs, v, (size_t)c * N * sizeof(u64), hipMemcpyDeviceToDevice, stream));
         if (P->logN > 12) {
-            hipLaunchKernelGGL(encode_near_kernel, dim3(N / FFT_TILE, c), dim3(FFT_THREADS), 0, stream, v, ft.enc,
+            hipLaunchKernelGGL(encode_near_kernel, dim3(N / FFT_TILE, c), dim3(ENC_THREADS), 0, stream, v, ft.enc,
                                ft.colmap, out, P->logN);
             CKKS_LAUNCH_CHECK("encode_near_kernel");
         }

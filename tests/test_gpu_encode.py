@@ -283,3 +283,45 @@ def test_decode_is_no_further_from_exact_than_an_n_point_transform(logN):
     ours = float(np.sqrt(np.mean((got.real - er) ** 2 + (got.imag - ei) ** 2)))
     theirs = float(np.sqrt(np.mean((r2 - er) ** 2 + (i2 - ei) ** 2)))
     assert ours <= theirs, (ours / theirs, logN)
+
+
+def _encode_n_point(z, scale, real):
+    """Coefficients by the plain radix-2 decimation-in-frequency transform of N points, one rounding per operation."""
+    n = z.shape[-1]
+    N, k = 2 * n, np.arange(2 * n)
+    pi = np.longdouble("3.14159265358979323846264338327950288")
+    wr, wi = np.cos(2 * pi * k[:n] / N).astype(np.float64), (-np.sin(2 * pi * k[:n] / N)).astype(np.float64)
+    e, at = 1, np.empty(n, dtype=np.int64)
+    for j in range(n):
+        at[j], e = (e - 1) >> 1, e * 5 % (2 * N)
+    re, im = np.empty((2, len(z), N))
+    x, y = z.real, np.zeros(z.shape) if real else z.imag
+    re[:, at], im[:, at], re[:, N - 1 - at], im[:, N - 1 - at] = x, y, x, -y
+    h = n
+    while h >= 1:
+        a, b = (v.reshape(len(z), -1, 2, h) for v in (re, im))
+        xr, xi, dr, di = a[:, :, 0] + a[:, :, 1], b[:, :, 0] + b[:, :, 1], a[:, :, 0] - a[:, :, 1], b[:, :, 0] - b[:, :, 1]
+        cr, ci = wr[::n // h], wi[::n // h]
+        a[:, :, 0], b[:, :, 0], a[:, :, 1], b[:, :, 1] = xr, xi, dr * cr - di * ci, dr * ci + di * cr
+        h //= 2
+    place = _bitrev(N.bit_length() - 1)
+    re, im = re[:, place], im[:, place]
+    tr, ti = np.cos(pi * k / N).astype(np.float64), (-np.sin(pi * k / N)).astype(np.float64)
+    m = np.rint((re * tr - im * ti) * (scale / N)).astype(np.int64)
+    if real:
+        m[:, n] = 0
+        m[:, n + 1:] = -m[:, 1:n][:, ::-1]
+    return m
+
+
+@pytest.mark.parametrize("logN,count", [(12, 2), (13, 65), (14, 3), (15, 2), (16, 2), (17, 1)])
+def test_encode_has_the_bits_of_a_plain_transform(logN, count):
+    """Whatever the passes are.  At a scale of 2^56 a coefficient holds the last bits of its double: one operation in another
+    order shows."""
+    from paper_2604_09975_amd import binding as B
+    O = helpers.small_oracle(logN, L=3, K=1, dnum=3, qbits=50, pbits=57)
+    _, P = make_pair(O)
+    z = _slots(W.rng(logN), count, O.n)
+    for flags in (0, B.ENCODE_REAL):
+        got = B.ckks_encode(P, _cdev(z), 2.0 ** 56, flags).cpu().numpy()
+        assert (got == _encode_n_point(z, 2.0 ** 56, bool(flags))).all()
