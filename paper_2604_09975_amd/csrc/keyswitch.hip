@@ -413,7 +413,7 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void modup_tile_kernel(const u64
 //      arrive once for both): exact sums of 25-bit pieces of y, onto the ciphertext primes by mid_convert, onto the special
 //      primes with factors in 30-bit parts and one Montgomery reduction of the recombined 90-bit sum -> LDS;
 //   3. wavefront t: the columns of target t from LDS, first forward round (fp64 or integer butterflies), out.
-// A wavefront per row has the row's twiddles, modulus and addresses in scalar registers: 124 vector registers for digits of
+// A wavefront per row has the row's twiddles, modulus and addresses in scalar registers: 114 vector registers for digits of
 // eight limbs, which two such workgroups per CU leave.  With 32 threads per row (tiles of 512 coefficients, 256 threads) it is
 // 148 and 186 registers with the quotient and the folding butterflies, two or three wavefronts per SIMD for four: 32
 // ciphertexts of 24 limbs 421 and 444 us, 365 now.
@@ -809,9 +809,9 @@ __global__ __launch_bounds__(KS_THREADS) void merged_ip_kernel(MergedRot rots, c
 // Bound by the chain of a workgroup's loads, transform and gather (two workgroups of 512 threads per CU hide each other's)
 // and by the integer butterflies of the special limbs.  RL = 3: eight residues a thread, whose sums, keys and transform fit
 // the 128 registers that two workgroups leave (RL = 4 takes 200 and more; any spilling costs more than the fusion gives: 2.98
-// ms where this takes 1.81).  A digit's key loads are issued before the barrier in front of its products; the next digit
+// ms where this took 1.81).  A digit's key loads are issued before the barrier in front of its products; the next digit
 // loaded there as well spills or gains nothing.  QKV projection, 63 rotations of 24 + 8 limbs: 1.43 ms of tile passes and
-// 1.04 of merged_ip_kernel before, 1.81 now (the call 17.05 -> 16.38 ms).
+// 1.04 of merged_ip_kernel before, 1.81 in one (the call 17.05 -> 16.38 ms), 1.58 with the folding butterflies.
 template <u32 RL>
 __global__ __launch_bounds__(Tile<RL>::THREADS, 4) void merged_tile_kernel(MergedRot rots, const u64 *__restrict__ digits,
                                                                         size_t dig_w, const u64 *__restrict__ c0_base,
@@ -1713,7 +1713,7 @@ static u32 build_pack(const SwitchItem *items, u32 n, ItemPack &pack) {
 
 // A workgroup of merged_tile_kernel is a chain of all rotations and digits, so few of them leave the chip idle that long, and 512
 // fit at a time.  Workgroups (ring, ciphertexts, digits), whole calls with 15 rotations, separate tile passes /
-// merged_tile_kernel, us:
+// merged_tile_kernel, us (before butterflies on 60-bit primes that fold, which shorten a chain more than a tile pass):
 //   up to three digits: 256 (2^15, 2, 3) 767 / 826, 288 (2^13, 12, 2) 675 / 656, 312 (2^15, 3, 3) 864 / 907, 320 (2^16, 1, 2)
 //     851 / 821, 384 (2^15, 3, 3) 1033 / 988, 512 (2^14, 16, 3) 1606 / 1109, 544 (2^14, 17, 3) 1720 / 1171;
 //   more digits, of few ciphertexts: longer chains, beside a separate kernel that reads a key once for three ciphertexts: 320

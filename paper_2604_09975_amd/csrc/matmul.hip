@@ -138,7 +138,7 @@ static inline PackedShape packed_shape(u32 N, u32 level, u32 GQ, u32 BP, bool wh
 // What bounds it (QKV layer, 34.0 GB of records, 2.4 GB of bank, 1.8 GB of sums): memory, 4.95 TB/s with SH = 4, 7.74 ms; 8.43
 // ms with a bank stream for each wavefront (8.32 to 8.47 from card to card), an earlier form of which, 8.45 ms, took 8.40 without the products, 4.36 without the record loads and 7.05 without the
 // bank loads (5.1 TB/s; a plain read reaches 5.3).  The kernel with a quotient per product was bound by fp64 issue: 8.66 ms
-// with the vector units 92 % busy; these sums keep them 55 % busy.
+// with the vector units 92 % busy; these sums keep them 62 % busy.
 template <bool SYM, bool PACKED, u32 NP, u32 SH = 0>
 __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *__restrict__ bank,
                                                               const void *__restrict__ w, u64 *__restrict__ acc,

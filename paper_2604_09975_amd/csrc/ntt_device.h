@@ -35,12 +35,13 @@ struct Tile {
 // its operands, then for each round's twiddles and exchange.  With 1024 threads four wavefronts share the wait, every load
 // of the operands is on its way at once, and the operands of a key switch's last pass arrive during its transform.
 // 512 workgroups of 1024 threads are two per CU, which is what runs at a time of the kernels of up to 64 registers (the
-// transforms, gather_intt, the rescales).  us with 256 threads, with wide tiles up to 512 and up to 1024 workgroups:
+// transforms, gather_intt, the rescales).  us with 256 threads, with wide tiles up to 512 and up to 1024 workgroups (calls as
+// long as they were when the line was drawn):
 // ip_intt_kernel of 7 switches at 2^12 (14 workgroups) 19.3 -> 11.5; whole calls: toy projection at 2^12 145 / 112 / 112,
 // product and rescale at 2^15 (12 + 4 primes) 130 / 104 / 104, one rotation at 2^16, level 17 (544 and 928 workgroups in two of
 // its kernels) 154 / 137 / 143, 24 switches and 12 rescales at 2^14 (960 in one) 165 / 146 / 155.  512 threads with 8
 // residues: 113, 105, 140, 151.
-// ip_intt_kernel (82 registers) and passb_final_kernel (128) run one such workgroup per CU, so from 257 on there are two
+// ip_intt_kernel (76 registers) and passb_final_kernel (103 to 106) run one such workgroup per CU, so from 257 on there are two
 // rounds of them.  The first is the faster one all the same: calls of 320 / 480 / 512 workgroups in it (five switches at 2^15,
 // 30 at 2^14, two at 2^16) 83.7 / 127.0 / 87.3 us, by 256 threads from 257 on 87.6 / 133.4 / 90.1.  The second is not always,
 // 0.5 to 2.9 % of a call either way: one rotation at 2^16, levels 9 / 12 / 16 (288 / 384 / 512 in it) 91.6 / 93.2 / 96.6, by 256
