@@ -289,6 +289,20 @@ __global__ __launch_bounds__(FFT_THREADS) void decode_small_kernel(double2 *__re
         out[(size_t)blockIdx.x * n + i] = make_double2(tile[i].x * inv_scale, tile[i].y * inv_scale);
 }
 
+// Workgroup -> tile x of vector y.  Workgroups go to the XCDs round-robin, each of which has its own L2: every eight vectors
+// are dealt to the eight, all tiles of one to the same, which find each other's lines of slots and scratch there and complete
+// each other's lines of coefficients (a mirrored run k -> N - k crosses lines).  Without and with, us: 40 / 96 / 200 general
+// vectors at 2^14 17.2 / 37.5 / 75.7 and 13.8 / 30.3 / 63.0, at 2^15 28.9 / 51.5 / 107 and 23.7 / 48.0 / 94.8, 16 / 96 at
+// 2^16 22.7 / 78.2 and 20.4 / 77.8; 2^17 the same.  The vectors after the last eight: in order.
+__device__ __forceinline__ void encode_place(u32 &x, u32 &y) {
+    x = blockIdx.x, y = blockIdx.y;
+    if (y >= (gridDim.y & ~7u)) return;
+    const u32 lin = y * gridDim.x + x, slot = lin >> 3;
+    y = uniform_div(slot, gridDim.x);
+    x = slot - y * gridDim.x;
+    y = y * 8 + (lin & 7);
+}
+
 // Far pass of encode: slots -> scratch (columns in the order of their slots).  N = 256 << S rows of 256.
 // bin[j] = t_j.  grid: x = group of 4096 >> S columns, y = vector
 template <u32 S>
@@ -298,20 +312,22 @@ __global__ __launch_bounds__(ENC_THREADS, 4) void encode_far_kernel(const double
                                                                  const u32 *__restrict__ bin, u32 real) {
     constexpr u32 COLS = FFT_TILE >> S, SC = COLS / 2, ROWS = 1u << S, N = 256u << S, TPC = ROWS / 8;
     __shared__ double2 tile[FFT_LDS];
-    const double2 *src = slots + (size_t)blockIdx.y * (N / 2) + blockIdx.x * SC;
+    u32 grp, vec;
+    encode_place(grp, vec);
+    const double2 *src = slots + (size_t)vec * (N / 2) + grp * SC;
 #pragma unroll
     for (u32 l = 0; l < FFT_TILE / 2 / ENC_THREADS; ++l) {
         const u32 idx = threadIdx.x + ENC_THREADS * l, x = idx % SC, j = x + 128 * (idx / SC);
         double2 z = src[j];
         if (real) z.y = 0.0;
-        const u32 row = bin[blockIdx.x * SC + j] >> 8;
+        const u32 row = bin[grp * SC + j] >> 8;
         tile[fft_slot(row * COLS + x)] = z;
         tile[fft_slot((ROWS - 1 - row) * COLS + SC + x)] = make_double2(z.x, -z.y);
     }
     __syncthreads();
     const u32 col = threadIdx.x % COLS, q = threadIdx.x / COLS;              // q < TPC
-    const u32 place = blockIdx.x * COLS + col;                               // as the twiddles lie
-    double2 *dst = out + (size_t)blockIdx.y * N + place;
+    const u32 place = grp * COLS + col;                                      // as the twiddles lie
+    double2 *dst = out + (size_t)vec * N + place;
     // G stages on row bits B0 .. B0+G-1: a thread takes 8 >> G of the 2^(S-G) combinations of the other row bits
     auto group = [&](auto b0, auto g) {
         constexpr u32 B0 = decltype(b0)::value, G = decltype(g)::value, R = 1u << G;
@@ -354,12 +370,14 @@ __global__ __launch_bounds__(ENC_THREADS, 4) void encode_near_kernel(const doubl
                                                                      const u32 *__restrict__ colmap, EncodeOut coef,
                                                                      u32 logN) {
     __shared__ double2 tile[FFT_LDS];
-    const u32 tid = threadIdx.x, f = blockIdx.x, fb = logN - 12;
-    coef.c += (size_t)blockIdx.y << logN;
+    const u32 tid = threadIdx.x, fb = logN - 12;
+    u32 f, vec;
+    encode_place(f, vec);
+    coef.c += (size_t)vec << logN;
     double2 v[8];
     {
         const u32 place = tid & 255, odd = tid >> 8, lo = colmap[place];
-        const double2 *v0 = scratch + ((size_t)blockIdx.y << logN) + (f << 8) + place;
+        const double2 *v0 = scratch + ((size_t)vec << logN) + (f << 8) + place;
 #pragma unroll
         for (u32 r = 0; r < 8; ++r) v[r] = v0[(size_t)(2 * r + odd) << (fb + 8)];      // run 2r + odd
 #pragma unroll

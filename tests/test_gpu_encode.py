@@ -314,7 +314,7 @@ def _encode_n_point(z, scale, real):
     return m
 
 
-@pytest.mark.parametrize("logN,count", [(12, 2), (13, 65), (14, 3), (15, 2), (16, 2), (17, 1)])
+@pytest.mark.parametrize("logN,count", [(12, 2), (13, 65), (14, 3), (14, 11), (15, 8), (16, 2), (17, 1)])
 def test_encode_has_the_bits_of_a_plain_transform(logN, count):
     """Whatever the passes are.  At a scale of 2^56 a coefficient holds the last bits of its double: one operation in another
     order shows."""
