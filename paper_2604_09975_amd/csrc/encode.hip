@@ -147,17 +147,35 @@ struct DecodeIn {
     __device__ __forceinline__ double2 get(const Raw &w) const { return make_double2(lift(w.a0, w.a1), lift(w.b0, w.b1)); }
 };
 
+// Workgroup -> tile x of vector y.  Workgroups go to the XCDs round-robin, each of which has its own L2: every eight vectors
+// are dealt to the eight, all tiles of one to the same, which find each other's lines of slots and scratch there and complete
+// each other's lines of coefficients (a mirrored run k -> N - k crosses lines).  Encode without and with, us: 40 / 96 / 200 general
+// vectors at 2^14 17.2 / 37.5 / 75.7 and 13.8 / 30.3 / 63.0, at 2^15 28.9 / 51.5 / 107 and 23.7 / 48.0 / 94.8, 16 / 96 at
+// 2^16 22.7 / 78.2 and 20.4 / 77.8; 2^17 the same.  Decode, for eight vectors and more at 2^14 to
+// 2^16: 64 vectors at 2^14 15.9 and 13.6, 40 at 2^15 17.9 and 14.6, 16 / 200 at 2^16 18.4 / 104 and 13.8 / 100; at 2^13, where
+// a vector is one tile, and for fewer vectors the step costs 1 to 3 %, at 2^17 it gives 20 % of 16 and takes 2 % of 40.  The
+// vectors after the last eight: in order.
+__device__ __forceinline__ void deal_vectors(u32 &x, u32 &y) {
+    if (y >= (gridDim.y & ~7u)) return;
+    const u32 lin = y * gridDim.x + x, slot = lin >> 3;
+    y = uniform_div(slot, gridDim.x);
+    x = slot - y * gridDim.x;
+    y = y * 8 + (lin & 7);
+}
+
 // Far pass of decode: scratch -> slots, times inv_scale.  n = 256 << S.
 // grid: x = group of 4096 >> S columns, y = vector
-template <u32 S>
+template <u32 S, bool DEAL>
 __global__ __launch_bounds__(FFT_THREADS) void decode_far_kernel(const double2 *__restrict__ in, double2 *__restrict__ out,
                                                                  const double2 *__restrict__ tw, double inv_scale) {
     constexpr u32 COLS = FFT_TILE >> S, LOW = S - 4, SUB = 1u << LOW, n = 256u << S;
     __shared__ double2 tile[FFT_LDS];
+    u32 grp = blockIdx.x, vec = blockIdx.y;
+    if (DEAL) deal_vectors(grp, vec);
     const u32 col = threadIdx.x % COLS, q = threadIdx.x / COLS;              // q < SUB
-    const u32 pcol = blockIdx.x * COLS + col;
-    const double2 *src = in + (size_t)blockIdx.y * n + pcol;
-    double2 *dst = out + (size_t)blockIdx.y * n + pcol;
+    const u32 pcol = grp * COLS + col;
+    const double2 *src = in + (size_t)vec * n + pcol;
+    double2 *dst = out + (size_t)vec * n + pcol;
     double2 v[16];
     // rows (q + SUB * m) * SUB + r, r < SUB: the low row bits; rows r * SUB + q: the top four
     auto low_row = [&](u32 e) { return (q + SUB * (e >> LOW)) * SUB + (e & (SUB - 1)); };
@@ -179,13 +197,16 @@ __global__ __launch_bounds__(FFT_THREADS) void decode_far_kernel(const double2 *
 }
 
 // Near pass of decode: residues -> scratch.  grid: x = n / 4096, y = vector
+template <bool DEAL>
 __global__ __launch_bounds__(FFT_THREADS) void decode_near_kernel(double2 *__restrict__ scratch,
                                                                   const double2 *__restrict__ tw, DecodeIn coef,
                                                                   size_t coef_stride, u32 logn) {
     __shared__ double2 tile[FFT_LDS];
-    const u32 tid = threadIdx.x, h = tid >> 4, c = tid & 15, f = blockIdx.x, fb = logn - 12;
-    double2 *v0 = scratch + ((size_t)blockIdx.y << logn) + (((h << fb) + f) << 8);     // run h of the tile
-    coef.r += blockIdx.y * coef_stride;
+    const u32 tid = threadIdx.x, h = tid >> 4, c = tid & 15, fb = logn - 12;
+    u32 f = blockIdx.x, vec = blockIdx.y;
+    if (DEAL) deal_vectors(f, vec);
+    double2 *v0 = scratch + ((size_t)vec << logn) + (((h << fb) + f) << 8);     // run h of the tile
+    coef.r += vec * coef_stride;
     // coefficient side: thread (m & 15 = h, hh = c) holds element lo = bitrev8(m) of run bitrev4(hh), k as below
     const u32 ch = __brev(c) >> 28, fk = (fb ? __brev(f) >> (32 - fb) : 0) * 16 + c;
     auto side = [&](u32 r) { return fft_slot(ch * 256 + (__brev(h + 16 * r) >> 24)); };
@@ -216,11 +237,14 @@ __global__ __launch_bounds__(FFT_THREADS) void decode_near_kernel(double2 *__res
 // The same by 1024 threads with four elements each: the same operations on the same values, two stages at a time instead of
 // four, with all of a thread's coefficients and twiddles on their way at once and, a run belonging to one wavefront, no
 // barrier behind the first exchange.
+template <bool DEAL>
 __global__ __launch_bounds__(1024) void decode_near_wide_kernel(double2 *__restrict__ scratch, const double2 *__restrict__ tw,
                                                                 DecodeIn coef, size_t coef_stride, u32 logn) {
     __shared__ double2 tile[FFT_LDS];
-    const u32 tid = threadIdx.x, f = blockIdx.x, fb = logn - 12;
-    coef.r += blockIdx.y * coef_stride;
+    const u32 tid = threadIdx.x, fb = logn - 12;
+    u32 f = blockIdx.x, vec = blockIdx.y;
+    if (DEAL) deal_vectors(f, vec);
+    coef.r += vec * coef_stride;
     {
         const u32 h = tid >> 4, c = tid & 15, ch = __brev(c) >> 28, fk = (fb ? __brev(f) >> (32 - fb) : 0) * 16 + c;
         DecodeIn::Raw w[4];
@@ -230,7 +254,7 @@ __global__ __launch_bounds__(1024) void decode_near_wide_kernel(double2 *__restr
         for (u32 r = 0; r < 4; ++r) tile[fft_slot(ch * 256 + (__brev(h + 64 * r) >> 24))] = coef.get(w[r]);
     }
     const u32 run = tid >> 6, lane = tid & 63;
-    double2 *v0 = scratch + ((size_t)blockIdx.y << logn) + (((run << fb) + f) << 8);
+    double2 *v0 = scratch + ((size_t)vec << logn) + (((run << fb) + f) << 8);
     double2 w[4][3];                                               // of the halves 4^k and 2 4^k
 #pragma unroll
     for (u32 k = 0; k < 4; ++k) {
@@ -289,20 +313,6 @@ __global__ __launch_bounds__(FFT_THREADS) void decode_small_kernel(double2 *__re
         out[(size_t)blockIdx.x * n + i] = make_double2(tile[i].x * inv_scale, tile[i].y * inv_scale);
 }
 
-// Workgroup -> tile x of vector y.  Workgroups go to the XCDs round-robin, each of which has its own L2: every eight vectors
-// are dealt to the eight, all tiles of one to the same, which find each other's lines of slots and scratch there and complete
-// each other's lines of coefficients (a mirrored run k -> N - k crosses lines).  Without and with, us: 40 / 96 / 200 general
-// vectors at 2^14 17.2 / 37.5 / 75.7 and 13.8 / 30.3 / 63.0, at 2^15 28.9 / 51.5 / 107 and 23.7 / 48.0 / 94.8, 16 / 96 at
-// 2^16 22.7 / 78.2 and 20.4 / 77.8; 2^17 the same.  The vectors after the last eight: in order.
-__device__ __forceinline__ void encode_place(u32 &x, u32 &y) {
-    x = blockIdx.x, y = blockIdx.y;
-    if (y >= (gridDim.y & ~7u)) return;
-    const u32 lin = y * gridDim.x + x, slot = lin >> 3;
-    y = uniform_div(slot, gridDim.x);
-    x = slot - y * gridDim.x;
-    y = y * 8 + (lin & 7);
-}
-
 // Far pass of encode: slots -> scratch (columns in the order of their slots).  N = 256 << S rows of 256.
 // bin[j] = t_j.  grid: x = group of 4096 >> S columns, y = vector
 template <u32 S>
@@ -312,8 +322,8 @@ __global__ __launch_bounds__(ENC_THREADS, 4) void encode_far_kernel(const double
                                                                  const u32 *__restrict__ bin, u32 real) {
     constexpr u32 COLS = FFT_TILE >> S, SC = COLS / 2, ROWS = 1u << S, N = 256u << S, TPC = ROWS / 8;
     __shared__ double2 tile[FFT_LDS];
-    u32 grp, vec;
-    encode_place(grp, vec);
+    u32 grp = blockIdx.x, vec = blockIdx.y;
+    deal_vectors(grp, vec);
     const double2 *src = slots + (size_t)vec * (N / 2) + grp * SC;
 #pragma unroll
     for (u32 l = 0; l < FFT_TILE / 2 / ENC_THREADS; ++l) {
@@ -371,8 +381,8 @@ __global__ __launch_bounds__(ENC_THREADS, 4) void encode_near_kernel(const doubl
                                                                      u32 logN) {
     __shared__ double2 tile[FFT_LDS];
     const u32 tid = threadIdx.x, fb = logN - 12;
-    u32 f, vec;
-    encode_place(f, vec);
+    u32 f = blockIdx.x, vec = blockIdx.y;
+    deal_vectors(f, vec);
     coef.c += (size_t)vec << logN;
     double2 v[8];
     {
@@ -639,14 +649,17 @@ int ckks_decode(ckks_params_t *P, const uint64_t *d_res, uint32_t nlimbs, uint32
         const u32 c = std::min(chunk, count - done);
         double2 *slots = (double2 *)d_slots + (size_t)done * n;
         const DecodeIn in{d_res + done * stride, n, nlimbs, q0, q1, q0inv, m1, q0inv_fp, nlimbs > 1 ? 1.0 / (double)q1 : 0.0};
+        const bool deal = c >= 8 && P->logN >= 14 && P->logN <= 16;      // see deal_vectors
 #define FAR_LAUNCH(S)                                                                                                \
-    hipLaunchKernelGGL(decode_far_kernel<S>, dim3(1u << (S - 4), c), dim3(FFT_THREADS), 0, stream, v, slots, ft.dec, \
-                       1.0 / scale)
+    hipLaunchKernelGGL((deal ? decode_far_kernel<S, true> : decode_far_kernel<S, false>), dim3(1u << (S - 4), c),     \
+                       dim3(FFT_THREADS), 0, stream, v, slots, ft.dec, 1.0 / scale)
         if (n >= FFT_TILE) {
             // a workgroup of either kind per CU or less: 5 / 16 / 32 / 64 vectors at 2^15 (20 to 256 workgroups) 14.5 / 15.9 /
             // 20.3 / 24.5 us by 256 threads, 13.6 / 14.5 / 18.1 / 22.6 by 1024; 48 at 2^16 (384) 28.8 and 29.8
             const bool wide = n / FFT_TILE * c <= 256;
-            hipLaunchKernelGGL(wide ? decode_near_wide_kernel : decode_near_kernel, dim3(n / FFT_TILE, c),
+            hipLaunchKernelGGL(wide ? (deal ? decode_near_wide_kernel<true> : decode_near_wide_kernel<false>)
+                               : (deal ? decode_near_kernel<true> : decode_near_kernel<false>),
+                               dim3(n / FFT_TILE, c),
                                dim3(wide ? 1024 : FFT_THREADS), 0, stream, v, ft.dec, in, stride, logn);
             CKKS_LAUNCH_CHECK("decode_near_kernel");
         }
