@@ -214,17 +214,18 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
     };
     const u32 top_shift = (lane & 1) * 4;
     const bool live = bpt < bp1;
-    // SH: segment wave * SEG + z of two steps' bank residues
+    // SH: segment wave * SEG + z of two steps' bank residues.  A step outside the range must read zeros here too: the records are
+    // of four steps whatever the range, so these residues alone keep its weights out of the sum.  The descriptor is the
+    // chunk's own, with no scalar offset, which need not take part in the range check
     auto fetch_shared = [&](u32 g2) {
 #pragma unroll
         for (u32 z = 0; z < SEG; ++z) {
             const u32 sg = wave * SEG + z, cw = sg / SEGS, st = sg / (2 * HV) % 2, c = sg / HV % 2, h = sg % HV, gq = 2 * g2 + st;
             const u32 cb = (run * SHC + cw) * REC_CHUNK;
-            const int bytes = gq >= gq0 && gq < gq_end ? (int)(N * sizeof(double)) : 0;
+            const int bytes = gq >= gq0 && gq < gq_end ? (int)(REC_CHUNK * sizeof(double)) : 0;
             const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<double *>(bank + ((size_t)gq * 2 + c) * w_stride + row), 0, bytes, 0x00020000);
-            xg[z] = __builtin_bit_cast(dvec_t, __builtin_amdgcn_raw_buffer_load_b128(
-                                                   rs, (int)(lane * 16), (int)((h ? N - REC_CHUNK - cb : cb) * 8), 0));
+                const_cast<double *>(bank + ((size_t)gq * 2 + c) * w_stride + row + (h ? N - REC_CHUNK - cb : cb)), 0, bytes, 0x00020000);
+            xg[z] = __builtin_bit_cast(dvec_t, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(lane * 16), 0, 0));
         }
     };
     auto keep_shared = [&](u32 buf) {

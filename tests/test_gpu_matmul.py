@@ -488,10 +488,14 @@ def test_arena_of_a_projection(L, dnum, C, N1, G, B_out):
 @pytest.mark.parametrize("logN,level,C,G,B_out,N1,kinds", [(14, 5, 4, 3, 6, 2, "r"), (14, 5, 4, 3, 5, 2, "r"), (14, 4, 4, 5, 13, 2, "r"),
                                                             (14, 5, 4, 3, 7, 2, "gr"),          # general inputs, then a real one
                                                             (16, 4, 2, 66, 4, 1, "g"), (16, 4, 2, 66, 6, 1, "g"),
-                                                            (16, 4, 2, 67, 5, 1, "g")])
+                                                            (16, 4, 2, 67, 5, 1, "g"),
+                                                            # the border of the two kinds inside a record of four steps
+                                                            (14, 5, 4, 4, 3, 1, "gr"), (14, 5, 4, 4, 7, 1, "rg"),
+                                                            (16, 4, 2, 72, 4, 1, "gr"), (16, 4, 2, 72, 6, 1, "gr")])
 def test_wavefronts_that_share_the_bank(logN, level, C, G, B_out, N1, kinds):
     """Launches of 256 workgroups and more whose wavefronts share bank residues by four (three and seven tiles, the last ones short,
-    steps behind the last whole record) and by two; kinds of the input groups, the first letter for all but the last of two."""
+    steps behind the last whole record) and by two; kinds of the input groups, the first letter for all but the last of two, where
+    either launch masks the other's steps of a record they share."""
     import oracle
     B = _B()
     O = oracle.Oracle(logN, oracle.find_primes(50, logN, level), oracle.find_primes(60, logN, 2), 1 if level > 8 else level)
