@@ -495,7 +495,7 @@ def test_arena_of_a_projection(L, dnum, C, N1, G, B_out):
 def test_wavefronts_that_share_the_bank(logN, level, C, G, B_out, N1, kinds):
     """Launches of 256 workgroups and more whose wavefronts share bank residues by four (three and seven tiles, the last ones short,
     steps behind the last whole record) and by two; kinds of the input groups, the first letter for all but the last of two, where
-    either launch masks the other's steps of a record they share."""
+    either launch masks the other's steps of a record they share.  Every output block: each wavefront of a workgroup takes a tile."""
     import oracle
     B = _B()
     O = oracle.Oracle(logN, oracle.find_primes(50, logN, level), oracle.find_primes(60, logN, 2), 1 if level > 8 else level)
@@ -515,6 +515,6 @@ def test_wavefronts_that_share_the_bank(logN, level, C, G, B_out, N1, kinds):
     w = B.ckks_weights_create(P, level, m, C, G, B_out, N1)
     B.ckks_weights_set_diagonals(w, 0, to_dev(diag.reshape(-1, O.N)))
     got = to_host(B.ckks_ctpt_matmul(P, w, to_dev(x), baby, giant)[0])
-    for b in (0, B_out - 1):
-        want = O.ctpt_matmul(level, m, G, B_out, N1, N2, diag, None, 0, x, keys[0], keys[1], b_first=b, b_count=1)
+    want = O.ctpt_matmul(level, m, G, B_out, N1, N2, diag, None, 0, x, keys[0], keys[1])
+    for b in range(B_out):
         assert (got[b] == want[b]).all(), b
