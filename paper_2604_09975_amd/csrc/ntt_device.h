@@ -543,8 +543,13 @@ __device__ __forceinline__ void pass_b_inv_from_lds(const F &f, u32 logN, u64 *l
 #pragma unroll
     for (u32 j = 0; j < TL::R; ++j) v[j] = f.from_bits(lds[RN::slot(j)]);
     round_inv<RL, 0>(f, v, logN, blockIdx.x, tw0, logN == 12);
+    if (logN == 12) {                                                // one branch: not one per residue
 #pragma unroll
-    for (u32 j = 0; j < TL::R; ++j) store(base + RN::elem(j), logN == 12 ? f.out(v[j]) : f.half(v[j]));
+        for (u32 j = 0; j < TL::R; ++j) store(base + RN::elem(j), f.out(v[j]));
+    } else {
+#pragma unroll
+        for (u32 j = 0; j < TL::R; ++j) store(base + RN::elem(j), f.half(v[j]));
+    }
 }
 
 // Whole pass with coalesced stores (forward) / coalesced loads (inverse).
