@@ -113,8 +113,14 @@ constexpr int INT_ROWS = 0, FP_ROWS = 1, BOTH_ROWS = 2;
 // 383 us, column pass 273 -> 250.  Below that the next pass finds them there: 25 x 14 rows at 2^16 164 us, streamed 182.
 constexpr int STREAMED = 4;
 constexpr int WIDE = 8;                      // + WIDE: tiles by 1024 threads (pass B only)
+// WAVES per SIMD of pass A at 2^17, forward: the butterflies of three kinds of primes take 170 registers, 168 leave a third
+// wavefront (two to four constants spilled).  us with two and three: 8 rows of 60-bit primes, batches of 5 / 12, 47.2 / 92.8 and
+// 42.7 / 90.4, of 61 and 60 bits, 5: 58.3 and 55.2; batches of 1 to 3 up to 2 % the other way.  Inverse (171) it gains as much
+// at a batch of 5 and loses as much at 1.
+template <bool INV, u32 LOGR>
+constexpr u32 WAVES = LOGR == 5 && !INV ? 3 : 1;
 template <bool INV, u32 LOGR, int KIND_NT>
-__global__ __launch_bounds__((KIND_NT & WIDE) != 0 ? Tile<WIDE_RL>::THREADS : NTT_THREADS) void ntt_fast_kernel(u64 *__restrict__ data,
+__global__ __launch_bounds__((KIND_NT & WIDE) != 0 ? Tile<WIDE_RL>::THREADS : NTT_THREADS, (WAVES<INV, LOGR>)) void ntt_fast_kernel(u64 *__restrict__ data,
                                                                const ModConst *__restrict__ mods,
                                                                const ModFp *__restrict__ modf,
                                                                const u64 *__restrict__ tw,
