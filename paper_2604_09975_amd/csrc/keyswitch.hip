@@ -443,7 +443,7 @@ __global__ __launch_bounds__(MidTile<LOGR>::THREADS, 4) void modup_mid_kernel(co
                                                         const u64 *__restrict__ ninvs,
                                                         const u32 *__restrict__ up_ft,
                                                         const u32 *__restrict__ up_mats, u32 level, u32 K, u32 L,
-                                                        u32 alpha, u32 beta, u32 tsplit) {
+                                                        u32 alpha, u32 beta, u32 tsplit, u32 tg) {
     typedef MidTile<LOGR> MT;
     constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, MID_TILE = MT::SIZE, COLS = MT::COLS, PER = MT::PER;
     static_assert(UP_TG == 8 && AM <= 8, "the target tiles reuse the 8 rows of source tiles");
@@ -493,8 +493,9 @@ __global__ __launch_bounds__(MidTile<LOGR>::THREADS, 4) void modup_mid_kernel(co
     for (u32 e = 0; e < 2; ++e) mid_pieces<AM, 25>(yraw[e], yp[e]);
     u64 *dig = digits + ((size_t)r * beta + j) * Wl * N;
     const u32 nt = Wl - nd;                                          // targets: all rows outside the digit
-    for (u32 u0 = tpart * UP_TG; u0 < nt; u0 += tsplit * UP_TG) {
-        for (u32 tt = 0; tt < UP_TG && u0 + tt < nt; ++tt) {
+    for (u32 u0 = tpart * tg; u0 < nt; u0 += tsplit * tg) {
+        const u32 here = min(tg, nt - u0);
+        for (u32 tt = 0; tt < UP_TG && tt < here; ++tt) {
             const u32 uu = u0 + tt, t = uu < lo ? uu : uu + nd;      // row of the extended basis
             u64 res[2];
             if (t < level) {
@@ -545,7 +546,7 @@ __global__ __launch_bounds__(MidTile<LOGR>::THREADS, 4) void modup_mid_kernel(co
         }
         if constexpr (LOGR == 0) continue;
         __syncthreads();
-        if (u0 + grp < nt) {
+        if (grp < here) {
             const u32 uu = u0 + grp, t = uu < lo ? uu : uu + nd;
             const u32 gl = t < level ? t : L + (t - level);
             const RowBuf dst(dig + (size_t)t * N, N);
@@ -1076,7 +1077,7 @@ __global__ __launch_bounds__(MidTile<LOGR>::THREADS, 4) void moddown_mid_kernel(
                                                           const double *__restrict__ twf_fwd,
                                                           const u32 *__restrict__ dn_mats, u32 level, u32 K, u32 L,
                                                           u32 ystride, u32 yoff, const u64 *__restrict__ t_rows,
-                                                          u32 tsplit, bool streamed) {
+                                                          u32 tsplit, u32 tg, bool streamed) {
     typedef MidTile<LOGR> MT;
     constexpr u32 logN = 12 + LOGR, N = 1u << logN, R = 1u << LOGR, MID_TILE = MT::SIZE, COLS = MT::COLS, PER = MT::PER;
     static_assert(MID_TG == 8 && KM <= 8, "the correction tiles reuse the 8 rows of special-limb tiles");
@@ -1144,9 +1145,6 @@ __global__ __launch_bounds__(MidTile<LOGR>::THREADS, 4) void moddown_mid_kernel(
             rp[e] = r >= ml.q ? r - ml.q : r;                       // r' = (r + h) mod q_last
         }
     }
-    // as few groups as there can be, of one size: a lone call waits for the longest (one of 17 limbs, 8 + 8 + 1 / 6 + 6 + 5
-    // targets: 21.1 / 19.1 us; ModUp, whose last digit has 24 targets there, gains nothing by it)
-    const u32 groups = max(1u, (n_out + MID_TG - 1) / MID_TG), tg = (n_out + groups - 1) / groups;
     for (u32 i0 = tpart * tg; i0 < n_out; i0 += tsplit * tg) {
         const u32 here = min(tg, n_out - i0);
         for (u32 t = 0; t < MID_TG && t < here; ++t) {
@@ -1297,6 +1295,17 @@ static moddown_mid_t moddown_mid_for(const ckks_params *p) {
     }
 }
 
+// Targets of a group: as few groups as there can be, of one size (a lone call waits for the longest: ModDown of 17 limbs, 8 + 8 + 1 /
+// 6 + 6 + 5 targets: 21.1 / 19.1 us; ModUp, whose last digit has 24 targets there, gains nothing by it), and where these leave
+// CUs without a workgroup, as many as there are CUs: small groups convert less behind one another.  us, groups as few as there can be /
+// up to 256 workgroups in both conversions: one rotation at 2^16, 12 + 6 primes of 40 and 49 bits, level 6, one digit 55.5 and 48.9;
+// 24 + 8 primes, level 1 / 4 / 6 53.6 / 57.5 / 60.6 and 48.8 / 50.0 / 52.6; 2^15, 8 + 4, one digit of four 51.7 and 46.4; 2^14, 6 + 2
+// 47.8 and 44.3; 2^13, 8 + 8 52.3 and 45.2.  Up to 512, ModDown at 2^16 takes 3 % more than with as few as there can be.
+static u32 group_size(u32 workgroups, u32 targets) {
+    const u32 groups = std::max<u32>({1, (targets + MID_TG - 1) / MID_TG, std::min(targets, 256 / workgroups)});
+    return std::max<u32>(1, (targets + groups - 1) / groups);
+}
+
 // Workgroups among which ModDown splits the target groups of a tile: up to three for each of the 256 CUs, which run two at a
 // time.  The line hardly matters: whole calls with at most 256 / 384 / 512 / 768 / 1024 / 1536 workgroups, us: one rotation at
 // 2^16, level 24 134.4 / 133.3 / 133.4 / 133.2 / 133.5 / 133.3, three at level 17 189.7 / 189.6 / 189.5 / 186.4 / 186.5 / 190.4,
@@ -1306,10 +1315,11 @@ static u32 target_split(u32 workgroups, u32 groups) { return std::max<u32>(1, st
 static void launch_moddown_mid(const ckks_params *p, const u64 *y, u64 *w, u32 n, u32 level, u32 ystride, u32 yoff,
                                hipStream_t stream, const u64 *t_rows = nullptr) {
     const u32 tiles = p->N / mid_tile(p), threads = mid_tile(p) / 2;
-    const u32 tsplit = target_split(tiles * n * 2, (level - (t_rows ? 1 : 0) + MID_TG - 1) / MID_TG);
+    const u32 n_out = level - (t_rows ? 1 : 0), wgs = tiles * n * 2, tg = group_size(wgs, n_out);
+    const u32 tsplit = target_split(wgs, (n_out + tg - 1) / tg);
     hipLaunchKernelGGL(t_rows ? moddown_mid_for<true>(p) : moddown_mid_for<false>(p), dim3(tiles * tsplit, n * 2),
                        dim3(threads), 0, stream, y, w, p->d_mod, p->d_modf, p->d_modf_dn, p->d_tws_inv, p->d_twf_inv,
-                       p->d_ninvs_dn, p->d_twf_fwd, p->d_dn_mats, level, p->K, p->L, ystride, yoff, t_rows, tsplit,
+                       p->d_ninvs_dn, p->d_twf_fwd, p->d_dn_mats, level, p->K, p->L, ystride, yoff, t_rows, tsplit, tg,
                        (size_t)n * 2 * level * p->N * sizeof(u64) > STREAM_BYTES);
 }
 
@@ -1654,14 +1664,15 @@ static int decompose_from_tmp(ckks_params *p, const LevelTables *lt, u32 n, u64 
             return CKKS_OK;
         }
         // the column passes of both transforms ride in the base conversion: c1 read once, digits written once
-        const u32 tgroups = (Wl - std::min(alpha, level) + UP_TG - 1) / UP_TG, tiles = N / mid_tile(p);
+        const u32 nt = Wl - std::min(alpha, level), tgroups = (nt + UP_TG - 1) / UP_TG, tiles = N / mid_tile(p), wgs = n * beta * tiles;
         // all target groups apart below 1024 workgroups (two per CU run at a time): one rotation at 2^16, level 24 / 17 / 9, two
         // at level 24, a product and rescale at 2^16 and 2^15 133.4 / 120.4 / 83.8, 184.2, 188.5 and 85.2 us; never split 135.0 /
         // 123.8 / 88.8, 186.0, 190.3 and 89.6; as many parts as make up to 256, 512, 768 or 1536 workgroups within 0.5 % of either
-        const u32 tsplit = n * beta * tiles < 1024 ? std::max<u32>(1, tgroups) : 1;
+        const u32 tg = wgs * tgroups < 256 ? group_size(wgs, nt) : UP_TG;
+        const u32 tsplit = wgs < 1024 ? (nt + tg - 1) / tg : 1;
         hipLaunchKernelGGL(modup_mid_for(p), dim3(tiles * tsplit, beta, n), dim3(mid_tile(p) / 2), 0, stream, d_tmp,
                            d_digits, p->d_mod, p->d_modf, lt->d_modf_up, p->d_twf_inv, p->d_twf_fwd, p->d_tws_fwd,
-                           p->d_ninvs, lt->d_up_ft, lt->d_up_mats, level, K, L, alpha, beta, tsplit);
+                           p->d_ninvs, lt->d_up_ft, lt->d_up_mats, level, K, L, alpha, beta, tsplit, tg);
         CKKS_LAUNCH_CHECK("modup_mid_kernel");
         p->limb_ntts += (u64)n * beta * Wl - (u64)n * level;
         return half ? CKKS_OK : transform_digits(p, level, n, d_digits, stream, 2);

@@ -104,6 +104,24 @@ def test_rotations_by_either_gather(steps):
             assert steps[i] != s or torch.equal(got[i], want), i
 
 
+@pytest.mark.parametrize("logN,L,K,dnum,level,pbits", [(13, 8, 8, 1, 8, 60), (13, 3, 1, 3, 1, 60), (13, 12, 4, 3, 11, 49), (14, 8, 5, 1, 7, 55),
+                                                       (14, 9, 2, 9, 5, 60), (15, 8, 4, 2, 8, 49), (15, 7, 7, 1, 7, 61),
+                                                       (16, 6, 6, 1, 6, 49), (16, 4, 3, 2, 3, 60), (16, 12, 2, 6, 9, 60)])
+def test_target_groups_of_a_lone_switch(logN, L, K, dnum, level, pbits):
+    """Conversions of few workgroups take small groups of targets, down to one and with a shorter last one, of digits whose targets
+    are not all as many; twenty switches of the same rotation take groups of eight."""
+    from paper_2604_09975_amd import binding as B
+    O = helpers.small_oracle(logN, L=L, K=K, dnum=dnum, qbits=50 if pbits > 50 else 45, pbits=pbits)
+    _, P = make_pair(O)
+    r = W.rng(1500 + logN + L)
+    ct, key = _edge_residues(r, O.q[:level], O.N, (2,)), _edge_residues(r, O.moduli, O.N, (O.dnum, 2))
+    h = B.ckks_galois_key_load(P, O.galois_elt(3), to_dev(key))
+    one = to_host(B.ckks_rotate_hoisted(P, to_dev(ct), level, [3], [h]))[0]
+    assert (one == O.rotate_hoisted(ct, level, [O.galois_elt(3)], [key])[0]).all()
+    many = to_host(B.ckks_rotate_hoisted(P, to_dev(ct), level, [3] * 20, [h] * 20))
+    assert all((g == one).all() for g in many)
+
+
 @pytest.mark.parametrize("logN,level", [(12, 11), (13, 12), (16, 12)])
 def test_more_digit_rows_than_one_launch_describes(logN, level):
     """Twelve digits of one limb: 132 rows and more of extended digits, above the 128 of one row map; the forward tile passes go
