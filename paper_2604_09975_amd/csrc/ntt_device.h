@@ -140,9 +140,10 @@ struct FieldPm {
     typedef int64_t T;
     template <bool U> using W = TwPm<U>;
     // bounds in units of q / 256 (a canonical value: 256): of a product of a value bounded by b, of normalised values and of
-    // those that the rounds of an inverse pass leave; and what keeps every value, sum and difference below 2^63 - 2^33
+    // those that the rounds of an inverse pass leave; and of every value, sum and difference: below 7.5 2^b, where norm ends for
+    // b = 60 (mul takes up to 2^63 - 2^33)
     static constexpr bool BOUNDED = true;
-    static constexpr u32 NORMED = 129, INV_BASE = 264, LIMIT = 2022;
+    static constexpr u32 NORMED = 129, INV_BASE = 264, LIMIT = 1919;
     static constexpr u32 product(u32 b) { return 201 + (9 * b + 255) / 256; }
     u64 q, q8;
     int64_t r31, mid;                       // 2^31 and -2^(b-1)
@@ -169,7 +170,7 @@ struct FieldPm {
         const int4 t = (tw + idx)[k];
         return TwPm<U>{t.x, t.y, t.z, t.w};
     }
-    // |x| <= 2^(b-1) + 8 c
+    // x -> x - round(x / 2^b) q, at most 2^(b-1) + |x / 2^b| c + c / 2 (from fold30: 2^(b-1) + 2^26).  hi - lo fits 32 bits below 7.5 2^60
     __device__ __forceinline__ void norm(T &x) const {
         const int hi = (int)(x >> 32), lo = __builtin_amdgcn_sbfe(hi, 0, s);
         const int64_t y = (int64_t)((u64)(u32)lo << 32 | (u32)x);
