@@ -162,17 +162,18 @@ def test_more_vectors_than_one_chunk():
     assert (back - z).abs().max().item() <= 0.5 * O.N / 2.0**30
 
 
-@pytest.mark.parametrize("logN,count", [(13, 64), (15, 63), (16, 32), (16, 33)])
+@pytest.mark.parametrize("logN,count", [(13, 64), (14, 8), (15, 63), (16, 32), (16, 33), (17, 9)])
 def test_decode_on_either_side_of_the_wide_near_pass(logN, count):
     """Up to 256 workgroups the near pass takes 1024 threads, above 256: the same operations on the same values, so a batch
-    (256 workgroups at 2^16 x 32, 264 at x 33) gives the bits of single calls, and both are the oracle's slots."""
+    (256 workgroups at 2^16 x 32, 264 at x 33) gives the bits of single calls, and both are the oracle's slots.  Every vector: from
+    eight on at 2^14 to 2^16 a workgroup's vector and tile are not its grid position."""
     from paper_2604_09975_amd import binding as B
     O = helpers.small_oracle(logN, L=2, K=1, dnum=2, qbits=50, pbits=57)
     _, P = make_pair(O)
     m = W.rng(630 + logN).integers(-(1 << 40), 1 << 40, (count, O.N))
     res = to_dev(np.stack([(m % int(q)).astype(np.uint64) for q in O.q], axis=1))
     got = B.ckks_decode(P, res, 2, 2.0**36)
-    for i in (0, count // 2, count - 1):
+    for i in range(count):
         assert torch.equal(torch.view_as_real(got[i]), torch.view_as_real(B.ckks_decode(P, res[i:i + 1].contiguous(), 2, 2.0**36)[0]))
     want = E.decode(m[0], 2.0**36, O.N)
     assert np.abs(got[0].cpu().numpy() - want).max() / np.abs(want).max() < 1e-13
@@ -314,9 +315,9 @@ def _encode_n_point(z, scale, real):
     return m
 
 
-@pytest.mark.parametrize("logN,count", [(12, 2), (13, 65), (14, 3), (14, 11), (15, 8), (16, 2), (17, 1)])
+@pytest.mark.parametrize("logN,count", [(12, 2), (13, 65), (14, 3), (14, 11), (15, 8), (16, 2), (16, 9), (17, 1), (17, 9)])
 def test_encode_has_the_bits_of_a_plain_transform(logN, count):
-    """Whatever the passes are.  At a scale of 2^56 a coefficient holds the last bits of its double: one operation in another
+    """Whatever the passes are, and whichever workgroup takes a tile (eight vectors and more are dealt out).  At a scale of 2^56 a coefficient holds the last bits of its double: one operation in another
     order shows."""
     from paper_2604_09975_amd import binding as B
     O = helpers.small_oracle(logN, L=3, K=1, dnum=3, qbits=50, pbits=57)
