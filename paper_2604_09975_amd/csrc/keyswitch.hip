@@ -544,34 +544,35 @@ __global__ __launch_bounds__(MidTile<LOGR>::THREADS, 4) void modup_mid_kernel(co
                     wlds[tt * MID_TILE + e * MT::THREADS + tid] = res[e];
             }
         }
-        if constexpr (LOGR == 0) continue;
-        __syncthreads();
-        if (grp < here) {
-            const u32 uu = u0 + grp, t = uu < lo ? uu : uu + nd;
-            const u32 gl = t < level ? t : L + (t - level);
-            const RowBuf dst(dig + (size_t)t * N, N);
-            const ModFp mf = modf[gl];
+        if constexpr (LOGR != 0) {
+            __syncthreads();
+            if (grp < here) {
+                const u32 uu = u0 + grp, t = uu < lo ? uu : uu + nd;
+                const u32 gl = t < level ? t : L + (t - level);
+                const RowBuf dst(dig + (size_t)t * N, N);
+                const ModFp mf = modf[gl];
 #pragma unroll
-            for (u32 c = 0; c < PER; ++c) {
-                const u32 col = lane + 64 * c;
-                if (mf.ok) {
-                    const FieldFp ff = make_field_fp(mf, twf_fwd, gl, logN);
-                    double v[R];
+                for (u32 c = 0; c < PER; ++c) {
+                    const u32 col = lane + 64 * c;
+                    if (mf.ok) {
+                        const FieldFp ff = make_field_fp(mf, twf_fwd, gl, logN);
+                        double v[R];
 #pragma unroll
-                    for (u32 jj = 0; jj < R; ++jj)
-                        v[jj] = __longlong_as_double((long long)wlds[grp * MID_TILE + jj * COLS + col]);
-                    radix_fwd<LOGR>(ff, v, 0, 0);
+                        for (u32 jj = 0; jj < R; ++jj)
+                            v[jj] = __longlong_as_double((long long)wlds[grp * MID_TILE + jj * COLS + col]);
+                        radix_fwd<LOGR>(ff, v, 0, 0);
 #pragma unroll
-                    for (u32 jj = 0; jj < R; ++jj) dst.store(jj * 4096 + c0, col, ff.half(v[jj]));
-                } else {
-                    auto load = [&](u32 at, u32) { return wlds[grp * MID_TILE + (at >> 12) * COLS + col]; };
-                    auto store = [&](u32 at, u32, u64 v) { dst.store(at + c0, col, v); };
-                    with_int_field(mf, mods, tws_fwd, ninvs, gl, logN,
-                                   [&](const auto &f) { pass_a_body<false, LOGR>(f, c0 + col, load, store); });
+                        for (u32 jj = 0; jj < R; ++jj) dst.store(jj * 4096 + c0, col, ff.half(v[jj]));
+                    } else {
+                        auto load = [&](u32 at, u32) { return wlds[grp * MID_TILE + (at >> 12) * COLS + col]; };
+                        auto store = [&](u32 at, u32, u64 v) { dst.store(at + c0, col, v); };
+                        with_int_field(mf, mods, tws_fwd, ninvs, gl, logN,
+                                       [&](const auto &f) { pass_a_body<false, LOGR>(f, c0 + col, load, store); });
+                    }
                 }
             }
+            __syncthreads();
         }
-        __syncthreads();
     }
 }
 
@@ -1170,32 +1171,33 @@ __global__ __launch_bounds__(MidTile<LOGR>::THREADS, 4) void moddown_mid_kernel(
                     wlds[t * MID_TILE + e * MT::THREADS + tid] = (u64)__double_as_longlong(v);
             }
         }
-        if constexpr (LOGR == 0) continue;
-        __syncthreads();
-        if (grp < here) {
-            const u32 i = i0 + grp;
-            const FieldFp ff = make_field_fp(modf[i], twf_fwd, i, logN);
-            const RowBuf dst(w + ((size_t)pc * level + i) * N, N);
+        if constexpr (LOGR != 0) {
+            __syncthreads();
+            if (grp < here) {
+                const u32 i = i0 + grp;
+                const FieldFp ff = make_field_fp(modf[i], twf_fwd, i, logN);
+                const RowBuf dst(w + ((size_t)pc * level + i) * N, N);
 #pragma unroll
-            for (u32 c = 0; c < PER; ++c) {
-                const u32 col = lane + 64 * c;
-                double v[R];
+                for (u32 c = 0; c < PER; ++c) {
+                    const u32 col = lane + 64 * c;
+                    double v[R];
 #pragma unroll
-                for (u32 j = 0; j < R; ++j)
-                    v[j] = __longlong_as_double((long long)wlds[grp * MID_TILE + j * COLS + col]);
-                radix_fwd<LOGR>(ff, v, 0, 0);
-                // w of a large batch goes past the caches: it is read once, by the next kernel, which then finds the digit
-                // rows there (passb_final_kernel of 24 switches 524 -> 510 us)
-                if (streamed) {
+                    for (u32 j = 0; j < R; ++j)
+                        v[j] = __longlong_as_double((long long)wlds[grp * MID_TILE + j * COLS + col]);
+                    radix_fwd<LOGR>(ff, v, 0, 0);
+                    // w of a large batch goes past the caches: it is read once, by the next kernel, which then finds the digit
+                    // rows there (passb_final_kernel of 24 switches 524 -> 510 us)
+                    if (streamed) {
 #pragma unroll
-                    for (u32 j = 0; j < R; ++j) dst.store<true>(j * 4096 + c0, col, ff.half(v[j]));
-                } else {
+                        for (u32 j = 0; j < R; ++j) dst.store<true>(j * 4096 + c0, col, ff.half(v[j]));
+                    } else {
 #pragma unroll
-                    for (u32 j = 0; j < R; ++j) dst.store(j * 4096 + c0, col, ff.half(v[j]));
+                        for (u32 j = 0; j < R; ++j) dst.store(j * 4096 + c0, col, ff.half(v[j]));
+                    }
                 }
             }
+            __syncthreads();
         }
-        __syncthreads();
     }
 }
 

@@ -1658,10 +1658,11 @@ static int rescale_rows(ckks_params *P, const u64 *d_in, u32 level, u32 rows, u6
         // workgroups, us: 2^16, level 24 37.2 / 34.9 / 33.7 / 33.6 / 33.3, level 12 28.5 and 27.7, 2^15, level 12 20.7 and 19.4;
         // two at 2^15 27.7 and 26.9, six 41.1 / 40.8 / 40.9 / 41.0 / 42.3, four at 2^16 84.5 / 84.7 / 84.3 / 84.4 / 86.5
         const u32 tsplit = std::max<u32>(1, std::min<u32>((level - 1 + 7) / 8, 768 / (N / RS_TILE * rows)));
-        if (mid)
+        if (mid) {
             hipLaunchKernelGGL(mid, dim3(N / RS_TILE * tsplit, rows), dim3(256), 0, stream, d_r, d_out, P->d_modf, P->d_mod,
-                           P->d_twf_inv, P->d_twf_fwd, level, tsplit);
-        CKKS_LAUNCH_CHECK("rescale_mid_kernel");
+                               P->d_twf_inv, P->d_twf_fwd, level, tsplit);
+            CKKS_LAUNCH_CHECK("rescale_mid_kernel");
+        }
         hipLaunchKernelGGL(wide_out ? rescale_tile_kernel<WIDE_RL> : rescale_tile_kernel<4>, dim3(N >> 12, level - 1, rows),
                            dim3(tile_threads(wide_out)), 0, stream, d_in, d_out, d_r,
                            P->d_modf, P->d_mod, P->d_twf_fwd, qlinv, level, P->logN);

@@ -80,7 +80,6 @@ struct FieldInt {
     u64 q, q2;
     const ulonglong2 *tw;
     TwInt n0, n1;
-    __device__ __forceinline__ TwInt scale() const { return n0; }
     __device__ __forceinline__ T in(u64 x) const { return x; }
     __device__ __forceinline__ u64 out(T x) const {
         if (x >= q2) x -= q2;
@@ -151,7 +150,6 @@ struct FieldPm {
     u32 s, p2s;                             // s and 2^s
     const int4 *tw;
     TwPm<true> n0, n1;
-    __device__ __forceinline__ TwPm<true> scale() const { return n0; }
     __device__ __forceinline__ T in(u64 x) const { return (T)x; }
     __device__ __forceinline__ u64 out(T x) const {
         const u64 y = (u64)x + q8;          // [0, 16 q)
@@ -233,7 +231,6 @@ struct FieldFp {
     static constexpr bool BOUNDED = false;
     double q, u, n0, n1;
     const double *tw;
-    __device__ __forceinline__ double scale() const { return n0; }
     __device__ __forceinline__ T in(u64 x) const {
         return __longlong_as_double((long long)(x | 0x4330000000000000ull)) - 4503599627370496.0;
     }
@@ -585,25 +582,24 @@ struct RowBuf {
     }
 };
 
-// pass A for N = 2^(12+LOGR): the first LOGR stages pair residues 4096 apart, so a thread that owns one of the 4096
+// pass A for N = 2^(12+LOGR), LOGR > 0: the first LOGR stages pair residues 4096 apart, so a thread that owns one of the 4096
 // columns holds its 2^LOGR rows in registers: no LDS, every access a run of consecutive residues.  col: the thread's
-// column; load(at, col) / store(at, col, value) see residues at index at + col of the polynomial, canonical on the
-// side of the coefficients, at the same for
-// all threads: a scalar address to which a thread adds one 32-bit offset (an address per row would take 32 registers).
+// column; load(at, col) / store(at, col, value) see residues at index at + col of the polynomial, canonical on the side of
+// the coefficients, at the same for all threads: a scalar address to which a thread adds one 32-bit offset (an address per
+// row would take 32 registers).
 template <bool INV, u32 LOGR, class F, class Load, class Store>
 __device__ __forceinline__ void pass_a_body(const F &f, u32 col, Load load, Store store) {
+    static_assert(LOGR > 0, "at N = 2^12 the tile pass is the whole transform");
     constexpr u32 R = 1u << LOGR;
     typename F::T v[R];
 #pragma unroll
-    for (u32 j = 0; j < R; ++j) v[j] = INV && LOGR != 0 ? f.from_bits(load(j * 4096, col)) : f.in(load(j * 4096, col));
-    if constexpr (INV && LOGR == 0)
-        v[0] = f.mul(v[0], f.scale());                              // N = 2^12: no stage is left, the scaling is
-    else if constexpr (INV)
+    for (u32 j = 0; j < R; ++j) v[j] = INV ? f.from_bits(load(j * 4096, col)) : f.in(load(j * 4096, col));
+    if constexpr (INV)
         radix_inv<LOGR, true, false>(f, v, 0, 0, true);
     else
         radix_fwd<LOGR>(f, v, 0, 0);
 #pragma unroll
-    for (u32 j = 0; j < R; ++j) store(j * 4096, col, INV || LOGR == 0 ? f.out(v[j]) : f.half(v[j]));
+    for (u32 j = 0; j < R; ++j) store(j * 4096, col, INV ? f.out(v[j]) : f.half(v[j]));
 }
 
 // Field objects for limb `limb` from the parameter tables.

@@ -229,7 +229,7 @@ int ckks_params::build_level_tables(u32 level) {
                 if (b != i) fk = hmul(fk, mod[b] % pk, pk);
             for (u32 b = 0; b < 2; ++b) {
                 u64 g = hmul(fk, hpow(2, 25 * b, pk), pk);
-                if (!folds(pk) || pk >> 50 == 0) g = hmul(g, hmod[L + k].one, pk);
+                if (!folds(pk)) g = hmul(g, hmod[L + k].one, pk);
                 for (u32 c = 0; c < 2; ++c)                    // used for primes below 2^60
                     mats[((((size_t)dj * K + k) * am + da) * 2 + b) * 2 + c] = (u32)(g >> (30 * c)) & 0x3FFFFFFFu;
             }
