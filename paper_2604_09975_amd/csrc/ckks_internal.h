@@ -35,6 +35,12 @@ struct ModFp {
     u32 pm;                // 1 if q = 2^b - c, 51 <= b <= 60, c < 2^(b-35) (the folding integer butterflies apply)
 };
 
+// q = 2^b - c with 51 <= b <= 60 and 0 < c < 2^(b-35): products fold at 2^b (FieldPm)
+inline bool folds(u64 q) {
+    const u32 b = 64 - (u32)__builtin_clzll(q);
+    return b > 50 && b <= 60 && (((u64)1 << b) - q) >> (b - 35) == 0;
+}
+
 // Half-open device ranges [a, a + na) and [b, b + nb) of 64-bit words share a word.
 inline bool words_overlap(const void *a, size_t na, const void *b, size_t nb) {
     const uintptr_t a0 = (uintptr_t)a, a1 = a0 + na * sizeof(u64), b0 = (uintptr_t)b, b1 = b0 + nb * sizeof(u64);

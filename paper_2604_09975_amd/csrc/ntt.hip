@@ -100,19 +100,22 @@ __global__ __launch_bounds__(NTT_THREADS) void ntt_pass_kernel(u64 *__restrict__
 // LOGR: 1 .. 5 = pass A of N = 2^(12+LOGR) (its first / last LOGR stages, registers only; a thread takes 16 residues,
 // i.e. 16 >> LOGR columns, so that short rows keep as many loads in flight per wavefront as long ones), 0 = pass B (12
 // stages in a 4096 tile)
-// KIND: the rows' primes are all below 2^50 (FP_ROWS: fp64 butterflies), all above (INT_ROWS: integer butterflies) or of
-// both kinds (BOTH_ROWS).  One launch for rows of both kinds at every size: a launch each, the workgroups of the other kind
-// returning at once, costs the latency of a workgroup twice where the chip is not full (the digits of one ciphertext at level
-// 17 of 24 + 8 primes 17 + 25 us) and its last waves twice where it is, and the union of the two register budgets (pass B 90
+// KINDS: the rows' primes are all below 2^50 (FP_ROWS: fp64 butterflies), all above and none folds (INT_ROWS), all above
+// (INT_ROWS + PM_ROWS) or of any kind (ALL_ROWS).  One launch for rows of several kinds at every size: a launch each, the workgroups of
+// the other kind returning at once, costs the latency of a workgroup twice where the chip is not full (the digits of one ciphertext at
+// level 17 of 24 + 8 primes 17 + 25 us) and its last waves twice where it is, and the union of the register budgets (pass B 90
 // and 98, against 72 and 70 of the fp64 butterflies) keeps the wavefronts that the LDS tile admits.  Two launches and one,
 // transform of 50- and 60-bit rows, forward, us: 4096 workgroups at 2^16 112 / 105, 26624 650 / 629, 2560 at 2^15 78 / 63,
 // 10240 279 / 251, 2560 and 12800 at 2^14 103 / 68 and 513 / 333, 16000 at 2^13 683 / 418, 3072 at 2^17 93 / 83; inverse alike.
-constexpr int INT_ROWS = 0, FP_ROWS = 1, BOTH_ROWS = 2;
+// Rows that do not fold on their own: beside the folding butterflies their tile pass takes 90 registers for 70, a whole forward
+// transform of 26 limbs of 61 bits, 30 at a time, at 2^13 61.9 us for 60.5, at 2^14 118 for 115.  Of the other mixtures none gains
+// by a kernel of its own (rows that all fold, fp64 and folding, fp64 and quotients: within 1 % at 1, 5 and 30 polynomials).
+constexpr int FP_ROWS = 1, INT_ROWS = 2, PM_ROWS = 4, ALL_ROWS = 7;
 // + STREAMED: residues go past the caches' replacement order (arrays above STREAM_BYTES): a pass uses each once, and the
 // twiddles, as many bytes as a tile and shared by the rows of a limb, stay in L2.  64 x 24 rows at 2^16: tile pass 409 ->
 // 383 us, column pass 273 -> 250.  Below that the next pass finds them there: 25 x 14 rows at 2^16 164 us, streamed 182.
-constexpr int STREAMED = 4;
-constexpr int WIDE = 8;                      // + WIDE: tiles by 1024 threads (pass B only)
+constexpr int STREAMED = 8;
+constexpr int WIDE = 16;                     // + WIDE: tiles by 1024 threads (pass B only)
 // WAVES per SIMD of pass A at 2^17, forward: the butterflies of three kinds of primes take 170 registers, 168 leave a third
 // wavefront (two to four constants spilled).  us with two and three: 8 rows of 60-bit primes, batches of 5 / 12, 47.2 / 92.8 and
 // 42.7 / 90.4, of 61 and 60 bits, 5: 58.3 and 55.2; batches of 1 to 3 up to 2 % the other way.  Inverse (171) it gains as much
@@ -127,11 +130,11 @@ __global__ __launch_bounds__((KIND_NT & WIDE) != 0 ? Tile<WIDE_RL>::THREADS : NT
                                                                const double *__restrict__ twf,
                                                                const u64 *__restrict__ ninv, LimbIds ids,
                                                                u32 n_limbs, u32 logN) {
-    constexpr int KIND = KIND_NT & 3;
+    constexpr int KINDS = KIND_NT & ALL_ROWS;
     constexpr bool NT = (KIND_NT & STREAMED) != 0;
     constexpr u32 RL = (KIND_NT & WIDE) != 0 ? WIDE_RL : 4;
     __shared__ u64 lds[LOGR ? 1 : Tile<RL>::WORDS];
-    const u32 row = KIND == BOTH_ROWS ? gridDim.y - 1 - blockIdx.y : blockIdx.y;   // special limbs come last: start with them
+    const u32 row = (KINDS & FP_ROWS) && KINDS != FP_ROWS ? gridDim.y - 1 - blockIdx.y : blockIdx.y;   // special limbs come last: start with them
     const u32 limb = ids.id[row - uniform_div(row, n_limbs) * n_limbs];
     if (limb == SKIP_ROW) return;
     const ModFp mf = modf[limb];
@@ -156,22 +159,22 @@ __global__ __launch_bounds__((KIND_NT & WIDE) != 0 ? Tile<WIDE_RL>::THREADS : NT
                 pass_a_body<INV, LOGR>(f, (c * gridDim.x + blockIdx.x) * NTT_THREADS + threadIdx.x, load_a, store_a);
         }
     };
-    if (KIND == FP_ROWS || (KIND == BOTH_ROWS && mf.ok))
+    if ((KINDS & FP_ROWS) && (KINDS == FP_ROWS || mf.ok))
         go(make_field_fp(mf, twf, limb, logN));
-    else
-        with_int_field(mf, mods, tw, ninv, limb, logN, go);
+    else if ((KINDS & PM_ROWS) && (!(KINDS & INT_ROWS) || mf.pm))
+        go(make_field_pm(mods, tw, ninv, limb, logN));
+    else if (KINDS & INT_ROWS)
+        go(make_field_int(mods, tw, ninv, limb, logN));
 }
 
 template <bool INV, u32 LOGR>
 static void launch_fast(const ckks_params *p, u64 *d_data, const LimbIds &ids, u32 n_limbs, u32 rows,
                         hipStream_t stream, bool scaled_dn) {
-    bool any_fp = false, any_int = false;
+    int kinds = 0;
     for (u32 i = 0; i < n_limbs; ++i) {
         if (ids.id[i] == SKIP_ROW) continue;
-        if ((p->mod[ids.id[i]] >> 50) == 0)
-            any_fp = true;
-        else
-            any_int = true;
+        const u64 q = p->mod[ids.id[i]];
+        kinds |= (q >> 50) == 0 ? FP_ROWS : folds(q) ? PM_ROWS : INT_ROWS;
     }
     const u32 blocks = LOGR == 0 ? p->N >> 12 : LOGR < 4 ? 1u << LOGR : 16;
 #define FAST_LAUNCH(KIND)                                                                                            \
@@ -181,12 +184,14 @@ static void launch_fast(const ckks_params *p, u64 *d_data, const LimbIds &ids, u
                        p->logN)
 #define FAST_LAUNCH_KIND(F)                                                                                          \
     do {                                                                                                             \
-        if (any_fp && any_int)                                                                                       \
-            FAST_LAUNCH(BOTH_ROWS + (F));                                                                            \
-        else if (any_fp)                                                                                             \
-            FAST_LAUNCH(FP_ROWS + (F));                                                                              \
-        else if (any_int)                                                                                            \
-            FAST_LAUNCH(INT_ROWS + (F));                                                                             \
+        switch (kinds) {                                                                                             \
+            case FP_ROWS: FAST_LAUNCH(FP_ROWS + (F)); break;                                                         \
+            case INT_ROWS: FAST_LAUNCH(INT_ROWS + (F)); break;                                                       \
+            case 0: break;                                                                                           \
+            case PM_ROWS:                                                                                            \
+            case INT_ROWS + PM_ROWS: FAST_LAUNCH(INT_ROWS + PM_ROWS + (F)); break;                                   \
+            default: FAST_LAUNCH(ALL_ROWS + (F));                                                                    \
+        }                                                                                                            \
     } while (0)
     constexpr int W = LOGR == 0 ? WIDE : 0;
     if (LOGR == 0 && wide_tiles((u64)blocks * rows))

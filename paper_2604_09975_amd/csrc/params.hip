@@ -108,11 +108,6 @@ static ModConst make_mod(u64 q) {
 static u64 to_mont(u64 x, const ModConst &m) { return hmul(x % m.q, m.one, m.q); }
 static u64 shoup(u64 w, u64 q) { return (u64)((((wide)w) << 64) / q); }   // floor(w * 2^64 / q), w < q
 
-// q = 2^b - c with 51 <= b <= 60 and 0 < c < 2^(b-35): products fold at 2^b (FieldPm)
-static bool folds(u64 q) {
-    const u32 b = 64 - (u32)__builtin_clzll(q);
-    return b > 50 && b <= 60 && (((u64)1 << b) - q) >> (b - 35) == 0;
-}
 // w mod q as signed halves of 32 bits, w = hi 2^s + lo with |lo| <= 2^(s-1), s = b - 32
 static u64 fold_halves(u64 w, u64 q) {
     const u32 s = 32 - (u32)__builtin_clzll(q), sh = 64 - s;

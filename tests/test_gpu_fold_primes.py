@@ -52,6 +52,28 @@ def test_transforms_either_side_of_the_fold(logN, batch):
         assert (to_host(d) == x).all()
 
 
+@pytest.mark.parametrize("logN,batch", [(12, 4), (12, 300), (13, 3), (14, 150), (15, 2), (16, 40), (17, 1), (17, 5)])
+def test_transforms_of_rows_of_one_kind(logN, batch):
+    """Rows none of which folds have a kernel of their own, rows that all fold share one with these: each kind alone, in few tiles
+    (1024 threads), many and streamed, against the rows of a transform of both kinds in turn, and the first ones against the oracle."""
+    from paper_2604_09975_amd import binding as B
+    p = [x for b in (58, 60) for x in _edge_primes(b, logN)] + oracle.find_primes(61, logN, 2)
+    O, P = make_pair(oracle.Oracle(logN, p[:len(p) // 2], p[len(p) // 2:], 1))
+    folds = [i for i, q in enumerate(p) if q.bit_length() <= 60 and (1 << q.bit_length()) - q < 1 << (q.bit_length() - 35)]
+    assert 2 <= len(folds) <= len(p) - 4
+    x = _edge_residues(W.rng(70 + logN), O.moduli, O.N, (batch,))
+    for inverse in (False, True):
+        fn = B.ckks_intt if inverse else B.ckks_ntt
+        both = to_dev(x)
+        fn(P, both, list(range(len(p))), batch)
+        both = to_host(both)
+        assert (both[:2] == O.ntt_batch(x[:2], list(range(len(p))), inverse=inverse)).all()
+        for ids in (folds, [i for i in range(len(p)) if i not in folds]):
+            d = to_dev(x[:, ids])
+            fn(P, d, ids, batch)
+            assert (to_host(d) == both[:, ids]).all()
+
+
 @pytest.mark.parametrize("logN,L,dnum,steps", [(12, 4, 2, 1), (13, 4, 1, 20), (14, 3, 3, 2), (15, 4, 2, 1), (16, 4, 2, 1)])
 def test_key_switch_either_side_of_the_fold(logN, L, dnum, steps):
     """Special primes on both sides: one kernel then serves rows of either kind."""
