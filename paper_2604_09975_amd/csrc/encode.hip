@@ -151,7 +151,7 @@ struct DecodeIn {
 // are dealt to the eight, all tiles of one to the same, which find each other's lines of slots and scratch there and complete
 // each other's lines of coefficients (a mirrored run k -> N - k crosses lines).  Encode without and with, us: 40 / 96 / 200 general
 // vectors at 2^14 17.2 / 37.5 / 75.7 and 13.8 / 30.3 / 63.0, at 2^15 28.9 / 51.5 / 107 and 23.7 / 48.0 / 94.8, 16 / 96 at
-// 2^16 22.7 / 78.2 and 20.4 / 77.8; 2^17 the same.  Decode, for eight vectors and more at 2^14 to
+// 2^16 22.7 / 78.2 and 20.4 / 77.8; 2^17 the same, 2^13 too (8 to 400 vectors, two tiles each: within 1 %).  Decode, for eight vectors and more at 2^14 to
 // 2^16: 64 vectors at 2^14 15.9 and 13.6, 40 at 2^15 17.9 and 14.6, 16 / 200 at 2^16 18.4 / 104 and 13.8 / 100; at 2^13, where
 // a vector is one tile, and for fewer vectors the step costs 1 to 3 %, at 2^17 it gives 20 % of 16 and takes 2 % of 40.  The
 // vectors after the last eight: in order.

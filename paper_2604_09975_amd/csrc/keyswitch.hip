@@ -415,8 +415,8 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void modup_tile_kernel(const u64
 //   3. wavefront t: the columns of target t from LDS, first forward round (fp64 or integer butterflies), out.
 // A wavefront per row has the row's twiddles, modulus and addresses in scalar registers: 114 vector registers for digits of
 // eight limbs, which two such workgroups per CU leave.  With 32 threads per row (tiles of 512 coefficients, 256 threads) it is
-// 148 and 186 registers with the quotient and the folding butterflies, two or three wavefronts per SIMD for four: 32
-// ciphertexts of 24 limbs 421 and 444 us, 365 now.
+// 148 and 186 registers with the quotient and the folding butterflies, two or three wavefronts per SIMD for four.  32
+// ciphertexts of 24 limbs, in a projection's giant step, 514 us so with quotients, 420 now; one of 17 limbs 28.2 and 24.9.
 // At N = 2^12 (LOGR = 0; for consumers that transform the digits themselves) the tile passes are whole transforms, the inverse
 // one carries the scaling, and a thread converts and stores its own coefficients, without LDS.
 // c1_half [n][level][N]: c1 after the inverse tile pass; digits [n][beta][level+K][N]: rows of targets outside the
@@ -1518,8 +1518,8 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void passb_final_kernel(ItemPack
 #pragma unroll
         for (u32 e = 0; e < EPP; ++e) {
             const u32 loc = TL::pair(tid, i0 + e);
-            // RL < 4: one array for c0 or the addend (128 registers is what 16 wavefronts a workgroup leave); where both are added,
-            // the addend comes now
+            // RL < 4: one array for c0 or the addend (128 registers is what 16 wavefronts a workgroup leave); where both are
+            // added, the addend comes now
             if (RL < 4) ov[e] = accumulate && fold ? load_add(loc) : pair_t{0, 0};
             __builtin_amdgcn_sched_barrier(0);
             cv[e] = turned<PAIR>(cv[e], kp[e]);
@@ -1728,7 +1728,8 @@ static u32 build_pack(const SwitchItem *items, u32 n, ItemPack &pack) {
 
 // A workgroup of merged_tile_kernel is a chain of all rotations and digits, so few of them leave the chip idle that long, and 512
 // fit at a time.  Workgroups (ring, ciphertexts, digits), whole calls with 15 rotations, separate tile passes /
-// merged_tile_kernel, us (before butterflies on 60-bit primes that fold, which shorten a chain more than a tile pass):
+// merged_tile_kernel, us (before the folding butterflies; with them 288 and 320 of 50- and 60-bit primes, (2^14, 9, 3) 680 / 662
+// and (2^14, 10, 3) 793 / 705):
 //   up to three digits: 256 (2^15, 2, 3) 767 / 826, 288 (2^13, 12, 2) 675 / 656, 312 (2^15, 3, 3) 864 / 907, 320 (2^16, 1, 2)
 //     851 / 821, 384 (2^15, 3, 3) 1033 / 988, 512 (2^14, 16, 3) 1606 / 1109, 544 (2^14, 17, 3) 1720 / 1171;
 //   more digits, of few ciphertexts: longer chains, beside a separate kernel that reads a key once for three ciphertexts: 320
@@ -1740,6 +1741,11 @@ static u32 build_pack(const SwitchItem *items, u32 n, ItemPack &pack) {
 //     1271 / 1176.
 // More rows of digits than one row map describes: their own tile passes are a launch per digit and ciphertext (2^14, 11
 // ciphertexts, 12 digits: 19130 / 3783).
+// With ciphertext primes of 58 and 60 bits that fold (both are measured, 15 rotations, 58 / 60 bits) the line for integer rows is
+// within 5 % of the faster side, on either: just below it 384 (2^15, 3, 3) 1369 / 1342 and 1310 / 1310, (2^15, 4, 3) 1358 / 1315 and 1329 /
+// 1300, 400 (2^14, 10, 3) 1368 / 1314 and 1343 / 1289, 440 (2^14, 22, 4) 1943 / 2048 and 1941 / 2046, 576 (2^14, 9, 5) 2790 / 2861 and 2688 /
+// 2706, (2^14, 12, 4) 2251 / 2309 and 2216 / 2288; above it 512 (2^15, 4, 3) 1803 / 1643 and 1754 / 1557, 640 (2^14, 20, 3) 2226 / 2094
+// and 2219 / 2074, 896 (2^14, 14, 5) 4295 / 4008 and 4119 / 3898.
 bool merged_from_half(const ckks_params *p, u32 level, u32 n) {
     const u32 Wl = level + p->K, beta = (level + p->alpha - 1) / p->alpha, units = (p->N >> 12) * Wl;
     const u32 workgroups = units * n;                            // at most 2^5 * 64 * 32

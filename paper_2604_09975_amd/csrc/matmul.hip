@@ -136,9 +136,10 @@ static inline PackedShape packed_shape(u32 N, u32 level, u32 GQ, u32 BP, bool wh
 // (7818 -> 7742 us).  Every wavefront of a workgroup runs every step, those beyond the last tile for the barriers alone.  (Waves
 // that read the bank through the vector L1 together, without LDS, take 12 to 19 ms.)
 // What bounds it (QKV layer, 34.0 GB of records, 2.4 GB of bank, 1.8 GB of sums): memory, 4.95 TB/s with SH = 4, 7.74 ms; 8.43
-// ms with a bank stream for each wavefront (8.32 to 8.47 from card to card), an earlier form of which, 8.45 ms, took 8.40 without the products, 4.36 without the record loads and 7.05 without the
-// bank loads (5.1 TB/s; a plain read reaches 5.3).  The kernel with a quotient per product was bound by fp64 issue: 8.66 ms
-// with the vector units 92 % busy; these sums keep them 62 % busy.
+// ms with a bank stream for each wavefront (8.32 to 8.47 from card to card), an earlier form of which, 8.45 ms, took 8.40
+// without the products, 4.36 without the record loads and 7.05 without the bank loads (5.1 TB/s; a plain read reaches 5.3).
+// The kernel with a quotient per product was bound by fp64 issue: 8.66 ms with the vector units 92 % busy; these sums keep
+// them 62 % busy.
 template <bool SYM, bool PACKED, u32 NP, u32 SH = 0>
 __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *__restrict__ bank,
                                                               const void *__restrict__ w, u64 *__restrict__ acc,
@@ -477,8 +478,8 @@ __global__ __launch_bounds__(EW_THREADS) void copy_blocks_kernel(u64 *__restrict
 }
 
 // y_b = base_b + the rotated accumulators of block b among the cn items of a batch; item r belongs to block (c0 + r) % B.
-// base is y itself from the second batch on.  bias: [B][level][N] added to component 0, or null.  blockIdx.y = component * level + limb, blockIdx.z = block; two residues per
-// thread.
+// base is y itself from the second batch on.  bias: [B][level][N] added to component 0, or null.  blockIdx.y = component *
+// level + limb, blockIdx.z = block; two residues per thread.
 __global__ __launch_bounds__(EW_THREADS) void add_rotations_kernel(u64 *y, const u64 *base,
                                                                    size_t base_stride, const u64 *__restrict__ items,
                                                                    const u64 *__restrict__ bias,
@@ -707,7 +708,7 @@ __global__ __launch_bounds__(EW_THREADS) void to_weight_form_kernel(u64 *data, c
 //   rescale_intt_kernel:  inverse tile pass of the dropped limb, read where it lies;
 //   rescale_mid_kernel:   its column pass, r' = r + floor(q_l/2) mod q_l, the rounding term r' mod q_i - floor(q_l/2) mod
 //                         q_i of every remaining limb and the column pass of its forward transform, on tiles of
-//                         512 coefficients as in moddown_mid_kernel;
+//                         512 coefficients, 32 threads a row;
 //   rescale_tile_kernel:  forward tile pass and (c - NTT(delta)) q_l^-1.
 // At N = 2^12 the tile passes are whole transforms, and the last kernel forms the rounding terms it transforms itself.
 constexpr u32 RS_TILE = 512;

@@ -123,13 +123,14 @@ constexpr int WIDE = 16;                     // + WIDE: tiles by 1024 threads (p
 template <bool INV, u32 LOGR>
 constexpr u32 WAVES = LOGR == 5 && !INV ? 3 : 1;
 template <bool INV, u32 LOGR, int KIND_NT>
-__global__ __launch_bounds__((KIND_NT & WIDE) != 0 ? Tile<WIDE_RL>::THREADS : NTT_THREADS, (WAVES<INV, LOGR>)) void ntt_fast_kernel(u64 *__restrict__ data,
-                                                               const ModConst *__restrict__ mods,
-                                                               const ModFp *__restrict__ modf,
-                                                               const u64 *__restrict__ tw,
-                                                               const double *__restrict__ twf,
-                                                               const u64 *__restrict__ ninv, LimbIds ids,
-                                                               u32 n_limbs, u32 logN) {
+__global__ __launch_bounds__((KIND_NT & WIDE) != 0 ? Tile<WIDE_RL>::THREADS : NTT_THREADS, (WAVES<INV, LOGR>))
+void ntt_fast_kernel(u64 *__restrict__ data,
+                     const ModConst *__restrict__ mods,
+                     const ModFp *__restrict__ modf,
+                     const u64 *__restrict__ tw,
+                     const double *__restrict__ twf,
+                     const u64 *__restrict__ ninv, LimbIds ids,
+                     u32 n_limbs, u32 logN) {
     constexpr int KINDS = KIND_NT & ALL_ROWS;
     constexpr bool NT = (KIND_NT & STREAMED) != 0;
     constexpr u32 RL = (KIND_NT & WIDE) != 0 ? WIDE_RL : 4;
