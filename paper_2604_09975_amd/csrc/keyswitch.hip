@@ -1476,8 +1476,8 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void passb_final_kernel(ItemPack
     auto load = [&](u32 idx) -> u64 { return __builtin_nontemporal_load(wrow + idx); };
     const ModFp mf = modf[i];
     // epilogue on pairs of adjacent residues (16-byte accesses to the streamed operands), two pairs at a time so
-    // that their loads are in flight together (RL < 4: all of them, during the transform).  Keys, w and the output are streamed once: non-temporal, so that
-    // they do not push the digit rows (re-read by every item of the batch) out of L2.
+    // that their loads are in flight together (RL < 4: all of them, during the transform).  Keys, w and the output are streamed
+    // once: non-temporal, so that they do not push the digit rows (re-read by every item of the batch) out of L2.
     const u32 tid = threadIdx.x, base = blockIdx.x << 12;
     constexpr u32 EPP = RL < 4 ? TL::R / 2 : EPI / 2;
     const bool fold = comp == 0 && it.c0;
