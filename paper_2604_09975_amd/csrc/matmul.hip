@@ -446,9 +446,15 @@ __global__ __launch_bounds__(MM_THREADS, 2) void diag_mac_kernel(const double *_
 //   whole limbs: 2^15 [8] 1433 / 1340 / 1341, [7] 1295 / 1248 / 1203, [6] 605 / 556 / 590, [5] 951 / 953 / 1015, [4] 768 / 708 / 715,
 //     [3] 625 / 614 / 569; 2^16 [3] 917 / 918 / 865, [2] 667 / 618 / 648; a small bank, 2^14 [6] 63.1 / 65.1 / 65.1, 2^13 [4] 10.8 /
 //     13.1 / 12.9.
-static u32 share_of(u32 store, u32 tiles, u32 N, u32 n_limbs, bool small_bank) {
+// Half records of short sums: from 24 steps on, or 12 without idle wavefronts.  A short sum has no loop to hide the first two steps'
+// way through LDS in.  us, own / four, steps [tiles] of 24 limbs at 2^16: 2 [6] 172 / 208, 4 214 / 241, 8 321 / 351, 10 377 / 430,
+// 14 488 / 524, 18 588 / 630, 22 702 / 744, 24 732 / 729, 26 795 / 803; 8 limbs at 2^16: 6 [3] 53 / 63, 10 [3] 80 / 89, 18 126 / 132, 24
+// 163 / 162, 2 [9] 88 / 104, 16 [9] 280 / 278; 24 limbs at 2^14: 2 [9] 66 / 80, 6 120 / 135, 16 [3] 74 / 74, 64 240 / 223; without
+// idle wavefronts, 12 limbs at 2^15 [8]: 10 138 / 140, 12 147 / 147, 14 171 / 167, 16 189 / 173, 20 229 / 214, 28 301 / 273.
+static u32 share_of(u32 store, u32 tiles, u32 steps, u32 N, u32 n_limbs, bool small_bank) {
     const u32 four = (tiles + 3) / 4 * 4, chunks = N / REC_CHUNK / (store == 1 ? 2 : 1);
     if ((store != 1 && (store != 2 || small_bank)) || tiles < 2 || (u64)(four / 4) * chunks * n_limbs < 256) return 1;
+    if (store == 1 && steps < (four == tiles ? 12u : 24u)) return 1;
     if (store == 2 && tiles % 2 == 0 && 5 * four > 6 * tiles) return 2;
     return 3 * four <= 4 * tiles ? 4 : 1;
 }
@@ -1392,7 +1398,7 @@ int ckks_ctpt_matmul(ckks_params_t *P, const ckks_weights_t *w, const uint64_t *
         else                                                                                                       \
             MM_LAUNCH(SYM, true, TB, RUNS, WPTR);                                                                  \
     } while (0)
-                const u32 share = share_of(w->block_packed[grp], tiles4, N, n_fp, few);
+                const u32 share = share_of(w->block_packed[grp], tiles4, q1 - q0, N, n_fp, few);
                 if (w->block_packed[grp] == 1 && share == 4)
                     MM_SHARED(true, 4, N / 256, w->d_wp);
                 else if (w->block_packed[grp] == 2 && share == 4)

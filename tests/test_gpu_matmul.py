@@ -491,7 +491,10 @@ def test_arena_of_a_projection(L, dnum, C, N1, G, B_out):
                                                             (16, 4, 2, 67, 5, 1, "g"),
                                                             # the border of the two kinds inside a record of four steps
                                                             (14, 5, 4, 4, 3, 1, "gr"), (14, 5, 4, 4, 7, 1, "rg"),
-                                                            (16, 4, 2, 72, 4, 1, "gr"), (16, 4, 2, 72, 6, 1, "gr")])
+                                                            (16, 4, 2, 72, 4, 1, "gr"), (16, 4, 2, 72, 6, 1, "gr"),
+                                                            # half records: 24 steps and more, or 12 where no wavefront is idle
+                                                            (14, 5, 4, 12, 6, 2, "r"), (14, 5, 4, 13, 5, 2, "r"), (14, 4, 4, 27, 7, 1, "r"),
+                                                            (14, 5, 4, 27, 7, 1, "rg"), (14, 5, 4, 6, 8, 2, "r"), (14, 5, 4, 15, 4, 1, "rg")])
 def test_wavefronts_that_share_the_bank(logN, level, C, G, B_out, N1, kinds):
     """Launches of 256 workgroups and more whose wavefronts share bank residues by four (three and seven tiles, the last ones short,
     steps behind the last whole record) and by two; kinds of the input groups, the first letter for all but the last of two, where
