@@ -102,7 +102,11 @@ __global__ __launch_bounds__(Tile<RL>::THREADS) void gather_intt_kernel(PtrPack 
 
 // (out0, out1, t2) = (a0 b0, a0 b1 + a1 b0, a1 b1), pointwise, and the inverse tile pass of t2, which the relinearisation
 // decomposes: t2 as it is and, half transformed, tmp.  As two kernels a product and rescale at 2^15 (12 + 4 primes) took 4.5 us
-// longer: a launch, and 64-bit Montgomery products where primes below 2^50 have cheaper ones.
+// longer: a launch, and 64-bit Montgomery products where primes below 2^50 have cheaper ones.  Where they have not, a workgroup is a
+// chain of those products and of the butterflies, and below 2^15 the launch costs less than that: a product on primes of 61 bits, one
+// kernel / two, 2^12, 2 limbs 50.5 / 49.7, 6 59.4 / 58.4, 2^13, 12 100.4 / 98.5, 2^14, 12 123.2 / 121.5 us, of 52 bits 47.5 / 46.9, 56.9 /
+// 55.8, 93.7 / 92.5, 117.5 / 116.6, of 58 as those; 2^15, 12 limbs of 61 / 58 / 52 bits 114.3 / 110.5 / 107.9 and 115.2 / 112.1 / 109.0,
+// 2^16, 24 of 52 234 and 237.  Of 50 bits: 2^12, 6 33.6 and 34.1, 2^14, 12 93.7 and 94.8, 2^15, 12 61.5 and 64.8.
 // grid: x = 4096-residue tiles, y = limb
 template <u32 RL>
 __global__ __launch_bounds__(Tile<RL>::THREADS) void tensor_intt_kernel(const u64 *__restrict__ a, const u64 *__restrict__ b,
@@ -2209,7 +2213,9 @@ int ckks_ctmul(ckks_params_t *P, const uint64_t *d_ct_a, const uint64_t *d_ct_b,
     int rc = P->ensure_scratch((dig_w + 2 * lim_w + switch_scratch_words(P, level, 1)) * sizeof(u64), stream);
     if (rc) return rc;
     u64 *d_digits = (u64 *)P->d_scratch, *d_tmp = d_digits + dig_w, *d_t2 = d_tmp + lim_w, *d_work = d_t2 + lim_w;
-    if (fast_ring(P)) {
+    bool one = fast_ring(P);                                 // see tensor_intt_kernel
+    for (u32 i = 0; i < level && P->logN < 15; ++i) one = one && (P->mod[i] >> 50) == 0;
+    if (one) {
         const LevelTables *lt = nullptr;
         rc = P->level_tables(level, &lt);
         if (rc) return rc;

@@ -44,7 +44,10 @@ def test_small_rings_generic_path(L, K, dnum, level, qbits, pbits):
 
 @pytest.mark.parametrize("logN,L,K,dnum,level,qbits,pbits", [(12, 4, 2, 2, 3, 50, 60), (12, 4, 4, 1, 4, 52, 60), (12, 3, 3, 1, 2, 61, 62),
                                                               (13, 4, 2, 2, 4, 50, 60), (14, 3, 2, 3, 3, 56, 61),
-                                                              (17, 18, 3, 6, 17, 50, 60)])     # 544 tiles
+                                                              (17, 18, 3, 6, 17, 50, 60),      # 544 tiles
+                                                              # primes from 2^50 up: in one kernel from 2^15 on
+                                                              (15, 4, 4, 1, 4, 52, 60), (15, 3, 2, 3, 3, 58, 61),
+                                                              (16, 4, 2, 2, 3, 61, 62), (17, 18, 3, 6, 17, 58, 60)])
 def test_tensor_product_within_the_first_transform_pass(logN, L, K, dnum, level, qbits, pbits):
     """Rows of either kind of prime, the ring whose tile is the whole transform, more tiles than go out wide; residues of q - 1
     among uniform ones, and a ciphertext times itself."""
